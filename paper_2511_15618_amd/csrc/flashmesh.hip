@@ -10,6 +10,7 @@
 #include <cstring>
 #include <mutex>
 #include <cstdlib>
+#include <functional>
 #include <string>
 #include <type_traits>
 #include <vector>
@@ -112,12 +113,34 @@ struct fm_ctx {
   float *spv_out, *spf_out, *hfv_out, *dh, *dkeep, *dtmp, *dlogits;
   float *dist_c, *dist_v, *dist_f;
   void *dxn, *dq, *datt, *dmid;
-  Replay replay;
+  StepParams params{};     // host copy of the settings below, StepParams on the device
+  StepParams* params_dev = nullptr;
   int *gen_tok, *gen_len;  // block buffers used by fm_generate
   int* gen_acc;
-  int* host_flag;          // pinned: [0] alive flag, [1..S] lagged copy of the committed lengths
-  std::vector<int> len_bound;   // host upper bound on each sequence's committed coordinate length
-  long commits = 0;             // fm_commit calls so far
+  unsigned* commits_dev = nullptr;   // number of the fm_generate call << 20 | its commits so far
+  unsigned generation = 0;           // fm_generate calls so far, 12 bits
+  Progress* prog = nullptr;          // pinned, written by k_commit
+  unsigned long long* host_counts = nullptr;   // pinned, written by k_finish
+  // Recorded launch sequences.  A decode step is several hundred launches whose arguments never change.  Enqueueing one costs the
+  // host 2.6 to 4 us, which bounds the step where the kernels are shorter than that; a graph costs it next to nothing, but
+  // 7 us of device time of its own.
+  struct GraphKey {
+    int what;              // G_*
+    int flags;             // launches that depend on a setting (sampling, correct stage, speculative)
+    const void* p[4];      // caller's buffers
+    bool operator==(const GraphKey& o) const { return what == o.what && flags == o.flags && !memcmp(p, o.p, sizeof p); }
+  };
+  struct Graph {
+    GraphKey key;
+    hipGraphExec_t exec = nullptr;
+    unsigned long used = 0;
+  };
+  std::vector<Graph> graphs;
+  unsigned long graph_clock = 0;
+  bool graphs_on = true;
+  hipStream_t rec_stream = nullptr;   // recording only, nothing runs on it
+  enum { E_BEGIN, E_END, E_P0, E_P1, E_P2, E_P3, E_COUNT };
+  hipEvent_t ev[E_COUNT] = {};
   bool sticky_error = false;    // a launch wrapper refused its arguments (message in err); reported by the entry point
   // persistent verify kernel (one sequence, block <= 32, half-precision path)
   bool persist;
@@ -125,7 +148,7 @@ struct fm_ctx {
   PkArgs pk;
   PrefillLayer* pf_layers = nullptr;   // per-block table of the tiled prefill GEMM (null: per-block launches)
   int pf_n = 0, pf_grid = 0;           // blocks in the table; workgroups of its launch (one per compute unit, multiple of 8)
-  unsigned pk_epoch;
+  unsigned* pk_epoch;      // device: passes so far
   size_t pk_lds;           // dynamic LDS of the persistent kernel (none at present)
   double weight_bytes;
 };
@@ -168,17 +191,81 @@ int dalloc_t(fm_ctx* c, void** p, size_t n) {  // n elements of the storage type
 }
 #define TRY(x) do { int rc_ = (x); if (rc_ != FM_OK) return rc_; } while (0)
 
+enum { G_DRAFT = 1, G_VERIFY, G_STEP };
+#define FM_GRAPHS 8      // recorded sequences a context keeps (least recently used goes first)
+
+void drop_graphs(fm_ctx* c) {
+  for (auto& g : c->graphs) if (g.exec) (void)hipGraphExecDestroy(g.exec);
+  c->graphs.clear();
+}
+
+void release(fm_ctx* c) {
+  drop_graphs(c);
+  if (c->rec_stream) (void)hipStreamDestroy(c->rec_stream);
+  for (hipEvent_t e : c->ev) if (e) (void)hipEventDestroy(e);
+  for (void* p : c->allocs) (void)hipFree(p);
+  if (c->prog) (void)hipHostFree(c->prog);
+  if (c->host_counts) (void)hipHostFree(c->host_counts);
+  delete c;
+}
+
+// Runs `enqueue` (launches on c->stream whose arguments follow from `key` alone) as a graph.  The first call with a key launches
+// directly unless `now`; the second records and replays, later ones replay.  A stream that the caller is recording takes
+// the launches themselves, and so does a context whose recording failed once.
+int run_graphed(fm_ctx* c, const fm_ctx::GraphKey& key, bool now, const std::function<int()>& enqueue) {
+  if (!c->graphs_on) return enqueue();
+  if (c->stream) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &cs) != hipSuccess) (void)hipGetLastError();
+    if (cs != hipStreamCaptureStatusNone) return enqueue();
+  }
+  fm_ctx::Graph* g = nullptr;
+  for (auto& x : c->graphs) if (x.key == key) g = &x;
+  const bool known = g != nullptr;
+  if (!g) {
+    if (c->graphs.size() >= FM_GRAPHS) {
+      size_t old = 0;
+      for (size_t i = 1; i < c->graphs.size(); i++) if (c->graphs[i].used < c->graphs[old].used) old = i;
+      // the stream may still be working on the launch of the one that goes
+      if (c->graphs[old].exec) { HIPCHK(c, hipStreamSynchronize(c->stream)); (void)hipGraphExecDestroy(c->graphs[old].exec); }
+      c->graphs[old] = fm_ctx::Graph{};
+      g = &c->graphs[old];
+    } else {
+      c->graphs.emplace_back();
+      g = &c->graphs.back();
+    }
+    g->key = key;
+  }
+  g->used = ++c->graph_clock;
+  if (!g->exec) {
+    if (!known && !now) return enqueue();
+    hipStream_t user = c->stream;
+    hipGraph_t graph = nullptr;
+    if (!c->rec_stream && hipStreamCreateWithFlags(&c->rec_stream, hipStreamNonBlocking) != hipSuccess) c->rec_stream = nullptr;
+    hipError_t e = c->rec_stream ? hipStreamBeginCapture(c->rec_stream, hipStreamCaptureModeThreadLocal) : hipErrorUnknown;
+    int rc = FM_OK;
+    if (e == hipSuccess) {
+      c->stream = c->rec_stream;
+      rc = enqueue();
+      c->stream = user;
+      e = hipStreamEndCapture(c->rec_stream, &graph);
+      if (rc == FM_OK && e == hipSuccess) e = hipGraphInstantiate(&g->exec, graph, nullptr, nullptr, 0);
+      if (graph) (void)hipGraphDestroy(graph);
+    }
+    if (rc != FM_OK) { g->exec = nullptr; return rc; }
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      g->exec = nullptr;
+      c->graphs_on = false;
+      return enqueue();
+    }
+  }
+  HIPCHK(c, hipGraphLaunch(g->exec, c->stream));
+  return FM_OK;
+}
+
 int level_cap(const fm_ctx* c, int level) { return level == 0 ? c->D.capc : level == 1 ? c->D.capv : c->D.capf; }
 int level_window(const fm_ctx* c, int level) { return level == 0 ? c->D.wc : level == 1 ? c->D.wv : c->D.wf; }
-// Upper bound on the keys any row of the next pass can see at `level`, from the host's bound on the committed
-// lengths (a commit adds at most block_max tokens; fm_read_state and the generate loop tighten it).
-int level_key_bound(const fm_ctx* c, int level) {
-  int b = 0;
-  for (int s = 0; s < c->D.S; s++) b = std::max(b, c->len_bound[s]);
-  const long keys = (long)b + c->D.Bm;                  // positions P .. P + block_max - 1 are in the pass
-  const long k = level == 0 ? keys : level == 1 ? (keys + 2) / 3 + 1 : (keys + 8) / 9 + 1;
-  return (int)std::min<long>(k, level_cap(c, level));
-}
 const int kStackLevel[5] = {0, 1, 2, 1, 0};
 
 // ------------------------------------------------------------------------------------------
@@ -199,9 +286,8 @@ void gemm(fm_ctx* c, int epi, const void* X, long ldx, long gsx, const void* W, 
 
 template <typename T>
 void attention(fm_ctx* c, const void* q, const int* limit, int rows, int RPS, const void* Kc, const void* Vc,
-               long seq_stride, int cap, void* out, const int* flag, bool dense = false, int key_bound = 1 << 30,
-               int window = 0) {
-  if (mfma_attn_launch<T>(c->mres, q, limit, rows, RPS, Kc, Vc, seq_stride, cap, out, c->D.H, flag, dense, key_bound, window, c->stream, c->D.hd)) return;
+               long seq_stride, int cap, void* out, const int* flag, bool dense = false, int window = 0) {
+  if (mfma_attn_launch<T>(c->mres, q, limit, rows, RPS, Kc, Vc, seq_stride, cap, out, c->D.H, flag, dense, window, c->stream, c->D.hd)) return;
   // the plain kernel reads row-major caches: only the fp32 path has those
   if (!std::is_same<T, float>::value) { fail(c, FM_EINVAL, "attention: unsupported row set (%d rows, %d per sequence)", rows, RPS); c->sticky_error = true; return; }
 #define FM_ATTN(HDV) hipLaunchKernelGGL((k_attn_simple<T, HDV>), dim3(rows, c->D.H), dim3(256), 0, c->stream, (const T*)q, limit, RPS, \
@@ -276,7 +362,7 @@ void run_block(fm_ctx* c, const Layer& L, int level) {
     rope_append<T>(c, c->qkv, (long)3 * d, c->cs[level], c->pos[level], rows, RPS, c->qT, L.Kc, L.Vc, cap, flag);
   }
   attention<T>(c, c->qT, c->pos[level], rows, RPS, L.Kc, L.Vc, (long)cache_seq_elems(c, cap), cap, c->attT, flag, false,
-               level_key_bound(c, level), level_window(c, level));
+               level_window(c, level));
   gemm<T>(c, EPI_F32, c->attT, d, 0, L.wo, 0, h, d, 0, h, d, 0, rows, d, d, 1, flag);
   gemm_norm<T>(c, EPI_T, h, L.g2, L.cq, c->qT, d, rows, d, flag);
   attention<T>(c, c->qT, c->limx[level], rows, RPS, L.Km, L.Vm, (long)cache_seq_elems(c, D.M), D.M, c->attT, flag, true);
@@ -310,7 +396,7 @@ const unsigned* pass_failed(const fm_ctx* c) { return c->persist ? c->pk.abort_w
 // then the accepted length per sequence
 void choose_and_accept(fm_ctx* c, const float* logits, int32_t* accepted) {
   const Dims& D = c->D;
-  if (c->smp.temperature > 0.f) {
+  if (c->params.temperature > 0.f) {
     hipLaunchKernelGGL(k_sample_rows, dim3(c->Rc), dim3(256), 0, c->stream, c->st, D, logits, c->smp);
     hipLaunchKernelGGL(k_accept, dim3(1), dim3(64), 0, c->stream, c->st, D, accepted, (const int*)c->smp.accflag, pass_failed(c));
   } else {
@@ -324,12 +410,11 @@ int verify_impl(fm_ctx* c, const int32_t* block_tok, const int32_t* block_len, f
   const Dims& D = c->D;
   const int d = D.d;
   hipLaunchKernelGGL(k_verify_setup, dim3(std::min(16, (D.S * D.Bm * (D.hd / 2) + 255) / 256)), dim3(256), 0, c->stream, c->st, D, c->inv, block_tok, block_len,
-                     c->pos[0], c->pos[1], c->pos[2], c->limx[0], c->limx[1], c->limx[2], c->cs[0], c->cs[1], c->cs[2]);
+                     c->pos[0], c->pos[1], c->pos[2], c->limx[0], c->limx[1], c->limx[2], c->cs[0], c->cs[1], c->cs[2], c->persist ? c->pk_epoch : nullptr);
   if (c->persist) {
     // the whole backbone forward in one launch (see fm_kernels_persist.h), then greedy choice and acceptance
     float* lgp = logits_out ? logits_out : c->logits;
     c->pk.logits = lgp;
-    c->pk.epoch = ++c->pk_epoch;
     if (c->pk.RS == 32) hipLaunchKernelGGL(k_verify_persist<2>, dim3(PK_NWG), dim3(256), c->pk_lds, c->stream, c->pk);
     else hipLaunchKernelGGL(k_verify_persist<1>, dim3(PK_NWG), dim3(256), c->pk_lds, c->stream, c->pk);
     choose_and_accept(c, lgp, accepted);
@@ -380,7 +465,7 @@ void run_sp(fm_ctx* c, int set, const SpLevel& sp, const Layer& last, int level,
   gemm<T>(c, EPI_F32, c->dxn, (long)G * d, d, sp.wq, dd, c->dtmp, (long)G * d, d, nullptr, 0, 0, D.S, d, d, G, flag);
   rope_append<T>(c, c->dtmp, (long)d, c->dr.cs[set], c->dr.pos[set], rows, G, c->dq, nullptr, nullptr, cap, flag);
   attention<T>(c, c->dq, c->dr.lim[set], rows, G, last.Kc, last.Vc, (long)cache_seq_elems(c, cap), cap, c->datt, flag, false,
-               level_key_bound(c, level), level_window(c, level));
+               level_window(c, level));
   gemm<T>(c, EPI_T, c->datt, (long)G * d, d, sp.wo, dd, c->dxn, (long)G * d, d, nullptr, 0, 0, D.S, d, d, G, flag);
   gemm<T>(c, EPI_T, c->dxn, (long)G * d, d, sp.cq, dd, c->dq, (long)G * d, d, nullptr, 0, 0, D.S, d, d, G, flag);
   attention<T>(c, c->dq, c->dr.limx[set], rows, G, last.Km, last.Vm, (long)cache_seq_elems(c, D.M), D.M, c->datt, flag, true);
@@ -409,8 +494,7 @@ void run_sp_all(fm_ctx* c, const int* flag) {
   for (int z = 0; z < 3; z++) {
     const int cap = level_cap(c, lev[z]);
     lv[z] = AttnLevelHost{(const f16_t*)c->dq + off * d, c->dr.lim[set[z]], nrow[z], last[z]->Kc, last[z]->Vc,
-                          (long)cache_seq_elems(c, cap), cap, (f16_t*)c->datt + off * d, false, level_key_bound(c, lev[z]),
-                          level_window(c, lev[z])};
+                          (long)cache_seq_elems(c, cap), cap, (f16_t*)c->datt + off * d, false, level_window(c, lev[z])};
     off += nrow[z];
   }
   if (!mfma_attn_launch_levels(c->mres, lv, S, G, D.H, flag, c->stream)) { fail(c, FM_EINVAL, "merged SP attention: unsupported row sets"); c->sticky_error = true; return; }
@@ -419,7 +503,7 @@ void run_sp_all(fm_ctx* c, const int* flag) {
   off = 0;
   for (int z = 0; z < 3; z++) {
     lv[z] = AttnLevelHost{(const f16_t*)c->dq + off * d, c->dr.limx[set[z]], nrow[z], last[z]->Km, last[z]->Vm,
-                          (long)cache_seq_elems(c, D.M), D.M, (f16_t*)c->datt + off * d, true, 1 << 30, 0};
+                          (long)cache_seq_elems(c, D.M), D.M, (f16_t*)c->datt + off * d, true, 0};
     off += nrow[z];
   }
   if (!mfma_attn_launch_levels(c->mres, lv, S, G, D.H, flag, c->stream)) { fail(c, FM_EINVAL, "merged SP cross-attention: unsupported row sets"); c->sticky_error = true; return; }
@@ -444,7 +528,7 @@ void run_hf(fm_ctx* c, int set, const HfLevel& hf, int mult, const Layer& last, 
   gemm<T>(c, EPI_F32, c->dxn, ld, d, hf.wq, dd, c->dtmp, ld, d, nullptr, 0, 0, Mg, d, d, G, flag);
   rope_append<T>(c, c->dtmp, (long)d, c->dr.cs[set], c->dr.pos[set], rows, per_seq, c->dq, nullptr, nullptr, cap, flag);
   attention<T>(c, c->dq, c->dr.lim[set], rows, per_seq, last.Kc, last.Vc, (long)cache_seq_elems(c, cap), cap, c->datt, flag, false,
-               level_key_bound(c, level), level_window(c, level));
+               level_window(c, level));
   gemm<T>(c, EPI_GELU_T, c->datt, ld, d, hf.w1, dh, c->dmid, (long)G * c->hff, c->hff, nullptr, 0, 0, Mg, c->hff, d, G, flag);
   gemm<T>(c, EPI_F32, c->dmid, (long)G * c->hff, c->hff, hf.w2, dh, out, ld, d, c->dkeep, ld, d, Mg, d, c->hff, G, flag);
 }
@@ -483,7 +567,28 @@ int draft_impl(fm_ctx* c, int32_t* block_tok, int32_t* block_len, int speculativ
     }
   }
   hipLaunchKernelGGL(k_merge, dim3(D.S), dim3(1024), 0, c->stream, c->st, D, c->dr, c->dist_c, c->dist_v, c->dist_f,
-                     c->replay, speculative, block_tok, block_len, c->smp);
+                     speculative, block_tok, block_len, c->smp);
+  HIPCHK(c, hipGetLastError());
+  return FM_OK;
+}
+
+int draft_any(fm_ctx* c, int32_t* block_tok, int32_t* block_len, int speculative) {
+  return c->bf16 ? draft_impl<f16_t>(c, block_tok, block_len, speculative) : draft_impl<float>(c, block_tok, block_len, speculative);
+}
+int verify_any(fm_ctx* c, const int32_t* block_tok, const int32_t* block_len, float* logits, int32_t* accepted) {
+  return c->bf16 ? verify_impl<f16_t>(c, block_tok, block_len, logits, accepted) : verify_impl<float>(c, block_tok, block_len, logits, accepted);
+}
+// settings that decide which launches a step consists of
+int step_flags(const fm_ctx* c, int speculative) {
+  return (speculative ? 1 : 0) | (c->params.temperature > 0.f ? 2 : 0) | (c->correct_hist << 2);
+}
+int commit_any(fm_ctx* c, const int32_t* accepted, bool report) {
+  hipLaunchKernelGGL(k_commit, dim3(1), dim3(64), 0, c->stream, c->st, c->D, accepted, pass_failed(c), c->commits_dev, report ? c->prog : nullptr);
+  HIPCHK(c, hipGetLastError());
+  return FM_OK;
+}
+int put_params(fm_ctx* c) {
+  hipLaunchKernelGGL(k_set_params, dim3(1), dim3(64), 0, c->stream, c->params_dev, c->params);
   HIPCHK(c, hipGetLastError());
   return FM_OK;
 }
@@ -549,10 +654,11 @@ int check_persist(fm_ctx* c) {
   const unsigned rearm[9] = {0u, 0xFFFFFFFFu, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
   HIPCHK(c, hipMemcpy(c->pk.abort_word, rearm, sizeof rearm, hipMemcpyHostToDevice));
   c->persist = false;
+  drop_graphs(c);
   c->persist_failures++;
   return fail(c, FM_EHIP, "persistent verify kernel timed out: earliest stuck stage %u; first missing element: stage %u "
-              "workgroup %u thread %u index %u expected tag %u saw %u (epoch %u); passes since then accepted nothing, the "
-              "context continues with one launch per operator", w[1], w[5], w[6], w[7], w[8], w[3], w[4], c->pk_epoch);
+              "workgroup %u thread %u index %u expected tag %u saw %u; passes since then accepted nothing, the "
+              "context continues with one launch per operator", w[1], w[5], w[6], w[7], w[8], w[3], w[4]);
 }
 
 // Build the parameter tables and the list of (blob range -> device destination) in manifest order.
@@ -725,7 +831,8 @@ int build_persist(fm_ctx* c) {
     if (e[0] == '1') TRY(dalloc(c, &a.prof, 1024));
     if (const char* ps = getenv("FM_PROFILE_STAGE")) a.prof_stage = atoi(ps); else a.prof_stage = -1;
   }
-  c->pk_epoch = 0;
+  TRY(dalloc(c, &c->pk_epoch, 1));
+  a.epoch_word = c->pk_epoch;
   // test hooks for the bounded waits: a shorter bound, and an embedding that publishes under the wrong tag
   a.timeout_ticks = PK_TIMEOUT_TICKS;
   a.test_skew = 0;
@@ -837,7 +944,8 @@ int build_buffers(fm_ctx* c) {
   TRY(dalloc(c, &c->dist_c, S * std::max(D.Dc, 1) * D.V));
   TRY(dalloc(c, &c->dist_v, S * std::max(D.nhfc, 1) * D.V)); TRY(dalloc(c, &c->dist_f, S * std::max(D.nhfc, 1) * D.V));
   TRY(dalloc(c, &c->lab_v, S * std::max(D.nspv, 1) * 3)); TRY(dalloc(c, &c->lab_f, S * std::max(D.nhfv, 1) * 3));
-  c->smp = Sampling{0.f, 0ull, nullptr, nullptr, nullptr, nullptr, 0};
+  TRY(dalloc(c, &c->params_dev, 1)); TRY(dalloc(c, &c->commits_dev, 1));
+  c->smp = Sampling{c->params_dev, nullptr, nullptr, nullptr, nullptr};
   TRY(dalloc(c, &c->smp.qrow, S * D.Bm * D.V)); TRY(dalloc(c, &c->smp.qsum, S * D.Bm));
   TRY(dalloc(c, &c->smp.qtok, S * D.Bm)); TRY(dalloc(c, &c->smp.accflag, S * D.Bm));
   c->db = DraftBufs{c->tap_c, c->tap_v, c->tap_f, c->ring_yf, c->spv_out, c->spf_out, c->hfv_out, spv_rs, spf_rs};
@@ -875,7 +983,14 @@ int build_buffers(fm_ctx* c) {
       c->pf_grid = std::max(8, prop.multiProcessorCount / 8 * 8);
     }
   }
-  if (hipHostMalloc((void**)&c->host_flag, 64 + sizeof(int) * (size_t)c->D.S) != hipSuccess) return fail(c, FM_ENOMEM, "hipHostMalloc failed");
+  if (hipHostMalloc((void**)&c->prog, sizeof(Progress)) != hipSuccess || hipHostMalloc((void**)&c->host_counts, 99 * sizeof(unsigned long long)) != hipSuccess)
+    return fail(c, FM_ENOMEM, "hipHostMalloc failed");
+  memset(c->prog, 0, sizeof(Progress));
+  for (int i = 0; i < fm_ctx::E_COUNT; i++) HIPCHK(c, hipEventCreate(&c->ev[i]));
+  // fp32 launches are shorter than the host needs to enqueue one; the half path's are longer, and there a graph only adds its own
+  // 7 us (step of the medium model, one sequence: 2055 us as launches, 2071 us as two graphs).
+  const char* ge = getenv("FM_GRAPH");          // "0" / "1": never / always (measurement switch)
+  c->graphs_on = ge ? ge[0] != '0' : !c->bf16;
   return FM_OK;
 }
 
@@ -939,9 +1054,6 @@ int fm_create(const fm_config* cfg, void* hip_stream, fm_ctx** out) {
   for (int i = 0; i < 64; i++) c->inv.v[i] = std::pow((double)g.rope_base, -(double)i / (hd / 2.0));
   c->weights_loaded = false;
   c->prefilled.assign(D.S, false);
-  c->len_bound.assign(D.S, D.maxtok);
-  c->replay = Replay{nullptr, 0, 0, 0.f, 0ull};
-  c->host_flag = nullptr;
   {
     const int nl = g.l_cpre + g.l_cpost + g.l_vpre + g.l_vpost + g.l_face;
     const char* env = getenv("FM_PERSIST");
@@ -974,9 +1086,7 @@ int fm_create(const fm_config* cfg, void* hip_stream, fm_ctx** out) {
   }
   if (rc != FM_OK) {
     fprintf(stderr, "fm_create: %s\n", c->err.c_str());
-    for (void* p : c->allocs) (void)hipFree(p);
-    if (c->host_flag) (void)hipHostFree(c->host_flag);
-    delete c;
+    release(c);
     return rc;
   }
   // algorithmic weight bytes of one verify pass
@@ -990,9 +1100,7 @@ int fm_create(const fm_config* cfg, void* hip_stream, fm_ctx** out) {
 int fm_destroy(fm_ctx* c) {
   if (!c) return FM_EINVAL;
   (void)hipStreamSynchronize(c->stream);
-  for (void* p : c->allocs) (void)hipFree(p);
-  if (c->host_flag) (void)hipHostFree(c->host_flag);
-  delete c;
+  release(c);
   return FM_OK;
 }
 
@@ -1037,7 +1145,7 @@ int fm_prefill_condition(fm_ctx* c, int32_t seq, const float* mem_dev) {
   if (seq < 0 || seq >= c->D.S) return fail(c, FM_EINVAL, "sequence %d out of range [0,%d)", seq, c->D.S);
   if (!mem_dev) return fail(c, FM_EINVAL, "null condition memory");
   int rc = c->bf16 ? prefill_impl<f16_t>(c, seq, mem_dev, c->stage) : prefill_impl<float>(c, seq, mem_dev, c->stage);
-  if (rc == FM_OK) { c->prefilled[seq] = true; c->len_bound[seq] = 0; }
+  if (rc == FM_OK) c->prefilled[seq] = true;
   return rc;
 }
 
@@ -1052,7 +1160,7 @@ int fm_prefill_condition_static(fm_ctx* c, int32_t seq, const float* mem_dev) {
     return fail(c, FM_EINVAL, "condition memory of %d x %d needs %zu staging bytes, the static area holds %u: use fm_prefill_condition",
                 c->D.M, c->D.d, need, (unsigned)FM_STATIC_SCRATCH_BYTES);
   int rc = c->bf16 ? prefill_impl<f16_t>(c, seq, mem_dev, c->static_scratch) : prefill_impl<float>(c, seq, mem_dev, c->static_scratch);
-  if (rc == FM_OK) { c->prefilled[seq] = true; c->len_bound[seq] = 0; }
+  if (rc == FM_OK) c->prefilled[seq] = true;
   return rc;
 }
 
@@ -1060,16 +1168,17 @@ int fm_draft(fm_ctx* c, int32_t* block_tok, int32_t* block_len) {
   if (!c) return FM_EINVAL;
   if (!c->weights_loaded) return fail(c, FM_ESTATE, "weights not loaded");
   if (!block_tok || !block_len) return fail(c, FM_EINVAL, "null block buffer");
-  const int rc = c->bf16 ? draft_impl<f16_t>(c, block_tok, block_len, 1) : draft_impl<float>(c, block_tok, block_len, 1);
+  const int rc = run_graphed(c, fm_ctx::GraphKey{G_DRAFT, step_flags(c, 1), {block_tok, block_len, nullptr, nullptr}}, false,
+                             [&] { return draft_any(c, block_tok, block_len, 1); });
   return rc == FM_OK && c->sticky_error ? FM_EINVAL : rc;
 }
 
 int fm_set_sampling(fm_ctx* c, float temperature, uint64_t seed) {
   if (!c) return FM_EINVAL;
   if (!(temperature >= 0.f) || temperature > 1e4f) return fail(c, FM_EINVAL, "temperature %g outside [0, 1e4]", (double)temperature);
-  c->smp.temperature = temperature;
-  c->smp.seed = seed;
-  return FM_OK;
+  c->params.temperature = temperature;
+  c->params.seed = seed;
+  return put_params(c);
 }
 
 int fm_set_correct(fm_ctx* c, int32_t hist_vertices) {
@@ -1094,25 +1203,21 @@ int fm_verify_block(fm_ctx* c, const int32_t* block_tok, const int32_t* block_le
   if (!c) return FM_EINVAL;
   if (!c->weights_loaded) return fail(c, FM_ESTATE, "weights not loaded");
   if (!block_tok || !block_len || !accepted) return fail(c, FM_EINVAL, "null block / accepted buffer");
-  const int rc = c->bf16 ? verify_impl<f16_t>(c, block_tok, block_len, logits, accepted)
-                         : verify_impl<float>(c, block_tok, block_len, logits, accepted);
+  const int rc = run_graphed(c, fm_ctx::GraphKey{G_VERIFY, step_flags(c, 1), {block_tok, block_len, logits, accepted}}, false,
+                             [&] { return verify_any(c, block_tok, block_len, logits, accepted); });
   return rc == FM_OK && c->sticky_error ? FM_EINVAL : rc;
 }
 
 int fm_commit(fm_ctx* c, const int32_t* accepted) {
   if (!c) return FM_EINVAL;
   if (!accepted) return fail(c, FM_EINVAL, "null accepted buffer");
-  hipLaunchKernelGGL(k_commit, dim3(1), dim3(64), 0, c->stream, c->st, c->D, accepted, pass_failed(c));
-  HIPCHK(c, hipGetLastError());
-  for (int s = 0; s < c->D.S; s++) c->len_bound[s] = std::min(c->len_bound[s] + c->D.Bm, c->D.maxtok);
-  c->commits++;
-  return FM_OK;
+  return commit_any(c, accepted, false);
 }
 
 int fm_set_budget(fm_ctx* c, int32_t max_faces) {
   if (!c) return FM_EINVAL;
   if (max_faces < 1 || 9 * max_faces > c->D.maxtok) return fail(c, FM_EINVAL, "max_faces %d outside [1,%d]", max_faces, c->D.maxtok / 9);
-  hipLaunchKernelGGL(k_set_budget, dim3(1), dim3(64), 0, c->stream, c->st, c->D, 9 * max_faces);
+  hipLaunchKernelGGL(k_set_budget, dim3(1), dim3(64), 0, c->stream, c->st, c->D, 9 * max_faces, 0u, c->commits_dev);
   HIPCHK(c, hipGetLastError());
   return FM_OK;
 }
@@ -1121,8 +1226,8 @@ int fm_set_draft_replay(fm_ctx* c, const int32_t* stream_dev, int32_t stride, in
   if (!c) return FM_EINVAL;
   if (stream_dev && (stride < n_valid || n_valid < 0 || !(keep_prob >= 0.f && keep_prob <= 1.f)))
     return fail(c, FM_EINVAL, "bad replay arguments");
-  c->replay = Replay{stream_dev, stride, n_valid, keep_prob, (unsigned long long)seed};
-  return FM_OK;
+  c->params.replay = Replay{stream_dev, stride, n_valid, keep_prob, (unsigned long long)seed};
+  return put_params(c);
 }
 
 int fm_read_state(fm_ctx* c, int32_t* host_out) {
@@ -1135,7 +1240,6 @@ int fm_read_state(fm_ctx* c, int32_t* host_out) {
   HIPCHK(c, hipMemcpy(fin.data(), c->st.fin, S * 4, hipMemcpyDeviceToHost));
   TRY(check_persist(c));
   for (int s = 0; s < S; s++) {
-    c->len_bound[s] = P[s];
     host_out[s * 6 + 0] = P[s];
     host_out[s * 6 + 1] = (P[s] + 2) / 3;
     host_out[s * 6 + 2] = (P[s] + 8) / 9;
@@ -1160,7 +1264,7 @@ int fm_debug_profile(fm_ctx* c, uint64_t* host_out, int32_t n) {
 int fm_debug_draft(fm_ctx* c, int32_t which, float* host_out) {
   if (!c) return FM_EINVAL;
   const Dims& D = c->D;
-  if (which == -1 || which == -2) { c->smp.keep_rows = which == -1 ? 1 : 0; return FM_OK; }
+  if (which == -1 || which == -2) { c->params.keep_rows = which == -1 ? 1 : 0; return put_params(c); }
   if (!host_out) return fail(c, FM_EINVAL, "null output");
   const float* src = which == 0 ? c->smp.qrow : which == 1 ? c->lab_v : which == 2 ? c->lab_f : nullptr;
   if (!src) return fail(c, FM_EINVAL, "draft buffer %d out of range", which);
@@ -1366,100 +1470,125 @@ int fm_generate(fm_ctx* c, int32_t max_faces, int32_t speculative, int32_t* out_
   if (!out_tok || !out_len) return fail(c, FM_EINVAL, "null output buffer");
   for (int s = 0; s < c->D.S; s++)
     if (!c->prefilled[s]) return fail(c, FM_ESTATE, "sequence %d has no condition memory", s);
-  TRY(fm_set_budget(c, max_faces));
+  if (max_faces < 1 || 9 * max_faces > c->D.maxtok) return fail(c, FM_EINVAL, "max_faces %d outside [1,%d]", max_faces, c->D.maxtok / 9);
   const Dims& D = c->D;
-  // events: whole loop, lagged flag copy, and the four phase marks of a sampled step; destroyed on every way out
-  enum { E_BEGIN, E_END, E_FLAG, E_P0, E_P1, E_P2, E_P3, E_COUNT };
-  struct Events {
-    hipEvent_t e[E_COUNT] = {};
-    ~Events() { for (hipEvent_t x : e) if (x) (void)hipEventDestroy(x); }
-  } ev;
-  for (int i = 0; i < E_COUNT; i++) HIPCHK(c, hipEventCreate(&ev.e[i]));
-  HIPCHK(c, hipMemsetAsync(c->st.acc_hist, 0, 3 * 32 * sizeof(unsigned long long), c->stream));
-  HIPCHK(c, hipMemsetAsync(c->st.counters, 0, 3 * sizeof(unsigned long long), c->stream));
-  HIPCHK(c, hipEventRecord(ev.e[E_BEGIN], c->stream));
+  c->generation = c->generation % 0xFFFu + 1;
+  hipLaunchKernelGGL(k_set_budget, dim3(1), dim3(64), 0, c->stream, c->st, D, 9 * max_faces, c->generation, c->commits_dev);
+  HIPCHK(c, hipGetLastError());
+  HIPCHK(c, hipEventRecord(c->ev[fm_ctx::E_BEGIN], c->stream));
+  const int flags = step_flags(c, speculative);
+  const int per_step = speculative ? D.Bm : 1;         // most tokens a step can commit
+  auto draft = [&]() -> int {
+    TRY(draft_any(c, c->gen_tok, c->gen_len, speculative));
+    return speculative && c->correct_hist > 0 ? fm_correct(c, c->gen_tok, c->gen_len, nullptr) : FM_OK;
+  };
+  auto verify = [&]() -> int { return verify_any(c, c->gen_tok, c->gen_len, nullptr, c->gen_acc); };
+  auto whole = [&]() -> int { TRY(draft()); TRY(verify()); return commit_any(c, c->gen_acc, true); };
+  const fm_ctx::GraphKey kd{G_DRAFT, flags, {c->gen_tok, c->gen_len, c->gen_acc, c}}, kv{G_VERIFY, flags, {c->gen_tok, c->gen_len, nullptr, c->gen_acc}},
+      ks{G_STEP, flags, {c->gen_tok, c->gen_len, nullptr, c->gen_acc}};
+  const int sample_every = 32;
   const long max_steps = 9L * max_faces + 1 + 128;     // + the steps a failed pass of the single-launch kernel may void
-  const int check_every = 32;
-  bool pending = false, done = false, phase_pending = false;
-  long commits_at_copy = 0, phase_samples = 0;
+  bool phase_pending = false;
+  long phase_samples = 0;
   double ms_phase[3] = {0.0, 0.0, 0.0};
   auto take_phases = [&]() -> int {
     float a = 0.f, b = 0.f, d = 0.f;
-    HIPCHK(c, hipEventElapsedTime(&a, ev.e[E_P0], ev.e[E_P1]));
-    HIPCHK(c, hipEventElapsedTime(&b, ev.e[E_P1], ev.e[E_P2]));
-    HIPCHK(c, hipEventElapsedTime(&d, ev.e[E_P2], ev.e[E_P3]));
+    HIPCHK(c, hipEventElapsedTime(&a, c->ev[fm_ctx::E_P0], c->ev[fm_ctx::E_P1]));
+    HIPCHK(c, hipEventElapsedTime(&b, c->ev[fm_ctx::E_P1], c->ev[fm_ctx::E_P2]));
+    HIPCHK(c, hipEventElapsedTime(&d, c->ev[fm_ctx::E_P2], c->ev[fm_ctx::E_P3]));
     ms_phase[0] += a; ms_phase[1] += b; ms_phase[2] += d;
     phase_samples++;
     phase_pending = false;
     return FM_OK;
   };
-  int rc = FM_OK;
-  for (long step = 0; step < max_steps && !done && rc == FM_OK; step++) {
-    // one step per interval carries the phase marks, once the marks of the previous sample have been read
-    bool sample = step % check_every == 1;
-    if (sample && phase_pending) {
-      if (hipEventQuery(ev.e[E_P3]) == hipSuccess) TRY(take_phases());
-      else { (void)hipGetLastError(); sample = false; }
+  // what the device has reported: steps committed by every sequence, and per sequence its length then (-1 = finished)
+  long done = 0;
+  bool alive = true, failed = false;
+  int len[64];
+  auto look = [&]() {
+    unsigned least = 0xFFFFFu;
+    alive = failed = false;
+    for (int s = 0; s < D.S; s++) {
+      const unsigned long long w = __atomic_load_n(&c->prog->seq[s], __ATOMIC_RELAXED);
+      const unsigned gen = (unsigned)(w >> 52), v = (unsigned)w;
+      const unsigned ahead = gen == c->generation ? ((unsigned)(w >> 32) - (unsigned)done) & 0xFFFFFu : 0u;    // commits since `done`
+      least = std::min(least, ahead);
+      len[s] = gen != c->generation ? 0 : v == 1 ? -1 : (int)v - 2;
+      if (done + ahead > 0 && v == 0) failed = true;
+      if (done + ahead == 0 || len[s] != -1) alive = true;
     }
-    if (sample) HIPCHK(c, hipEventRecord(ev.e[E_P0], c->stream));
-    rc = c->bf16 ? draft_impl<f16_t>(c, c->gen_tok, c->gen_len, speculative) : draft_impl<float>(c, c->gen_tok, c->gen_len, speculative);
-    if (rc == FM_OK && speculative && c->correct_hist > 0) rc = fm_correct(c, c->gen_tok, c->gen_len, nullptr);
-    if (rc == FM_OK && sample) HIPCHK(c, hipEventRecord(ev.e[E_P1], c->stream));
-    if (rc == FM_OK)
-      rc = c->bf16 ? verify_impl<f16_t>(c, c->gen_tok, c->gen_len, nullptr, c->gen_acc)
-                   : verify_impl<float>(c, c->gen_tok, c->gen_len, nullptr, c->gen_acc);
-    if (rc == FM_OK && sample) HIPCHK(c, hipEventRecord(ev.e[E_P2], c->stream));
-    if (rc == FM_OK) rc = fm_commit(c, c->gen_acc);
-    if (rc == FM_OK && sample) { HIPCHK(c, hipEventRecord(ev.e[E_P3], c->stream)); phase_pending = true; }
-    if (rc == FM_OK && c->sticky_error) rc = FM_EINVAL;
-    if (rc != FM_OK) break;
-    if ((step + 1) % check_every == 0) {
-      // look at the flag copied one interval ago, then queue the next copy: the device never waits for the host
-      if (pending) {
-        HIPCHK(c, hipEventSynchronize(ev.e[E_FLAG]));
-        if (c->host_flag[0] == 0) done = true;
-        // the lengths of one interval ago bound today's: every commit since then added at most block_max
-        const long since = c->commits - commits_at_copy;
-        for (int s = 0; s < D.S; s++)
-          c->len_bound[s] = (int)std::min<long>(c->len_bound[s], c->host_flag[16 + s] + since * D.Bm);
-        if (c->host_flag[1] != 0) {
-          // the single-launch verify kernel gave up in some pass of the last interval: nothing was accepted or
-          // committed since, so the loop simply goes on with one launch per operator (message kept in fm_last_error)
-          HIPCHK(c, hipStreamSynchronize(c->stream));
-          (void)check_persist(c);
-          pending = false;
-          continue;
+    done += least;
+  };
+  int rc = FM_OK;
+  for (long step = 0; step < max_steps; step++) {
+    // The device must never wait for the host, and no step must run for nothing.  A further step is enqueued at once while it
+    // cannot be the one after the last: some sequence stays below its budget even if all that is enqueued is accepted whole (where
+    // EOS may be emitted: one step more than the device has finished).  Else only when the device has finished what it has.
+    for (unsigned spins = 1;; spins++) {
+      look();
+      const long ahead = step - done;              // steps enqueued and not yet committed
+      if (ahead == 0 || (done > 0 && (failed || !alive))) break;
+      if (!D.ban && ahead < 2) break;
+      if (D.ban && done > 0 && ahead < 6) {
+        bool sure = false;
+        for (int s = 0; s < D.S; s++) sure |= len[s] >= 0 && len[s] + per_step * ahead < 9L * max_faces;
+        if (sure) break;
+      }
+      if (spins % 4096 == 0) {
+        const hipError_t q = hipStreamQuery(c->stream);
+        if (q != hipSuccess && q != hipErrorNotReady) return fail(c, FM_EHIP, "decode loop: %s", hipGetErrorString(q));
+        (void)hipGetLastError();
+        if (q == hipSuccess) {
+          look();
+          if (step - done > 0) return fail(c, FM_EHIP, "decode loop: the stream is idle but %ld steps were not reported", step - done);
         }
       }
-      if (!done) {
-        HIPCHK(c, hipMemcpyAsync(c->host_flag, c->st.alive, sizeof(int), hipMemcpyDeviceToHost, c->stream));
-        if (c->persist)
-          HIPCHK(c, hipMemcpyAsync(c->host_flag + 1, c->pk.abort_word, sizeof(int), hipMemcpyDeviceToHost, c->stream));
-        else
-          c->host_flag[1] = 0;
-        HIPCHK(c, hipMemcpyAsync(c->host_flag + 16, c->st.P, sizeof(int) * (size_t)D.S, hipMemcpyDeviceToHost, c->stream));
-        commits_at_copy = c->commits;
-        HIPCHK(c, hipEventRecord(ev.e[E_FLAG], c->stream));
-        pending = true;
-      }
+#if defined(__x86_64__)
+      __builtin_ia32_pause();
+#endif
     }
+    if (done > 0 && failed) {
+      // the single-launch verify kernel gave up in some pass: nothing was accepted or committed since, so the loop
+      // simply goes on with one launch per operator (message kept in fm_last_error)
+      HIPCHK(c, hipStreamSynchronize(c->stream));
+      (void)check_persist(c);
+    } else if (done > 0 && !alive) {
+      break;
+    }
+    // one step per interval carries the phase marks, once the marks of the previous sample have been read
+    bool sample = step % sample_every == 1;
+    if (sample && phase_pending) {
+      if (hipEventQuery(c->ev[fm_ctx::E_P3]) == hipSuccess) TRY(take_phases());
+      else { (void)hipGetLastError(); sample = false; }
+    }
+    if (sample) {
+      HIPCHK(c, hipEventRecord(c->ev[fm_ctx::E_P0], c->stream));
+      rc = run_graphed(c, kd, true, draft);
+      if (rc == FM_OK) {
+        HIPCHK(c, hipEventRecord(c->ev[fm_ctx::E_P1], c->stream));
+        rc = run_graphed(c, kv, true, verify);
+      }
+      if (rc == FM_OK) {
+        HIPCHK(c, hipEventRecord(c->ev[fm_ctx::E_P2], c->stream));
+        rc = commit_any(c, c->gen_acc, true);
+      }
+      if (rc == FM_OK) { HIPCHK(c, hipEventRecord(c->ev[fm_ctx::E_P3], c->stream)); phase_pending = true; }
+    } else {
+      rc = run_graphed(c, ks, true, whole);
+    }
+    if (rc == FM_OK && c->sticky_error) rc = FM_EINVAL;
+    if (rc != FM_OK) return rc;
   }
-  if (rc != FM_OK) return rc;
-  HIPCHK(c, hipEventRecord(ev.e[E_END], c->stream));
-  // outputs: x_1 .. x_P per sequence
-  for (int s = 0; s < D.S; s++)
-    HIPCHK(c, hipMemcpyAsync(out_tok + (size_t)s * D.maxtok, c->st.hist + (size_t)s * (D.maxtok + 1) + 1, (size_t)D.maxtok * 4,
-                             hipMemcpyDeviceToDevice, c->stream));
-  HIPCHK(c, hipMemcpyAsync(out_len, c->st.P, (size_t)D.S * 4, hipMemcpyDeviceToDevice, c->stream));
+  HIPCHK(c, hipEventRecord(c->ev[fm_ctx::E_END], c->stream));
+  hipLaunchKernelGGL(k_finish, dim3(std::min(32, (D.maxtok + 255) / 256), D.S), dim3(256), 0, c->stream, c->st, D, out_tok, out_len, c->host_counts);
+  HIPCHK(c, hipGetLastError());
   HIPCHK(c, hipStreamSynchronize(c->stream));
-  TRY(check_persist(c));      // a failure in the very last interval: reported, the caller may call again
+  TRY(check_persist(c));      // a failure in the very last step: reported, the caller may call again
   if (phase_pending) TRY(take_phases());
   if (stats) {
-    unsigned long long cnt[3], hist[3 * 32];
-    HIPCHK(c, hipMemcpy(cnt, c->st.counters, sizeof cnt, hipMemcpyDeviceToHost));
-    HIPCHK(c, hipMemcpy(hist, c->st.acc_hist, sizeof hist, hipMemcpyDeviceToHost));
+    const unsigned long long *cnt = c->host_counts, *hist = c->host_counts + 3;
     float ms = 0.f;
-    HIPCHK(c, hipEventElapsedTime(&ms, ev.e[E_BEGIN], ev.e[E_END]));
+    HIPCHK(c, hipEventElapsedTime(&ms, c->ev[fm_ctx::E_BEGIN], c->ev[fm_ctx::E_END]));
     stats->steps = (int64_t)cnt[0];
     stats->tokens = (int64_t)cnt[1];
     for (int k = 0; k < 3; k++)

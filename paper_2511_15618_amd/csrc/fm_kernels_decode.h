@@ -1,0 +1,550 @@
+// Decode-path kernels of the half-precision contexts (gfx950, v_mfma_f32_16x16x32_f16): the skinny GEMM and the block
+// attention that every operator of a verify pass and of the draft heads is made of.
+//
+// A pass is a chain of several hundred dependent launches of 9 to ~100 rows each, so what bounds it is the length of one
+// launch, not a rate: a launch boundary in a replayed graph costs 1.7 to 2.9 us on this chip, one trip to memory about
+// 1 us.  The kernels here are therefore written for ONE trip to memory each: everything a workgroup will need (operand
+// fragments, row statistics, residual, positions) is requested before the first value is used.
+//
+// Activations between launches ("tiled" buffers) are halves in MFMA operand order, [row tile of 16][K/32][64 lanes][8],
+// like the weights: a fragment is one contiguous 1 KiB burst and goes from memory to the matrix core with no conversion.
+// RMSNorm never reads a row twice: whoever produces the fp32 residual stream also stores half(x * gain) of the norm
+// that comes next and, per 16 columns, the sum of squares of each row; the GEMM behind the norm adds those up and
+// applies 1/rms, a scalar per row, to its result tile.
+//
+// Operands are swapped with respect to Y = X W^T (the weight fragment is operand A): a lane of the result tile then
+// owns ONE row and four neighbouring columns, so that residual loads and all stores are vectors and the row scale is
+// one value per lane.
+#pragma once
+#include <type_traits>
+#include "fm_device.h"
+#include "fm_kernels_basic.h"
+#include "fm_kernels_mfma.h"
+
+typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+
+// element offset of (row m, column n) in a tiled buffer of KT = columns / 32
+__device__ __forceinline__ long tile_off(int m, int n, int KT) {
+  return ((long)(m >> 4) * KT + (n >> 5)) * 512 + ((m & 15) + 16 * ((n & 31) >> 3)) * 8 + (n & 7);
+}
+
+// Row r of a row set [sequence][row q of the sequence] -> (group, row of the group) of a grouped GEMM: `G` parameter
+// sets, `mult` rows of a sequence per set, sets numbered from `base`, `tiles` row tiles per group.
+struct RowMap {
+  int G, mult, base, tiles;
+};
+__device__ __forceinline__ long map_off(const RowMap& rm, int s, int q, int n, int KT) {
+  const int g = rm.G == 1 ? 0 : q % rm.G, k = rm.G == 1 ? q : q / rm.G;
+  return (long)(rm.base + g) * rm.tiles * KT * 512 + tile_off(s * rm.mult + k, n, KT);
+}
+
+// ------------------------------------------------------------------------------------------
+// GEMM
+// ------------------------------------------------------------------------------------------
+enum { DE_RES = 0, DE_GELU, DE_ROW, DE_TILE, DE_F32, DE_QKV, DE_ROPE };
+
+struct DecGemm {
+  const f16_t* A; long gsa;      // tiled activations, elements per group
+  const f16_t* W; long gsw;      // tiled weights, elements per group
+  int M, N, KT;                  // rows per group, columns, K / 32
+  const float* ssq;              // NORM: [row tile][K/16][16] sums of squares of 16 columns each
+  float inv_k, eps;
+  const int* run_flag;           // the launch is skipped when *run_flag == 0 (may be null)
+  // outputs (which of them: the epilogue)
+  void* Y; long ldy, gsy;        // row-major output: fp32 (DE_RES, DE_F32) or half (DE_ROW, DE_QKV q, DE_ROPE)
+  const float* R; long ldr, gsr; // fp32 rows added (DE_RES, DE_F32; may be null, may be Y)
+  f16_t* X; long gsx;            // tiled half output of width N (DE_GELU, DE_TILE; DE_RES: x * gain, may be null)
+  const float* gain;             // DE_RES: gain of the norm that follows
+  float* ssq_out;                // DE_RES: [row tile][N/16][16]
+  const int* pos;                // DE_RES with rings, DE_QKV: position of each row, -1 = inactive
+  int RPS;                       // rows per sequence
+  float *tap, *ring; int rs;     // DE_RES: rings (rs entries per sequence) that receive the old row (tap) and the new row
+  const float2* cs;              // DE_QKV, DE_ROPE: [row][hd/2] (cos, sin); DE_ROPE: row = m * ldc + group
+  int ldc, hd;
+  f16_t *Kc, *Vc; long seq_stride; int capb, H;   // DE_QKV: blocked caches
+};
+
+// MT row tiles x NC column tiles of 16 per workgroup, NW waves split K.
+// U fragments per wave and chunk: the first chunk (all of the K slice for the usual shapes) is in flight before
+// anything is waited for, later chunks one ahead.
+template <int MT, int NC, int NW, int U, bool LOOP, int EPI, bool NORM>
+__global__ __launch_bounds__(NW * 64) void k_dec_gemm(DecGemm a) {
+  constexpr int T = MT * NC;
+  extern __shared__ f32x4 dg_smem[];
+  f32x4* red = dg_smem;                                    // [NW][T][64]
+  float* sq = (float*)(dg_smem + NW * T * 64);             // [NW][MT][16]
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int g = lane >> 4, rl = lane & 15;
+  const int grp = blockIdx.z, mb = blockIdx.y, nt0 = blockIdx.x * NC;
+  const int rf = a.run_flag ? *a.run_flag : 1;
+  const int KT = a.KT, mt0 = mb * MT;
+  const int ntile = (a.M + 15) / 16;
+  const f16_t* Ap = a.A + (long)grp * a.gsa + lane * 8;
+  const f16_t* Wp = a.W + (long)grp * a.gsw + (long)nt0 * KT * 512 + lane * 8;
+  const int FW = (KT + NW - 1) / NW, kt0 = wave * FW, nk = min(FW, KT - kt0);
+  f32x4 acc[MT][NC];
+#pragma unroll
+  for (int mt = 0; mt < MT; mt++)
+#pragma unroll
+    for (int c = 0; c < NC; c++) acc[mt][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  f16x8 wc[NC][U], ac[MT][U];
+  auto load_chunk = [&](f16x8 (&w)[NC][U], f16x8 (&x)[MT][U], int i0) {
+#pragma unroll
+    for (int u = 0; u < U; u++)
+      if (i0 + u < nk) {
+        const long kt = kt0 + i0 + u;
+#pragma unroll
+        for (int c = 0; c < NC; c++) w[c][u] = *reinterpret_cast<const f16x8*>(Wp + ((long)c * KT + kt) * 512);
+#pragma unroll
+        for (int mt = 0; mt < MT; mt++) {
+          const int t = min(mt0 + mt, ntile - 1);          // a tile past the last one is computed on the last one's rows, never stored
+          x[mt][u] = *reinterpret_cast<const f16x8*>(Ap + ((long)t * KT + kt) * 512);
+        }
+      }
+  };
+  load_chunk(wc, ac, 0);
+  // operands of the epilogue of this wave's first result tile
+  const int tm = wave / NC, tc = wave % NC;
+  const int em = (mt0 + tm) * 16 + rl, en = (nt0 + tc) * 16 + g * 4;
+  const bool eon = wave < T && em < a.M;
+  f32x4 rv = f32x4{0.f, 0.f, 0.f, 0.f}, gv = rv, c0 = rv, c1 = rv;
+  int ep = -1;
+  if (eon) {
+    if ((EPI == DE_RES || EPI == DE_F32) && a.R && (EPI == DE_RES || a.N % 16 == 0))
+      rv = *reinterpret_cast<const f32x4*>(a.R + (long)grp * a.gsr + (long)em * a.ldr + en);
+    if (EPI == DE_RES) {
+      if (a.gain) gv = *reinterpret_cast<const f32x4*>(a.gain + en);
+      if (a.pos) ep = a.pos[em];
+    }
+    if (EPI == DE_QKV || EPI == DE_ROPE) {
+      if (EPI == DE_QKV) ep = a.pos[em];
+      const int part = EPI == DE_QKV ? ((nt0 + tc) * 16) / (a.H * a.hd) : 0;
+      if (part < 2) {
+        const int qd = ((nt0 + tc) % (a.hd >> 4));
+        const long row = EPI == DE_QKV ? em : (long)em * a.ldc + grp;
+        const f32x4* cp = reinterpret_cast<const f32x4*>(a.cs + row * (a.hd >> 1) + qd * 8 + (g & 1) * 4);
+        c0 = cp[0]; c1 = cp[1];
+      }
+    }
+  }
+  float ss[MT];
+  if constexpr (NORM) {
+    const int ns = KT * 2;
+#pragma unroll
+    for (int mt = 0; mt < MT; mt++) {
+      const float* sp = a.ssq + (long)min(mt0 + mt, ntile - 1) * ns * 16 + rl;
+      float t = 0.f;
+      for (int i = wave * 4 + g; i < ns; i += NW * 4) t += sp[i * 16];
+      ss[mt] = t;
+    }
+  }
+  asm volatile("" ::: "memory");      // the loads above stay above the exit
+  if (rf == 0) return;
+  auto mul_chunk = [&](f16x8 (&w)[NC][U], f16x8 (&x)[MT][U], int i0) {
+#pragma unroll
+    for (int u = 0; u < U; u++)
+      if (i0 + u < nk) {
+#pragma unroll
+        for (int mt = 0; mt < MT; mt++)
+#pragma unroll
+          for (int c = 0; c < NC; c++) acc[mt][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w[c][u], x[mt][u], acc[mt][c], 0, 0, 0);
+      }
+  };
+  if constexpr (LOOP) {
+    for (int i0 = 0; i0 < nk; i0 += 2 * U) {
+      f16x8 wn[NC][U], an[MT][U];
+      load_chunk(wn, an, i0 + U);
+      mul_chunk(wc, ac, i0);
+      load_chunk(wc, ac, i0 + 2 * U);
+      mul_chunk(wn, an, i0 + U);
+    }
+  } else {
+    mul_chunk(wc, ac, 0);
+  }
+  // the waves' K slices meet in LDS and are added in wave order
+#pragma unroll
+  for (int mt = 0; mt < MT; mt++) {
+#pragma unroll
+    for (int c = 0; c < NC; c++) red[(wave * T + mt * NC + c) * 64 + lane] = acc[mt][c];
+    if constexpr (NORM) {
+      float t = ss[mt];
+      t += __shfl_xor(t, 16, 64);
+      t += __shfl_xor(t, 32, 64);
+      if (g == 0) sq[(wave * MT + mt) * 16 + rl] = t;
+    }
+  }
+  __syncthreads();
+  for (int t = wave; t < T; t += NW) {
+    const int mt = t / NC, ntc = nt0 + t % NC;
+    const int m = (mt0 + mt) * 16 + rl, n = ntc * 16 + g * 4;
+    f32x4 v = red[t * 64 + lane];
+#pragma unroll
+    for (int w = 1; w < NW; w++) v += red[(w * T + t) * 64 + lane];
+    if constexpr (NORM) {
+      float tot = sq[mt * 16 + rl];
+#pragma unroll
+      for (int w = 1; w < NW; w++) tot += sq[(w * MT + mt) * 16 + rl];
+      v *= 1.0f / sqrtf(tot * a.inv_k + a.eps);
+    }
+    const bool on = m < a.M;
+    const bool first = t == wave && T <= NW;     // operands already here
+    if constexpr (EPI == DE_RES) {
+      if (on) {
+        if (!first && a.R) rv = *reinterpret_cast<const f32x4*>(a.R + (long)m * a.ldr + n);
+        if (!first && a.gain) gv = *reinterpret_cast<const f32x4*>(a.gain + n);
+        if (!first && a.pos) ep = a.pos[m];
+        v += rv;
+        *reinterpret_cast<f32x4*>((float*)a.Y + (long)m * a.ldy + n) = v;
+        if (a.X) {
+          f16x4 o;
+#pragma unroll
+          for (int i = 0; i < 4; i++) o[i] = (f16_t)(v[i] * gv[i]);
+          *reinterpret_cast<f16x4*>(a.X + tile_off(m, n, a.N >> 5)) = o;
+        }
+        if (ep >= 0) {
+          const long ro = ((long)(m / a.RPS) * a.rs + (ep & (a.rs - 1))) * a.N + n;
+          if (a.tap) *reinterpret_cast<f32x4*>(a.tap + ro) = rv;
+          if (a.ring) *reinterpret_cast<f32x4*>(a.ring + ro) = v;
+        }
+      }
+      if (a.ssq_out) {
+        float s2 = v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+        s2 += __shfl_xor(s2, 16, 64);
+        s2 += __shfl_xor(s2, 32, 64);
+        if (g == 0 && on) a.ssq_out[((long)(mt0 + mt) * (a.N >> 4) + ntc) * 16 + rl] = s2;
+      }
+    } else if constexpr (EPI == DE_GELU || EPI == DE_TILE) {
+      if (on) {
+        f16x4 o;
+#pragma unroll
+        for (int i = 0; i < 4; i++) o[i] = (f16_t)(EPI == DE_GELU ? gelu_tanh_f(v[i]) : v[i]);
+        *reinterpret_cast<f16x4*>(a.X + (long)grp * a.gsx + tile_off(m, n, a.N >> 5)) = o;
+      }
+    } else if constexpr (EPI == DE_ROW) {
+      if (on) {
+        f16x4 o;
+#pragma unroll
+        for (int i = 0; i < 4; i++) o[i] = (f16_t)v[i];
+        *reinterpret_cast<f16x4*>((f16_t*)a.Y + (long)grp * a.gsy + (long)m * a.ldy + n) = o;
+      }
+    } else if constexpr (EPI == DE_F32) {
+      if (on) {
+        float* y = (float*)a.Y + (long)grp * a.gsy + (long)m * a.ldy + n;
+        if (a.N % 16 == 0) {
+          if (!first && a.R) rv = *reinterpret_cast<const f32x4*>(a.R + (long)grp * a.gsr + (long)m * a.ldr + n);
+          v += rv;
+          *reinterpret_cast<f32x4*>(y) = v;
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; i++)
+            if (n + i < a.N) y[i] = v[i] + (a.R ? a.R[(long)grp * a.gsr + (long)m * a.ldr + n + i] : 0.f);
+        }
+      }
+    } else {
+      // q, k, v projection (or the q projection of the draft heads).  Tiles of the q and k parts hold 8 rotary pairs of a
+      // head: columns 0..7 the first halves, 8..15 the second halves, so the partner of a value sits 32 lanes away.
+      const int d = a.H * a.hd, part = EPI == DE_QKV ? (ntc * 16) / d : 0, cp = ntc * 16 - part * d;
+      const int hh = cp / a.hd, qd = (cp - hh * a.hd) >> 4;
+      int dim = qd * 16 + g * 4;
+      if (part < 2) {
+        if (!first) {
+          const long row = EPI == DE_QKV ? min(m, a.M - 1) : (long)min(m, a.M - 1) * a.ldc + grp;
+          const f32x4* cq = reinterpret_cast<const f32x4*>(a.cs + row * (a.hd >> 1) + qd * 8 + (g & 1) * 4);
+          c0 = cq[0]; c1 = cq[1];
+        }
+        const f32x4 cx = {c0[0], c0[2], c1[0], c1[2]}, sx = {c0[1], c0[3], c1[1], c1[3]};
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+          const float o = __shfl_xor(v[i], 32, 64);
+          v[i] = g < 2 ? v[i] * cx[i] - o * sx[i] : v[i] * cx[i] + o * sx[i];
+        }
+        dim = (g < 2 ? 0 : a.hd >> 1) + qd * 8 + (g & 1) * 4;
+      }
+      if (on) {
+        f16x4 o;
+#pragma unroll
+        for (int i = 0; i < 4; i++) o[i] = (f16_t)v[i];
+        if (part == 0) {
+          *reinterpret_cast<f16x4*>((f16_t*)a.Y + (long)grp * a.gsy + (long)m * a.ldy + hh * a.hd + dim) = o;
+        } else {
+          if (!first) ep = a.pos[m];
+          if (ep >= 0) {
+            const int p = ep % (a.capb * 32);        // the cache is a ring when a window is set
+            const int r = p & 31;
+            const long base = (long)(m / a.RPS) * a.seq_stride + ((long)hh * a.capb + (p >> 5)) * (32 * a.hd);
+            if (part == 1) {
+              const int f = (r >> 4) * (a.hd >> 5) + (dim >> 5), ln = (r & 15) + 16 * ((dim & 31) >> 3);
+              *reinterpret_cast<f16x4*>(a.Kc + base + (f * 64 + ln) * 8 + (dim & 7)) = o;
+            } else {
+              const int slot = ((r & 15) >> 2) * 8 + (r >> 4) * 4 + (r & 3);
+#pragma unroll
+              for (int i = 0; i < 4; i++) a.Vc[base + (dim + i) * 32 + slot] = o[i];
+            }
+          }
+        }
+      }
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------------
+// Attention over a blocked K/V cache (layouts: kblk_off / vblk_off), up to 32 query rows of a sequence per workgroup
+// ------------------------------------------------------------------------------------------
+// The 32-key blocks of a head are dealt to the NW waves of `ns` workgroups in turn: block b belongs to wave b % NW of
+// split (b / NW) % ns.  The deal depends on nothing but the launch configuration, so the arithmetic of one query row never
+// depends on what else is in the block or on how far the sequence has grown (speculative and one-token decoding agree
+// bit for bit), and it is balanced at every length: short contexts keep all keys in one workgroup (no merge), long
+// ones use all of them.  Partial results of several splits are merged by k_dec_merge in split order.
+struct AttnSet {
+  const f16_t* q;            // [sequence][RS rows][d] rotated queries
+  const int* limit;          // [sequence][RS] last visible key, -1 = inactive row
+  int rows, q0, RS;          // this launch takes rows q0 .. q0 + rows of every sequence
+  const f16_t *Kc, *Vc;
+  long seq_stride;           // elements between the caches of two sequences
+  int capb, window, ns;      // capacity in blocks, sliding window (0 = none; the cache is then a ring), splits
+  RowMap rm;                 // where the rows go in the tiled output
+  f16_t* out;
+};
+#define FM_ATTN_SETS 4
+struct AttnArgs {
+  AttnSet set[FM_ATTN_SETS];
+  int S, H, ns_max;
+  float* ws;                 // [set][sequence][head][ns_max][QT*16*HD unnormalised O | QT*16 running max (log2 units) | QT*16 sums]
+  const int* run_flag;
+};
+__device__ __forceinline__ AttnSet attn_set(const AttnArgs& a, int z) { return z == 0 ? a.set[0] : z == 1 ? a.set[1] : z == 2 ? a.set[2] : a.set[3]; }
+__device__ __forceinline__ int attn_active(int maxlim, int capb, int ns, int NW) {      // splits that hold visible keys
+  const int nblk = min((maxlim + 32) >> 5, capb);
+  return max(1, min(ns, (nblk + NW - 1) / NW));
+}
+
+template <int QT, int HD, int NW>
+__global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
+  constexpr int NQ = QT * 16, KC = HD / 32, DT = HD / 16, BLK = 32 * HD, PSZ = NQ * HD + 2 * NQ, LD = HD + 4;
+  extern __shared__ f32x4 da_smem[];
+  float* lo = (float*)da_smem;              // [NW][NQ][LD]
+  float* lm = lo + NW * NQ * LD;            // [NW][NQ]
+  float* ll = lm + NW * NQ;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int g = lane >> 4, ql = lane & 15;
+  const int hh = blockIdx.x, split = blockIdx.y, s = blockIdx.z % a.S, z = blockIdx.z / a.S;
+  const AttnSet A = attn_set(a, z);
+  if (split >= A.ns) return;
+  const int rf = a.run_flag ? *a.run_flag : 1;
+  const int d = a.H * HD;
+  const float kScale = (HD == 64 ? 0.125f : 1.0f / sqrtf((float)HD)) * 1.4426950408889634f;   // 1/sqrt(HD) * log2(e)
+  const f16_t* Kb = A.Kc + (long)s * A.seq_stride + (long)hh * A.capb * BLK + lane * 8;
+  const f16_t* Vb = A.Vc + (long)s * A.seq_stride + (long)hh * A.capb * BLK + ql * 32 + g * 8;
+  // the first block of this wave is inside the cache whatever the length: request it before anything else is known
+  const int bstep = A.ns * NW;
+  int b = split * NW + wave;
+  f16x8 kf[2 * KC], vf[DT];
+  auto load_block = [&](int blk) {
+#pragma unroll
+    for (int f = 0; f < 2 * KC; f++) kf[f] = *reinterpret_cast<const f16x8*>(Kb + (long)blk * BLK + f * 512);
+#pragma unroll
+    for (int dt = 0; dt < DT; dt++) vf[dt] = *reinterpret_cast<const f16x8*>(Vb + (long)blk * BLK + dt * 512);
+  };
+  load_block(min(b, A.capb - 1));
+  int lim[QT], first[QT];
+  f16x8 qf[QT][KC];
+  int maxlim = -1;
+#pragma unroll
+  for (int t = 0; t < QT; t++) {
+    const int qi = t * 16 + ql;
+    const bool on = qi < A.rows;
+    const long row = (long)s * A.RS + A.q0 + (on ? qi : 0);
+    lim[t] = on ? A.limit[row] : -1;
+    const f16_t* qp = A.q + row * d + hh * HD + g * 8;
+#pragma unroll
+    for (int kc = 0; kc < KC; kc++) qf[t][kc] = *reinterpret_cast<const f16x8*>(qp + kc * 32);
+  }
+  asm volatile("" ::: "memory");      // the loads above stay above the exit
+  if (rf == 0) return;
+#pragma unroll
+  for (int t = 0; t < QT; t++) {
+    first[t] = A.window > 0 ? max(lim[t] - A.window + 1, 0) : 0;     // sliding window: keys first .. lim
+    maxlim = max(maxlim, lim[t]);
+  }
+#pragma unroll
+  for (int o = 1; o < 16; o <<= 1) maxlim = max(maxlim, __shfl_xor(maxlim, o, 64));
+  maxlim = __builtin_amdgcn_readfirstlane(maxlim);
+  // With a window the cache is a ring of capb blocks: position p lives in slot p mod (32 capb), and a slot holds
+  // the latest position written to it.  Seen from the newest visible position `maxlim`, slot j holds lapbase + j if that
+  // is <= maxlim, else the position one lap earlier (anything newer in the ring is a stale row of a rejected block: it
+  // maps below the window and is masked).  Without a window lapbase = 0.
+  const int nblk = min((maxlim + 32) >> 5, A.capb);
+  const int ringn = A.capb * 32;
+  const int lapbase = A.window > 0 ? max(maxlim, 0) / ringn * ringn : 0;
+  const int nact = attn_active(maxlim, A.capb, A.ns, NW);
+  if (split >= nact) return;
+
+  float mrun[QT], lrun[QT];
+  f32x4 o[QT][DT];
+#pragma unroll
+  for (int t = 0; t < QT; t++) {
+    mrun[t] = -INFINITY;
+    lrun[t] = 0.f;
+#pragma unroll
+    for (int dt = 0; dt < DT; dt++) o[t][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  for (; b < nblk; b += bstep) {
+    f16x8 kn[2 * KC], vn[DT];
+    if (b + bstep < nblk) {
+#pragma unroll
+      for (int f = 0; f < 2 * KC; f++) kn[f] = *reinterpret_cast<const f16x8*>(Kb + (long)(b + bstep) * BLK + f * 512);
+#pragma unroll
+      for (int dt = 0; dt < DT; dt++) vn[dt] = *reinterpret_cast<const f16x8*>(Vb + (long)(b + bstep) * BLK + dt * 512);
+    }
+#pragma unroll
+    for (int t = 0; t < QT; t++) {
+      // scores, transposed: sT[hb][i] = <K[key], Q[q]> for key = b*32 + hb*16 + g*4 + i, q = this lane's row
+      f32x4 sT[2];
+#pragma unroll
+      for (int hb = 0; hb < 2; hb++) {
+        f32x4 zz = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kc = 0; kc < KC; kc++) zz = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf[hb * KC + kc], qf[t][kc], zz, 0, 0, 0);
+        sT[hb] = zz;
+      }
+      float mx = -INFINITY;
+#pragma unroll
+      for (int hb = 0; hb < 2; hb++)
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+          int key = lapbase + b * 32 + hb * 16 + g * 4 + i;     // absolute position held by this slot
+          key = key > maxlim ? key - ringn : key;
+          const float v = (key <= lim[t] && key >= first[t]) ? sT[hb][i] * kScale : -INFINITY;
+          sT[hb][i] = v;
+          mx = fmaxf(mx, v);
+        }
+      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      const float mnew = fmaxf(mrun[t], mx);
+      const float msafe = mnew == -INFINITY ? 0.f : mnew;
+      const float alpha = __builtin_amdgcn_exp2f(mrun[t] - msafe);   // exp2(-inf) = 0 on the first block
+      mrun[t] = mnew;
+      f16x8 pf;
+      float psum = 0.f;
+#pragma unroll
+      for (int hb = 0; hb < 2; hb++)
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+          const float p = __builtin_amdgcn_exp2f(sT[hb][i] - msafe);
+          psum += p;
+          pf[hb * 4 + i] = (f16_t)p;
+        }
+      lrun[t] = lrun[t] * alpha + psum;
+#pragma unroll
+      for (int dt = 0; dt < DT; dt++) {
+        o[t][dt] *= alpha;
+        o[t][dt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vf[dt], pf, o[t][dt], 0, 0, 0);   // O^T[dim][q]
+      }
+    }
+    if (b + bstep < nblk) {
+#pragma unroll
+      for (int f = 0; f < 2 * KC; f++) kf[f] = kn[f];
+#pragma unroll
+      for (int dt = 0; dt < DT; dt++) vf[dt] = vn[dt];
+    }
+  }
+  // combine the waves of the workgroup that had keys
+#pragma unroll
+  for (int t = 0; t < QT; t++) {
+    float l = lrun[t];
+    l += __shfl_xor(l, 16, 64);
+    l += __shfl_xor(l, 32, 64);
+    if (g == 0) { lm[wave * NQ + t * 16 + ql] = mrun[t]; ll[wave * NQ + t * 16 + ql] = l; }
+#pragma unroll
+    for (int dt = 0; dt < DT; dt++) *reinterpret_cast<f32x4*>(lo + (wave * NQ + t * 16 + ql) * LD + dt * 16 + g * 4) = o[t][dt];
+  }
+  __syncthreads();
+  const int wact = max(1, min(NW, nblk - split * NW));
+  float* part = a.ws + (((long)blockIdx.z * a.H + hh) * a.ns_max + split) * PSZ;
+  for (int e = threadIdx.x; e < A.rows * (HD / 4); e += NW * 64) {
+    const int qi = e / (HD / 4), dim = e % (HD / 4) * 4;
+    float M = -INFINITY;
+    for (int w = 0; w < wact; w++) M = fmaxf(M, lm[w * NQ + qi]);
+    const float Ms = M == -INFINITY ? 0.f : M;
+    f32x4 num = f32x4{0.f, 0.f, 0.f, 0.f};
+    float den = 0.f;
+    for (int w = 0; w < wact; w++) {
+      const float f = __builtin_amdgcn_exp2f(lm[w * NQ + qi] - Ms);
+      num += *reinterpret_cast<const f32x4*>(lo + (w * NQ + qi) * LD + dim) * f;
+      den += ll[w * NQ + qi] * f;
+    }
+    if (nact == 1) {
+      f16x4 ov;
+#pragma unroll
+      for (int i = 0; i < 4; i++) ov[i] = (f16_t)(den > 0.f ? num[i] / den : 0.f);
+      *reinterpret_cast<f16x4*>(A.out + map_off(A.rm, s, A.q0 + qi, hh * HD + dim, d >> 5)) = ov;
+    } else {
+      *reinterpret_cast<f32x4*>(part + qi * HD + dim) = num;
+      if (dim == 0) { part[NQ * HD + qi] = M; part[NQ * HD + NQ + qi] = den; }
+    }
+  }
+}
+
+// Merge of the partial results of the splits, one workgroup per (head, sequence and set); (sequence, head) pairs whose
+// keys fitted one split were written by the attention launch already.  All partials of a thread are in flight at once.
+template <int QT, int HD, int NW>
+__global__ __launch_bounds__(256) void k_dec_merge(AttnArgs a) {
+  constexpr int NQ = QT * 16, PSZ = NQ * HD + 2 * NQ, C = 8;
+  const int hh = blockIdx.x, s = blockIdx.y % a.S, z = blockIdx.y / a.S;
+  const AttnSet A = attn_set(a, z);
+  const int rf = a.run_flag ? *a.run_flag : 1;
+  const float* base = a.ws + ((long)blockIdx.y * a.H + hh) * a.ns_max * PSZ;
+  int maxlim = (int)(threadIdx.x & 31) < A.rows ? A.limit[(long)s * A.RS + A.q0 + (threadIdx.x & 31)] : -1;
+  // the first splits are requested before it is known how many there are (the workspace holds ns_max of them)
+  int e = threadIdx.x;
+  int qi = e / (HD / 4), dim = e % (HD / 4) * 4;
+  f32x4 v[C];
+  float m[C], l[C];
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int j = 0; j < C; j++) {
+      const int k = min(k0 + j, a.ns_max - 1), q = min(qi, NQ - 1);
+      const float* p = base + (long)k * PSZ;
+      v[j] = *reinterpret_cast<const f32x4*>(p + q * HD + dim);
+      m[j] = p[NQ * HD + q];
+      l[j] = p[NQ * HD + NQ + q];
+    }
+  };
+  load(0);
+  asm volatile("" ::: "memory");
+  if (rf == 0 || A.ns <= 1) return;
+#pragma unroll
+  for (int o = 1; o < 32; o <<= 1) maxlim = max(maxlim, __shfl_xor(maxlim, o, 64));
+  const int n = attn_active(maxlim, A.capb, A.ns, NW);
+  if (n == 1) return;
+  for (; e < A.rows * (HD / 4); e += 256) {
+    if (e != (int)threadIdx.x) {
+      qi = e / (HD / 4); dim = e % (HD / 4) * 4;
+      load(0);
+    }
+    float M = -INFINITY, den = 0.f;
+    f32x4 num = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int k0 = 0; k0 < n; k0 += C) {
+      if (k0 > 0) load(k0);
+      float Mc = M;
+#pragma unroll
+      for (int j = 0; j < C; j++) if (k0 + j < n) Mc = fmaxf(Mc, m[j]);
+      const float Ms = Mc == -INFINITY ? 0.f : Mc;
+      const float sc = __builtin_amdgcn_exp2f(M - Ms);
+      num *= sc;
+      den *= sc;
+      M = Mc;
+#pragma unroll
+      for (int j = 0; j < C; j++)
+        if (k0 + j < n) {
+          const float f = __builtin_amdgcn_exp2f(m[j] - Ms);
+          num += v[j] * f;
+          den += l[j] * f;
+        }
+    }
+    f16x4 ov;
+#pragma unroll
+    for (int i = 0; i < 4; i++) ov[i] = (f16_t)(den > 0.f ? num[i] / den : 0.f);
+    *reinterpret_cast<f16x4*>(A.out + map_off(A.rm, s, A.q0 + qi, hh * HD + dim, (a.H * HD) >> 5)) = ov;
+  }
+}

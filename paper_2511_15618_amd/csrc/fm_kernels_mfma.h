@@ -772,13 +772,13 @@ inline size_t mfma_attn_ws_floats(int S, int H, int hd = 64) {
 
 template <typename T>
 bool mfma_attn_launch(const MfmaRes&, const void*, const int*, int, int, const void*, const void*, long, int, void*, int,
-                      const int*, bool, int, int, hipStream_t, int = 64) { return false; }
+                      const int*, bool, int, hipStream_t, int = 64) { return false; }
 
 // `cap` = key capacity of the cache (positions); caches are laid out in 32-key blocks
 template <>
 inline bool mfma_attn_launch<f16_t>(const MfmaRes& res, const void* q, const int* limit, int rows, int RPS, const void* Kc,
                                     const void* Vc, long seq_stride, int cap, void* out, int H, const int* flag,
-                                    bool dense, int key_bound, int window, hipStream_t st, int hd) {
+                                    bool dense, int window, hipStream_t st, int hd) {
   if (RPS < 1 || rows % RPS != 0) return false;
   if (hd != 64 && hd != 96 && hd != 128) return false;
   if (window > 0 && (cap % 32 != 0 || window > cap)) return false;     // a ring is a whole number of blocks
@@ -796,16 +796,11 @@ inline bool mfma_attn_launch<f16_t>(const MfmaRes& res, const void* q, const int
     const int want = target / (H * S) > 0 ? target / (H * S) : 1;
     nsplit = nsplit > want ? want : nsplit;
   }
-  // `key_bound` is the host's upper bound on the visible keys: ranges past it hold nothing and are not launched
-  const int per = (capb + nsplit - 1) / nsplit;
-  const int bound_blocks = ((key_bound < cap ? key_bound : cap) + 31) / 32;
-  int launched = (bound_blocks + per - 1) / per;
-  launched = launched < 1 ? 1 : launched > nsplit ? nsplit : launched;
-  dim3 grid(launched, H, S);
+  dim3 grid(nsplit, H, S);       // ranges past the committed length hold nothing and leave at once
   // With many workgroups the in-kernel merge loses: every workgroup pays an agent-scope release fence (an L2
   // write-back, and those queue up per XCD).  Then the partials go out as plain stores and a second, tiny
   // launch merges them; the arithmetic is the same either way.
-  const int defer = res.attn_merge == 2 ? 2 : (launched > 1 && (long)launched * H * S > 256) ? 1 : 0;
+  const int defer = res.attn_merge == 2 ? 2 : (nsplit > 1 && (long)nsplit * H * S > 256) ? 1 : 0;
   // at most 32 query rows of a sequence per launch (16 for the wide heads, whose partial tiles would not fit the
   // LDS of a 32-row launch); longer row sets go out in chunks
   const int d = H * hd;
@@ -831,11 +826,11 @@ inline bool mfma_attn_launch<f16_t>(const MfmaRes& res, const void* q, const int
 }
 
 // One launch (plus the merge launch) for up to three row sets of one sequence, each with its own cache.
-// `dense`, `key_bound`, `window` per set as in mfma_attn_launch.  Returns false if a set does not fit one q-tile.
+// `dense`, `window` per set as in mfma_attn_launch.  Returns false if a set does not fit one q-tile.
 // `rows` = rows of the set per sequence; q, limit and out point at the set's first row of sequence 0 in buffers with RS
 // rows per sequence; S sequences.
 struct AttnLevelHost {
-  const void* q; const int* limit; int rows; const void *Kc, *Vc; long seq_stride; int cap; void* out; bool dense; int key_bound, window;
+  const void* q; const int* limit; int rows; const void *Kc, *Vc; long seq_stride; int cap; void* out; bool dense; int window;
 };
 inline bool mfma_attn_launch_levels(const MfmaRes& res, const AttnLevelHost (&lv)[3], int S, int RS, int H, const int* flag,
                                     hipStream_t st) {
@@ -859,12 +854,8 @@ inline bool mfma_attn_launch_levels(const MfmaRes& res, const AttnLevelHost (&lv
       nsplit = nsplit > want ? want : nsplit;
     }
     A.nsplit_cfg = nsplit;
-    const int per = (A.capb + nsplit - 1) / nsplit;
-    const int bound_blocks = ((h.key_bound < h.cap ? h.key_bound : h.cap) + 31) / 32;
-    int launched = (bound_blocks + per - 1) / per;
-    launched = launched < 1 ? 1 : launched > nsplit ? nsplit : launched;
-    gx = launched > gx ? launched : gx;
-    total += (long)launched * H * S;
+    gx = nsplit > gx ? nsplit : gx;
+    total += (long)nsplit * H * S;
   }
   const int defer = res.attn_merge == 2 ? 2 : (gx > 1 && total > 256) ? 1 : 0;
   hipLaunchKernelGGL(k_attn_mfma_levels, dim3(gx, H, 3 * S), dim3(256), 0, st, L, H, res.attn_ws, res.attn_counters, defer, flag);

@@ -82,7 +82,7 @@ struct PkArgs {
   u64 *newK, *newV;         // [H][RS][32]
   u64 *partS, *partX;       // [H][PK_MAXSPLIT][RS/16][PK_PART]
   u64* w2part;              // [d/16][RS/16][3][256]: partial tiles of the K-quarters 1..3 of the FFN down projection
-  unsigned epoch;
+  const unsigned* epoch_word;  // passes so far, counted by k_verify_setup
   u64 timeout_ticks;        // bound of every wait (100 MHz wall clock)
   int two_phase;            // waits first watch one element per lane and only then read everything (0: the full read is the poll)
   unsigned test_skew;       // test hook: added to the tag the embedding publishes, so that nothing downstream ever arrives
@@ -180,7 +180,7 @@ __device__ __forceinline__ bool pk_fetch(unsigned (&out)[N], int n, bool active,
 // waits for row 0 of the stack output from EVERY tile (a tile stores only after its last read).
 __device__ __forceinline__ bool pk_wait_stack(const PkArgs& a, const u64* hT, unsigned tag, int stage, int rows);
 
-#define PK_TAG(a, l) ((a).epoch * 64u + (unsigned)(l) + 1u)
+#define PK_TAG(l) (epoch * 64u + (unsigned)(l) + 1u)      // epoch: local of the kernel
 
 __device__ __forceinline__ bool pk_wait_stack(const PkArgs& a, const u64* hT, unsigned tag, int stage, int rows) {
   unsigned s4[4];
@@ -744,6 +744,7 @@ __device__ __forceinline__ bool pk_merge_unit(const PkArgs& a, int maxlim, int R
 
 template <int QT>
 __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
+  const unsigned epoch = __builtin_amdgcn_readfirstlane((int)*a.epoch_word);
   if (*a.run_flag == 0) return;
   __shared__ PkShared<QT> sh;
   const int RS = QT * 16, RH = QT * 8;     // rows of an exchange region (= a.RS), and half of it: the row count of a half-pair region in units of d
@@ -787,9 +788,9 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
     const f16_t* e = a.emb + (long)a.vtok[r] * d;
     for (int i = threadIdx.x; i < d; i += 256) {     // region of layer 0, and its half-pair copy (d is a multiple of 128)
       const float v = onr ? (float)e[i] : 0.f;
-      pk_stf(a.hA + (long)r * d + i, v, PK_TAG(a, 0) + a.test_skew);
+      pk_stf(a.hA + (long)r * d + i, v, PK_TAG(0) + a.test_skew);
       const float w = __shfl_xor(v, 1, 64);
-      if ((i & 1) == 0) pk_st(a.xA + (long)r * (d >> 1) + (i >> 1), pk_pack(v, w), PK_TAG(a, 0) + a.test_skew);
+      if ((i & 1) == 0) pk_st(a.xA + (long)r * (d >> 1) + (i >> 1), pk_pack(v, w), PK_TAG(0) + a.test_skew);
     }
   }
   PK_NEXT(a.R[0]);
@@ -799,7 +800,7 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
       const int l = a.first[st] + li;
       const PkLayer& L = a.layers[l];
       const int lev = L.level, R = a.R[lev];
-      const unsigned tag = PK_TAG(a, l);
+      const unsigned tag = PK_TAG(l);
       const int* pos = a.pos[lev];
       const int capb = a.capb[lev];
       // this layer's own regions of the exchange buffers
@@ -947,7 +948,7 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
                 ring = st == 0 ? a.ring_hc : st == 1 ? a.ring_hv : st == 2 ? a.ring_yf : a.ring_yv;
                 rs = st == 0 ? 32 : st == 2 ? 8 : 16;
               }
-              pk_epi_residual(a, c, nt, old, dst + (long)row0 * d, xdst ? xdst + row0 * hd : nullptr, PK_TAG(a, l + 1), Rl, prow,
+              pk_epi_residual(a, c, nt, old, dst + (long)row0 * d, xdst ? xdst + row0 * hd : nullptr, PK_TAG(l + 1), Rl, prow,
                               nullptr, ring, rs);
             }
           }
@@ -958,7 +959,7 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
     }
     // ---- level transition after stack st; everything it produces carries the tag of the next layer
     const int ln = a.first[st] + a.count[st];
-    const unsigned tagn = PK_TAG(a, ln);
+    const unsigned tagn = PK_TAG(ln);
     if (st == 0 || st == 1) {
       // shorten: coarse slot k pools fine positions 3j-2..3j (this pass: stack output; older: ring; before the start: 0)
       const int fl = st, cl = st + 1;
@@ -1013,7 +1014,7 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
       // upsample: fine row = skip (output of the level's first half) + coarse output of slot floor(pos/3)
       const int fl = st == 2 ? 1 : 0, cl = fl + 1;
       const u64* skip = a.hT[st == 2 ? 1 : 0];
-      const unsigned tag_skip = PK_TAG(a, a.first[st == 2 ? 1 : 0] + a.count[st == 2 ? 1 : 0]);
+      const unsigned tag_skip = PK_TAG(a.first[st == 2 ? 1 : 0] + a.count[st == 2 ? 1 : 0]);
       const float* ring = st == 2 ? a.ring_yf : a.ring_yv;
       const int rs = st == 2 ? 8 : 16;
       const int Rf_ = a.R[fl], Rc_ = a.R[cl];
@@ -1051,7 +1052,7 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
       const int nt = u / RG, row0 = (u % RG) * 16, Rl = min(16, R - row0);
       f32x4 c;
       if (!pk_gemm_tile<1>(a, sh, (pk_cw_t)a.lm + (long)nt * (d / 32) * 512, d / 32, a.xA + (long)l * RH * d + (long)row0 * (d >> 1),
-                           PK_TAG(a, l), (pk_cf_t)a.gf, Rl, c, stage)) return;
+                           PK_TAG(l), (pk_cf_t)a.gf, Rl, c, stage)) return;
       if (wave == 0) {
         const int lane = threadIdx.x & 63, g = lane >> 4, n = nt * 16 + (lane & 15);
 #pragma unroll

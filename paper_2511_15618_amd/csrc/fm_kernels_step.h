@@ -46,7 +46,8 @@ __device__ __forceinline__ int eff_block_len(const StateDev& st, const Dims& D, 
 __global__ __launch_bounds__(256) void k_verify_setup(StateDev st, Dims D, InvFreq inv, const int* __restrict__ block_tok,
                                                        const int* __restrict__ block_len, int* pos_c, int* pos_v, int* pos_f,
                                                        int* limx_c, int* limx_v, int* limx_f, float2* cs_c, float2* cs_v,
-                                                       float2* cs_f) {
+                                                       float2* cs_f, unsigned* epoch) {
+  if (epoch && blockIdx.x == 0 && threadIdx.x == 0) *epoch += 1;     // pass counter of the single-launch verify kernel
   const int tid = blockIdx.x * 256 + threadIdx.x, nth = gridDim.x * 256;
   // position of row idx of a level, -1 for a row the block does not reach
   auto row_c = [&](int idx) {
@@ -121,11 +122,26 @@ __global__ void k_accept(StateDev st, Dims D, int* __restrict__ accepted_out, co
   if (accepted_out) accepted_out[s] = a;
 }
 
-// An accepted length of 0 (a pass that did not complete) leaves the sequence as it is.
-__global__ void k_commit(StateDev st, Dims D, const int* __restrict__ accepted, const unsigned* __restrict__ failed) {
+// What the host may look at while the device runs ahead of it: one pinned word per sequence, written by the commits of
+// fm_generate.  Count and state travel in one word, so nothing has to be ordered.
+//   upper half: number of the fm_generate call (12 bits), commits since its start (20 bits)
+//   lower half: 0 = the single-launch verify kernel gave up, 1 = sequence finished, else committed length + 2
+struct Progress { unsigned long long seq[64]; };
+
+// An accepted length of 0 (a pass that did not complete) leaves the sequence as it is.  prog: null for the caller's own commits.
+__global__ void k_commit(StateDev st, Dims D, const int* __restrict__ accepted, const unsigned* __restrict__ failed, unsigned* commits,
+                         Progress* prog) {
   const int s = threadIdx.x;
   __shared__ int any_live;
-  if (failed && *failed) return;
+  auto report = [&](bool bad) {
+    if (!prog) return;
+    const unsigned n = *commits + 1;       // one wave: read by all lanes before lane 0 writes it
+    if (s == 0) *commits = n;
+    if (s < D.S)
+      __hip_atomic_store(&prog->seq[s], (unsigned long long)n << 32 | (unsigned)(bad ? 0 : st.fin[s] ? 1 : st.P[s] + 2), __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_SYSTEM);
+  };
+  if (failed && *failed) { report(true); return; }
   if (s == 0) any_live = 0;
   __syncthreads();
   if (s < D.S) {
@@ -151,16 +167,32 @@ __global__ void k_commit(StateDev st, Dims D, const int* __restrict__ accepted, 
     }
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int alive = 0;
-    for (int i = 0; i < D.S; i++) alive += st.fin[i] ? 0 : 1;
+  const int alive = __popcll(__ballot(s < D.S && !st.fin[s]));      // one wave: at most 64 sequences
+  if (s == 0) {
     st.alive[0] = alive;
     if (any_live) st.counters[0] += 1;
   }
+  report(false);
+}
+
+// End of fm_generate: x_1 .. of every sequence and its length to the caller, counters to pinned host memory.
+__global__ __launch_bounds__(256) void k_finish(StateDev st, Dims D, int* __restrict__ out_tok, int* __restrict__ out_len,
+                                                unsigned long long* __restrict__ host_counts) {
+  const int s = blockIdx.y;
+  const int* h = st.hist + (long)s * (D.maxtok + 1) + 1;
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < D.maxtok; i += gridDim.x * 256) out_tok[(long)s * D.maxtok + i] = h[i];
+  if (blockIdx.x == 0 && threadIdx.x == 0) out_len[s] = st.P[s];
+  if (blockIdx.x == 0 && s == 0 && threadIdx.x < 99) host_counts[threadIdx.x] = threadIdx.x < 3 ? st.counters[threadIdx.x] : st.acc_hist[threadIdx.x - 3];
 }
 
 // New token budget: sequences that have not ended with EOS become live again if they are below it.
-__global__ void k_set_budget(StateDev st, Dims D, int budget) {
+// generation > 0: the start of fm_generate call number `generation` (statistics and the commit counter start over)
+__global__ void k_set_budget(StateDev st, Dims D, int budget, unsigned generation, unsigned* commits) {
+  if (generation) {
+    if (threadIdx.x == 0) *commits = generation << 20;
+    for (int i = threadIdx.x; i < 96; i += 64) st.acc_hist[i] = 0;
+    if (threadIdx.x < 3) st.counters[threadIdx.x] = 0;
+  }
   if (threadIdx.x != 0) return;
   st.budget[0] = budget;
   int alive = 0;
@@ -195,14 +227,30 @@ __global__ void k_reset_seq(StateDev st, Dims D, int s, int bos) {
 #define FM_U_ACCEPT 1
 #define FM_U_RESAMPLE 2
 
-struct Sampling {
-  float temperature;            // 0 = greedy decoding
+// Settings that a caller may change between steps.  They live in device memory (k_set_params writes them in stream order), so
+// that a step recorded as a graph stays valid when they change.
+struct Replay {
+  const int* stream;  // [S][stride], stream[p - 1] = x_p
+  int stride, n_valid;
+  float keep;
   unsigned long long seed;
+};
+struct StepParams {
+  Replay replay;
+  float temperature;            // 0 = greedy decoding
+  unsigned long long seed;      // of the sampled decoding
+  int keep_rows;                // test hook: greedy decoding also leaves the averaged rows in qrow (read by fm_debug_draft)
+};
+__global__ void k_set_params(StepParams* dst, StepParams v) {
+  if (threadIdx.x == 0) *dst = v;
+}
+
+struct Sampling {
+  const StepParams* p;
   float* qrow;                  // [S][Bm][V] averaged draft distribution behind draft index i (unnormalised over the admissible tokens)
   float* qsum;                  // [S][Bm]    its sum over the admissible tokens
   int* qtok;                    // [S][Bm]    the token drawn from it (-1: none)
   int* accflag;                 // [S][Bm]    row i: draft i + 1 passed the rejection test
-  int keep_rows;                // test hook: greedy decoding also leaves the averaged rows in qrow (read by fm_debug_draft)
 };
 
 __device__ __forceinline__ float sample_uniform(unsigned long long seed, int purpose, int seq, int pos);
@@ -389,13 +437,6 @@ __global__ __launch_bounds__(256) void k_dist_store(const float* __restrict__ lo
   for (int i = threadIdx.x; i < D.V; i += 256) dst[i] = expf(x[i] - mx) * inv;
 }
 
-struct Replay {
-  const int* stream;  // [S][stride], stream[p - 1] = x_p
-  int stride, n_valid;
-  float keep;
-  unsigned long long seed;
-};
-
 __device__ __forceinline__ float replay_uniform(unsigned long long seed, unsigned long long seq, unsigned long long pos) {
   unsigned long long z = seed * 0x9E3779B97F4A7C15ull + seq * 0xBF58476D1CE4E5B9ull + pos * 0x94D049BB133111EBull +
                          0x2545F4914F6CDD1Dull;
@@ -421,7 +462,8 @@ __global__ __launch_bounds__(256) void k_sample_rows(StateDev st, Dims D, const 
   if (i >= len) return;
   const int nlim = D.ban ? D.nbins : D.V;
   const float* x = logits + (long)row * D.V;
-  const float invT = 1.0f / sm.temperature;
+  const unsigned long long seed = sm.p->seed;
+  const float invT = 1.0f / sm.p->temperature;
   // max and sum of exp((x - max) / T)
   float mx = -INFINITY;
   for (int j = threadIdx.x; j < nlim; j += 256) mx = fmaxf(mx, x[j]);
@@ -449,9 +491,9 @@ __global__ __launch_bounds__(256) void k_sample_rows(StateDev st, Dims D, const 
   bool accepted = false;
   if (has_draft && xd >= 0 && xd < nlim) {
     const float pa = pf(xd), qa = fromq ? q[xd] * invZq : 1.0f;
-    accepted = sample_uniform(sm.seed, FM_U_ACCEPT, s, pos) * qa < pa;
+    accepted = sample_uniform(seed, FM_U_ACCEPT, s, pos) * qa < pa;
   }
-  const float u = sample_uniform(sm.seed, FM_U_RESAMPLE, s, pos);
+  const float u = sample_uniform(seed, FM_U_RESAMPLE, s, pos);
   int y;
   if (!has_draft) {
     y = block_inverse_cdf(nlim, u, pf, sh, &si);
@@ -477,11 +519,13 @@ __global__ __launch_bounds__(256) void k_sample_rows(StateDev st, Dims D, const 
 // each future position, take the greedy token, stop at the first uncovered position.
 __global__ __launch_bounds__(1024) void k_merge(StateDev st, Dims D, DraftRows R, const float* __restrict__ dist_c,
                                                 const float* __restrict__ dist_v, const float* __restrict__ dist_f,
-                                                Replay rp, int speculative, int* __restrict__ block_tok,
+                                                int speculative, int* __restrict__ block_tok,
                                                 int* __restrict__ block_len, Sampling sm) {
   __shared__ float sh[1026];
   __shared__ int sidx;
-  if (sm.temperature > 0.f)
+  const StepParams pr = *sm.p;
+  const Replay& rp = pr.replay;
+  if (pr.temperature > 0.f)
     for (int i = threadIdx.x; i < D.Bm; i += blockDim.x) sm.qtok[blockIdx.x * D.Bm + i] = -1;
   const int s = blockIdx.x;
   int* tok = block_tok + (long)s * D.Bm;
@@ -519,7 +563,7 @@ __global__ __launch_bounds__(1024) void k_merge(StateDev st, Dims D, DraftRows R
     if (basef >= 0 && tf >= D.t0 && tf < D.n) rows[cnt++] = dist_f + ((long)s * D.nhfc + (tf - D.t0)) * D.V;
     return cnt;
   };
-  if (sm.temperature > 0.f) {
+  if (pr.temperature > 0.f) {
     // sampled decoding: keep the averaged distribution (the proposal the verify pass tests against) and draw from it
     for (int p = spos + 2; len < D.Bm && p < budget; p++) {
       const float* rows[3];
@@ -534,7 +578,7 @@ __global__ __launch_bounds__(1024) void k_merge(StateDev st, Dims D, DraftRows R
         qr[i] = a * inv;
       }
       __syncthreads();
-      const int b = block_inverse_cdf(nlim, sample_uniform(sm.seed, FM_U_DRAFT, s, p), [&](int i) { return qr[i]; }, sh, &sidx);
+      const int b = block_inverse_cdf(nlim, sample_uniform(pr.seed, FM_U_DRAFT, s, p), [&](int i) { return qr[i]; }, sh, &sidx);
       if (threadIdx.x == 0) { tok[len] = b; sm.qtok[s * D.Bm + len] = b; sm.qsum[s * D.Bm + len] = sh[blockDim.x]; }
       __syncthreads();
       len++;
@@ -568,7 +612,7 @@ __global__ __launch_bounds__(1024) void k_merge(StateDev st, Dims D, DraftRows R
           for (int k = 0; k < 4; k++)
             if (i0 + 64 * k < nlim) {
               argmax_merge(bv, bi, a[k] * inv, i0 + 64 * k);
-              if (sm.keep_rows) sm.qrow[((long)s * D.Bm + idx) * D.V + i0 + 64 * k] = a[k] * inv;
+              if (pr.keep_rows) sm.qrow[((long)s * D.Bm + idx) * D.V + i0 + 64 * k] = a[k] * inv;
             }
         }
 #pragma unroll
