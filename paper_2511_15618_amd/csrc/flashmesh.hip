@@ -19,6 +19,7 @@
 #include "fm_kernels_basic.h"
 #include "fm_kernels_step.h"
 #include "fm_kernels_mfma.h"
+#include "fm_kernels_decode.h"
 #include "fm_kernels_persist.h"
 #include "fm_kernels_prefill.h"
 
@@ -37,7 +38,6 @@ namespace {
 struct Layer {
   float *g1, *g2, *g3;
   void *wqkv, *wo, *cq, *ckv, *co, *w1, *w2;  // storage type T, [out, in]
-  void* wqkv_rp;                               // persistent path: q/k tiles hold whole rotary pairs
   void *Kc, *Vc;                               // [S][H][cap][64]
   void *Km, *Vm;                               // [S][H][M][64]
   int level;                                   // 0 coordinate, 1 vertex, 2 face
@@ -54,7 +54,7 @@ struct HfLevel {
   void *wq, *w1, *w2;
 };
 
-struct LoadItem { size_t blob_off, n; void* dst; bool f32; int N, K, perm; };  // N, K > 0: linear weight [N, K]
+struct LoadItem { size_t blob_off, n; void* dst; bool f32; int N, K, rope; };  // N, K > 0: linear weight [N, K], the first `rope` rows of queries / keys
 
 // device address of `scratch` on each GPU, looked up once per device (at the first fm_create on it)
 std::mutex g_scratch_mu;
@@ -85,7 +85,6 @@ struct fm_ctx {
   float* gf;
   SpLevel sp[3];
   SpLevel sp_all;          // the heads of all three levels as one group list, in memory order point, face, coordinate
-  bool sp_merged = false;  // half path, 64-wide heads: the three SP chains run as one chain of grouped launches
   const float** lm_src = nullptr;   // rows of the output head's input: coordinate SP head outputs, then coordinate HF outputs
   HfLevel hfc, hfv;
   float* label_w;     // label head of the correct stage [3][d]
@@ -103,7 +102,15 @@ struct fm_ctx {
   float* h[3];
   void *xn, *qT, *attT, *mid;
   float *qkv, *logits;
-  MfmaRes mres;       // workspaces of the MFMA kernels (half-precision path)
+  MfmaRes mres;       // per-block prefill GEMM (half-precision path)
+  // half-precision path, one launch per operator: per level the input of the next norm's GEMM (x * gain, tiled) and the row sums of
+  // squares; attention output and FFN hidden rows (tiled), queries, attention workspace
+  f16_t *xg[3], *attX, *midX;
+  float* ssq[3];
+  float* attn_ws;
+  unsigned* attn_arrived;
+  f16_t *dX, *dmidX;  // draft heads: tiled rows of a grouped GEMM, FFN hidden rows
+  int sp_tiles = 1, hf_tiles[2] = {1, 1};   // row tiles per parameter set: SP heads; HF sets (vertex, coordinate)
   float* stage;       // staging for weight conversion / prefill GEMM output
   size_t stage_elems;
   unsigned char* static_scratch = nullptr;   // this GPU's copy of the file-scope staging array
@@ -286,10 +293,7 @@ void gemm(fm_ctx* c, int epi, const void* X, long ldx, long gsx, const void* W, 
 
 template <typename T>
 void attention(fm_ctx* c, const void* q, const int* limit, int rows, int RPS, const void* Kc, const void* Vc,
-               long seq_stride, int cap, void* out, const int* flag, bool dense = false, int window = 0) {
-  if (mfma_attn_launch<T>(c->mres, q, limit, rows, RPS, Kc, Vc, seq_stride, cap, out, c->D.H, flag, dense, window, c->stream, c->D.hd)) return;
-  // the plain kernel reads row-major caches: only the fp32 path has those
-  if (!std::is_same<T, float>::value) { fail(c, FM_EINVAL, "attention: unsupported row set (%d rows, %d per sequence)", rows, RPS); c->sticky_error = true; return; }
+               long seq_stride, int cap, void* out, const int* flag, int window = 0) {
 #define FM_ATTN(HDV) hipLaunchKernelGGL((k_attn_simple<T, HDV>), dim3(rows, c->D.H), dim3(256), 0, c->stream, (const T*)q, limit, RPS, \
                                         (const T*)Kc, (const T*)Vc, seq_stride, cap, (T*)out, c->D.H, flag, window)
   if (c->D.hd == 64) FM_ATTN(64); else if (c->D.hd == 96) FM_ATTN(96); else FM_ATTN(128);
@@ -303,19 +307,11 @@ void rmsnorm(fm_ctx* c, const float* src, const float* const* srcptr, const floa
                      c->D.d, c->cfg.rms_eps, flag);
 }
 
-// Y = RMSNorm(h; gain) W^T for the rows of the fp32 residual stream h [rows, d].  Half-precision path: one fused
-// launch (the GEMM normalises on the fly); fp32 path: norm into `xn`, then the plain GEMM.
+// Y = RMSNorm(h; gain) W^T for the rows of the fp32 residual stream h [rows, d]: norm into `xn`, then the GEMM
 template <typename T>
 void gemm_norm(fm_ctx* c, int epi, const float* h, const float* gain, const void* W, void* Y, long ldy, int rows, int N,
                const int* flag) {
   const int d = c->D.d;
-  if (std::is_same<T, f16_t>::value) {
-    GemmArgs a{h, d, 0, W, 0, Y, ldy, 0, nullptr, 0, 0, rows, N, d, flag, gain, c->cfg.rms_eps, nullptr, nullptr, 0, nullptr, nullptr, 0, 0, 0};
-    if (mfma_gemm_launch<T>(c->mres, a, epi, 1, c->stream)) return;
-    fail(c, FM_EINVAL, "gemm_norm: unsupported shape M=%d N=%d K=%d", rows, N, d);
-    c->sticky_error = true;
-    return;
-  }
   rmsnorm<T>(c, h, nullptr, gain, 0, c->xn, nullptr, rows, flag);
   gemm<T>(c, epi, c->xn, d, 0, W, 0, Y, ldy, 0, nullptr, 0, 0, rows, N, d, 1, flag);
 }
@@ -324,17 +320,10 @@ void gemm_norm(fm_ctx* c, int epi, const float* h, const float* gain, const void
 template <typename T>
 void rope_append(fm_ctx* c, const float* qkv, long ldq, const float2* cs, const int* pos, int rows, int RPS, void* q,
                  void* Kc, void* Vc, int cap, const int* flag) {
-  if (std::is_same<T, f16_t>::value) {
-#define FM_ROPEH(HDV) hipLaunchKernelGGL((k_rope_append_h<HDV>), dim3(rows), dim3(256), 0, c->stream, qkv, ldq, cs, pos, RPS, (f16_t*)q, \
-                                         (f16_t*)Kc, (f16_t*)Vc, c->D.H, (cap + 31) / 32, flag)
-    if (c->D.hd == 64) FM_ROPEH(64); else if (c->D.hd == 96) FM_ROPEH(96); else FM_ROPEH(128);
-#undef FM_ROPEH
-  } else {
-#define FM_ROPE(HDV) hipLaunchKernelGGL((k_rope_append<float, HDV>), dim3(rows), dim3(256), 0, c->stream, qkv, ldq, cs, pos, RPS, (float*)q, \
-                                        (float*)Kc, (float*)Vc, c->D.H, cap, flag)
-    if (c->D.hd == 64) FM_ROPE(64); else if (c->D.hd == 96) FM_ROPE(96); else FM_ROPE(128);
+#define FM_ROPE(HDV) hipLaunchKernelGGL((k_rope_append<T, HDV>), dim3(rows), dim3(256), 0, c->stream, qkv, ldq, cs, pos, RPS, (T*)q, \
+                                        (T*)Kc, (T*)Vc, c->D.H, cap, flag)
+  if (c->D.hd == 64) FM_ROPE(64); else if (c->D.hd == 96) FM_ROPE(96); else FM_ROPE(128);
 #undef FM_ROPE
-  }
 }
 
 // elements of one (sequence) slice of a K or V cache with `cap` key positions
@@ -351,21 +340,13 @@ void run_block(fm_ctx* c, const Layer& L, int level) {
   const int cap = level_cap(c, level);
   float* h = c->h[level];
   const int* flag = c->st.alive;
-  if (std::is_same<T, f16_t>::value && D.hd == 64) {
-    // norm1, fused q,k,v projection, rotary, q out and cache append in one launch (written for 64-wide heads; the
-    // wider heads of the paper's own shapes take the two launches below)
-    GemmArgs a{h, d, 0, L.wqkv, 0, c->qT, d, 0, nullptr, 0, 0, rows, 3 * d, d, flag, L.g1, c->cfg.rms_eps,
-               c->cs[level], c->pos[level], RPS, L.Kc, L.Vc, (long)cache_seq_elems(c, cap), (cap + 31) / 32, D.H};
-    if (!mfma_gemm_launch<T>(c->mres, a, EPI_QKV, 1, c->stream)) { fail(c, FM_EINVAL, "qkv: unsupported shape"); c->sticky_error = true; }
-  } else {
-    gemm_norm<T>(c, EPI_F32, h, L.g1, L.wqkv, c->qkv, 3 * d, rows, 3 * d, flag);
-    rope_append<T>(c, c->qkv, (long)3 * d, c->cs[level], c->pos[level], rows, RPS, c->qT, L.Kc, L.Vc, cap, flag);
-  }
-  attention<T>(c, c->qT, c->pos[level], rows, RPS, L.Kc, L.Vc, (long)cache_seq_elems(c, cap), cap, c->attT, flag, false,
+  gemm_norm<T>(c, EPI_F32, h, L.g1, L.wqkv, c->qkv, 3 * d, rows, 3 * d, flag);
+  rope_append<T>(c, c->qkv, (long)3 * d, c->cs[level], c->pos[level], rows, RPS, c->qT, L.Kc, L.Vc, cap, flag);
+  attention<T>(c, c->qT, c->pos[level], rows, RPS, L.Kc, L.Vc, (long)cache_seq_elems(c, cap), cap, c->attT, flag,
                level_window(c, level));
   gemm<T>(c, EPI_F32, c->attT, d, 0, L.wo, 0, h, d, 0, h, d, 0, rows, d, d, 1, flag);
   gemm_norm<T>(c, EPI_T, h, L.g2, L.cq, c->qT, d, rows, d, flag);
-  attention<T>(c, c->qT, c->limx[level], rows, RPS, L.Km, L.Vm, (long)cache_seq_elems(c, D.M), D.M, c->attT, flag, true);
+  attention<T>(c, c->qT, c->limx[level], rows, RPS, L.Km, L.Vm, (long)cache_seq_elems(c, D.M), D.M, c->attT, flag);
   gemm<T>(c, EPI_F32, c->attT, d, 0, L.co, 0, h, d, 0, h, d, 0, rows, d, d, 1, flag);
   gemm_norm<T>(c, EPI_GELU_T, h, L.g3, L.w1, c->mid, c->ff, rows, c->ff, flag);
   gemm<T>(c, EPI_F32, c->mid, c->ff, 0, L.w2, 0, h, d, 0, h, d, 0, rows, d, c->ff, 1, flag);
@@ -406,23 +387,19 @@ void choose_and_accept(fm_ctx* c, const float* logits, int32_t* accepted) {
 }
 
 template <typename T>
+void verify_setup(fm_ctx* c, const int32_t* block_tok, const int32_t* block_len, bool embed) {
+  const Dims& D = c->D;
+  const bool half = std::is_same<T, f16_t>::value;
+  hipLaunchKernelGGL((k_verify_setup<T>), dim3(c->Rc + c->Rv + c->Rf), dim3(256), 0, c->stream, c->st, D, c->inv, block_tok, block_len,
+                     c->pos[0], c->pos[1], c->pos[2], c->limx[0], c->limx[1], c->limx[2], c->cs[0], c->cs[1], c->cs[2], c->persist ? c->pk_epoch : nullptr,
+                     embed ? (const T*)c->emb : nullptr, c->h[0], half ? c->xg[0] : nullptr, half ? c->stacks[0][0].g1 : nullptr, half ? c->ssq[0] : nullptr);
+}
+
+template <typename T>
 int verify_impl(fm_ctx* c, const int32_t* block_tok, const int32_t* block_len, float* logits_out, int32_t* accepted) {
   const Dims& D = c->D;
   const int d = D.d;
-  hipLaunchKernelGGL(k_verify_setup, dim3(std::min(16, (D.S * D.Bm * (D.hd / 2) + 255) / 256)), dim3(256), 0, c->stream, c->st, D, c->inv, block_tok, block_len,
-                     c->pos[0], c->pos[1], c->pos[2], c->limx[0], c->limx[1], c->limx[2], c->cs[0], c->cs[1], c->cs[2], c->persist ? c->pk_epoch : nullptr);
-  if (c->persist) {
-    // the whole backbone forward in one launch (see fm_kernels_persist.h), then greedy choice and acceptance
-    float* lgp = logits_out ? logits_out : c->logits;
-    c->pk.logits = lgp;
-    if (c->pk.RS == 32) hipLaunchKernelGGL(k_verify_persist<2>, dim3(PK_NWG), dim3(256), c->pk_lds, c->stream, c->pk);
-    else hipLaunchKernelGGL(k_verify_persist<1>, dim3(PK_NWG), dim3(256), c->pk_lds, c->stream, c->pk);
-    choose_and_accept(c, lgp, accepted);
-    HIPCHK(c, hipGetLastError());
-    return FM_OK;
-  }
-  hipLaunchKernelGGL((k_embed<T>), dim3(c->Rc), dim3(256), 0, c->stream, c->st.vtok, c->pos[0], (const T*)c->emb,
-                     c->h[0], d);
+  verify_setup<T>(c, block_tok, block_len, true);
   const int* flag = c->st.alive;
   // coordinate level, first half
   run_stack<T>(c, 0, nullptr, 0);
@@ -464,53 +441,221 @@ void run_sp(fm_ctx* c, int set, const SpLevel& sp, const Layer& last, int level,
   rmsnorm<T>(c, nullptr, c->dr.src[set], sp.g, G, c->dxn, c->dkeep, rows, flag);
   gemm<T>(c, EPI_F32, c->dxn, (long)G * d, d, sp.wq, dd, c->dtmp, (long)G * d, d, nullptr, 0, 0, D.S, d, d, G, flag);
   rope_append<T>(c, c->dtmp, (long)d, c->dr.cs[set], c->dr.pos[set], rows, G, c->dq, nullptr, nullptr, cap, flag);
-  attention<T>(c, c->dq, c->dr.lim[set], rows, G, last.Kc, last.Vc, (long)cache_seq_elems(c, cap), cap, c->datt, flag, false,
+  attention<T>(c, c->dq, c->dr.lim[set], rows, G, last.Kc, last.Vc, (long)cache_seq_elems(c, cap), cap, c->datt, flag,
                level_window(c, level));
   gemm<T>(c, EPI_T, c->datt, (long)G * d, d, sp.wo, dd, c->dxn, (long)G * d, d, nullptr, 0, 0, D.S, d, d, G, flag);
   gemm<T>(c, EPI_T, c->dxn, (long)G * d, d, sp.cq, dd, c->dq, (long)G * d, d, nullptr, 0, 0, D.S, d, d, G, flag);
-  attention<T>(c, c->dq, c->dr.limx[set], rows, G, last.Km, last.Vm, (long)cache_seq_elems(c, D.M), D.M, c->datt, flag, true);
+  attention<T>(c, c->dq, c->dr.limx[set], rows, G, last.Km, last.Vm, (long)cache_seq_elems(c, D.M), D.M, c->datt, flag);
   gemm<T>(c, EPI_T, c->datt, (long)G * d, d, sp.co, dd, c->dxn, (long)G * d, d, nullptr, 0, 0, D.S, d, d, G, flag);
   gemm<T>(c, EPI_F32, c->dxn, (long)G * d, d, sp.lin, dd, out, ldo, gso, c->dkeep, (long)G * d, d, D.S, d, d, G, flag);
 }
 
-// The SP chains (Eq. 1) of all three levels as one chain of grouped launches (half path): the row set is, per sequence,
-// the point-, face- and coordinate-level rows behind each other, every GEMM is grouped over all heads (S rows per head),
-// and the two attention launches take one cache per level.  Same arithmetic per row as run_sp.  Rows of a level that
-// does not fire in this step carry limit -1 (no keys) and produce values nobody reads.
+// ------------------------------------------------------------------------------------------
+// Half-precision path, one launch per operator (fm_kernels_decode.h)
+// ------------------------------------------------------------------------------------------
+int level_rows(const fm_ctx* c, int level) { return level == 0 ? c->Rc : level == 1 ? c->Rv : c->Rf; }
+int level_rps(const fm_ctx* c, int level) { return level == 0 ? c->D.Bm : level == 1 ? c->D.VB : c->D.FB; }
+
+void refuse(fm_ctx* c, const char* what) { fail(c, FM_EINVAL, "%s: unsupported row set", what); c->sticky_error = true; }
+
+// one transformer block on the row set of `level` (Sec. 3.1: self-attention, cross-attention to c, FFN).  next_gain: gain of
+// the norm behind the block (null: none reads its output).  tap / ring: rings that receive the block's input / output rows.
+void run_block_h(fm_ctx* c, const Layer& L, int level, const float* next_gain, float* tap, float* ring, int rs) {
+  const Dims& D = c->D;
+  const int d = D.d, rows = level_rows(c, level), RPS = level_rps(c, level), cap = level_cap(c, level);
+  const int* flag = c->st.alive;
+  DecGemm b{};                       // what all GEMMs of the block share
+  b.M = rows; b.run_flag = flag; b.eps = c->cfg.rms_eps; b.RPS = RPS; b.H = D.H; b.hd = D.hd;
+  auto normed = [&](const void* W, int N) {
+    DecGemm a = b;
+    a.A = c->xg[level]; a.W = (const f16_t*)W; a.N = N; a.KT = d / 32; a.ssq = c->ssq[level]; a.inv_k = 1.0f / d;
+    return a;
+  };
+  auto residual = [&](const f16_t* X, const void* W, int K, const float* gain) {
+    DecGemm a = b;
+    a.A = X; a.W = (const f16_t*)W; a.N = d; a.KT = K / 32;
+    a.Y = c->h[level]; a.ldy = d; a.R = c->h[level]; a.ldr = d;
+    a.gain = gain; a.X = gain ? c->xg[level] : nullptr; a.ssq_out = gain ? c->ssq[level] : nullptr;
+    return a;
+  };
+  auto attn = [&](const int* limit, void* K, void* V, int kcap, int window) {
+    AttnArgs t{};
+    t.S = D.S; t.H = D.H; t.ws = c->attn_ws; t.arrived = c->attn_arrived; t.run_flag = flag;
+    t.set[0] = AttnSet{(const f16_t*)c->qT, limit, RPS, 0, RPS, (const f16_t*)K, (const f16_t*)V, (long)cache_seq_elems(c, kcap), (kcap + 31) / 32, window, 1,
+                       RowMap{1, RPS, 0, 0}, c->attX};
+    if (!dec_attention(t, 1, D.hd, c->stream)) refuse(c, "attention");
+  };
+  {
+    DecGemm a = normed(L.wqkv, 3 * d);
+    a.Y = c->qT; a.ldy = d; a.cs = c->cs[level]; a.pos = c->pos[level];
+    a.Kc = (f16_t*)L.Kc; a.Vc = (f16_t*)L.Vc; a.seq_stride = (long)cache_seq_elems(c, cap); a.capb = (cap + 31) / 32;
+    dec_gemm<DE_QKV, true>(a, 1, c->stream);
+  }
+  attn(c->pos[level], L.Kc, L.Vc, cap, level_window(c, level));
+  {
+    DecGemm a = residual(c->attX, L.wo, d, L.g2);
+    if (tap) { a.tap = tap; a.pos = c->pos[level]; a.rs = rs; }
+    dec_gemm<DE_RES, false>(a, 1, c->stream);
+  }
+  {
+    DecGemm a = normed(L.cq, d);
+    a.Y = c->qT; a.ldy = d;
+    dec_gemm<DE_ROW, true>(a, 1, c->stream);
+  }
+  attn(c->limx[level], L.Km, L.Vm, D.M, 0);
+  dec_gemm<DE_RES, false>(residual(c->attX, L.co, d, L.g3), 1, c->stream);
+  {
+    DecGemm a = normed(L.w1, c->ff);
+    a.X = c->midX;
+    dec_gemm<DE_GELU, true>(a, 1, c->stream);
+  }
+  {
+    DecGemm a = residual(c->midX, L.w2, c->ff, next_gain);
+    if (ring) { a.ring = ring; a.pos = c->pos[level]; a.rs = rs; }
+    dec_gemm<DE_RES, false>(a, 1, c->stream);
+  }
+}
+
+// The backbone forward of a pass whose rows k_verify_setup has prepared (embedded rows in h[0], xg[0], ssq[0]).
+void forward_h(fm_ctx* c, float* logits) {
+  const Dims& D = c->D;
+  const int d = D.d;
+  float* tap[5] = {nullptr, nullptr, c->tap_f, c->tap_v, c->tap_c};
+  float* ring[5] = {c->ring_hc, c->ring_hv, c->ring_yf, c->ring_yv, nullptr};
+  const int rsz[3] = {RS_C, RS_V, RS_F};
+  for (int st = 0; st < 5; st++) {
+    const int level = kStackLevel[st];
+    const size_t n = c->stacks[st].size();
+    for (size_t i = 0; i < n; i++) {
+      const bool last = i + 1 == n;
+      const float* gain = !last ? c->stacks[st][i + 1].g1 : st == 4 ? c->gf : nullptr;
+      run_block_h(c, c->stacks[st][i], level, gain, last ? tap[st] : nullptr, last ? ring[st] : nullptr, rsz[level]);
+    }
+    if (st < 2) {          // shorten onto the next coarser level
+      const int cl = st + 1;
+      hipLaunchKernelGGL(k_dec_pool3, dim3(level_rows(c, cl)), dim3(256), 0, c->stream, ring[st], rsz[level], c->pos[cl], level_rps(c, cl), c->attX, d);
+      DecGemm a{};
+      a.A = c->attX; a.W = (const f16_t*)(st == 0 ? c->short_cv : c->short_vf); a.M = level_rows(c, cl); a.N = d; a.KT = d / 32; a.run_flag = c->st.alive;
+      a.Y = c->h[cl]; a.ldy = d; a.X = c->xg[cl]; a.gain = c->stacks[st + 1][0].g1; a.ssq_out = c->ssq[cl];
+      dec_gemm<DE_RES, false>(a, 1, c->stream);
+    } else if (st < 4) {   // upsample onto the next finer level (repeat + skip)
+      const int fl = level - 1;
+      hipLaunchKernelGGL(k_dec_upsample, dim3(level_rows(c, fl)), dim3(256), 0, c->stream, c->h[fl], c->pos[fl], level_rps(c, fl), ring[st], rsz[level], d,
+                         c->xg[fl], c->stacks[st + 1][0].g1, c->ssq[fl]);
+    }
+  }
+  DecGemm a{};
+  a.A = c->xg[0]; a.W = (const f16_t*)c->lm; a.M = c->Rc; a.N = D.V; a.KT = d / 32; a.ssq = c->ssq[0]; a.inv_k = 1.0f / d; a.eps = c->cfg.rms_eps;
+  a.run_flag = c->st.alive; a.Y = logits; a.ldy = D.V;
+  dec_gemm<DE_F32, true>(a, 1, c->stream);
+}
+
+int verify_half(fm_ctx* c, const int32_t* block_tok, const int32_t* block_len, float* logits_out, int32_t* accepted) {
+  float* lg = logits_out ? logits_out : c->logits;
+  verify_setup<f16_t>(c, block_tok, block_len, !c->persist);
+  if (c->persist) {
+    // the whole backbone forward in one launch (see fm_kernels_persist.h)
+    c->pk.logits = lg;
+    if (c->pk.RS == 32) hipLaunchKernelGGL(k_verify_persist<2>, dim3(PK_NWG), dim3(256), c->pk_lds, c->stream, c->pk);
+    else hipLaunchKernelGGL(k_verify_persist<1>, dim3(PK_NWG), dim3(256), c->pk_lds, c->stream, c->pk);
+  } else {
+    forward_h(c, lg);
+  }
+  choose_and_accept(c, lg, accepted);      // greedy choice (or sampled) and acceptance
+  HIPCHK(c, hipGetLastError());
+  return FM_OK;
+}
+
+// Query projection of draft rows: grouped GEMM over `G` sets of `M` rows each with the rotation applied, row (set g, m) -> m * G + g
+void draft_query(fm_ctx* c, const void* W, int M, int G, int tiles, const float2* cs, const int* flag) {
+  const int d = c->D.d;
+  DecGemm a{};
+  a.A = c->dX; a.gsa = (long)tiles * 16 * d; a.W = (const f16_t*)W; a.gsw = (long)d * d; a.M = M; a.N = d; a.KT = d / 32; a.run_flag = flag;
+  a.Y = c->dq; a.ldy = (long)G * d; a.gsy = d; a.cs = cs; a.ldc = G; a.hd = c->D.hd; a.H = c->D.H;
+  dec_gemm<DE_ROPE, false>(a, G, c->stream);
+}
+
+// The SP chains (Eq. 1) of all three levels as one chain of grouped launches: the row set is, per sequence, the point-,
+// face- and coordinate-level rows behind each other, every GEMM is grouped over all heads (S rows per head), and the
+// two attention launches take one cache per level.  Rows of a level that does not fire in this step carry limit -1 (no
+// keys) and produce values nobody reads.
 void run_sp_all(fm_ctx* c, const int* flag) {
-  typedef f16_t T;
   const Dims& D = c->D;
   const SpLevel& A = c->sp_all;
   const int d = D.d, G = A.cnt, S = D.S, rows = S * G;
   if (G == 0) return;
-  const long dd = (long)d * d, ld = (long)G * d;
-  const int nrow[3] = {D.nspv, D.nspf, D.Dc}, lev[3] = {1, 2, 0}, set[3] = {1, 2, 0};
+  const RowMap rm{G, 1, 0, c->sp_tiles};
+  const int nrow[3] = {D.nspv, D.nspf, D.Dc}, lev[3] = {1, 2, 0};
   const Layer* last[3] = {&c->stacks[3].back(), &c->stacks[2].back(), &c->stacks[4].back()};
-  rmsnorm<T>(c, nullptr, c->dr.src[1], A.g, G, c->dxn, c->dkeep, rows, flag);
-  gemm<T>(c, EPI_F32, c->dxn, ld, d, A.wq, dd, c->dtmp, ld, d, nullptr, 0, 0, S, d, d, G, flag);
-  rope_append<T>(c, c->dtmp, (long)d, c->dr.cs[1], c->dr.pos[1], rows, G, c->dq, nullptr, nullptr, 32, flag);
-  AttnLevelHost lv[3];
-  long off = 0;
-  for (int z = 0; z < 3; z++) {
-    const int cap = level_cap(c, lev[z]);
-    lv[z] = AttnLevelHost{(const f16_t*)c->dq + off * d, c->dr.lim[set[z]], nrow[z], last[z]->Kc, last[z]->Vc,
-                          (long)cache_seq_elems(c, cap), cap, (f16_t*)c->datt + off * d, false, level_window(c, lev[z])};
-    off += nrow[z];
-  }
-  if (!mfma_attn_launch_levels(c->mres, lv, S, G, D.H, flag, c->stream)) { fail(c, FM_EINVAL, "merged SP attention: unsupported row sets"); c->sticky_error = true; return; }
-  gemm<T>(c, EPI_T, c->datt, ld, d, A.wo, dd, c->dxn, ld, d, nullptr, 0, 0, S, d, d, G, flag);
-  gemm<T>(c, EPI_T, c->dxn, ld, d, A.cq, dd, c->dq, ld, d, nullptr, 0, 0, S, d, d, G, flag);
-  off = 0;
-  for (int z = 0; z < 3; z++) {
-    lv[z] = AttnLevelHost{(const f16_t*)c->dq + off * d, c->dr.limx[set[z]], nrow[z], last[z]->Km, last[z]->Vm,
-                          (long)cache_seq_elems(c, D.M), D.M, (f16_t*)c->datt + off * d, true, 0};
-    off += nrow[z];
-  }
-  if (!mfma_attn_launch_levels(c->mres, lv, S, G, D.H, flag, c->stream)) { fail(c, FM_EINVAL, "merged SP cross-attention: unsupported row sets"); c->sticky_error = true; return; }
-  gemm<T>(c, EPI_T, c->datt, ld, d, A.co, dd, c->dxn, ld, d, nullptr, 0, 0, S, d, d, G, flag);
+  auto attn = [&](const int* limit, bool cross) {
+    AttnArgs t{};
+    t.S = S; t.H = D.H; t.ws = c->attn_ws; t.arrived = c->attn_arrived; t.run_flag = flag;
+    int n = 0, q0 = 0;
+    for (int z = 0; z < 3; z++) {
+      const int cap = cross ? D.M : level_cap(c, lev[z]);
+      if (nrow[z] > 0)
+        t.set[n++] = AttnSet{(const f16_t*)c->dq, limit, nrow[z], q0, G, (const f16_t*)(cross ? last[z]->Km : last[z]->Kc), (const f16_t*)(cross ? last[z]->Vm : last[z]->Vc),
+                             (long)cache_seq_elems(c, cap), (cap + 31) / 32, cross ? 0 : level_window(c, lev[z]), 1, rm, c->dX};
+      q0 += nrow[z];
+    }
+    if (!dec_attention(t, n, D.hd, c->stream)) refuse(c, "SP attention");
+  };
+  DecGemm g{};
+  g.A = c->dX; g.gsa = (long)c->sp_tiles * 16 * d; g.gsw = (long)d * d; g.M = S; g.N = d; g.KT = d / 32; g.run_flag = flag;
+  hipLaunchKernelGGL(k_dec_rmsnorm, dim3(rows), dim3(256), 0, c->stream, c->dr.src[1], A.g, G, c->dX, rm, G, c->dkeep, d, c->cfg.rms_eps, flag);
+  draft_query(c, A.wq, S, G, c->sp_tiles, c->dr.cs[1], flag);
+  attn(c->dr.lim[1], false);
+  // output projection of the self-attention, then straight (no norm, Eq. 1) the cross-attention query
+  DecGemm a = g;
+  a.W = (const f16_t*)A.wo; a.X = c->dmidX; a.gsx = g.gsa;
+  dec_gemm<DE_TILE, false>(a, G, c->stream);
+  a = g;
+  a.A = c->dmidX; a.W = (const f16_t*)A.cq; a.Y = c->dq; a.ldy = (long)G * d; a.gsy = d;
+  dec_gemm<DE_ROW, false>(a, G, c->stream);
+  attn(c->dr.limx[1], true);
+  a = g;
+  a.W = (const f16_t*)A.co; a.X = c->dmidX; a.gsx = g.gsa;
+  dec_gemm<DE_TILE, false>(a, G, c->stream);
   // outputs: per sequence the point, face and coordinate rows behind each other (spv_out, spf_out and the rows the output
   // head's pointer table names)
-  gemm<T>(c, EPI_F32, c->dxn, ld, d, A.lin, dd, c->spv_out, ld, d, c->dkeep, ld, d, S, d, d, G, flag);
+  a = g;
+  a.A = c->dmidX; a.W = (const f16_t*)A.lin; a.Y = c->spv_out; a.ldy = (long)G * d; a.gsy = d; a.R = c->dkeep; a.ldr = (long)G * d; a.gsr = d;
+  dec_gemm<DE_F32, false>(a, G, c->stream);
+}
+
+// HF block chain (Eq. 3-6): row sets 3 (vertex level) and 4 (coordinate level, mult = 2: the point and the face pipeline
+// share the parameter sets)
+void run_hf_h(fm_ctx* c, int set, const HfLevel& hf, int mult, const Layer& last, int level, float* out, const int* flag) {
+  const Dims& D = c->D;
+  const int d = D.d, G = hf.cnt, per_seq = G * mult, rows = D.S * per_seq, Mg = D.S * mult, tiles = c->hf_tiles[set - 3];
+  if (G == 0) return;
+  const RowMap rm{G, mult, 0, tiles};
+  hipLaunchKernelGGL(k_dec_rmsnorm, dim3(rows), dim3(256), 0, c->stream, c->dr.src[set], hf.g, G, c->dX, rm, per_seq, c->dkeep, d, c->cfg.rms_eps, flag);
+  draft_query(c, hf.wq, Mg, G, tiles, c->dr.cs[set], flag);
+  AttnArgs t{};
+  t.S = D.S; t.H = D.H; t.ws = c->attn_ws; t.arrived = c->attn_arrived; t.run_flag = flag;
+  const int cap = level_cap(c, level);
+  int n = 0;
+  for (int q0 = 0; q0 < per_seq; q0 += 32)      // at most 48 rows per sequence: one or two sets
+    t.set[n++] = AttnSet{(const f16_t*)c->dq, c->dr.lim[set], std::min(32, per_seq - q0), q0, per_seq, (const f16_t*)last.Kc, (const f16_t*)last.Vc,
+                         (long)cache_seq_elems(c, cap), (cap + 31) / 32, level_window(c, level), 1, rm, c->dX};
+  if (!dec_attention(t, n, D.hd, c->stream)) refuse(c, "HF attention");
+  DecGemm a{};
+  a.A = c->dX; a.gsa = (long)tiles * 16 * d; a.W = (const f16_t*)hf.w1; a.gsw = (long)d * c->hff; a.M = Mg; a.N = c->hff; a.KT = d / 32; a.run_flag = flag;
+  a.X = c->dmidX; a.gsx = (long)tiles * 16 * c->hff;
+  dec_gemm<DE_GELU, false>(a, G, c->stream);
+  a.A = c->dmidX; a.gsa = a.gsx; a.W = (const f16_t*)hf.w2; a.N = d; a.KT = c->hff / 32; a.X = nullptr;
+  a.Y = out; a.ldy = (long)G * d; a.gsy = d; a.R = c->dkeep; a.ldr = (long)G * d; a.gsr = d;
+  dec_gemm<DE_F32, false>(a, G, c->stream);
+}
+
+// Output head on the draft rows (coordinate SP heads, then the coordinate HF rows)
+void draft_logits_h(fm_ctx* c, int n, const int* flag) {
+  const Dims& D = c->D;
+  hipLaunchKernelGGL(k_dec_rmsnorm, dim3(n), dim3(256), 0, c->stream, c->lm_src, c->gf, 0, c->dX, RowMap{1, 0, 0, 0}, n, (float*)nullptr, D.d, c->cfg.rms_eps, flag);
+  DecGemm a{};
+  a.A = c->dX; a.W = (const f16_t*)c->lm; a.M = n; a.N = D.V; a.KT = D.d / 32; a.run_flag = flag; a.Y = c->dlogits; a.ldy = D.V;
+  dec_gemm<DE_F32, false>(a, 1, c->stream);
 }
 
 // HF block chain (Eq. 3-6) for row set `set`: `per_seq` rows per sequence, `G` parameter sets, `mult`
@@ -527,7 +672,7 @@ void run_hf(fm_ctx* c, int set, const HfLevel& hf, int mult, const Layer& last, 
   rmsnorm<T>(c, nullptr, c->dr.src[set], hf.g, G, c->dxn, c->dkeep, rows, flag);
   gemm<T>(c, EPI_F32, c->dxn, ld, d, hf.wq, dd, c->dtmp, ld, d, nullptr, 0, 0, Mg, d, d, G, flag);
   rope_append<T>(c, c->dtmp, (long)d, c->dr.cs[set], c->dr.pos[set], rows, per_seq, c->dq, nullptr, nullptr, cap, flag);
-  attention<T>(c, c->dq, c->dr.lim[set], rows, per_seq, last.Kc, last.Vc, (long)cache_seq_elems(c, cap), cap, c->datt, flag, false,
+  attention<T>(c, c->dq, c->dr.lim[set], rows, per_seq, last.Kc, last.Vc, (long)cache_seq_elems(c, cap), cap, c->datt, flag,
                level_window(c, level));
   gemm<T>(c, EPI_GELU_T, c->datt, ld, d, hf.w1, dh, c->dmid, (long)G * c->hff, c->hff, nullptr, 0, 0, Mg, c->hff, d, G, flag);
   gemm<T>(c, EPI_F32, c->dmid, (long)G * c->hff, c->hff, hf.w2, dh, out, ld, d, c->dkeep, ld, d, Mg, d, c->hff, G, flag);
@@ -538,13 +683,14 @@ int draft_impl(fm_ctx* c, int32_t* block_tok, int32_t* block_len, int speculativ
   const Dims& D = c->D;
   const int d = D.d;
   if (speculative) {
-    hipLaunchKernelGGL(k_draft_setup, dim3(D.S), dim3(256), 0, c->stream, c->st, D, c->inv, c->dr, c->db);
+    hipLaunchKernelGGL(k_draft_setup, dim3(D.S, (D.Dc + D.nspv + D.nspf + D.nhfv + 2 * D.nhfc + 7) / 8 + (D.Dc + D.nspv + D.nspf + D.nhfv + 2 * D.nhfc == 0)), dim3(256), 0, c->stream, c->st, D, c->inv, c->dr, c->db);
     const int *f_alive = c->dr.flags, *f_v = c->dr.flags + 1, *f_f = c->dr.flags + 2;
     const Layer& lastc = c->stacks[4].back();
     const Layer& lastv = c->stacks[3].back();
     const Layer& lastf = c->stacks[2].back();
     const int nLM = D.S * (D.Dc + 2 * D.nhfc);
-    if (std::is_same<T, f16_t>::value && c->sp_merged) {
+    constexpr bool half = std::is_same<T, f16_t>::value;
+    if constexpr (half) {
       run_sp_all(c, f_alive);
     } else {
       // coordinate level: SP heads straight to the output head
@@ -554,14 +700,20 @@ int draft_impl(fm_ctx* c, int32_t* block_tok, int32_t* block_len, int speculativ
       // face level: SP heads on the face feature, vertex-level HF, then coordinate HF rows of pipe 1
       run_sp<T>(c, 2, c->sp[2], lastf, 2, c->spf_out, (long)D.nspf * d, d, f_f);
     }
-    run_hf<T>(c, 3, c->hfv, 1, lastv, 1, c->hfv_out, f_f);
+    if constexpr (half) run_hf_h(c, 3, c->hfv, 1, lastv, 1, c->hfv_out, f_f);
+    else run_hf<T>(c, 3, c->hfv, 1, lastv, 1, c->hfv_out, f_f);
     if (c->correct_hist > 0 && D.nspv + D.nhfv > 0)     // label rows of the point-level features (Sec. 3.2)
       hipLaunchKernelGGL(k_label_rows, dim3(D.S * (D.nspv + D.nhfv)), dim3(64), 0, c->stream, D, c->dr, c->spv_out, c->db.spv_rs, c->hfv_out,
                          c->label_w, c->lab_v, c->lab_f);
-    run_hf<T>(c, 4, c->hfc, 2, lastc, 0, c->dh + (long)D.S * D.Dc * d, f_alive);
+    float* hfc_out = c->dh + (long)D.S * D.Dc * d;
+    if constexpr (half) run_hf_h(c, 4, c->hfc, 2, lastc, 0, hfc_out, f_alive);
+    else run_hf<T>(c, 4, c->hfc, 2, lastc, 0, hfc_out, f_alive);
     if (nLM > 0) {
-      rmsnorm<T>(c, nullptr, c->lm_src, c->gf, 0, c->dxn, nullptr, nLM, f_alive);
-      gemm<T>(c, EPI_F32, c->dxn, d, 0, c->lm, 0, c->dlogits, D.V, 0, nullptr, 0, 0, nLM, D.V, d, 1, f_alive);
+      if constexpr (half) draft_logits_h(c, nLM, f_alive);
+      else {
+        rmsnorm<T>(c, nullptr, c->lm_src, c->gf, 0, c->dxn, nullptr, nLM, f_alive);
+        gemm<T>(c, EPI_F32, c->dxn, d, 0, c->lm, 0, c->dlogits, D.V, 0, nullptr, 0, 0, nLM, D.V, d, 1, f_alive);
+      }
       hipLaunchKernelGGL(k_dist_store, dim3(nLM), dim3(256), 0, c->stream, c->dlogits, D, c->dr, c->dist_c, c->dist_v,
                          c->dist_f);
     }
@@ -576,7 +728,7 @@ int draft_any(fm_ctx* c, int32_t* block_tok, int32_t* block_len, int speculative
   return c->bf16 ? draft_impl<f16_t>(c, block_tok, block_len, speculative) : draft_impl<float>(c, block_tok, block_len, speculative);
 }
 int verify_any(fm_ctx* c, const int32_t* block_tok, const int32_t* block_len, float* logits, int32_t* accepted) {
-  return c->bf16 ? verify_impl<f16_t>(c, block_tok, block_len, logits, accepted) : verify_impl<float>(c, block_tok, block_len, logits, accepted);
+  return c->bf16 ? verify_half(c, block_tok, block_len, logits, accepted) : verify_impl<float>(c, block_tok, block_len, logits, accepted);
 }
 // settings that decide which launches a step consists of
 int step_flags(const fm_ctx* c, int speculative) {
@@ -609,7 +761,7 @@ int prefill_impl(fm_ctx* c, int seq, const float* mem_dev, void* stage_area) {
   if (std::is_same<T, f16_t>::value && c->pf_layers) {
     // memory -> MFMA fragment order (the same tiling as a weight matrix), then one launch for all blocks
     f16_t* Xt = (f16_t*)stage_area;
-    hipLaunchKernelGGL(k_tile_weight, dim3(1024), dim3(256), 0, c->stream, mem_dev, Xt, D.M, d, D.M, 0);
+    hipLaunchKernelGGL(k_tile_weight, dim3(1024), dim3(256), 0, c->stream, mem_dev, Xt, D.M, d, D.M, 0, D.hd);
 #define FM_PREFILL(HDV) hipLaunchKernelGGL((k_prefill_kv<HDV>), dim3(c->pf_grid), dim3(256), PF_LDS_BYTES, c->stream, (const f16_t*)Xt, \
                                            (const PrefillLayer*)c->pf_layers, (long)((size_t)seq * cache_seq_elems(c, D.M)), d / 32, d, D.M, c->pf_n)
     if (D.hd == 64) FM_PREFILL(64); else if (D.hd == 96) FM_PREFILL(96); else FM_PREFILL(128);
@@ -667,7 +819,8 @@ int build_params(fm_ctx* c) {
   const size_t d = D.d, ff = c->ff, hff = c->hff, V = D.V;
   size_t off = 0;
   auto item = [&](void* dst, size_t n, bool f32) { c->items.push_back({off, n, dst, f32, 0, 0, 0}); off += n; };
-  auto lin = [&](void* dst, size_t N, size_t K) { c->items.push_back({off, N * K, dst, false, (int)N, (int)K, 0}); off += N * K; };
+  // rope: leading rows that belong to queries or keys (half path: rotary pairs meet in one tile, see k_tile_weight)
+  auto lin = [&](void* dst, size_t N, size_t K, size_t rope = 0) { c->items.push_back({off, N * K, dst, false, (int)N, (int)K, (int)rope}); off += N * K; };
   auto at = [&](void* base, size_t elems) { return (void*)((uint8_t*)base + elems * c->esz); };
 
   TRY(dalloc_t(c, &c->emb, V * d));
@@ -686,15 +839,7 @@ int build_params(fm_ctx* c) {
       TRY(dalloc_t(c, &L.Kc, D.S * cache_seq_elems(c, cap))); TRY(dalloc_t(c, &L.Vc, D.S * cache_seq_elems(c, cap)));
       TRY(dalloc_t(c, &L.Km, D.S * cache_seq_elems(c, D.M))); TRY(dalloc_t(c, &L.Vm, D.S * cache_seq_elems(c, D.M)));
       item(L.g1, d, true);
-      if (c->bf16 && D.hd == 64) {
-        // half path: the q and k tiles of the fused projection hold whole rotary pairs (both verify paths apply
-        // the rotation in the GEMM epilogue), so only the permuted tiling is kept
-        c->items.push_back({off, 3 * d * d, L.wqkv, false, (int)(3 * d), (int)d, (int)d});
-        L.wqkv_rp = L.wqkv;
-        off += 3 * d * d;
-      } else {
-        lin(L.wqkv, 3 * d, d);   // wq, wk, wv are consecutive in the blob
-      }
+      lin(L.wqkv, 3 * d, d, 2 * d);   // wq, wk, wv are consecutive in the blob
       lin(L.wo, d, d);
       item(L.g2, d, true);
       lin(L.cq, d, d);
@@ -734,7 +879,7 @@ int build_params(fm_ctx* c) {
     const size_t n = s.cnt;
     for (size_t k = 0; k < n; k++) {
       item(s.g + k * d, d, true);
-      lin(at(s.wq, k * d * d), d, d); lin(at(s.wo, k * d * d), d, d);
+      lin(at(s.wq, k * d * d), d, d, d); lin(at(s.wo, k * d * d), d, d);
       lin(at(s.cq, k * d * d), d, d); lin(at(s.co, k * d * d), d, d);
       lin(at(s.lin, k * d * d), d, d);
     }
@@ -749,7 +894,7 @@ int build_params(fm_ctx* c) {
     TRY(dalloc_t(c, &h.wq, n * d * d)); TRY(dalloc_t(c, &h.w1, n * hff * d)); TRY(dalloc_t(c, &h.w2, n * d * hff));
     for (size_t k = 0; k < n; k++) {
       item(h.g + k * d, d, true);
-      lin(at(h.wq, k * d * d), d, d);
+      lin(at(h.wq, k * d * d), d, d, d);
       lin(at(h.w1, k * hff * d), hff, d);
       lin(at(h.w2, k * d * hff), d, hff);
     }
@@ -775,7 +920,7 @@ int build_persist(fm_ctx* c) {
       const Layer& L = c->stacks[st][i];
       PkLayer p{};
       p.g1 = (pk_cf_t)L.g1; p.g2 = (pk_cf_t)L.g2; p.g3 = (pk_cf_t)L.g3;
-      p.wqkv = (pk_cw_t)L.wqkv_rp; p.wo = (pk_cw_t)L.wo; p.cq = (pk_cw_t)L.cq; p.co = (pk_cw_t)L.co;
+      p.wqkv = (pk_cw_t)L.wqkv; p.wo = (pk_cw_t)L.wo; p.cq = (pk_cw_t)L.cq; p.co = (pk_cw_t)L.co;
       p.w1 = (pk_cw_t)L.w1; p.w2 = (pk_cw_t)L.w2;
       p.Kc = (pk_w_t)L.Kc; p.Vc = (pk_w_t)L.Vc; p.Km = (pk_cw_t)L.Km; p.Vm = (pk_cw_t)L.Vm;
       p.level = L.level;
@@ -870,6 +1015,16 @@ int build_buffers(fm_ctx* c) {
   for (int l = 0; l < 3; l++) {
     TRY(dalloc(c, &c->pos[l], rows[l])); TRY(dalloc(c, &c->limx[l], rows[l]));
     TRY(dalloc(c, &c->cs[l], rows[l] * 64)); TRY(dalloc(c, &c->h[l], rows[l] * d));
+    if (c->bf16) {
+      const size_t tiles = (rows[l] + 15) / 16;
+      TRY(dalloc(c, &c->xg[l], tiles * 16 * d)); TRY(dalloc(c, &c->ssq[l], tiles * d));
+    }
+  }
+  if (c->bf16) {
+    const size_t tiles = (rows[0] + 15) / 16;
+    TRY(dalloc(c, &c->attX, tiles * 16 * d)); TRY(dalloc(c, &c->midX, tiles * 16 * c->ff));
+    TRY(dalloc(c, &c->attn_arrived, (size_t)FM_ATTN_SETS * D.S * D.H));
+    TRY(dalloc(c, &c->attn_ws, attn_ws_floats(D.H, D.S, FM_ATTN_SETS, D.hd)));
   }
   TRY(dalloc_t(c, &c->xn, rows[0] * d)); TRY(dalloc_t(c, &c->qT, rows[0] * d)); TRY(dalloc_t(c, &c->attT, rows[0] * d));
   TRY(dalloc_t(c, &c->mid, rows[0] * c->ff));
@@ -889,8 +1044,6 @@ int build_buffers(fm_ctx* c) {
     TRY(dalloc(c, &c->dr.lim[i], nset[i])); TRY(dalloc(c, &c->dr.limx[i], nset[i]));
     TRY(dalloc(c, &c->dr.cs[i], nset[i] * 64));
   }
-  const char* spm = getenv("FM_SP_MERGED");      // "0": one chain of launches per level
-  c->sp_merged = c->bf16 && D.hd == 64 && D.Dc <= 16 && D.nspv <= 16 && D.nspf <= 16 && !(spm && spm[0] == '0');
   const int G_all = D.Dc + D.nspv + D.nspf;
   {
     // One table for the three SP row sets.  Merged chain: rows [sequence][point heads | face heads | coordinate heads],
@@ -905,8 +1058,8 @@ int build_buffers(fm_ctx* c) {
     const int cnt[5] = {D.Dc, D.nspv, D.nspf, D.nhfv, 2 * D.nhfc};
     for (int i = 0; i < 5; i++) c->dr.rs[i] = cnt[i];
     for (int i = 0; i < 3; i++) {
-      const size_t first = c->sp_merged ? first_m[i] : first_s[i];
-      if (c->sp_merged) c->dr.rs[i] = G_all;
+      const size_t first = c->bf16 ? first_m[i] : first_s[i];
+      if (c->bf16) c->dr.rs[i] = G_all;
       c->dr.src[i] = src + first; c->dr.pos[i] = pos + first; c->dr.lim[i] = lim + first;
       c->dr.limx[i] = limx + first; c->dr.cs[i] = cs + first * np;
     }
@@ -919,7 +1072,7 @@ int build_buffers(fm_ctx* c) {
   // rows (coordinate SP heads of every sequence, then the coordinate HF rows) through a pointer table either way.
   TRY(dalloc(c, &c->dh, nLM * d));
   int spv_rs = std::max(D.nspv, 1), spf_rs = D.nspf;
-  if (c->sp_merged) {
+  if (c->bf16) {
     TRY(dalloc(c, &c->spv_out, (size_t)S * std::max(G_all, 1) * d));
     c->spf_out = c->spv_out + (size_t)D.nspv * d;
     spv_rs = spf_rs = G_all;
@@ -930,7 +1083,7 @@ int build_buffers(fm_ctx* c) {
   {
     std::vector<const float*> tab(std::max<size_t>(nLM, 1));
     for (size_t i = 0; i < nLM; i++) {
-      if (c->sp_merged && i < S * (size_t)D.Dc) tab[i] = c->spv_out + ((i / D.Dc) * G_all + D.nspv + D.nspf + i % D.Dc) * d;
+      if (c->bf16 && i < S * (size_t)D.Dc) tab[i] = c->spv_out + ((i / D.Dc) * G_all + D.nspv + D.nspf + i % D.Dc) * d;
       else tab[i] = c->dh + i * d;
     }
     TRY(dalloc(c, (const float***)&c->lm_src, tab.size()));
@@ -941,6 +1094,12 @@ int build_buffers(fm_ctx* c) {
   TRY(dalloc(c, &c->dkeep, rmax * d)); TRY(dalloc(c, &c->dtmp, rmax * d));
   TRY(dalloc_t(c, &c->dxn, rmax * d)); TRY(dalloc_t(c, &c->dq, rmax * d)); TRY(dalloc_t(c, &c->datt, rmax * d));
   TRY(dalloc_t(c, &c->dmid, rmax * c->hff));
+  if (c->bf16) {
+    c->sp_tiles = (int)(S + 15) / 16; c->hf_tiles[0] = (int)(S + 15) / 16; c->hf_tiles[1] = (int)(2 * S + 15) / 16;
+    const size_t sp = (size_t)G_all * c->sp_tiles, hv = (size_t)D.nhfv * c->hf_tiles[0], hc = (size_t)D.nhfc * c->hf_tiles[1], lmt = (nLM + 15) / 16;
+    TRY(dalloc(c, &c->dX, std::max(std::max(sp, hv), std::max(std::max(hc, lmt), (size_t)1)) * 16 * d));
+    TRY(dalloc(c, &c->dmidX, std::max(std::max(sp * d, std::max(hv, hc) * c->hff), (size_t)1) * 16));
+  }
   TRY(dalloc(c, &c->dist_c, S * std::max(D.Dc, 1) * D.V));
   TRY(dalloc(c, &c->dist_v, S * std::max(D.nhfc, 1) * D.V)); TRY(dalloc(c, &c->dist_f, S * std::max(D.nhfc, 1) * D.V));
   TRY(dalloc(c, &c->lab_v, S * std::max(D.nspv, 1) * 3)); TRY(dalloc(c, &c->lab_f, S * std::max(D.nhfv, 1) * 3));
@@ -951,17 +1110,8 @@ int build_buffers(fm_ctx* c) {
   c->db = DraftBufs{c->tap_c, c->tap_v, c->tap_f, c->ring_yf, c->spv_out, c->spf_out, c->hfv_out, spv_rs, spf_rs};
   TRY(dalloc(c, &c->gen_tok, S * D.Bm)); TRY(dalloc(c, &c->gen_len, S)); TRY(dalloc(c, &c->gen_acc, S));
   if (c->persist) TRY(build_persist(c));
-  c->mres = MfmaRes{nullptr, nullptr, 0, 0, 0, 768, 0, 0};
-  if (const char* e = getenv("FM_ATTN_MERGE")) c->mres.attn_merge = atoi(e);   // measurement switch, see MfmaRes
-  if (const char* e = getenv("FM_ATTN_WGS")) c->mres.attn_wgs = atoi(e);       // measurement switch: workgroups per self-attention launch
-  if (const char* e = getenv("FM_GEMM_NC")) c->mres.gemm_nc = atoi(e);         // measurement switch: 1 = one column tile per workgroup
-  if (const char* e = getenv("FM_GEMM_WAVES")) c->mres.gemm_waves = atoi(e);   // measurement switch: 4, 8 or 16
-  if (const char* e = getenv("FM_GEMM_MT_CAP")) c->mres.gemm_mt_cap = atoi(e); // measurement switch: up to 2, 3, 5 or 8 row tiles per workgroup
+  c->mres = MfmaRes{};
   if (c->bf16) {
-    c->mres.attn_ws_floats = mfma_attn_ws_floats(3 * D.S, D.H, D.hd);       // 3: the merged SP launch has three row sets per sequence
-    TRY(dalloc(c, &c->mres.attn_ws, c->mres.attn_ws_floats, false));
-    TRY(dalloc(c, &c->mres.attn_counters, (size_t)3 * D.S * D.H));
-
     // tiled prefill GEMM: whole 256 x 128 output tiles only (keys x dims for V, dims x keys for K)
     const char* pt = getenv("FM_PREFILL_TILED");     // "0" forces the per-block GEMM + scatter launches
     if (D.M % 256 == 0 && d % 256 == 0 && !(pt && pt[0] == '0')) {
@@ -1124,7 +1274,7 @@ int fm_load_weights(fm_ctx* c, const float* blob, size_t n_floats) {
         if (c->bf16 && it.N > 0) {
           if (n != it.n) return fail(c, FM_EINVAL, "staging buffer smaller than a weight matrix");
           hipLaunchKernelGGL(k_tile_weight, dim3(1024), dim3(256), 0, c->stream, c->stage, (f16_t*)it.dst, it.N, it.K,
-                             (it.N + 15) / 16 * 16, it.perm);
+                             (it.N + 15) / 16 * 16, it.rope, c->D.hd);
         } else if (c->bf16)
           hipLaunchKernelGGL((k_convert<f16_t>), dim3(1024), dim3(256), 0, c->stream, c->stage, (f16_t*)it.dst + done, (long)n);
         else
@@ -1439,23 +1589,24 @@ int fm_measure_gemm(fm_ctx* c, int32_t rows, double* host_out) {
   };
 #define PK_TRY(x) do { if ((x) != hipSuccess) { (void)hipGetLastError(); cleanup(); return fail(c, FM_EHIP, "GEMM probe: %s failed", #x); } } while (0)
   PK_TRY(hipStreamSynchronize(c->stream));
-  PK_TRY(hipMalloc((void**)&X, (size_t)rows * d * 2)); PK_TRY(hipMalloc((void**)&Y, (size_t)rows * N * 2));
-  PK_TRY(hipMemsetAsync(X, 0, (size_t)rows * d * 2, c->stream));
+  const size_t prow = (size_t)(rows + 15) / 16 * 16;
+  PK_TRY(hipMalloc((void**)&X, prow * d * 2)); PK_TRY(hipMalloc((void**)&Y, prow * N * 2));
+  PK_TRY(hipMemsetAsync(X, 0, prow * d * 2, c->stream));
   PK_TRY(hipEventCreate(&e0)); PK_TRY(hipEventCreate(&e1));
   // Y[rows, ff] = gelu(X[rows, d] W1^T): the FFN up projection of the first block, half in and out
-  GemmArgs a{X, d, 0, L.w1, 0, Y, N, 0, nullptr, 0, 0, rows, N, d, nullptr, nullptr, 0.f, nullptr, nullptr, 0, nullptr, nullptr, 0, 0, 0};
+  DecGemm a{};
+  a.A = X; a.W = (const f16_t*)L.w1; a.M = rows; a.N = N; a.KT = d / 32; a.X = Y;
   const int reps = rows <= 256 ? 50 : 10;
   float ms = 0.f;
-  if (!mfma_gemm_launch<f16_t>(c->mres, a, EPI_GELU_T, 1, c->stream)) { cleanup(); return fail(c, FM_EINVAL, "GEMM probe: unsupported shape"); }
   // FM_GEMM_PROBE_CYCLE = n: successive launches walk the up projections of n different blocks (n x 8 d^2 bytes
   // of weights), which tells a last-level-cache hit from an L2 hit from HBM
   std::vector<const void*> ws;
   for (int st = 0; st < 5; st++) for (auto& Lx : c->stacks[st]) ws.push_back(Lx.w1);
   int cyc = 1;
   if (const char* e = getenv("FM_GEMM_PROBE_CYCLE")) cyc = std::max(1, std::min(atoi(e), (int)ws.size()));
-  for (int i = 0; i < cyc; i++) { a.W = ws[i]; mfma_gemm_launch<f16_t>(c->mres, a, EPI_GELU_T, 1, c->stream); }
+  for (int i = 0; i < cyc; i++) { a.W = (const f16_t*)ws[i]; dec_gemm<DE_GELU, false>(a, 1, c->stream); }
   PK_TRY(hipEventRecord(e0, c->stream));
-  for (int i = 0; i < reps; i++) { a.W = ws[i % cyc]; mfma_gemm_launch<f16_t>(c->mres, a, EPI_GELU_T, 1, c->stream); }
+  for (int i = 0; i < reps; i++) { a.W = (const f16_t*)ws[i % cyc]; dec_gemm<DE_GELU, false>(a, 1, c->stream); }
   PK_TRY(hipEventRecord(e1, c->stream)); PK_TRY(hipEventSynchronize(e1)); PK_TRY(hipEventElapsedTime(&ms, e0, e1));
   host_out[0] = ms / reps;
   host_out[1] = 2.0 * rows * (double)N * d * reps / (ms * 1e-3) / 1e12;

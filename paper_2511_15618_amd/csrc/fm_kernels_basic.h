@@ -105,18 +105,6 @@ __global__ __launch_bounds__(256) void k_rmsnorm(const float* __restrict__ src, 
 }
 
 // ------------------------------------------------------------------------------------------
-// Embedding lookup (inactive slots become zero rows)
-// ------------------------------------------------------------------------------------------
-template <typename T>
-__global__ void k_embed(const int* __restrict__ tok, const int* __restrict__ pos, const T* __restrict__ emb,
-                        float* __restrict__ h, int d) {
-  const int r = blockIdx.x;
-  const bool on = pos[r] >= 0;
-  const T* e = emb + (long)tok[r] * d;
-  for (int i = threadIdx.x; i < d; i += blockDim.x) h[(long)r * d + i] = on ? Store<T>::ld(e + i) : 0.f;
-}
-
-// ------------------------------------------------------------------------------------------
 // Rotary position + K/V append.  qkv fp32 [R][3d] -> q (T) [R][d]; K/V caches [S][H][cap][HD].
 // cs[r][i] = (cos, sin) of pos * base^(-i/(HD/2)), i < HD/2; pair (i, i + HD/2).
 // ------------------------------------------------------------------------------------------

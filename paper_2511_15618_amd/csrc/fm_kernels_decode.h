@@ -294,7 +294,7 @@ __global__ __launch_bounds__(NW * 64) void k_dec_gemm(DecGemm a) {
 // split (b / NW) % ns.  The deal depends on nothing but the launch configuration, so the arithmetic of one query row never
 // depends on what else is in the block or on how far the sequence has grown (speculative and one-token decoding agree
 // bit for bit), and it is balanced at every length: short contexts keep all keys in one workgroup (no merge), long
-// ones use all of them.  Partial results of several splits are merged by k_dec_merge in split order.
+// ones use all of them.  Partial results of several splits are merged, in split order, by the workgroup that arrives last.
 struct AttnSet {
   const f16_t* q;            // [sequence][RS rows][d] rotated queries
   const int* limit;          // [sequence][RS] last visible key, -1 = inactive row
@@ -307,16 +307,25 @@ struct AttnSet {
 };
 #define FM_ATTN_SETS 4
 struct AttnArgs {
-  AttnSet set[FM_ATTN_SETS];
+  AttnSet set[FM_ATTN_SETS];     // first member of the only kernel argument (attn_set)
   int S, H, ns_max;
+  unsigned* arrived;         // [set][sequence][head] splits that have published their part, zero between launches
   float* ws;                 // [set][sequence][head][ns_max][QT*16*HD unnormalised O | QT*16 running max (log2 units) | QT*16 sums]
   const int* run_flag;
 };
-__device__ __forceinline__ AttnSet attn_set(const AttnArgs& a, int z) { return z == 0 ? a.set[0] : z == 1 ? a.set[1] : z == 2 ? a.set[2] : a.set[3]; }
+// the set of this workgroup, read from the argument segment itself: indexing the by-value argument would copy it to scratch memory
+typedef const __attribute__((address_space(4))) AttnSet* attn_set_t;
+__device__ __forceinline__ attn_set_t attn_set(int z) {
+  return (attn_set_t)((const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr() + (size_t)z * sizeof(AttnSet));
+}
 __device__ __forceinline__ int attn_active(int maxlim, int capb, int ns, int NW) {      // splits that hold visible keys
   const int nblk = min((maxlim + 32) >> 5, capb);
   return max(1, min(ns, (nblk + NW - 1) / NW));
 }
+
+// 16- and 4-byte agent-scope loads whose wait the caller states (the compiler would keep atomic loads one by one)
+__device__ __forceinline__ void ld_agent4(f32x4& v, const float* p) { asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(v) : "v"(p) : "memory"); }
+__device__ __forceinline__ void ld_agent1(float& v, const float* p) { asm volatile("global_load_dword %0, %1, off sc1" : "=v"(v) : "v"(p) : "memory"); }
 
 template <int QT, int HD, int NW>
 __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
@@ -328,34 +337,38 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int g = lane >> 4, ql = lane & 15;
   const int hh = blockIdx.x, split = blockIdx.y, s = blockIdx.z % a.S, z = blockIdx.z / a.S;
-  const AttnSet A = attn_set(a, z);
-  if (split >= A.ns) return;
+  const attn_set_t A = attn_set(z);
+  const RowMap rm{A->rm.G, A->rm.mult, A->rm.base, A->rm.tiles};
+  if (split >= A->ns) return;
   const int rf = a.run_flag ? *a.run_flag : 1;
   const int d = a.H * HD;
   const float kScale = (HD == 64 ? 0.125f : 1.0f / sqrtf((float)HD)) * 1.4426950408889634f;   // 1/sqrt(HD) * log2(e)
-  const f16_t* Kb = A.Kc + (long)s * A.seq_stride + (long)hh * A.capb * BLK + lane * 8;
-  const f16_t* Vb = A.Vc + (long)s * A.seq_stride + (long)hh * A.capb * BLK + ql * 32 + g * 8;
+  const f16_t* Kb = A->Kc + (long)s * A->seq_stride + (long)hh * A->capb * BLK + lane * 8;
+  const f16_t* Vb = A->Vc + (long)s * A->seq_stride + (long)hh * A->capb * BLK + ql * 32 + g * 8;
   // the first block of this wave is inside the cache whatever the length: request it before anything else is known
-  const int bstep = A.ns * NW;
+  const int bstep = A->ns * NW;
   int b = split * NW + wave;
   f16x8 kf[2 * KC], vf[DT];
-  auto load_block = [&](int blk) {
+  auto load_k = [&](int blk) {
 #pragma unroll
     for (int f = 0; f < 2 * KC; f++) kf[f] = *reinterpret_cast<const f16x8*>(Kb + (long)blk * BLK + f * 512);
+  };
+  auto load_v = [&](int blk) {
 #pragma unroll
     for (int dt = 0; dt < DT; dt++) vf[dt] = *reinterpret_cast<const f16x8*>(Vb + (long)blk * BLK + dt * 512);
   };
-  load_block(min(b, A.capb - 1));
+  load_k(min(b, A->capb - 1));
+  load_v(min(b, A->capb - 1));
   int lim[QT], first[QT];
   f16x8 qf[QT][KC];
   int maxlim = -1;
 #pragma unroll
   for (int t = 0; t < QT; t++) {
     const int qi = t * 16 + ql;
-    const bool on = qi < A.rows;
-    const long row = (long)s * A.RS + A.q0 + (on ? qi : 0);
-    lim[t] = on ? A.limit[row] : -1;
-    const f16_t* qp = A.q + row * d + hh * HD + g * 8;
+    const bool on = qi < A->rows;
+    const long row = (long)s * A->RS + A->q0 + (on ? qi : 0);
+    lim[t] = on ? A->limit[row] : -1;
+    const f16_t* qp = A->q + row * d + hh * HD + g * 8;
 #pragma unroll
     for (int kc = 0; kc < KC; kc++) qf[t][kc] = *reinterpret_cast<const f16x8*>(qp + kc * 32);
   }
@@ -363,7 +376,7 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
   if (rf == 0) return;
 #pragma unroll
   for (int t = 0; t < QT; t++) {
-    first[t] = A.window > 0 ? max(lim[t] - A.window + 1, 0) : 0;     // sliding window: keys first .. lim
+    first[t] = A->window > 0 ? max(lim[t] - A->window + 1, 0) : 0;     // sliding window: keys first .. lim
     maxlim = max(maxlim, lim[t]);
   }
 #pragma unroll
@@ -373,10 +386,10 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
   // the latest position written to it.  Seen from the newest visible position `maxlim`, slot j holds lapbase + j if that
   // is <= maxlim, else the position one lap earlier (anything newer in the ring is a stale row of a rejected block: it
   // maps below the window and is masked).  Without a window lapbase = 0.
-  const int nblk = min((maxlim + 32) >> 5, A.capb);
-  const int ringn = A.capb * 32;
-  const int lapbase = A.window > 0 ? max(maxlim, 0) / ringn * ringn : 0;
-  const int nact = attn_active(maxlim, A.capb, A.ns, NW);
+  const int nblk = min((maxlim + 32) >> 5, A->capb);
+  const int ringn = A->capb * 32;
+  const int lapbase = A->window > 0 ? max(maxlim, 0) / ringn * ringn : 0;
+  const int nact = attn_active(maxlim, A->capb, A->ns, NW);
   if (split >= nact) return;
 
   float mrun[QT], lrun[QT];
@@ -388,25 +401,24 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
 #pragma unroll
     for (int dt = 0; dt < DT; dt++) o[t][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
+  // The operands of the next block are requested into the registers of this one as soon as those are free: its keys behind the
+  // score products, its values behind the output products.
   for (; b < nblk; b += bstep) {
-    f16x8 kn[2 * KC], vn[DT];
-    if (b + bstep < nblk) {
+    const int bn = min(b + bstep, A->capb - 1);
+    // scores, transposed: sT[t][hb][i] = <K[key], Q[q]> for key = b*32 + hb*16 + g*4 + i, q = this lane's row
+    f32x4 sT[QT][2];
 #pragma unroll
-      for (int f = 0; f < 2 * KC; f++) kn[f] = *reinterpret_cast<const f16x8*>(Kb + (long)(b + bstep) * BLK + f * 512);
-#pragma unroll
-      for (int dt = 0; dt < DT; dt++) vn[dt] = *reinterpret_cast<const f16x8*>(Vb + (long)(b + bstep) * BLK + dt * 512);
-    }
-#pragma unroll
-    for (int t = 0; t < QT; t++) {
-      // scores, transposed: sT[hb][i] = <K[key], Q[q]> for key = b*32 + hb*16 + g*4 + i, q = this lane's row
-      f32x4 sT[2];
+    for (int t = 0; t < QT; t++)
 #pragma unroll
       for (int hb = 0; hb < 2; hb++) {
         f32x4 zz = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int kc = 0; kc < KC; kc++) zz = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf[hb * KC + kc], qf[t][kc], zz, 0, 0, 0);
-        sT[hb] = zz;
+        sT[t][hb] = zz;
       }
+    if (b + bstep < nblk) load_k(bn);
+#pragma unroll
+    for (int t = 0; t < QT; t++) {
       float mx = -INFINITY;
 #pragma unroll
       for (int hb = 0; hb < 2; hb++)
@@ -414,8 +426,8 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
         for (int i = 0; i < 4; i++) {
           int key = lapbase + b * 32 + hb * 16 + g * 4 + i;     // absolute position held by this slot
           key = key > maxlim ? key - ringn : key;
-          const float v = (key <= lim[t] && key >= first[t]) ? sT[hb][i] * kScale : -INFINITY;
-          sT[hb][i] = v;
+          const float v = (key <= lim[t] && key >= first[t]) ? sT[t][hb][i] * kScale : -INFINITY;
+          sT[t][hb][i] = v;
           mx = fmaxf(mx, v);
         }
       mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
@@ -430,7 +442,7 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
       for (int hb = 0; hb < 2; hb++)
 #pragma unroll
         for (int i = 0; i < 4; i++) {
-          const float p = __builtin_amdgcn_exp2f(sT[hb][i] - msafe);
+          const float p = __builtin_amdgcn_exp2f(sT[t][hb][i] - msafe);
           psum += p;
           pf[hb * 4 + i] = (f16_t)p;
         }
@@ -441,12 +453,7 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
         o[t][dt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vf[dt], pf, o[t][dt], 0, 0, 0);   // O^T[dim][q]
       }
     }
-    if (b + bstep < nblk) {
-#pragma unroll
-      for (int f = 0; f < 2 * KC; f++) kf[f] = kn[f];
-#pragma unroll
-      for (int dt = 0; dt < DT; dt++) vf[dt] = vn[dt];
-    }
+    if (b + bstep < nblk) load_v(bn);
   }
   // combine the waves of the workgroup that had keys
 #pragma unroll
@@ -461,7 +468,7 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
   __syncthreads();
   const int wact = max(1, min(NW, nblk - split * NW));
   float* part = a.ws + (((long)blockIdx.z * a.H + hh) * a.ns_max + split) * PSZ;
-  for (int e = threadIdx.x; e < A.rows * (HD / 4); e += NW * 64) {
+  for (int e = threadIdx.x; e < A->rows * (HD / 4); e += NW * 64) {
     const int qi = e / (HD / 4), dim = e % (HD / 4) * 4;
     float M = -INFINITY;
     for (int w = 0; w < wact; w++) M = fmaxf(M, lm[w * NQ + qi]);
@@ -477,58 +484,51 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
       f16x4 ov;
 #pragma unroll
       for (int i = 0; i < 4; i++) ov[i] = (f16_t)(den > 0.f ? num[i] / den : 0.f);
-      *reinterpret_cast<f16x4*>(A.out + map_off(A.rm, s, A.q0 + qi, hh * HD + dim, d >> 5)) = ov;
+      *reinterpret_cast<f16x4*>(A->out + map_off(rm, s, A->q0 + qi, hh * HD + dim, d >> 5)) = ov;
     } else {
-      *reinterpret_cast<f32x4*>(part + qi * HD + dim) = num;
-      if (dim == 0) { part[NQ * HD + qi] = M; part[NQ * HD + NQ + qi] = den; }
+#pragma unroll
+      for (int i = 0; i < 4; i++) st_agent(part + qi * HD + dim + i, num[i]);
+      if (dim == 0) { st_agent(part + NQ * HD + qi, M); st_agent(part + NQ * HD + NQ + qi, den); }
     }
   }
-}
-
-// Merge of the partial results of the splits, one workgroup per (head, sequence and set); (sequence, head) pairs whose
-// keys fitted one split were written by the attention launch already.  All partials of a thread are in flight at once.
-template <int QT, int HD, int NW>
-__global__ __launch_bounds__(256) void k_dec_merge(AttnArgs a) {
-  constexpr int NQ = QT * 16, PSZ = NQ * HD + 2 * NQ, C = 8;
-  const int hh = blockIdx.x, s = blockIdx.y % a.S, z = blockIdx.y / a.S;
-  const AttnSet A = attn_set(a, z);
-  const int rf = a.run_flag ? *a.run_flag : 1;
-  const float* base = a.ws + ((long)blockIdx.y * a.H + hh) * a.ns_max * PSZ;
-  int maxlim = (int)(threadIdx.x & 31) < A.rows ? A.limit[(long)s * A.RS + A.q0 + (threadIdx.x & 31)] : -1;
-  // the first splits are requested before it is known how many there are (the workspace holds ns_max of them)
-  int e = threadIdx.x;
-  int qi = e / (HD / 4), dim = e % (HD / 4) * 4;
-  f32x4 v[C];
-  float m[C], l[C];
-  auto load = [&](int k0) {
-#pragma unroll
-    for (int j = 0; j < C; j++) {
-      const int k = min(k0 + j, a.ns_max - 1), q = min(qi, NQ - 1);
-      const float* p = base + (long)k * PSZ;
-      v[j] = *reinterpret_cast<const f32x4*>(p + q * HD + dim);
-      m[j] = p[NQ * HD + q];
-      l[j] = p[NQ * HD + NQ + q];
-    }
-  };
-  load(0);
-  asm volatile("" ::: "memory");
-  if (rf == 0 || A.ns <= 1) return;
-#pragma unroll
-  for (int o = 1; o < 32; o <<= 1) maxlim = max(maxlim, __shfl_xor(maxlim, o, 64));
-  const int n = attn_active(maxlim, A.capb, A.ns, NW);
-  if (n == 1) return;
-  for (; e < A.rows * (HD / 4); e += 256) {
-    if (e != (int)threadIdx.x) {
-      qi = e / (HD / 4); dim = e % (HD / 4) * 4;
-      load(0);
-    }
+  if (nact == 1) return;
+  // The parts went out as agent-scope stores, written through to where all dies see them: once a wave's stores have completed
+  // (vmcnt 0) they are visible, and no cache has to be written back.  The last of the active splits reads them all the same way.
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0)
+  __syncthreads();
+  int* last = (int*)da_smem;
+  if (threadIdx.x == 0) {
+    unsigned* cnt = a.arrived + (long)blockIdx.z * a.H + hh;
+    const unsigned old = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *last = old == (unsigned)nact - 1;
+    if (*last) __hip_atomic_store(cnt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  if (!*last) return;
+  const float* base = a.ws + ((long)blockIdx.z * a.H + hh) * a.ns_max * PSZ;
+  constexpr int C = 8;      // splits whose parts a thread has in flight together
+  for (int e = threadIdx.x; e < A->rows * (HD / 4); e += NW * 64) {
+    const int qi = e / (HD / 4), dim = e % (HD / 4) * 4;
     float M = -INFINITY, den = 0.f;
     f32x4 num = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < n; k0 += C) {
-      if (k0 > 0) load(k0);
+    for (int k0 = 0; k0 < nact; k0 += C) {
+      f32x4 v[C];
+      float m[C], l[C];
+#pragma unroll
+      for (int j = 0; j < C; j++) {
+        const float* p = base + (long)min(k0 + j, nact - 1) * PSZ;
+        ld_agent4(v[j], p + qi * HD + dim);
+        ld_agent1(m[j], p + NQ * HD + qi);
+        ld_agent1(l[j], p + NQ * HD + NQ + qi);
+      }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       float Mc = M;
 #pragma unroll
-      for (int j = 0; j < C; j++) if (k0 + j < n) Mc = fmaxf(Mc, m[j]);
+      for (int j = 0; j < C; j++) {
+        asm volatile("" : "+v"(v[j]), "+v"(m[j]), "+v"(l[j]));      // uses stay behind the wait
+        if (k0 + j < nact) Mc = fmaxf(Mc, m[j]);
+      }
       const float Ms = Mc == -INFINITY ? 0.f : Mc;
       const float sc = __builtin_amdgcn_exp2f(M - Ms);
       num *= sc;
@@ -536,7 +536,7 @@ __global__ __launch_bounds__(256) void k_dec_merge(AttnArgs a) {
       M = Mc;
 #pragma unroll
       for (int j = 0; j < C; j++)
-        if (k0 + j < n) {
+        if (k0 + j < nact) {
           const float f = __builtin_amdgcn_exp2f(m[j] - Ms);
           num += v[j] * f;
           den += l[j] * f;
@@ -545,6 +545,161 @@ __global__ __launch_bounds__(256) void k_dec_merge(AttnArgs a) {
     f16x4 ov;
 #pragma unroll
     for (int i = 0; i < 4; i++) ov[i] = (f16_t)(den > 0.f ? num[i] / den : 0.f);
-    *reinterpret_cast<f16x4*>(A.out + map_off(A.rm, s, A.q0 + qi, hh * HD + dim, (a.H * HD) >> 5)) = ov;
+    *reinterpret_cast<f16x4*>(A->out + map_off(rm, s, A->q0 + qi, hh * HD + dim, d >> 5)) = ov;
   }
+}
+
+// ------------------------------------------------------------------------------------------
+// Rows that enter the chain: normalised rows of the draft heads, pooled groups, upsampled rows
+// ------------------------------------------------------------------------------------------
+// sum of squares of 16 columns from the four lanes that hold four columns each
+__device__ __forceinline__ float quad_sum(float v) {
+  v += __shfl_xor(v, 1, 64);
+  v += __shfl_xor(v, 2, 64);
+  return v;
+}
+// four columns n.. of row m of a residual stream: fp32 row, half(x * gain) in tiled order, sum of squares per 16 columns
+__device__ __forceinline__ void put_row4(const f32x4& v, int m, int n, int d, float* h, f16_t* xg, const float* gain, float* ssq) {
+  *reinterpret_cast<f32x4*>(h + (long)m * d + n) = v;
+  const f32x4 gv = *reinterpret_cast<const f32x4*>(gain + n);
+  f16x4 o;
+#pragma unroll
+  for (int i = 0; i < 4; i++) o[i] = (f16_t)(v[i] * gv[i]);
+  *reinterpret_cast<f16x4*>(xg + tile_off(m, n, d >> 5)) = o;
+  const float t = quad_sum(v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3]);
+  if ((threadIdx.x & 3) == 0) ssq[((long)(m >> 4) * (d >> 4) + (n >> 4)) * 16 + (m & 15)] = t;
+}
+
+// RMSNorm of gathered rows into the tiled input of a grouped GEMM (row r = s * per_seq + q, gain of head r % gain_mod),
+// keeping the fp32 rows for a later residual add
+__global__ __launch_bounds__(256) void k_dec_rmsnorm(const float* const* __restrict__ srcptr, const float* __restrict__ gain, int gain_mod,
+                                                      f16_t* __restrict__ out, RowMap rm, int per_seq, float* __restrict__ keep, int d,
+                                                      float eps, const int* run_flag) {
+  const int r = blockIdx.x;
+  const int rf = run_flag ? *run_flag : 1;
+  const float* x = srcptr[r];
+  const float* g = gain + (long)(gain_mod ? r % gain_mod : 0) * d;
+  __shared__ float red[4];
+  if (rf == 0) return;
+  float ss = 0.f;
+  f32x4 v0 = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int n = threadIdx.x * 4; n < d; n += 1024) {
+    const f32x4 v = *reinterpret_cast<const f32x4*>(x + n);
+    if (n < 1024) v0 = v;
+    ss += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+  }
+  ss = wave_sum(ss);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  ss = red[0] + red[1] + red[2] + red[3];
+  const float inv = 1.0f / sqrtf(ss / (float)d + eps);
+  for (int n = threadIdx.x * 4; n < d; n += 1024) {
+    const f32x4 v = n < 1024 ? v0 : *reinterpret_cast<const f32x4*>(x + n);
+    const f32x4 gv = *reinterpret_cast<const f32x4*>(g + n);
+    if (keep) *reinterpret_cast<f32x4*>(keep + (long)r * d + n) = v;
+    f16x4 o;
+#pragma unroll
+    for (int i = 0; i < 4; i++) o[i] = (f16_t)(v[i] * inv * gv[i]);
+    *reinterpret_cast<f16x4*>(out + map_off(rm, r / per_seq, r % per_seq, n, d >> 5)) = o;
+  }
+}
+
+// coarse slot j pools fine rows 3j-2, 3j-1, 3j (rows before the start count as zero; always / 3)
+__global__ __launch_bounds__(256) void k_dec_pool3(const float* __restrict__ ring_fine, int RSf, const int* __restrict__ pos_coarse,
+                                                    int RPS, f16_t* __restrict__ out, int d) {
+  const int r = blockIdx.x, j = pos_coarse[r], s = r / RPS;
+  for (int n = threadIdx.x * 4; n < d; n += 1024) {
+    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (j >= 0) {
+      for (int k = 3 * j - 2; k <= 3 * j; k++)
+        if (k >= 0) acc += *reinterpret_cast<const f32x4*>(ring_fine + ((long)s * RSf + (k & (RSf - 1))) * d + n);
+    }
+    f16x4 o;
+#pragma unroll
+    for (int i = 0; i < 4; i++) o[i] = (f16_t)(acc[i] / 3.0f);
+    *reinterpret_cast<f16x4*>(out + tile_off(r, n, d >> 5)) = o;
+  }
+}
+
+// fine row at position p: its own stream (the skip) plus the coarse output of slot floor(p/3)
+__global__ __launch_bounds__(256) void k_dec_upsample(float* __restrict__ h, const int* __restrict__ pos, int RPS,
+                                                       const float* __restrict__ ring_coarse, int RSc, int d, f16_t* __restrict__ xg,
+                                                       const float* __restrict__ gain, float* __restrict__ ssq) {
+  const int r = blockIdx.x, p = pos[r];
+  const float* c = ring_coarse + ((long)(r / RPS) * RSc + ((max(p, 0) / 3) & (RSc - 1))) * d;
+  for (int n = threadIdx.x * 4; n < d; n += 1024) {
+    f32x4 v = *reinterpret_cast<const f32x4*>(h + (long)r * d + n);
+    if (p >= 0) v += *reinterpret_cast<const f32x4*>(c + n);
+    put_row4(v, r, n, d, h, xg, gain, ssq);
+  }
+}
+
+// ------------------------------------------------------------------------------------------
+// Launch rules
+// ------------------------------------------------------------------------------------------
+template <int MT, int NC, int NW, int U, bool LOOP, int EPI, bool NORM>
+void dec_gemm_launch(const DecGemm& a, int groups, hipStream_t st) {
+  const int tiles = (a.M + 15) / 16, NT = (a.N + 15) / 16;
+  const size_t lds = (size_t)NW * MT * NC * 1024 + NW * MT * 64;
+  if (lds > 65536) (void)hipFuncSetAttribute((const void*)k_dec_gemm<MT, NC, NW, U, LOOP, EPI, NORM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipLaunchKernelGGL((k_dec_gemm<MT, NC, NW, U, LOOP, EPI, NORM>), dim3((NT + NC - 1) / NC, (tiles + MT - 1) / MT, groups), dim3(NW * 64), lds, st, a);
+}
+
+// Which tile a launch gets.  gridDim.x = column tiles comes first in the block order, so the row tiles of a column tile run on
+// one die (the count of column tiles is a multiple of 8 for all weights but the output head's) and share its L2.
+// Measured in a chain of dependent launches over cold weights (us; M rows, d = K of the first four):
+//   M = 9, d = 1024: projection 3.7, up 4.5, down 6.8      M = 27, d = 768: 3.5, 4.4, 5.9
+//   M = 72, d = 1024: 4.1, 6.7, 7.6                        M = 72, d = 1536: 5.1, 11.1, 11.7
+template <int EPI, bool NORM>
+void dec_gemm(const DecGemm& a, int groups, hipStream_t st) {
+  const int tiles = (a.M + 15) / 16, NT = (a.N + 15) / 16, KT = a.KT;
+  const long wgs = (long)NT * tiles * groups;
+  const bool pairs = NT % 2 == 0;
+  // tall problems: operands shared by more of a workgroup's results, K in double-buffered chunks
+  if (tiles >= 8 && pairs) return dec_gemm_launch<4, 2, 8, 4, true, EPI, NORM>(a, groups, st);
+  // K too long for one trip
+  if (KT > 128) return wgs > 400 && pairs ? dec_gemm_launch<1, 2, 8, 8, true, EPI, NORM>(a, groups, st) : dec_gemm_launch<1, 1, 8, 8, true, EPI, NORM>(a, groups, st);
+  // long K: 8 or 16 waves hold the whole K of their columns in flight
+  if (KT > 64) return wgs > 200 && tiles >= 2 ? dec_gemm_launch<2, 1, 16, 8, false, EPI, NORM>(a, groups, st) : dec_gemm_launch<1, 1, 8, 16, false, EPI, NORM>(a, groups, st);
+  // few workgroups: one tile each
+  if (wgs <= 400 || !pairs) return dec_gemm_launch<1, 1, 4, 16, false, EPI, NORM>(a, groups, st);
+  // many: two column tiles share the activations
+  return KT <= 32 ? dec_gemm_launch<1, 2, 4, 8, false, EPI, NORM>(a, groups, st) : dec_gemm_launch<1, 2, 8, 8, false, EPI, NORM>(a, groups, st);
+}
+
+// Splits of an attention launch over `pairs` (head, sequence, set) triples: at most one workgroup of eight waves per compute
+// unit (256), a number of workgroups that divides them unevenly costs more than idle ones: with 96 pairs (d = 1536, 4
+// sequences) the step takes 4186 us with 2 splits, 4603 with 3, 4410 with 5; with 128 pairs 3231 with 2, 3475 with 3, 3423 with 4.
+inline int attn_splits(long pairs, int capb, int NW) {
+  const long ns = pairs < 256 ? 256 / pairs : 1;
+  const int most = (capb + NW - 1) / NW;
+  return (int)(ns > most ? most : ns);
+}
+inline size_t attn_ws_floats(int H, int S, int sets, int hd) {
+  const long pairs = (long)H * S * sets;      // pairs * splits < 2048 / 8 + pairs, parts of up to 32 rows
+  return (size_t)(256 + pairs) * (32 * hd + 64);
+}
+
+template <int QT, int HD, int NW>
+void dec_attn_go(const AttnArgs& a, int nset, hipStream_t st) {
+  const size_t lds = ((size_t)NW * QT * 16 * (HD + 4) + 2 * NW * QT * 16) * 4;
+  if (lds > 65536) (void)hipFuncSetAttribute((const void*)k_dec_attn<QT, HD, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipLaunchKernelGGL((k_dec_attn<QT, HD, NW>), dim3(a.H, a.ns_max, a.S * nset), dim3(NW * 64), lds, st, a);
+}
+
+// Attention of `nset` row sets (at most 32 rows each) in one launch.
+inline bool dec_attention(AttnArgs& a, int nset, int hd, hipStream_t st) {
+  constexpr int NW = 8;
+  int QT = 1;
+  a.ns_max = 1;
+  for (int z = 0; z < nset; z++) {
+    if (a.set[z].rows > 32) return false;
+    if (a.set[z].rows > 16) QT = 2;
+    a.set[z].ns = attn_splits((long)a.H * a.S * nset, a.set[z].capb, NW);
+    if (a.set[z].ns > a.ns_max) a.ns_max = a.set[z].ns;
+  }
+  if (hd == 64) { if (QT == 1) dec_attn_go<1, 64, NW>(a, nset, st); else dec_attn_go<2, 64, NW>(a, nset, st); }
+  else if (hd == 96) { if (QT == 1) dec_attn_go<1, 96, NW>(a, nset, st); else dec_attn_go<2, 96, NW>(a, nset, st); }
+  else { if (QT == 1) dec_attn_go<1, 128, NW>(a, nset, st); else dec_attn_go<2, 128, NW>(a, nset, st); }
+  return true;
 }

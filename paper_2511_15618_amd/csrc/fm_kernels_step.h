@@ -4,6 +4,7 @@
 #pragma once
 #include "fm_device.h"
 #include "fm_kernels_basic.h"
+#include "fm_kernels_decode.h"
 
 struct InvFreq { double v[64]; };  // base^(-i/(hd/2)) for the hd/2 rotary pairs of a head, computed in double on the host
 
@@ -42,65 +43,50 @@ __device__ __forceinline__ int eff_block_len(const StateDev& st, const Dims& D, 
   return max(len, 0);
 }
 
-// (any number of workgroups: every entry is computed from the committed state alone)
+// Rows of one verify pass, one workgroup per row (coordinate rows, then vertex, then face rows): position, last visible key of
+// the cross-attention, rotary table; every entry follows from the committed state alone.  emb != null: coordinate rows also get
+// their embedding as fp32 residual stream and, for the half path (xg != null), as input of the first projection.
+template <typename T>
 __global__ __launch_bounds__(256) void k_verify_setup(StateDev st, Dims D, InvFreq inv, const int* __restrict__ block_tok,
                                                        const int* __restrict__ block_len, int* pos_c, int* pos_v, int* pos_f,
                                                        int* limx_c, int* limx_v, int* limx_f, float2* cs_c, float2* cs_v,
-                                                       float2* cs_f, unsigned* epoch) {
+                                                       float2* cs_f, unsigned* epoch, const T* __restrict__ emb, float* __restrict__ h,
+                                                       f16_t* __restrict__ xg, const float* __restrict__ gain, float* __restrict__ ssq) {
   if (epoch && blockIdx.x == 0 && threadIdx.x == 0) *epoch += 1;     // pass counter of the single-launch verify kernel
-  const int tid = blockIdx.x * 256 + threadIdx.x, nth = gridDim.x * 256;
-  // position of row idx of a level, -1 for a row the block does not reach
-  auto row_c = [&](int idx) {
-    const int s = idx / D.Bm, i = idx % D.Bm;
-    return i < eff_block_len(st, D, s, block_len) ? st.P[s] + i : -1;
-  };
-  auto row_v = [&](int idx) {
-    const int s = idx / D.VB, k = idx % D.VB;
-    const int len = eff_block_len(st, D, s, block_len), P = st.P[s];
-    const int j = (P + 2) / 3 + k;
-    return 3 * j < P + len ? j : -1;
-  };
-  auto row_f = [&](int idx) {
-    const int s = idx / D.FB, k = idx % D.FB;
-    const int len = eff_block_len(st, D, s, block_len), P = st.P[s];
-    const int f = (P + 8) / 9 + k;
-    return 9 * f < P + len ? f : -1;
-  };
-  for (int idx = tid; idx < D.S * D.Bm; idx += nth) {
-    const int s = idx / D.Bm, i = idx % D.Bm;
-    const int p = row_c(idx);
-    pos_c[idx] = p;
-    limx_c[idx] = p >= 0 ? D.M - 1 : -1;
-    int t = p >= 0 ? block_tok[idx] : D.pad;
-    if (t < 0 || t >= D.V) t = D.pad;
-    st.vtok[idx] = t;
-    if (i == 0) st.vlen[s] = eff_block_len(st, D, s, block_len);
-  }
-  for (int idx = tid; idx < D.S * D.VB; idx += nth) {
-    const int p = row_v(idx);
-    pos_v[idx] = p;
-    limx_v[idx] = p >= 0 ? D.M - 1 : -1;
-  }
-  for (int idx = tid; idx < D.S * D.FB; idx += nth) {
-    const int p = row_f(idx);
-    pos_f[idx] = p;
-    limx_f[idx] = p >= 0 ? D.M - 1 : -1;
+  const int Rc = D.S * D.Bm, Rv = D.S * D.VB;
+  const int level = (int)blockIdx.x < Rc ? 0 : (int)blockIdx.x < Rc + Rv ? 1 : 2;
+  const int idx = blockIdx.x - (level == 0 ? 0 : level == 1 ? Rc : Rc + Rv);
+  const int per = level == 0 ? D.Bm : level == 1 ? D.VB : D.FB, step = level == 0 ? 1 : level == 1 ? 3 : 9;
+  const int s = idx / per, i = idx % per;
+  const int bt = level == 0 ? block_tok[idx] : 0;
+  const int len = eff_block_len(st, D, s, block_len), P = st.P[s];
+  const int q = (P + step - 1) / step + i;
+  const int p = step * q < P + len ? q : -1;       // a row the block does not reach is inactive
+  const int t = p >= 0 && bt >= 0 && bt < D.V ? bt : D.pad;
+  if (threadIdx.x == 0) {
+    (level == 0 ? pos_c : level == 1 ? pos_v : pos_f)[idx] = p;
+    (level == 0 ? limx_c : level == 1 ? limx_v : limx_f)[idx] = p >= 0 ? D.M - 1 : -1;
+    if (level == 0) {
+      st.vtok[idx] = t;
+      if (i == 0) st.vlen[s] = len;
+    }
   }
   const int np = D.hd >> 1;      // rotary pairs per head
-  for (int idx = tid; idx < D.S * D.Bm * np; idx += nth) {
-    const int p = row_c(idx / np);
-    const double a = (p < 0 ? 0.0 : (double)p) * inv.v[idx % np];
-    cs_c[idx] = make_float2((float)cos(a), (float)sin(a));
+  if ((int)threadIdx.x < np) {
+    double sn, c;
+    sincos((double)max(p, 0) * inv.v[threadIdx.x], &sn, &c);
+    (level == 0 ? cs_c : level == 1 ? cs_v : cs_f)[(long)idx * np + threadIdx.x] = make_float2((float)c, (float)sn);
   }
-  for (int idx = tid; idx < D.S * D.VB * np; idx += nth) {
-    const int p = row_v(idx / np);
-    const double a = (p < 0 ? 0.0 : (double)p) * inv.v[idx % np];
-    cs_v[idx] = make_float2((float)cos(a), (float)sin(a));
-  }
-  for (int idx = tid; idx < D.S * D.FB * np; idx += nth) {
-    const int p = row_f(idx / np);
-    const double a = (p < 0 ? 0.0 : (double)p) * inv.v[idx % np];
-    cs_f[idx] = make_float2((float)cos(a), (float)sin(a));
+  if (level == 0 && emb) {
+    const T* e = emb + (long)t * D.d;
+    for (int n = threadIdx.x * 4; n < D.d; n += 1024) {
+      f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (p >= 0)
+#pragma unroll
+        for (int k = 0; k < 4; k++) v[k] = Store<T>::ld(e + n + k);
+      if (xg) put_row4(v, idx, n, D.d, h, xg, gain, ssq);
+      else *reinterpret_cast<f32x4*>(h + (long)idx * D.d + n) = v;
+    }
   }
 }
 
@@ -329,12 +315,13 @@ __device__ __forceinline__ void set_row(const DraftRows& R, int set, int r, cons
     R.limx[set][r] = lim >= 0 ? M - 1 : -1;
   }
   for (int i = lane32; i < np; i += 32) {        // np = rotary pairs per head
-    const double a = (lim >= 0 ? (double)pos : 0.0) * inv.v[i];
-    R.cs[set][(long)r * np + i] = make_float2((float)cos(a), (float)sin(a));
+    double sn, c;
+    sincos((lim >= 0 ? (double)pos : 0.0) * inv.v[i], &sn, &c);
+    R.cs[set][(long)r * np + i] = make_float2((float)c, (float)sn);
   }
 }
 
-// One workgroup per sequence, 32 threads per row at a time.  The three launch flags (any sequence alive / firing at the
+// 32 threads per row, eight rows per workgroup, workgroups (sequence, row chunk).  The three launch flags (any sequence alive / firing at the
 // point level / at the face level) depend on the committed state only, so every workgroup could derive them; workgroup 0
 // does, for all sequences, and writes them.
 __global__ __launch_bounds__(256) void k_draft_setup(StateDev st, Dims D, InvFreq inv, DraftRows R, DraftBufs B) {
@@ -349,7 +336,7 @@ __global__ __launch_bounds__(256) void k_draft_setup(StateDev st, Dims D, InvFre
     firev = alive && D.m > 0 && ((v % 3) != 0 || !D.ruleA) && st.firedv[s] != v;
     firef = alive && D.n > 0 && st.firedf[s] != f;
   };
-  if (blockIdx.x == 0) {
+  if (blockIdx.x == 0 && blockIdx.y == 0) {
     __shared__ int f_any[3];
     if (threadIdx.x < 3) f_any[threadIdx.x] = 0;
     __syncthreads();
@@ -367,25 +354,36 @@ __global__ __launch_bounds__(256) void k_draft_setup(StateDev st, Dims D, InvFre
     const int s = blockIdx.x;
     bool alive, firev, firef; int spos, v, f;
     predicates(s, alive, firev, firef, spos, v, f);
-    if (threadIdx.x == 0) { R.alive[s] = alive; R.firev[s] = firev; R.firef[s] = firef; }
+    if (blockIdx.y == 0 && threadIdx.x == 0) { R.alive[s] = alive; R.firev[s] = firev; R.firef[s] = firef; }
     const float* tapc = B.tap_c + ((long)s * 32 + (spos & 31)) * d;
     const float* tapv = B.tap_v + ((long)s * 16 + (v & 15)) * d;
     const float* tapf = B.tap_f + ((long)s * 8 + (f & 7)) * d;
     const float* yf = B.ring_yf + ((long)s * 8 + (f & 7)) * d;
-    // set 0: coordinate SP heads k = 1..Dc on the coordinate tap at s
-    for (int k = grp; k < D.Dc; k += 8) set_row(R, 0, s * R.rs[0] + k, tapc, spos, alive ? spos : -1, D.M, inv, lane32, D.hd >> 1);
-    // set 1: point SP heads on the vertex tap of v
-    for (int k = grp; k < D.nspv; k += 8) set_row(R, 1, s * R.rs[1] + k, tapv, v, firev ? v : -1, D.M, inv, lane32, D.hd >> 1);
-    // set 2: face SP heads on the face tap of f
-    for (int k = grp; k < D.nspf; k += 8) set_row(R, 2, s * R.rs[2] + k, tapf, f, firef ? f : -1, D.M, inv, lane32, D.hd >> 1);
-    // set 3: vertex-level HF, vertex offsets j = j0..n/3-1 from vertex token 3f; input = face feature j/3
-    for (int q = grp; q < D.nhfv; q += 8) {
+    // row of this thread group: the five sets behind each other
+    int q = blockIdx.y * 8 + grp;
+    if (q < D.Dc) {                    // set 0: coordinate SP heads k = 1..Dc on the coordinate tap at s
+      set_row(R, 0, s * R.rs[0] + q, tapc, spos, alive ? spos : -1, D.M, inv, lane32, D.hd >> 1);
+      return;
+    }
+    q -= D.Dc;
+    if (q < D.nspv) {                  // set 1: point SP heads on the vertex tap of v
+      set_row(R, 1, s * R.rs[1] + q, tapv, v, firev ? v : -1, D.M, inv, lane32, D.hd >> 1);
+      return;
+    }
+    q -= D.nspv;
+    if (q < D.nspf) {                  // set 2: face SP heads on the face tap of f
+      set_row(R, 2, s * R.rs[2] + q, tapf, f, firef ? f : -1, D.M, inv, lane32, D.hd >> 1);
+      return;
+    }
+    q -= D.nspf;
+    if (q < D.nhfv) {                  // set 3: vertex-level HF, vertex offsets j = j0..n/3-1 from vertex token 3f; input = face feature j/3
       const int j = q + D.j0;
       const float* src = (j < 3) ? yf : B.spf_out + ((long)s * B.spf_rs + (j / 3 - 1)) * d;
       set_row(R, 3, s * D.nhfv + q, src, 3 * f + j, firef ? 3 * f : -1, D.M, inv, lane32, D.hd >> 1);
+      return;
     }
-    // set 4: coordinate-level HF, offsets t = t0..; pipe 0 = point pipeline, pipe 1 = face pipeline
-    for (int q = grp; q < 2 * D.nhfc; q += 8) {
+    q -= D.nhfv;
+    if (q < 2 * D.nhfc) {              // set 4: coordinate-level HF, offsets t = t0..; pipe 0 = point pipeline, pipe 1 = face pipeline
       const int pipe = q / D.nhfc, t = q % D.nhfc + D.t0;
       const int r = s * 2 * D.nhfc + q;
       if (pipe == 0) {
