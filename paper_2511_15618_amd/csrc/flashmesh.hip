@@ -381,8 +381,8 @@ void choose_and_accept(fm_ctx* c, const float* logits, int32_t* accepted) {
     hipLaunchKernelGGL(k_sample_rows, dim3(c->Rc), dim3(256), 0, c->stream, c->st, D, logits, c->smp);
     hipLaunchKernelGGL(k_accept, dim3(1), dim3(64), 0, c->stream, c->st, D, accepted, (const int*)c->smp.accflag, pass_failed(c));
   } else {
-    hipLaunchKernelGGL(k_argmax_rows, dim3(c->Rc), dim3(256), 0, c->stream, logits, D.V, D.ban ? D.nbins : D.V, c->st.y, c->st.counters + 2);
-    hipLaunchKernelGGL(k_accept, dim3(1), dim3(64), 0, c->stream, c->st, D, accepted, (const int*)nullptr, pass_failed(c));
+    hipLaunchKernelGGL(k_choose_greedy, dim3(D.S), dim3(1024), 0, c->stream, c->st, D, logits, D.ban ? D.nbins : D.V, accepted, pass_failed(c),
+                       c->st.counters + 2);
   }
 }
 

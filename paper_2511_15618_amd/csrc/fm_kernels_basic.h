@@ -265,47 +265,8 @@ __global__ void k_upsample_add(float* __restrict__ h, const int* __restrict__ po
 }
 
 // ------------------------------------------------------------------------------------------
-// Greedy choice per row: lowest index among exact ties, over [0, nlim)
+// Greedy choice: lowest index among exact ties
 // ------------------------------------------------------------------------------------------
 __device__ __forceinline__ void argmax_merge(float& bv, int& bi, float v, int i) {
   if (v > bv || (v == bv && i < bi)) { bv = v; bi = i; }
-}
-
-__device__ __forceinline__ int block_argmax(float bv, int bi, float* sv, int* si) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    float ov = __shfl_xor(bv, o, 64);
-    int oi = __shfl_xor(bi, o, 64);
-    argmax_merge(bv, bi, ov, oi);
-  }
-  const int wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  if ((threadIdx.x & 63) == 0) { sv[wave] = bv; si[wave] = bi; }
-  __syncthreads();
-  bv = sv[0]; bi = si[0];
-  for (int w = 1; w < nw; w++) argmax_merge(bv, bi, sv[w], si[w]);
-  __syncthreads();
-  return bi;
-}
-
-// `nonfinite` (may be null): counts the rows whose admissible logits hold an infinity or a NaN - half-precision
-// activations beyond 65504 overflow silently on the way, and this is where it shows
-__global__ __launch_bounds__(256) void k_argmax_rows(const float* __restrict__ logits, int V, int nlim, int* __restrict__ y,
-                                                      unsigned long long* __restrict__ nonfinite) {
-  __shared__ float sv[4];
-  __shared__ int si[4];
-  const float* x = logits + (long)blockIdx.x * V;
-  float bv = -INFINITY;
-  int bi = 0x7fffffff;
-  int bad = 0;
-  for (int i = threadIdx.x; i < nlim; i += 256) {
-    const float v = x[i];
-    bad |= !(fabsf(v) <= 3.0e38f);
-    argmax_merge(bv, bi, v, i);
-  }
-  bad = __syncthreads_or(bad);
-  const int b = block_argmax(bv, bi, sv, si);
-  if (threadIdx.x == 0) {
-    y[blockIdx.x] = b;
-    if (bad && nonfinite) atomicAdd(nonfinite, 1ull);
-  }
 }

@@ -90,22 +90,69 @@ __global__ __launch_bounds__(256) void k_verify_setup(StateDev st, Dims D, InvFr
   }
 }
 
-// accepted = 1 + number of leading drafts that equal the backbone's greedy prediction; with sampled decoding
-// (accflag != null) 1 + number of leading drafts that passed the rejection test (flag of row i is about draft i + 1)
-// (failed != null and *failed != 0: the forward pass gave up and its logits mean nothing; every accepted length is 0)
+// accepted = 1 + number of leading drafts that equal the backbone's greedy prediction; with sampled decoding 1 + number of
+// leading drafts that passed the rejection test (flag of row i is about draft i + 1).  `passed(i)`: draft i + 1 stands.
+// (failed: the forward pass gave up and its logits mean nothing; the accepted length is 0)
+template <class F>
+__device__ __forceinline__ void accept_seq(const StateDev& st, int s, int len, int* accepted_out, bool failed, F passed) {
+  int a = 0;
+  if (len > 0 && !failed) {
+    a = 1;
+    while (a < len && passed(a - 1)) a++;
+  }
+  st.acc[s] = a;
+  if (accepted_out) accepted_out[s] = a;
+}
+
 __global__ void k_accept(StateDev st, Dims D, int* __restrict__ accepted_out, const int* __restrict__ accflag,
                          const unsigned* __restrict__ failed) {
   const int s = threadIdx.x;
   if (s >= D.S) return;
+  accept_seq(st, s, st.vlen[s], accepted_out, failed && *failed, [&](int i) { return accflag[s * D.Bm + i] != 0; });
+}
+
+// Greedy choice of every row of a sequence (lowest index among exact ties, over [0, nlim)) and its accepted length: one
+// workgroup per sequence, one wave per row, 16 values per lane in flight.  `nonfinite` counts rows whose admissible logits
+// hold an infinity or a NaN: half-precision activations beyond 65504 overflow silently, and this is where it shows.
+__global__ __launch_bounds__(1024) void k_choose_greedy(StateDev st, Dims D, const float* __restrict__ logits, int nlim,
+                                                         int* __restrict__ accepted_out, const unsigned* __restrict__ failed,
+                                                         unsigned long long* __restrict__ nonfinite) {
+  __shared__ int sy[32], stok[32];
+  const int s = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int len = st.vlen[s];
-  int a = 0;
-  if (len > 0 && !(failed && *failed)) {
-    a = 1;
-    if (accflag) while (a < len && accflag[s * D.Bm + a - 1]) a++;
-    else while (a < len && st.vtok[s * D.Bm + a] == st.y[s * D.Bm + a - 1]) a++;
+  const bool bad_pass = failed && *failed;
+  if ((int)threadIdx.x < D.Bm) stok[threadIdx.x] = st.vtok[s * D.Bm + threadIdx.x];
+  for (int i = wave; i < D.Bm; i += 16) {
+    const float* x = logits + (long)(s * D.Bm + i) * D.V;
+    float bv = -INFINITY;
+    int bi = 0x7fffffff;
+    bool bad = false;
+    for (int i0 = lane; i0 < nlim; i0 += 1024) {
+      float v[16];
+#pragma unroll
+      for (int k = 0; k < 16; k++) v[k] = i0 + 64 * k < nlim ? x[i0 + 64 * k] : 0.f;
+#pragma unroll
+      for (int k = 0; k < 16; k++)
+        if (i0 + 64 * k < nlim) {
+          bad |= !(fabsf(v[k]) <= 3.0e38f);
+          argmax_merge(bv, bi, v[k], i0 + 64 * k);
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      const float ov = __shfl_xor(bv, o, 64);
+      const int oi = __shfl_xor(bi, o, 64);
+      argmax_merge(bv, bi, ov, oi);
+    }
+    bad = __any(bad);
+    if (lane == 0) {
+      sy[i] = bi;
+      st.y[s * D.Bm + i] = bi;
+      if (bad) atomicAdd(nonfinite, 1ull);
+    }
   }
-  st.acc[s] = a;
-  if (accepted_out) accepted_out[s] = a;
+  __syncthreads();
+  if (threadIdx.x == 0) accept_seq(st, s, len, accepted_out, bad_pass, [&](int i) { return stok[i + 1] == sy[i]; });
 }
 
 // What the host may look at while the device runs ahead of it: one pinned word per sequence, written by the commits of
@@ -241,46 +288,50 @@ struct Sampling {
 
 __device__ __forceinline__ float sample_uniform(unsigned long long seed, int purpose, int seq, int pos);
 
-// Inverse CDF in index order over n weights, by one workgroup of up to 1024 threads: thread t owns the contiguous
-// chunk [t*chunk, (t+1)*chunk); `wf(i)` gives weight i.  Returns the smallest i whose cumulative weight exceeds
-// u * total (the last index with weight if rounding leaves none), the same in every thread.  sh: blockDim + 2 floats
-// (the total is left in sh[blockDim]), si: 1 int.
-template <class F>
-__device__ __forceinline__ int block_inverse_cdf(int n, float u, F wf, float* sh, int* si) {
-  const int t = threadIdx.x, nt = blockDim.x;
-  const int chunk = (n + nt - 1) / nt;
-  const int i0 = min(t * chunk, n), i1 = min(i0 + chunk, n);
-  float local = 0.f;
-  for (int i = i0; i < i1; i++) local += wf(i);
-  sh[t] = local;
-  if (t == 0) *si = -1;
-  __syncthreads();
-  if (t == 0) {
-    float run = 0.f;
-    for (int k = 0; k < nt; k++) { const float v = sh[k]; sh[k] = run; run += v; }
-    sh[nt] = run;
+// inclusive prefix sum over the lanes of a wave
+__device__ __forceinline__ float wave_scan(float v) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const float u = __shfl_up(v, o, 64);
+    if (lane >= o) v += u;
   }
-  __syncthreads();
-  const float thr = u * sh[nt];
-  const float excl = sh[t];
-  if (i0 < i1 && excl <= thr && excl + local > thr) {
+  return v;
+}
+
+// Inverse CDF in index order over n weights by one wave: lane t owns the contiguous chunk [t*chunk, (t+1)*chunk); `wf(i)`
+// gives weight i.  Returns, in every lane, the smallest i whose cumulative weight exceeds u * total (the last index with weight
+// if rounding leaves none).
+template <class F>
+__device__ __forceinline__ int wave_inverse_cdf(int n, float u, F wf, float& total) {
+  const int lane = threadIdx.x & 63;
+  const int chunk = (n + 63) / 64;
+  const int i0 = min(lane * chunk, n), i1 = min(i0 + chunk, n);
+  float local = 0.f;
+  int last = -1;
+  for (int i = i0; i < i1; i++) {
+    const float w = wf(i);
+    local += w;
+    if (w > 0.f) last = i;
+  }
+  const float incl = wave_scan(local), excl = incl - local;
+  total = __shfl(incl, 63, 64);
+  const float thr = u * total;
+  int pick = 0x7fffffff;
+  if (i0 < i1 && incl > thr) {
     float run = excl;
     for (int i = i0; i < i1; i++) {
       run += wf(i);
-      if (run > thr) { *si = i; break; }
+      if (run > thr) { pick = i; break; }
     }
+    if (pick == 0x7fffffff) pick = last >= 0 ? last : i1 - 1;      // rounding between the chunk's sum and its walk
   }
-  __syncthreads();
-  if (*si < 0 && t == 0) {
-    int last = 0;
-    for (int i = 0; i < n; i++)
-      if (wf(i) > 0.f) last = i;
-    *si = last;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    pick = min(pick, __shfl_xor(pick, o, 64));
+    last = max(last, __shfl_xor(last, o, 64));
   }
-  __syncthreads();
-  const int r = *si;
-  __syncthreads();
-  return r;
+  return pick != 0x7fffffff ? pick : max(last, 0);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -418,21 +469,31 @@ __global__ __launch_bounds__(256) void k_dist_store(const float* __restrict__ lo
   if (!dst) return;
   const float* x = logits + (long)r * D.V;
   __shared__ float red[4];
+  // the first 2048 logits stay in registers between the two passes
+  float v[8];
+#pragma unroll
+  for (int k = 0; k < 8; k++) v[k] = (int)threadIdx.x + 256 * k < D.V ? x[threadIdx.x + 256 * k] : -INFINITY;
   float mx = -INFINITY;
-  for (int i = threadIdx.x; i < D.V; i += 256) mx = fmaxf(mx, x[i]);
+#pragma unroll
+  for (int k = 0; k < 8; k++) mx = fmaxf(mx, v[k]);
+  for (int i = threadIdx.x + 2048; i < D.V; i += 256) mx = fmaxf(mx, x[i]);
   mx = wave_max(mx);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
   __syncthreads();
   mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
   __syncthreads();
   float sum = 0.f;
-  for (int i = threadIdx.x; i < D.V; i += 256) sum += expf(x[i] - mx);
+#pragma unroll
+  for (int k = 0; k < 8; k++) { v[k] = expf(v[k] - mx); sum += v[k]; }
+  for (int i = threadIdx.x + 2048; i < D.V; i += 256) sum += expf(x[i] - mx);
   sum = wave_sum(sum);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = sum;
   __syncthreads();
   sum = red[0] + red[1] + red[2] + red[3];
   const float inv = 1.0f / sum;
-  for (int i = threadIdx.x; i < D.V; i += 256) dst[i] = expf(x[i] - mx) * inv;
+#pragma unroll
+  for (int k = 0; k < 8; k++) if ((int)threadIdx.x + 256 * k < D.V) dst[threadIdx.x + 256 * k] = v[k] * inv;
+  for (int i = threadIdx.x + 2048; i < D.V; i += 256) dst[i] = expf(x[i] - mx) * inv;
 }
 
 __device__ __forceinline__ float replay_uniform(unsigned long long seed, unsigned long long seq, unsigned long long pos) {
@@ -453,8 +514,7 @@ __device__ __forceinline__ float sample_uniform(unsigned long long seed, int pur
 // drawn from the stored distribution counts as a proposal with all its mass on it), and the token emitted after this
 // row if the accepted prefix ends here: from max(p - q, 0) after a rejection, from p after the last row.
 __global__ __launch_bounds__(256) void k_sample_rows(StateDev st, Dims D, const float* __restrict__ logits, Sampling sm) {
-  __shared__ float sh[260];
-  __shared__ int si;
+  __shared__ float sh[4];
   const int row = blockIdx.x, s = row / D.Bm, i = row % D.Bm;
   const int len = st.vlen[s];
   if (i >= len) return;
@@ -492,20 +552,16 @@ __global__ __launch_bounds__(256) void k_sample_rows(StateDev st, Dims D, const 
     accepted = sample_uniform(seed, FM_U_ACCEPT, s, pos) * qa < pa;
   }
   const float u = sample_uniform(seed, FM_U_RESAMPLE, s, pos);
+  if (threadIdx.x >= 64) return;      // the draw is one wave's work
+  float tot = 0.f;
   int y;
   if (!has_draft) {
-    y = block_inverse_cdf(nlim, u, pf, sh, &si);
+    y = wave_inverse_cdf(nlim, u, pf, tot);
   } else {
     auto wf = [&](int j) { return fromq ? fmaxf(pf(j) - q[j] * invZq, 0.f) : (j == xd ? 0.f : pf(j)); };
+    y = wave_inverse_cdf(nlim, u, wf, tot);
     // all the mass can vanish only if p and q agree everywhere (or p sits on the draft alone): then p itself
-    float tot = 0.f;
-    for (int j = threadIdx.x; j < nlim; j += 256) tot += wf(j);
-    tot = wave_sum(tot);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = tot;
-    __syncthreads();
-    tot = sh[0] + sh[1] + sh[2] + sh[3];
-    __syncthreads();
-    y = tot > 0.f ? block_inverse_cdf(nlim, u, wf, sh, &si) : block_inverse_cdf(nlim, u, pf, sh, &si);
+    if (!(tot > 0.f)) y = wave_inverse_cdf(nlim, u, pf, tot);
   }
   if (threadIdx.x == 0) {
     st.y[row] = y;
@@ -513,45 +569,52 @@ __global__ __launch_bounds__(256) void k_sample_rows(StateDev st, Dims D, const 
   }
 }
 
-// One workgroup per sequence: update the draft bookkeeping, average the distributions that cover
-// each future position, take the greedy token, stop at the first uncovered position.
+// One workgroup per sequence: update the draft bookkeeping, average the distributions that cover each future position and
+// take the greedy (or draw the sampled) token, one wave per draft index; the block ends at the first uncovered position.
+// Everything the state holds is read in one trip, the rows of an index in another.
 __global__ __launch_bounds__(1024) void k_merge(StateDev st, Dims D, DraftRows R, const float* __restrict__ dist_c,
                                                 const float* __restrict__ dist_v, const float* __restrict__ dist_f,
                                                 int speculative, int* __restrict__ block_tok,
                                                 int* __restrict__ block_len, Sampling sm) {
-  __shared__ float sh[1026];
-  __shared__ int sidx;
+  __shared__ int stok[32];
+  __shared__ int slen;
+  const int s = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const StepParams pr = *sm.p;
   const Replay& rp = pr.replay;
-  if (pr.temperature > 0.f)
-    for (int i = threadIdx.x; i < D.Bm; i += blockDim.x) sm.qtok[blockIdx.x * D.Bm + i] = -1;
-  const int s = blockIdx.x;
+  const int fin = st.fin[s], P = st.P[s], budget = st.budget[0], mainTok = st.main[s];
+  const int firev = R.firev[s], firef = R.firef[s], oldv = st.basev[s], oldf = st.basef[s];
   int* tok = block_tok + (long)s * D.Bm;
-  if (st.fin[s]) {
+  const bool sampled = pr.temperature > 0.f;
+  if (sampled && (int)threadIdx.x < D.Bm) sm.qtok[s * D.Bm + threadIdx.x] = -1;
+  if (fin) {
     if (threadIdx.x == 0) block_len[s] = 0;
     return;
   }
-  const int P = st.P[s], budget = st.budget[0];
-  if (threadIdx.x == 0) tok[0] = st.main[s];
+  if (threadIdx.x == 0) tok[0] = mainTok;
   if (P == 0 || !speculative) {
     if (threadIdx.x == 0) { block_len[s] = 1; st.kind[s] = 0; }
     return;
   }
+  // synthetic draft source: the known continuation, each token kept with probability `keep`
+  const int n_replay = rp.stream ? max(min(D.Bm - 1, min(budget - 1 - P, rp.n_valid - P)), 0) : 0;
+  const int t = threadIdx.x;
+  const int truth = t >= 1 && t <= n_replay ? rp.stream[(long)s * rp.stride + P + t - 1] : 0;
   const int spos = P - 1;
   const int basec = spos;
-  const int basev = R.firev[s] ? 3 * (spos / 3) : st.basev[s];
-  const int basef = R.firef[s] ? 9 * (spos / 9) : st.basef[s];
+  const int basev = firev ? 3 * (spos / 3) : oldv;
+  const int basef = firef ? 9 * (spos / 9) : oldf;
   __syncthreads();   // every thread has read the old state
   if (threadIdx.x == 0) {
     st.basec[s] = basec; st.basev[s] = basev; st.basef[s] = basef;
-    if (R.firev[s]) st.firedv[s] = spos / 3;
-    if (R.firef[s]) st.firedf[s] = spos / 9;
-    st.kind[s] = R.firef[s] ? 2 : R.firev[s] ? 1 : 0;
+    if (firev) st.firedv[s] = spos / 3;
+    if (firef) st.firedf[s] = spos / 9;
+    st.kind[s] = firef ? 2 : firev ? 1 : 0;
   }
   const int nlim = D.ban ? D.nbins : D.V;
-  int len = 1;
-  // the averaged distributions behind draft index idx (position spos + 1 + idx), if any level covers it
-  auto rows_of = [&](int p, const float* (&rows)[3]) {
+  for (int idx = 1 + wave; idx < D.Bm; idx += 16) {
+    // the averaged distributions behind draft index idx (position spos + 1 + idx), if any level covers it
+    const int p = spos + 1 + idx;
+    const float* rows[3];
     int cnt = 0;
     const int kc = p - (basec + 2);
     if (kc >= 0 && kc < D.Dc) rows[cnt++] = dist_c + ((long)s * D.Dc + kc) * D.V;
@@ -559,60 +622,41 @@ __global__ __launch_bounds__(1024) void k_merge(StateDev st, Dims D, DraftRows R
     if (basev >= 0 && tv >= D.t0 && tv < D.m) rows[cnt++] = dist_v + ((long)s * D.nhfc + (tv - D.t0)) * D.V;
     const int tf = p - 1 - basef;
     if (basef >= 0 && tf >= D.t0 && tf < D.n) rows[cnt++] = dist_f + ((long)s * D.nhfc + (tf - D.t0)) * D.V;
-    return cnt;
-  };
-  if (pr.temperature > 0.f) {
-    // sampled decoding: keep the averaged distribution (the proposal the verify pass tests against) and draw from it
-    for (int p = spos + 2; len < D.Bm && p < budget; p++) {
-      const float* rows[3];
-      const int cnt = rows_of(p, rows);
-      if (cnt == 0) break;
+    int bi = -1;
+    if (cnt > 0) {
       const float inv = 1.0f / (float)cnt;
-      float* qr = sm.qrow + ((long)s * D.Bm + len) * D.V;
-      for (int i = threadIdx.x; i < nlim; i += blockDim.x) {
-        float a = rows[0][i];
-        if (cnt > 1) a += rows[1][i];
-        if (cnt > 2) a += rows[2][i];
-        qr[i] = a * inv;
-      }
-      __syncthreads();
-      const int b = block_inverse_cdf(nlim, sample_uniform(pr.seed, FM_U_DRAFT, s, p), [&](int i) { return qr[i]; }, sh, &sidx);
-      if (threadIdx.x == 0) { tok[len] = b; sm.qtok[s * D.Bm + len] = b; sm.qsum[s * D.Bm + len] = sh[blockDim.x]; }
-      __syncthreads();
-      len++;
-    }
-  } else {
-    // greedy: one wave per draft index, all indices at once; the block then ends at the first index nothing covers
-    __shared__ int stok[32];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for (int idx = 1 + wave; idx < D.Bm; idx += (int)(blockDim.x >> 6)) {
-      const float* rows[3];
-      const int cnt = rows_of(spos + 1 + idx, rows);
-      int bi = -1;
-      if (cnt > 0) {
-        const float inv = 1.0f / (float)cnt;
-        float bv = -INFINITY;
-        bi = 0x7fffffff;
-        // four strides of the vocabulary per step, all loads of a step in flight together
-        for (int i0 = lane; i0 < nlim; i0 += 256) {
-          float a[4];
+      const float *r0 = rows[0], *r1 = cnt > 1 ? rows[1] : nullptr, *r2 = cnt > 2 ? rows[2] : nullptr;
+      float* qr = sampled || pr.keep_rows ? sm.qrow + ((long)s * D.Bm + idx) * D.V : nullptr;
+      float bv = -INFINITY;
+      bi = 0x7fffffff;
+      for (int i0 = lane; i0 < nlim; i0 += 1024) {
+        float a[16], b[16], c[16];
 #pragma unroll
-          for (int k = 0; k < 4; k++) {
-            const int i = i0 + 64 * k;
-            a[k] = 0.f;
-            if (i < nlim) {
-              a[k] = rows[0][i];
-              if (cnt > 1) a[k] += rows[1][i];
-              if (cnt > 2) a[k] += rows[2][i];
-            }
-          }
-#pragma unroll
-          for (int k = 0; k < 4; k++)
-            if (i0 + 64 * k < nlim) {
-              argmax_merge(bv, bi, a[k] * inv, i0 + 64 * k);
-              if (pr.keep_rows) sm.qrow[((long)s * D.Bm + idx) * D.V + i0 + 64 * k] = a[k] * inv;
-            }
+        for (int k = 0; k < 16; k++) {
+          const int i = min(i0 + 64 * k, nlim - 1);
+          a[k] = r0[i];
+          b[k] = r1 ? r1[i] : 0.f;
+          c[k] = r2 ? r2[i] : 0.f;
         }
+#pragma unroll
+        for (int k = 0; k < 16; k++)
+          if (i0 + 64 * k < nlim) {
+            float v = a[k];
+            if (r1) v += b[k];
+            if (r2) v += c[k];
+            v *= inv;
+            argmax_merge(bv, bi, v, i0 + 64 * k);
+            if (qr) qr[i0 + 64 * k] = v;
+          }
+      }
+      if (sampled) {
+        // the kept row is the proposal that the verify pass tests against; a wave reads back what its own lanes stored
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        float total;
+        bi = wave_inverse_cdf(nlim, sample_uniform(pr.seed, FM_U_DRAFT, s, p), [&](int i) { return qr[i]; }, total);
+        if (lane == 0 && p < budget) { sm.qtok[s * D.Bm + idx] = bi; sm.qsum[s * D.Bm + idx] = total; }
+      } else {
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) {
           const float ov = __shfl_xor(bv, o, 64);
@@ -620,28 +664,28 @@ __global__ __launch_bounds__(1024) void k_merge(StateDev st, Dims D, DraftRows R
           argmax_merge(bv, bi, ov, oi);
         }
       }
-      if (lane == 0) stok[idx] = bi;
     }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      while (len < D.Bm && spos + 1 + len < budget && stok[len] >= 0) { tok[len] = stok[len]; len++; }
-      stok[0] = len;
-    }
-    __syncthreads();
-    len = stok[0];
+    if (lane == 0) stok[idx] = bi;
   }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int len = 1;
+    while (len < D.Bm && spos + 1 + len < budget && stok[len] >= 0) len++;
+    slen = len;
+  }
+  __syncthreads();
+  int len = slen;
+  if (sampled && t >= len && t < D.Bm) sm.qtok[s * D.Bm + t] = -1;
   if (rp.stream) {
-    // synthetic draft source: the known continuation, each token kept with probability `keep`
-    int n = min(D.Bm - 1, min(budget - 1 - P, rp.n_valid - P));
-    n = max(n, 0);
-    const int t = threadIdx.x;
-    if (t >= 1 && t <= n) {
-      const int p = P + t;
-      const int truth = rp.stream[(long)s * rp.stride + p - 1];
-      const bool keep = replay_uniform(rp.seed, (unsigned long long)s, (unsigned long long)p) < rp.keep;
+    if (t >= 1 && t <= n_replay) {
+      const bool keep = replay_uniform(rp.seed, (unsigned long long)s, (unsigned long long)(P + t)) < rp.keep;
       tok[t] = keep ? truth : (truth + 1) % D.nbins;
+    } else if (t > n_replay && t >= 1 && t < len) {
+      tok[t] = stok[t];
     }
-    len = 1 + n;
+    len = 1 + n_replay;
+  } else if (t >= 1 && t < len) {
+    tok[t] = stok[t];
   }
   if (threadIdx.x == 0) block_len[s] = len;
 }
