@@ -115,8 +115,8 @@ int fm_prefill_condition(fm_ctx* ctx, int32_t seq, const float* mem_dev);
  * same result, but the staging area of the call (the condition memory re-ordered for the matrix units, or, on the fp32
  * path, its converted copy and one block's K/V rows) lives in a 16 MiB device array that is part of the library image
  * instead of memory owned by the context.  The call allocates and frees nothing.  FM_EINVAL with a message when the
- * configuration needs more staging than 16 MiB (mem_len * d_model * 2 bytes in half precision with mem_len and d_model
- * multiples of 256, else mem_len * d_model * (element size + 8)).  Every GPU holds one such array for all contexts on
+ * configuration needs more staging than 16 MiB (half precision: mem_len rounded up to 32, times d_model * 2 bytes; d_model below
+ * 128 and the fp32 path: mem_len * d_model * (element size + 8)).  Every GPU holds one such array for all contexts on
  * it: calls that overlap in time on one GPU (different streams or contexts) race on it; calls on one stream are safe. */
 int fm_prefill_condition_static(fm_ctx* ctx, int32_t seq, const float* mem_dev);
 

@@ -102,7 +102,6 @@ struct fm_ctx {
   float* h[3];
   void *xn, *qT, *attT, *mid;
   float *qkv, *logits;
-  MfmaRes mres;       // per-block prefill GEMM (half-precision path)
   // half-precision path, one launch per operator: per level the input of the next norm's GEMM (x * gain, tiled) and the row sums of
   // squares; attention output and FFN hidden rows (tiled), queries, attention workspace
   f16_t *xg[3], *attX, *midX;
@@ -281,10 +280,7 @@ const int kStackLevel[5] = {0, 1, 2, 1, 0};
 template <typename T>
 void gemm(fm_ctx* c, int epi, const void* X, long ldx, long gsx, const void* W, long gsw, void* Y, long ldy, long gsy,
           const float* R, long ldr, long gsr, int M, int N, int K, int groups, const int* flag) {
-  GemmArgs a{X, ldx, gsx, W, gsw, Y, ldy, gsy, R, ldr, gsr, M, N, K, flag, nullptr, 0.f, nullptr, nullptr, 0, nullptr, nullptr, 0, 0, 0};
-  if (mfma_gemm_launch<T>(c->mres, a, epi, groups, c->stream)) return;
-  // the plain kernel reads row-major weights: only the fp32 path has those
-  if (!std::is_same<T, float>::value) { fail(c, FM_EINVAL, "gemm: unsupported shape M=%d N=%d K=%d", M, N, K); c->sticky_error = true; return; }
+  GemmArgs a{X, ldx, gsx, W, gsw, Y, ldy, gsy, R, ldr, gsr, M, N, K, flag};
   dim3 grid((N + 3) / 4, groups);
   if (epi == EPI_F32) hipLaunchKernelGGL((k_gemm_simple<T, EPI_F32>), grid, dim3(256), 0, c->stream, a);
   else if (epi == EPI_GELU_T) hipLaunchKernelGGL((k_gemm_simple<T, EPI_GELU_T>), grid, dim3(256), 0, c->stream, a);
@@ -745,49 +741,65 @@ int put_params(fm_ctx* c) {
   return FM_OK;
 }
 
-// staging bytes a prefill call needs: the memory in fragment order (tiled GEMM), or the memory in the storage type
-// followed by the fp32 K/V rows of one block
+// staging bytes a prefill call needs: half path: the memory in fragment order (whole 32-row blocks) and, for models narrower than the tiled
+// GEMM takes, the fp32 K/V rows of one block behind it; fp32 path: the memory and those rows
 size_t prefill_stage_bytes(const fm_ctx* c) {
-  const size_t M = c->D.M, d = c->D.d;
-  if (c->bf16 && c->pf_layers) return M * d * sizeof(f16_t);
+  const size_t M = c->D.M, d = c->D.d, M32 = (M + 31) / 32 * 32;
+  if (c->bf16) return M32 * d * sizeof(f16_t) + (c->pf_layers ? 0 : M * 2 * d * sizeof(float));
   return M * d * c->esz + M * 2 * d * sizeof(float);
 }
 
-template <typename T>
-int prefill_impl(fm_ctx* c, int seq, const float* mem_dev, void* stage_area) {
+int prefill_half(fm_ctx* c, int seq, const float* mem_dev, void* stage_area) {
   const Dims& D = c->D;
-  const int d = D.d;
-  // condition memory in the storage type (dmid is large enough: M*d <= checked at create)
-  if (std::is_same<T, f16_t>::value && c->pf_layers) {
-    // memory -> MFMA fragment order (the same tiling as a weight matrix), then one launch for all blocks
-    f16_t* Xt = (f16_t*)stage_area;
-    hipLaunchKernelGGL(k_tile_weight, dim3(1024), dim3(256), 0, c->stream, mem_dev, Xt, D.M, d, D.M, 0, D.hd);
-#define FM_PREFILL(HDV) hipLaunchKernelGGL((k_prefill_kv<HDV>), dim3(c->pf_grid), dim3(256), PF_LDS_BYTES, c->stream, (const f16_t*)Xt, \
-                                           (const PrefillLayer*)c->pf_layers, (long)((size_t)seq * cache_seq_elems(c, D.M)), d / 32, d, D.M, c->pf_n)
-    if (D.hd == 64) FM_PREFILL(64); else if (D.hd == 96) FM_PREFILL(96); else FM_PREFILL(128);
-#undef FM_PREFILL
-    hipLaunchKernelGGL(k_reset_seq, dim3(1), dim3(64), 0, c->stream, c->st, D, seq, D.nbins);
-    HIPCHK(c, hipGetLastError());
-    return FM_OK;
+  const int d = D.d, M32 = (D.M + 31) / 32 * 32;
+  // memory -> MFMA fragment order (the same tiling as a weight matrix, zero rows up to whole key blocks)
+  f16_t* Xt = (f16_t*)stage_area;
+  hipLaunchKernelGGL(k_tile_weight, dim3(std::min(2048, (M32 * (d / 8) + 255) / 256)), dim3(256), 0, c->stream, mem_dev, Xt, D.M, d, M32, 0, D.hd);
+  const long seq_off = (long)((size_t)seq * cache_seq_elems(c, D.M));
+  if (c->pf_layers) {
+#define FM_PREFILL(HDV)                                                                                                            \
+  {                                                                                                                                \
+    if (D.M % 256 == 0 && d % 256 == 0)                                                                                            \
+      hipLaunchKernelGGL((k_prefill_kv<HDV, false>), dim3(c->pf_grid), dim3(256), PF_LDS_BYTES, c->stream, (const f16_t*)Xt,       \
+                         (const PrefillLayer*)c->pf_layers, seq_off, d / 32, d, D.M, c->pf_n);                                     \
+    else                                                                                                                           \
+      hipLaunchKernelGGL((k_prefill_kv<HDV, true>), dim3(c->pf_grid), dim3(256), PF_LDS_BYTES, c->stream, (const f16_t*)Xt,        \
+                         (const PrefillLayer*)c->pf_layers, seq_off, d / 32, d, D.M, c->pf_n);                                     \
   }
-  T* memT = (T*)stage_area;  // [M*d] T followed by fp32 [M][2d]
-  float* kv = (float*)((unsigned char*)stage_area + (size_t)D.M * d * sizeof(T));
-  hipLaunchKernelGGL((k_convert<T>), dim3(512), dim3(256), 0, c->stream, mem_dev, memT, (long)D.M * d);
-  for (int st = 0; st < 5; st++)
-    for (auto& L : c->stacks[st]) {
-      gemm<T>(c, EPI_F32, memT, d, 0, L.ckv, 0, kv, 2 * d, 0, nullptr, 0, 0, D.M, 2 * d, d, 1, nullptr);
-      T* Km = (T*)L.Km + (size_t)seq * cache_seq_elems(c, D.M);
-      T* Vm = (T*)L.Vm + (size_t)seq * cache_seq_elems(c, D.M);
-      if (std::is_same<T, f16_t>::value) {
-#define FM_MEMKVH(HDV) hipLaunchKernelGGL((k_mem_kv_store_h<HDV>), dim3(D.M), dim3(256), 0, c->stream, kv, (f16_t*)Km, (f16_t*)Vm, D.H, D.M, \
+    if (D.hd == 64) FM_PREFILL(64) else if (D.hd == 96) FM_PREFILL(96) else FM_PREFILL(128)
+#undef FM_PREFILL
+  } else {
+    float* kv = (float*)(Xt + (size_t)M32 * d);
+    for (int st = 0; st < 5; st++)
+      for (auto& L : c->stacks[st]) {
+        DecGemm a{};
+        a.A = Xt; a.W = (const f16_t*)L.ckv; a.M = D.M; a.N = 2 * d; a.KT = d / 32; a.Y = kv; a.ldy = 2 * d;
+        dec_gemm<DE_F32, false>(a, 1, c->stream);
+#define FM_MEMKVH(HDV) hipLaunchKernelGGL((k_mem_kv_store_h<HDV>), dim3(D.M), dim3(256), 0, c->stream, kv, (f16_t*)L.Km + seq_off, (f16_t*)L.Vm + seq_off, D.H, D.M, \
                                           (D.M + 31) / 32)
         if (D.hd == 64) FM_MEMKVH(64); else if (D.hd == 96) FM_MEMKVH(96); else FM_MEMKVH(128);
 #undef FM_MEMKVH
-      } else {
-#define FM_MEMKV(HDV) hipLaunchKernelGGL((k_mem_kv_store<float, HDV>), dim3(D.M), dim3(256), 0, c->stream, kv, (float*)Km, (float*)Vm, D.H, D.M)
-        if (D.hd == 64) FM_MEMKV(64); else if (D.hd == 96) FM_MEMKV(96); else FM_MEMKV(128);
-#undef FM_MEMKV
       }
+  }
+  hipLaunchKernelGGL(k_reset_seq, dim3(1), dim3(64), 0, c->stream, c->st, D, seq, D.nbins);
+  HIPCHK(c, hipGetLastError());
+  return FM_OK;
+}
+
+int prefill_f32(fm_ctx* c, int seq, const float* mem_dev, void* stage_area) {
+  const Dims& D = c->D;
+  const int d = D.d;
+  float* memT = (float*)stage_area;  // [M*d], then [M][2d]
+  float* kv = memT + (size_t)D.M * d;
+  hipLaunchKernelGGL((k_convert<float>), dim3(512), dim3(256), 0, c->stream, mem_dev, memT, (long)D.M * d);
+  for (int st = 0; st < 5; st++)
+    for (auto& L : c->stacks[st]) {
+      gemm<float>(c, EPI_F32, memT, d, 0, L.ckv, 0, kv, 2 * d, 0, nullptr, 0, 0, D.M, 2 * d, d, 1, nullptr);
+      float* Km = (float*)L.Km + (size_t)seq * cache_seq_elems(c, D.M);
+      float* Vm = (float*)L.Vm + (size_t)seq * cache_seq_elems(c, D.M);
+#define FM_MEMKV(HDV) hipLaunchKernelGGL((k_mem_kv_store<float, HDV>), dim3(D.M), dim3(256), 0, c->stream, kv, Km, Vm, D.H, D.M)
+      if (D.hd == 64) FM_MEMKV(64); else if (D.hd == 96) FM_MEMKV(96); else FM_MEMKV(128);
+#undef FM_MEMKV
     }
   hipLaunchKernelGGL(k_reset_seq, dim3(1), dim3(64), 0, c->stream, c->st, D, seq, D.nbins);
   HIPCHK(c, hipGetLastError());
@@ -1033,7 +1045,7 @@ int build_buffers(fm_ctx* c) {
   size_t big = std::max((size_t)c->ff * d, (size_t)c->hff * d);
   big = std::max(big, 3 * d * d);
   big = std::max(big, (size_t)D.V * d);
-  c->stage_elems = std::max(big, (size_t)D.M * d + (size_t)D.M * 2 * d);
+  c->stage_elems = std::max(big, (size_t)(D.M + 31) / 32 * 32 * d + (size_t)D.M * 2 * d);
   TRY(dalloc(c, &c->stage, c->stage_elems));
   // draft rows
   const size_t nset[5] = {S * D.Dc, S * D.nspv, S * D.nspf, S * D.nhfv, S * 2 * D.nhfc};
@@ -1110,11 +1122,8 @@ int build_buffers(fm_ctx* c) {
   c->db = DraftBufs{c->tap_c, c->tap_v, c->tap_f, c->ring_yf, c->spv_out, c->spf_out, c->hfv_out, spv_rs, spf_rs};
   TRY(dalloc(c, &c->gen_tok, S * D.Bm)); TRY(dalloc(c, &c->gen_len, S)); TRY(dalloc(c, &c->gen_acc, S));
   if (c->persist) TRY(build_persist(c));
-  c->mres = MfmaRes{};
   if (c->bf16) {
-    // tiled prefill GEMM: whole 256 x 128 output tiles only (keys x dims for V, dims x keys for K)
-    const char* pt = getenv("FM_PREFILL_TILED");     // "0" forces the per-block GEMM + scatter launches
-    if (D.M % 256 == 0 && d % 256 == 0 && !(pt && pt[0] == '0')) {
+    if (d >= 128) {            // one launch for all blocks; narrower models: one GEMM and one scatter launch per block
       std::vector<PrefillLayer> tab;
       for (int st = 0; st < 5; st++)
         for (auto& L : c->stacks[st]) tab.push_back(PrefillLayer{(const f16_t*)L.ckv, (f16_t*)L.Km, (f16_t*)L.Vm});
@@ -1123,9 +1132,9 @@ int build_buffers(fm_ctx* c) {
       c->pf_layers = (PrefillLayer*)raw;
       HIPCHK(c, hipMemcpy(c->pf_layers, tab.data(), tab.size() * sizeof(PrefillLayer), hipMemcpyHostToDevice));
       c->pf_n = (int)tab.size();
-      HIPCHK(c, hipFuncSetAttribute((const void*)k_prefill_kv<64>, hipFuncAttributeMaxDynamicSharedMemorySize, PF_LDS_BYTES));
-      HIPCHK(c, hipFuncSetAttribute((const void*)k_prefill_kv<96>, hipFuncAttributeMaxDynamicSharedMemorySize, PF_LDS_BYTES));
-      HIPCHK(c, hipFuncSetAttribute((const void*)k_prefill_kv<128>, hipFuncAttributeMaxDynamicSharedMemorySize, PF_LDS_BYTES));
+#define FM_PREFILL_LDS(HDV, E) HIPCHK(c, hipFuncSetAttribute((const void*)k_prefill_kv<HDV, E>, hipFuncAttributeMaxDynamicSharedMemorySize, PF_LDS_BYTES))
+      FM_PREFILL_LDS(64, false); FM_PREFILL_LDS(64, true); FM_PREFILL_LDS(96, false); FM_PREFILL_LDS(96, true); FM_PREFILL_LDS(128, false); FM_PREFILL_LDS(128, true);
+#undef FM_PREFILL_LDS
       hipDeviceProp_t prop;
       int dev = 0;
       HIPCHK(c, hipGetDevice(&dev));
@@ -1294,7 +1303,7 @@ int fm_prefill_condition(fm_ctx* c, int32_t seq, const float* mem_dev) {
   if (!c->weights_loaded) return fail(c, FM_ESTATE, "weights not loaded");
   if (seq < 0 || seq >= c->D.S) return fail(c, FM_EINVAL, "sequence %d out of range [0,%d)", seq, c->D.S);
   if (!mem_dev) return fail(c, FM_EINVAL, "null condition memory");
-  int rc = c->bf16 ? prefill_impl<f16_t>(c, seq, mem_dev, c->stage) : prefill_impl<float>(c, seq, mem_dev, c->stage);
+  int rc = c->bf16 ? prefill_half(c, seq, mem_dev, c->stage) : prefill_f32(c, seq, mem_dev, c->stage);
   if (rc == FM_OK) c->prefilled[seq] = true;
   return rc;
 }
@@ -1309,7 +1318,7 @@ int fm_prefill_condition_static(fm_ctx* c, int32_t seq, const float* mem_dev) {
   if (need > FM_STATIC_SCRATCH_BYTES)
     return fail(c, FM_EINVAL, "condition memory of %d x %d needs %zu staging bytes, the static area holds %u: use fm_prefill_condition",
                 c->D.M, c->D.d, need, (unsigned)FM_STATIC_SCRATCH_BYTES);
-  int rc = c->bf16 ? prefill_impl<f16_t>(c, seq, mem_dev, c->static_scratch) : prefill_impl<float>(c, seq, mem_dev, c->static_scratch);
+  int rc = c->bf16 ? prefill_half(c, seq, mem_dev, c->static_scratch) : prefill_f32(c, seq, mem_dev, c->static_scratch);
   if (rc == FM_OK) c->prefilled[seq] = true;
   return rc;
 }

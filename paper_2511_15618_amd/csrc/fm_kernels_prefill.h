@@ -35,20 +35,22 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 #define PF_WAIT_VM(N) __builtin_amdgcn_s_waitcnt(0x0F70 | ((N) & 15) | (((N) >> 4) << 14))
 
 // Launch: gridDim.x a multiple of 8 (one workgroup per compute unit), 256 threads, PF_LDS_BYTES of dynamic LDS.
-// Needs M % 256 == 0, d % 256 == 0 (whole tiles), KT = d / 32 and HD (the head width, a multiple of 32) dividing d.
-template <int HD>
+// EDGE = false: M and d are multiples of 256 (whole tiles; the clamps cost 4 %).  EDGE = true: any M; d a multiple of HD (the head width, a multiple of 32) and at least 128 (KT = d / 32 >= 4: the stages of one tile cover
+// the ring).  Tiles that reach past the last memory row or weight row are multiplied whole, their fragments clamped to the last
+// one that exists, and store only what exists (whole 32-key blocks: Xt holds zero rows up to a multiple of 32).
+template <int HD, bool EDGE>
 __global__ __launch_bounds__(256, 1) void k_prefill_kv(const f16_t* __restrict__ Xt, const PrefillLayer* __restrict__ layers,
                                                        long seq_off, int KT, int d, int M, int n_layers) {
   extern __shared__ pf_u32x4 pf_smem[];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int wm = wave >> 1, wn = wave & 1;
-  const int nx = M >> 8, nw = d >> 8;
+  const int nx = (M + 255) >> 8, nw = (d + 255) >> 8;
   const int total = 2 * nx * nw * n_layers;
   // A 32-row x 16-k operand of the 32x32x16 MFMA (lane l: row l%32, k (l/32)*8..+8) is gathered from two of the
   // stored 16-row x 32-k fragments: half h of the K-step, row group (l%32)/16 -> stored lane (2h + l/32)*16 + l%16.
   const int lrow = ((lane & 31) >> 4) * 64 + (lane >> 5) * 16 + (lane & 15);
   const int xbase = wm * 512 + lrow, wbase = 1024 + wn * 512 + lrow;
-  const int capb = M >> 5;
+  const int capb = (M + 31) >> 5;
 
   // Tile sequence.  Workgroup b runs on die b % 8, and each die has its own L2: a die takes gridDim/8 consecutive
   // tiles of the sequence per round, and the sequence is ordered in groups of XT memory tiles x all 2 nw weight tiles
@@ -59,7 +61,7 @@ __global__ __launch_bounds__(256, 1) void k_prefill_kv(const f16_t* __restrict__
   int n_my = 0;
   while (tile_of(n_my) < total) n_my++;
   if (n_my == 0) return;
-  const int XT = (nx & 3) == 0 ? 4 : 1;
+  const int XT = nx % 4 == 0 ? 4 : nx % 3 == 0 ? 3 : nx % 2 == 0 ? 2 : 1;
   // The result tile of a workgroup is 256 rows of operand A by 256 rows of operand B.  V tiles are c W_v^T
   // (A = memory rows = keys, B = W_v rows = dims), K tiles are W_k c^T (A = W_k rows = dims, B = keys): the
   // two kinds differ only in where A and B come from and in the epilogue.
@@ -80,17 +82,21 @@ __global__ __launch_bounds__(256, 1) void k_prefill_kv(const f16_t* __restrict__
   typedef __attribute__((address_space(3))) void* lvoid_t;
   int c_r = 0, c_kt = 0, c_slot = 0;
   gptr_t c_src;
+  const int fstride = KT * 64;
+  int c_off[EDGE ? 8 : 1];       // fragment j of this wave: offset from the first in 16-byte elements (whole tiles: j * KT * 64)
   auto cursor_tile = [&](int r) {
     int a0, b0, layer; bool is_v;
     desc(tile_of(r), a0, b0, is_v, layer);
     const pf_u32x4* W = reinterpret_cast<const pf_u32x4*>(layers[layer].W);
     const pf_u32x4* X = reinterpret_cast<const pf_u32x4*>(Xt);
-    const pf_u32x4* Ab = is_v ? X + (long)(a0 / 16) * KT * 64 : W + (long)(a0 / 16) * KT * 64;
-    const pf_u32x4* Bb = is_v ? W + (long)((d + b0) / 16) * KT * 64 : X + (long)(b0 / 16) * KT * 64;
-    c_src = (gptr_t)((wave < 2 ? Ab : Bb) + (long)((wave & 1) * 8) * KT * 64 + lane);
+    // this wave's operand: rows of the memory (16 capb / 8 fragments of 16 rows), or of W_v / W_k (d / 16)
+    const bool mem = is_v == (wave < 2);
+    const int f0 = (wave < 2 ? a0 : b0) / 16 + (wave & 1) * 8, last = (mem ? capb * 2 : d / 16) - 1, first = EDGE ? min(f0, last) : f0;
+    c_src = (gptr_t)((mem ? X : W + (is_v ? (long)(d / 16) * KT * 64 : 0)) + (long)first * KT * 64 + lane);
+#pragma unroll
+    for (int j = 0; j < (EDGE ? 8 : 0); j++) c_off[j] = (min(f0 + j, last) - first) * KT * 64;
   };
   cursor_tile(0);
-  const int fstride = KT * 64;
   // the loads of the next stage of the stream into the next ring slot: lane l of a load writes its 16 bytes at
   // (wave-uniform LDS address) + 16 l, which is the fragment order the operands are read in
   auto issue = [&]() {
@@ -98,7 +104,7 @@ __global__ __launch_bounds__(256, 1) void k_prefill_kv(const f16_t* __restrict__
     gptr_t src = c_src + c_kt * 64;
 #pragma unroll
     for (int j = 0; j < 8; j++)
-      __builtin_amdgcn_global_load_lds((gvoid_t)(src + j * fstride), (lvoid_t)(dst + j * 64), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((gvoid_t)(src + (EDGE ? c_off[EDGE ? j : 0] : j * fstride)), (lvoid_t)(dst + j * 64), 16, 0, 0);
     c_slot = c_slot + 1 == PF_STAGES ? 0 : c_slot + 1;
     // past the end the cursor stays on the last stage: the extra loads land in a slot nobody reads any more
     if (c_kt + 1 < KT) c_kt++;
@@ -159,10 +165,13 @@ __global__ __launch_bounds__(256, 1) void k_prefill_kv(const f16_t* __restrict__
   __builtin_amdgcn_s_barrier();
   int slot_c = 0;
   PF_READ(cx, cw, pf_smem, 0);
+  // whether the last epilogue issued all of its PF_STORES stores: only then may a wait count on them being in flight (a tile at
+  // the edge skips some, and its next stages wait for the loads alone, which is always enough)
+  bool all_stores = true;
   for (int r = 0; r < n_my; r++) {
     int kt0 = 0;
     if (r > 0)
-      for (; kt0 < PF_STAGES - 2; kt0++) PF_STAGE(true, true);
+      for (; kt0 < PF_STAGES - 2; kt0++) PF_STAGE(true, !EDGE || all_stores);
     for (int kt = kt0; kt < KT - 1; kt++) PF_STAGE(true, false);
     PF_STAGE(false, false);
     {
@@ -170,6 +179,7 @@ __global__ __launch_bounds__(256, 1) void k_prefill_kv(const f16_t* __restrict__
       // column l%32 (a row of B) and the A rows (j/4)*8 + (l/32)*4 + j%4, j = 0..15, i.e. four runs of four rows.
       int a0, b0, layer; bool is_v;
       desc(tile_of(r), a0, b0, is_v, layer);
+      if (EDGE) all_stores = (is_v ? b0 : a0) + 256 <= d && ((is_v ? a0 : b0) >> 5) + 8 <= capb;
       const PrefillLayer L = layers[layer];
       const int hl4 = (lane >> 5) * 4, c32 = lane & 31;
       typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
@@ -184,13 +194,14 @@ __global__ __launch_bounds__(256, 1) void k_prefill_kv(const f16_t* __restrict__
             // rows = keys, column = dim.  Keys r..r+3 and r+16..r+19 of a block sit next to each other in the V
             // layout: runs j/4 = q and q+2 make one 16-byte store
             const int row0 = a0 + wm * 128 + x * 32 + hl4;
+            const bool on = !EDGE || (col < d && (row0 >> 5) < capb);
             f16_t* base = L.Vm + seq_off + (long)(col / HD) * capb * (32 * HD);
 #pragma unroll
             for (int q = 0; q < 2; q++) {
               f16x8o o;
 #pragma unroll
               for (int i = 0; i < 4; i++) { o[i] = (f16_t)acc[x][w][q * 4 + i]; o[4 + i] = (f16_t)acc[x][w][(q + 2) * 4 + i]; }
-              *(__attribute__((address_space(1))) f16x8o*)(base + vblk_off<HD>(row0 + q * 8, col % HD)) = o;
+              if (on) *(__attribute__((address_space(1))) f16x8o*)(base + vblk_off<HD>(row0 + q * 8, col % HD)) = o;
             }
           } else {
             // rows = dims, column = key.  Lanes l and l+32 hold dims 0-3 and 4-7 of the same 8-dim run of a key, which
@@ -207,7 +218,7 @@ __global__ __launch_bounds__(256, 1) void k_prefill_kv(const f16_t* __restrict__
               const auto s1 = __builtin_amdgcn_permlane32_swap(l2[1], h2[1], false, false);
               const pf_u32x4 o = {s0[0], s1[0], s0[1], s1[1]};
               const int e0 = a0 + wm * 128 + x * 32 + (2 * qp + (lane >> 5)) * 8;   // first dim of the run this lane stores
-              *(__attribute__((address_space(1))) pf_u32x4*)(L.Km + seq_off + (long)(e0 / HD) * capb * (32 * HD) + kblk_off<HD>(col, e0 % HD)) = o;
+              if (!EDGE || (e0 < d && (col >> 5) < capb)) *(__attribute__((address_space(1))) pf_u32x4*)(L.Km + seq_off + (long)(e0 / HD) * capb * (32 * HD) + kblk_off<HD>(col, e0 % HD)) = o;
             }
           }
 #pragma unroll
