@@ -455,8 +455,8 @@ int level_rps(const fm_ctx* c, int level) { return level == 0 ? c->D.Bm : level 
 void refuse(fm_ctx* c, const char* what) { fail(c, FM_EINVAL, "%s: unsupported row set", what); c->sticky_error = true; }
 
 // one transformer block on the row set of `level` (Sec. 3.1: self-attention, cross-attention to c, FFN).  next_gain: gain of
-// the norm behind the block (null: none reads its output).  tap / ring: rings that receive the block's input / output rows.
-void run_block_h(fm_ctx* c, const Layer& L, int level, const float* next_gain, float* tap, float* ring, int rs) {
+// the norm behind the block (null: none reads its output); next_qkv: first weights of the block behind it (may be null).  tap / ring: rings that receive the block's input / output rows.
+void run_block_h(fm_ctx* c, const Layer& L, int level, const float* next_gain, float* tap, float* ring, int rs, const void* next_qkv) {
   const Dims& D = c->D;
   const int d = D.d, rows = level_rows(c, level), RPS = level_rps(c, level), cap = level_cap(c, level);
   const int* flag = c->st.alive;
@@ -474,8 +474,22 @@ void run_block_h(fm_ctx* c, const Layer& L, int level, const float* next_gain, f
     a.gain = gain; a.X = gain ? c->xg[level] : nullptr; a.ssq_out = gain ? c->ssq[level] : nullptr;
     return a;
   };
-  auto attn = [&](const int* limit, void* K, void* V, int kcap, int window) {
+  // Weights that the attention launches read ahead (k_dec_attn): the two projections behind each always; behind the cross-attention all
+  // up to the next attention where they and the memory's keys and values stay under 48 MB.  Beyond that the launch is bound by
+  // its own stream or L2 (32 MB) does not keep what it read: d = 768 x 3: 1286 -> 1223 us a step with all, 1259 with the projections;
+  // d = 1024, one sequence: 2286 -> 2132, 2222; eight sequences (134 MB of keys and values): 3220 -> 3327, 3214; d = 1536 x 4: 4173 -> 4370, 4122.
+  const double cross_bytes = 4.0 * D.S * D.M * d + 2.0 * d * d + 4.0 * d * c->ff + 6.0 * d * d;
+  auto attn = [&](const int* limit, void* K, void* V, int kcap, int window, bool cross) {
     AttnArgs t{};
+    int n = 0;
+    auto ahead = [&](const void* W, int N, int Kw) { if (W) t.next[n++] = WeightRange{(const f16_t*)W, Kw / 32 * 1024, N / 16}; };
+    if (cross) {
+      ahead(L.co, d, d);
+      if (cross_bytes <= 48e6) { ahead(L.w1, c->ff, d); ahead(L.w2, d, c->ff); ahead(next_qkv, 3 * d, d); }
+    } else {
+      ahead(L.wo, d, d);
+      ahead(L.cq, d, d);
+    }
     t.S = D.S; t.H = D.H; t.ws = c->attn_ws; t.arrived = c->attn_arrived; t.run_flag = flag;
     t.set[0] = AttnSet{(const f16_t*)c->qT, limit, RPS, 0, RPS, (const f16_t*)K, (const f16_t*)V, (long)cache_seq_elems(c, kcap), (kcap + 31) / 32, window, 1,
                        RowMap{1, RPS, 0, 0}, c->attX};
@@ -487,7 +501,7 @@ void run_block_h(fm_ctx* c, const Layer& L, int level, const float* next_gain, f
     a.Kc = (f16_t*)L.Kc; a.Vc = (f16_t*)L.Vc; a.seq_stride = (long)cache_seq_elems(c, cap); a.capb = (cap + 31) / 32;
     dec_gemm<DE_QKV, true>(a, 1, c->stream);
   }
-  attn(c->pos[level], L.Kc, L.Vc, cap, level_window(c, level));
+  attn(c->pos[level], L.Kc, L.Vc, cap, level_window(c, level), false);
   {
     DecGemm a = residual(c->attX, L.wo, d, L.g2);
     if (tap) { a.tap = tap; a.pos = c->pos[level]; a.rs = rs; }
@@ -498,7 +512,7 @@ void run_block_h(fm_ctx* c, const Layer& L, int level, const float* next_gain, f
     a.Y = c->qT; a.ldy = d;
     dec_gemm<DE_ROW, true>(a, 1, c->stream);
   }
-  attn(c->limx[level], L.Km, L.Vm, D.M, 0);
+  attn(c->limx[level], L.Km, L.Vm, D.M, 0, true);
   dec_gemm<DE_RES, false>(residual(c->attX, L.co, d, L.g3), 1, c->stream);
   {
     DecGemm a = normed(L.w1, c->ff);
@@ -525,7 +539,7 @@ void forward_h(fm_ctx* c, float* logits) {
     for (size_t i = 0; i < n; i++) {
       const bool last = i + 1 == n;
       const float* gain = !last ? c->stacks[st][i + 1].g1 : st == 4 ? c->gf : nullptr;
-      run_block_h(c, c->stacks[st][i], level, gain, last ? tap[st] : nullptr, last ? ring[st] : nullptr, rsz[level]);
+      run_block_h(c, c->stacks[st][i], level, gain, last ? tap[st] : nullptr, last ? ring[st] : nullptr, rsz[level], !last ? c->stacks[st][i + 1].wqkv : nullptr);
     }
     if (st < 2) {          // shorten onto the next coarser level
       const int cl = st + 1;

@@ -306,12 +306,16 @@ struct AttnSet {
   f16_t* out;
 };
 #define FM_ATTN_SETS 4
+// Weights that a launch reads ahead for the ones behind it: `groups` column tiles of `bytes` each.
+struct WeightRange { const f16_t* W; int bytes, groups; };
 struct AttnArgs {
   AttnSet set[FM_ATTN_SETS];     // first member of the only kernel argument (attn_set)
   int S, H, ns_max;
   unsigned* arrived;         // [set][sequence][head] splits that have published their part, zero between launches
   float* ws;                 // [set][sequence][head][ns_max][QT*16*HD unnormalised O | QT*16 running max (log2 units) | QT*16 sums]
   const int* run_flag;
+  int nset, ahead;           // planes of the grid (blockIdx.z) that attend: nset * S; `ahead` more read weights ahead
+  WeightRange next[4];
 };
 // the set of this workgroup, read from the argument segment itself: indexing the by-value argument would copy it to scratch memory
 typedef const __attribute__((address_space(4))) AttnSet* attn_set_t;
@@ -337,6 +341,26 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int g = lane >> 4, ql = lane & 15;
   const int hh = blockIdx.x, split = blockIdx.y, s = blockIdx.z % a.S, z = blockIdx.z / a.S;
+  if (z >= a.nset) {
+    // Read ahead: the GEMMs behind this launch wait for cold weights, about a third of their 4 us, while a short attention leaves the
+    // memory idle.  L2 outlives a launch; each die has its own, and workgroup i runs on die i mod 8, as do the column tiles
+    // i mod 8 of a GEMM (only the speed depends on that).  The data goes to LDS and is never looked at.
+    const int plane = gridDim.x * gridDim.y, base = plane * a.nset * a.S, id = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
+    const int die = id & 7, rank = (id - base) >> 3, ranks = max(1, (plane * a.ahead) >> 3);
+    if (rank >= ranks) return;
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      const int bytes = a.next[r].bytes, groups = a.next[r].groups;
+      for (int x = die + 8 * rank; x < groups; x += 8 * ranks) {
+        const char* src = (const char*)a.next[r].W + (long)x * bytes + lane * 16;
+        for (int o = wave * 1024; o < bytes; o += NW * 1024)
+          __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + o),
+                                           (__attribute__((address_space(3))) void*)((char*)da_smem + wave * 1024), 16, 0, 0);
+      }
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0)
+    return;
+  }
   const attn_set_t A = attn_set(z);
   const RowMap rm{A->rm.G, A->rm.mult, A->rm.base, A->rm.tiles};
   if (split >= A->ns) return;
@@ -684,7 +708,7 @@ template <int QT, int HD, int NW>
 void dec_attn_go(const AttnArgs& a, int nset, hipStream_t st) {
   const size_t lds = ((size_t)NW * QT * 16 * (HD + 4) + 2 * NW * QT * 16) * 4;
   if (lds > 65536) (void)hipFuncSetAttribute((const void*)k_dec_attn<QT, HD, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  hipLaunchKernelGGL((k_dec_attn<QT, HD, NW>), dim3(a.H, a.ns_max, a.S * nset), dim3(NW * 64), lds, st, a);
+  hipLaunchKernelGGL((k_dec_attn<QT, HD, NW>), dim3(a.H, a.ns_max, a.S * nset + a.ahead), dim3(NW * 64), lds, st, a);
 }
 
 // Attention of `nset` row sets (at most 32 rows each) in one launch.
@@ -698,6 +722,8 @@ inline bool dec_attention(AttnArgs& a, int nset, int hd, hipStream_t st) {
     a.set[z].ns = attn_splits((long)a.H * a.S * nset, a.set[z].capb, NW);
     if (a.set[z].ns > a.ns_max) a.ns_max = a.set[z].ns;
   }
+  a.nset = nset;
+  a.ahead = a.next[0].W ? (48 + a.H * a.ns_max - 1) / (a.H * a.ns_max) : 0;      // about 48 workgroups (32 to 128: no difference)
   if (hd == 64) { if (QT == 1) dec_attn_go<1, 64, NW>(a, nset, st); else dec_attn_go<2, 64, NW>(a, nset, st); }
   else if (hd == 96) { if (QT == 1) dec_attn_go<1, 96, NW>(a, nset, st); else dec_attn_go<2, 96, NW>(a, nset, st); }
   else { if (QT == 1) dec_attn_go<1, 128, NW>(a, nset, st); else dec_attn_go<2, 128, NW>(a, nset, st); }
