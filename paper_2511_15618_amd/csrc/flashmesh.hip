@@ -1160,10 +1160,11 @@ int build_buffers(fm_ctx* c) {
     return fail(c, FM_ENOMEM, "hipHostMalloc failed");
   memset(c->prog, 0, sizeof(Progress));
   for (int i = 0; i < fm_ctx::E_COUNT; i++) HIPCHK(c, hipEventCreate(&c->ev[i]));
-  // fp32 launches are shorter than the host needs to enqueue one; the half path's are longer, and there a graph only adds its own
-  // 7 us (step of the medium model, one sequence: 2055 us as launches, 2071 us as two graphs).
+  // The launches of the fp32 path and of narrow half-precision models are shorter than the host needs to enqueue one (d = 256, 3 sequences: 18.9
+  // ms a mesh as launches, 15.6 as graphs); from about d = 768 there is no difference, and the single-launch verify kernel leaves
+  // few launches (medium model, one sequence: 2055 us as launches, 2071 us as two graphs).
   const char* ge = getenv("FM_GRAPH");          // "0" / "1": never / always (measurement switch)
-  c->graphs_on = ge ? ge[0] != '0' : !c->bf16;
+  c->graphs_on = ge ? ge[0] != '0' : !c->bf16 || (!c->persist && D.d <= 512);
   return FM_OK;
 }
 
