@@ -100,15 +100,15 @@ struct fm_ctx {
   int *pos[3], *limx[3];
   float2* cs[3];
   float* h[3];
-  void *xn, *qT, *attT, *mid;
-  float *qkv, *logits;
-  // half-precision path, one launch per operator: per level the input of the next norm's GEMM (x * gain, tiled) and the row sums of
+  void* qT;
+  float* logits;
+  // one launch per operator: per level the input of the next norm's GEMM (x * gain, tiled) and the row sums of
   // squares; attention output and FFN hidden rows (tiled), queries, attention workspace
-  f16_t *xg[3], *attX, *midX;
+  void *xg[3], *attX, *midX;
   float* ssq[3];
   float* attn_ws;
   unsigned* attn_arrived;
-  f16_t *dX, *dmidX;  // draft heads: tiled rows of a grouped GEMM, FFN hidden rows
+  void *dX, *dmidX;   // draft heads: tiled rows of a grouped GEMM, FFN hidden rows
   int sp_tiles = 1, hf_tiles[2] = {1, 1};   // row tiles per parameter set: SP heads; HF sets (vertex, coordinate)
   float* stage;       // staging for weight conversion / prefill GEMM output
   size_t stage_elems;
@@ -116,9 +116,9 @@ struct fm_ctx {
   // draft scratch
   DraftRows dr;
   DraftBufs db;
-  float *spv_out, *spf_out, *hfv_out, *dh, *dkeep, *dtmp, *dlogits;
+  float *spv_out, *spf_out, *hfv_out, *dh, *dkeep, *dlogits;
   float *dist_c, *dist_v, *dist_f;
-  void *dxn, *dq, *datt, *dmid;
+  void* dq;
   StepParams params{};     // host copy of the settings below, StepParams on the device
   StepParams* params_dev = nullptr;
   int *gen_tok, *gen_len;  // block buffers used by fm_generate
@@ -274,95 +274,9 @@ int level_cap(const fm_ctx* c, int level) { return level == 0 ? c->D.capc : leve
 int level_window(const fm_ctx* c, int level) { return level == 0 ? c->D.wc : level == 1 ? c->D.wv : c->D.wf; }
 const int kStackLevel[5] = {0, 1, 2, 1, 0};
 
-// ------------------------------------------------------------------------------------------
-// launch wrappers
-// ------------------------------------------------------------------------------------------
-template <typename T>
-void gemm(fm_ctx* c, int epi, const void* X, long ldx, long gsx, const void* W, long gsw, void* Y, long ldy, long gsy,
-          const float* R, long ldr, long gsr, int M, int N, int K, int groups, const int* flag) {
-  GemmArgs a{X, ldx, gsx, W, gsw, Y, ldy, gsy, R, ldr, gsr, M, N, K, flag};
-  dim3 grid((N + 3) / 4, groups);
-  if (epi == EPI_F32) hipLaunchKernelGGL((k_gemm_simple<T, EPI_F32>), grid, dim3(256), 0, c->stream, a);
-  else if (epi == EPI_GELU_T) hipLaunchKernelGGL((k_gemm_simple<T, EPI_GELU_T>), grid, dim3(256), 0, c->stream, a);
-  else hipLaunchKernelGGL((k_gemm_simple<T, EPI_T>), grid, dim3(256), 0, c->stream, a);
-}
-
-template <typename T>
-void attention(fm_ctx* c, const void* q, const int* limit, int rows, int RPS, const void* Kc, const void* Vc,
-               long seq_stride, int cap, void* out, const int* flag, int window = 0) {
-#define FM_ATTN(HDV) hipLaunchKernelGGL((k_attn_simple<T, HDV>), dim3(rows, c->D.H), dim3(256), 0, c->stream, (const T*)q, limit, RPS, \
-                                        (const T*)Kc, (const T*)Vc, seq_stride, cap, (T*)out, c->D.H, flag, window)
-  if (c->D.hd == 64) FM_ATTN(64); else if (c->D.hd == 96) FM_ATTN(96); else FM_ATTN(128);
-#undef FM_ATTN
-}
-
-template <typename T>
-void rmsnorm(fm_ctx* c, const float* src, const float* const* srcptr, const float* gain, int gain_mod, void* out,
-             float* keep, int rows, const int* flag) {
-  hipLaunchKernelGGL((k_rmsnorm<T>), dim3(rows), dim3(256), 0, c->stream, src, srcptr, gain, gain_mod, (T*)out, keep,
-                     c->D.d, c->cfg.rms_eps, flag);
-}
-
-// Y = RMSNorm(h; gain) W^T for the rows of the fp32 residual stream h [rows, d]: norm into `xn`, then the GEMM
-template <typename T>
-void gemm_norm(fm_ctx* c, int epi, const float* h, const float* gain, const void* W, void* Y, long ldy, int rows, int N,
-               const int* flag) {
-  const int d = c->D.d;
-  rmsnorm<T>(c, h, nullptr, gain, 0, c->xn, nullptr, rows, flag);
-  gemm<T>(c, epi, c->xn, d, 0, W, 0, Y, ldy, 0, nullptr, 0, 0, rows, N, d, 1, flag);
-}
-
-// rotary position on q (and k), conversion to the storage type, optional append to a K/V cache
-template <typename T>
-void rope_append(fm_ctx* c, const float* qkv, long ldq, const float2* cs, const int* pos, int rows, int RPS, void* q,
-                 void* Kc, void* Vc, int cap, const int* flag) {
-#define FM_ROPE(HDV) hipLaunchKernelGGL((k_rope_append<T, HDV>), dim3(rows), dim3(256), 0, c->stream, qkv, ldq, cs, pos, RPS, (T*)q, \
-                                        (T*)Kc, (T*)Vc, c->D.H, cap, flag)
-  if (c->D.hd == 64) FM_ROPE(64); else if (c->D.hd == 96) FM_ROPE(96); else FM_ROPE(128);
-#undef FM_ROPE
-}
-
 // elements of one (sequence) slice of a K or V cache with `cap` key positions
 size_t cache_seq_elems(const fm_ctx* c, int cap) {
-  return c->bf16 ? (size_t)c->D.H * ((cap + 31) / 32) * 32 * c->D.hd : (size_t)c->D.H * cap * c->D.hd;
-}
-
-// one transformer block on the row set of `level` (Sec. 3.1: self-attention, cross-attention to c, FFN)
-template <typename T>
-void run_block(fm_ctx* c, const Layer& L, int level) {
-  const Dims& D = c->D;
-  const int d = D.d, rows = level == 0 ? c->Rc : level == 1 ? c->Rv : c->Rf;
-  const int RPS = level == 0 ? D.Bm : level == 1 ? D.VB : D.FB;
-  const int cap = level_cap(c, level);
-  float* h = c->h[level];
-  const int* flag = c->st.alive;
-  gemm_norm<T>(c, EPI_F32, h, L.g1, L.wqkv, c->qkv, 3 * d, rows, 3 * d, flag);
-  rope_append<T>(c, c->qkv, (long)3 * d, c->cs[level], c->pos[level], rows, RPS, c->qT, L.Kc, L.Vc, cap, flag);
-  attention<T>(c, c->qT, c->pos[level], rows, RPS, L.Kc, L.Vc, (long)cache_seq_elems(c, cap), cap, c->attT, flag,
-               level_window(c, level));
-  gemm<T>(c, EPI_F32, c->attT, d, 0, L.wo, 0, h, d, 0, h, d, 0, rows, d, d, 1, flag);
-  gemm_norm<T>(c, EPI_T, h, L.g2, L.cq, c->qT, d, rows, d, flag);
-  attention<T>(c, c->qT, c->limx[level], rows, RPS, L.Km, L.Vm, (long)cache_seq_elems(c, D.M), D.M, c->attT, flag);
-  gemm<T>(c, EPI_F32, c->attT, d, 0, L.co, 0, h, d, 0, h, d, 0, rows, d, d, 1, flag);
-  gemm_norm<T>(c, EPI_GELU_T, h, L.g3, L.w1, c->mid, c->ff, rows, c->ff, flag);
-  gemm<T>(c, EPI_F32, c->mid, c->ff, 0, L.w2, 0, h, d, 0, h, d, 0, rows, d, c->ff, 1, flag);
-}
-
-void ring_save(fm_ctx* c, const float* src, float* ring, int level, int RS) {
-  const Dims& D = c->D;
-  const int rows = level == 0 ? c->Rc : level == 1 ? c->Rv : c->Rf;
-  const int RPS = level == 0 ? D.Bm : level == 1 ? D.VB : D.FB;
-  hipLaunchKernelGGL(k_ring_save, dim3(rows), dim3(256), 0, c->stream, src, ring, c->pos[level], RPS, RS, D.d);
-}
-
-template <typename T>
-void run_stack(fm_ctx* c, int stack, float* tap_ring, int tap_rs) {
-  const int level = kStackLevel[stack];
-  const size_t n = c->stacks[stack].size();
-  for (size_t i = 0; i < n; i++) {
-    if (tap_ring && i == n - 1) ring_save(c, c->h[level], tap_ring, level, tap_rs);
-    run_block<T>(c, c->stacks[stack][i], level);
-  }
+  return (size_t)c->D.H * ((cap + 31) / 32) * 32 * c->D.hd;
 }
 
 // Word that the single-launch verify kernel raises when one of its bounded waits gave up (null on the per-operator
@@ -385,69 +299,13 @@ void choose_and_accept(fm_ctx* c, const float* logits, int32_t* accepted) {
 template <typename T>
 void verify_setup(fm_ctx* c, const int32_t* block_tok, const int32_t* block_len, bool embed) {
   const Dims& D = c->D;
-  const bool half = std::is_same<T, f16_t>::value;
   hipLaunchKernelGGL((k_verify_setup<T>), dim3(c->Rc + c->Rv + c->Rf), dim3(256), 0, c->stream, c->st, D, c->inv, block_tok, block_len,
                      c->pos[0], c->pos[1], c->pos[2], c->limx[0], c->limx[1], c->limx[2], c->cs[0], c->cs[1], c->cs[2], c->persist ? c->pk_epoch : nullptr,
-                     embed ? (const T*)c->emb : nullptr, c->h[0], half ? c->xg[0] : nullptr, half ? c->stacks[0][0].g1 : nullptr, half ? c->ssq[0] : nullptr);
-}
-
-template <typename T>
-int verify_impl(fm_ctx* c, const int32_t* block_tok, const int32_t* block_len, float* logits_out, int32_t* accepted) {
-  const Dims& D = c->D;
-  const int d = D.d;
-  verify_setup<T>(c, block_tok, block_len, true);
-  const int* flag = c->st.alive;
-  // coordinate level, first half
-  run_stack<T>(c, 0, nullptr, 0);
-  ring_save(c, c->h[0], c->ring_hc, 0, RS_C);
-  // shorten coordinate -> vertex
-  hipLaunchKernelGGL((k_pool3<T>), dim3(c->Rv), dim3(256), 0, c->stream, c->ring_hc, RS_C, c->pos[1], D.VB, (T*)c->xn, d);
-  gemm<T>(c, EPI_F32, c->xn, d, 0, c->short_cv, 0, c->h[1], d, 0, nullptr, 0, 0, c->Rv, d, d, 1, flag);
-  run_stack<T>(c, 1, nullptr, 0);
-  ring_save(c, c->h[1], c->ring_hv, 1, RS_V);
-  // shorten vertex -> face
-  hipLaunchKernelGGL((k_pool3<T>), dim3(c->Rf), dim3(256), 0, c->stream, c->ring_hv, RS_V, c->pos[2], D.FB, (T*)c->xn, d);
-  gemm<T>(c, EPI_F32, c->xn, d, 0, c->short_vf, 0, c->h[2], d, 0, nullptr, 0, 0, c->Rf, d, d, 1, flag);
-  run_stack<T>(c, 2, c->tap_f, RS_F);
-  ring_save(c, c->h[2], c->ring_yf, 2, RS_F);
-  // upsample face -> vertex (repeat + skip), vertex level second half
-  hipLaunchKernelGGL(k_upsample_add, dim3(c->Rv), dim3(256), 0, c->stream, c->h[1], c->pos[1], D.VB, c->ring_yf, RS_F, d);
-  run_stack<T>(c, 3, c->tap_v, RS_V);
-  ring_save(c, c->h[1], c->ring_yv, 1, RS_V);
-  // upsample vertex -> coordinate, coordinate level second half
-  hipLaunchKernelGGL(k_upsample_add, dim3(c->Rc), dim3(256), 0, c->stream, c->h[0], c->pos[0], D.Bm, c->ring_yv, RS_V, d);
-  run_stack<T>(c, 4, c->tap_c, RS_C);
-  // output head, greedy prediction, acceptance
-  float* lg = logits_out ? logits_out : c->logits;
-  gemm_norm<T>(c, EPI_F32, c->h[0], c->gf, c->lm, lg, D.V, c->Rc, D.V, flag);
-  choose_and_accept(c, lg, accepted);
-  HIPCHK(c, hipGetLastError());
-  return FM_OK;
-}
-
-// SP head chain (Eq. 1) for the row set `set` of one level; writes fp32 features to out (row stride ldo)
-template <typename T>
-void run_sp(fm_ctx* c, int set, const SpLevel& sp, const Layer& last, int level, float* out, long ldo, long gso,
-            const int* flag) {
-  const Dims& D = c->D;
-  const int d = D.d, G = sp.cnt, rows = D.S * G;
-  if (G == 0) return;
-  const int cap = level_cap(c, level);
-  const long dd = (long)d * d;
-  rmsnorm<T>(c, nullptr, c->dr.src[set], sp.g, G, c->dxn, c->dkeep, rows, flag);
-  gemm<T>(c, EPI_F32, c->dxn, (long)G * d, d, sp.wq, dd, c->dtmp, (long)G * d, d, nullptr, 0, 0, D.S, d, d, G, flag);
-  rope_append<T>(c, c->dtmp, (long)d, c->dr.cs[set], c->dr.pos[set], rows, G, c->dq, nullptr, nullptr, cap, flag);
-  attention<T>(c, c->dq, c->dr.lim[set], rows, G, last.Kc, last.Vc, (long)cache_seq_elems(c, cap), cap, c->datt, flag,
-               level_window(c, level));
-  gemm<T>(c, EPI_T, c->datt, (long)G * d, d, sp.wo, dd, c->dxn, (long)G * d, d, nullptr, 0, 0, D.S, d, d, G, flag);
-  gemm<T>(c, EPI_T, c->dxn, (long)G * d, d, sp.cq, dd, c->dq, (long)G * d, d, nullptr, 0, 0, D.S, d, d, G, flag);
-  attention<T>(c, c->dq, c->dr.limx[set], rows, G, last.Km, last.Vm, (long)cache_seq_elems(c, D.M), D.M, c->datt, flag);
-  gemm<T>(c, EPI_T, c->datt, (long)G * d, d, sp.co, dd, c->dxn, (long)G * d, d, nullptr, 0, 0, D.S, d, d, G, flag);
-  gemm<T>(c, EPI_F32, c->dxn, (long)G * d, d, sp.lin, dd, out, ldo, gso, c->dkeep, (long)G * d, d, D.S, d, d, G, flag);
+                     embed ? (const T*)c->emb : nullptr, c->h[0], (T*)c->xg[0], c->stacks[0][0].g1, c->ssq[0]);
 }
 
 // ------------------------------------------------------------------------------------------
-// Half-precision path, one launch per operator (fm_kernels_decode.h)
+// One launch per operator (fm_kernels_decode.h), in both storage types
 // ------------------------------------------------------------------------------------------
 int level_rows(const fm_ctx* c, int level) { return level == 0 ? c->Rc : level == 1 ? c->Rv : c->Rf; }
 int level_rps(const fm_ctx* c, int level) { return level == 0 ? c->D.Bm : level == 1 ? c->D.VB : c->D.FB; }
@@ -456,7 +314,8 @@ void refuse(fm_ctx* c, const char* what) { fail(c, FM_EINVAL, "%s: unsupported r
 
 // one transformer block on the row set of `level` (Sec. 3.1: self-attention, cross-attention to c, FFN).  next_gain: gain of
 // the norm behind the block (null: none reads its output); next_qkv: first weights of the block behind it (may be null).  tap / ring: rings that receive the block's input / output rows.
-void run_block_h(fm_ctx* c, const Layer& L, int level, const float* next_gain, float* tap, float* ring, int rs, const void* next_qkv) {
+template <typename T>
+void run_block(fm_ctx* c, const Layer& L, int level, const float* next_gain, float* tap, float* ring, int rs, const void* next_qkv) {
   const Dims& D = c->D;
   const int d = D.d, rows = level_rows(c, level), RPS = level_rps(c, level), cap = level_cap(c, level);
   const int* flag = c->st.alive;
@@ -464,12 +323,12 @@ void run_block_h(fm_ctx* c, const Layer& L, int level, const float* next_gain, f
   b.M = rows; b.run_flag = flag; b.eps = c->cfg.rms_eps; b.RPS = RPS; b.H = D.H; b.hd = D.hd;
   auto normed = [&](const void* W, int N) {
     DecGemm a = b;
-    a.A = c->xg[level]; a.W = (const f16_t*)W; a.N = N; a.KT = d / 32; a.ssq = c->ssq[level]; a.inv_k = 1.0f / d;
+    a.A = c->xg[level]; a.W = W; a.N = N; a.KT = d / 32; a.ssq = c->ssq[level]; a.inv_k = 1.0f / d;
     return a;
   };
-  auto residual = [&](const f16_t* X, const void* W, int K, const float* gain) {
+  auto residual = [&](const void* X, const void* W, int K, const float* gain) {
     DecGemm a = b;
-    a.A = X; a.W = (const f16_t*)W; a.N = d; a.KT = K / 32;
+    a.A = X; a.W = W; a.N = d; a.KT = K / 32;
     a.Y = c->h[level]; a.ldy = d; a.R = c->h[level]; a.ldr = d;
     a.gain = gain; a.X = gain ? c->xg[level] : nullptr; a.ssq_out = gain ? c->ssq[level] : nullptr;
     return a;
@@ -478,11 +337,11 @@ void run_block_h(fm_ctx* c, const Layer& L, int level, const float* next_gain, f
   // up to the next attention where they and the memory's keys and values stay under 48 MB.  Beyond that the launch is bound by
   // its own stream or L2 (32 MB) does not keep what it read: d = 768 x 3: 1286 -> 1223 us a step with all, 1259 with the projections;
   // d = 1024, one sequence: 2286 -> 2132, 2222; eight sequences (134 MB of keys and values): 3220 -> 3327, 3214; d = 1536 x 4: 4173 -> 4370, 4122.
-  const double cross_bytes = 4.0 * D.S * D.M * d + 2.0 * d * d + 4.0 * d * c->ff + 6.0 * d * d;
+  const double cross_bytes = sizeof(T) * (2.0 * D.S * D.M * d + 4.0 * d * d + 2.0 * d * c->ff);
   auto attn = [&](const int* limit, void* K, void* V, int kcap, int window, bool cross) {
     AttnArgs t{};
     int n = 0;
-    auto ahead = [&](const void* W, int N, int Kw) { if (W) t.next[n++] = WeightRange{(const f16_t*)W, Kw / 32 * 1024, N / 16}; };
+    auto ahead = [&](const void* W, int N, int Kw) { if (W) t.next[n++] = WeightRange{W, Kw / 32 * 1024, N / 16}; };
     if (cross) {
       ahead(L.co, d, d);
       if (cross_bytes <= 48e6) { ahead(L.w1, c->ff, d); ahead(L.w2, d, c->ff); ahead(next_qkv, 3 * d, d); }
@@ -491,43 +350,44 @@ void run_block_h(fm_ctx* c, const Layer& L, int level, const float* next_gain, f
       ahead(L.cq, d, d);
     }
     t.S = D.S; t.H = D.H; t.ws = c->attn_ws; t.arrived = c->attn_arrived; t.run_flag = flag;
-    t.set[0] = AttnSet{(const f16_t*)c->qT, limit, RPS, 0, RPS, (const f16_t*)K, (const f16_t*)V, (long)cache_seq_elems(c, kcap), (kcap + 31) / 32, window, 1,
+    t.set[0] = AttnSet{c->qT, limit, RPS, 0, RPS, K, V, (long)cache_seq_elems(c, kcap), (kcap + 31) / 32, window, 1,
                        RowMap{1, RPS, 0, 0}, c->attX};
-    if (!dec_attention(t, 1, D.hd, c->stream)) refuse(c, "attention");
+    if (!dec_attention<T>(t, 1, D.hd, c->stream)) refuse(c, "attention");
   };
   {
     DecGemm a = normed(L.wqkv, 3 * d);
     a.Y = c->qT; a.ldy = d; a.cs = c->cs[level]; a.pos = c->pos[level];
-    a.Kc = (f16_t*)L.Kc; a.Vc = (f16_t*)L.Vc; a.seq_stride = (long)cache_seq_elems(c, cap); a.capb = (cap + 31) / 32;
-    dec_gemm<DE_QKV, true>(a, 1, c->stream);
+    a.Kc = L.Kc; a.Vc = L.Vc; a.seq_stride = (long)cache_seq_elems(c, cap); a.capb = (cap + 31) / 32;
+    dec_gemm<T, DE_QKV, true>(a, 1, c->stream);
   }
   attn(c->pos[level], L.Kc, L.Vc, cap, level_window(c, level), false);
   {
     DecGemm a = residual(c->attX, L.wo, d, L.g2);
     if (tap) { a.tap = tap; a.pos = c->pos[level]; a.rs = rs; }
-    dec_gemm<DE_RES, false>(a, 1, c->stream);
+    dec_gemm<T, DE_RES, false>(a, 1, c->stream);
   }
   {
     DecGemm a = normed(L.cq, d);
     a.Y = c->qT; a.ldy = d;
-    dec_gemm<DE_ROW, true>(a, 1, c->stream);
+    dec_gemm<T, DE_ROW, true>(a, 1, c->stream);
   }
   attn(c->limx[level], L.Km, L.Vm, D.M, 0, true);
-  dec_gemm<DE_RES, false>(residual(c->attX, L.co, d, L.g3), 1, c->stream);
+  dec_gemm<T, DE_RES, false>(residual(c->attX, L.co, d, L.g3), 1, c->stream);
   {
     DecGemm a = normed(L.w1, c->ff);
     a.X = c->midX;
-    dec_gemm<DE_GELU, true>(a, 1, c->stream);
+    dec_gemm<T, DE_GELU, true>(a, 1, c->stream);
   }
   {
     DecGemm a = residual(c->midX, L.w2, c->ff, next_gain);
     if (ring) { a.ring = ring; a.pos = c->pos[level]; a.rs = rs; }
-    dec_gemm<DE_RES, false>(a, 1, c->stream);
+    dec_gemm<T, DE_RES, false>(a, 1, c->stream);
   }
 }
 
 // The backbone forward of a pass whose rows k_verify_setup has prepared (embedded rows in h[0], xg[0], ssq[0]).
-void forward_h(fm_ctx* c, float* logits) {
+template <typename T>
+void forward(fm_ctx* c, float* logits) {
   const Dims& D = c->D;
   const int d = D.d;
   float* tap[5] = {nullptr, nullptr, c->tap_f, c->tap_v, c->tap_c};
@@ -539,37 +399,38 @@ void forward_h(fm_ctx* c, float* logits) {
     for (size_t i = 0; i < n; i++) {
       const bool last = i + 1 == n;
       const float* gain = !last ? c->stacks[st][i + 1].g1 : st == 4 ? c->gf : nullptr;
-      run_block_h(c, c->stacks[st][i], level, gain, last ? tap[st] : nullptr, last ? ring[st] : nullptr, rsz[level], !last ? c->stacks[st][i + 1].wqkv : nullptr);
+      run_block<T>(c, c->stacks[st][i], level, gain, last ? tap[st] : nullptr, last ? ring[st] : nullptr, rsz[level], !last ? c->stacks[st][i + 1].wqkv : nullptr);
     }
     if (st < 2) {          // shorten onto the next coarser level
       const int cl = st + 1;
-      hipLaunchKernelGGL(k_dec_pool3, dim3(level_rows(c, cl)), dim3(256), 0, c->stream, ring[st], rsz[level], c->pos[cl], level_rps(c, cl), c->attX, d);
+      hipLaunchKernelGGL((k_dec_pool3<T>), dim3(level_rows(c, cl)), dim3(256), 0, c->stream, ring[st], rsz[level], c->pos[cl], level_rps(c, cl), (T*)c->attX, d);
       DecGemm a{};
-      a.A = c->attX; a.W = (const f16_t*)(st == 0 ? c->short_cv : c->short_vf); a.M = level_rows(c, cl); a.N = d; a.KT = d / 32; a.run_flag = c->st.alive;
+      a.A = c->attX; a.W = st == 0 ? c->short_cv : c->short_vf; a.M = level_rows(c, cl); a.N = d; a.KT = d / 32; a.run_flag = c->st.alive;
       a.Y = c->h[cl]; a.ldy = d; a.X = c->xg[cl]; a.gain = c->stacks[st + 1][0].g1; a.ssq_out = c->ssq[cl];
-      dec_gemm<DE_RES, false>(a, 1, c->stream);
+      dec_gemm<T, DE_RES, false>(a, 1, c->stream);
     } else if (st < 4) {   // upsample onto the next finer level (repeat + skip)
       const int fl = level - 1;
-      hipLaunchKernelGGL(k_dec_upsample, dim3(level_rows(c, fl)), dim3(256), 0, c->stream, c->h[fl], c->pos[fl], level_rps(c, fl), ring[st], rsz[level], d,
-                         c->xg[fl], c->stacks[st + 1][0].g1, c->ssq[fl]);
+      hipLaunchKernelGGL((k_dec_upsample<T>), dim3(level_rows(c, fl)), dim3(256), 0, c->stream, c->h[fl], c->pos[fl], level_rps(c, fl), ring[st], rsz[level], d,
+                         (T*)c->xg[fl], c->stacks[st + 1][0].g1, c->ssq[fl]);
     }
   }
   DecGemm a{};
-  a.A = c->xg[0]; a.W = (const f16_t*)c->lm; a.M = c->Rc; a.N = D.V; a.KT = d / 32; a.ssq = c->ssq[0]; a.inv_k = 1.0f / d; a.eps = c->cfg.rms_eps;
+  a.A = c->xg[0]; a.W = c->lm; a.M = c->Rc; a.N = D.V; a.KT = d / 32; a.ssq = c->ssq[0]; a.inv_k = 1.0f / d; a.eps = c->cfg.rms_eps;
   a.run_flag = c->st.alive; a.Y = logits; a.ldy = D.V;
-  dec_gemm<DE_F32, true>(a, 1, c->stream);
+  dec_gemm<T, DE_F32, true>(a, 1, c->stream);
 }
 
-int verify_half(fm_ctx* c, const int32_t* block_tok, const int32_t* block_len, float* logits_out, int32_t* accepted) {
+template <typename T>
+int verify_impl(fm_ctx* c, const int32_t* block_tok, const int32_t* block_len, float* logits_out, int32_t* accepted) {
   float* lg = logits_out ? logits_out : c->logits;
-  verify_setup<f16_t>(c, block_tok, block_len, !c->persist);
+  verify_setup<T>(c, block_tok, block_len, !c->persist);
   if (c->persist) {
     // the whole backbone forward in one launch (see fm_kernels_persist.h)
     c->pk.logits = lg;
     if (c->pk.RS == 32) hipLaunchKernelGGL(k_verify_persist<2>, dim3(PK_NWG), dim3(256), c->pk_lds, c->stream, c->pk);
     else hipLaunchKernelGGL(k_verify_persist<1>, dim3(PK_NWG), dim3(256), c->pk_lds, c->stream, c->pk);
   } else {
-    forward_h(c, lg);
+    forward<T>(c, lg);
   }
   choose_and_accept(c, lg, accepted);      // greedy choice (or sampled) and acceptance
   HIPCHK(c, hipGetLastError());
@@ -577,19 +438,21 @@ int verify_half(fm_ctx* c, const int32_t* block_tok, const int32_t* block_len, f
 }
 
 // Query projection of draft rows: grouped GEMM over `G` sets of `M` rows each with the rotation applied, row (set g, m) -> m * G + g
+template <typename T>
 void draft_query(fm_ctx* c, const void* W, int M, int G, int tiles, const float2* cs, const int* flag) {
   const int d = c->D.d;
   DecGemm a{};
-  a.A = c->dX; a.gsa = (long)tiles * 16 * d; a.W = (const f16_t*)W; a.gsw = (long)d * d; a.M = M; a.N = d; a.KT = d / 32; a.run_flag = flag;
+  a.A = c->dX; a.gsa = (long)tiles * 16 * d; a.W = W; a.gsw = (long)d * d; a.M = M; a.N = d; a.KT = d / 32; a.run_flag = flag;
   a.Y = c->dq; a.ldy = (long)G * d; a.gsy = d; a.cs = cs; a.ldc = G; a.hd = c->D.hd; a.H = c->D.H;
-  dec_gemm<DE_ROPE, false>(a, G, c->stream);
+  dec_gemm<T, DE_ROPE, false>(a, G, c->stream);
 }
 
 // The SP chains (Eq. 1) of all three levels as one chain of grouped launches: the row set is, per sequence, the point-,
 // face- and coordinate-level rows behind each other, every GEMM is grouped over all heads (S rows per head), and the
 // two attention launches take one cache per level.  Rows of a level that does not fire in this step carry limit -1 (no
 // keys) and produce values nobody reads.
-void run_sp_all(fm_ctx* c, const int* flag) {
+template <typename T>
+void run_sp(fm_ctx* c, const int* flag) {
   const Dims& D = c->D;
   const SpLevel& A = c->sp_all;
   const int d = D.d, G = A.cnt, S = D.S, rows = S * G;
@@ -604,88 +467,70 @@ void run_sp_all(fm_ctx* c, const int* flag) {
     for (int z = 0; z < 3; z++) {
       const int cap = cross ? D.M : level_cap(c, lev[z]);
       if (nrow[z] > 0)
-        t.set[n++] = AttnSet{(const f16_t*)c->dq, limit, nrow[z], q0, G, (const f16_t*)(cross ? last[z]->Km : last[z]->Kc), (const f16_t*)(cross ? last[z]->Vm : last[z]->Vc),
+        t.set[n++] = AttnSet{c->dq, limit, nrow[z], q0, G, cross ? last[z]->Km : last[z]->Kc, cross ? last[z]->Vm : last[z]->Vc,
                              (long)cache_seq_elems(c, cap), (cap + 31) / 32, cross ? 0 : level_window(c, lev[z]), 1, rm, c->dX};
       q0 += nrow[z];
     }
-    if (!dec_attention(t, n, D.hd, c->stream)) refuse(c, "SP attention");
+    if (!dec_attention<T>(t, n, D.hd, c->stream)) refuse(c, "SP attention");
   };
   DecGemm g{};
   g.A = c->dX; g.gsa = (long)c->sp_tiles * 16 * d; g.gsw = (long)d * d; g.M = S; g.N = d; g.KT = d / 32; g.run_flag = flag;
-  hipLaunchKernelGGL(k_dec_rmsnorm, dim3(rows), dim3(256), 0, c->stream, c->dr.src[1], A.g, G, c->dX, rm, G, c->dkeep, d, c->cfg.rms_eps, flag);
-  draft_query(c, A.wq, S, G, c->sp_tiles, c->dr.cs[1], flag);
+  hipLaunchKernelGGL((k_dec_rmsnorm<T>), dim3(rows), dim3(256), 0, c->stream, c->dr.src[1], A.g, G, (T*)c->dX, rm, G, c->dkeep, d, c->cfg.rms_eps, flag);
+  draft_query<T>(c, A.wq, S, G, c->sp_tiles, c->dr.cs[1], flag);
   attn(c->dr.lim[1], false);
   // output projection of the self-attention, then straight (no norm, Eq. 1) the cross-attention query
   DecGemm a = g;
-  a.W = (const f16_t*)A.wo; a.X = c->dmidX; a.gsx = g.gsa;
-  dec_gemm<DE_TILE, false>(a, G, c->stream);
+  a.W = A.wo; a.X = c->dmidX; a.gsx = g.gsa;
+  dec_gemm<T, DE_TILE, false>(a, G, c->stream);
   a = g;
-  a.A = c->dmidX; a.W = (const f16_t*)A.cq; a.Y = c->dq; a.ldy = (long)G * d; a.gsy = d;
-  dec_gemm<DE_ROW, false>(a, G, c->stream);
+  a.A = c->dmidX; a.W = A.cq; a.Y = c->dq; a.ldy = (long)G * d; a.gsy = d;
+  dec_gemm<T, DE_ROW, false>(a, G, c->stream);
   attn(c->dr.limx[1], true);
   a = g;
-  a.W = (const f16_t*)A.co; a.X = c->dmidX; a.gsx = g.gsa;
-  dec_gemm<DE_TILE, false>(a, G, c->stream);
+  a.W = A.co; a.X = c->dmidX; a.gsx = g.gsa;
+  dec_gemm<T, DE_TILE, false>(a, G, c->stream);
   // outputs: per sequence the point, face and coordinate rows behind each other (spv_out, spf_out and the rows the output
   // head's pointer table names)
   a = g;
-  a.A = c->dmidX; a.W = (const f16_t*)A.lin; a.Y = c->spv_out; a.ldy = (long)G * d; a.gsy = d; a.R = c->dkeep; a.ldr = (long)G * d; a.gsr = d;
-  dec_gemm<DE_F32, false>(a, G, c->stream);
+  a.A = c->dmidX; a.W = A.lin; a.Y = c->spv_out; a.ldy = (long)G * d; a.gsy = d; a.R = c->dkeep; a.ldr = (long)G * d; a.gsr = d;
+  dec_gemm<T, DE_F32, false>(a, G, c->stream);
 }
 
 // HF block chain (Eq. 3-6): row sets 3 (vertex level) and 4 (coordinate level, mult = 2: the point and the face pipeline
 // share the parameter sets)
-void run_hf_h(fm_ctx* c, int set, const HfLevel& hf, int mult, const Layer& last, int level, float* out, const int* flag) {
+template <typename T>
+void run_hf(fm_ctx* c, int set, const HfLevel& hf, int mult, const Layer& last, int level, float* out, const int* flag) {
   const Dims& D = c->D;
   const int d = D.d, G = hf.cnt, per_seq = G * mult, rows = D.S * per_seq, Mg = D.S * mult, tiles = c->hf_tiles[set - 3];
   if (G == 0) return;
   const RowMap rm{G, mult, 0, tiles};
-  hipLaunchKernelGGL(k_dec_rmsnorm, dim3(rows), dim3(256), 0, c->stream, c->dr.src[set], hf.g, G, c->dX, rm, per_seq, c->dkeep, d, c->cfg.rms_eps, flag);
-  draft_query(c, hf.wq, Mg, G, tiles, c->dr.cs[set], flag);
+  hipLaunchKernelGGL((k_dec_rmsnorm<T>), dim3(rows), dim3(256), 0, c->stream, c->dr.src[set], hf.g, G, (T*)c->dX, rm, per_seq, c->dkeep, d, c->cfg.rms_eps, flag);
+  draft_query<T>(c, hf.wq, Mg, G, tiles, c->dr.cs[set], flag);
   AttnArgs t{};
   t.S = D.S; t.H = D.H; t.ws = c->attn_ws; t.arrived = c->attn_arrived; t.run_flag = flag;
   const int cap = level_cap(c, level);
   int n = 0;
   for (int q0 = 0; q0 < per_seq; q0 += 32)      // at most 48 rows per sequence: one or two sets
-    t.set[n++] = AttnSet{(const f16_t*)c->dq, c->dr.lim[set], std::min(32, per_seq - q0), q0, per_seq, (const f16_t*)last.Kc, (const f16_t*)last.Vc,
+    t.set[n++] = AttnSet{c->dq, c->dr.lim[set], std::min(32, per_seq - q0), q0, per_seq, last.Kc, last.Vc,
                          (long)cache_seq_elems(c, cap), (cap + 31) / 32, level_window(c, level), 1, rm, c->dX};
-  if (!dec_attention(t, n, D.hd, c->stream)) refuse(c, "HF attention");
+  if (!dec_attention<T>(t, n, D.hd, c->stream)) refuse(c, "HF attention");
   DecGemm a{};
-  a.A = c->dX; a.gsa = (long)tiles * 16 * d; a.W = (const f16_t*)hf.w1; a.gsw = (long)d * c->hff; a.M = Mg; a.N = c->hff; a.KT = d / 32; a.run_flag = flag;
+  a.A = c->dX; a.gsa = (long)tiles * 16 * d; a.W = hf.w1; a.gsw = (long)d * c->hff; a.M = Mg; a.N = c->hff; a.KT = d / 32; a.run_flag = flag;
   a.X = c->dmidX; a.gsx = (long)tiles * 16 * c->hff;
-  dec_gemm<DE_GELU, false>(a, G, c->stream);
-  a.A = c->dmidX; a.gsa = a.gsx; a.W = (const f16_t*)hf.w2; a.N = d; a.KT = c->hff / 32; a.X = nullptr;
+  dec_gemm<T, DE_GELU, false>(a, G, c->stream);
+  a.A = c->dmidX; a.gsa = a.gsx; a.W = hf.w2; a.N = d; a.KT = c->hff / 32; a.X = nullptr;
   a.Y = out; a.ldy = (long)G * d; a.gsy = d; a.R = c->dkeep; a.ldr = (long)G * d; a.gsr = d;
-  dec_gemm<DE_F32, false>(a, G, c->stream);
+  dec_gemm<T, DE_F32, false>(a, G, c->stream);
 }
 
 // Output head on the draft rows (coordinate SP heads, then the coordinate HF rows)
-void draft_logits_h(fm_ctx* c, int n, const int* flag) {
-  const Dims& D = c->D;
-  hipLaunchKernelGGL(k_dec_rmsnorm, dim3(n), dim3(256), 0, c->stream, c->lm_src, c->gf, 0, c->dX, RowMap{1, 0, 0, 0}, n, (float*)nullptr, D.d, c->cfg.rms_eps, flag);
-  DecGemm a{};
-  a.A = c->dX; a.W = (const f16_t*)c->lm; a.M = n; a.N = D.V; a.KT = D.d / 32; a.run_flag = flag; a.Y = c->dlogits; a.ldy = D.V;
-  dec_gemm<DE_F32, false>(a, 1, c->stream);
-}
-
-// HF block chain (Eq. 3-6) for row set `set`: `per_seq` rows per sequence, `G` parameter sets, `mult`
-// consecutive row groups of G sharing the sets (mult = 2 for the coordinate level: point and face pipelines)
 template <typename T>
-void run_hf(fm_ctx* c, int set, const HfLevel& hf, int mult, const Layer& last, int level, float* out, const int* flag) {
+void draft_logits(fm_ctx* c, int n, const int* flag) {
   const Dims& D = c->D;
-  const int d = D.d, G = hf.cnt, per_seq = G * mult, rows = D.S * per_seq;
-  if (G == 0) return;
-  const int cap = level_cap(c, level);
-  const long dd = (long)d * d, dh = (long)d * c->hff;
-  const int Mg = D.S * mult;           // rows per parameter set
-  const long ld = (long)G * d;         // stride between those rows
-  rmsnorm<T>(c, nullptr, c->dr.src[set], hf.g, G, c->dxn, c->dkeep, rows, flag);
-  gemm<T>(c, EPI_F32, c->dxn, ld, d, hf.wq, dd, c->dtmp, ld, d, nullptr, 0, 0, Mg, d, d, G, flag);
-  rope_append<T>(c, c->dtmp, (long)d, c->dr.cs[set], c->dr.pos[set], rows, per_seq, c->dq, nullptr, nullptr, cap, flag);
-  attention<T>(c, c->dq, c->dr.lim[set], rows, per_seq, last.Kc, last.Vc, (long)cache_seq_elems(c, cap), cap, c->datt, flag,
-               level_window(c, level));
-  gemm<T>(c, EPI_GELU_T, c->datt, ld, d, hf.w1, dh, c->dmid, (long)G * c->hff, c->hff, nullptr, 0, 0, Mg, c->hff, d, G, flag);
-  gemm<T>(c, EPI_F32, c->dmid, (long)G * c->hff, c->hff, hf.w2, dh, out, ld, d, c->dkeep, ld, d, Mg, d, c->hff, G, flag);
+  hipLaunchKernelGGL((k_dec_rmsnorm<T>), dim3(n), dim3(256), 0, c->stream, c->lm_src, c->gf, 0, (T*)c->dX, RowMap{1, 0, 0, 0}, n, (float*)nullptr, D.d, c->cfg.rms_eps, flag);
+  DecGemm a{};
+  a.A = c->dX; a.W = c->lm; a.M = n; a.N = D.V; a.KT = D.d / 32; a.run_flag = flag; a.Y = c->dlogits; a.ldy = D.V;
+  dec_gemm<T, DE_F32, false>(a, 1, c->stream);
 }
 
 template <typename T>
@@ -694,36 +539,19 @@ int draft_impl(fm_ctx* c, int32_t* block_tok, int32_t* block_len, int speculativ
   const int d = D.d;
   if (speculative) {
     hipLaunchKernelGGL(k_draft_setup, dim3(D.S, (D.Dc + D.nspv + D.nspf + D.nhfv + 2 * D.nhfc + 7) / 8 + (D.Dc + D.nspv + D.nspf + D.nhfv + 2 * D.nhfc == 0)), dim3(256), 0, c->stream, c->st, D, c->inv, c->dr, c->db);
-    const int *f_alive = c->dr.flags, *f_v = c->dr.flags + 1, *f_f = c->dr.flags + 2;
+    const int *f_alive = c->dr.flags, *f_f = c->dr.flags + 2;
     const Layer& lastc = c->stacks[4].back();
     const Layer& lastv = c->stacks[3].back();
-    const Layer& lastf = c->stacks[2].back();
     const int nLM = D.S * (D.Dc + 2 * D.nhfc);
-    constexpr bool half = std::is_same<T, f16_t>::value;
-    if constexpr (half) {
-      run_sp_all(c, f_alive);
-    } else {
-      // coordinate level: SP heads straight to the output head
-      run_sp<T>(c, 0, c->sp[0], lastc, 0, c->dh, (long)D.Dc * d, d, f_alive);
-      // point level: SP heads on the vertex feature; their outputs feed the coordinate HF rows of pipe 0
-      run_sp<T>(c, 1, c->sp[1], lastv, 1, c->spv_out, (long)D.nspv * d, d, f_v);
-      // face level: SP heads on the face feature, vertex-level HF, then coordinate HF rows of pipe 1
-      run_sp<T>(c, 2, c->sp[2], lastf, 2, c->spf_out, (long)D.nspf * d, d, f_f);
-    }
-    if constexpr (half) run_hf_h(c, 3, c->hfv, 1, lastv, 1, c->hfv_out, f_f);
-    else run_hf<T>(c, 3, c->hfv, 1, lastv, 1, c->hfv_out, f_f);
+    run_sp<T>(c, f_alive);
+    run_hf<T>(c, 3, c->hfv, 1, lastv, 1, c->hfv_out, f_f);
     if (c->correct_hist > 0 && D.nspv + D.nhfv > 0)     // label rows of the point-level features (Sec. 3.2)
       hipLaunchKernelGGL(k_label_rows, dim3(D.S * (D.nspv + D.nhfv)), dim3(64), 0, c->stream, D, c->dr, c->spv_out, c->db.spv_rs, c->hfv_out,
                          c->label_w, c->lab_v, c->lab_f);
     float* hfc_out = c->dh + (long)D.S * D.Dc * d;
-    if constexpr (half) run_hf_h(c, 4, c->hfc, 2, lastc, 0, hfc_out, f_alive);
-    else run_hf<T>(c, 4, c->hfc, 2, lastc, 0, hfc_out, f_alive);
+    run_hf<T>(c, 4, c->hfc, 2, lastc, 0, hfc_out, f_alive);
     if (nLM > 0) {
-      if constexpr (half) draft_logits_h(c, nLM, f_alive);
-      else {
-        rmsnorm<T>(c, nullptr, c->lm_src, c->gf, 0, c->dxn, nullptr, nLM, f_alive);
-        gemm<T>(c, EPI_F32, c->dxn, d, 0, c->lm, 0, c->dlogits, D.V, 0, nullptr, 0, 0, nLM, D.V, d, 1, f_alive);
-      }
+      draft_logits<T>(c, nLM, f_alive);
       hipLaunchKernelGGL(k_dist_store, dim3(nLM), dim3(256), 0, c->stream, c->dlogits, D, c->dr, c->dist_c, c->dist_v,
                          c->dist_f);
     }
@@ -738,7 +566,7 @@ int draft_any(fm_ctx* c, int32_t* block_tok, int32_t* block_len, int speculative
   return c->bf16 ? draft_impl<f16_t>(c, block_tok, block_len, speculative) : draft_impl<float>(c, block_tok, block_len, speculative);
 }
 int verify_any(fm_ctx* c, const int32_t* block_tok, const int32_t* block_len, float* logits, int32_t* accepted) {
-  return c->bf16 ? verify_half(c, block_tok, block_len, logits, accepted) : verify_impl<float>(c, block_tok, block_len, logits, accepted);
+  return c->bf16 ? verify_impl<f16_t>(c, block_tok, block_len, logits, accepted) : verify_impl<float>(c, block_tok, block_len, logits, accepted);
 }
 // settings that decide which launches a step consists of
 int step_flags(const fm_ctx* c, int speculative) {
@@ -755,20 +583,20 @@ int put_params(fm_ctx* c) {
   return FM_OK;
 }
 
-// staging bytes a prefill call needs: half path: the memory in fragment order (whole 32-row blocks) and, for models narrower than the tiled
-// GEMM takes, the fp32 K/V rows of one block behind it; fp32 path: the memory and those rows
+// staging bytes a prefill call needs: the memory in operand order (whole 32-row blocks) and, where the tiled GEMM does not run
+// (fp32, models narrower than it takes), the fp32 K/V rows of one block behind it
 size_t prefill_stage_bytes(const fm_ctx* c) {
   const size_t M = c->D.M, d = c->D.d, M32 = (M + 31) / 32 * 32;
-  if (c->bf16) return M32 * d * sizeof(f16_t) + (c->pf_layers ? 0 : M * 2 * d * sizeof(float));
-  return M * d * c->esz + M * 2 * d * sizeof(float);
+  return M32 * d * c->esz + (c->pf_layers ? 0 : M * 2 * d * sizeof(float));
 }
 
-int prefill_half(fm_ctx* c, int seq, const float* mem_dev, void* stage_area) {
+template <typename T>
+int prefill_impl(fm_ctx* c, int seq, const float* mem_dev, void* stage_area) {
   const Dims& D = c->D;
   const int d = D.d, M32 = (D.M + 31) / 32 * 32;
   // memory -> MFMA fragment order (the same tiling as a weight matrix, zero rows up to whole key blocks)
-  f16_t* Xt = (f16_t*)stage_area;
-  hipLaunchKernelGGL(k_tile_weight, dim3(std::min(2048, (M32 * (d / 8) + 255) / 256)), dim3(256), 0, c->stream, mem_dev, Xt, D.M, d, M32, 0, D.hd);
+  T* Xt = (T*)stage_area;
+  hipLaunchKernelGGL((k_tile_weight<T>), dim3(std::min(2048, (M32 * (d / 8) + 255) / 256)), dim3(256), 0, c->stream, mem_dev, Xt, D.M, d, M32, 0, D.hd);
   const long seq_off = (long)((size_t)seq * cache_seq_elems(c, D.M));
   if (c->pf_layers) {
 #define FM_PREFILL(HDV)                                                                                                            \
@@ -787,34 +615,14 @@ int prefill_half(fm_ctx* c, int seq, const float* mem_dev, void* stage_area) {
     for (int st = 0; st < 5; st++)
       for (auto& L : c->stacks[st]) {
         DecGemm a{};
-        a.A = Xt; a.W = (const f16_t*)L.ckv; a.M = D.M; a.N = 2 * d; a.KT = d / 32; a.Y = kv; a.ldy = 2 * d;
-        dec_gemm<DE_F32, false>(a, 1, c->stream);
-#define FM_MEMKVH(HDV) hipLaunchKernelGGL((k_mem_kv_store_h<HDV>), dim3(D.M), dim3(256), 0, c->stream, kv, (f16_t*)L.Km + seq_off, (f16_t*)L.Vm + seq_off, D.H, D.M, \
+        a.A = Xt; a.W = L.ckv; a.M = D.M; a.N = 2 * d; a.KT = d / 32; a.Y = kv; a.ldy = 2 * d;
+        dec_gemm<T, DE_F32, false>(a, 1, c->stream);
+#define FM_MEMKVH(HDV) hipLaunchKernelGGL((k_mem_kv_store<T, HDV>), dim3(D.M), dim3(256), 0, c->stream, kv, (T*)L.Km + seq_off, (T*)L.Vm + seq_off, D.H, D.M, \
                                           (D.M + 31) / 32)
         if (D.hd == 64) FM_MEMKVH(64); else if (D.hd == 96) FM_MEMKVH(96); else FM_MEMKVH(128);
 #undef FM_MEMKVH
       }
   }
-  hipLaunchKernelGGL(k_reset_seq, dim3(1), dim3(64), 0, c->stream, c->st, D, seq, D.nbins);
-  HIPCHK(c, hipGetLastError());
-  return FM_OK;
-}
-
-int prefill_f32(fm_ctx* c, int seq, const float* mem_dev, void* stage_area) {
-  const Dims& D = c->D;
-  const int d = D.d;
-  float* memT = (float*)stage_area;  // [M*d], then [M][2d]
-  float* kv = memT + (size_t)D.M * d;
-  hipLaunchKernelGGL((k_convert<float>), dim3(512), dim3(256), 0, c->stream, mem_dev, memT, (long)D.M * d);
-  for (int st = 0; st < 5; st++)
-    for (auto& L : c->stacks[st]) {
-      gemm<float>(c, EPI_F32, memT, d, 0, L.ckv, 0, kv, 2 * d, 0, nullptr, 0, 0, D.M, 2 * d, d, 1, nullptr);
-      float* Km = (float*)L.Km + (size_t)seq * cache_seq_elems(c, D.M);
-      float* Vm = (float*)L.Vm + (size_t)seq * cache_seq_elems(c, D.M);
-#define FM_MEMKV(HDV) hipLaunchKernelGGL((k_mem_kv_store<float, HDV>), dim3(D.M), dim3(256), 0, c->stream, kv, Km, Vm, D.H, D.M)
-      if (D.hd == 64) FM_MEMKV(64); else if (D.hd == 96) FM_MEMKV(96); else FM_MEMKV(128);
-#undef FM_MEMKV
-    }
   hipLaunchKernelGGL(k_reset_seq, dim3(1), dim3(64), 0, c->stream, c->st, D, seq, D.nbins);
   HIPCHK(c, hipGetLastError());
   return FM_OK;
@@ -1041,20 +849,16 @@ int build_buffers(fm_ctx* c) {
   for (int l = 0; l < 3; l++) {
     TRY(dalloc(c, &c->pos[l], rows[l])); TRY(dalloc(c, &c->limx[l], rows[l]));
     TRY(dalloc(c, &c->cs[l], rows[l] * 64)); TRY(dalloc(c, &c->h[l], rows[l] * d));
-    if (c->bf16) {
-      const size_t tiles = (rows[l] + 15) / 16;
-      TRY(dalloc(c, &c->xg[l], tiles * 16 * d)); TRY(dalloc(c, &c->ssq[l], tiles * d));
-    }
+    const size_t tiles = (rows[l] + 15) / 16;
+    TRY(dalloc_t(c, &c->xg[l], tiles * 16 * d)); TRY(dalloc(c, &c->ssq[l], tiles * d));
   }
-  if (c->bf16) {
+  {
     const size_t tiles = (rows[0] + 15) / 16;
-    TRY(dalloc(c, &c->attX, tiles * 16 * d)); TRY(dalloc(c, &c->midX, tiles * 16 * c->ff));
+    TRY(dalloc_t(c, &c->attX, tiles * 16 * d)); TRY(dalloc_t(c, &c->midX, tiles * 16 * c->ff));
     TRY(dalloc(c, &c->attn_arrived, (size_t)FM_ATTN_SETS * D.S * D.H));
     TRY(dalloc(c, &c->attn_ws, attn_ws_floats(D.H, D.S, FM_ATTN_SETS, D.hd)));
   }
-  TRY(dalloc_t(c, &c->xn, rows[0] * d)); TRY(dalloc_t(c, &c->qT, rows[0] * d)); TRY(dalloc_t(c, &c->attT, rows[0] * d));
-  TRY(dalloc_t(c, &c->mid, rows[0] * c->ff));
-  TRY(dalloc(c, &c->qkv, rows[0] * 3 * d)); TRY(dalloc(c, &c->logits, rows[0] * D.V));
+  TRY(dalloc_t(c, &c->qT, rows[0] * d)); TRY(dalloc(c, &c->logits, rows[0] * D.V));
   // staging: conversion of the largest tensor, or the prefill (memory in T + fp32 K/V of one layer)
   size_t big = std::max((size_t)c->ff * d, (size_t)c->hff * d);
   big = std::max(big, 3 * d * d);
@@ -1072,59 +876,43 @@ int build_buffers(fm_ctx* c) {
   }
   const int G_all = D.Dc + D.nspv + D.nspf;
   {
-    // One table for the three SP row sets.  Merged chain: rows [sequence][point heads | face heads | coordinate heads],
-    // as the heads lie in memory, so that a grouped launch over all heads sees S rows per head with one stride.
-    // Otherwise the three sets behind each other, each [sequence][head].
+    // One table for the three SP row sets: rows [sequence][point heads | face heads | coordinate heads], as the heads lie in
+    // memory, so that a grouped launch over all heads sees S rows per head with one stride.
     const size_t nsp = nset[0] + nset[1] + nset[2], np = (size_t)D.hd / 2;
     maxset = std::max(maxset, nsp);
     const float** src; int *pos, *lim, *limx; float2* cs;
     TRY(dalloc(c, (const float***)&src, nsp)); TRY(dalloc(c, &pos, nsp)); TRY(dalloc(c, &lim, nsp)); TRY(dalloc(c, &limx, nsp));
     TRY(dalloc(c, &cs, nsp * 64));
-    const size_t first_m[3] = {(size_t)D.nspv + D.nspf, 0, (size_t)D.nspv}, first_s[3] = {nset[1] + nset[2], 0, nset[1]};
-    const int cnt[5] = {D.Dc, D.nspv, D.nspf, D.nhfv, 2 * D.nhfc};
-    for (int i = 0; i < 5; i++) c->dr.rs[i] = cnt[i];
+    const size_t first[3] = {(size_t)D.nspv + D.nspf, 0, (size_t)D.nspv};
+    for (int i = 0; i < 5; i++) c->dr.rs[i] = i < 3 ? G_all : i == 3 ? D.nhfv : 2 * D.nhfc;
     for (int i = 0; i < 3; i++) {
-      const size_t first = c->bf16 ? first_m[i] : first_s[i];
-      if (c->bf16) c->dr.rs[i] = G_all;
-      c->dr.src[i] = src + first; c->dr.pos[i] = pos + first; c->dr.lim[i] = lim + first;
-      c->dr.limx[i] = limx + first; c->dr.cs[i] = cs + first * np;
+      c->dr.src[i] = src + first[i]; c->dr.pos[i] = pos + first[i]; c->dr.lim[i] = lim + first[i];
+      c->dr.limx[i] = limx + first[i]; c->dr.cs[i] = cs + first[i] * np;
     }
   }
   TRY(dalloc(c, &c->dr.alive, S)); TRY(dalloc(c, &c->dr.firev, S)); TRY(dalloc(c, &c->dr.firef, S)); TRY(dalloc(c, &c->dr.flags, 4));
   TRY(dalloc(c, &c->hfv_out, nset[3] * d));
   const size_t nLM = S * (D.Dc + 2 * D.nhfc);
-  // Outputs of the SP heads.  Merged chain: one buffer [sequence][point | face | coordinate heads][d]; otherwise one
-  // buffer per level, the coordinate level's being the first rows of the output head's input.  The output head reads its
-  // rows (coordinate SP heads of every sequence, then the coordinate HF rows) through a pointer table either way.
+  // Outputs of the SP heads: one buffer [sequence][point | face | coordinate heads][d].  The output head reads its rows
+  // (coordinate SP heads of every sequence, then the coordinate HF rows) through a pointer table.
   TRY(dalloc(c, &c->dh, nLM * d));
-  int spv_rs = std::max(D.nspv, 1), spf_rs = D.nspf;
-  if (c->bf16) {
-    TRY(dalloc(c, &c->spv_out, (size_t)S * std::max(G_all, 1) * d));
-    c->spf_out = c->spv_out + (size_t)D.nspv * d;
-    spv_rs = spf_rs = G_all;
-  } else {
-    TRY(dalloc(c, &c->spv_out, nset[1] * d));
-    TRY(dalloc(c, &c->spf_out, nset[2] * d));
-  }
+  TRY(dalloc(c, &c->spv_out, (size_t)S * std::max(G_all, 1) * d));
+  c->spf_out = c->spv_out + (size_t)D.nspv * d;
   {
     std::vector<const float*> tab(std::max<size_t>(nLM, 1));
-    for (size_t i = 0; i < nLM; i++) {
-      if (c->bf16 && i < S * (size_t)D.Dc) tab[i] = c->spv_out + ((i / D.Dc) * G_all + D.nspv + D.nspf + i % D.Dc) * d;
-      else tab[i] = c->dh + i * d;
-    }
+    for (size_t i = 0; i < nLM; i++)
+      tab[i] = i < S * (size_t)D.Dc ? c->spv_out + ((i / D.Dc) * G_all + D.nspv + D.nspf + i % D.Dc) * d : c->dh + i * d;
     TRY(dalloc(c, (const float***)&c->lm_src, tab.size()));
     HIPCHK(c, hipMemcpy(c->lm_src, tab.data(), tab.size() * sizeof(float*), hipMemcpyHostToDevice));
   }
   TRY(dalloc(c, &c->dlogits, nLM * D.V));
   const size_t rmax = std::max(maxset, nLM);
-  TRY(dalloc(c, &c->dkeep, rmax * d)); TRY(dalloc(c, &c->dtmp, rmax * d));
-  TRY(dalloc_t(c, &c->dxn, rmax * d)); TRY(dalloc_t(c, &c->dq, rmax * d)); TRY(dalloc_t(c, &c->datt, rmax * d));
-  TRY(dalloc_t(c, &c->dmid, rmax * c->hff));
-  if (c->bf16) {
+  TRY(dalloc(c, &c->dkeep, rmax * d)); TRY(dalloc_t(c, &c->dq, rmax * d));
+  {
     c->sp_tiles = (int)(S + 15) / 16; c->hf_tiles[0] = (int)(S + 15) / 16; c->hf_tiles[1] = (int)(2 * S + 15) / 16;
     const size_t sp = (size_t)G_all * c->sp_tiles, hv = (size_t)D.nhfv * c->hf_tiles[0], hc = (size_t)D.nhfc * c->hf_tiles[1], lmt = (nLM + 15) / 16;
-    TRY(dalloc(c, &c->dX, std::max(std::max(sp, hv), std::max(std::max(hc, lmt), (size_t)1)) * 16 * d));
-    TRY(dalloc(c, &c->dmidX, std::max(std::max(sp * d, std::max(hv, hc) * c->hff), (size_t)1) * 16));
+    TRY(dalloc_t(c, &c->dX, std::max(std::max(sp, hv), std::max(std::max(hc, lmt), (size_t)1)) * 16 * d));
+    TRY(dalloc_t(c, &c->dmidX, std::max(std::max(sp * d, std::max(hv, hc) * c->hff), (size_t)1) * 16));
   }
   TRY(dalloc(c, &c->dist_c, S * std::max(D.Dc, 1) * D.V));
   TRY(dalloc(c, &c->dist_v, S * std::max(D.nhfc, 1) * D.V)); TRY(dalloc(c, &c->dist_f, S * std::max(D.nhfc, 1) * D.V));
@@ -1133,7 +921,7 @@ int build_buffers(fm_ctx* c) {
   c->smp = Sampling{c->params_dev, nullptr, nullptr, nullptr, nullptr};
   TRY(dalloc(c, &c->smp.qrow, S * D.Bm * D.V)); TRY(dalloc(c, &c->smp.qsum, S * D.Bm));
   TRY(dalloc(c, &c->smp.qtok, S * D.Bm)); TRY(dalloc(c, &c->smp.accflag, S * D.Bm));
-  c->db = DraftBufs{c->tap_c, c->tap_v, c->tap_f, c->ring_yf, c->spv_out, c->spf_out, c->hfv_out, spv_rs, spf_rs};
+  c->db = DraftBufs{c->tap_c, c->tap_v, c->tap_f, c->ring_yf, c->spv_out, c->spf_out, c->hfv_out, G_all, G_all};
   TRY(dalloc(c, &c->gen_tok, S * D.Bm)); TRY(dalloc(c, &c->gen_len, S)); TRY(dalloc(c, &c->gen_acc, S));
   if (c->persist) TRY(build_persist(c));
   if (c->bf16) {
@@ -1295,10 +1083,11 @@ int fm_load_weights(fm_ctx* c, const float* blob, size_t n_floats) {
         HIPCHK(c, hipMemcpyAsync((float*)it.dst + done, blob + it.blob_off + done, n * 4, hipMemcpyHostToDevice, c->stream));
       } else {
         HIPCHK(c, hipMemcpyAsync(c->stage, blob + it.blob_off + done, n * 4, hipMemcpyHostToDevice, c->stream));
-        if (c->bf16 && it.N > 0) {
+        if (it.N > 0) {
           if (n != it.n) return fail(c, FM_EINVAL, "staging buffer smaller than a weight matrix");
-          hipLaunchKernelGGL(k_tile_weight, dim3(1024), dim3(256), 0, c->stream, c->stage, (f16_t*)it.dst, it.N, it.K,
-                             (it.N + 15) / 16 * 16, it.rope, c->D.hd);
+          const int Npad = (it.N + 15) / 16 * 16;
+          if (c->bf16) hipLaunchKernelGGL((k_tile_weight<f16_t>), dim3(1024), dim3(256), 0, c->stream, c->stage, (f16_t*)it.dst, it.N, it.K, Npad, it.rope, c->D.hd);
+          else hipLaunchKernelGGL((k_tile_weight<float>), dim3(1024), dim3(256), 0, c->stream, c->stage, (float*)it.dst, it.N, it.K, Npad, it.rope, c->D.hd);
         } else if (c->bf16)
           hipLaunchKernelGGL((k_convert<f16_t>), dim3(1024), dim3(256), 0, c->stream, c->stage, (f16_t*)it.dst + done, (long)n);
         else
@@ -1318,7 +1107,7 @@ int fm_prefill_condition(fm_ctx* c, int32_t seq, const float* mem_dev) {
   if (!c->weights_loaded) return fail(c, FM_ESTATE, "weights not loaded");
   if (seq < 0 || seq >= c->D.S) return fail(c, FM_EINVAL, "sequence %d out of range [0,%d)", seq, c->D.S);
   if (!mem_dev) return fail(c, FM_EINVAL, "null condition memory");
-  int rc = c->bf16 ? prefill_half(c, seq, mem_dev, c->stage) : prefill_f32(c, seq, mem_dev, c->stage);
+  int rc = c->bf16 ? prefill_impl<f16_t>(c, seq, mem_dev, c->stage) : prefill_impl<float>(c, seq, mem_dev, c->stage);
   if (rc == FM_OK) c->prefilled[seq] = true;
   return rc;
 }
@@ -1333,7 +1122,7 @@ int fm_prefill_condition_static(fm_ctx* c, int32_t seq, const float* mem_dev) {
   if (need > FM_STATIC_SCRATCH_BYTES)
     return fail(c, FM_EINVAL, "condition memory of %d x %d needs %zu staging bytes, the static area holds %u: use fm_prefill_condition",
                 c->D.M, c->D.d, need, (unsigned)FM_STATIC_SCRATCH_BYTES);
-  int rc = c->bf16 ? prefill_half(c, seq, mem_dev, c->static_scratch) : prefill_f32(c, seq, mem_dev, c->static_scratch);
+  int rc = c->bf16 ? prefill_impl<f16_t>(c, seq, mem_dev, c->static_scratch) : prefill_impl<float>(c, seq, mem_dev, c->static_scratch);
   if (rc == FM_OK) c->prefilled[seq] = true;
   return rc;
 }
@@ -1481,16 +1270,12 @@ int fm_debug_mem_kv(fm_ctx* c, int32_t seq, int32_t block, float* host_k, float*
     for (int m = 0; m < D.M; m++)
       for (int i = 0; i < D.d; i++) {
         const int hh = i / hd, e = i % hd;
-        if (c->bf16) {
-          // the blocked layouts of the half path: 32-key blocks of a head; K in MFMA fragment order, V as [dim][key slot]
-          const int r = m & 31;
-          size_t o = ((size_t)hh * capb + (m >> 5)) * 32 * hd;
-          if (kv == 0) o += (size_t)((((r >> 4) * (hd / 32) + (e >> 5)) * 64 + (r & 15) + 16 * ((e & 31) >> 3)) * 8 + (e & 7));
-          else o += (size_t)e * 32 + ((r & 15) >> 2) * 8 + (r >> 4) * 4 + (r & 3);
-          out[(size_t)m * D.d + i] = (float)((const f16_t*)raw.data())[o];
-        } else {
-          out[(size_t)m * D.d + i] = ((const float*)raw.data())[((size_t)hh * D.M + m) * hd + e];
-        }
+        // the blocked layouts: 32-key blocks of a head; K in MFMA fragment order, V as [dim][key slot]
+        const int r = m & 31;
+        size_t o = ((size_t)hh * capb + (m >> 5)) * 32 * hd;
+        if (kv == 0) o += (size_t)((((r >> 4) * (hd / 32) + (e >> 5)) * 64 + (r & 15) + 16 * ((e & 31) >> 3)) * 8 + (e & 7));
+        else o += (size_t)e * 32 + ((r & 15) >> 2) * 8 + (r >> 4) * 4 + (r & 3);
+        out[(size_t)m * D.d + i] = c->bf16 ? (float)((const f16_t*)raw.data())[o] : ((const float*)raw.data())[o];
       }
   }
   return FM_OK;
@@ -1628,9 +1413,9 @@ int fm_measure_gemm(fm_ctx* c, int32_t rows, double* host_out) {
   for (int st = 0; st < 5; st++) for (auto& Lx : c->stacks[st]) ws.push_back(Lx.w1);
   int cyc = 1;
   if (const char* e = getenv("FM_GEMM_PROBE_CYCLE")) cyc = std::max(1, std::min(atoi(e), (int)ws.size()));
-  for (int i = 0; i < cyc; i++) { a.W = (const f16_t*)ws[i]; dec_gemm<DE_GELU, false>(a, 1, c->stream); }
+  for (int i = 0; i < cyc; i++) { a.W = ws[i]; dec_gemm<f16_t, DE_GELU, false>(a, 1, c->stream); }
   PK_TRY(hipEventRecord(e0, c->stream));
-  for (int i = 0; i < reps; i++) { a.W = (const f16_t*)ws[i % cyc]; dec_gemm<DE_GELU, false>(a, 1, c->stream); }
+  for (int i = 0; i < reps; i++) { a.W = ws[i % cyc]; dec_gemm<f16_t, DE_GELU, false>(a, 1, c->stream); }
   PK_TRY(hipEventRecord(e1, c->stream)); PK_TRY(hipEventSynchronize(e1)); PK_TRY(hipEventElapsedTime(&ms, e0, e1));
   host_out[0] = ms / reps;
   host_out[1] = 2.0 * rows * (double)N * d * reps / (ms * 1e-3) / 1e12;

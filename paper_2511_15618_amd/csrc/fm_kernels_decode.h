@@ -1,5 +1,5 @@
-// Decode-path kernels of the half-precision contexts (gfx950, v_mfma_f32_16x16x32_f16): the skinny GEMM and the block
-// attention that every operator of a verify pass and of the draft heads is made of.
+// Decode-path kernels (gfx950): the skinny GEMM and the block attention that every operator of a verify pass and of the draft
+// heads is made of, in both storage types (T = half or float; what follows says "half" where the storage type is meant).
 //
 // A pass is a chain of several hundred dependent launches of 9 to ~100 rows each, so what bounds it is the length of one
 // launch, not a rate: a launch boundary in a replayed graph costs 1.7 to 2.9 us on this chip, one trip to memory about
@@ -20,8 +20,6 @@
 #include "fm_device.h"
 #include "fm_kernels_basic.h"
 #include "fm_kernels_mfma.h"
-
-typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 
 // element offset of (row m, column n) in a tiled buffer of KT = columns / 32
 __device__ __forceinline__ long tile_off(int m, int n, int KT) {
@@ -44,8 +42,8 @@ __device__ __forceinline__ long map_off(const RowMap& rm, int s, int q, int n, i
 enum { DE_RES = 0, DE_GELU, DE_ROW, DE_TILE, DE_F32, DE_QKV, DE_ROPE };
 
 struct DecGemm {
-  const f16_t* A; long gsa;      // tiled activations, elements per group
-  const f16_t* W; long gsw;      // tiled weights, elements per group
+  const void* A; long gsa;       // tiled activations, elements per group
+  const void* W; long gsw;       // tiled weights, elements per group
   int M, N, KT;                  // rows per group, columns, K / 32
   const float* ssq;              // NORM: [row tile][K/16][16] sums of squares of 16 columns each
   float inv_k, eps;
@@ -53,7 +51,7 @@ struct DecGemm {
   // outputs (which of them: the epilogue)
   void* Y; long ldy, gsy;        // row-major output: fp32 (DE_RES, DE_F32) or half (DE_ROW, DE_QKV q, DE_ROPE)
   const float* R; long ldr, gsr; // fp32 rows added (DE_RES, DE_F32; may be null, may be Y)
-  f16_t* X; long gsx;            // tiled half output of width N (DE_GELU, DE_TILE; DE_RES: x * gain, may be null)
+  void* X; long gsx;             // tiled half output of width N (DE_GELU, DE_TILE; DE_RES: x * gain, may be null)
   const float* gain;             // DE_RES: gain of the norm that follows
   float* ssq_out;                // DE_RES: [row tile][N/16][16]
   const int* pos;                // DE_RES with rings, DE_QKV: position of each row, -1 = inactive
@@ -61,44 +59,46 @@ struct DecGemm {
   float *tap, *ring; int rs;     // DE_RES: rings (rs entries per sequence) that receive the old row (tap) and the new row
   const float2* cs;              // DE_QKV, DE_ROPE: [row][hd/2] (cos, sin); DE_ROPE: row = m * ldc + group
   int ldc, hd;
-  f16_t *Kc, *Vc; long seq_stride; int capb, H;   // DE_QKV: blocked caches
+  void *Kc, *Vc; long seq_stride; int capb, H;   // DE_QKV: blocked caches
 };
 
 // MT row tiles x NC column tiles of 16 per workgroup, NW waves split K.
 // U fragments per wave and chunk: the first chunk (all of the K slice for the usual shapes) is in flight before
 // anything is waited for, later chunks one ahead.
-template <int MT, int NC, int NW, int U, bool LOOP, int EPI, bool NORM>
+template <typename T, int MT, int NC, int NW, int U, bool LOOP, int EPI, bool NORM>
 __global__ __launch_bounds__(NW * 64) void k_dec_gemm(DecGemm a) {
-  constexpr int T = MT * NC;
+  typedef typename Op<T>::V8 V8;
+  typedef typename Op<T>::V4 V4;
+  constexpr int NTILE = MT * NC;
   extern __shared__ f32x4 dg_smem[];
-  f32x4* red = dg_smem;                                    // [NW][T][64]
-  float* sq = (float*)(dg_smem + NW * T * 64);             // [NW][MT][16]
+  f32x4* red = dg_smem;                                    // [NW][tiles][64]
+  float* sq = (float*)(dg_smem + NW * NTILE * 64);             // [NW][MT][16]
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int g = lane >> 4, rl = lane & 15;
   const int grp = blockIdx.z, mb = blockIdx.y, nt0 = blockIdx.x * NC;
   const int rf = a.run_flag ? *a.run_flag : 1;
   const int KT = a.KT, mt0 = mb * MT;
   const int ntile = (a.M + 15) / 16;
-  const f16_t* Ap = a.A + (long)grp * a.gsa + lane * 8;
-  const f16_t* Wp = a.W + (long)grp * a.gsw + (long)nt0 * KT * 512 + lane * 8;
+  const T* Ap = (const T*)a.A + (long)grp * a.gsa + lane * 8;
+  const T* Wp = (const T*)a.W + (long)grp * a.gsw + (long)nt0 * KT * 512 + lane * 8;
   const int FW = (KT + NW - 1) / NW, kt0 = wave * FW, nk = min(FW, KT - kt0);
   f32x4 acc[MT][NC];
 #pragma unroll
   for (int mt = 0; mt < MT; mt++)
 #pragma unroll
     for (int c = 0; c < NC; c++) acc[mt][c] = f32x4{0.f, 0.f, 0.f, 0.f};
-  f16x8 wc[NC][U], ac[MT][U];
-  auto load_chunk = [&](f16x8 (&w)[NC][U], f16x8 (&x)[MT][U], int i0) {
+  V8 wc[NC][U], ac[MT][U];
+  auto load_chunk = [&](V8 (&w)[NC][U], V8 (&x)[MT][U], int i0) {
 #pragma unroll
     for (int u = 0; u < U; u++)
       if (i0 + u < nk) {
         const long kt = kt0 + i0 + u;
 #pragma unroll
-        for (int c = 0; c < NC; c++) w[c][u] = *reinterpret_cast<const f16x8*>(Wp + ((long)c * KT + kt) * 512);
+        for (int c = 0; c < NC; c++) w[c][u] = *reinterpret_cast<const V8*>(Wp + ((long)c * KT + kt) * 512);
 #pragma unroll
         for (int mt = 0; mt < MT; mt++) {
           const int t = min(mt0 + mt, ntile - 1);          // a tile past the last one is computed on the last one's rows, never stored
-          x[mt][u] = *reinterpret_cast<const f16x8*>(Ap + ((long)t * KT + kt) * 512);
+          x[mt][u] = *reinterpret_cast<const V8*>(Ap + ((long)t * KT + kt) * 512);
         }
       }
   };
@@ -106,7 +106,7 @@ __global__ __launch_bounds__(NW * 64) void k_dec_gemm(DecGemm a) {
   // operands of the epilogue of this wave's first result tile
   const int tm = wave / NC, tc = wave % NC;
   const int em = (mt0 + tm) * 16 + rl, en = (nt0 + tc) * 16 + g * 4;
-  const bool eon = wave < T && em < a.M;
+  const bool eon = wave < NTILE && em < a.M;
   f32x4 rv = f32x4{0.f, 0.f, 0.f, 0.f}, gv = rv, c0 = rv, c1 = rv;
   int ep = -1;
   if (eon) {
@@ -140,19 +140,19 @@ __global__ __launch_bounds__(NW * 64) void k_dec_gemm(DecGemm a) {
   }
   asm volatile("" ::: "memory");      // the loads above stay above the exit
   if (rf == 0) return;
-  auto mul_chunk = [&](f16x8 (&w)[NC][U], f16x8 (&x)[MT][U], int i0) {
+  auto mul_chunk = [&](V8 (&w)[NC][U], V8 (&x)[MT][U], int i0) {
 #pragma unroll
     for (int u = 0; u < U; u++)
       if (i0 + u < nk) {
 #pragma unroll
         for (int mt = 0; mt < MT; mt++)
 #pragma unroll
-          for (int c = 0; c < NC; c++) acc[mt][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w[c][u], x[mt][u], acc[mt][c], 0, 0, 0);
+          for (int c = 0; c < NC; c++) acc[mt][c] = Op<T>::mul(w[c][u], x[mt][u], acc[mt][c]);
       }
   };
   if constexpr (LOOP) {
     for (int i0 = 0; i0 < nk; i0 += 2 * U) {
-      f16x8 wn[NC][U], an[MT][U];
+      V8 wn[NC][U], an[MT][U];
       load_chunk(wn, an, i0 + U);
       mul_chunk(wc, ac, i0);
       load_chunk(wc, ac, i0 + 2 * U);
@@ -165,7 +165,7 @@ __global__ __launch_bounds__(NW * 64) void k_dec_gemm(DecGemm a) {
 #pragma unroll
   for (int mt = 0; mt < MT; mt++) {
 #pragma unroll
-    for (int c = 0; c < NC; c++) red[(wave * T + mt * NC + c) * 64 + lane] = acc[mt][c];
+    for (int c = 0; c < NC; c++) red[(wave * NTILE + mt * NC + c) * 64 + lane] = acc[mt][c];
     if constexpr (NORM) {
       float t = ss[mt];
       t += __shfl_xor(t, 16, 64);
@@ -174,12 +174,12 @@ __global__ __launch_bounds__(NW * 64) void k_dec_gemm(DecGemm a) {
     }
   }
   __syncthreads();
-  for (int t = wave; t < T; t += NW) {
+  for (int t = wave; t < NTILE; t += NW) {
     const int mt = t / NC, ntc = nt0 + t % NC;
     const int m = (mt0 + mt) * 16 + rl, n = ntc * 16 + g * 4;
     f32x4 v = red[t * 64 + lane];
 #pragma unroll
-    for (int w = 1; w < NW; w++) v += red[(w * T + t) * 64 + lane];
+    for (int w = 1; w < NW; w++) v += red[(w * NTILE + t) * 64 + lane];
     if constexpr (NORM) {
       float tot = sq[mt * 16 + rl];
 #pragma unroll
@@ -187,7 +187,7 @@ __global__ __launch_bounds__(NW * 64) void k_dec_gemm(DecGemm a) {
       v *= 1.0f / sqrtf(tot * a.inv_k + a.eps);
     }
     const bool on = m < a.M;
-    const bool first = t == wave && T <= NW;     // operands already here
+    const bool first = t == wave && NTILE <= NW;     // operands already here
     if constexpr (EPI == DE_RES) {
       if (on) {
         if (!first && a.R) rv = *reinterpret_cast<const f32x4*>(a.R + (long)m * a.ldr + n);
@@ -196,10 +196,10 @@ __global__ __launch_bounds__(NW * 64) void k_dec_gemm(DecGemm a) {
         v += rv;
         *reinterpret_cast<f32x4*>((float*)a.Y + (long)m * a.ldy + n) = v;
         if (a.X) {
-          f16x4 o;
+          V4 o;
 #pragma unroll
-          for (int i = 0; i < 4; i++) o[i] = (f16_t)(v[i] * gv[i]);
-          *reinterpret_cast<f16x4*>(a.X + tile_off(m, n, a.N >> 5)) = o;
+          for (int i = 0; i < 4; i++) o[i] = (T)(v[i] * gv[i]);
+          *reinterpret_cast<V4*>((T*)a.X + tile_off(m, n, a.N >> 5)) = o;
         }
         if (ep >= 0) {
           const long ro = ((long)(m / a.RPS) * a.rs + (ep & (a.rs - 1))) * a.N + n;
@@ -215,17 +215,17 @@ __global__ __launch_bounds__(NW * 64) void k_dec_gemm(DecGemm a) {
       }
     } else if constexpr (EPI == DE_GELU || EPI == DE_TILE) {
       if (on) {
-        f16x4 o;
+        V4 o;
 #pragma unroll
-        for (int i = 0; i < 4; i++) o[i] = (f16_t)(EPI == DE_GELU ? gelu_tanh_f(v[i]) : v[i]);
-        *reinterpret_cast<f16x4*>(a.X + (long)grp * a.gsx + tile_off(m, n, a.N >> 5)) = o;
+        for (int i = 0; i < 4; i++) o[i] = (T)(EPI == DE_GELU ? gelu_tanh_f(v[i]) : v[i]);
+        *reinterpret_cast<V4*>((T*)a.X + (long)grp * a.gsx + tile_off(m, n, a.N >> 5)) = o;
       }
     } else if constexpr (EPI == DE_ROW) {
       if (on) {
-        f16x4 o;
+        V4 o;
 #pragma unroll
-        for (int i = 0; i < 4; i++) o[i] = (f16_t)v[i];
-        *reinterpret_cast<f16x4*>((f16_t*)a.Y + (long)grp * a.gsy + (long)m * a.ldy + n) = o;
+        for (int i = 0; i < 4; i++) o[i] = (T)v[i];
+        *reinterpret_cast<V4*>((T*)a.Y + (long)grp * a.gsy + (long)m * a.ldy + n) = o;
       }
     } else if constexpr (EPI == DE_F32) {
       if (on) {
@@ -261,11 +261,11 @@ __global__ __launch_bounds__(NW * 64) void k_dec_gemm(DecGemm a) {
         dim = (g < 2 ? 0 : a.hd >> 1) + qd * 8 + (g & 1) * 4;
       }
       if (on) {
-        f16x4 o;
+        V4 o;
 #pragma unroll
-        for (int i = 0; i < 4; i++) o[i] = (f16_t)v[i];
+        for (int i = 0; i < 4; i++) o[i] = (T)v[i];
         if (part == 0) {
-          *reinterpret_cast<f16x4*>((f16_t*)a.Y + (long)grp * a.gsy + (long)m * a.ldy + hh * a.hd + dim) = o;
+          *reinterpret_cast<V4*>((T*)a.Y + (long)grp * a.gsy + (long)m * a.ldy + hh * a.hd + dim) = o;
         } else {
           if (!first) ep = a.pos[m];
           if (ep >= 0) {
@@ -274,11 +274,11 @@ __global__ __launch_bounds__(NW * 64) void k_dec_gemm(DecGemm a) {
             const long base = (long)(m / a.RPS) * a.seq_stride + ((long)hh * a.capb + (p >> 5)) * (32 * a.hd);
             if (part == 1) {
               const int f = (r >> 4) * (a.hd >> 5) + (dim >> 5), ln = (r & 15) + 16 * ((dim & 31) >> 3);
-              *reinterpret_cast<f16x4*>(a.Kc + base + (f * 64 + ln) * 8 + (dim & 7)) = o;
+              *reinterpret_cast<V4*>((T*)a.Kc + base + (f * 64 + ln) * 8 + (dim & 7)) = o;
             } else {
               const int slot = ((r & 15) >> 2) * 8 + (r >> 4) * 4 + (r & 3);
 #pragma unroll
-              for (int i = 0; i < 4; i++) a.Vc[base + (dim + i) * 32 + slot] = o[i];
+              for (int i = 0; i < 4; i++) ((T*)a.Vc)[base + (dim + i) * 32 + slot] = o[i];
             }
           }
         }
@@ -296,18 +296,18 @@ __global__ __launch_bounds__(NW * 64) void k_dec_gemm(DecGemm a) {
 // bit for bit), and it is balanced at every length: short contexts keep all keys in one workgroup (no merge), long
 // ones use all of them.  Partial results of several splits are merged, in split order, by the workgroup that arrives last.
 struct AttnSet {
-  const f16_t* q;            // [sequence][RS rows][d] rotated queries
+  const void* q;             // [sequence][RS rows][d] rotated queries
   const int* limit;          // [sequence][RS] last visible key, -1 = inactive row
   int rows, q0, RS;          // this launch takes rows q0 .. q0 + rows of every sequence
-  const f16_t *Kc, *Vc;
+  const void *Kc, *Vc;
   long seq_stride;           // elements between the caches of two sequences
   int capb, window, ns;      // capacity in blocks, sliding window (0 = none; the cache is then a ring), splits
   RowMap rm;                 // where the rows go in the tiled output
-  f16_t* out;
+  void* out;
 };
 #define FM_ATTN_SETS 4
 // Weights that a launch reads ahead for the ones behind it: `groups` column tiles of `bytes` each.
-struct WeightRange { const f16_t* W; int bytes, groups; };
+struct WeightRange { const void* W; int bytes, groups; };
 struct AttnArgs {
   AttnSet set[FM_ATTN_SETS];     // first member of the only kernel argument (attn_set)
   int S, H, ns_max;
@@ -331,8 +331,10 @@ __device__ __forceinline__ int attn_active(int maxlim, int capb, int ns, int NW)
 __device__ __forceinline__ void ld_agent4(f32x4& v, const float* p) { asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(v) : "v"(p) : "memory"); }
 __device__ __forceinline__ void ld_agent1(float& v, const float* p) { asm volatile("global_load_dword %0, %1, off sc1" : "=v"(v) : "v"(p) : "memory"); }
 
-template <int QT, int HD, int NW>
+template <typename T, int QT, int HD, int NW>
 __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
+  typedef typename Op<T>::V8 V8;
+  typedef typename Op<T>::V4 V4;
   constexpr int NQ = QT * 16, KC = HD / 32, DT = HD / 16, BLK = 32 * HD, PSZ = NQ * HD + 2 * NQ, LD = HD + 4;
   extern __shared__ f32x4 da_smem[];
   float* lo = (float*)da_smem;              // [NW][NQ][LD]
@@ -367,24 +369,24 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
   const int rf = a.run_flag ? *a.run_flag : 1;
   const int d = a.H * HD;
   const float kScale = (HD == 64 ? 0.125f : 1.0f / sqrtf((float)HD)) * 1.4426950408889634f;   // 1/sqrt(HD) * log2(e)
-  const f16_t* Kb = A->Kc + (long)s * A->seq_stride + (long)hh * A->capb * BLK + lane * 8;
-  const f16_t* Vb = A->Vc + (long)s * A->seq_stride + (long)hh * A->capb * BLK + ql * 32 + g * 8;
+  const T* Kb = (const T*)A->Kc + (long)s * A->seq_stride + (long)hh * A->capb * BLK + lane * 8;
+  const T* Vb = (const T*)A->Vc + (long)s * A->seq_stride + (long)hh * A->capb * BLK + ql * 32 + g * 8;
   // the first block of this wave is inside the cache whatever the length: request it before anything else is known
   const int bstep = A->ns * NW;
   int b = split * NW + wave;
-  f16x8 kf[2 * KC], vf[DT];
+  V8 kf[2 * KC], vf[DT];
   auto load_k = [&](int blk) {
 #pragma unroll
-    for (int f = 0; f < 2 * KC; f++) kf[f] = *reinterpret_cast<const f16x8*>(Kb + (long)blk * BLK + f * 512);
+    for (int f = 0; f < 2 * KC; f++) kf[f] = *reinterpret_cast<const V8*>(Kb + (long)blk * BLK + f * 512);
   };
   auto load_v = [&](int blk) {
 #pragma unroll
-    for (int dt = 0; dt < DT; dt++) vf[dt] = *reinterpret_cast<const f16x8*>(Vb + (long)blk * BLK + dt * 512);
+    for (int dt = 0; dt < DT; dt++) vf[dt] = *reinterpret_cast<const V8*>(Vb + (long)blk * BLK + dt * 512);
   };
   load_k(min(b, A->capb - 1));
   load_v(min(b, A->capb - 1));
   int lim[QT], first[QT];
-  f16x8 qf[QT][KC];
+  V8 qf[QT][KC];
   int maxlim = -1;
 #pragma unroll
   for (int t = 0; t < QT; t++) {
@@ -392,9 +394,9 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
     const bool on = qi < A->rows;
     const long row = (long)s * A->RS + A->q0 + (on ? qi : 0);
     lim[t] = on ? A->limit[row] : -1;
-    const f16_t* qp = A->q + row * d + hh * HD + g * 8;
+    const T* qp = (const T*)A->q + row * d + hh * HD + g * 8;
 #pragma unroll
-    for (int kc = 0; kc < KC; kc++) qf[t][kc] = *reinterpret_cast<const f16x8*>(qp + kc * 32);
+    for (int kc = 0; kc < KC; kc++) qf[t][kc] = *reinterpret_cast<const V8*>(qp + kc * 32);
   }
   asm volatile("" ::: "memory");      // the loads above stay above the exit
   if (rf == 0) return;
@@ -437,7 +439,7 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
       for (int hb = 0; hb < 2; hb++) {
         f32x4 zz = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int kc = 0; kc < KC; kc++) zz = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf[hb * KC + kc], qf[t][kc], zz, 0, 0, 0);
+        for (int kc = 0; kc < KC; kc++) zz = Op<T>::mul(kf[hb * KC + kc], qf[t][kc], zz);
         sT[t][hb] = zz;
       }
     if (b + bstep < nblk) load_k(bn);
@@ -460,7 +462,7 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
       const float msafe = mnew == -INFINITY ? 0.f : mnew;
       const float alpha = __builtin_amdgcn_exp2f(mrun[t] - msafe);   // exp2(-inf) = 0 on the first block
       mrun[t] = mnew;
-      f16x8 pf;
+      V8 pf;
       float psum = 0.f;
 #pragma unroll
       for (int hb = 0; hb < 2; hb++)
@@ -468,13 +470,13 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
         for (int i = 0; i < 4; i++) {
           const float p = __builtin_amdgcn_exp2f(sT[t][hb][i] - msafe);
           psum += p;
-          pf[hb * 4 + i] = (f16_t)p;
+          pf[hb * 4 + i] = (T)p;
         }
       lrun[t] = lrun[t] * alpha + psum;
 #pragma unroll
       for (int dt = 0; dt < DT; dt++) {
         o[t][dt] *= alpha;
-        o[t][dt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vf[dt], pf, o[t][dt], 0, 0, 0);   // O^T[dim][q]
+        o[t][dt] = Op<T>::mul(vf[dt], pf, o[t][dt]);   // O^T[dim][q]
       }
     }
     if (b + bstep < nblk) load_v(bn);
@@ -505,10 +507,10 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
       den += ll[w * NQ + qi] * f;
     }
     if (nact == 1) {
-      f16x4 ov;
+      V4 ov;
 #pragma unroll
-      for (int i = 0; i < 4; i++) ov[i] = (f16_t)(den > 0.f ? num[i] / den : 0.f);
-      *reinterpret_cast<f16x4*>(A->out + map_off(rm, s, A->q0 + qi, hh * HD + dim, d >> 5)) = ov;
+      for (int i = 0; i < 4; i++) ov[i] = (T)(den > 0.f ? num[i] / den : 0.f);
+      *reinterpret_cast<V4*>((T*)A->out + map_off(rm, s, A->q0 + qi, hh * HD + dim, d >> 5)) = ov;
     } else {
 #pragma unroll
       for (int i = 0; i < 4; i++) st_agent(part + qi * HD + dim + i, num[i]);
@@ -566,10 +568,10 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
           den += l[j] * f;
         }
     }
-    f16x4 ov;
+    V4 ov;
 #pragma unroll
-    for (int i = 0; i < 4; i++) ov[i] = (f16_t)(den > 0.f ? num[i] / den : 0.f);
-    *reinterpret_cast<f16x4*>(A->out + map_off(rm, s, A->q0 + qi, hh * HD + dim, d >> 5)) = ov;
+    for (int i = 0; i < 4; i++) ov[i] = (T)(den > 0.f ? num[i] / den : 0.f);
+    *reinterpret_cast<V4*>((T*)A->out + map_off(rm, s, A->q0 + qi, hh * HD + dim, d >> 5)) = ov;
   }
 }
 
@@ -583,21 +585,24 @@ __device__ __forceinline__ float quad_sum(float v) {
   return v;
 }
 // four columns n.. of row m of a residual stream: fp32 row, half(x * gain) in tiled order, sum of squares per 16 columns
-__device__ __forceinline__ void put_row4(const f32x4& v, int m, int n, int d, float* h, f16_t* xg, const float* gain, float* ssq) {
+template <typename T>
+__device__ __forceinline__ void put_row4(const f32x4& v, int m, int n, int d, float* h, T* xg, const float* gain, float* ssq) {
   *reinterpret_cast<f32x4*>(h + (long)m * d + n) = v;
   const f32x4 gv = *reinterpret_cast<const f32x4*>(gain + n);
-  f16x4 o;
+  typedef typename Op<T>::V4 V4;
+  V4 o;
 #pragma unroll
-  for (int i = 0; i < 4; i++) o[i] = (f16_t)(v[i] * gv[i]);
-  *reinterpret_cast<f16x4*>(xg + tile_off(m, n, d >> 5)) = o;
+  for (int i = 0; i < 4; i++) o[i] = (T)(v[i] * gv[i]);
+  *reinterpret_cast<V4*>(xg + tile_off(m, n, d >> 5)) = o;
   const float t = quad_sum(v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3]);
   if ((threadIdx.x & 3) == 0) ssq[((long)(m >> 4) * (d >> 4) + (n >> 4)) * 16 + (m & 15)] = t;
 }
 
 // RMSNorm of gathered rows into the tiled input of a grouped GEMM (row r = s * per_seq + q, gain of head r % gain_mod),
 // keeping the fp32 rows for a later residual add
+template <typename T>
 __global__ __launch_bounds__(256) void k_dec_rmsnorm(const float* const* __restrict__ srcptr, const float* __restrict__ gain, int gain_mod,
-                                                      f16_t* __restrict__ out, RowMap rm, int per_seq, float* __restrict__ keep, int d,
+                                                      T* __restrict__ out, RowMap rm, int per_seq, float* __restrict__ keep, int d,
                                                       float eps, const int* run_flag) {
   const int r = blockIdx.x;
   const int rf = run_flag ? *run_flag : 1;
@@ -621,16 +626,17 @@ __global__ __launch_bounds__(256) void k_dec_rmsnorm(const float* const* __restr
     const f32x4 v = n < 1024 ? v0 : *reinterpret_cast<const f32x4*>(x + n);
     const f32x4 gv = *reinterpret_cast<const f32x4*>(g + n);
     if (keep) *reinterpret_cast<f32x4*>(keep + (long)r * d + n) = v;
-    f16x4 o;
+    typename Op<T>::V4 o;
 #pragma unroll
-    for (int i = 0; i < 4; i++) o[i] = (f16_t)(v[i] * inv * gv[i]);
-    *reinterpret_cast<f16x4*>(out + map_off(rm, r / per_seq, r % per_seq, n, d >> 5)) = o;
+    for (int i = 0; i < 4; i++) o[i] = (T)(v[i] * inv * gv[i]);
+    *reinterpret_cast<typename Op<T>::V4*>(out + map_off(rm, r / per_seq, r % per_seq, n, d >> 5)) = o;
   }
 }
 
 // coarse slot j pools fine rows 3j-2, 3j-1, 3j (rows before the start count as zero; always / 3)
+template <typename T>
 __global__ __launch_bounds__(256) void k_dec_pool3(const float* __restrict__ ring_fine, int RSf, const int* __restrict__ pos_coarse,
-                                                    int RPS, f16_t* __restrict__ out, int d) {
+                                                    int RPS, T* __restrict__ out, int d) {
   const int r = blockIdx.x, j = pos_coarse[r], s = r / RPS;
   for (int n = threadIdx.x * 4; n < d; n += 1024) {
     f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -638,16 +644,17 @@ __global__ __launch_bounds__(256) void k_dec_pool3(const float* __restrict__ rin
       for (int k = 3 * j - 2; k <= 3 * j; k++)
         if (k >= 0) acc += *reinterpret_cast<const f32x4*>(ring_fine + ((long)s * RSf + (k & (RSf - 1))) * d + n);
     }
-    f16x4 o;
+    typename Op<T>::V4 o;
 #pragma unroll
-    for (int i = 0; i < 4; i++) o[i] = (f16_t)(acc[i] / 3.0f);
-    *reinterpret_cast<f16x4*>(out + tile_off(r, n, d >> 5)) = o;
+    for (int i = 0; i < 4; i++) o[i] = (T)(acc[i] / 3.0f);
+    *reinterpret_cast<typename Op<T>::V4*>(out + tile_off(r, n, d >> 5)) = o;
   }
 }
 
 // fine row at position p: its own stream (the skip) plus the coarse output of slot floor(p/3)
+template <typename T>
 __global__ __launch_bounds__(256) void k_dec_upsample(float* __restrict__ h, const int* __restrict__ pos, int RPS,
-                                                       const float* __restrict__ ring_coarse, int RSc, int d, f16_t* __restrict__ xg,
+                                                       const float* __restrict__ ring_coarse, int RSc, int d, T* __restrict__ xg,
                                                        const float* __restrict__ gain, float* __restrict__ ssq) {
   const int r = blockIdx.x, p = pos[r];
   const float* c = ring_coarse + ((long)(r / RPS) * RSc + ((max(p, 0) / 3) & (RSc - 1))) * d;
@@ -661,12 +668,12 @@ __global__ __launch_bounds__(256) void k_dec_upsample(float* __restrict__ h, con
 // ------------------------------------------------------------------------------------------
 // Launch rules
 // ------------------------------------------------------------------------------------------
-template <int MT, int NC, int NW, int U, bool LOOP, int EPI, bool NORM>
+template <typename T, int MT, int NC, int NW, int U, bool LOOP, int EPI, bool NORM>
 void dec_gemm_launch(const DecGemm& a, int groups, hipStream_t st) {
   const int tiles = (a.M + 15) / 16, NT = (a.N + 15) / 16;
   const size_t lds = (size_t)NW * MT * NC * 1024 + NW * MT * 64;
-  if (lds > 65536) (void)hipFuncSetAttribute((const void*)k_dec_gemm<MT, NC, NW, U, LOOP, EPI, NORM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  hipLaunchKernelGGL((k_dec_gemm<MT, NC, NW, U, LOOP, EPI, NORM>), dim3((NT + NC - 1) / NC, (tiles + MT - 1) / MT, groups), dim3(NW * 64), lds, st, a);
+  if (lds > 65536) (void)hipFuncSetAttribute((const void*)k_dec_gemm<T, MT, NC, NW, U, LOOP, EPI, NORM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipLaunchKernelGGL((k_dec_gemm<T, MT, NC, NW, U, LOOP, EPI, NORM>), dim3((NT + NC - 1) / NC, (tiles + MT - 1) / MT, groups), dim3(NW * 64), lds, st, a);
 }
 
 // Which tile a launch gets.  gridDim.x = column tiles comes first in the block order, so the row tiles of a column tile run on
@@ -674,21 +681,27 @@ void dec_gemm_launch(const DecGemm& a, int groups, hipStream_t st) {
 // Measured in a chain of dependent launches over cold weights (us; M rows, d = K of the first four):
 //   M = 9, d = 1024: projection 3.7, up 4.5, down 6.8      M = 27, d = 768: 3.5, 4.4, 5.9
 //   M = 72, d = 1024: 4.1, 6.7, 7.6                        M = 72, d = 1536: 5.1, 11.1, 11.7
-template <int EPI, bool NORM>
+template <typename T, int EPI, bool NORM>
 void dec_gemm(const DecGemm& a, int groups, hipStream_t st) {
   const int tiles = (a.M + 15) / 16, NT = (a.N + 15) / 16, KT = a.KT;
   const long wgs = (long)NT * tiles * groups;
   const bool pairs = NT % 2 == 0;
-  // tall problems: operands shared by more of a workgroup's results, K in double-buffered chunks
-  if (tiles >= 8 && pairs) return dec_gemm_launch<4, 2, 8, 4, true, EPI, NORM>(a, groups, st);
-  // K too long for one trip
-  if (KT > 128) return wgs > 400 && pairs ? dec_gemm_launch<1, 2, 8, 8, true, EPI, NORM>(a, groups, st) : dec_gemm_launch<1, 1, 8, 8, true, EPI, NORM>(a, groups, st);
-  // long K: 8 or 16 waves hold the whole K of their columns in flight
-  if (KT > 64) return wgs > 200 && tiles >= 2 ? dec_gemm_launch<2, 1, 16, 8, false, EPI, NORM>(a, groups, st) : dec_gemm_launch<1, 1, 8, 16, false, EPI, NORM>(a, groups, st);
-  // few workgroups: one tile each
-  if (wgs <= 400 || !pairs) return dec_gemm_launch<1, 1, 4, 16, false, EPI, NORM>(a, groups, st);
-  // many: two column tiles share the activations
-  return KT <= 32 ? dec_gemm_launch<1, 2, 4, 8, false, EPI, NORM>(a, groups, st) : dec_gemm_launch<1, 2, 8, 8, false, EPI, NORM>(a, groups, st);
+  if constexpr (std::is_same<T, float>::value) {
+    // fp32: small models; operands take twice the registers
+    if (tiles >= 8 && pairs) return dec_gemm_launch<T, 2, 2, 8, 2, true, EPI, NORM>(a, groups, st);
+    return KT <= 32 ? dec_gemm_launch<T, 1, 1, 4, 8, false, EPI, NORM>(a, groups, st) : dec_gemm_launch<T, 1, 1, 8, 4, true, EPI, NORM>(a, groups, st);
+  } else {
+    // tall problems: operands shared by more of a workgroup's results, K in double-buffered chunks
+    if (tiles >= 8 && pairs) return dec_gemm_launch<T, 4, 2, 8, 4, true, EPI, NORM>(a, groups, st);
+    // K too long for one trip
+    if (KT > 128) return wgs > 400 && pairs ? dec_gemm_launch<T, 1, 2, 8, 8, true, EPI, NORM>(a, groups, st) : dec_gemm_launch<T, 1, 1, 8, 8, true, EPI, NORM>(a, groups, st);
+    // long K: 8 or 16 waves hold the whole K of their columns in flight
+    if (KT > 64) return wgs > 200 && tiles >= 2 ? dec_gemm_launch<T, 2, 1, 16, 8, false, EPI, NORM>(a, groups, st) : dec_gemm_launch<T, 1, 1, 8, 16, false, EPI, NORM>(a, groups, st);
+    // few workgroups: one tile each
+    if (wgs <= 400 || !pairs) return dec_gemm_launch<T, 1, 1, 4, 16, false, EPI, NORM>(a, groups, st);
+    // many: two column tiles share the activations
+    return KT <= 32 ? dec_gemm_launch<T, 1, 2, 4, 8, false, EPI, NORM>(a, groups, st) : dec_gemm_launch<T, 1, 2, 8, 8, false, EPI, NORM>(a, groups, st);
+  }
 }
 
 // Splits of an attention launch over `pairs` (head, sequence, set) triples: at most one workgroup of eight waves per compute
@@ -704,16 +717,17 @@ inline size_t attn_ws_floats(int H, int S, int sets, int hd) {
   return (size_t)(256 + pairs) * (32 * hd + 64);
 }
 
-template <int QT, int HD, int NW>
+template <typename T, int QT, int HD, int NW>
 void dec_attn_go(const AttnArgs& a, int nset, hipStream_t st) {
   const size_t lds = ((size_t)NW * QT * 16 * (HD + 4) + 2 * NW * QT * 16) * 4;
-  if (lds > 65536) (void)hipFuncSetAttribute((const void*)k_dec_attn<QT, HD, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  hipLaunchKernelGGL((k_dec_attn<QT, HD, NW>), dim3(a.H, a.ns_max, a.S * nset + a.ahead), dim3(NW * 64), lds, st, a);
+  if (lds > 65536) (void)hipFuncSetAttribute((const void*)k_dec_attn<T, QT, HD, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipLaunchKernelGGL((k_dec_attn<T, QT, HD, NW>), dim3(a.H, a.ns_max, a.S * nset + a.ahead), dim3(NW * 64), lds, st, a);
 }
 
 // Attention of `nset` row sets (at most 32 rows each) in one launch.
-inline bool dec_attention(AttnArgs& a, int nset, int hd, hipStream_t st) {
-  constexpr int NW = 8;
+template <typename T>
+bool dec_attention(AttnArgs& a, int nset, int hd, hipStream_t st) {
+  constexpr int NW = std::is_same<T, float>::value ? 4 : 8;      // fp32 operands need the registers of four waves per workgroup
   int QT = 1;
   a.ns_max = 1;
   for (int z = 0; z < nset; z++) {
@@ -724,8 +738,8 @@ inline bool dec_attention(AttnArgs& a, int nset, int hd, hipStream_t st) {
   }
   a.nset = nset;
   a.ahead = a.next[0].W ? (48 + a.H * a.ns_max - 1) / (a.H * a.ns_max) : 0;      // about 48 workgroups (32 to 128: no difference)
-  if (hd == 64) { if (QT == 1) dec_attn_go<1, 64, NW>(a, nset, st); else dec_attn_go<2, 64, NW>(a, nset, st); }
-  else if (hd == 96) { if (QT == 1) dec_attn_go<1, 96, NW>(a, nset, st); else dec_attn_go<2, 96, NW>(a, nset, st); }
-  else { if (QT == 1) dec_attn_go<1, 128, NW>(a, nset, st); else dec_attn_go<2, 128, NW>(a, nset, st); }
+  if (hd == 64) { if (QT == 1) dec_attn_go<T, 1, 64, NW>(a, nset, st); else dec_attn_go<T, 2, 64, NW>(a, nset, st); }
+  else if (hd == 96) { if (QT == 1) dec_attn_go<T, 1, 96, NW>(a, nset, st); else dec_attn_go<T, 2, 96, NW>(a, nset, st); }
+  else { if (QT == 1) dec_attn_go<T, 1, 128, NW>(a, nset, st); else dec_attn_go<T, 2, 128, NW>(a, nset, st); }
   return true;
 }

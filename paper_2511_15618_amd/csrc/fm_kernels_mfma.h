@@ -1,15 +1,36 @@
-// Layouts of the half-precision path (gfx950, v_mfma_f32_16x16x32_f16) and what puts data into them: weights in operand order, blocked K/V
-// caches, agent-scope access for exchanges inside a launch.
+// Layouts of weights, activations and K/V caches in matrix-operand order (gfx950) and what puts data into them; agent-scope access for
+// exchanges inside a launch.
 //
-// MFMA 16x16x32 operand layout (lane l of 64):
+// MFMA 16x16x32 f16 operand layout (lane l of 64):
 //   A[16 x 32]: row l%16, k = (l/16)*8 .. +8      B[32 x 16]: col l%16, k = (l/16)*8 .. +8
 //   C[16 x 16]: col l%16, rows (l/16)*4 + i, i = 0..3
+// The fp32 path uses the same layouts with eight floats in the place of eight halves: component j of the eight is one 16x16x4 f32
+// MFMA (A: row l%16, k = l/16), i.e. the eight of them sum over the same 32 k.
 #pragma once
 #include <type_traits>
 #include "fm_device.h"
 #include "fm_kernels_basic.h"
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+
+// operands of a storage type: a lane's eight k values, four neighbouring columns, and the product over 32 k
+template <typename T> struct Op;
+template <> struct Op<f16_t> {
+  typedef f16x8 V8;
+  typedef f16x4 V4;
+  static __device__ __forceinline__ f32x4 mul(const V8& a, const V8& b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
+};
+template <> struct Op<float> {
+  typedef f32x8 V8;
+  typedef f32x4 V4;
+  static __device__ __forceinline__ f32x4 mul(const V8& a, const V8& b, f32x4 c) {
+#pragma unroll
+    for (int j = 0; j < 8; j++) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], c, 0, 0, 0);
+    return c;
+  }
+};
 
 // Values that workgroups of one launch hand to each other (attention parts) are written and read at agent scope: the stores are
 // written through to where all dies see them, the loads bypass the die's own L2.
@@ -18,7 +39,7 @@ __device__ __forceinline__ void st_agent(float* p, float v) {
 }
 
 // ------------------------------------------------------------------------------------------
-// Cache layouts of the half-precision path: one 32-key block of a head = 32 HD halves (4 KiB for the 64-wide heads
+// Cache layouts: one 32-key block of a head = 32 HD values (4 KiB of halves for the 64-wide heads
 // of the benchmark configurations; HD = 96 and 128 are the paper's own model shapes)
 // ------------------------------------------------------------------------------------------
 // K: HD/16 A-fragments per block, fragment f = (key/16)*(HD/32) + dim/32, lane = key%16 + 16*((dim%32)/8)
@@ -38,23 +59,24 @@ __device__ __forceinline__ long vblk_off(int key, int dim) {
   return (long)(key >> 5) * (32 * HD) + dim * 32 + slot;
 }
 
-template <int HD>
-__global__ void k_mem_kv_store_h(const float* __restrict__ kv, f16_t* __restrict__ Kc, f16_t* __restrict__ Vc, int H,
+template <typename T, int HD>
+__global__ void k_mem_kv_store(const float* __restrict__ kv, T* __restrict__ Kc, T* __restrict__ Vc, int H,
                                  int M, int capb) {
   const int m = blockIdx.x;
   const int d = H * HD;
   for (int i = threadIdx.x; i < d; i += blockDim.x) {
     const int hh = i / HD, e = i % HD;
     const long base = (long)hh * capb * (32 * HD);
-    Kc[base + kblk_off<HD>(m, e)] = (f16_t)kv[(long)m * 2 * d + i];
-    Vc[base + vblk_off<HD>(m, e)] = (f16_t)kv[(long)m * 2 * d + d + i];
+    Kc[base + kblk_off<HD>(m, e)] = (T)kv[(long)m * 2 * d + i];
+    Vc[base + vblk_off<HD>(m, e)] = (T)kv[(long)m * 2 * d + d + i];
   }
 }
 
-// weights [N][K] fp32 (bf16-valued) -> half, tiled: fragment (nt, kt) holds W[nt*16 + l%16][kt*32 + (l/16)*8 + j]
+// weights [N][K] fp32 -> storage type (half: bf16-valued, exact), tiled: fragment (nt, kt) holds W[nt*16 + l%16][kt*32 + (l/16)*8 + j]
 // rope_rows > 0 (projections to queries and keys): rows below it belong to heads of width hd whose rotary pairs (i, i + hd/2)
 // must meet in one result tile: tile q of a head holds dims q*8..+8 and hd/2 + q*8..+8, i.e. both halves of 8 pairs.
-__global__ void k_tile_weight(const float* __restrict__ src, f16_t* __restrict__ dst, int N, int K, int Npad, int rope_rows, int hd) {
+template <typename T>
+__global__ void k_tile_weight(const float* __restrict__ src, T* __restrict__ dst, int N, int K, int Npad, int rope_rows, int hd) {
   const long total = (long)Npad * K / 8;
   for (long v = blockIdx.x * (long)blockDim.x + threadIdx.x; v < total; v += (long)gridDim.x * blockDim.x) {
     const int lane = (int)(v & 63);
@@ -67,9 +89,9 @@ __global__ void k_tile_weight(const float* __restrict__ src, f16_t* __restrict__
       const int hh = n / hd, qd = (n % hd) >> 4, c = n & 15;
       n = hh * hd + (c < 8 ? qd * 8 + c : hd / 2 + qd * 8 + (c - 8));
     }
-    f16x8 o;
+    typename Op<T>::V8 o;
 #pragma unroll
-    for (int j = 0; j < 8; j++) o[j] = n < N ? (f16_t)src[(long)n * K + k + j] : (f16_t)0.f;
-    *reinterpret_cast<f16x8*>(dst + v * 8) = o;
+    for (int j = 0; j < 8; j++) o[j] = n < N ? (T)src[(long)n * K + k + j] : (T)0.f;
+    *reinterpret_cast<typename Op<T>::V8*>(dst + v * 8) = o;
   }
 }

@@ -45,13 +45,13 @@ __device__ __forceinline__ int eff_block_len(const StateDev& st, const Dims& D, 
 
 // Rows of one verify pass, one workgroup per row (coordinate rows, then vertex, then face rows): position, last visible key of
 // the cross-attention, rotary table; every entry follows from the committed state alone.  emb != null: coordinate rows also get
-// their embedding as fp32 residual stream and, for the half path (xg != null), as input of the first projection.
+// their embedding as fp32 residual stream and as input of the first projection.
 template <typename T>
 __global__ __launch_bounds__(256) void k_verify_setup(StateDev st, Dims D, InvFreq inv, const int* __restrict__ block_tok,
                                                        const int* __restrict__ block_len, int* pos_c, int* pos_v, int* pos_f,
                                                        int* limx_c, int* limx_v, int* limx_f, float2* cs_c, float2* cs_v,
                                                        float2* cs_f, unsigned* epoch, const T* __restrict__ emb, float* __restrict__ h,
-                                                       f16_t* __restrict__ xg, const float* __restrict__ gain, float* __restrict__ ssq) {
+                                                       T* __restrict__ xg, const float* __restrict__ gain, float* __restrict__ ssq) {
   if (epoch && blockIdx.x == 0 && threadIdx.x == 0) *epoch += 1;     // pass counter of the single-launch verify kernel
   const int Rc = D.S * D.Bm, Rv = D.S * D.VB;
   const int level = (int)blockIdx.x < Rc ? 0 : (int)blockIdx.x < Rc + Rv ? 1 : 2;
@@ -84,8 +84,7 @@ __global__ __launch_bounds__(256) void k_verify_setup(StateDev st, Dims D, InvFr
       if (p >= 0)
 #pragma unroll
         for (int k = 0; k < 4; k++) v[k] = Store<T>::ld(e + n + k);
-      if (xg) put_row4(v, idx, n, D.d, h, xg, gain, ssq);
-      else *reinterpret_cast<f32x4*>(h + (long)idx * D.d + n) = v;
+      put_row4<T>(v, idx, n, D.d, h, xg, gain, ssq);
     }
   }
 }
