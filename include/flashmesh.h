@@ -150,7 +150,9 @@ int fm_correct(fm_ctx* ctx, int32_t* block_tok_dev, const int32_t* block_len_dev
  * replayed, corrected or written by the caller - counts as a proposal with all its mass on it), and the next main token
  * comes from max(p - q, 0) after the first rejection, from p after a fully accepted block.  The emitted stream is then
  * distributed like token-by-token sampling from the backbone.  Uniforms are counter based, keyed by (seed, sequence,
- * absolute position, purpose), so a run is reproducible.  temperature = 0 (the default) is greedy decoding. */
+ * absolute position, purpose), so a run is reproducible.  temperature = 0 (the default) is greedy decoding.
+ * The setting (and that of fm_set_draft_replay) takes effect in stream order; steps that the caller has recorded as a graph follow
+ * it when they are replayed: a verify pass recorded with T > 0 is greedy at 0, one recorded at 0 stays greedy. */
 int fm_set_sampling(fm_ctx* ctx, float temperature, uint64_t seed);
 
 /* Verify stage (Sec. 3.3): one causal backbone forward over each sequence's block at positions

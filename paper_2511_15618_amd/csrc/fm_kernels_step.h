@@ -520,7 +520,7 @@ __global__ __launch_bounds__(256) void k_sample_rows(StateDev st, Dims D, const 
   const int nlim = D.ban ? D.nbins : D.V;
   const float* x = logits + (long)row * D.V;
   const unsigned long long seed = sm.p->seed;
-  const float invT = 1.0f / sm.p->temperature;
+  const float invT = fminf(1.0f / sm.p->temperature, 3.0e38f);      // temperature 0 (set after the step was recorded): all mass on the maximum
   // max and sum of exp((x - max) / T)
   float mx = -INFINITY;
   for (int j = threadIdx.x; j < nlim; j += 256) mx = fmaxf(mx, x[j]);
