@@ -341,7 +341,7 @@ void run_block(fm_ctx* c, const Layer& L, int level, const float* next_gain, flo
   auto attn = [&](const int* limit, void* K, void* V, int kcap, int window, bool cross) {
     AttnArgs t{};
     int n = 0;
-    auto ahead = [&](const void* W, int N, int Kw) { if (W) t.next[n++] = WeightRange{W, Kw / 32 * 1024, N / 16}; };
+    auto ahead = [&](const void* W, int N, int Kw) { if (W) t.next[n++] = WeightRange{W, Kw * 16 * (int)sizeof(T), N / 16}; };
     if (cross) {
       ahead(L.co, d, d);
       if (cross_bytes <= 48e6) { ahead(L.w1, c->ff, d); ahead(L.w2, d, c->ff); ahead(next_qkv, 3 * d, d); }
