@@ -1,0 +1,139 @@
+"""The decode kernels (skinny GEMM, block attention, choice and merge) and the edge instance of the prefill kernel, at the sizes
+where their tilings and launch rules change, against the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+import synth_inputs as si
+
+pytestmark = pytest.mark.gpu
+
+# the bars of the lock-step tests (see parity_harness for how they carry over to probabilities)
+TOL = {"f32": 1e-4, "bf16": 2e-2}
+
+
+def _cfg(name, d, heads, mem, dtype, batch, faces, dc, m, n, bins=32, **kw):
+    return si.Config(name, d, heads, bins, 1, 1, 1, 1, 2, mem, dtype, batch, faces, dc, m, n, **kw)
+
+
+CASES = [
+    # more than seven row tiles (13 x 9 rows): the tall tile, with a last row tile of 5 rows; memory one row past a tile
+    _cfg("tall_rows", 192, 2, 257, "bf16", 13, 4, 2, 9, 9),
+    # hidden rows of more than 64 and more than 128 K fragments, few and many workgroups (24 sets of heads, two row tiles)
+    _cfg("long_k", 192, 3, 72, "bf16", 9, 6, 2, 9, 27, ffn_mult=12, hf_ffn_mult=12),
+    _cfg("longest_k", 192, 2, 40, "bf16", 9, 6, 2, 9, 27, ffn_mult=22, hf_ffn_mult=22),
+    # K between 32 and 64 fragments with many workgroups; a width that is no multiple of 128
+    _cfg("mid_k", 384, 6, 300, "bf16", 3, 6, 2, 9, 27),
+    _cfg("odd_width", 320, 5, 31, "bf16", 2, 4, 2, 9, 9, bins=45),
+    # several splits of the memory's keys with one and two query tiles, every head width (last block partly filled)
+    _cfg("splits_hd64", 128, 2, 1001, "bf16", 2, 6, 2, 9, 9),
+    _cfg("splits_hd64_two", 128, 2, 1001, "bf16", 2, 6, 2, 15, 18),
+    _cfg("splits_hd96", 192, 2, 700, "bf16", 2, 6, 2, 15, 18),
+    _cfg("splits_hd128", 256, 2, 289, "bf16", 2, 6, 2, 15, 18),
+    # more than 32 draft rows per sequence: two row sets of one attention launch
+    _cfg("two_sets", 128, 2, 40, "bf16", 2, 8, 2, 27, 27),
+    # fp32: tall tiles in the condition GEMM, K past one trip, splits, head widths
+    _cfg("f32_tall", 128, 2, 131, "f32", 2, 6, 2, 9, 9),
+    _cfg("f32_long_k", 320, 5, 33, "f32", 2, 4, 2, 9, 9, ffn_mult=5, hf_ffn_mult=5),
+    _cfg("f32_splits_hd96", 192, 2, 290, "f32", 2, 6, 2, 15, 18),
+    _cfg("f32_splits_hd128", 256, 2, 513, "f32", 1, 6, 2, 15, 18),
+    # vocabulary past the registers of the draft softmax (2048 entries)
+    _cfg("wide_vocab", 128, 2, 40, "bf16", 2, 4, 2, 9, 9, bins=2100),
+]
+
+
+@pytest.mark.parametrize("cfg", CASES, ids=lambda c: c.name)
+def test_lockstep_where_tilings_change(cfg):
+    from parity_harness import lockstep
+    print("case", cfg.name, flush=True)
+    rep, streams, fm = lockstep(cfg, cfg.faces, TOL[cfg.dtype], max_steps=12)
+    print(rep, flush=True)
+    assert rep.steps > 0 and fm.verify_path() == 0
+
+
+@pytest.mark.parametrize("name", ["t_f32_1815", "wide"])
+def test_sampled_choice_over_wide_rows(name):
+    """Draws from rows that are no whole number of waves, and past the registers of the draft softmax."""
+    from parity_harness import lockstep
+    cfg = CASES[-1].replace(name=name) if name == "wide" else si.TEST_CONFIGS[name].replace(n_bins=67)
+    print("case", name, flush=True)
+    rep, _, _ = lockstep(cfg, cfg.faces, TOL[cfg.dtype], max_steps=10, sampling=(0.8, 5))
+    print(rep, flush=True)
+
+
+@pytest.mark.parametrize("d,heads,mem", [(128, 2, 1), (128, 2, 33), (192, 2, 255), (320, 5, 257), (384, 3, 511), (640, 5, 769)])
+def test_condition_kv_at_tile_edges(d, heads, mem):
+    """Memories and widths that are no whole 256-row tiles, every element against float64.  The bound: the memory rounded to half
+    (2^-11 relative, the weights are exact), d products summed in fp32, one more rounding to half."""
+    from oracle.hourglass import Model
+    from paper_2511_15618_amd import FlashMesh
+    from paper_2511_15618_amd.binding import config_struct
+    cfg = _cfg("edges", d, heads, mem, "bf16", 2, 2, 2, 0, 0)
+    print("case", d, heads, mem, flush=True)
+    w = si.make_weights(cfg, 0)
+    model, fm = Model(cfg, w), FlashMesh(config_struct(cfg))
+    fm.load_weights(si.pack_blob(cfg, w))
+    mems = [si.make_memory(cfg, s) for s in range(2)]
+    for s in range(2):
+        fm.prefill_condition(s, torch.from_numpy(mems[s]).cuda())
+    blocks = [f"{st}.{i}." for st in si.STACKS for i in range(model.layers[st])]
+    for s in range(2):
+        for b, pfx in enumerate(blocks):
+            for ref, dev, wn in zip(model.mem_kv(pfx, mems[s]), fm.debug_mem_kv(s, b), ("ck", "cv")):
+                ref = ref.reshape(mem, d)
+                mag = np.abs(np.asarray(mems[s], np.float64)) @ np.abs(model.w[pfx + wn]).T
+                bound = 1.05 * ((2.0 ** -11 + (d + 2) * 2.0 ** -24) * mag + 2.0 ** -11 * np.abs(ref)) + 1e-30
+                assert (np.abs(dev - ref) <= bound).all(), (s, pfx, wn)
+
+
+@pytest.mark.parametrize("name", ["t_f32_99", "t_bf16_99"])
+def test_recorded_steps_follow_buffers_and_settings(name):
+    """Steps are replayed as recorded launches: more block buffers than a context keeps recordings for, settings that change
+    between steps and whole-mesh calls of several lengths give what the first, unrecorded pass over the same mesh gave."""
+    from paper_2511_15618_amd import FlashMesh
+    from paper_2511_15618_amd.binding import config_struct
+    cfg = si.TEST_CONFIGS[name]
+    fm = FlashMesh(config_struct(cfg))
+    fm.load_weights(si.pack_blob(cfg, si.make_weights(cfg, 0)))
+    mems = [torch.from_numpy(si.make_memory(cfg, s)).cuda() for s in range(cfg.batch)]
+
+    def begin():
+        for s, mem in enumerate(mems):
+            fm.prefill_condition(s, mem)
+
+    def mesh(faces):
+        begin()
+        tok, n, _ = fm.generate(faces, True)
+        return [tok[s, :int(n[s])].tolist() for s in range(cfg.batch)]
+
+    def stepped(faces, buffers):
+        begin()
+        fm.set_budget(faces)
+        acc = torch.zeros(cfg.batch, dtype=torch.int32, device="cuda")
+        out = [[] for _ in range(cfg.batch)]
+        for i in range(9 * faces):
+            tok, ln = buffers[i % len(buffers)]
+            fm.draft(tok, ln)
+            fm.verify_block(tok, ln, None, acc)
+            blocks, took = tok.tolist(), acc.tolist()
+            fm.commit(acc)
+            state = fm.read_state()
+            for s in range(cfg.batch):
+                if took[s]:
+                    out[s] += blocks[s][1:took[s]] + [int(state[s, 3])]
+            if state[:, 4].all():
+                break
+        return out
+
+    whole = mesh(cfg.faces)
+    assert [len(x) for x in whole] == [9 * cfg.faces] * cfg.batch
+    many = [fm.new_block() for _ in range(11)]
+    for buffers in (many[:1], many, many[:2]):
+        assert stepped(cfg.faces, buffers) == whole
+    for faces in (1, 2, cfg.faces):
+        assert mesh(faces) == [x[:9 * faces] for x in whole]
+    fm.set_sampling(0.9, 4)
+    drawn = mesh(cfg.faces)
+    assert stepped(cfg.faces, many[:2]) == drawn and drawn != whole
+    fm.set_sampling(0.0, 0)
+    assert mesh(cfg.faces) == whole and stepped(cfg.faces, many[:2]) == whole
