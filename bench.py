@@ -258,7 +258,7 @@ def main():
         for e in sweep:
             e["frac_of_mfma_peak"] = e["TFLOPs"] / MFMA_PEAK_TFLOPS
             e["weight_GBs"] = 2.0 * cfg.d_model * cfg.ffn_mult * cfg.d_model / (e["ms"] * 1e-3) / 1e9
-        print(json.dumps({"gemm_sweep": f"Y[rows, {cfg.ffn_mult * cfg.d_model}] = gelu(X[rows, {cfg.d_model}] W^T), k_gemm_mfma", "rows": sweep}))
+        print(json.dumps({"gemm_sweep": f"Y[rows, {cfg.ffn_mult * cfg.d_model}] = gelu(X[rows, {cfg.d_model}] W^T), k_dec_gemm", "rows": sweep}))
         return
     mems = [si.make_memory(cfg, s) for s in range(cfg.batch)]
     mems_dev = [torch.from_numpy(m).cuda() for m in mems]

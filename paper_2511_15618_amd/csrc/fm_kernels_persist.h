@@ -444,7 +444,7 @@ __device__ __forceinline__ void pk_epi_qkv(const PkArgs& a, const PkLayer& L, co
 }
 
 // ------------------------------------------------------------------------------------------
-// Attention over one key range of one head (flash-decoding split), same arithmetic as k_attn_mfma<QT>: QT tiles of
+// Attention over one key range of one head (flash-decoding split), same arithmetic as k_dec_attn: QT tiles of
 // 16 query rows share every K/V block that is loaded.  Keys of this pass (positions >= P0) are taken from the
 // exchange buffers, older keys from the cache.  lim[t]: last key the lane's row of tile t may see (-1: unused slot).
 // Partial results: tile t of (head, split) at part + t * PK_PART.
