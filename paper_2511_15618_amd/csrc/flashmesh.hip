@@ -772,17 +772,23 @@ int build_persist(fm_ctx* c) {
   a.D = D; a.ff = c->ff; a.eps = c->cfg.rms_eps;
   a.R[0] = D.Bm; a.R[1] = D.VB; a.R[2] = D.FB;
   const int caps[3] = {D.capc, D.capv, D.capf};
+  // splits of a head's keys: about one attention unit per workgroup, no more than there are groups of four blocks (one per wave),
+  // as few as give the same longest walk, and no more parts than a merge takes in one trip to memory (16).  Steps in us, d = 1024 (16
+  // heads) and d = 512 (8 heads): 16 splits 1966 / 836, 12 1972 / 859, 8 2022 / 871, 4 2238 / 919; 32 splits at d = 512, in two trips: 849
+  auto splits = [&](int capb) {
+    int ns = std::max(1, std::min(PK_NWG / D.H, PK_MAXSPLIT));
+    if (const char* e = getenv("FM_PK_NSPLIT")) ns = std::max(1, std::min(atoi(e), PK_MAXSPLIT));       // measurement switch: splits per head
+    const int groups = (capb + 3) / 4, rounds = (groups + ns - 1) / ns;
+    return (groups + rounds - 1) / rounds;
+  };
   for (int l = 0; l < 3; l++) {
     a.capb[l] = (caps[l] + 31) / 32;
-    int ns = PK_NWG / D.H;                       // about one attention unit per workgroup
-    if (const char* e = getenv("FM_PK_NSPLIT")) ns = std::max(1, atoi(e));       // measurement switch: key ranges per head
-    ns = std::min(ns, std::max(1, a.capb[l] / 2));
-    a.nsplit[l] = std::max(1, std::min(ns, PK_MAXSPLIT));
+    a.nsplit[l] = splits(a.capb[l]);
     a.pos[l] = c->pos[l]; a.limx[l] = c->limx[l]; a.cs[l] = c->cs[l];
     a.win[l] = level_window(c, l);
   }
   a.capbM = (D.M + 31) / 32;
-  a.nsplitM = std::max(1, std::min(std::min(PK_NWG / D.H, std::max(1, a.capbM / 2)), PK_MAXSPLIT));
+  a.nsplitM = splits(a.capbM);
   a.vtok = c->st.vtok;
   a.ring_hc = c->ring_hc; a.ring_hv = c->ring_hv; a.ring_yf = c->ring_yf; a.ring_yv = c->ring_yv;
   a.tap[0] = c->tap_c; a.tap[1] = c->tap_v; a.tap[2] = c->tap_f;

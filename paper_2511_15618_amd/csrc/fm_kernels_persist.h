@@ -27,7 +27,7 @@
 typedef unsigned long long u64;
 
 #define PK_NWG 256
-#define PK_MAXSPLIT 64
+#define PK_MAXSPLIT 16                    // parts that a merge unit takes in one round of loads
 #define PK_PART (16 * 64 + 32)            // per (head, split): 16x64 unnormalised O, 16 running maxima, 16 sums
 #define PK_TIMEOUT_TICKS 20000000ull      // default bound of every wait: 200 ms of the 100 MHz wall clock
 
@@ -443,9 +443,13 @@ __device__ __forceinline__ void pk_epi_qkv(const PkArgs& a, const PkLayer& L, co
   }
 }
 
+__device__ __forceinline__ int pk_active(int nblk, int ns) { return max(1, min(ns, (nblk + 3) >> 2)); }      // splits that hold visible keys
+
 // ------------------------------------------------------------------------------------------
-// Attention over one key range of one head (flash-decoding split), same arithmetic as k_dec_attn: QT tiles of
-// 16 query rows share every K/V block that is loaded.  Keys of this pass (positions >= P0) are taken from the
+// Attention over one split of the keys of one head (flash-decoding), same arithmetic and deal as k_dec_attn: block b of 32 keys
+// belongs to wave b % 4 of split (b / 4) % ns, which is balanced at every length and does not depend on it.  QT tiles of
+// 16 query rows share every K/V block that is loaded.  The first K/V block of a wave is requested before the wait for
+// the queries, the next one behind it.  Keys of this pass (positions >= P0) are taken from the
 // exchange buffers, older keys from the cache.  lim[t]: last key the lane's row of tile t may see (-1: unused slot).
 // Partial results: tile t of (head, split) at part + t * PK_PART.
 // ------------------------------------------------------------------------------------------
@@ -460,6 +464,7 @@ __device__ __forceinline__ bool pk_attn_unit(const PkArgs& a, SH& sh, const u64*
   // With a window the cache is a ring of capb blocks (a multiple of four): position p lives in slot p mod (32 capb);
   // seen from the newest visible position, slot j holds lapbase + j if that is <= maxlim, else the position one
   // lap earlier.  Without a window lapbase = 0 and nothing wraps.
+  maxlim = __builtin_amdgcn_readfirstlane(maxlim);
   const int nblk = min((maxlim + 32) >> 5, capb);
   const int ringn = capb * 32;
   const int lapbase = max(maxlim, 0) / ringn * ringn;
@@ -471,35 +476,35 @@ __device__ __forceinline__ bool pk_attn_unit(const PkArgs& a, SH& sh, const u64*
     on[t] = t * 16 + ql < R;
     first[t] = window > 0 ? max(lim[t] - window + 1, 0) : 0;
   }
-  const int per = (capb + nsplit_cfg - 1) / nsplit_cfg;
-  const int nsplit = max(1, (nblk + per - 1) / per);
-  if (split >= nsplit) return true;      // nothing visible in this range: the merge knows the same count
-  const int b0 = split * per, b1 = min(b0 + per, nblk);
+  if (split >= pk_active(nblk, nsplit_cfg)) return true;      // nothing visible in this split: the merge knows the same count
+  const int b0 = split * 4 + wave, step = nsplit_cfg * 4;     // this wave's blocks: b0, b0 + step, ...
 
   // The wave's query fragments and, if one of its blocks holds rows written by this pass, those rows, in ONE
   // batch.  K fragment f = (hb, dh) holds key b*32 + hb*16 + lane%16, dims dh*32 + g*8..+8 (4 elements);
   // V fragment dt holds dim dt*16 + lane%16 and the 8 slots g*8 + j <-> key b*32 + (j/4)*16 + g*4 + j%4.
   int bov = -1;
   if (overlay) {
-    const int cand[2] = {(P0 % ringn) >> 5, ((P0 + R - 1) % ringn) >> 5};     // slot blocks of the rows of this pass
+    // slot blocks of the rows of this pass: neighbours (also around a ring, whose blocks are a multiple of four), so in different waves;
+    // rows past the end of a cache that is no ring do not exist
+    const int end = window > 0 ? (P0 + R - 1) % ringn : min(P0 + R - 1, ringn - 1);
+    const int cand[2] = {(P0 % ringn) >> 5, end >> 5};
 #pragma unroll
     for (int k = 0; k < 2; k++) {
       const int b = cand[k];
-      if (b >= b0 + wave && b < b1 && ((b - b0 - wave) & 3) == 0) bov = b;
+      if (b < nblk && (b & 3) == wave && (b >> 2) % nsplit_cfg == split) bov = b;
     }
+    bov = __builtin_amdgcn_readfirstlane(bov);
   }
-  // the first K/V block of this wave depends on nothing from this pass: request it before waiting for q
-  pk_cw_t Kb = Kc + (long)hh * capb * 2048;
-  pk_cw_t Vb = Vc + (long)hh * capb * 2048;
-  f16x8 kf[4], vf[4];
-  if (b0 + wave < b1) {
-    pk_cw_t kp = Kb + (long)(b0 + wave) * 2048 + lane * 8;
-    pk_cw_t vp = Vb + (long)(b0 + wave) * 2048 + (lane & 15) * 32 + g * 8;
+  pk_cw_t Kb = Kc + (long)hh * capb * 2048 + lane * 8;
+  pk_cw_t Vb = Vc + (long)hh * capb * 2048 + (lane & 15) * 32 + g * 8;
+  f16x8 ka[2][4], va[2][4];
+  auto load = [&](f16x8 (&kf)[4], f16x8 (&vf)[4], int b) {
 #pragma unroll
-    for (int f = 0; f < 4; f++) kf[f] = *(const PK_GLOBAL f16x8*)(kp + f * 512);
+    for (int f = 0; f < 4; f++) kf[f] = *(const PK_GLOBAL f16x8*)(Kb + (long)b * 2048 + f * 512);
 #pragma unroll
-    for (int dt = 0; dt < 4; dt++) vf[dt] = *(const PK_GLOBAL f16x8*)(vp + dt * 512);
-  }
+    for (int dt = 0; dt < 4; dt++) vf[dt] = *(const PK_GLOBAL f16x8*)(Vb + (long)b * 2048 + dt * 512);
+  };
+  if (b0 < nblk) load(ka[0], va[0], b0);
   // q of this lane: dims g*8..+8 and 32 + g*8..+8 of the head = two runs of four tagged elements = four 16-byte
   // agent-scope loads per query tile, simply repeated until every tag matches (small enough to poll with the data itself)
   typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
@@ -567,17 +572,7 @@ __device__ __forceinline__ bool pk_attn_unit(const PkArgs& a, SH& sh, const u64*
 #pragma unroll
     for (int dt = 0; dt < 4; dt++) o[t][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  for (int b = b0 + wave; b < b1; b += 4) {
-    // the next block of this wave is requested before the current one is multiplied
-    f16x8 kn[4], vn[4];
-    if (b + 4 < b1) {
-      pk_cw_t kp = Kb + (long)(b + 4) * 2048 + lane * 8;
-      pk_cw_t vp = Vb + (long)(b + 4) * 2048 + (lane & 15) * 32 + g * 8;
-#pragma unroll
-      for (int f = 0; f < 4; f++) kn[f] = *(const PK_GLOBAL f16x8*)(kp + f * 512);
-#pragma unroll
-      for (int dt = 0; dt < 4; dt++) vn[dt] = *(const PK_GLOBAL f16x8*)(vp + dt * 512);
-    }
+  auto attend = [&](f16x8 (&kf)[4], f16x8 (&vf)[4], int b) {
     if (b == bov) {
 #pragma unroll
       for (int f = 0; f < 4; f++) {
@@ -641,9 +636,13 @@ __device__ __forceinline__ bool pk_attn_unit(const PkArgs& a, SH& sh, const u64*
         o[t][dt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vf[dt], pf, o[t][dt], 0, 0, 0);
       }
     }
-    if (b + 4 < b1) {
-#pragma unroll
-      for (int f = 0; f < 4; f++) { kf[f] = kn[f]; vf[f] = vn[f]; }
+  };
+  for (int b = b0; b < nblk; b += 2 * step) {
+    if (b + step < nblk) load(ka[1], va[1], b + step);
+    attend(ka[0], va[0], b);
+    if (b + step < nblk) {
+      if (b + 2 * step < nblk) load(ka[0], va[0], b + 2 * step);
+      attend(ka[1], va[1], b + step);
     }
   }
 #pragma unroll
@@ -680,52 +679,63 @@ __device__ __forceinline__ bool pk_attn_unit(const PkArgs& a, SH& sh, const u64*
   return true;
 }
 
-// merge of the splits of one head (one quarter of its dims per unit) into the half-pair attention output;
-// thread = (row, dim), splits summed in a fixed order
+// Merge of the splits of one head (one quarter of its dims per unit) into the half-pair attention output: wave w takes the rows
+// w, w + 4, ..., a lane one dim and the splits g, g + 4, ... (g = lane / 16), all parts in one trip (PK_MAXSPLIT); no wave waits for another
+// (parts that meet in LDS behind a barrier instead: fewer loads, but 0.9 us longer).  Lanes and groups are added in a fixed order.
 // (rg: the row group, R: its rows; the split count comes from the largest limit of the whole level, as in the units
 // that wrote the partial results)
 template <int QT>
 __device__ __forceinline__ bool pk_merge_unit(const PkArgs& a, int maxlim, int R, int rg, int capb, int nsplit_cfg,
                                               int hh, int dq, const u64* parts, u64* att, unsigned tag, int stage) {
   const int d = a.D.d;
-  const int nblk = min((maxlim + 32) >> 5, capb);
-  const int per = (capb + nsplit_cfg - 1) / nsplit_cfg;
-  const int nsplit = max(1, (nblk + per - 1) / per);
+  const int nsplit = __builtin_amdgcn_readfirstlane(pk_active(min((maxlim + 32) >> 5, capb), nsplit_cfg));
   const long rec = (long)QT * PK_PART;                 // one (head, split) record: a tile per row group
   const u64* base = parts + (long)hh * PK_MAXSPLIT * rec + (long)rg * PK_PART;
-  const int qi = threadIdx.x >> 4, dim = dq * 16 + (threadIdx.x & 15);
-  const bool on = qi < R;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int g = lane >> 4, dim = dq * 16 + (lane & 15);
+  const int need = (nsplit + 3) >> 2;                  // splits of a lane
+  // element i: (k-th split of the lane, j-th row of the wave, word); what does not exist reads a neighbour and is not used
+  auto part = [&](int k, int j, int w) {
+    const int row = min(wave + 4 * j, R - 1);
+    const u64* p = base + (long)min(g + 4 * k, nsplit - 1) * rec;
+    return p + (w == 0 ? 16 * 64 + row : w == 1 ? 16 * 64 + 16 + row : row * 64 + dim);
+  };
+  auto merge = [&](int j, auto raw) {                  // raw(k, w): words of row wave + 4 j
+    float M = -INFINITY, num = 0.f, den = 0.f;
+#pragma unroll
+    for (int k = 0; k < 4; k++) if (g + 4 * k < nsplit) M = fmaxf(M, __uint_as_float(raw(k, 0)));
+    M = fmaxf(M, __shfl_xor(M, 16, 64));
+    M = fmaxf(M, __shfl_xor(M, 32, 64));
+    const float Ms = M == -INFINITY ? 0.f : M;
+#pragma unroll
+    for (int k = 0; k < 4; k++)
+      if (g + 4 * k < nsplit) {
+        const float f = __builtin_amdgcn_exp2f(__uint_as_float(raw(k, 0)) - Ms);
+        den += __uint_as_float(raw(k, 1)) * f;
+        num += __uint_as_float(raw(k, 2)) * f;
+      }
+    den += __shfl_xor(den, 16, 64); num += __shfl_xor(num, 16, 64);
+    den += __shfl_xor(den, 32, 64); num += __shfl_xor(num, 32, 64);
+    const float v = den > 0.f ? num / den : 0.f;
+    const float o = __shfl_xor(v, 1, 64);
+    if (lane < 16 && (lane & 1) == 0 && wave + 4 * j < R)
+      pk_st(att + (long)(rg * 16 + wave + 4 * j) * (d >> 1) + ((hh * 64 + dim) >> 1), pk_pack(v, o), tag);
+  };
   bool ok = true;
-  // splits are folded in a fixed order, 16 at a time, with the usual running-maximum rescale
-  float M = -INFINITY, num = 0.f, den = 0.f;
-  for (int k0 = 0; k0 < nsplit; k0 += 16) {
-    unsigned raw[48];
-    const int n = min(16, nsplit - k0);
-    ok = pk_fetch<48>(raw, 3 * n, on, tag, [&](int i) {
-      const u64* p = base + (long)(k0 + i / 3) * rec;
-      const int w = i % 3;
-      return w == 0 ? p + 16 * 64 + qi : w == 1 ? p + 16 * 64 + 16 + qi : p + qi * 64 + dim;
-    }, a, stage) && ok;
-    float Mc = M;
+  if (wave < R) {
+    if (R <= 4) {
+      unsigned raw[12];
+      ok = pk_fetch<12>(raw, 3 * need, true, tag, [&](int i) { return part(i / 3, 0, i % 3); }, a, stage);
+      if (ok) merge(0, [&](int k, int w) { return raw[3 * k + w]; });
+    } else {
+      unsigned raw[48];
+      ok = pk_fetch<48>(raw, 12 * need, true, tag, [&](int i) { return part(i / 12, i / 3 % 4, i % 3); }, a, stage);
+      if (ok) {
 #pragma unroll
-    for (int i = 0; i < 16; i++) if (i < n && on) Mc = fmaxf(Mc, __uint_as_float(raw[3 * i]));
-    const float Ms = Mc == -INFINITY ? 0.f : Mc;
-    const float scale = __builtin_amdgcn_exp2f(M - Ms);     // exp2(-inf) = 0 for the first chunk
-    num *= scale;
-    den *= scale;
-    M = Mc;
-#pragma unroll
-    for (int i = 0; i < 16; i++) {
-      if (i < n && on) {
-        const float f = __builtin_amdgcn_exp2f(__uint_as_float(raw[3 * i]) - Ms);
-        den += __uint_as_float(raw[3 * i + 1]) * f;
-        num += __uint_as_float(raw[3 * i + 2]) * f;
+        for (int j = 0; j < 4; j++) merge(j, [&](int k, int w) { return raw[12 * k + 3 * j + w]; });
       }
     }
   }
-  const float v = den > 0.f ? num / den : 0.f;
-  const float w = __shfl_xor(v, 1, 64);
-  if (on && (dim & 1) == 0) pk_st(att + (long)(rg * 16 + qi) * (d >> 1) + ((hh * 64 + dim) >> 1), pk_pack(v, w), tag);
   if (__syncthreads_or(!ok)) return false;
   return true;
 }
@@ -835,8 +845,7 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
         const int ns = a.nsplit[lev];
         const int P0 = firstP[lev];
         PK_MINE(H * ns) {
-          // range-major: the ranges that hold keys come first, so that with more ranges than a workgroup can take at once
-          // the non-empty ones still spread over all workgroups
+          // split-major: the splits that hold keys come first and spread over all workgroups
           const int hh = u % H, sp = u / H;
           if (!pk_attn_unit<QT>(a, sh, a.q, limS[lev], maxS[lev], R, L.Kc, L.Vc, capb, ns, hh, sp, true, P0,
                                 a.partS + ((long)hh * PK_MAXSPLIT + sp) * (RS >> 4) * PK_PART, tag, stage, a.win[lev])) return;

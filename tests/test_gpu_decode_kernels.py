@@ -1,4 +1,4 @@
-"""The decode kernels (skinny GEMM, block attention, choice and merge) and the edge instance of the prefill kernel, at the sizes
+"""The decode kernels (skinny GEMM, block attention, choice and merge, attention of the single-launch kernel) and the edge instance of the prefill kernel, at the sizes
 where their tilings and launch rules change, against the CPU oracle."""
 import numpy as np
 import pytest
@@ -30,6 +30,9 @@ CASES = [
     _cfg("splits_hd64_two", 128, 2, 1001, "bf16", 2, 6, 2, 15, 18),
     _cfg("splits_hd96", 192, 2, 700, "bf16", 2, 6, 2, 15, 18),
     _cfg("splits_hd128", 256, 2, 289, "bf16", 2, 6, 2, 15, 18),
+    # the single-launch kernel: one split per group of four key blocks, the last group partly filled; two query tiles
+    _cfg("one_launch_splits", 128, 2, 1001, "bf16", 1, 6, 2, 9, 9),
+    _cfg("one_launch_two_tiles", 256, 4, 545, "bf16", 1, 6, 2, 15, 18),
     # more than 32 draft rows per sequence: two row sets of one attention launch
     _cfg("two_sets", 128, 2, 40, "bf16", 2, 8, 2, 27, 27),
     # fp32: tall tiles in the condition GEMM, K past one trip, splits, head widths
@@ -48,7 +51,7 @@ def test_lockstep_where_tilings_change(cfg):
     print("case", cfg.name, flush=True)
     rep, streams, fm = lockstep(cfg, cfg.faces, TOL[cfg.dtype], max_steps=12)
     print(rep, flush=True)
-    assert rep.steps > 0 and fm.verify_path() == 0
+    assert rep.steps > 0 and fm.verify_path() == (cfg.name.startswith("one_launch"))
 
 
 @pytest.mark.parametrize("name", ["t_f32_1815", "wide"])
