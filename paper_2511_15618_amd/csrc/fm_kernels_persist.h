@@ -84,7 +84,7 @@ struct PkArgs {
   u64* w2part;              // [d/16][RS/16][3][256]: partial tiles of the K-quarters 1..3 of the FFN down projection
   const unsigned* epoch_word;  // passes so far, counted by k_verify_setup
   u64 timeout_ticks;        // bound of every wait (100 MHz wall clock)
-  int two_phase;            // waits first watch one element per lane and only then read everything (0: the full read is the poll)
+  int two_phase;            // GEMM waits first watch one element per lane and only then read everything (0: the full read comes first)
   unsigned test_skew;       // test hook: added to the tag the embedding publishes, so that nothing downstream ever arrives
   unsigned* abort_word;     // [0] abort flag, [1] earliest stage that gave up, [2] claim, [3..8] expected tag, tag seen,
                             // stage, workgroup, thread, element of the first missing value
@@ -125,24 +125,12 @@ __device__ __forceinline__ bool pk_expired(const PkArgs& a, u64 t0, int stage) {
 }
 
 // Wave-wide fetch of N tagged elements per lane (addresses from `addr(i)`, i < n <= N); inactive lanes get 0.
-// All loads are issued before any is checked; the whole set is re-read until every tag matches.
+// All loads are issued before any is checked; the whole set is re-read until every tag matches.  (Watching one element first costs a
+// second trip once it is there: 40 us of a step at d = 1024.  The abort word is another trip, so it is looked at every 64 rounds only.)
 template <int N, class F>
 __device__ __forceinline__ bool pk_fetch(unsigned (&out)[N], int n, bool active, unsigned tag, F addr, const PkArgs& a, int stage) {
   const u64 t0 = wall_clock64();
   int it = 0;
-  // (a.two_phase: watch one element per lane first; otherwise the full read comes first and the watching only starts
-  // after a read that came back incomplete)
-  auto watch = [&]() -> bool {
-    while (true) {
-      bool ok = true;
-      if (active && n > 0) ok = (unsigned)(pk_ld(addr(0)) >> 32) == tag;
-      if (__all(ok)) return true;
-      if ((++it & 7) == 0 && pk_expired(a, t0, stage)) return false;
-      __builtin_amdgcn_s_sleep(4);
-    }
-  };
-  if (N > 1 && a.two_phase && !watch()) return false;
-  // phase 2: read everything, again until complete
   while (true) {
     // all loads are issued back to back (the compiler keeps agent-scope loads in program order and would
     // otherwise wait for each one before the next), only then are the tags looked at
@@ -159,7 +147,7 @@ __device__ __forceinline__ bool pk_fetch(unsigned (&out)[N], int n, bool active,
       if (active && i < n) ok = ok && ((unsigned)(v[i] >> 32) == tag);
     }
     if (__all(ok)) return true;
-    if ((++it & 3) == 0 && pk_expired(a, t0, stage)) {
+    if ((++it & 63) == 0 && pk_expired(a, t0, stage)) {
       // diagnostics of the first element found missing: expected tag, tag seen, stage, workgroup, thread
       if (!ok && atomicCAS(a.abort_word + 2, 0u, 1u) == 0u) {
         unsigned seen = 0, idx = 0;
@@ -170,8 +158,7 @@ __device__ __forceinline__ bool pk_fetch(unsigned (&out)[N], int n, bool active,
       }
       return false;
     }
-    if (N > 1) { if (!watch()) return false; }
-    else __builtin_amdgcn_s_sleep(2);
+    __builtin_amdgcn_s_sleep(1);
   }
 }
 
@@ -242,7 +229,8 @@ __device__ __forceinline__ bool pk_gemm_tile(const PkArgs& a, SH& sh, pk_cw_t Wt
   // The full fragment read is its own validity check, so a unit whose input is already there pays one round trip.
   // When a read comes back incomplete the wave falls back to watching one element per lane (lane l: fragment l/8, its
   // first or second half - a producer tile owns half a fragment row - in one of the last four rows) and reads the
-  // fragments again once those show the tag: waiting costs the memory system 64 small loads per round, not 32 KiB.
+  // fragments again once those show the tag: waiting costs the memory system 64 small loads per round, not 32 KiB (reading all
+  // again instead, steps in us: d = 1024 1893 -> 1905, d = 512 800 -> 810; for up to four rows only: 1904, 805).
   const int fs_ = min(lane >> 3, FW - 1), hs_ = (lane >> 2) & 1, rs_ = max(R - 1 - (lane & 3), 0);
 #define PK_WATCH(AW)                                                                                          \
   {                                                                                                           \
@@ -250,8 +238,8 @@ __device__ __forceinline__ bool pk_gemm_tile(const PkArgs& a, SH& sh, pk_cw_t Wt
     while (good) {                                                                                            \
       const bool okw = (unsigned)(pk_ld(sent) >> 32) == tagA;                                                 \
       if (__all(okw)) break;                                                                                  \
-      if ((++it & 7) == 0 && pk_expired(a, t0, stage)) { good = false; break; }                               \
-      __builtin_amdgcn_s_sleep(4);                                                                            \
+      if ((++it & 63) == 0 && pk_expired(a, t0, stage)) { good = false; break; }                               \
+      __builtin_amdgcn_s_sleep(1);                                                                            \
     }                                                                                                         \
   }
   if (a.two_phase) PK_WATCH(Aw)
@@ -277,7 +265,7 @@ __device__ __forceinline__ bool pk_gemm_tile(const PkArgs& a, SH& sh, pk_cw_t Wt
       ok = ok && v[i][1] == tagA && v[i][3] == tagA;      /* unused slots were preset to the tag */           \
     }                                                                                                         \
     if (__all(ok)) break;                                                                                     \
-    if ((++it & 3) == 0 && pk_expired(a, t0, stage)) { good = false; break; }                                 \
+    if ((++it & 63) == 0 && pk_expired(a, t0, stage)) { good = false; break; }                                 \
     PK_WATCH(AW)                                                                                              \
   }
   PK_FETCH_FRAGS(mine, Aw)
@@ -535,7 +523,7 @@ __device__ __forceinline__ bool pk_attn_unit(const PkArgs& a, SH& sh, const u64*
           okq = okq && qv[t][j][1] == tag && qv[t][j][3] == tag;
         }
       if (__all(okq)) break;
-      if ((++it & 7) == 0 && pk_expired(a, t0, stage)) { ok = false; break; }
+      if ((++it & 63) == 0 && pk_expired(a, t0, stage)) { ok = false; break; }
     }
 #pragma unroll
     for (int t = 0; t < QT; t++) {
