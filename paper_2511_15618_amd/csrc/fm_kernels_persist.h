@@ -18,7 +18,7 @@
 // polls, so all workgroups leave and the host reports an error instead of hanging.
 //
 // Arithmetic is kept batch-invariant exactly like the per-launch kernels: fixed 32-key blocks, fixed
-// split ranges, fixed merge order, rows never mixed in a GEMM.
+// deal of the blocks to the splits, fixed merge order, rows never mixed in a GEMM.
 #pragma once
 #include "fm_device.h"
 #include "fm_kernels_mfma.h"
