@@ -584,16 +584,20 @@ int put_params(fm_ctx* c) {
 }
 
 // staging bytes a prefill call needs: the memory in operand order (whole 32-row blocks) and, where the tiled GEMM does not run
-// (fp32, models narrower than it takes), the fp32 K/V rows of one block behind it
+// (fp32, models narrower than it takes), the fp32 K/V rows of one block behind it.  There the two are taken for unpadded
+// rows: an area that the padding does not fit takes the keys and the values of a block one after the other (prefill_impl).
 size_t prefill_stage_bytes(const fm_ctx* c) {
   const size_t M = c->D.M, d = c->D.d, M32 = (M + 31) / 32 * 32;
-  return M32 * d * c->esz + (c->pf_layers ? 0 : M * 2 * d * sizeof(float));
+  return c->pf_layers ? M32 * d * c->esz : M * d * (c->esz + 2 * sizeof(float));
 }
 
 template <typename T>
-int prefill_impl(fm_ctx* c, int seq, const float* mem_dev, void* stage_area) {
+int prefill_impl(fm_ctx* c, int seq, const float* mem_dev, void* stage_area, size_t stage_bytes) {
   const Dims& D = c->D;
   const int d = D.d, M32 = (D.M + 31) / 32 * 32;
+  const size_t tiled = (size_t)M32 * d * sizeof(T), rows = (size_t)D.M * d * sizeof(float);      // memory in operand order; keys or values of one block
+  const int parts = tiled + 2 * rows <= stage_bytes ? 1 : 2;       // keys and values of a block together, or in turn
+  if (tiled + (c->pf_layers ? 0 : 2 / parts * rows) > stage_bytes) return fail(c, FM_EINVAL, "condition memory of %d x %d does not fit its staging area", D.M, d);
   // memory -> MFMA fragment order (the same tiling as a weight matrix, zero rows up to whole key blocks)
   T* Xt = (T*)stage_area;
   hipLaunchKernelGGL((k_tile_weight<T>), dim3(std::min(2048, (M32 * (d / 8) + 255) / 256)), dim3(256), 0, c->stream, mem_dev, Xt, D.M, d, M32, 0, D.hd);
@@ -613,15 +617,17 @@ int prefill_impl(fm_ctx* c, int seq, const float* mem_dev, void* stage_area) {
   } else {
     float* kv = (float*)(Xt + (size_t)M32 * d);
     for (int st = 0; st < 5; st++)
-      for (auto& L : c->stacks[st]) {
-        DecGemm a{};
-        a.A = Xt; a.W = L.ckv; a.M = D.M; a.N = 2 * d; a.KT = d / 32; a.Y = kv; a.ldy = 2 * d;
-        dec_gemm<T, DE_F32, false>(a, 1, c->stream);
-#define FM_MEMKVH(HDV) hipLaunchKernelGGL((k_mem_kv_store<T, HDV>), dim3(D.M), dim3(256), 0, c->stream, kv, (T*)L.Km + seq_off, (T*)L.Vm + seq_off, D.H, D.M, \
-                                          (D.M + 31) / 32)
-        if (D.hd == 64) FM_MEMKVH(64); else if (D.hd == 96) FM_MEMKVH(96); else FM_MEMKVH(128);
+      for (auto& L : c->stacks[st])
+        for (int part = 0; part < parts; part++) {
+          DecGemm a{};
+          a.A = Xt; a.W = (const T*)L.ckv + (size_t)part * d * d; a.M = D.M; a.N = 2 * d / parts; a.KT = d / 32; a.Y = kv; a.ldy = a.N;
+          dec_gemm<T, DE_F32, false>(a, 1, c->stream);
+          const float *k = part == 0 ? kv : nullptr, *v = parts == 1 ? kv + d : part == 1 ? kv : nullptr;
+#define FM_MEMKVH(HDV) hipLaunchKernelGGL((k_mem_kv_store<T, HDV>), dim3(D.M), dim3(256), 0, c->stream, k, v, a.N, (T*)L.Km + seq_off, (T*)L.Vm + seq_off, \
+                                          D.H, D.M, (D.M + 31) / 32)
+          if (D.hd == 64) FM_MEMKVH(64); else if (D.hd == 96) FM_MEMKVH(96); else FM_MEMKVH(128);
 #undef FM_MEMKVH
-      }
+        }
   }
   hipLaunchKernelGGL(k_reset_seq, dim3(1), dim3(64), 0, c->stream, c->st, D, seq, D.nbins);
   HIPCHK(c, hipGetLastError());
@@ -1113,7 +1119,8 @@ int fm_prefill_condition(fm_ctx* c, int32_t seq, const float* mem_dev) {
   if (!c->weights_loaded) return fail(c, FM_ESTATE, "weights not loaded");
   if (seq < 0 || seq >= c->D.S) return fail(c, FM_EINVAL, "sequence %d out of range [0,%d)", seq, c->D.S);
   if (!mem_dev) return fail(c, FM_EINVAL, "null condition memory");
-  int rc = c->bf16 ? prefill_impl<f16_t>(c, seq, mem_dev, c->stage) : prefill_impl<float>(c, seq, mem_dev, c->stage);
+  const size_t room = c->stage_elems * sizeof(float);
+  int rc = c->bf16 ? prefill_impl<f16_t>(c, seq, mem_dev, c->stage, room) : prefill_impl<float>(c, seq, mem_dev, c->stage, room);
   if (rc == FM_OK) c->prefilled[seq] = true;
   return rc;
 }
@@ -1128,7 +1135,8 @@ int fm_prefill_condition_static(fm_ctx* c, int32_t seq, const float* mem_dev) {
   if (need > FM_STATIC_SCRATCH_BYTES)
     return fail(c, FM_EINVAL, "condition memory of %d x %d needs %zu staging bytes, the static area holds %u: use fm_prefill_condition",
                 c->D.M, c->D.d, need, (unsigned)FM_STATIC_SCRATCH_BYTES);
-  int rc = c->bf16 ? prefill_impl<f16_t>(c, seq, mem_dev, c->static_scratch) : prefill_impl<float>(c, seq, mem_dev, c->static_scratch);
+  int rc = c->bf16 ? prefill_impl<f16_t>(c, seq, mem_dev, c->static_scratch, FM_STATIC_SCRATCH_BYTES)
+                   : prefill_impl<float>(c, seq, mem_dev, c->static_scratch, FM_STATIC_SCRATCH_BYTES);
   if (rc == FM_OK) c->prefilled[seq] = true;
   return rc;
 }

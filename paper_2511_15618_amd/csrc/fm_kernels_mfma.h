@@ -59,16 +59,17 @@ __device__ __forceinline__ long vblk_off(int key, int dim) {
   return (long)(key >> 5) * (32 * HD) + dim * 32 + slot;
 }
 
+// fp32 key rows and value rows [M][ld] of a condition memory -> blocked caches (a null pair: not in this call)
 template <typename T, int HD>
-__global__ void k_mem_kv_store(const float* __restrict__ kv, T* __restrict__ Kc, T* __restrict__ Vc, int H,
+__global__ void k_mem_kv_store(const float* __restrict__ k, const float* __restrict__ v, int ld, T* __restrict__ Kc, T* __restrict__ Vc, int H,
                                  int M, int capb) {
   const int m = blockIdx.x;
   const int d = H * HD;
   for (int i = threadIdx.x; i < d; i += blockDim.x) {
     const int hh = i / HD, e = i % HD;
     const long base = (long)hh * capb * (32 * HD);
-    Kc[base + kblk_off<HD>(m, e)] = (T)kv[(long)m * 2 * d + i];
-    Vc[base + vblk_off<HD>(m, e)] = (T)kv[(long)m * 2 * d + d + i];
+    if (k) Kc[base + kblk_off<HD>(m, e)] = (T)k[(long)m * ld + i];
+    if (v) Vc[base + vblk_off<HD>(m, e)] = (T)v[(long)m * ld + i];
   }
 }
 

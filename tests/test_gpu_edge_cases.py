@@ -1,0 +1,43 @@
+"""Calls at the edge of what the entry points take: staging areas that are just large enough, settings of extreme size, values that
+are not finite, and what a call costs its own thread."""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+import synth_inputs as si
+
+pytestmark = pytest.mark.gpu
+
+
+def _ctx(cfg, edit=None):
+    from paper_2511_15618_amd import FlashMesh
+    from paper_2511_15618_amd.binding import config_struct
+    w = si.make_weights(cfg, 0)
+    if edit:
+        edit(w)
+    fm = FlashMesh(config_struct(cfg))
+    fm.load_weights(si.pack_blob(cfg, w))
+    return fm
+
+
+@pytest.mark.parametrize("d,heads,mem,dtype", [(256, 4, 5461, "f32"), (64, 1, 26214, "bf16"), (192, 2, 7281, "f32")])
+def test_static_prefill_takes_all_that_its_area_holds(d, heads, mem, dtype):
+    """mem_len * d_model * (element size + 8) bytes, the largest memory below 16 MiB: the padding to whole key blocks does not count.
+    The keys and values are those of the allocating call, bit for bit; one row more is refused."""
+    esz = 4 if dtype == "f32" else 2
+    assert mem * d * (esz + 8) <= 16 << 20 < (mem + 1) * d * (esz + 8)
+    print("case static area", d, mem, dtype, flush=True)
+    cfg = si.Config("static", d, heads, 32, 1, 1, 1, 1, 1, mem, dtype, 2, 2, 2, 0, 0)
+    fm = _ctx(cfg)
+    x = torch.from_numpy(si.make_memory(cfg, 0)).cuda()
+    fm.prefill_condition(0, x)
+    fm.prefill_condition_static(1, x)
+    for block in range(cfg.n_layers):
+        for a, b in zip(fm.debug_mem_kv(0, block), fm.debug_mem_kv(1, block)):
+            assert np.array_equal(a, b) and np.abs(a).max() > 0, block
+    more = cfg.replace(mem_len=mem + 1)
+    fm = _ctx(more)
+    y = torch.from_numpy(si.make_memory(more, 0)).cuda()
+    assert fm.lib.fm_prefill_condition_static(fm.h, 0, C.c_void_p(y.data_ptr())) == -1
