@@ -132,9 +132,10 @@ struct fm_ctx {
   // 7 us of device time of its own.
   struct GraphKey {
     int what;              // G_*
-    int flags;             // launches that depend on a setting (sampling, correct stage, speculative)
+    int flags;             // launches that depend on a setting (speculative, sampling)
+    int hist;              // and on the correct stage: its vertices, 0 = off
     const void* p[4];      // caller's buffers
-    bool operator==(const GraphKey& o) const { return what == o.what && flags == o.flags && !memcmp(p, o.p, sizeof p); }
+    bool operator==(const GraphKey& o) const { return what == o.what && flags == o.flags && hist == o.hist && !memcmp(p, o.p, sizeof p); }
   };
   struct Graph {
     GraphKey key;
@@ -570,7 +571,7 @@ int verify_any(fm_ctx* c, const int32_t* block_tok, const int32_t* block_len, fl
 }
 // settings that decide which launches a step consists of
 int step_flags(const fm_ctx* c, int speculative) {
-  return (speculative ? 1 : 0) | (c->params.temperature > 0.f ? 2 : 0) | (c->correct_hist << 2);
+  return (speculative ? 1 : 0) | (c->params.temperature > 0.f ? 2 : 0);
 }
 int commit_any(fm_ctx* c, const int32_t* accepted, bool report) {
   hipLaunchKernelGGL(k_commit, dim3(1), dim3(64), 0, c->stream, c->st, c->D, accepted, pass_failed(c), c->commits_dev, report ? c->prog : nullptr);
@@ -1145,7 +1146,7 @@ int fm_draft(fm_ctx* c, int32_t* block_tok, int32_t* block_len) {
   if (!c) return FM_EINVAL;
   if (!c->weights_loaded) return fail(c, FM_ESTATE, "weights not loaded");
   if (!block_tok || !block_len) return fail(c, FM_EINVAL, "null block buffer");
-  const int rc = run_graphed(c, fm_ctx::GraphKey{G_DRAFT, step_flags(c, 1), {block_tok, block_len, nullptr, nullptr}}, false,
+  const int rc = run_graphed(c, fm_ctx::GraphKey{G_DRAFT, step_flags(c, 1), c->correct_hist, {block_tok, block_len, nullptr, nullptr}}, false,
                              [&] { return draft_any(c, block_tok, block_len, 1); });
   return rc == FM_OK && c->sticky_error ? FM_EINVAL : rc;
 }
@@ -1180,7 +1181,7 @@ int fm_verify_block(fm_ctx* c, const int32_t* block_tok, const int32_t* block_le
   if (!c) return FM_EINVAL;
   if (!c->weights_loaded) return fail(c, FM_ESTATE, "weights not loaded");
   if (!block_tok || !block_len || !accepted) return fail(c, FM_EINVAL, "null block / accepted buffer");
-  const int rc = run_graphed(c, fm_ctx::GraphKey{G_VERIFY, step_flags(c, 1), {block_tok, block_len, logits, accepted}}, false,
+  const int rc = run_graphed(c, fm_ctx::GraphKey{G_VERIFY, step_flags(c, 1), c->correct_hist, {block_tok, block_len, logits, accepted}}, false,
                              [&] { return verify_any(c, block_tok, block_len, logits, accepted); });
   return rc == FM_OK && c->sticky_error ? FM_EINVAL : rc;
 }
@@ -1450,7 +1451,7 @@ int fm_generate(fm_ctx* c, int32_t max_faces, int32_t speculative, int32_t* out_
   hipLaunchKernelGGL(k_set_budget, dim3(1), dim3(64), 0, c->stream, c->st, D, 9 * max_faces, c->generation, c->commits_dev);
   HIPCHK(c, hipGetLastError());
   HIPCHK(c, hipEventRecord(c->ev[fm_ctx::E_BEGIN], c->stream));
-  const int flags = step_flags(c, speculative);
+  const int flags = step_flags(c, speculative), hist = c->correct_hist;
   const int per_step = speculative ? D.Bm : 1;         // most tokens a step can commit
   auto draft = [&]() -> int {
     TRY(draft_any(c, c->gen_tok, c->gen_len, speculative));
@@ -1458,8 +1459,8 @@ int fm_generate(fm_ctx* c, int32_t max_faces, int32_t speculative, int32_t* out_
   };
   auto verify = [&]() -> int { return verify_any(c, c->gen_tok, c->gen_len, nullptr, c->gen_acc); };
   auto whole = [&]() -> int { TRY(draft()); TRY(verify()); return commit_any(c, c->gen_acc, true); };
-  const fm_ctx::GraphKey kd{G_DRAFT, flags, {c->gen_tok, c->gen_len, c->gen_acc, c}}, kv{G_VERIFY, flags, {c->gen_tok, c->gen_len, nullptr, c->gen_acc}},
-      ks{G_STEP, flags, {c->gen_tok, c->gen_len, nullptr, c->gen_acc}};
+  const fm_ctx::GraphKey kd{G_DRAFT, flags, hist, {c->gen_tok, c->gen_len, c->gen_acc, c}}, kv{G_VERIFY, flags, hist, {c->gen_tok, c->gen_len, nullptr, c->gen_acc}},
+      ks{G_STEP, flags, hist, {c->gen_tok, c->gen_len, nullptr, c->gen_acc}};
   const int sample_every = 32;
   const long max_steps = 9L * max_faces + 1 + 128;     // + the steps a failed pass of the single-launch kernel may void
   bool phase_pending = false;
@@ -1560,13 +1561,13 @@ int fm_generate(fm_ctx* c, int32_t max_faces, int32_t speculative, int32_t* out_
   TRY(check_persist(c));      // a failure in the very last step: reported, the caller may call again
   if (phase_pending) TRY(take_phases());
   if (stats) {
-    const unsigned long long *cnt = c->host_counts, *hist = c->host_counts + 3;
+    const unsigned long long *cnt = c->host_counts, *acc = c->host_counts + 3;
     float ms = 0.f;
     HIPCHK(c, hipEventElapsedTime(&ms, c->ev[fm_ctx::E_BEGIN], c->ev[fm_ctx::E_END]));
     stats->steps = (int64_t)cnt[0];
     stats->tokens = (int64_t)cnt[1];
     for (int k = 0; k < 3; k++)
-      for (int i = 0; i < 32; i++) stats->acc_hist[k][i] = (int64_t)hist[k * 32 + i];
+      for (int i = 0; i < 32; i++) stats->acc_hist[k][i] = (int64_t)acc[k * 32 + i];
     stats->ms_total = ms;
     const double n = phase_samples > 0 ? (double)phase_samples : 1.0;
     stats->ms_draft = ms_phase[0] / n; stats->ms_verify = ms_phase[1] / n; stats->ms_commit = ms_phase[2] / n;

@@ -41,3 +41,25 @@ def test_static_prefill_takes_all_that_its_area_holds(d, heads, mem, dtype):
     fm = _ctx(more)
     y = torch.from_numpy(si.make_memory(more, 0)).cuda()
     assert fm.lib.fm_prefill_condition_static(fm.h, 0, C.c_void_p(y.data_ptr())) == -1
+
+
+@pytest.mark.parametrize("hist", [1 << 30, (1 << 31) - 1])
+def test_correct_stage_with_the_longest_histories(hist):
+    """Steps recorded with the correct stage off are not replayed for it, however many historical vertices it looks at."""
+    cfg = si.TEST_CONFIGS["t_f32_99"]
+    print("case history", hist, flush=True)
+
+    def labels(before):
+        fm = _ctx(cfg)
+        mems = [torch.from_numpy(si.make_memory(cfg, s)).cuda() for s in range(cfg.batch)]
+        for n in before:
+            for s, m in enumerate(mems):
+                fm.prefill_condition(s, m)
+            fm.set_correct(n)
+            out, _, st = fm.generate(cfg.faces, True)
+        return out.cpu(), st.hist(), fm.debug_draft(1), fm.debug_draft(2)
+
+    got, want = labels([0, 0, hist]), labels([hist])
+    assert np.allclose(want[2].sum(-1), 1, atol=1e-5)              # the label rows of a stage that is on
+    assert torch.equal(got[0], want[0]) and got[1] == want[1]
+    assert np.array_equal(got[2], want[2]) and np.array_equal(got[3], want[3])
