@@ -123,7 +123,7 @@ struct fm_ctx {
   StepParams* params_dev = nullptr;
   int *gen_tok, *gen_len;  // block buffers used by fm_generate
   int* gen_acc;
-  unsigned* commits_dev = nullptr;   // number of the fm_generate call << 20 | its commits so far
+  unsigned* commits_dev = nullptr;   // number of the fm_generate call and its commits so far (fm_progress.h)
   unsigned generation = 0;           // fm_generate calls so far, 12 bits
   Progress* prog = nullptr;          // pinned, written by k_commit
   unsigned long long* host_counts = nullptr;   // pinned, written by k_finish
@@ -1481,12 +1481,12 @@ int fm_generate(fm_ctx* c, int32_t max_faces, int32_t speculative, int32_t* out_
   bool alive = true, failed = false;
   int len[64];
   auto look = [&]() {
-    unsigned least = 0xFFFFFu;
+    unsigned least = FM_COMMIT_MASK;
     alive = failed = false;
     for (int s = 0; s < D.S; s++) {
       const unsigned long long w = __atomic_load_n(&c->prog->seq[s], __ATOMIC_RELAXED);
-      const unsigned gen = (unsigned)(w >> 52), v = (unsigned)w;
-      const unsigned ahead = gen == c->generation ? ((unsigned)(w >> 32) - (unsigned)done) & 0xFFFFFu : 0u;    // commits since `done`
+      const unsigned gen = progress_call(w), v = progress_state(w);
+      const unsigned ahead = gen == c->generation ? progress_ahead(w, done) : 0u;      // commits since `done`
       least = std::min(least, ahead);
       len[s] = gen != c->generation ? 0 : v == 1 ? -1 : (int)v - 2;
       if (done + ahead > 0 && v == 0) failed = true;

@@ -3,6 +3,7 @@
 // and a little fp32; every kernel is a single small launch.
 #pragma once
 #include "fm_device.h"
+#include "fm_progress.h"
 #include "fm_kernels_basic.h"
 #include "fm_kernels_decode.h"
 
@@ -154,10 +155,8 @@ __global__ __launch_bounds__(1024) void k_choose_greedy(StateDev st, Dims D, con
   if (threadIdx.x == 0) accept_seq(st, s, len, accepted_out, bad_pass, [&](int i) { return stok[i + 1] == sy[i]; });
 }
 
-// What the host may look at while the device runs ahead of it: one pinned word per sequence, written by the commits of
-// fm_generate.  Count and state travel in one word, so nothing has to be ordered.
-//   upper half: number of the fm_generate call (12 bits), commits since its start (20 bits)
-//   lower half: 0 = the single-launch verify kernel gave up, 1 = sequence finished, else committed length + 2
+// What the host may look at while the device runs ahead of it: one pinned word per sequence (fm_progress.h), written by the
+// commits of fm_generate.
 struct Progress { unsigned long long seq[64]; };
 
 // An accepted length of 0 (a pass that did not complete) leaves the sequence as it is.  prog: null for the caller's own commits.
@@ -167,11 +166,10 @@ __global__ void k_commit(StateDev st, Dims D, const int* __restrict__ accepted, 
   __shared__ int any_live;
   auto report = [&](bool bad) {
     if (!prog) return;
-    const unsigned n = *commits + 1;       // one wave: read by all lanes before lane 0 writes it
+    const unsigned n = progress_next(*commits);       // one wave: read by all lanes before lane 0 writes it
     if (s == 0) *commits = n;
     if (s < D.S)
-      __hip_atomic_store(&prog->seq[s], (unsigned long long)n << 32 | (unsigned)(bad ? 0 : st.fin[s] ? 1 : st.P[s] + 2), __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_SYSTEM);
+      __hip_atomic_store(&prog->seq[s], progress_word(n, bad ? 0 : st.fin[s] ? 1 : st.P[s] + 2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   };
   if (failed && *failed) { report(true); return; }
   if (s == 0) any_live = 0;
@@ -221,7 +219,7 @@ __global__ __launch_bounds__(256) void k_finish(StateDev st, Dims D, int* __rest
 // generation > 0: the start of fm_generate call number `generation` (statistics and the commit counter start over)
 __global__ void k_set_budget(StateDev st, Dims D, int budget, unsigned generation, unsigned* commits) {
   if (generation) {
-    if (threadIdx.x == 0) *commits = generation << 20;
+    if (threadIdx.x == 0) *commits = progress_start(generation);
     for (int i = threadIdx.x; i < 96; i += 64) st.acc_hist[i] = 0;
     if (threadIdx.x < 3) st.counters[threadIdx.x] = 0;
   }
