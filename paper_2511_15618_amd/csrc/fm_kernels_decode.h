@@ -430,6 +430,14 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
   // The operands of the next block are requested into the registers of this one as soon as those are free: its keys behind the
   // score products, its values behind the output products.
   for (; b < nblk; b += bstep) {
+    // Slots that this stream has not reached hold what an earlier mesh left there.  Their probability is 0, but 0 times a value that is
+    // not finite is NaN: they count as zero rows.
+    if (lapbase == 0 && b * 32 + 31 > maxlim) {
+#pragma unroll
+      for (int dt = 0; dt < DT; dt++)
+#pragma unroll
+        for (int j = 0; j < 8; j++) vf[dt][j] = b * 32 + (j >> 2) * 16 + g * 4 + (j & 3) > maxlim ? (T)0.f : vf[dt][j];
+    }
     const int bn = min(b + bstep, A->capb - 1);
     // scores, transposed: sT[t][hb][i] = <K[key], Q[q]> for key = b*32 + hb*16 + g*4 + i, q = this lane's row
     f32x4 sT[QT][2];
@@ -481,13 +489,14 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
     }
     if (b + bstep < nblk) load_v(bn);
   }
-  // combine the waves of the workgroup that had keys
+  // Combine the waves of the workgroup that had keys.  An inactive row carries a negative sum and gives 0; a row with keys whose
+  // sum is NaN or 0 (scores that are not finite) gives NaN, which the pass counts.
 #pragma unroll
   for (int t = 0; t < QT; t++) {
     float l = lrun[t];
     l += __shfl_xor(l, 16, 64);
     l += __shfl_xor(l, 32, 64);
-    if (g == 0) { lm[wave * NQ + t * 16 + ql] = mrun[t]; ll[wave * NQ + t * 16 + ql] = l; }
+    if (g == 0) { lm[wave * NQ + t * 16 + ql] = lim[t] < 0 ? 0.f : mrun[t]; ll[wave * NQ + t * 16 + ql] = lim[t] < 0 ? -1.f : l; }
 #pragma unroll
     for (int dt = 0; dt < DT; dt++) *reinterpret_cast<f32x4*>(lo + (wave * NQ + t * 16 + ql) * LD + dt * 16 + g * 4) = o[t][dt];
   }
@@ -509,7 +518,7 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
     if (nact == 1) {
       V4 ov;
 #pragma unroll
-      for (int i = 0; i < 4; i++) ov[i] = (T)(den > 0.f ? num[i] / den : 0.f);
+      for (int i = 0; i < 4; i++) ov[i] = (T)(den < 0.f ? 0.f : num[i] / den);
       *reinterpret_cast<V4*>((T*)A->out + map_off(rm, s, A->q0 + qi, hh * HD + dim, d >> 5)) = ov;
     } else {
 #pragma unroll
@@ -570,7 +579,7 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
     }
     V4 ov;
 #pragma unroll
-    for (int i = 0; i < 4; i++) ov[i] = (T)(den > 0.f ? num[i] / den : 0.f);
+    for (int i = 0; i < 4; i++) ov[i] = (T)(den < 0.f ? 0.f : num[i] / den);
     *reinterpret_cast<V4*>((T*)A->out + map_off(rm, s, A->q0 + qi, hh * HD + dim, d >> 5)) = ov;
   }
 }

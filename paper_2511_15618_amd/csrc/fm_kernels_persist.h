@@ -572,8 +572,10 @@ __device__ __forceinline__ bool pk_attn_unit(const PkArgs& a, SH& sh, const u64*
         const int dim = dt * 16 + (lane & 15);
 #pragma unroll
         for (int j = 0; j < 8; j++) {
-          const int nr = held(b * 32 + (j >> 2) * 16 + g * 4 + (j & 3)) - P0;
-          if (nr >= 0 && nr < R) {
+          // From this pass: positions >= P0, all of them rows of it.  A slot that this stream has not reached (position below 0) takes the
+          // value too that was fetched for it, the first row's: its probability is 0, but what an earlier mesh left there may not be
+          // finite, and 0 times that is NaN.
+          if ((unsigned)held(b * 32 + (j >> 2) * 16 + g * 4 + (j & 3)) >= (unsigned)P0) {
             const unsigned w = raw[16 + dt * 8 + j];
             const unsigned short hbits = (dim & 1) ? (unsigned short)(w >> 16) : (unsigned short)(w & 0xFFFFu);
             vf[dt][j] = __builtin_bit_cast(f16_t, hbits);
@@ -638,7 +640,8 @@ __device__ __forceinline__ bool pk_attn_unit(const PkArgs& a, SH& sh, const u64*
     float l = lrun[t];
     l += __shfl_xor(l, 16, 64);
     l += __shfl_xor(l, 32, 64);
-    if (g == 0) { sh.lm[wave][t * 16 + ql] = mrun[t]; sh.ll[wave][t * 16 + ql] = l; }
+    // (an inactive row carries a negative sum and gives 0; a row with keys whose sum is NaN or 0 gives NaN, which the pass counts)
+    if (g == 0) { sh.lm[wave][t * 16 + ql] = lim[t] < 0 ? 0.f : mrun[t]; sh.ll[wave][t * 16 + ql] = lim[t] < 0 ? -1.f : l; }
 #pragma unroll
     for (int dt = 0; dt < 4; dt++)
 #pragma unroll
@@ -704,7 +707,7 @@ __device__ __forceinline__ bool pk_merge_unit(const PkArgs& a, int maxlim, int R
       }
     den += __shfl_xor(den, 16, 64); num += __shfl_xor(num, 16, 64);
     den += __shfl_xor(den, 32, 64); num += __shfl_xor(num, 32, 64);
-    const float v = den > 0.f ? num / den : 0.f;
+    const float v = den < 0.f ? 0.f : num / den;
     const float o = __shfl_xor(v, 1, 64);
     if (lane < 16 && (lane & 1) == 0 && wave + 4 * j < R)
       pk_st(att + (long)(rg * 16 + wave + 4 * j) * (d >> 1) + ((hh * 64 + dim) >> 1), pk_pack(v, o), tag);

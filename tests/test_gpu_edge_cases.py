@@ -1,5 +1,5 @@
 """Calls at the edge of what the entry points take: staging areas that are just large enough, settings of extreme size, values that
-are not finite, and what a call costs its own thread."""
+are not finite."""
 import ctypes as C
 
 import numpy as np
@@ -11,12 +11,10 @@ import synth_inputs as si
 pytestmark = pytest.mark.gpu
 
 
-def _ctx(cfg, edit=None):
+def _ctx(cfg):
     from paper_2511_15618_amd import FlashMesh
     from paper_2511_15618_amd.binding import config_struct
     w = si.make_weights(cfg, 0)
-    if edit:
-        edit(w)
     fm = FlashMesh(config_struct(cfg))
     fm.load_weights(si.pack_blob(cfg, w))
     return fm
@@ -63,3 +61,52 @@ def test_correct_stage_with_the_longest_histories(hist):
     assert np.allclose(want[2].sum(-1), 1, atol=1e-5)              # the label rows of a stage that is on
     assert torch.equal(got[0], want[0]) and got[1] == want[1]
     assert np.array_equal(got[2], want[2]) and np.array_equal(got[3], want[3])
+
+
+def _small(name, d, heads, mem, dtype, batch):
+    return si.Config(name, d, heads, 32, 1, 1, 1, 1, 2, mem, dtype, batch, 6, 2, 9, 9)
+
+
+# keys of a memory in one split and in several, both verify paths, both storage types, two head widths
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")], ids=["nan", "inf"])
+@pytest.mark.parametrize("cfg", [_small("f32", 128, 2, 24, "f32", 2), _small("f32_splits", 192, 2, 290, "f32", 2),
+                                 _small("half", 128, 2, 40, "bf16", 3), _small("half_splits", 128, 2, 1001, "bf16", 2),
+                                 _small("one_launch", 128, 2, 40, "bf16", 1), _small("one_launch_splits", 128, 2, 1001, "bf16", 1)],
+                         ids=lambda c: c.name)
+def test_memory_that_is_not_finite(cfg, bad):
+    """A condition memory with one value that is not finite: the logits of its sequence show it and its rows are counted, the other
+    sequences do not see it, and neither does the next mesh of the sequence, over caches that still hold the first one's rows."""
+    print("case memory", cfg.name, bad, flush=True)
+    mems = [torch.from_numpy(si.make_memory(cfg, s)).cuda() for s in range(cfg.batch)]
+    broken = mems[0].clone()
+    broken[cfg.mem_len // 2, 3] = bad
+
+    def first_pass(fm, mem0):
+        for s, m in enumerate([mem0] + mems[1:]):
+            fm.prefill_condition(s, m)
+        tok, ln = fm.new_block()
+        tok[:] = torch.arange(fm.block_max, device="cuda", dtype=torch.int32)
+        tok[:, 0] = cfg.bos
+        ln[:] = fm.block_max
+        acc = torch.zeros(cfg.batch, dtype=torch.int32, device="cuda")
+        logits = torch.zeros(cfg.batch, fm.block_max, cfg.vocab, device="cuda")
+        fm.verify_block(tok, ln, logits, acc)
+        return logits.cpu()
+
+    def mesh(fm, mem0):
+        for s, m in enumerate([mem0] + mems[1:]):
+            fm.prefill_condition(s, m)
+        out, n, st = fm.generate(cfg.faces, True)
+        assert n.tolist() == [9 * cfg.faces] * cfg.batch
+        return out.cpu(), int(st.nonfinite_rows)
+
+    fm = _ctx(cfg)
+    want, (want_tok, healthy) = first_pass(fm, mems[0]), mesh(fm, mems[0])
+    assert healthy == 0 and torch.isfinite(want).all()
+    fm = _ctx(cfg)
+    got, (tok, counted) = first_pass(fm, broken), mesh(fm, broken)
+    assert not torch.isfinite(got[0]).any() and counted > 0
+    assert torch.equal(got[1:], want[1:]) and torch.equal(tok[1:], want_tok[1:])
+    assert torch.equal(first_pass(fm, mems[0]), want)
+    tok, counted = mesh(fm, mems[0])
+    assert counted == 0 and torch.equal(tok, want_tok)
