@@ -178,7 +178,9 @@ int fm_commit(fm_ctx* ctx, const int32_t* accepted_len_dev);
 /* Whole loop, device side: repeat draft -> verify -> commit until every sequence has max_faces faces
  * or ended with EOS.  speculative = 0 runs plain one-token-per-step greedy decoding of the same
  * backbone.  out_tok_dev [batch, max_tokens] receives x_1.., out_len_dev [batch] their count.
- * host_stats may be NULL.  Sequences must have been prefetched with fm_prefill_condition. */
+ * host_stats may be NULL.  Sequences must have been prefetched with fm_prefill_condition.
+ * The call returns when the mesh is complete.  Its thread sleeps between looks at the lengths that commits report, except
+ * for the last steps of a mesh, which depend on them one by one. */
 int fm_generate(fm_ctx* ctx, int32_t max_faces, int32_t speculative, int32_t* out_tok_dev,
                 int32_t* out_len_dev, fm_stats* host_stats);
 

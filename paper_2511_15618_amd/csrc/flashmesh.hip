@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -12,6 +13,7 @@
 #include <cstdlib>
 #include <functional>
 #include <string>
+#include <thread>
 #include <type_traits>
 #include <vector>
 
@@ -1499,7 +1501,9 @@ int fm_generate(fm_ctx* c, int32_t max_faces, int32_t speculative, int32_t* out_
     // The device must never wait for the host, and no step must run for nothing.  A further step is enqueued at once while it
     // cannot be the one after the last: some sequence stays below its budget even if all that is enqueued is accepted whole (where
     // EOS may be emitted: one step more than the device has finished).  Else only when the device has finished what it has.
-    for (unsigned spins = 1;; spins++) {
+    // While steps are queued behind the one that runs the thread sleeps between looks (20 us, about 75 with the scheduler's slack: no step is
+    // as short); only for the last steps of a mesh, each of which the device would wait behind, does it look all the time.
+    for (unsigned looks = 1;; looks++) {
       look();
       const long ahead = step - done;              // steps enqueued and not yet committed
       if (ahead == 0 || (done > 0 && (failed || !alive))) break;
@@ -1509,7 +1513,7 @@ int fm_generate(fm_ctx* c, int32_t max_faces, int32_t speculative, int32_t* out_
         for (int s = 0; s < D.S; s++) sure |= len[s] >= 0 && len[s] + per_step * ahead < 9L * max_faces;
         if (sure) break;
       }
-      if (spins % 4096 == 0) {
+      if (looks % 512 == 0) {
         const hipError_t q = hipStreamQuery(c->stream);
         if (q != hipSuccess && q != hipErrorNotReady) return fail(c, FM_EHIP, "decode loop: %s", hipGetErrorString(q));
         (void)hipGetLastError();
@@ -1518,8 +1522,12 @@ int fm_generate(fm_ctx* c, int32_t max_faces, int32_t speculative, int32_t* out_
           if (step - done > 0) return fail(c, FM_EHIP, "decode loop: the stream is idle but %ld steps were not reported", step - done);
         }
       }
+      if (ahead > 1) {
+        std::this_thread::sleep_for(std::chrono::microseconds(20));
+        continue;
+      }
 #if defined(__x86_64__)
-      __builtin_ia32_pause();
+      for (int i = 0; i < 8; i++) __builtin_ia32_pause();
 #endif
     }
     if (done > 0 && failed) {

@@ -1,6 +1,7 @@
 """Calls at the edge of what the entry points take: staging areas that are just large enough, settings of extreme size, values that
-are not finite."""
+are not finite, and what a call costs its own thread."""
 import ctypes as C
+import time
 
 import numpy as np
 import pytest
@@ -110,3 +111,23 @@ def test_memory_that_is_not_finite(cfg, bad):
     assert torch.equal(first_pass(fm, mems[0]), want)
     tok, counted = mesh(fm, mems[0])
     assert counted == 0 and torch.equal(tok, want_tok)
+
+
+@pytest.mark.parametrize("ban", [1, 0], ids=["to_the_budget", "to_eos"])
+def test_generate_leaves_its_core_to_others(ban):
+    """The thread that calls fm_generate sleeps while the device works: its CPU time stays below half of the call's time, where a thread
+    that looks all the time has all of it (enqueueing the 30 launches of a step takes about 0.1 ms of its 0.8)."""
+    cfg = si.Config("core", 512, 8, 64, 2, 2, 4, 4, 8, 1024, "bf16", 1, 60, 2, 9, 9, ban_specials=ban)
+    print("case core", ban, flush=True)
+    fm = _ctx(cfg)
+    mem = torch.from_numpy(si.make_memory(cfg, 0)).cuda()
+    shares = []
+    for _ in range(3):
+        fm.prefill_condition(0, mem)
+        torch.cuda.synchronize()
+        wall, cpu = time.perf_counter(), time.thread_time()
+        _, _, st = fm.generate(cfg.faces, True)
+        wall, cpu = time.perf_counter() - wall, time.thread_time() - cpu
+        print(f"steps {st.steps}, {wall * 1e3:.1f} ms, {cpu * 1e3:.1f} ms of CPU time", flush=True)
+        shares.append(cpu / wall)
+    assert st.steps >= 20 and min(shares) < 0.5
