@@ -327,10 +327,6 @@ __device__ __forceinline__ int attn_active(int maxlim, int capb, int ns, int NW)
   return max(1, min(ns, (nblk + NW - 1) / NW));
 }
 
-// 16- and 4-byte agent-scope loads whose wait the caller states (the compiler would keep atomic loads one by one)
-__device__ __forceinline__ void ld_agent4(f32x4& v, const float* p) { asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(v) : "v"(p) : "memory"); }
-__device__ __forceinline__ void ld_agent1(float& v, const float* p) { asm volatile("global_load_dword %0, %1, off sc1" : "=v"(v) : "v"(p) : "memory"); }
-
 template <typename T, int QT, int HD, int NW>
 __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
   typedef typename Op<T>::V8 V8;
@@ -541,7 +537,8 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
   }
   __syncthreads();
   if (!*last) return;
-  const float* base = a.ws + ((long)blockIdx.z * a.H + hh) * a.ns_max * PSZ;
+  const agent_buf_t parts = agent_buf(a.ws + ((long)blockIdx.z * a.H + hh) * a.ns_max * PSZ, nact * PSZ * 4);
+  agent_again();
   constexpr int C = 8;      // splits whose parts a thread has in flight together
   for (int e = threadIdx.x; e < A->rows * (HD / 4); e += NW * 64) {
     const int qi = e / (HD / 4), dim = e % (HD / 4) * 4;
@@ -552,18 +549,15 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
       float m[C], l[C];
 #pragma unroll
       for (int j = 0; j < C; j++) {
-        const float* p = base + (long)min(k0 + j, nact - 1) * PSZ;
-        ld_agent4(v[j], p + qi * HD + dim);
-        ld_agent1(m[j], p + NQ * HD + qi);
-        ld_agent1(l[j], p + NQ * HD + NQ + qi);
+        const int p = min(k0 + j, nact - 1) * PSZ;
+        v[j] = __builtin_bit_cast(f32x4, ld_agent4(parts, (p + qi * HD + dim) * 4));
+        m[j] = __uint_as_float(ld_agent1(parts, (p + NQ * HD + qi) * 4));
+        l[j] = __uint_as_float(ld_agent1(parts, (p + NQ * HD + NQ + qi) * 4));
       }
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       float Mc = M;
 #pragma unroll
-      for (int j = 0; j < C; j++) {
-        asm volatile("" : "+v"(v[j]), "+v"(m[j]), "+v"(l[j]));      // uses stay behind the wait
+      for (int j = 0; j < C; j++)
         if (k0 + j < nact) Mc = fmaxf(Mc, m[j]);
-      }
       const float Ms = Mc == -INFINITY ? 0.f : Mc;
       const float sc = __builtin_amdgcn_exp2f(M - Ms);
       num *= sc;

@@ -37,6 +37,15 @@ template <> struct Op<float> {
 __device__ __forceinline__ void st_agent(float* p, float v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// The loads come as buffer loads (byte offset `o` into `bytes` from a uniform base, 0 beyond them): the compiler knows them, so it keeps many in
+// flight where atomic loads would go one by one, and places every wait itself.  It may also take two of them for one: a loop that
+// polls has a compiler barrier (agent_again) in front of them.
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef __amdgpu_buffer_rsrc_t agent_buf_t;
+__device__ __forceinline__ agent_buf_t agent_buf(const void* base, int bytes) { return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00027000); }
+__device__ __forceinline__ u32x4 ld_agent4(agent_buf_t b, int o) { return __builtin_amdgcn_raw_buffer_load_b128(b, o, 0, 16); }      // 16: sc1
+__device__ __forceinline__ unsigned ld_agent1(agent_buf_t b, int o) { return __builtin_amdgcn_raw_buffer_load_b32(b, o, 0, 16); }
+__device__ __forceinline__ void agent_again() { asm volatile("" ::: "memory"); }
 
 // ------------------------------------------------------------------------------------------
 // Cache layouts: one 32-key block of a head = 32 HD values (4 KiB of halves for the 64-wide heads

@@ -195,7 +195,6 @@ template <int ASRC, class SH>
 __device__ __forceinline__ bool pk_gemm_tile(const PkArgs& a, SH& sh, pk_cw_t Wt, int KT, const u64* A,
                                              unsigned tagA, pk_cf_t gain, int R, f32x4& result, int stage,
                                              int lda = 0) {
-  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
   constexpr int NL = 2;       // 16-byte loads per fragment and lane
   constexpr int EF = 16;      // tagged elements (half pairs) per fragment row
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -220,9 +219,10 @@ __device__ __forceinline__ bool pk_gemm_tile(const PkArgs& a, SH& sh, pk_cw_t Wt
         gl[2 * f + 1] = *(const PK_GLOBAL f32x4*)(gp + 4);
       }
   }
-  // this wave's part of the rows: element (wave*FW + f)*EF + g*(EF/4) of row r is where fragment f starts
+  // this wave's part of the rows: element (wave*FW + f)*EF + g*(EF/4) of row r is where fragment f starts; rows past the last read 0
   const u64* Aw = A + (long)(wave * FW) * EF;
-  const u64* mine = Aw + (long)min(r, R - 1) * lda + g * (EF / 4);
+  const agent_buf_t Ab = agent_buf(A, ((R - 1) * lda + KT * EF) * 8);
+  const int mine = on ? (r * lda + (wave * FW) * EF + g * (EF / 4)) * 8 : 1 << 30;
   const u64 t0 = wall_clock64();
   int it = 0;
   bool good = true;
@@ -244,31 +244,25 @@ __device__ __forceinline__ bool pk_gemm_tile(const PkArgs& a, SH& sh, pk_cw_t Wt
   }
   if (a.two_phase) PK_WATCH(Aw)
   PK_MARK(1);
-  // phase 2: the fragments (inline asm loads: the wait is explicit, and every destination is passed through
-  // an empty asm afterwards to pin its uses behind the wait)
+  // phase 2: the fragments
   u32x4 v[8 * NL];
-#define PK_FETCH_FRAGS(MINE, AW)                                                                              \
-  while (good) {                                                                                              \
-    _Pragma("unroll") for (int f = 0; f < 8; f++) {                                                           \
-      _Pragma("unroll") for (int j = 0; j < NL; j++) {                                                        \
-        v[f * NL + j] = u32x4{tagA, tagA, tagA, tagA};                                                        \
-        if (f < FW && on) {                                                                                   \
-          const u64* p = (MINE) + f * EF + 2 * j;                                                             \
-          asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(v[f * NL + j]) : "v"(p) : "memory");      \
-        }                                                                                                     \
-      }                                                                                                       \
-    }                                                                                                         \
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                                                          \
-    bool ok = true;                                                                                           \
-    _Pragma("unroll") for (int i = 0; i < 8 * NL; i++) {                                                      \
-      asm volatile("" : "+v"(v[i]));                                                                          \
-      ok = ok && v[i][1] == tagA && v[i][3] == tagA;      /* unused slots were preset to the tag */           \
-    }                                                                                                         \
-    if (__all(ok)) break;                                                                                     \
-    if ((++it & 63) == 0 && pk_expired(a, t0, stage)) { good = false; break; }                                 \
-    PK_WATCH(AW)                                                                                              \
+  while (good) {
+    agent_again();
+#pragma unroll
+    for (int f = 0; f < 8; f++)
+      if (f < FW)
+#pragma unroll
+        for (int j = 0; j < NL; j++) v[f * NL + j] = ld_agent4(Ab, mine + (f * EF + 2 * j) * 8);
+    unsigned diff = 0;
+#pragma unroll
+    for (int f = 0; f < 8; f++)
+      if (f < FW)
+#pragma unroll
+        for (int j = 0; j < NL; j++) diff |= (v[f * NL + j][1] ^ tagA) | (v[f * NL + j][3] ^ tagA);
+    if (__all(diff == 0 || !on)) break;
+    if ((++it & 63) == 0 && pk_expired(a, t0, stage)) { good = false; break; }
+    PK_WATCH(Aw)
   }
-  PK_FETCH_FRAGS(mine, Aw)
   PK_MARK(2);
   if (ASRC == 1) {
     // RMSNorm without a barrier in front of the multiplication: the MFMA runs on half(x * gain) and the per-row
@@ -278,8 +272,7 @@ __device__ __forceinline__ bool pk_gemm_tile(const PkArgs& a, SH& sh, pk_cw_t Wt
 #pragma unroll
     for (int f = 0; f < 8; f++) {
       if (f < FW) {
-        u32x4 pk = u32x4{0u, 0u, 0u, 0u};
-        if (on && good) pk = u32x4{v[2 * f][0], v[2 * f][2], v[2 * f + 1][0], v[2 * f + 1][2]};
+        const u32x4 pk = {v[2 * f][0], v[2 * f][2], v[2 * f + 1][0], v[2 * f + 1][2]};
         const f16x8 xh = __builtin_bit_cast(f16x8, pk);
         f16x8 av;
 #pragma unroll
@@ -298,13 +291,11 @@ __device__ __forceinline__ bool pk_gemm_tile(const PkArgs& a, SH& sh, pk_cw_t Wt
 #pragma unroll
     for (int f = 0; f < 8; f++) {
       if (f < FW) {
-        u32x4 pk = u32x4{0u, 0u, 0u, 0u};
-        if (on && good) pk = u32x4{v[2 * f][0], v[2 * f][2], v[2 * f + 1][0], v[2 * f + 1][2]};
+        const u32x4 pk = {v[2 * f][0], v[2 * f][2], v[2 * f + 1][0], v[2 * f + 1][2]};
         acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, pk), wf[f], acc, 0, 0, 0);
       }
     }
   }
-#undef PK_FETCH_FRAGS
 #undef PK_WATCH
   sh.red[wave][lane] = acc;
   if (__syncthreads_or(!good)) return false;
@@ -495,34 +486,28 @@ __device__ __forceinline__ bool pk_attn_unit(const PkArgs& a, SH& sh, const u64*
   if (b0 < nblk) load(ka[0], va[0], b0);
   // q of this lane: dims g*8..+8 and 32 + g*8..+8 of the head = two runs of four tagged elements = four 16-byte
   // agent-scope loads per query tile, simply repeated until every tag matches (small enough to poll with the data itself)
-  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
   f16x8 qf0[QT], qf1[QT];
   bool ok = true;
   {
-    const u64* qp[QT];
+    const agent_buf_t qb = agent_buf(qbuf, QT * 16 * (d >> 1) * 8);
+    int qo[QT];
 #pragma unroll
-    for (int t = 0; t < QT; t++) qp[t] = qbuf + (long)(on[t] ? t * 16 + ql : 0) * (d >> 1) + ((hh * 64 + g * 8) >> 1);
+    for (int t = 0; t < QT; t++) qo[t] = ((on[t] ? t * 16 + ql : 0) * (d >> 1) + ((hh * 64 + g * 8) >> 1)) * 8;
     const u64 t0 = wall_clock64();
     int it = 0;
     u32x4 qv[QT][4];
     while (true) {
+      agent_again();
 #pragma unroll
       for (int t = 0; t < QT; t++)
 #pragma unroll
-        for (int j = 0; j < 4; j++) {
-          const u64* p = qp[t] + (j >> 1) * 16 + (j & 1) * 2;
-          asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(qv[t][j]) : "v"(p) : "memory");
-        }
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      bool okq = true;
+        for (int j = 0; j < 4; j++) qv[t][j] = ld_agent4(qb, qo[t] + ((j >> 1) * 16 + (j & 1) * 2) * 8);
+      unsigned diff = 0;
 #pragma unroll
       for (int t = 0; t < QT; t++)
 #pragma unroll
-        for (int j = 0; j < 4; j++) {
-          asm volatile("" : "+v"(qv[t][j]));
-          okq = okq && qv[t][j][1] == tag && qv[t][j][3] == tag;
-        }
-      if (__all(okq)) break;
+        for (int j = 0; j < 4; j++) diff |= (qv[t][j][1] ^ tag) | (qv[t][j][3] ^ tag);
+      if (__all(diff == 0)) break;
       if ((++it & 63) == 0 && pk_expired(a, t0, stage)) { ok = false; break; }
     }
 #pragma unroll

@@ -282,7 +282,6 @@ __global__ __launch_bounds__(256) void k_probe_mfma(float* __restrict__ sink, in
 __global__ __launch_bounds__(256) void k_probe_exchange(unsigned long long* buf, unsigned* arrive, unsigned* abort_word,
                                                         unsigned long long* ticks, int vol, int nstage, int mode) {
   typedef unsigned long long u64;
-  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
   const int nwg = gridDim.x;
   auto expired = [&](u64 t0) -> bool {
     if (__hip_atomic_load(abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return true;
@@ -303,6 +302,7 @@ __global__ __launch_bounds__(256) void k_probe_exchange(unsigned long long* buf,
   const int per = vol / nwg, n16 = vol / 2;
   for (int t = 1; t <= nstage; t++) {
     u64* g = buf + (long)(t % 3) * vol;
+    const agent_buf_t gb = agent_buf(g, vol * 8);
     if (mode == 1) {
       if (blockIdx.x > 1) break;
       if (threadIdx.x == 0) {
@@ -320,18 +320,15 @@ __global__ __launch_bounds__(256) void k_probe_exchange(unsigned long long* buf,
     const u64 t0 = wall_clock64();
     int it = 0;
     while (true) {
+      agent_again();
       u32x4 v[12];
 #pragma unroll
-      for (int j = 0; j < 12; j++)
-        if (256 * j < n16) {        // uniform guard, clamped address (n16 <= 3072)
-          const u64* p = g + 2 * (long)min((int)threadIdx.x + 256 * j, n16 - 1);
-          asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(v[j]) : "v"(p) : "memory");
-        }
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      for (int j = 0; j < 12; j++)        // uniform guard, clamped address (n16 <= 3072)
+        if (256 * j < n16) v[j] = ld_agent4(gb, 16 * min((int)threadIdx.x + 256 * j, n16 - 1));
       bool ok = true;
 #pragma unroll
       for (int j = 0; j < 12; j++)
-        if (256 * j < n16) { asm volatile("" : "+v"(v[j])); ok = ok && v[j][1] == (unsigned)t && v[j][3] == (unsigned)t; }
+        if (256 * j < n16) ok = ok & (v[j][1] == (unsigned)t) & (v[j][3] == (unsigned)t);
       if (__syncthreads_and(ok)) break;
       if ((++it & 3) == 0 && __syncthreads_or(expired(t0))) return;
     }
