@@ -18,7 +18,6 @@
 #include <vector>
 
 #include "fm_device.h"
-#include "fm_kernels_basic.h"
 #include "fm_kernels_step.h"
 #include "fm_kernels_mfma.h"
 #include "fm_kernels_decode.h"
@@ -513,7 +512,7 @@ void run_hf(fm_ctx* c, int set, const HfLevel& hf, int mult, const Layer& last, 
   t.S = D.S; t.H = D.H; t.ws = c->attn_ws; t.arrived = c->attn_arrived; t.run_flag = flag;
   const int cap = level_cap(c, level);
   int n = 0;
-  for (int q0 = 0; q0 < per_seq; q0 += 32)      // at most 48 rows per sequence: one or two sets
+  for (int q0 = 0; q0 < per_seq; q0 += 32)      // at most 54 rows per sequence: one or two sets
     t.set[n++] = AttnSet{c->dq, c->dr.lim[set], std::min(32, per_seq - q0), q0, per_seq, last.Kc, last.Vc,
                          (long)cache_seq_elems(c, cap), (cap + 31) / 32, level_window(c, level), 1, rm, c->dX};
   if (!dec_attention<T>(t, n, D.hd, c->stream)) refuse(c, "HF attention");
@@ -542,7 +541,7 @@ int draft_impl(fm_ctx* c, int32_t* block_tok, int32_t* block_len, int speculativ
   const int d = D.d;
   if (speculative) {
     hipLaunchKernelGGL(k_draft_setup, dim3(D.S, (D.Dc + D.nspv + D.nspf + D.nhfv + 2 * D.nhfc + 7) / 8 + (D.Dc + D.nspv + D.nspf + D.nhfv + 2 * D.nhfc == 0)), dim3(256), 0, c->stream, c->st, D, c->inv, c->dr, c->db);
-    const int *f_alive = c->dr.flags, *f_f = c->dr.flags + 2;
+    const int *f_alive = c->dr.flags, *f_f = c->dr.flags + 1;
     const Layer& lastc = c->stacks[4].back();
     const Layer& lastv = c->stacks[3].back();
     const int nLM = D.S * (D.Dc + 2 * D.nhfc);
@@ -830,8 +829,6 @@ int build_persist(fm_ctx* c) {
   // test hooks for the bounded waits: a shorter bound, and an embedding that publishes under the wrong tag
   a.timeout_ticks = PK_TIMEOUT_TICKS;
   a.test_skew = 0;
-  a.two_phase = 0;
-  if (const char* e = getenv("FM_PK_TWO_PHASE")) a.two_phase = atoi(e);
   if (const char* e = getenv("FM_PK_TIMEOUT_TICKS")) a.timeout_ticks = strtoull(e, nullptr, 10);
   if (const char* e = getenv("FM_PK_TEST_SKEW")) a.test_skew = (unsigned)atoi(e);
   c->pk_lds = 0;   // the kernel uses static LDS only
@@ -854,7 +851,7 @@ int build_buffers(fm_ctx* c) {
   TRY(dalloc(c, &st.P, S)); TRY(dalloc(c, &st.main, S)); TRY(dalloc(c, &st.fin, S));
   TRY(dalloc(c, &st.firedv, S)); TRY(dalloc(c, &st.firedf, S));
   TRY(dalloc(c, &st.basec, S)); TRY(dalloc(c, &st.basev, S)); TRY(dalloc(c, &st.basef, S));
-  TRY(dalloc(c, &st.vlen, S)); TRY(dalloc(c, &st.vtok, S * D.Bm)); TRY(dalloc(c, &st.y, S * D.Bm)); TRY(dalloc(c, &st.acc, S));
+  TRY(dalloc(c, &st.vlen, S)); TRY(dalloc(c, &st.vtok, S * D.Bm)); TRY(dalloc(c, &st.y, S * D.Bm));
   TRY(dalloc(c, &st.hist, S * (D.maxtok + 1))); TRY(dalloc(c, &st.budget, 1)); TRY(dalloc(c, &st.alive, 1));
   TRY(dalloc(c, &st.acc_hist, 3 * 32)); TRY(dalloc(c, &st.counters, 3)); TRY(dalloc(c, &st.kind, S));
   TRY(dalloc(c, &c->ring_hc, S * RS_C * d)); TRY(dalloc(c, &c->tap_c, S * RS_C * d));
@@ -885,7 +882,7 @@ int build_buffers(fm_ctx* c) {
   size_t maxset = 1;
   for (int i = 3; i < 5; i++) {
     maxset = std::max(maxset, nset[i]);
-    TRY(dalloc(c, (const float***)&c->dr.src[i], nset[i])); TRY(dalloc(c, &c->dr.pos[i], nset[i]));
+    TRY(dalloc(c, (const float***)&c->dr.src[i], nset[i]));
     TRY(dalloc(c, &c->dr.lim[i], nset[i])); TRY(dalloc(c, &c->dr.limx[i], nset[i]));
     TRY(dalloc(c, &c->dr.cs[i], nset[i] * 64));
   }
@@ -895,17 +892,17 @@ int build_buffers(fm_ctx* c) {
     // memory, so that a grouped launch over all heads sees S rows per head with one stride.
     const size_t nsp = nset[0] + nset[1] + nset[2], np = (size_t)D.hd / 2;
     maxset = std::max(maxset, nsp);
-    const float** src; int *pos, *lim, *limx; float2* cs;
-    TRY(dalloc(c, (const float***)&src, nsp)); TRY(dalloc(c, &pos, nsp)); TRY(dalloc(c, &lim, nsp)); TRY(dalloc(c, &limx, nsp));
+    const float** src; int *lim, *limx; float2* cs;
+    TRY(dalloc(c, (const float***)&src, nsp)); TRY(dalloc(c, &lim, nsp)); TRY(dalloc(c, &limx, nsp));
     TRY(dalloc(c, &cs, nsp * 64));
     const size_t first[3] = {(size_t)D.nspv + D.nspf, 0, (size_t)D.nspv};
     for (int i = 0; i < 5; i++) c->dr.rs[i] = i < 3 ? G_all : i == 3 ? D.nhfv : 2 * D.nhfc;
     for (int i = 0; i < 3; i++) {
-      c->dr.src[i] = src + first[i]; c->dr.pos[i] = pos + first[i]; c->dr.lim[i] = lim + first[i];
+      c->dr.src[i] = src + first[i]; c->dr.lim[i] = lim + first[i];
       c->dr.limx[i] = limx + first[i]; c->dr.cs[i] = cs + first[i] * np;
     }
   }
-  TRY(dalloc(c, &c->dr.alive, S)); TRY(dalloc(c, &c->dr.firev, S)); TRY(dalloc(c, &c->dr.firef, S)); TRY(dalloc(c, &c->dr.flags, 4));
+  TRY(dalloc(c, &c->dr.alive, S)); TRY(dalloc(c, &c->dr.firev, S)); TRY(dalloc(c, &c->dr.firef, S)); TRY(dalloc(c, &c->dr.flags, 2));
   TRY(dalloc(c, &c->hfv_out, nset[3] * d));
   const size_t nLM = S * (D.Dc + 2 * D.nhfc);
   // Outputs of the SP heads: one buffer [sequence][point | face | coordinate heads][d].  The output head reads its rows

@@ -18,7 +18,6 @@
 #pragma once
 #include <type_traits>
 #include "fm_device.h"
-#include "fm_kernels_basic.h"
 #include "fm_kernels_mfma.h"
 
 // element offset of (row m, column n) in a tiled buffer of KT = columns / 32

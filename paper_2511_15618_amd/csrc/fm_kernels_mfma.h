@@ -9,7 +9,6 @@
 #pragma once
 #include <type_traits>
 #include "fm_device.h"
-#include "fm_kernels_basic.h"
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x8 __attribute__((ext_vector_type(8)));

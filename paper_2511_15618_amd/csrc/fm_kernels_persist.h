@@ -84,7 +84,6 @@ struct PkArgs {
   u64* w2part;              // [d/16][RS/16][3][256]: partial tiles of the K-quarters 1..3 of the FFN down projection
   const unsigned* epoch_word;  // passes so far, counted by k_verify_setup
   u64 timeout_ticks;        // bound of every wait (100 MHz wall clock)
-  int two_phase;            // GEMM waits first watch one element per lane and only then read everything (0: the full read comes first)
   unsigned test_skew;       // test hook: added to the tag the embedding publishes, so that nothing downstream ever arrives
   unsigned* abort_word;     // [0] abort flag, [1] earliest stage that gave up, [2] claim, [3..8] expected tag, tag seen,
                             // stage, workgroup, thread, element of the first missing value
@@ -220,7 +219,6 @@ __device__ __forceinline__ bool pk_gemm_tile(const PkArgs& a, SH& sh, pk_cw_t Wt
       }
   }
   // this wave's part of the rows: element (wave*FW + f)*EF + g*(EF/4) of row r is where fragment f starts; rows past the last read 0
-  const u64* Aw = A + (long)(wave * FW) * EF;
   const agent_buf_t Ab = agent_buf(A, ((R - 1) * lda + KT * EF) * 8);
   const int mine = on ? (r * lda + (wave * FW) * EF + g * (EF / 4)) * 8 : 1 << 30;
   const u64 t0 = wall_clock64();
@@ -232,19 +230,8 @@ __device__ __forceinline__ bool pk_gemm_tile(const PkArgs& a, SH& sh, pk_cw_t Wt
   // fragments again once those show the tag: waiting costs the memory system 64 small loads per round, not 32 KiB (reading all
   // again instead, steps in us: d = 1024 1893 -> 1905, d = 512 800 -> 810; for up to four rows only: 1904, 805).
   const int fs_ = min(lane >> 3, FW - 1), hs_ = (lane >> 2) & 1, rs_ = max(R - 1 - (lane & 3), 0);
-#define PK_WATCH(AW)                                                                                          \
-  {                                                                                                           \
-    const u64* sent = (AW) + (long)rs_ * lda + fs_ * EF + hs_ * (EF / 2);                                     \
-    while (good) {                                                                                            \
-      const bool okw = (unsigned)(pk_ld(sent) >> 32) == tagA;                                                 \
-      if (__all(okw)) break;                                                                                  \
-      if ((++it & 63) == 0 && pk_expired(a, t0, stage)) { good = false; break; }                               \
-      __builtin_amdgcn_s_sleep(1);                                                                            \
-    }                                                                                                         \
-  }
-  if (a.two_phase) PK_WATCH(Aw)
+  const u64* watched = A + (long)(wave * FW) * EF + (long)rs_ * lda + fs_ * EF + hs_ * (EF / 2);
   PK_MARK(1);
-  // phase 2: the fragments
   u32x4 v[8 * NL];
   while (good) {
     agent_again();
@@ -261,7 +248,10 @@ __device__ __forceinline__ bool pk_gemm_tile(const PkArgs& a, SH& sh, pk_cw_t Wt
         for (int j = 0; j < NL; j++) diff |= (v[f * NL + j][1] ^ tagA) | (v[f * NL + j][3] ^ tagA);
     if (__all(diff == 0 || !on)) break;
     if ((++it & 63) == 0 && pk_expired(a, t0, stage)) { good = false; break; }
-    PK_WATCH(Aw)
+    while (!__all((unsigned)(pk_ld(watched) >> 32) == tagA)) {
+      if ((++it & 63) == 0 && pk_expired(a, t0, stage)) { good = false; break; }
+      __builtin_amdgcn_s_sleep(1);
+    }
   }
   PK_MARK(2);
   if (ASRC == 1) {
@@ -296,7 +286,6 @@ __device__ __forceinline__ bool pk_gemm_tile(const PkArgs& a, SH& sh, pk_cw_t Wt
       }
     }
   }
-#undef PK_WATCH
   sh.red[wave][lane] = acc;
   if (__syncthreads_or(!good)) return false;
   PK_MARK(3);

@@ -4,14 +4,13 @@
 #pragma once
 #include "fm_device.h"
 #include "fm_progress.h"
-#include "fm_kernels_basic.h"
 #include "fm_kernels_decode.h"
 
 struct InvFreq { double v[64]; };  // base^(-i/(hd/2)) for the hd/2 rotary pairs of a head, computed in double on the host
 
 struct Dims {
   int d, H, V, S, Bm, VB, FB, M;
-  int hd;                // head width d / H: 64 (both storage types), 96 or 128 (fp32 storage only)
+  int hd;                // head width d / H: 64, 96 or 128
   int capc, capv, capf;  // K/V cache slots per level (rings when a window is set)
   int maxtok;            // longest stream (positions 1 .. maxtok)
   int wc, wv, wf;        // attention window per level in its own positions, 0 = unbounded
@@ -26,7 +25,7 @@ struct Dims {
 
 struct StateDev {
   int *P, *main, *fin, *firedv, *firedf, *basec, *basev, *basef;
-  int *vlen, *vtok, *y, *acc;
+  int *vlen, *vtok, *y;
   int* hist;          // [S][maxtok + 1], hist[p] = x_p
   int* budget;        // [1]
   int* alive;         // [1] unfinished sequences; doubles as the run flag of the step
@@ -100,7 +99,6 @@ __device__ __forceinline__ void accept_seq(const StateDev& st, int s, int len, i
     a = 1;
     while (a < len && passed(a - 1)) a++;
   }
-  st.acc[s] = a;
   if (accepted_out) accepted_out[s] = a;
 }
 
@@ -240,7 +238,7 @@ __global__ void k_reset_seq(StateDev st, Dims D, int s, int bos) {
   st.P[s] = 0; st.main[s] = bos; st.fin[s] = 0;
   st.firedv[s] = -1; st.firedf[s] = -1;
   st.basec[s] = -1000000; st.basev[s] = -1; st.basef[s] = -1;
-  st.vlen[s] = 0; st.acc[s] = 0;
+  st.vlen[s] = 0;
   st.hist[(long)s * (D.maxtok + 1)] = bos;
   int alive = 0;
   for (int i = 0; i < D.S; i++) alive += st.fin[i] ? 0 : 1;
@@ -337,12 +335,11 @@ __device__ __forceinline__ int wave_inverse_cdf(int n, float u, F wf, float& tot
 struct DraftRows {
   // five row sets: 0 SP coordinate, 1 SP point, 2 SP face, 3 HF vertex, 4 HF coordinate
   const float** src[5];
-  int* pos[5];
   int* lim[5];
   int* limx[5];
   float2* cs[5];
   int *alive, *firev, *firef;   // [S]
-  int* flags;                   // [0] any alive with P > 0, [1] any point firing, [2] any face firing
+  int* flags;                   // [0] any alive with P > 0, [1] any face firing
   int rs[5];                    // rows per sequence in the tables of a set: row (sequence s, head k) = s * rs + k.  The
                                 // set's own head count, or for the three SP sets the head count of all three together
                                 // when their tables are one table (point, face, coordinate heads behind each other)
@@ -358,7 +355,6 @@ __device__ __forceinline__ void set_row(const DraftRows& R, int set, int r, cons
                                         const InvFreq& inv, int lane32, int np = 32) {
   if (lane32 == 0) {
     R.src[set][r] = src;
-    R.pos[set][r] = lim >= 0 ? pos : -1;
     R.lim[set][r] = lim;
     R.limx[set][r] = lim >= 0 ? M - 1 : -1;
   }
@@ -369,8 +365,8 @@ __device__ __forceinline__ void set_row(const DraftRows& R, int set, int r, cons
   }
 }
 
-// 32 threads per row, eight rows per workgroup, workgroups (sequence, row chunk).  The three launch flags (any sequence alive / firing at the
-// point level / at the face level) depend on the committed state only, so every workgroup could derive them; workgroup 0
+// 32 threads per row, eight rows per workgroup, workgroups (sequence, row chunk).  The two launch flags (any sequence alive / firing at the
+// face level) depend on the committed state only, so every workgroup could derive them; workgroup 0
 // does, for all sequences, and writes them.
 __global__ __launch_bounds__(256) void k_draft_setup(StateDev st, Dims D, InvFreq inv, DraftRows R, DraftBufs B) {
   const int lane32 = threadIdx.x & 31, grp = threadIdx.x >> 5;  // 8 groups of 32
@@ -385,18 +381,17 @@ __global__ __launch_bounds__(256) void k_draft_setup(StateDev st, Dims D, InvFre
     firef = alive && D.n > 0 && st.firedf[s] != f;
   };
   if (blockIdx.x == 0 && blockIdx.y == 0) {
-    __shared__ int f_any[3];
-    if (threadIdx.x < 3) f_any[threadIdx.x] = 0;
+    __shared__ int f_any[2];
+    if (threadIdx.x < 2) f_any[threadIdx.x] = 0;
     __syncthreads();
     for (int s = threadIdx.x; s < D.S; s += blockDim.x) {
       bool alive, firev, firef; int spos, v, f;
       predicates(s, alive, firev, firef, spos, v, f);
       if (alive) atomicOr(&f_any[0], 1);
-      if (firev) atomicOr(&f_any[1], 1);
-      if (firef) atomicOr(&f_any[2], 1);
+      if (firef) atomicOr(&f_any[1], 1);
     }
     __syncthreads();
-    if (threadIdx.x < 3) R.flags[threadIdx.x] = f_any[threadIdx.x];
+    if (threadIdx.x < 2) R.flags[threadIdx.x] = f_any[threadIdx.x];
   }
   {
     const int s = blockIdx.x;
