@@ -340,7 +340,7 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
   const int hh = blockIdx.x, split = blockIdx.y, s = blockIdx.z % a.S, z = blockIdx.z / a.S;
   if (z >= a.nset) {
     // Read ahead: the GEMMs behind this launch wait for cold weights, about a third of their 4 us, while a short attention leaves the
-    // memory idle.  L2 outlives a launch; each die has its own, and workgroup i runs on die i mod 8, as do the column tiles
+    // memory and compute units idle.  L2 outlives a launch; each die has its own, and workgroup i runs on die i mod 8, as do the column tiles
     // i mod 8 of a GEMM (only the speed depends on that).  The data goes to LDS and is never looked at.
     const int plane = gridDim.x * gridDim.y, base = plane * a.nset * a.S, id = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
     const int die = id & 7, rank = (id - base) >> 3, ranks = max(1, (plane * a.ahead) >> 3);
@@ -553,6 +553,7 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
         m[j] = __uint_as_float(ld_agent1(parts, (p + NQ * HD + qi) * 4));
         l[j] = __uint_as_float(ld_agent1(parts, (p + NQ * HD + NQ + qi) * 4));
       }
+      agent_again();      // all of them go out here: the compiler would move some behind the tests below, a second trip
       float Mc = M;
 #pragma unroll
       for (int j = 0; j < C; j++)
@@ -739,7 +740,9 @@ bool dec_attention(AttnArgs& a, int nset, int hd, hipStream_t st) {
     if (a.set[z].ns > a.ns_max) a.ns_max = a.set[z].ns;
   }
   a.nset = nset;
-  a.ahead = a.next[0].W ? (48 + a.H * a.ns_max - 1) / (a.H * a.ns_max) : 0;      // about 48 workgroups (32 to 128: no difference)
+  // Readers come in whole planes of H * ns_max workgroups, 48 of them or more (32 to 128: no difference): 48 to 256.  Where one workgroup
+  // that attends fills a compute unit (two tiles of 128-wide heads: 137 KB of LDS) and these fill the chip, the readers run behind them.
+  a.ahead = a.next[0].W ? (48 + a.H * a.ns_max - 1) / (a.H * a.ns_max) : 0;
   if (hd == 64) { if (QT == 1) dec_attn_go<T, 1, 64, NW>(a, nset, st); else dec_attn_go<T, 2, 64, NW>(a, nset, st); }
   else if (hd == 96) { if (QT == 1) dec_attn_go<T, 1, 96, NW>(a, nset, st); else dec_attn_go<T, 2, 96, NW>(a, nset, st); }
   else { if (QT == 1) dec_attn_go<T, 1, 128, NW>(a, nset, st); else dec_attn_go<T, 2, 128, NW>(a, nset, st); }

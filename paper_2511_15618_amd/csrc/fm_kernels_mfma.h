@@ -37,8 +37,8 @@ __device__ __forceinline__ void st_agent(float* p, float v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // The loads come as buffer loads (byte offset `o` into `bytes` from a uniform base, 0 beyond them): the compiler knows them, so it keeps many in
-// flight where atomic loads would go one by one, and places every wait itself.  It may also take two of them for one: a loop that
-// polls has a compiler barrier (agent_again) in front of them.
+// flight where atomic loads would go one by one, and places every wait itself.  It may also take two of them for one, or move them: a loop
+// that polls has a compiler barrier (agent_again) in front of them, and so has a batch that is to leave together behind it.
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef __amdgpu_buffer_rsrc_t agent_buf_t;
 __device__ __forceinline__ agent_buf_t agent_buf(const void* base, int bytes) { return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00027000); }
