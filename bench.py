@@ -447,7 +447,7 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f16 (bf16-valued weights held as half, fp32 accumulate)",
+        "dtype": "f32" if cfg.dtype == "f32" else "f16 (bf16-valued weights held as half, fp32 accumulate)",
         "data": "synthetic",
         "config": {"workload": f"configs[{args.config}] {cfg.name}: d={cfg.d_model}, {cfg.n_layers} blocks, batch {cfg.batch}, "
                                f"{faces} faces ({9 * faces} tokens), block {cfg.block_max}, draft counts Dc={cfg.draft_coord} m={cfg.draft_point} n={cfg.draft_face}"
