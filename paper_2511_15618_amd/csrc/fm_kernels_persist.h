@@ -98,7 +98,17 @@ struct PkShared {
   float ssq[4][16];
   float lo[4][16 * QT][65];
   float lm[4][16 * QT], ll[4][16 * QT];
+  int bad;                  // raised by a wave whose wait gave up
 };
+
+// Barrier at which all waves learn whether one of them has given up.  (__syncthreads_or is three barriers and two trips to LDS, in
+// every unit: steps of 755 us at d = 512 and 1812 us at d = 1024 become 730 and 1754.)
+template <class SH>
+__device__ __forceinline__ bool pk_sync(SH& sh, bool good) {
+  if (!good) sh.bad = 1;
+  __syncthreads();
+  return sh.bad == 0;
+}
 
 __device__ __forceinline__ u64 pk_ld(const u64* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void pk_st(u64* p, unsigned payload, unsigned tag) {
@@ -288,7 +298,7 @@ __device__ __forceinline__ bool pk_gemm_tile(const PkArgs& a, SH& sh, pk_cw_t Wt
     }
   }
   sh.red[wave][lane] = acc;
-  if (__syncthreads_or(!good)) return false;
+  if (!pk_sync(sh, good)) return false;
   PK_MARK(3);
   if (wave == 0) {
     result = sh.red[0][lane] + sh.red[1][lane] + sh.red[2][lane] + sh.red[3][lane];
@@ -622,7 +632,7 @@ __device__ __forceinline__ bool pk_attn_unit(const PkArgs& a, SH& sh, const u64*
 #pragma unroll
       for (int i = 0; i < 4; i++) sh.lo[wave][t * 16 + ql][dt * 16 + g * 4 + i] = o[t][dt][i];
   }
-  if (__syncthreads_or(!ok)) return false;
+  if (!pk_sync(sh, ok)) return false;
   for (int e = threadIdx.x; e < QT * 16 * 64; e += 256) {
     const int qi = e >> 6, dim = e & 63;
     const float M = fmaxf(fmaxf(sh.lm[0][qi], sh.lm[1][qi]), fmaxf(sh.lm[2][qi], sh.lm[3][qi]));
@@ -651,7 +661,7 @@ __device__ __forceinline__ bool pk_attn_unit(const PkArgs& a, SH& sh, const u64*
 // (rg: the row group, R: its rows; the split count comes from the largest limit of the whole level, as in the units
 // that wrote the partial results)
 template <int QT>
-__device__ __forceinline__ bool pk_merge_unit(const PkArgs& a, int maxlim, int R, int rg, int capb, int nsplit_cfg,
+__device__ __forceinline__ bool pk_merge_unit(const PkArgs& a, PkShared<QT>& sh, int maxlim, int R, int rg, int capb, int nsplit_cfg,
                                               int hh, int dq, const u64* parts, u64* att, unsigned tag, int stage) {
   const int d = a.D.d;
   const int nsplit = __builtin_amdgcn_readfirstlane(pk_active(min((maxlim + 32) >> 5, capb), nsplit_cfg));
@@ -702,7 +712,7 @@ __device__ __forceinline__ bool pk_merge_unit(const PkArgs& a, int maxlim, int R
       }
     }
   }
-  if (__syncthreads_or(!ok)) return false;
+  if (!pk_sync(sh, ok)) return false;
   return true;
 }
 
@@ -723,6 +733,8 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
   const unsigned epoch = __builtin_amdgcn_readfirstlane((int)*a.epoch_word);
   if (*a.run_flag == 0) return;
   __shared__ PkShared<QT> sh;
+  if (threadIdx.x == 0) sh.bad = 0;
+  __syncthreads();
   const int RS = QT * 16, RH = QT * 8;     // rows of an exchange region (= a.RS), and half of it: the row count of a half-pair region in units of d
   const int d = a.D.d, H = a.D.H, ff = a.ff;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -819,7 +831,7 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
         PK_NEXT(H * ns);
         PK_MINE(4 * H * RG) {
           const int v = u / RG, rg = u % RG;
-          if (!pk_merge_unit<QT>(a, maxS[lev], min(16, R - rg * 16), rg, capb, ns, v >> 2, v & 3, a.partS, att_l, tag, stage)) return;
+          if (!pk_merge_unit<QT>(a, sh, maxS[lev], min(16, R - rg * 16), rg, capb, ns, v >> 2, v & 3, a.partS, att_l, tag, stage)) return;
         }
         PK_NEXT(4 * H * RG);
       }
@@ -835,7 +847,7 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
         if (wave == 0 && okr)
           pk_epi_residual(a, c, nt, old, hB_l + (long)row0 * d, xB_l + row0 * hd, tag, Rl, prow, L.tap ? a.tap[lev] : nullptr, nullptr,
                           lev == 0 ? 32 : lev == 1 ? 16 : 8);
-        if (__syncthreads_or(!okr)) return;
+        if (!pk_sync(sh, okr)) return;
       }
       PK_NEXT(d / 16 * RG);
       // ---- cross-attention query (norm2 on the fly)
@@ -858,7 +870,7 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
         PK_NEXT(H * ns);
         PK_MINE(4 * H * RG) {
           const int v = u / RG, rg = u % RG;
-          if (!pk_merge_unit<QT>(a, maxX[lev], min(16, R - rg * 16), rg, a.capbM, ns, v >> 2, v & 3, a.partX, att2_l, tag, stage)) return;
+          if (!pk_merge_unit<QT>(a, sh, maxX[lev], min(16, R - rg * 16), rg, a.capbM, ns, v >> 2, v & 3, a.partX, att2_l, tag, stage)) return;
         }
         PK_NEXT(4 * H * RG);
       }
@@ -872,7 +884,7 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
         if (wave == 0) okr = pk_res_prefetch(a, nt, hB_l + (long)row0 * d, tag, Rl, pos + row0, old, prow, stage);
         if (!pk_gemm_tile<0>(a, sh, L.co + (long)nt * (d / 32) * 512, d / 32, att2_l + row0 * hd, tag, nullptr, Rl, c, stage)) return;
         if (wave == 0 && okr) pk_epi_residual(a, c, nt, old, hC_l + (long)row0 * d, xC_l + row0 * hd, tag, Rl, prow, nullptr, nullptr, 8);
-        if (__syncthreads_or(!okr)) return;
+        if (!pk_sync(sh, okr)) return;
       }
       PK_NEXT(d / 16 * RG);
       // ---- FFN up (norm3 on the fly, GELU)
@@ -928,7 +940,7 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
             }
           }
         }
-        if (__syncthreads_or(!okr)) return;
+        if (!pk_sync(sh, okr)) return;
       }
       PK_NEXT(4 * (d / 16) * RG);
     }
@@ -964,7 +976,7 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
           }
           if (i < d) pk_st(a.pool + (long)st * 8 * d + (long)u * (d >> 1) + (i >> 1), pk_pack(s0 / 3.0f, s1 / 3.0f), tagn);
         }
-        if (__syncthreads_or(!ok)) return;
+        if (!pk_sync(sh, ok)) return;
       }
       PK_NEXT(Rc_);
       PK_MINE(d / 16) {
@@ -1014,7 +1026,7 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
           const float w = __shfl_xor(v, 1, 64);
           if ((i & 1) == 0) pk_st(a.xA + (long)ln * RH * d + (long)u * (d >> 1) + (i >> 1), pk_pack(v, w), tagn);
         }
-        if (__syncthreads_or(!ok)) return;
+        if (!pk_sync(sh, ok)) return;
       }
       PK_NEXT(Rf_);
     }
