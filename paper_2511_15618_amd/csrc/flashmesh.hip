@@ -1170,7 +1170,7 @@ int fm_correct(fm_ctx* c, int32_t* block_tok, const int32_t* block_len, int32_t*
   if (!c->weights_loaded) return fail(c, FM_ESTATE, "weights not loaded");
   if (c->correct_hist <= 0) return fail(c, FM_ESTATE, "correct stage is off: call fm_set_correct before the fm_draft whose block is corrected");
   if (!block_tok || !block_len) return fail(c, FM_EINVAL, "null block buffer");
-  hipLaunchKernelGGL(k_correct, dim3((c->D.S + 63) / 64), dim3(64), 0, c->stream, c->st, c->D, c->lab_v, c->lab_f, c->correct_hist,
+  hipLaunchKernelGGL(k_correct, dim3(c->D.S), dim3(64), 0, c->stream, c->st, c->D, c->lab_v, c->lab_f, c->correct_hist,
                      block_tok, block_len, labels_out);
   HIPCHK(c, hipGetLastError());
   return FM_OK;

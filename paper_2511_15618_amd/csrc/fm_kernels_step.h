@@ -302,12 +302,30 @@ __device__ __forceinline__ int wave_inverse_cdf(int n, float u, F wf, float& tot
   const int lane = threadIdx.x & 63;
   const int chunk = (n + 63) / 64;
   const int i0 = min(lane * chunk, n), i1 = min(i0 + chunk, n);
+  // The weights of a lane are asked for together and stay in registers (up to 1280 weights in all): the second walk ends at the pick, and a
+  // load in each of its rounds is a trip of its own.  Sums in index order either way.
+  constexpr int C = 20;
+  const bool kept = chunk <= C;
+  float w[C];
+  if (kept) {
+#pragma unroll
+    for (int k = 0; k < C; k++) w[k] = k < chunk ? wf(min(i0 + k, n - 1)) : 0.f;
+  }
   float local = 0.f;
   int last = -1;
-  for (int i = i0; i < i1; i++) {
-    const float w = wf(i);
-    local += w;
-    if (w > 0.f) last = i;
+  if (kept) {
+#pragma unroll
+    for (int k = 0; k < C; k++)
+      if (i0 + k < i1) {
+        local += w[k];
+        if (w[k] > 0.f) last = i0 + k;
+      }
+  } else {
+    for (int i = i0; i < i1; i++) {
+      const float x = wf(i);
+      local += x;
+      if (x > 0.f) last = i;
+    }
   }
   const float incl = wave_scan(local), excl = incl - local;
   total = __shfl(incl, 63, 64);
@@ -315,9 +333,18 @@ __device__ __forceinline__ int wave_inverse_cdf(int n, float u, F wf, float& tot
   int pick = 0x7fffffff;
   if (i0 < i1 && incl > thr) {
     float run = excl;
-    for (int i = i0; i < i1; i++) {
-      run += wf(i);
-      if (run > thr) { pick = i; break; }
+    if (kept) {
+#pragma unroll
+      for (int k = 0; k < C; k++)
+        if (i0 + k < i1) {
+          run += w[k];
+          if (run > thr && pick == 0x7fffffff) pick = i0 + k;
+        }
+    } else {
+      for (int i = i0; i < i1; i++) {
+        run += wf(i);
+        if (run > thr) { pick = i; break; }
+      }
     }
     if (pick == 0x7fffffff) pick = last >= 0 ? last : i1 - 1;      // rounding between the chunk's sum and its walk
   }
@@ -727,32 +754,40 @@ __global__ __launch_bounds__(64) void k_label_rows(Dims D, DraftRows R, const fl
 #define FM_LABEL_NEW 1
 #define FM_LABEL_INTRA 2
 
-// One thread per sequence (a block holds at most 27 tokens, i.e. 9 points): labels of the block's points from the
+// One wave per sequence (a block holds at most 27 tokens, i.e. 9 points): labels of the block's points from the
 // stored rows, the historical / intra-batch moves in ascending vertex order, then the z-y-x re-sort of the faces
 // that consist of draft tokens only.  Integer work on bin coordinates; the main token is never touched.
 // Vertex u owns x_{3u+1..3u+3}; block token i is x_{P+i}.
-__global__ void k_correct(StateDev st, Dims D, const float* __restrict__ lab_v, const float* __restrict__ lab_f,
-                          int hist_vertices, int* __restrict__ block_tok, const int* __restrict__ block_len,
-                          int* __restrict__ labels_out) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= D.S) return;
+// What bounds it is trips to memory, one behind the other: everything a block needs is read in two (state, then tokens, labels and the
+// first 64 historical vertices, one per lane), the moves work on LDS and registers.  (One thread per sequence that walked the history for
+// every point: 71 us a step at 64 vertices.)
+__global__ __launch_bounds__(64) void k_correct(StateDev st, Dims D, const float* __restrict__ lab_v, const float* __restrict__ lab_f,
+                                                int hist_vertices, int* __restrict__ block_tok, const int* __restrict__ block_len,
+                                                int* __restrict__ labels_out) {
+  __shared__ int stok[36];          // tokens of the block; a point past its end is never looked at
+  __shared__ int slab[9], spt[9];
+  const int s = blockIdx.x, lane = threadIdx.x;
   int* tok = block_tok + (long)s * D.Bm;
   int* lout = labels_out ? labels_out + (long)s * D.Bm : nullptr;
-  if (lout)
-    for (int i = 0; i < D.Bm; i++) lout[i] = -1;
-  if (st.fin[s]) return;
-  const int P = st.P[s];
-  int len = block_len[s];
-  len = min(len, D.Bm);
-  if (len < 4) return;
+  const int fin = st.fin[s], P = st.P[s], basev = st.basev[s], basef = st.basef[s];
+  const int len = min(block_len[s], D.Bm);
+  if (lout && lane < D.Bm) lout[lane] = -1;
+  if (fin || len < 4) return;
   const int u0 = (P + 2) / 3, u1 = (P + len - 4) / 3;
   if (u1 < u0) return;
   const int np = u1 - u0 + 1;                    // <= 9
-  int lab[9];
-  bool pt[9];
-  const int basev = st.basev[s], basef = st.basef[s];
-  for (int i = 0; i < np; i++) {
-    const int u = u0 + i;
+  const int* known = st.hist + (long)s * (D.maxtok + 1);     // x_0 .. x_P (the pending main token is x_P)
+  const int nkv = P / 3, h0 = max(0, nkv - hist_vertices);
+  auto vertex = [&](int h, int (&k)[3]) {
+    k[0] = known[3 * h + 1]; k[1] = known[3 * h + 2]; k[2] = known[3 * h + 3];
+  };
+  int hv[3] = {0, 0, 0};
+  const bool hon = h0 + lane < nkv;
+  if (hon) vertex(h0 + lane, hv);
+  if (lane < len) stok[lane] = tok[lane];
+  const int off = 3 * u0 + 1 - P;                // block index of the first point's z
+  if (lane < np) {
+    const int u = u0 + lane;
     float a[3] = {0.f, 0.f, 0.f};
     int cnt = 0;
     const int kv = basev >= 0 ? u - basev / 3 : 0;
@@ -776,60 +811,86 @@ __global__ void k_correct(StateDev st, Dims D, const float* __restrict__ lab_v, 
       if (m1 > best) { best = m1; l = 1; }
       if (m2 > best) { best = m2; l = 2; }
     }
-    lab[i] = l;
-    if (lout) lout[i] = l;
-    const int* c = tok + 3 * u + 1 - P;
-    pt[i] = c[0] >= 0 && c[0] < D.nbins && c[1] >= 0 && c[1] < D.nbins && c[2] >= 0 && c[2] < D.nbins;
+    slab[lane] = l;
+    if (lout) lout[lane] = l;
   }
-  const int* known = st.hist + (long)s * (D.maxtok + 1);     // x_0 .. x_P (the pending main token is x_P)
-  const int nkv = P / 3;
-  const int h0 = max(0, nkv - hist_vertices);
+  __syncthreads();
+  if (lane < np) {
+    const int* c = stok + off + 3 * lane;
+    spt[lane] = c[0] >= 0 && c[0] < D.nbins && c[1] >= 0 && c[1] < D.nbins && c[2] >= 0 && c[2] < D.nbins;
+  }
+  __syncthreads();
+  // Nearest candidate: the smallest distance, among equals the lowest index; -1 = none.  (A candidate at distance 0 is the point
+  // itself: moving there changes nothing.)
+  auto nearest = [&](long dd, int idx) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      const long od = __shfl_xor(dd, o, 64);
+      const int oi = __shfl_xor(idx, o, 64);
+      if (oi >= 0 && (idx < 0 || od < dd || (od == dd && oi < idx))) { dd = od; idx = oi; }
+    }
+    return idx;
+  };
+  auto dist = [](const int* c, const int* k) {
+    const long dz = c[0] - k[0], dy = c[1] - k[1], dx = c[2] - k[2];
+    return dz * dz + dy * dy + dx * dx;
+  };
   for (int i = 0; i < np; i++) {
-    if (!pt[i]) continue;
-    int* c = tok + 3 * (u0 + i) + 1 - P;
-    if (lab[i] == FM_LABEL_HIST) {
-      long best = -1;
+    if (!spt[i]) continue;
+    int* c = stok + off + 3 * i;
+    if (slab[i] == FM_LABEL_HIST) {
+      long best = 0;
       int bh = -1;
-      bool same = false;
-      for (int h = h0; h < nkv; h++) {
-        const int* k = known + 3 * h + 1;
-        if (!(k[0] < D.nbins && k[1] < D.nbins && k[2] < D.nbins)) continue;
-        const long dz = c[0] - k[0], dy = c[1] - k[1], dx = c[2] - k[2];
-        const long dd = dz * dz + dy * dy + dx * dx;
-        if (dd == 0) { same = true; break; }
+      auto offer = [&](const int* k, int h) {
+        if (!(k[0] < D.nbins && k[1] < D.nbins && k[2] < D.nbins)) return;
+        const long dd = dist(c, k);
         if (bh < 0 || dd < best) { best = dd; bh = h; }
+      };
+      if (hon) offer(hv, h0 + lane);
+      for (int h = h0 + 64 + lane; h < nkv; h += 64) {
+        int k[3];
+        vertex(h, k);
+        offer(k, h);
       }
-      if (!same && bh >= 0) { c[0] = known[3 * bh + 1]; c[1] = known[3 * bh + 2]; c[2] = known[3 * bh + 3]; }
-    } else if (lab[i] == FM_LABEL_INTRA) {
-      long best = -1;
+      bh = nearest(best, bh);
+      if (bh >= 0) {
+        int k[3] = {__shfl(hv[0], bh - h0, 64), __shfl(hv[1], bh - h0, 64), __shfl(hv[2], bh - h0, 64)};
+        if (bh - h0 >= 64) vertex(bh, k);
+        __syncthreads();
+        if (lane < 3) c[lane] = k[lane];
+      }
+    } else if (slab[i] == FM_LABEL_INTRA) {
+      long best = 0;
       int bw = -1;
       bool same = false;
-      for (int w = 0; w < np; w++) {
-        if (w == i || !pt[w]) continue;
-        const int* k = tok + 3 * (u0 + w) + 1 - P;
-        const long dz = c[0] - k[0], dy = c[1] - k[1], dx = c[2] - k[2];
-        const long dd = dz * dz + dy * dy + dx * dx;
-        if (dd == 0) { same = true; break; }
-        if (lab[w] == FM_LABEL_NEW && (u0 + w) / 3 != (u0 + i) / 3 && (bw < 0 || dd < best)) { best = dd; bw = w; }
+      if (lane < np && lane != i && spt[lane]) {
+        best = dist(c, stok + off + 3 * lane);
+        same = best == 0;
+        if (slab[lane] == FM_LABEL_NEW && (u0 + lane) / 3 != (u0 + i) / 3) bw = lane;
       }
-      if (!same && bw >= 0) {
-        const int* k = tok + 3 * (u0 + bw) + 1 - P;
-        c[0] = k[0]; c[1] = k[1]; c[2] = k[2];
-      }
+      same = __any(same);
+      bw = nearest(best, bw);
+      __syncthreads();
+      if (!same && bw >= 0 && lane < 3) c[lane] = stok[off + 3 * bw + lane];
+    }
+    __syncthreads();
+  }
+  // faces whose nine tokens are all drafts of this block: vertices in ascending (z, y, x) order, one lane per face
+  const int f = (u0 + 2) / 3 + lane;
+  if (f < (u1 + 1) / 3) {
+    const int i0 = 3 * f - u0;
+    if (spt[i0] && spt[i0 + 1] && spt[i0 + 2]) {
+      int* c = stok + off + 3 * i0;
+      for (int pass = 0; pass < 2; pass++)
+        for (int j = 0; j < 2 - pass; j++) {
+          int* a = c + 3 * j;
+          int* b = a + 3;
+          const bool gt = a[0] != b[0] ? a[0] > b[0] : a[1] != b[1] ? a[1] > b[1] : a[2] > b[2];
+          if (gt)
+            for (int k = 0; k < 3; k++) { const int t = a[k]; a[k] = b[k]; b[k] = t; }
+        }
     }
   }
-  // faces whose nine tokens are all drafts of this block: vertices in ascending (z, y, x) order
-  for (int f = (u0 + 2) / 3; f < (u1 + 1) / 3; f++) {
-    const int i0 = 3 * f - u0;
-    if (!(pt[i0] && pt[i0 + 1] && pt[i0 + 2])) continue;
-    int* c = tok + 3 * (3 * f) + 1 - P;
-    for (int pass = 0; pass < 2; pass++)
-      for (int j = 0; j < 2 - pass; j++) {
-        int* a = c + 3 * j;
-        int* b = a + 3;
-        const bool gt = a[0] != b[0] ? a[0] > b[0] : a[1] != b[1] ? a[1] > b[1] : a[2] > b[2];
-        if (gt)
-          for (int k = 0; k < 3; k++) { const int t = a[k]; a[k] = b[k]; b[k] = t; }
-      }
-  }
+  __syncthreads();
+  if (lane >= off && lane < off + 3 * np) tok[lane] = stok[lane];
 }

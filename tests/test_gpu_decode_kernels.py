@@ -64,6 +64,27 @@ def test_sampled_choice_over_wide_rows(name):
     print(rep, flush=True)
 
 
+@pytest.mark.parametrize("bins", [1280, 1281])
+def test_sampled_choice_at_the_limit_of_the_kept_weights(bins):
+    """Draws whose weights just fit a wave's registers (20 a lane), and one more."""
+    from parity_harness import lockstep
+    cfg = CASES[-1].replace(name="bins%d" % bins, n_bins=bins)
+    print("case", cfg.name, flush=True)
+    rep, _, _ = lockstep(cfg, cfg.faces, TOL[cfg.dtype], max_steps=8, sampling=(0.8, 5))
+    print(rep, flush=True)
+
+
+@pytest.mark.parametrize("hist", [64, 65, 100])
+def test_correct_stage_over_more_vertices_than_a_wave(hist):
+    """Historical vertices in one round of the wave, and in a second one; the longest blocks (9 points)."""
+    from parity_harness import lockstep
+    cfg = _cfg("hist%d" % hist, 128, 2, 24, "f32", 1, 36, 2, 9, 27, bins=64)
+    print("case", cfg.name, flush=True)
+    rep, streams, _ = lockstep(cfg, cfg.faces, TOL[cfg.dtype], correct_hist=hist)
+    print(rep, flush=True)
+    assert len(streams[0]) == 9 * cfg.faces and rep.corrected_blocks > 0
+
+
 @pytest.mark.parametrize("d,heads,mem", [(128, 2, 1), (128, 2, 33), (192, 2, 255), (320, 5, 257), (384, 3, 511), (640, 5, 769)])
 def test_condition_kv_at_tile_edges(d, heads, mem):
     """Memories and widths that are no whole 256-row tiles, every element against float64.  The bound: the memory rounded to half
