@@ -429,8 +429,7 @@ int verify_impl(fm_ctx* c, const int32_t* block_tok, const int32_t* block_len, f
   if (c->persist) {
     // the whole backbone forward in one launch (see fm_kernels_persist.h)
     c->pk.logits = lg;
-    if (c->pk.RS == 32) hipLaunchKernelGGL(k_verify_persist<2>, dim3(PK_NWG), dim3(256), c->pk_lds, c->stream, c->pk);
-    else hipLaunchKernelGGL(k_verify_persist<1>, dim3(PK_NWG), dim3(256), c->pk_lds, c->stream, c->pk);
+    hipLaunchKernelGGL(pk_kernel(c->pk), dim3(PK_NWG), dim3(256), c->pk_lds, c->stream, c->pk);
   } else {
     forward<T>(c, lg);
   }
@@ -835,8 +834,7 @@ int build_persist(fm_ctx* c) {
   // all 256 workgroups must be resident at once: they wait for each other's results
   int dev = 0, cus = 0, per_cu = 0;
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      (a.RS == 32 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_verify_persist<2>, 256, c->pk_lds)
-                  : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_verify_persist<1>, 256, c->pk_lds)) != hipSuccess ||
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, pk_kernel(a), 256, c->pk_lds) != hipSuccess ||
       (long)cus * per_cu < PK_NWG) {
     (void)hipGetLastError();
     c->persist = false;   // fall back to the per-launch path

@@ -50,6 +50,11 @@ struct PkLayer {
   int stack;      // 0 cpre, 1 vpre, 2 face, 3 vpost, 4 cpost
 };
 
+// Width of the model: FWT fragments of 32 per wave in a GEMM over d, i.e. d = 128 FWT, known to the compiler for the usual widths
+// (the hidden width is then 4 d), read from the arguments for the others (FWT = 0).
+struct PkArgs;
+template <int FWT> __device__ __forceinline__ int pk_d(const PkArgs& a);
+
 struct PkArgs {
   const PkLayer* layers;
   int n_layers;
@@ -91,6 +96,8 @@ struct PkArgs {
   int prof_stage;           // stage whose inner phases are timed into prof[600..]
   u64* prof;                // optional [1 + stages]: earliest start, latest completion per stage (wall clock ticks)
 };
+
+template <int FWT> __device__ __forceinline__ int pk_d(const PkArgs& a) { return FWT ? FWT * 128 : a.D.d; }
 
 template <int QT>
 struct PkShared {
@@ -174,13 +181,15 @@ __device__ __forceinline__ bool pk_fetch(unsigned (&out)[N], int n, bool active,
 // A level transition must not publish anything before the stack below it has finished with the shared
 // exchange buffers, even when its own rows are inactive or only need data of earlier passes: it first
 // waits for row 0 of the stack output from EVERY tile (a tile stores only after its last read).
+template <int FWT>
 __device__ __forceinline__ bool pk_wait_stack(const PkArgs& a, const u64* hT, unsigned tag, int stage, int rows);
 
 #define PK_TAG(l) (epoch * 64u + (unsigned)(l) + 1u)      // epoch: local of the kernel
 
+template <int FWT>
 __device__ __forceinline__ bool pk_wait_stack(const PkArgs& a, const u64* hT, unsigned tag, int stage, int rows) {
   unsigned s4[4];
-  const int d = a.D.d;
+  const int d = pk_d<FWT>(a);
   const int n = (d - (int)threadIdx.x + 255) / 256;     // columns threadIdx.x, +256, ... below d (d <= 1024)
   bool ok = pk_fetch<4>(s4, n, n > 0, tag, [&](int i) { return hT + threadIdx.x + 256 * i; }, a, stage);
   // a second row group is written by units of its own: their first row (16) as well
@@ -200,7 +209,7 @@ __device__ __forceinline__ bool pk_wait_stack(const PkArgs& a, const u64* hT, un
 // tagged half pairs, i.e. two 16-byte agent-scope loads.  No LDS staging, no barrier before the multiplication;
 // the tags are checked per lane and the whole set is re-read until complete.
 // ------------------------------------------------------------------------------------------
-template <int ASRC, class SH>
+template <int FWT, int ASRC, class SH>
 __device__ __forceinline__ bool pk_gemm_tile(const PkArgs& a, SH& sh, pk_cw_t Wt, int KT, const u64* A,
                                              unsigned tagA, pk_cf_t gain, int R, f32x4& result, int stage,
                                              int lda = 0) {
@@ -209,19 +218,20 @@ __device__ __forceinline__ bool pk_gemm_tile(const PkArgs& a, SH& sh, pk_cw_t Wt
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int r = lane & 15, g = lane >> 4;
   const bool on = r < R;
-  const int FW = KT >> 2;                  // fragments per wave (host guarantees KT % 4 == 0, KT <= 32)
-  const int K = KT * 32;
+  constexpr int NF = FWT ? FWT : 8;
+  const int FW = FWT ? FWT : KT >> 2;      // fragments per wave (host guarantees KT % 4 == 0, KT <= 32)
+  const int K = FW * 128;
   if (lda == 0) lda = K >> 1;
   f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
   // weights and gains go out before the wait for the activations: they depend on nothing
-  f16x8 wf[8];
+  f16x8 wf[NF];
 #pragma unroll
-  for (int f = 0; f < 8; f++)
+  for (int f = 0; f < NF; f++)
     if (f < FW) wf[f] = *(const PK_GLOBAL f16x8*)(Wt + ((long)(wave * FW + f) * 64 + lane) * 8);
-  f32x4 gl[ASRC == 1 ? 16 : 1];
+  f32x4 gl[ASRC == 1 ? 2 * NF : 1];
   if (ASRC == 1) {
 #pragma unroll
-    for (int f = 0; f < 8; f++)
+    for (int f = 0; f < NF; f++)
       if (f < FW) {
         const pk_cf_t gp = gain + (wave * FW + f) * 32 + g * 8;
         gl[2 * f] = *(const PK_GLOBAL f32x4*)gp;
@@ -243,17 +253,17 @@ __device__ __forceinline__ bool pk_gemm_tile(const PkArgs& a, SH& sh, pk_cw_t Wt
   const int fs_ = min(lane >> 3, FW - 1), hs_ = (lane >> 2) & 1, rs_ = max(R - 1 - (lane & 3), 0);
   const u64* watched = A + (long)(wave * FW) * EF + (long)rs_ * lda + fs_ * EF + hs_ * (EF / 2);
   PK_MARK(1);
-  u32x4 v[8 * NL];
+  u32x4 v[NF * NL];
   while (good) {
     agent_again();
 #pragma unroll
-    for (int f = 0; f < 8; f++)
+    for (int f = 0; f < NF; f++)
       if (f < FW)
 #pragma unroll
         for (int j = 0; j < NL; j++) v[f * NL + j] = ld_agent4(Ab, mine + (f * EF + 2 * j) * 8);
     unsigned diff = 0;
 #pragma unroll
-    for (int f = 0; f < 8; f++)
+    for (int f = 0; f < NF; f++)
       if (f < FW)
 #pragma unroll
         for (int j = 0; j < NL; j++) diff |= (v[f * NL + j][1] ^ tagA) | (v[f * NL + j][3] ^ tagA);
@@ -271,7 +281,7 @@ __device__ __forceinline__ bool pk_gemm_tile(const PkArgs& a, SH& sh, pk_cw_t Wt
     // squares: this lane's 8*FW values, then the four k-groups of the wave; the four waves meet in LDS below.
     float ss = 0.f;
 #pragma unroll
-    for (int f = 0; f < 8; f++) {
+    for (int f = 0; f < NF; f++) {
       if (f < FW) {
         const u32x4 pk = {v[2 * f][0], v[2 * f][2], v[2 * f + 1][0], v[2 * f + 1][2]};
         const f16x8 xh = __builtin_bit_cast(f16x8, pk);
@@ -290,7 +300,7 @@ __device__ __forceinline__ bool pk_gemm_tile(const PkArgs& a, SH& sh, pk_cw_t Wt
     if (g == 0) sh.ssq[wave][r] = ss;
   } else {
 #pragma unroll
-    for (int f = 0; f < 8; f++) {
+    for (int f = 0; f < NF; f++) {
       if (f < FW) {
         const u32x4 pk = {v[2 * f][0], v[2 * f][2], v[2 * f + 1][0], v[2 * f + 1][2]};
         acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, pk), wf[f], acc, 0, 0, 0);
@@ -317,20 +327,22 @@ __device__ __forceinline__ bool pk_gemm_tile(const PkArgs& a, SH& sh, pk_cw_t Wt
 // residual epilogue (wave 0): out[r][n] = old[r][n] + c; optional copies into position-indexed rings
 // The residual operand of a tile (complete long before the tile's GEMM input is) is fetched by wave 0 at the
 // start of the unit, so that its latency hides behind the wait for the GEMM input.
+template <int FWT>
 __device__ __forceinline__ bool pk_res_prefetch(const PkArgs& a, int nt, const u64* hold, unsigned tag_old, int R,
                                                 const int* pos, unsigned (&old)[4], int (&prow)[4], int stage) {
   const int lane = threadIdx.x & 63, g = lane >> 4, n = nt * 16 + (lane & 15);
-  const int d = a.D.d;
+  const int d = pk_d<FWT>(a);
 #pragma unroll
   for (int i = 0; i < 4; i++) prow[i] = pos[min(g * 4 + i, R - 1)];    // positions of the lane's rows, for the ring copies
   return pk_fetch<4>(old, 4, true, tag_old, [&](int i) { return hold + (long)min(g * 4 + i, R - 1) * d + n; }, a, stage);
 }
 
+template <int FWT>
 __device__ __forceinline__ void pk_epi_residual(const PkArgs& a, const f32x4& c, int nt, const unsigned (&old)[4],
                                                 u64* hout, u64* xout, unsigned tag_out, int R, const int (&prow)[4],
                                                 float* tap_ring, float* out_ring, int ring_size) {
   const int lane = threadIdx.x & 63, g = lane >> 4, n = nt * 16 + (lane & 15);
-  const int d = a.D.d;
+  const int d = pk_d<FWT>(a);
 #pragma unroll
   for (int i = 0; i < 4; i++) {
     const int r = g * 4 + i;
@@ -382,11 +394,11 @@ __device__ __forceinline__ void pk_qkv_prefetch(int nt, int d, int R, const int*
     pre.t[i] = part < 2 ? cs[(long)rr * 32 + qd * 8 + (col & 7)] : float2{1.f, 0.f};
   }
 }
-template <int QT>
+template <int QT, int FWT>
 __device__ __forceinline__ void pk_epi_qkv(const PkArgs& a, const PkLayer& L, const f32x4& c, int nt, unsigned tag, int R,
                                            const PkQkvPre& pre, int capb, int row0) {
   const int lane = threadIdx.x & 63, g = lane >> 4, col = lane & 15;
-  const int d = a.D.d;
+  const int d = pk_d<FWT>(a);
   const int part = (nt * 16) / d, cp = (nt * 16) % d;
   const int hh = cp >> 6, qd = (cp & 63) >> 4;
 #pragma unroll
@@ -432,13 +444,13 @@ __device__ __forceinline__ int pk_active(int nblk, int ns) { return max(1, min(n
 // exchange buffers, older keys from the cache.  lim[t]: last key the lane's row of tile t may see (-1: unused slot).
 // Partial results: tile t of (head, split) at part + t * PK_PART.
 // ------------------------------------------------------------------------------------------
-template <int QT, class SH>
+template <int QT, int FWT, class SH>
 __device__ __forceinline__ bool pk_attn_unit(const PkArgs& a, SH& sh, const u64* qbuf, const int (&lim)[QT], int maxlim, int R,
                                              pk_cw_t Kc, pk_cw_t Vc, int capb, int nsplit_cfg, int hh, int split,
                                              bool overlay, int P0, u64* part, unsigned tag, int stage, int window) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int g = lane >> 4, ql = lane & 15;
-  const int d = a.D.d;
+  const int d = pk_d<FWT>(a);
   const float kScale = 0.125f * 1.4426950408889634f;
   // With a window the cache is a ring of capb blocks (a multiple of four): position p lives in slot p mod (32 capb);
   // seen from the newest visible position, slot j holds lapbase + j if that is <= maxlim, else the position one
@@ -660,10 +672,10 @@ __device__ __forceinline__ bool pk_attn_unit(const PkArgs& a, SH& sh, const u64*
 // (parts that meet in LDS behind a barrier instead: fewer loads, but 0.9 us longer).  Lanes and groups are added in a fixed order.
 // (rg: the row group, R: its rows; the split count comes from the largest limit of the whole level, as in the units
 // that wrote the partial results)
-template <int QT>
+template <int QT, int FWT>
 __device__ __forceinline__ bool pk_merge_unit(const PkArgs& a, PkShared<QT>& sh, int maxlim, int R, int rg, int capb, int nsplit_cfg,
                                               int hh, int dq, const u64* parts, u64* att, unsigned tag, int stage) {
-  const int d = a.D.d;
+  const int d = pk_d<FWT>(a);
   const int nsplit = __builtin_amdgcn_readfirstlane(pk_active(min((maxlim + 32) >> 5, capb), nsplit_cfg));
   const long rec = (long)QT * PK_PART;                 // one (head, split) record: a tile per row group
   const u64* base = parts + (long)hh * PK_MAXSPLIT * rec + (long)rg * PK_PART;
@@ -728,7 +740,7 @@ __device__ __forceinline__ bool pk_merge_unit(const PkArgs& a, PkShared<QT>& sh,
     stage++;                                                                                        \
   } while (0)
 
-template <int QT>
+template <int QT, int FWT>
 __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
   const unsigned epoch = __builtin_amdgcn_readfirstlane((int)*a.epoch_word);
   if (*a.run_flag == 0) return;
@@ -736,7 +748,7 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
   if (threadIdx.x == 0) sh.bad = 0;
   __syncthreads();
   const int RS = QT * 16, RH = QT * 8;     // rows of an exchange region (= a.RS), and half of it: the row count of a half-pair region in units of d
-  const int d = a.D.d, H = a.D.H, ff = a.ff;
+  const int d = pk_d<FWT>(a), H = d / 64, ff = FWT ? 4 * d : a.ff;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   unsigned rr = 0;     // round-robin origin of the current stage (same in every workgroup)
   int stage = 0;
@@ -813,8 +825,8 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
         f32x4 c;
         PkQkvPre pre;
         if (wave == 0) pk_qkv_prefetch(nt, d, Rl, pos + row0, a.cs[lev] + (long)row0 * 32, pre);
-        if (!pk_gemm_tile<1>(a, sh, L.wqkv + (long)nt * (d / 32) * 512, d / 32, xA_l + row0 * hd, tag, L.g1, Rl, c, stage)) return;
-        if (wave == 0) pk_epi_qkv<QT>(a, L, c, nt, tag, Rl, pre, capb, row0);
+        if (!pk_gemm_tile<FWT, 1>(a, sh, L.wqkv + (long)nt * (d / 32) * 512, d / 32, xA_l + row0 * hd, tag, L.g1, Rl, c, stage)) return;
+        if (wave == 0) pk_epi_qkv<QT, FWT>(a, L, c, nt, tag, Rl, pre, capb, row0);
         __syncthreads();
       }
       PK_NEXT(3 * d / 16 * RG);
@@ -825,13 +837,13 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
         PK_MINE(H * ns) {
           // split-major: the splits that hold keys come first and spread over all workgroups
           const int hh = u % H, sp = u / H;
-          if (!pk_attn_unit<QT>(a, sh, a.q, limS[lev], maxS[lev], R, L.Kc, L.Vc, capb, ns, hh, sp, true, P0,
+          if (!pk_attn_unit<QT, FWT>(a, sh, a.q, limS[lev], maxS[lev], R, L.Kc, L.Vc, capb, ns, hh, sp, true, P0,
                                 a.partS + ((long)hh * PK_MAXSPLIT + sp) * (RS >> 4) * PK_PART, tag, stage, a.win[lev])) return;
         }
         PK_NEXT(H * ns);
         PK_MINE(4 * H * RG) {
           const int v = u / RG, rg = u % RG;
-          if (!pk_merge_unit<QT>(a, sh, maxS[lev], min(16, R - rg * 16), rg, capb, ns, v >> 2, v & 3, a.partS, att_l, tag, stage)) return;
+          if (!pk_merge_unit<QT, FWT>(a, sh, maxS[lev], min(16, R - rg * 16), rg, capb, ns, v >> 2, v & 3, a.partS, att_l, tag, stage)) return;
         }
         PK_NEXT(4 * H * RG);
       }
@@ -842,10 +854,10 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
         unsigned old[4];
         int prow[4];
         bool okr = true;
-        if (wave == 0) okr = pk_res_prefetch(a, nt, hA_l + (long)row0 * d, tag, Rl, pos + row0, old, prow, stage);
-        if (!pk_gemm_tile<0>(a, sh, L.wo + (long)nt * (d / 32) * 512, d / 32, att_l + row0 * hd, tag, nullptr, Rl, c, stage)) return;
+        if (wave == 0) okr = pk_res_prefetch<FWT>(a, nt, hA_l + (long)row0 * d, tag, Rl, pos + row0, old, prow, stage);
+        if (!pk_gemm_tile<FWT, 0>(a, sh, L.wo + (long)nt * (d / 32) * 512, d / 32, att_l + row0 * hd, tag, nullptr, Rl, c, stage)) return;
         if (wave == 0 && okr)
-          pk_epi_residual(a, c, nt, old, hB_l + (long)row0 * d, xB_l + row0 * hd, tag, Rl, prow, L.tap ? a.tap[lev] : nullptr, nullptr,
+          pk_epi_residual<FWT>(a, c, nt, old, hB_l + (long)row0 * d, xB_l + row0 * hd, tag, Rl, prow, L.tap ? a.tap[lev] : nullptr, nullptr,
                           lev == 0 ? 32 : lev == 1 ? 16 : 8);
         if (!pk_sync(sh, okr)) return;
       }
@@ -854,7 +866,7 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
       PK_MINE(d / 16 * RG) {
         const int nt = u / RG, row0 = (u % RG) * 16, Rl = min(16, R - row0);
         f32x4 c;
-        if (!pk_gemm_tile<1>(a, sh, L.cq + (long)nt * (d / 32) * 512, d / 32, xB_l + row0 * hd, tag, L.g2, Rl, c, stage)) return;
+        if (!pk_gemm_tile<FWT, 1>(a, sh, L.cq + (long)nt * (d / 32) * 512, d / 32, xB_l + row0 * hd, tag, L.g2, Rl, c, stage)) return;
         if (wave == 0) pk_epi_half(c, nt, a.q2 + row0 * hd, d >> 1, tag, Rl, false);
         __syncthreads();
       }
@@ -864,13 +876,13 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
         const int ns = a.nsplitM;
         PK_MINE(H * ns) {
           const int hh = u / ns, sp = u % ns;
-          if (!pk_attn_unit<QT>(a, sh, a.q2, limX[lev], maxX[lev], R, L.Km, L.Vm, a.capbM, ns, hh, sp, false, 0,
+          if (!pk_attn_unit<QT, FWT>(a, sh, a.q2, limX[lev], maxX[lev], R, L.Km, L.Vm, a.capbM, ns, hh, sp, false, 0,
                                 a.partX + ((long)hh * PK_MAXSPLIT + sp) * (RS >> 4) * PK_PART, tag, stage, 0)) return;
         }
         PK_NEXT(H * ns);
         PK_MINE(4 * H * RG) {
           const int v = u / RG, rg = u % RG;
-          if (!pk_merge_unit<QT>(a, sh, maxX[lev], min(16, R - rg * 16), rg, a.capbM, ns, v >> 2, v & 3, a.partX, att2_l, tag, stage)) return;
+          if (!pk_merge_unit<QT, FWT>(a, sh, maxX[lev], min(16, R - rg * 16), rg, a.capbM, ns, v >> 2, v & 3, a.partX, att2_l, tag, stage)) return;
         }
         PK_NEXT(4 * H * RG);
       }
@@ -881,9 +893,9 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
         unsigned old[4];
         int prow[4];
         bool okr = true;
-        if (wave == 0) okr = pk_res_prefetch(a, nt, hB_l + (long)row0 * d, tag, Rl, pos + row0, old, prow, stage);
-        if (!pk_gemm_tile<0>(a, sh, L.co + (long)nt * (d / 32) * 512, d / 32, att2_l + row0 * hd, tag, nullptr, Rl, c, stage)) return;
-        if (wave == 0 && okr) pk_epi_residual(a, c, nt, old, hC_l + (long)row0 * d, xC_l + row0 * hd, tag, Rl, prow, nullptr, nullptr, 8);
+        if (wave == 0) okr = pk_res_prefetch<FWT>(a, nt, hB_l + (long)row0 * d, tag, Rl, pos + row0, old, prow, stage);
+        if (!pk_gemm_tile<FWT, 0>(a, sh, L.co + (long)nt * (d / 32) * 512, d / 32, att2_l + row0 * hd, tag, nullptr, Rl, c, stage)) return;
+        if (wave == 0 && okr) pk_epi_residual<FWT>(a, c, nt, old, hC_l + (long)row0 * d, xC_l + row0 * hd, tag, Rl, prow, nullptr, nullptr, 8);
         if (!pk_sync(sh, okr)) return;
       }
       PK_NEXT(d / 16 * RG);
@@ -891,7 +903,7 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
       PK_MINE(ff / 16 * RG) {
         const int nt = u / RG, row0 = (u % RG) * 16, Rl = min(16, R - row0);
         f32x4 c;
-        if (!pk_gemm_tile<1>(a, sh, L.w1 + (long)nt * (d / 32) * 512, d / 32, xC_l + row0 * hd, tag, L.g3, Rl, c, stage)) return;
+        if (!pk_gemm_tile<FWT, 1>(a, sh, L.w1 + (long)nt * (d / 32) * 512, d / 32, xC_l + row0 * hd, tag, L.g3, Rl, c, stage)) return;
         if (wave == 0) pk_epi_half(c, nt, mid_l + (long)row0 * (ff >> 1), ff >> 1, tag, Rl, true);
         __syncthreads();
       }
@@ -908,8 +920,8 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
         unsigned old[4];
         int prow[4];
         bool okr = true;
-        if (wave == 0 && kq == 0) okr = pk_res_prefetch(a, nt, hC_l + (long)row0 * d, tag, Rl, pos + row0, old, prow, stage);
-        if (!pk_gemm_tile<0>(a, sh, L.w2 + ((long)nt * (ff / 32) + (long)kq * KTq) * 512, KTq,
+        if (wave == 0 && kq == 0) okr = pk_res_prefetch<FWT>(a, nt, hC_l + (long)row0 * d, tag, Rl, pos + row0, old, prow, stage);
+        if (!pk_gemm_tile<FWT, 0>(a, sh, L.w2 + ((long)nt * (ff / 32) + (long)kq * KTq) * 512, KTq,
                              mid_l + (long)row0 * (ff >> 1) + (long)kq * (ff / 8), tag, nullptr, Rl, c, stage, ff >> 1)) return;
         if (wave == 0) {
           const int lane = threadIdx.x & 63;
@@ -935,7 +947,7 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
                 ring = st == 0 ? a.ring_hc : st == 1 ? a.ring_hv : st == 2 ? a.ring_yf : a.ring_yv;
                 rs = st == 0 ? 32 : st == 2 ? 8 : 16;
               }
-              pk_epi_residual(a, c, nt, old, dst + (long)row0 * d, xdst ? xdst + row0 * hd : nullptr, PK_TAG(l + 1), Rl, prow,
+              pk_epi_residual<FWT>(a, c, nt, old, dst + (long)row0 * d, xdst ? xdst + row0 * hd : nullptr, PK_TAG(l + 1), Rl, prow,
                               nullptr, ring, rs);
             }
           }
@@ -957,7 +969,7 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
       for (int r = 0; r < Rf_; r++) if (a.pos[fl][r] >= 0) F0 = min(F0, a.pos[fl][r]);
       PK_MINE(Rc_) {
         const int j = a.pos[cl][u];
-        bool ok = pk_wait_stack(a, a.hT[st], tagn, stage, QT == 1 ? 16 : Rf_);
+        bool ok = pk_wait_stack<FWT>(a, a.hT[st], tagn, stage, QT == 1 ? 16 : Rf_);
         for (int i0 = 0; i0 < d; i0 += 512) {
           const int i = i0 + 2 * threadIdx.x;       // two adjacent columns per thread
           float s0 = 0.f, s1 = 0.f;
@@ -982,7 +994,7 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
       PK_MINE(d / 16) {
         f32x4 c;
         pk_cw_t W = (pk_cw_t)(st == 0 ? a.short_cv : a.short_vf) + (long)u * (d / 32) * 512;
-        if (!pk_gemm_tile<0>(a, sh, W, d / 32, a.pool + (long)st * 8 * d, tagn, nullptr, Rc_, c, stage)) return;
+        if (!pk_gemm_tile<FWT, 0>(a, sh, W, d / 32, a.pool + (long)st * 8 * d, tagn, nullptr, Rc_, c, stage)) return;
         if (wave == 0) {
           const int lane = threadIdx.x & 63, g = lane >> 4, n = u * 16 + (lane & 15);
 #pragma unroll
@@ -1009,7 +1021,7 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
         const int p = a.pos[fl][u];
         int slot = -1;
         if (p >= 0) for (int r = 0; r < Rc_; r++) if (a.pos[cl][r] == p / 3) slot = r;
-        bool ok = pk_wait_stack(a, a.hT[st], tagn, stage, QT == 1 ? 16 : Rc_);
+        bool ok = pk_wait_stack<FWT>(a, a.hT[st], tagn, stage, QT == 1 ? 16 : Rc_);
         for (int i = threadIdx.x; i < d; i += 256) {
           unsigned r0[1], r1[1];
           ok = pk_fetch<1>(r0, 1, true, tag_skip, [&](int) { return skip + (long)u * d + i; }, a, stage) && ok;
@@ -1038,7 +1050,7 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
     PK_MINE(NT * RG) {
       const int nt = u / RG, row0 = (u % RG) * 16, Rl = min(16, R - row0);
       f32x4 c;
-      if (!pk_gemm_tile<1>(a, sh, (pk_cw_t)a.lm + (long)nt * (d / 32) * 512, d / 32, a.xA + (long)l * RH * d + (long)row0 * (d >> 1),
+      if (!pk_gemm_tile<FWT, 1>(a, sh, (pk_cw_t)a.lm + (long)nt * (d / 32) * 512, d / 32, a.xA + (long)l * RH * d + (long)row0 * (d >> 1),
                            PK_TAG(l), (pk_cf_t)a.gf, Rl, c, stage)) return;
       if (wave == 0) {
         const int lane = threadIdx.x & 63, g = lane >> 4, n = nt * 16 + (lane & 15);
@@ -1049,4 +1061,19 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
       __syncthreads();
     }
   }
+}
+
+// The instance of a context: two row groups or one, and the width where it is one that the compiler knows.
+typedef void (*pk_kernel_t)(PkArgs);
+inline pk_kernel_t pk_kernel(const PkArgs& a) {
+  const int d = a.ff == 4 * a.D.d ? a.D.d : 0;
+#define PK_PICK(FWT) return a.RS == 32 ? k_verify_persist<2, FWT> : k_verify_persist<1, FWT>
+  switch (d) {
+    case 256: PK_PICK(2);
+    case 512: PK_PICK(4);
+    case 768: PK_PICK(6);
+    case 1024: PK_PICK(8);
+    default: PK_PICK(0);
+  }
+#undef PK_PICK
 }
