@@ -810,6 +810,7 @@ int build_persist(fm_ctx* c) {
   TRY(dalloc(c, &a.hA, (nl + 1) * RS * d)); TRY(dalloc(c, &a.hB, nl * RS * d)); TRY(dalloc(c, &a.hC, nl * RS * d));
   for (int i = 0; i < 4; i++) TRY(dalloc(c, &a.hT[i], RS * d));
   TRY(dalloc(c, &a.xA, (nl + 1) * RH * d)); TRY(dalloc(c, &a.xB, nl * RH * d)); TRY(dalloc(c, &a.xC, nl * RH * d));
+  TRY(dalloc(c, &a.sA, (nl + 1) * RS * d / 16)); TRY(dalloc(c, &a.sB, nl * RS * d / 16)); TRY(dalloc(c, &a.sC, nl * RS * d / 16));
   TRY(dalloc(c, &a.q, RH * d)); TRY(dalloc(c, &a.att, nl * RH * d)); TRY(dalloc(c, &a.q2, RH * d));
   TRY(dalloc(c, &a.att2, nl * RH * d));
   TRY(dalloc(c, &a.pool, 2 * 8 * d)); TRY(dalloc(c, &a.mid, nl * RH * c->ff));

@@ -31,6 +31,36 @@ template <> struct Op<float> {
   }
 };
 
+// Values of neighbouring lanes without the trip to LDS that a shuffle is (ds_bpermute, about 100 cycles in a serial chain).
+// Rows are the 16 lanes of equal lane / 16.
+template <int CTRL> __device__ __forceinline__ float lane_dpp(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float lane_xor1(float v) { return lane_dpp<0xB1>(v); }        // quad_perm [1, 0, 3, 2]
+__device__ __forceinline__ float lane_xor8(float v) { return lane_dpp<0x128>(v); }       // row_ror 8
+__device__ __forceinline__ float row16_sum(float v) {      // sum over a row, in each of its lanes
+  v += lane_dpp<0xB1>(v);
+  v += lane_dpp<0x4E>(v);        // quad_perm [2, 3, 0, 1]
+  v += lane_dpp<0x141>(v);       // row_half_mirror
+  v += lane_dpp<0x140>(v);       // row_mirror
+  return v;
+}
+// sum and maximum over the four rows, lane by lane, in each of them (the same results as with shuffles by 16 and 32)
+__device__ __forceinline__ float rows_sum(float v) {
+  const unsigned u = __float_as_uint(v);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const float w = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(w), __float_as_uint(w), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+__device__ __forceinline__ float rows_max(float v) {
+  const unsigned u = __float_as_uint(v);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const float w = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(w), __float_as_uint(w), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
 // Values that workgroups of one launch hand to each other (attention parts) are written and read at agent scope: the stores are
 // written through to where all dies see them, the loads bypass the die's own L2.
 __device__ __forceinline__ void st_agent(float* p, float v) {
@@ -43,6 +73,8 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef __amdgpu_buffer_rsrc_t agent_buf_t;
 __device__ __forceinline__ agent_buf_t agent_buf(const void* base, int bytes) { return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00027000); }
 __device__ __forceinline__ u32x4 ld_agent4(agent_buf_t b, int o) { return __builtin_amdgcn_raw_buffer_load_b128(b, o, 0, 16); }      // 16: sc1
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ u32x2 ld_agent2(agent_buf_t b, int o) { return __builtin_amdgcn_raw_buffer_load_b64(b, o, 0, 16); }
 __device__ __forceinline__ unsigned ld_agent1(agent_buf_t b, int o) { return __builtin_amdgcn_raw_buffer_load_b32(b, o, 0, 16); }
 __device__ __forceinline__ void agent_again() { asm volatile("" ::: "memory"); }
 

@@ -28,7 +28,7 @@ typedef unsigned long long u64;
 
 #define PK_NWG 256
 #define PK_MAXSPLIT 16                    // parts that a merge unit takes in one round of loads
-#define PK_PART (16 * 64 + 32)            // per (head, split): 16x64 unnormalised O, 16 running maxima, 16 sums
+#define PK_PART (16 * 64 + 32)            // per (head, split): 16x64 unnormalised O, 16 pairs of running maximum and sum
 #define PK_TIMEOUT_TICKS 20000000ull      // default bound of every wait: 200 ms of the 100 MHz wall clock
 
 // A pointer read from a table in memory is generic to the compiler, and loads through it become FLAT instructions,
@@ -79,7 +79,8 @@ struct PkArgs {
   // exchange buffers (u64 = payload | tag << 32)
   u64 *hA, *hB, *hC;        // [layers + 1][RS][d]: one region per layer, written once per launch
   u64* hT[4];               // outputs of cpre, vpre, face, vpost  [RS][d]
-  u64 *xA, *xB, *xC;        // [layers (+ 1)][RS][d/2]: the same activations as hA, hB, hC rounded to half pairs, for the GEMMs
+  u64 *xA, *xB, *xC;        // [layers (+ 1)][RS][d/2]: half(row of hA, hB, hC times the gain of the norm that reads it), pairs
+  u64 *sA, *sB, *sC;        // [layers (+ 1)][RS][d/16]: sums of squares of 16 columns of those rows
   u64 *q, *q2;              // [RS][d/2] rotated queries of the self- / cross-attention (half pairs)
   u64 *att, *att2;          // [layers][RS][d/2] attention outputs
   u64* pool;                // [2][16][d/2] pooled groups before the two shortening projections (coarse rows: at most 9)
@@ -99,12 +100,14 @@ struct PkArgs {
 
 template <int FWT> __device__ __forceinline__ int pk_d(const PkArgs& a) { return FWT ? FWT * 128 : a.D.d; }
 
+// Exchanges between the waves of a workgroup.  Two sets, used by the GEMM and attention units in turn: a unit writes its set, passes its one
+// barrier and reads; who writes the same set two units later has passed the barrier between, so all have read.
 template <int QT>
 struct PkShared {
-  f32x4 red[4][64];
-  float ssq[4][16];
-  float lo[4][16 * QT][65];
-  float lm[4][16 * QT], ll[4][16 * QT];
+  float red[2][4][4][64];
+  float ssq[2][4][16];
+  __align__(16) float lo[2][4][16 * QT][68];
+  float lm[2][4][16 * QT], ll[2][4][16 * QT];
   int bad;                  // raised by a wave whose wait gave up
 };
 
@@ -201,18 +204,20 @@ __device__ __forceinline__ bool pk_wait_stack(const PkArgs& a, const u64* hT, un
 #define PK_MARK(k) do { if (a.prof && stage == a.prof_stage && threadIdx.x == 0) atomicMax(a.prof + 600 + (k), (u64)wall_clock64()); } while (0)
 
 // ------------------------------------------------------------------------------------------
-// GEMM tile: C[16 rows x 16 cols] = A[16 x K] * W_tile^T, four waves split K (K <= 1024), result in wave 0.
-// A is a half-pair exchange buffer [16][K/2].  ASRC 1: the rows are RMS-normalised (gain g) on the fly; they are
-// the half-rounded copy that the producers of the fp32 residual stream write next to it.
+// GEMM tile: C[16 rows x 16 cols] = A[16 x K] * W_tile^T, four waves split K (K <= 1024).  Behind the one barrier of the unit every wave
+// owns a quarter of the result: wave w of lane (g, col) has row g*4 + w, column col in `result`.
+// A is a half-pair exchange buffer [16][K/2].  NORM: its rows are half(x * gain), written so by the producers of the residual stream
+// together with the sums of squares of every 16 columns, sq[row][K/16]; the row factor 1/rms goes onto the result.
+// (One wave doing the whole epilogue, and gain and sums computed here: 1.3 to 2 us from the arrival of the operands to the barrier, and
+// 1 to 3.3 us of epilogue, against 0.5 to 0.8 and 0.4 to 0.9; steps 707 -> 644 us at d = 512, 1692 -> 1526 at d = 1024, with the merge below.)
 // Every wave takes the MFMA A-fragments of its K-quarter straight from the exchange buffer: lane (r, g) of
 // fragment f needs the 8 consecutive values k0 = f*32 + g*8 .. +8 of row r, which are 32 contiguous bytes of
 // tagged half pairs, i.e. two 16-byte agent-scope loads.  No LDS staging, no barrier before the multiplication;
 // the tags are checked per lane and the whole set is re-read until complete.
 // ------------------------------------------------------------------------------------------
-template <int FWT, int ASRC, class SH>
-__device__ __forceinline__ bool pk_gemm_tile(const PkArgs& a, SH& sh, pk_cw_t Wt, int KT, const u64* A,
-                                             unsigned tagA, pk_cf_t gain, int R, f32x4& result, int stage,
-                                             int lda = 0) {
+template <int FWT, bool NORM, class SH>
+__device__ __forceinline__ bool pk_gemm_tile(const PkArgs& a, SH& sh, int& par, pk_cw_t Wt, int KT, const u64* A,
+                                             unsigned tagA, const u64* sq, int R, float& result, int stage, int lda = 0) {
   constexpr int NL = 2;       // 16-byte loads per fragment and lane
   constexpr int EF = 16;      // tagged elements (half pairs) per fragment row
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -222,26 +227,23 @@ __device__ __forceinline__ bool pk_gemm_tile(const PkArgs& a, SH& sh, pk_cw_t Wt
   const int FW = FWT ? FWT : KT >> 2;      // fragments per wave (host guarantees KT % 4 == 0, KT <= 32)
   const int K = FW * 128;
   if (lda == 0) lda = K >> 1;
-  f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-  // weights and gains go out before the wait for the activations: they depend on nothing
+  par ^= 1;
+  f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+  // weights go out before the wait for the activations: they depend on nothing
   f16x8 wf[NF];
 #pragma unroll
   for (int f = 0; f < NF; f++)
     if (f < FW) wf[f] = *(const PK_GLOBAL f16x8*)(Wt + ((long)(wave * FW + f) * 64 + lane) * 8);
-  f32x4 gl[ASRC == 1 ? 2 * NF : 1];
-  if (ASRC == 1) {
-#pragma unroll
-    for (int f = 0; f < NF; f++)
-      if (f < FW) {
-        const pk_cf_t gp = gain + (wave * FW + f) * 32 + g * 8;
-        gl[2 * f] = *(const PK_GLOBAL f32x4*)gp;
-        gl[2 * f + 1] = *(const PK_GLOBAL f32x4*)(gp + 4);
-      }
-  }
   // this wave's part of the rows: element (wave*FW + f)*EF + g*(EF/4) of row r is where fragment f starts; rows past the last lie outside the
   // buffer and read 0 (a branch around every load instead: step of d = 1024 1810 -> 1907 us, d = 512 761 -> 805)
   const agent_buf_t Ab = agent_buf(A, ((R - 1) * lda + KT * EF) * 8);
   const int mine = on ? (r * lda + (wave * FW) * EF + g * (EF / 4)) * 8 : 1 << 30;
+  // sums of squares of the columns of this K-quarter: pair p of 16-column sums belongs to fragment p, lane (r, g) takes p = g and g + 4
+  const agent_buf_t Sb = agent_buf(NORM ? sq : A, NORM ? R * FW * 8 * 8 : 0);
+  const bool son[2] = {on && g < FW, on && g + 4 < FW};
+  int so[2];
+#pragma unroll
+  for (int j = 0; j < 2; j++) so[j] = son[j] ? ((r * 4 + wave) * FW + g + 4 * j) * 16 : 1 << 30;
   const u64 t0 = wall_clock64();
   int it = 0;
   bool good = true;
@@ -253,7 +255,7 @@ __device__ __forceinline__ bool pk_gemm_tile(const PkArgs& a, SH& sh, pk_cw_t Wt
   const int fs_ = min(lane >> 3, FW - 1), hs_ = (lane >> 2) & 1, rs_ = max(R - 1 - (lane & 3), 0);
   const u64* watched = A + (long)(wave * FW) * EF + (long)rs_ * lda + fs_ * EF + hs_ * (EF / 2);
   PK_MARK(1);
-  u32x4 v[NF * NL];
+  u32x4 v[NF * NL], sv[2];
   while (good) {
     agent_again();
 #pragma unroll
@@ -261,12 +263,20 @@ __device__ __forceinline__ bool pk_gemm_tile(const PkArgs& a, SH& sh, pk_cw_t Wt
       if (f < FW)
 #pragma unroll
         for (int j = 0; j < NL; j++) v[f * NL + j] = ld_agent4(Ab, mine + (f * EF + 2 * j) * 8);
+    if (NORM) {
+      sv[0] = ld_agent4(Sb, so[0]);
+      if (NF > 4) sv[1] = ld_agent4(Sb, so[1]);
+    }
     unsigned diff = 0;
 #pragma unroll
     for (int f = 0; f < NF; f++)
       if (f < FW)
 #pragma unroll
         for (int j = 0; j < NL; j++) diff |= (v[f * NL + j][1] ^ tagA) | (v[f * NL + j][3] ^ tagA);
+    if (NORM) {
+      if (son[0]) diff |= (sv[0][1] ^ tagA) | (sv[0][3] ^ tagA);
+      if (NF > 4 && son[1]) diff |= (sv[1][1] ^ tagA) | (sv[1][3] ^ tagA);
+    }
     if (__all(diff == 0 || !on)) break;
     if ((++it & 63) == 0 && pk_expired(a, t0, stage)) { good = false; break; }
     while (!__all((unsigned)(pk_ld(watched) >> 32) == tagA)) {
@@ -275,161 +285,111 @@ __device__ __forceinline__ bool pk_gemm_tile(const PkArgs& a, SH& sh, pk_cw_t Wt
     }
   }
   PK_MARK(2);
-  if (ASRC == 1) {
-    // RMSNorm without a barrier in front of the multiplication: the MFMA runs on half(x * gain) and the per-row
-    // factor 1/rms, a scalar per output row, is applied to the accumulated tile afterwards.  Row sums of
-    // squares: this lane's 8*FW values, then the four k-groups of the wave; the four waves meet in LDS below.
-    float ss = 0.f;
 #pragma unroll
-    for (int f = 0; f < NF; f++) {
-      if (f < FW) {
-        const u32x4 pk = {v[2 * f][0], v[2 * f][2], v[2 * f + 1][0], v[2 * f + 1][2]};
-        const f16x8 xh = __builtin_bit_cast(f16x8, pk);
-        f16x8 av;
-#pragma unroll
-        for (int j = 0; j < 8; j++) {
-          const float x = (float)xh[j];
-          ss += x * x;
-          av[j] = (f16_t)(x * gl[2 * f + (j >> 2)][j & 3]);
-        }
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(av, wf[f], acc, 0, 0, 0);
-      }
-    }
-    ss += __shfl_xor(ss, 16, 64);
-    ss += __shfl_xor(ss, 32, 64);
-    if (g == 0) sh.ssq[wave][r] = ss;
-  } else {
-#pragma unroll
-    for (int f = 0; f < NF; f++) {
-      if (f < FW) {
-        const u32x4 pk = {v[2 * f][0], v[2 * f][2], v[2 * f + 1][0], v[2 * f + 1][2]};
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, pk), wf[f], acc, 0, 0, 0);
-      }
+  for (int f = 0; f < NF; f++) {
+    if (f < FW) {
+      const u32x4 pk = {v[2 * f][0], v[2 * f][2], v[2 * f + 1][0], v[2 * f + 1][2]};
+      acc[f & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, pk), wf[f], acc[f & 1], 0, 0, 0);
     }
   }
-  sh.red[wave][lane] = acc;
+  if (NORM) {       // what lies outside the buffer has read 0
+    float ss = __uint_as_float(sv[0][0]) + __uint_as_float(sv[0][2]);
+    if (NF > 4) ss += __uint_as_float(sv[1][0]) + __uint_as_float(sv[1][2]);
+    ss = rows_sum(ss);
+    if (g == 0) sh.ssq[par][wave][r] = ss;
+  }
+  acc[0] += acc[1];
+#pragma unroll
+  for (int i = 0; i < 4; i++) sh.red[par][wave][i][lane] = acc[0][i];
   if (!pk_sync(sh, good)) return false;
   PK_MARK(3);
-  if (wave == 0) {
-    result = sh.red[0][lane] + sh.red[1][lane] + sh.red[2][lane] + sh.red[3][lane];
-    if (ASRC == 1) {
-#pragma unroll
-      for (int i = 0; i < 4; i++) {      // result[i] belongs to row g*4 + i
-        const int row = g * 4 + i;
-        const float tot = sh.ssq[0][row] + sh.ssq[1][row] + sh.ssq[2][row] + sh.ssq[3][row];
-        result[i] *= 1.0f / sqrtf(tot / (float)K + a.eps);
-      }
-    }
+  result = sh.red[par][0][wave][lane] + sh.red[par][1][wave][lane] + sh.red[par][2][wave][lane] + sh.red[par][3][wave][lane];
+  if (NORM) {
+    const int row = g * 4 + wave;
+    const float tot = sh.ssq[par][0][row] + sh.ssq[par][1][row] + sh.ssq[par][2][row] + sh.ssq[par][3][row];
+    result *= 1.0f / sqrtf(tot / (float)K + a.eps);
   }
   return true;
 }
 
-// residual epilogue (wave 0): out[r][n] = old[r][n] + c; optional copies into position-indexed rings
-// The residual operand of a tile (complete long before the tile's GEMM input is) is fetched by wave 0 at the
-// start of the unit, so that its latency hides behind the wait for the GEMM input.
-template <int FWT>
-__device__ __forceinline__ bool pk_res_prefetch(const PkArgs& a, int nt, const u64* hold, unsigned tag_old, int R,
-                                                const int* pos, unsigned (&old)[4], int (&prow)[4], int stage) {
-  const int lane = threadIdx.x & 63, g = lane >> 4, n = nt * 16 + (lane & 15);
-  const int d = pk_d<FWT>(a);
-#pragma unroll
-  for (int i = 0; i < 4; i++) prow[i] = pos[min(g * 4 + i, R - 1)];    // positions of the lane's rows, for the ring copies
-  return pk_fetch<4>(old, 4, true, tag_old, [&](int i) { return hold + (long)min(g * 4 + i, R - 1) * d + n; }, a, stage);
-}
+// Epilogues: a thread has row g*4 + wave (wave, lane as above) and column n = nt*16 + lane%16 of the tile.
 
-template <int FWT>
-__device__ __forceinline__ void pk_epi_residual(const PkArgs& a, const f32x4& c, int nt, const unsigned (&old)[4],
-                                                u64* hout, u64* xout, unsigned tag_out, int R, const int (&prow)[4],
-                                                float* tap_ring, float* out_ring, int ring_size) {
-  const int lane = threadIdx.x & 63, g = lane >> 4, n = nt * 16 + (lane & 15);
-  const int d = pk_d<FWT>(a);
-#pragma unroll
-  for (int i = 0; i < 4; i++) {
-    const int r = g * 4 + i;
-    if (r < R) {
-      const float ho = __uint_as_float(old[i]);
-      const float v = ho + c[i];
-      pk_stf(hout + (long)r * d + n, v, tag_out);
-      if (xout) {        // half-pair copy for the GEMM that normalises this row next (r < R holds for the lane pair alike)
-        const float w = __shfl_xor(v, 1, 64);
-        if ((lane & 1) == 0) pk_st(xout + (long)r * (d >> 1) + (n >> 1), pk_pack(v, w), tag_out);
-      }
-      const int p = prow[i];
-      if (p >= 0) {
-        if (tap_ring) tap_ring[(long)(p & (ring_size - 1)) * d + n] = ho;
-        if (out_ring) out_ring[(long)(p & (ring_size - 1)) * d + n] = v;
-      }
-    }
+// One value of a row of the residual stream: the value, half(value * gain of the norm that reads it) and, per 16 columns, the sum of squares.
+// x null: no norm reads this row.
+__device__ __forceinline__ void pk_put_row(float v, bool on, int row, int n, int d, u64* h, u64* x, u64* sq, float gain, unsigned tag) {
+  const float xg = v * gain, w = lane_xor1(xg), ss = row16_sum(v * v);
+  if (!on) return;
+  if (x) {
+    if ((n & 1) == 0) pk_st(x + (long)row * (d >> 1) + (n >> 1), pk_pack(xg, w), tag);
+    if ((n & 15) == 0) pk_stf(sq + (long)row * (d >> 4) + (n >> 4), ss, tag);
   }
+  pk_stf(h + (long)row * d + n, v, tag);
 }
 
-// half-pair epilogue (wave 0): dst[r][n/2] = (c[n], c[n+1]) as halves, optional GELU
-__device__ __forceinline__ void pk_epi_half(const f32x4& c, int nt, u64* dst, int ld2, unsigned tag, int R, bool gelu) {
-  const int lane = threadIdx.x & 63, g = lane >> 4, n = nt * 16 + (lane & 15);
-#pragma unroll
-  for (int i = 0; i < 4; i++) {
-    const float v = gelu ? gelu_tanh_f(c[i]) : c[i];
-    const float w = __shfl_xor(v, 1, 64);
-    const int r = g * 4 + i;
-    if ((lane & 1) == 0 && r < R) {
-      pk_st(dst + (long)r * ld2 + (n >> 1), pk_pack(v, w), tag);
-    }
-  }
+// The residual operand of a tile (complete long before the tile's GEMM input is) is requested at the start of the unit and looked at behind
+// the multiplication; only then, if it was not there yet, it is waited for.
+struct PkOld { u32x2 v; int p; float gain; };
+template <int FWT>
+__device__ __forceinline__ void pk_res_request(const PkArgs& a, int n, const u64* hold, int R, const int* pos, pk_cf_t gain, PkOld& o) {
+  const int d = pk_d<FWT>(a), row = min(((threadIdx.x & 63) >> 4) * 4 + (int)(threadIdx.x >> 6), R - 1);
+  o.v = ld_agent2(agent_buf(hold, R * d * 8), (row * d + n) * 8);
+  o.p = pos[row];
+  o.gain = gain ? gain[n] : 0.f;
+}
+template <int FWT>
+__device__ __forceinline__ bool pk_res_take(const PkArgs& a, int n, const u64* hold, unsigned tag, int R, const PkOld& o, float& old, int stage) {
+  const int d = pk_d<FWT>(a), row = min(((threadIdx.x & 63) >> 4) * 4 + (int)(threadIdx.x >> 6), R - 1);
+  unsigned raw[1] = {o.v[0]};
+  bool ok = true;
+  if (!__all(o.v[1] == tag)) ok = pk_fetch<1>(raw, 1, true, tag, [&](int) { return hold + (long)row * d + n; }, a, stage);
+  old = __uint_as_float(raw[0]);
+  return ok;
 }
 
-// QKV epilogue (wave 0).  Tiles of the q and k parts hold 8 rotary pairs: columns 0..7 = dims qd*8.., columns
+// dst[row][n/2] = (c[n], c[n+1]) as halves
+__device__ __forceinline__ void pk_put_half(float v, bool on, int row, int n, u64* dst, int ld2, unsigned tag) {
+  const float w = lane_xor1(v);
+  if (on && (n & 1) == 0) pk_st(dst + (long)row * ld2 + (n >> 1), pk_pack(v, w), tag);
+}
+
+// QKV epilogue.  Tiles of the q and k parts hold 8 rotary pairs: columns 0..7 = dims qd*8.., columns
 // 8..15 = the same dims + 32.  q -> exchange buffer; k, v -> cache (for later passes) and exchange buffers.
 struct PkQkvPre {     // what the QKV epilogue needs besides the tile: requested before the tile's input arrives
-  float2 t[4];        // rotary (cos, sin) of the lane's pair for its four rows
-  int p[4];           // positions of those rows
+  float2 t;           // rotary (cos, sin) of the thread's pair in its row
+  int p;              // position of that row
 };
 __device__ __forceinline__ void pk_qkv_prefetch(int nt, int d, int R, const int* pos, const float2* cs, PkQkvPre& pre) {
-  const int lane = threadIdx.x & 63, g = lane >> 4, col = lane & 15;
+  const int lane = threadIdx.x & 63, col = lane & 15, rr = min((lane >> 4) * 4 + (int)(threadIdx.x >> 6), R - 1);
   const int part = (nt * 16) / d, cp = (nt * 16) % d;
   const int qd = (cp & 63) >> 4;
-#pragma unroll
-  for (int i = 0; i < 4; i++) {
-    const int rr = min(g * 4 + i, R - 1);
-    pre.p[i] = pos[rr];
-    pre.t[i] = part < 2 ? cs[(long)rr * 32 + qd * 8 + (col & 7)] : float2{1.f, 0.f};
-  }
+  pre.p = pos[rr];
+  pre.t = part < 2 ? cs[(long)rr * 32 + qd * 8 + (col & 7)] : float2{1.f, 0.f};
 }
 template <int QT, int FWT>
-__device__ __forceinline__ void pk_epi_qkv(const PkArgs& a, const PkLayer& L, const f32x4& c, int nt, unsigned tag, int R,
+__device__ __forceinline__ void pk_epi_qkv(const PkArgs& a, const PkLayer& L, float v, int nt, unsigned tag, int R,
                                            const PkQkvPre& pre, int capb, int row0) {
-  const int lane = threadIdx.x & 63, g = lane >> 4, col = lane & 15;
+  const int lane = threadIdx.x & 63, col = lane & 15, r = (lane >> 4) * 4 + (int)(threadIdx.x >> 6);
   const int d = pk_d<FWT>(a);
   const int part = (nt * 16) / d, cp = (nt * 16) % d;
   const int hh = cp >> 6, qd = (cp & 63) >> 4;
-#pragma unroll
-  for (int i = 0; i < 4; i++) {
-    const int r = g * 4 + i;
-    float v = c[i];
-    int dim;
-    if (part < 2) {
-      const int j = qd * 8 + (col & 7);
-      const float2 t = pre.t[i];
-      const float o = __shfl_xor(v, 8, 64);
-      v = col < 8 ? v * t.x - o * t.y : v * t.x + o * t.y;
-      dim = col < 8 ? j : j + 32;
-    } else {
-      dim = qd * 16 + col;
-    }
-    const float w = __shfl_xor(v, 1, 64);       // neighbour dim (dim ^ 1 sits in lane ^ 1 in every layout above)
-    const int p = pre.p[i];
-    if (r < R) {
-      if (part == 0) {
-        if ((lane & 1) == 0) pk_st(a.q + (long)(row0 + r) * (d >> 1) + ((hh * 64 + dim) >> 1), pk_pack(v, w), tag);
-      } else {
-        u64* nb = (part == 1 ? a.newK : a.newV) + ((long)hh * (QT * 16) + row0 + r) * 32;
-        if ((lane & 1) == 0) pk_st(nb + (dim >> 1), pk_pack(v, w), tag);
-        if (p >= 0) {
-          const int ps = p % (capb * 32);      // the cache is a ring when a window is set
-          const long base = (long)hh * capb * 2048;
-          if (part == 1) L.Kc[base + kblk_off(ps, dim)] = (f16_t)v;
-          else L.Vc[base + vblk_off(ps, dim)] = (f16_t)v;
-        }
-      }
+  int dim = qd * 16 + col;
+  if (part < 2) {
+    const float o = lane_xor8(v);
+    v = col < 8 ? v * pre.t.x - o * pre.t.y : v * pre.t.x + o * pre.t.y;
+    dim = (col < 8 ? 0 : 32) + qd * 8 + (col & 7);
+  }
+  const float w = lane_xor1(v);       // neighbour dim (dim ^ 1 sits in lane ^ 1 in every layout above)
+  if (r >= R) return;
+  if (part == 0) {
+    if ((lane & 1) == 0) pk_st(a.q + (long)(row0 + r) * (d >> 1) + ((hh * 64 + dim) >> 1), pk_pack(v, w), tag);
+  } else {
+    u64* nb = (part == 1 ? a.newK : a.newV) + ((long)hh * (QT * 16) + row0 + r) * 32;
+    if ((lane & 1) == 0) pk_st(nb + (dim >> 1), pk_pack(v, w), tag);
+    if (pre.p >= 0) {
+      const int ps = pre.p % (capb * 32);      // the cache is a ring when a window is set
+      const long base = (long)hh * capb * 2048;
+      if (part == 1) L.Kc[base + kblk_off(ps, dim)] = (f16_t)v;
+      else L.Vc[base + vblk_off(ps, dim)] = (f16_t)v;
     }
   }
 }
@@ -445,7 +405,7 @@ __device__ __forceinline__ int pk_active(int nblk, int ns) { return max(1, min(n
 // Partial results: tile t of (head, split) at part + t * PK_PART.
 // ------------------------------------------------------------------------------------------
 template <int QT, int FWT, class SH>
-__device__ __forceinline__ bool pk_attn_unit(const PkArgs& a, SH& sh, const u64* qbuf, const int (&lim)[QT], int maxlim, int R,
+__device__ __forceinline__ bool pk_attn_unit(const PkArgs& a, SH& sh, int& par, const u64* qbuf, const int (&lim)[QT], int maxlim, int R,
                                              pk_cw_t Kc, pk_cw_t Vc, int capb, int nsplit_cfg, int hh, int split,
                                              bool overlay, int P0, u64* part, unsigned tag, int stage, int window) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -468,6 +428,7 @@ __device__ __forceinline__ bool pk_attn_unit(const PkArgs& a, SH& sh, const u64*
     first[t] = window > 0 ? max(lim[t] - window + 1, 0) : 0;
   }
   if (split >= pk_active(nblk, nsplit_cfg)) return true;      // nothing visible in this split: the merge knows the same count
+  par ^= 1;
   const int b0 = split * 4 + wave, step = nsplit_cfg * 4;     // this wave's blocks: b0, b0 + step, ...
 
   // The wave's query fragments and, if one of its blocks holds rows written by this pass, those rows, in ONE
@@ -600,8 +561,7 @@ __device__ __forceinline__ bool pk_attn_unit(const PkArgs& a, SH& sh, const u64*
           sT[hb][i] = v;
           mx = fmaxf(mx, v);
         }
-      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      mx = rows_max(mx);
       const float mnew = fmaxf(mrun[t], mx);
       const float msafe = mnew == -INFINITY ? 0.f : mnew;
       const float alpha = __builtin_amdgcn_exp2f(mrun[t] - msafe);
@@ -634,98 +594,106 @@ __device__ __forceinline__ bool pk_attn_unit(const PkArgs& a, SH& sh, const u64*
   }
 #pragma unroll
   for (int t = 0; t < QT; t++) {
-    float l = lrun[t];
-    l += __shfl_xor(l, 16, 64);
-    l += __shfl_xor(l, 32, 64);
+    const float l = rows_sum(lrun[t]);
     // (an inactive row carries a negative sum and gives 0; a row with keys whose sum is NaN or 0 gives NaN, which the pass counts)
-    if (g == 0) { sh.lm[wave][t * 16 + ql] = lim[t] < 0 ? 0.f : mrun[t]; sh.ll[wave][t * 16 + ql] = lim[t] < 0 ? -1.f : l; }
+    if (g == 0) { sh.lm[par][wave][t * 16 + ql] = lim[t] < 0 ? 0.f : mrun[t]; sh.ll[par][wave][t * 16 + ql] = lim[t] < 0 ? -1.f : l; }
 #pragma unroll
-    for (int dt = 0; dt < 4; dt++)
-#pragma unroll
-      for (int i = 0; i < 4; i++) sh.lo[wave][t * 16 + ql][dt * 16 + g * 4 + i] = o[t][dt][i];
+    for (int dt = 0; dt < 4; dt++) *reinterpret_cast<f32x4*>(&sh.lo[par][wave][t * 16 + ql][dt * 16 + g * 4]) = o[t][dt];
   }
   if (!pk_sync(sh, ok)) return false;
-  for (int e = threadIdx.x; e < QT * 16 * 64; e += 256) {
-    const int qi = e >> 6, dim = e & 63;
-    const float M = fmaxf(fmaxf(sh.lm[0][qi], sh.lm[1][qi]), fmaxf(sh.lm[2][qi], sh.lm[3][qi]));
-    const float Ms = M == -INFINITY ? 0.f : M;
-    float num = 0.f, den = 0.f;
+  PK_MARK(3);
+  // the waves' parts meet: 16 threads per row, four dims each
 #pragma unroll
-    for (int w = 0; w < 4; w++) {
-      const float f = __builtin_amdgcn_exp2f(sh.lm[w][qi] - Ms);
-      num += sh.lo[w][qi][dim] * f;
-      den += sh.ll[w][qi] * f;
-    }
+  for (int t = 0; t < QT; t++) {
+    const int ql16 = threadIdx.x >> 4, qi = t * 16 + ql16, j = threadIdx.x & 15;
     if (qi < R) {
-      u64* pt = part + (long)(qi >> 4) * PK_PART;      // the row's tile
-      const int ql16 = qi & 15;
-      pk_stf(pt + ql16 * 64 + dim, num, tag);
-      if (dim == 0) { pk_stf(pt + 16 * 64 + ql16, M, tag); pk_stf(pt + 16 * 64 + 16 + ql16, den, tag); }
+      float m[4], f[4];
+#pragma unroll
+      for (int w = 0; w < 4; w++) m[w] = sh.lm[par][w][qi];
+      const float M = fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3]));
+      const float Ms = M == -INFINITY ? 0.f : M;
+      float den = 0.f;
+#pragma unroll
+      for (int w = 0; w < 4; w++) {
+        f[w] = __builtin_amdgcn_exp2f(m[w] - Ms);
+        den += sh.ll[par][w][qi] * f[w];
+      }
+      u64* pt = part + (long)t * PK_PART;
+#pragma unroll
+      for (int k = 0; k < 4; k++) {
+        const int dim = j + 16 * k;
+        float num = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; w++) num += sh.lo[par][w][qi][dim] * f[w];
+        pk_stf(pt + ql16 * 64 + dim, num, tag);
+      }
+      if (j < 2) pk_stf(pt + 16 * 64 + ql16 * 2 + j, j == 0 ? M : den, tag);
     }
   }
-  __syncthreads();
   return true;
 }
 
-// Merge of the splits of one head (one quarter of its dims per unit) into the half-pair attention output: wave w takes the rows
-// w, w + 4, ..., a lane one dim and the splits g, g + 4, ... (g = lane / 16), all parts in one trip (PK_MAXSPLIT); no wave waits for another
-// (parts that meet in LDS behind a barrier instead: fewer loads, but 0.9 us longer).  Lanes and groups are added in a fixed order.
-// (rg: the row group, R: its rows; the split count comes from the largest limit of the whole level, as in the units
+// Merge of the splits of one head into the half-pair attention output: a unit takes four rows, a wave each; lane (g, j) the dims 4j .. 4j+3 of
+// the splits g, g + 4, ..., all parts in one trip of 16-byte loads (PK_MAXSPLIT); no wave waits for another.  Splits and lanes are added
+// in a fixed order.  (A quarter of the dims per unit, one dim per lane and 8-byte loads, 48 of them: 3.6 us from the last part to the last trip at nine rows.)
+// (row0: the first of the four rows, R: rows of the level; the split count comes from the largest limit of the whole level, as in the units
 // that wrote the partial results)
-template <int QT, int FWT>
-__device__ __forceinline__ bool pk_merge_unit(const PkArgs& a, PkShared<QT>& sh, int maxlim, int R, int rg, int capb, int nsplit_cfg,
-                                              int hh, int dq, const u64* parts, u64* att, unsigned tag, int stage) {
+template <int QT, int FWT, class SH>
+__device__ __forceinline__ void pk_merge_unit(const PkArgs& a, SH& sh, int maxlim, int R, int row0, int capb, int nsplit_cfg,
+                                              int hh, const u64* parts, u64* att, unsigned tag, int stage) {
   const int d = pk_d<FWT>(a);
   const int nsplit = __builtin_amdgcn_readfirstlane(pk_active(min((maxlim + 32) >> 5, capb), nsplit_cfg));
-  const long rec = (long)QT * PK_PART;                 // one (head, split) record: a tile per row group
-  const u64* base = parts + (long)hh * PK_MAXSPLIT * rec + (long)rg * PK_PART;
+  constexpr int rec = QT * PK_PART * 8;                 // bytes of one (head, split) record: a tile per row group
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int g = lane >> 4, dim = dq * 16 + (lane & 15);
-  const int need = (nsplit + 3) >> 2;                  // splits of a lane
-  // element i: (k-th split of the lane, j-th row of the wave, word); what does not exist reads a neighbour and is not used
-  auto part = [&](int k, int j, int w) {
-    const int row = min(wave + 4 * j, R - 1);
-    const u64* p = base + (long)min(g + 4 * k, nsplit - 1) * rec;
-    return p + (w == 0 ? 16 * 64 + row : w == 1 ? 16 * 64 + 16 + row : row * 64 + dim);
-  };
-  auto merge = [&](int j, auto raw) {                  // raw(k, w): words of row wave + 4 j
-    float M = -INFINITY, num = 0.f, den = 0.f;
-#pragma unroll
-    for (int k = 0; k < 4; k++) if (g + 4 * k < nsplit) M = fmaxf(M, __uint_as_float(raw(k, 0)));
-    M = fmaxf(M, __shfl_xor(M, 16, 64));
-    M = fmaxf(M, __shfl_xor(M, 32, 64));
-    const float Ms = M == -INFINITY ? 0.f : M;
+  const int g = lane >> 4, j = lane & 15, row = row0 + wave;
+  if (row >= R) return;
+  const agent_buf_t pb = agent_buf(parts + (long)hh * PK_MAXSPLIT * QT * PK_PART, nsplit * rec);      // splits that do not exist read 0
+  const int tile = (row >> 4) * PK_PART * 8, r16 = row & 15;
+  u32x4 ml[4], va[4], vb[4];
+  const u64 t0 = wall_clock64();
+  int it = 0;
+  while (true) {
+    agent_again();
 #pragma unroll
     for (int k = 0; k < 4; k++)
-      if (g + 4 * k < nsplit) {
-        const float f = __builtin_amdgcn_exp2f(__uint_as_float(raw(k, 0)) - Ms);
-        den += __uint_as_float(raw(k, 1)) * f;
-        num += __uint_as_float(raw(k, 2)) * f;
+      if (4 * k < nsplit) {
+        const int o = (g + 4 * k) * rec + tile;
+        ml[k] = ld_agent4(pb, o + (16 * 64 + r16 * 2) * 8);
+        va[k] = ld_agent4(pb, o + (r16 * 64 + 4 * j) * 8);
+        vb[k] = ld_agent4(pb, o + (r16 * 64 + 4 * j + 2) * 8);
       }
-    den += __shfl_xor(den, 16, 64); num += __shfl_xor(num, 16, 64);
-    den += __shfl_xor(den, 32, 64); num += __shfl_xor(num, 32, 64);
-    const float v = den < 0.f ? 0.f : num / den;
-    const float o = __shfl_xor(v, 1, 64);
-    if (lane < 16 && (lane & 1) == 0 && wave + 4 * j < R)
-      pk_st(att + (long)(rg * 16 + wave + 4 * j) * (d >> 1) + ((hh * 64 + dim) >> 1), pk_pack(v, o), tag);
-  };
-  bool ok = true;
-  if (wave < R) {
-    if (R <= 4) {
-      unsigned raw[12];
-      ok = pk_fetch<12>(raw, 3 * need, true, tag, [&](int i) { return part(i / 3, 0, i % 3); }, a, stage);
-      if (ok) merge(0, [&](int k, int w) { return raw[3 * k + w]; });
-    } else {
-      unsigned raw[48];
-      ok = pk_fetch<48>(raw, 12 * need, true, tag, [&](int i) { return part(i / 12, i / 3 % 4, i % 3); }, a, stage);
-      if (ok) {
+    unsigned diff = 0;
 #pragma unroll
-        for (int j = 0; j < 4; j++) merge(j, [&](int k, int w) { return raw[12 * k + 3 * j + w]; });
-      }
-    }
+    for (int k = 0; k < 4; k++)
+      if (4 * k < nsplit && g + 4 * k < nsplit)
+        diff |= (ml[k][1] ^ tag) | (ml[k][3] ^ tag) | (va[k][1] ^ tag) | (va[k][3] ^ tag) | (vb[k][1] ^ tag) | (vb[k][3] ^ tag);
+    if (__all(diff == 0)) break;
+    if ((++it & 63) == 0 && pk_expired(a, t0, stage)) { sh.bad = 1; return; }
+    __builtin_amdgcn_s_sleep(1);
   }
-  if (!pk_sync(sh, ok)) return false;
-  return true;
+  PK_MARK(2);
+  float M = -INFINITY;
+#pragma unroll
+  for (int k = 0; k < 4; k++) if (g + 4 * k < nsplit) M = fmaxf(M, __uint_as_float(ml[k][0]));
+  M = rows_max(M);
+  const float Ms = M == -INFINITY ? 0.f : M;
+  float den = 0.f;
+  f32x4 num = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int k = 0; k < 4; k++)
+    if (g + 4 * k < nsplit) {
+      const float f = __builtin_amdgcn_exp2f(__uint_as_float(ml[k][0]) - Ms);
+      den += __uint_as_float(ml[k][2]) * f;
+      num[0] += __uint_as_float(va[k][0]) * f; num[1] += __uint_as_float(va[k][2]) * f;
+      num[2] += __uint_as_float(vb[k][0]) * f; num[3] += __uint_as_float(vb[k][2]) * f;
+    }
+  den = rows_sum(den);
+#pragma unroll
+  for (int i = 0; i < 4; i++) num[i] = rows_sum(num[i]);
+  if (g < 2) {       // row g of lanes stores dims 4j + 2g, 4j + 2g + 1
+    const float x = g == 0 ? num[0] : num[2], y = g == 0 ? num[1] : num[3];
+    pk_st(att + (long)row * (d >> 1) + hh * 32 + 2 * j + g, den < 0.f ? pk_pack(0.f, 0.f) : pk_pack(x / den, y / den), tag);
+  }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -751,7 +719,9 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
   const int d = pk_d<FWT>(a), H = d / 64, ff = FWT ? 4 * d : a.ff;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   unsigned rr = 0;     // round-robin origin of the current stage (same in every workgroup)
-  int stage = 0;
+  int stage = 0, par = 0;
+  // this thread's place in a GEMM tile: row of the group, column of the tile
+  const int er = ((threadIdx.x & 63) >> 4) * 4 + wave, ec = threadIdx.x & 15;
   bool worked = false;
   if (a.prof && threadIdx.x == 0) atomicMin(a.prof, (u64)wall_clock64());
 
@@ -786,11 +756,9 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
     const int r = u;
     const bool onr = a.pos[0][r] >= 0;
     const f16_t* e = a.emb + (long)a.vtok[r] * d;
-    for (int i = threadIdx.x; i < d; i += 256) {     // region of layer 0, and its half-pair copy (d is a multiple of 128)
+    for (int i = threadIdx.x; i < d; i += 256) {     // region of layer 0, and its copy for the first norm (d is a multiple of 128)
       const float v = onr ? (float)e[i] : 0.f;
-      pk_stf(a.hA + (long)r * d + i, v, PK_TAG(0) + a.test_skew);
-      const float w = __shfl_xor(v, 1, 64);
-      if ((i & 1) == 0) pk_st(a.xA + (long)r * (d >> 1) + (i >> 1), pk_pack(v, w), PK_TAG(0) + a.test_skew);
+      pk_put_row(v, true, r, i, d, a.hA, a.xA, a.sA, ((pk_cf_t)a.layers[0].g1)[i], PK_TAG(0) + a.test_skew);
     }
   }
   PK_NEXT(a.R[0]);
@@ -812,22 +780,25 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
       u64* const xA_n = a.xA + (long)(l + 1) * RH * d;
       u64* const xB_l = a.xB + (long)l * RH * d;
       u64* const xC_l = a.xC + (long)l * RH * d;
+      u64* const sA_l = a.sA + (long)l * RS * (d >> 4);
+      u64* const sB_l = a.sB + (long)l * RS * (d >> 4);
+      u64* const sC_l = a.sC + (long)l * RS * (d >> 4);
       u64* const att_l = a.att + (long)l * RH * d;
       u64* const att2_l = a.att2 + (long)l * RH * d;
       u64* const mid_l = a.mid + (long)l * RH * ff;
-      // GEMM and merge units take the rows in groups of 16: unit = (tile, row group); a group's rows are contiguous
+      // GEMM units take the rows in groups of 16: unit = (tile, row group); a group's rows are contiguous
       // in every exchange buffer, so a unit is the one-group code on offset pointers
       const int RG = QT == 1 ? 1 : (R + 15) >> 4;      // a compile-time 1 for blocks of up to 16 tokens
-      const long hd = d >> 1;
+      const int RQ = (R + 3) >> 2;                     // merge units: four rows of a head each
+      const long hd = d >> 1, sd = d >> 4;
       // ---- QKV (norm1 on the fly, rotary, q / new K,V out, cache append)
       PK_MINE(3 * d / 16 * RG) {
         const int nt = u / RG, row0 = (u % RG) * 16, Rl = min(16, R - row0);
-        f32x4 c;
+        float c;
         PkQkvPre pre;
-        if (wave == 0) pk_qkv_prefetch(nt, d, Rl, pos + row0, a.cs[lev] + (long)row0 * 32, pre);
-        if (!pk_gemm_tile<FWT, 1>(a, sh, L.wqkv + (long)nt * (d / 32) * 512, d / 32, xA_l + row0 * hd, tag, L.g1, Rl, c, stage)) return;
-        if (wave == 0) pk_epi_qkv<QT, FWT>(a, L, c, nt, tag, Rl, pre, capb, row0);
-        __syncthreads();
+        pk_qkv_prefetch(nt, d, Rl, pos + row0, a.cs[lev] + (long)row0 * 32, pre);
+        if (!pk_gemm_tile<FWT, true>(a, sh, par, L.wqkv + (long)nt * (d / 32) * 512, d / 32, xA_l + row0 * hd, tag, sA_l + row0 * sd, Rl, c, stage)) return;
+        pk_epi_qkv<QT, FWT>(a, L, c, nt, tag, Rl, pre, capb, row0);
       }
       PK_NEXT(3 * d / 16 * RG);
       // ---- self-attention splits
@@ -837,38 +808,33 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
         PK_MINE(H * ns) {
           // split-major: the splits that hold keys come first and spread over all workgroups
           const int hh = u % H, sp = u / H;
-          if (!pk_attn_unit<QT, FWT>(a, sh, a.q, limS[lev], maxS[lev], R, L.Kc, L.Vc, capb, ns, hh, sp, true, P0,
+          if (!pk_attn_unit<QT, FWT>(a, sh, par, a.q, limS[lev], maxS[lev], R, L.Kc, L.Vc, capb, ns, hh, sp, true, P0,
                                 a.partS + ((long)hh * PK_MAXSPLIT + sp) * (RS >> 4) * PK_PART, tag, stage, a.win[lev])) return;
         }
         PK_NEXT(H * ns);
-        PK_MINE(4 * H * RG) {
-          const int v = u / RG, rg = u % RG;
-          if (!pk_merge_unit<QT, FWT>(a, sh, maxS[lev], min(16, R - rg * 16), rg, capb, ns, v >> 2, v & 3, a.partS, att_l, tag, stage)) return;
-        }
-        PK_NEXT(4 * H * RG);
+        PK_MINE(H * RQ) pk_merge_unit<QT, FWT>(a, sh, maxS[lev], R, u / H * 4, capb, ns, u % H, a.partS, att_l, tag, stage);
+        PK_NEXT(H * RQ);
       }
       // ---- Wo + residual -> hB (tap: the layer input is what the draft heads of this level start from)
       PK_MINE(d / 16 * RG) {
         const int nt = u / RG, row0 = (u % RG) * 16, Rl = min(16, R - row0);
-        f32x4 c;
-        unsigned old[4];
-        int prow[4];
-        bool okr = true;
-        if (wave == 0) okr = pk_res_prefetch<FWT>(a, nt, hA_l + (long)row0 * d, tag, Rl, pos + row0, old, prow, stage);
-        if (!pk_gemm_tile<FWT, 0>(a, sh, L.wo + (long)nt * (d / 32) * 512, d / 32, att_l + row0 * hd, tag, nullptr, Rl, c, stage)) return;
-        if (wave == 0 && okr)
-          pk_epi_residual<FWT>(a, c, nt, old, hB_l + (long)row0 * d, xB_l + row0 * hd, tag, Rl, prow, L.tap ? a.tap[lev] : nullptr, nullptr,
-                          lev == 0 ? 32 : lev == 1 ? 16 : 8);
-        if (!pk_sync(sh, okr)) return;
+        const int n = nt * 16 + ec;
+        float c, old;
+        PkOld res;
+        pk_res_request<FWT>(a, n, hA_l + (long)row0 * d, Rl, pos + row0, L.g2, res);
+        if (!pk_gemm_tile<FWT, false>(a, sh, par, L.wo + (long)nt * (d / 32) * 512, d / 32, att_l + row0 * hd, tag, nullptr, Rl, c, stage)) return;
+        if (pk_res_take<FWT>(a, n, hA_l + (long)row0 * d, tag, Rl, res, old, stage)) {
+          pk_put_row(old + c, er < Rl, er, n, d, hB_l + (long)row0 * d, xB_l + row0 * hd, sB_l + row0 * sd, res.gain, tag);
+          if (L.tap && er < Rl && res.p >= 0) a.tap[lev][(long)(res.p & (lev == 0 ? 31 : lev == 1 ? 15 : 7)) * d + n] = old;
+        } else sh.bad = 1;
       }
       PK_NEXT(d / 16 * RG);
       // ---- cross-attention query (norm2 on the fly)
       PK_MINE(d / 16 * RG) {
         const int nt = u / RG, row0 = (u % RG) * 16, Rl = min(16, R - row0);
-        f32x4 c;
-        if (!pk_gemm_tile<FWT, 1>(a, sh, L.cq + (long)nt * (d / 32) * 512, d / 32, xB_l + row0 * hd, tag, L.g2, Rl, c, stage)) return;
-        if (wave == 0) pk_epi_half(c, nt, a.q2 + row0 * hd, d >> 1, tag, Rl, false);
-        __syncthreads();
+        float c;
+        if (!pk_gemm_tile<FWT, true>(a, sh, par, L.cq + (long)nt * (d / 32) * 512, d / 32, xB_l + row0 * hd, tag, sB_l + row0 * sd, Rl, c, stage)) return;
+        pk_put_half(c, er < Rl, er, nt * 16 + ec, a.q2 + row0 * hd, d >> 1, tag);
       }
       PK_NEXT(d / 16 * RG);
       // ---- cross-attention over the condition memory
@@ -876,36 +842,32 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
         const int ns = a.nsplitM;
         PK_MINE(H * ns) {
           const int hh = u / ns, sp = u % ns;
-          if (!pk_attn_unit<QT, FWT>(a, sh, a.q2, limX[lev], maxX[lev], R, L.Km, L.Vm, a.capbM, ns, hh, sp, false, 0,
+          if (!pk_attn_unit<QT, FWT>(a, sh, par, a.q2, limX[lev], maxX[lev], R, L.Km, L.Vm, a.capbM, ns, hh, sp, false, 0,
                                 a.partX + ((long)hh * PK_MAXSPLIT + sp) * (RS >> 4) * PK_PART, tag, stage, 0)) return;
         }
         PK_NEXT(H * ns);
-        PK_MINE(4 * H * RG) {
-          const int v = u / RG, rg = u % RG;
-          if (!pk_merge_unit<QT, FWT>(a, sh, maxX[lev], min(16, R - rg * 16), rg, a.capbM, ns, v >> 2, v & 3, a.partX, att2_l, tag, stage)) return;
-        }
-        PK_NEXT(4 * H * RG);
+        PK_MINE(H * RQ) pk_merge_unit<QT, FWT>(a, sh, maxX[lev], R, u / H * 4, a.capbM, ns, u % H, a.partX, att2_l, tag, stage);
+        PK_NEXT(H * RQ);
       }
       // ---- cross output projection + residual -> hC
       PK_MINE(d / 16 * RG) {
         const int nt = u / RG, row0 = (u % RG) * 16, Rl = min(16, R - row0);
-        f32x4 c;
-        unsigned old[4];
-        int prow[4];
-        bool okr = true;
-        if (wave == 0) okr = pk_res_prefetch<FWT>(a, nt, hB_l + (long)row0 * d, tag, Rl, pos + row0, old, prow, stage);
-        if (!pk_gemm_tile<FWT, 0>(a, sh, L.co + (long)nt * (d / 32) * 512, d / 32, att2_l + row0 * hd, tag, nullptr, Rl, c, stage)) return;
-        if (wave == 0 && okr) pk_epi_residual<FWT>(a, c, nt, old, hC_l + (long)row0 * d, xC_l + row0 * hd, tag, Rl, prow, nullptr, nullptr, 8);
-        if (!pk_sync(sh, okr)) return;
+        const int n = nt * 16 + ec;
+        float c, old;
+        PkOld res;
+        pk_res_request<FWT>(a, n, hB_l + (long)row0 * d, Rl, pos + row0, L.g3, res);
+        if (!pk_gemm_tile<FWT, false>(a, sh, par, L.co + (long)nt * (d / 32) * 512, d / 32, att2_l + row0 * hd, tag, nullptr, Rl, c, stage)) return;
+        if (pk_res_take<FWT>(a, n, hB_l + (long)row0 * d, tag, Rl, res, old, stage))
+          pk_put_row(old + c, er < Rl, er, n, d, hC_l + (long)row0 * d, xC_l + row0 * hd, sC_l + row0 * sd, res.gain, tag);
+        else sh.bad = 1;
       }
       PK_NEXT(d / 16 * RG);
       // ---- FFN up (norm3 on the fly, GELU)
       PK_MINE(ff / 16 * RG) {
         const int nt = u / RG, row0 = (u % RG) * 16, Rl = min(16, R - row0);
-        f32x4 c;
-        if (!pk_gemm_tile<FWT, 1>(a, sh, L.w1 + (long)nt * (d / 32) * 512, d / 32, xC_l + row0 * hd, tag, L.g3, Rl, c, stage)) return;
-        if (wave == 0) pk_epi_half(c, nt, mid_l + (long)row0 * (ff >> 1), ff >> 1, tag, Rl, true);
-        __syncthreads();
+        float c;
+        if (!pk_gemm_tile<FWT, true>(a, sh, par, L.w1 + (long)nt * (d / 32) * 512, d / 32, xC_l + row0 * hd, tag, sC_l + row0 * sd, Rl, c, stage)) return;
+        pk_put_half(gelu_tanh_f(c), er < Rl, er, nt * 16 + ec, mid_l + (long)row0 * (ff >> 1), ff >> 1, tag);
       }
       PK_NEXT(ff / 16 * RG);
       // ---- FFN down + residual -> next layer input, or the stack output (+ its ring for later passes).
@@ -916,43 +878,33 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
         const int nt = uv >> 2, kq = uv & 3;
         const int KTq = ff / 128;                       // fragments of one K-quarter
         u64* const w2p = a.w2part + ((long)nt * RG + rg) * 3 * 256;
-        f32x4 c;
-        unsigned old[4];
-        int prow[4];
-        bool okr = true;
-        if (wave == 0 && kq == 0) okr = pk_res_prefetch<FWT>(a, nt, hC_l + (long)row0 * d, tag, Rl, pos + row0, old, prow, stage);
-        if (!pk_gemm_tile<FWT, 0>(a, sh, L.w2 + ((long)nt * (ff / 32) + (long)kq * KTq) * 512, KTq,
-                             mid_l + (long)row0 * (ff >> 1) + (long)kq * (ff / 8), tag, nullptr, Rl, c, stage, ff >> 1)) return;
-        if (wave == 0) {
-          const int lane = threadIdx.x & 63;
-          if (kq > 0) {
+        const int n = nt * 16 + ec;
+        float c, old;
+        PkOld res;
+        // the norm behind this layer: the next one's first, the output head's behind the last
+        const bool out = L.last && st < 4;       // a stack output feeds a level transition, not a norm
+        if (kq == 0) pk_res_request<FWT>(a, n, hC_l + (long)row0 * d, Rl, pos + row0, out ? nullptr : L.last ? (pk_cf_t)a.gf : a.layers[l + 1].g1, res);
+        if (!pk_gemm_tile<FWT, false>(a, sh, par, L.w2 + ((long)nt * (ff / 32) + (long)kq * KTq) * 512, KTq,
+                                      mid_l + (long)row0 * (ff >> 1) + (long)kq * (ff / 8), tag, nullptr, Rl, c, stage, ff >> 1)) return;
+        if (kq > 0) {
+          pk_stf(w2p + (long)(kq - 1) * 256 + threadIdx.x, c, tag);
+        } else {
+          // rows that do not exist wait for nothing: nobody waits for them either, and the next layer writes the same partial tiles
+          unsigned pr[3];
+          if (pk_fetch<3>(pr, 3, er < Rl, tag, [&](int i) { return w2p + (long)i * 256 + threadIdx.x; }, a, stage) &&
+              pk_res_take<FWT>(a, n, hC_l + (long)row0 * d, tag, Rl, res, old, stage)) {
+            PK_MARK(4);
 #pragma unroll
-            for (int i = 0; i < 4; i++) pk_stf(w2p + (long)(kq - 1) * 256 + i * 64 + lane, c[i], tag);
-          } else {
-            unsigned pr[12];
-            okr = pk_fetch<12>(pr, 12, true, tag, [&](int i) { return w2p + (long)(i >> 2) * 256 + (i & 3) * 64 + lane; },
-                               a, stage) && okr;
-            if (okr) {
-#pragma unroll
-              for (int k = 0; k < 3; k++)
-#pragma unroll
-                for (int i = 0; i < 4; i++) c[i] += __uint_as_float(pr[k * 4 + i]);
-              u64* dst = hA_n;
-              u64* xdst = xA_n;
-              float* ring = nullptr;
-              int rs = 8;
-              if (L.last && st < 4) {
-                dst = a.hT[st];
-                xdst = nullptr;        // a stack output feeds a level transition, not a GEMM
-                ring = st == 0 ? a.ring_hc : st == 1 ? a.ring_hv : st == 2 ? a.ring_yf : a.ring_yv;
-                rs = st == 0 ? 32 : st == 2 ? 8 : 16;
-              }
-              pk_epi_residual<FWT>(a, c, nt, old, dst + (long)row0 * d, xdst ? xdst + row0 * hd : nullptr, PK_TAG(l + 1), Rl, prow,
-                              nullptr, ring, rs);
+            for (int k = 0; k < 3; k++) c += __uint_as_float(pr[k]);
+            const float v = old + c;
+            pk_put_row(v, er < Rl, er, n, d, (out ? a.hT[st] : hA_n) + (long)row0 * d, out ? nullptr : xA_n + row0 * hd,
+                       a.sA + (long)(l + 1) * RS * sd + row0 * sd, res.gain, PK_TAG(l + 1));
+            if (out && er < Rl && res.p >= 0) {
+              float* ring = st == 0 ? a.ring_hc : st == 1 ? a.ring_hv : st == 2 ? a.ring_yf : a.ring_yv;
+              ring[(long)(res.p & (st == 0 ? 31 : st == 2 ? 7 : 15)) * d + n] = v;
             }
-          }
+          } else sh.bad = 1;
         }
-        if (!pk_sync(sh, okr)) return;
       }
       PK_NEXT(4 * (d / 16) * RG);
     }
@@ -988,25 +940,15 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
           }
           if (i < d) pk_st(a.pool + (long)st * 8 * d + (long)u * (d >> 1) + (i >> 1), pk_pack(s0 / 3.0f, s1 / 3.0f), tagn);
         }
-        if (!pk_sync(sh, ok)) return;
+        if (!ok) sh.bad = 1;
       }
       PK_NEXT(Rc_);
       PK_MINE(d / 16) {
-        f32x4 c;
+        float c;
+        const float gain = a.layers[ln].g1[u * 16 + ec];
         pk_cw_t W = (pk_cw_t)(st == 0 ? a.short_cv : a.short_vf) + (long)u * (d / 32) * 512;
-        if (!pk_gemm_tile<FWT, 0>(a, sh, W, d / 32, a.pool + (long)st * 8 * d, tagn, nullptr, Rc_, c, stage)) return;
-        if (wave == 0) {
-          const int lane = threadIdx.x & 63, g = lane >> 4, n = u * 16 + (lane & 15);
-#pragma unroll
-          for (int i = 0; i < 4; i++) {
-            const float w = __shfl_xor(c[i], 1, 64);
-            if (g * 4 + i < Rc_) {
-              pk_stf(a.hA + (long)ln * RS * d + (long)(g * 4 + i) * d + n, c[i], tagn);
-              if ((lane & 1) == 0) pk_st(a.xA + (long)ln * RH * d + (long)(g * 4 + i) * (d >> 1) + (n >> 1), pk_pack(c[i], w), tagn);
-            }
-          }
-        }
-        __syncthreads();
+        if (!pk_gemm_tile<FWT, false>(a, sh, par, W, d / 32, a.pool + (long)st * 8 * d, tagn, nullptr, Rc_, c, stage)) return;
+        pk_put_row(c, er < Rc_, er, u * 16 + ec, d, a.hA + (long)ln * RS * d, a.xA + (long)ln * RH * d, a.sA + (long)ln * RS * (d >> 4), gain, tagn);
       }
       PK_NEXT(d / 16);
     } else if (st == 2 || st == 3) {
@@ -1034,11 +976,9 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
               v += ring[(long)((p / 3) & (rs - 1)) * d + i];
             }
           }
-          pk_stf(a.hA + (long)ln * RS * d + (long)u * d + i, v, tagn);
-          const float w = __shfl_xor(v, 1, 64);
-          if ((i & 1) == 0) pk_st(a.xA + (long)ln * RH * d + (long)u * (d >> 1) + (i >> 1), pk_pack(v, w), tagn);
+          pk_put_row(v, true, u, i, d, a.hA + (long)ln * RS * d, a.xA + (long)ln * RH * d, a.sA + (long)ln * RS * (d >> 4), a.layers[ln].g1[i], tagn);
         }
-        if (!pk_sync(sh, ok)) return;
+        if (!ok) sh.bad = 1;
       }
       PK_NEXT(Rf_);
     }
@@ -1049,16 +989,11 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
     const int NT = (a.D.V + 15) / 16, RG = QT == 1 ? 1 : (R + 15) >> 4;
     PK_MINE(NT * RG) {
       const int nt = u / RG, row0 = (u % RG) * 16, Rl = min(16, R - row0);
-      f32x4 c;
-      if (!pk_gemm_tile<FWT, 1>(a, sh, (pk_cw_t)a.lm + (long)nt * (d / 32) * 512, d / 32, a.xA + (long)l * RH * d + (long)row0 * (d >> 1),
-                           PK_TAG(l), (pk_cf_t)a.gf, Rl, c, stage)) return;
-      if (wave == 0) {
-        const int lane = threadIdx.x & 63, g = lane >> 4, n = nt * 16 + (lane & 15);
-#pragma unroll
-        for (int i = 0; i < 4; i++)
-          if (g * 4 + i < Rl && n < a.D.V) a.logits[(long)(row0 + g * 4 + i) * a.D.V + n] = c[i];
-      }
-      __syncthreads();
+      float c;
+      if (!pk_gemm_tile<FWT, true>(a, sh, par, (pk_cw_t)a.lm + (long)nt * (d / 32) * 512, d / 32, a.xA + (long)l * RH * d + (long)row0 * (d >> 1),
+                                   PK_TAG(l), a.sA + ((long)l * RS + row0) * (d >> 4), Rl, c, stage)) return;
+      const int n = nt * 16 + ec;
+      if (er < Rl && n < a.D.V) a.logits[(long)(row0 + er) * a.D.V + n] = c;
     }
   }
 }
