@@ -181,22 +181,22 @@ __device__ __forceinline__ bool pk_fetch(unsigned (&out)[N], int n, bool active,
   }
 }
 
-// A level transition must not publish anything before the stack below it has finished with the shared
-// exchange buffers, even when its own rows are inactive or only need data of earlier passes: it first
-// waits for row 0 of the stack output from EVERY tile (a tile stores only after its last read).
-template <int FWT>
-__device__ __forceinline__ bool pk_wait_stack(const PkArgs& a, const u64* hT, unsigned tag, int stage, int rows);
-
 #define PK_TAG(l) (epoch * 64u + (unsigned)(l) + 1u)      // epoch: local of the kernel
 
+// A level transition must not publish anything before the stack below it has finished with the shared
+// exchange buffers, even when its own rows are inactive or only need data of earlier passes: it first
+// waits for the stack output from EVERY tile, the first row of each of the tile's four waves (wave w stores rows w, w + 4, ...
+// behind its last read, of the partial tiles of the FFN down projection, and no barrier follows that one).  All in one trip.
 template <int FWT>
 __device__ __forceinline__ bool pk_wait_stack(const PkArgs& a, const u64* hT, unsigned tag, int stage, int rows) {
-  unsigned s4[4];
+  unsigned seen[16];
   const int d = pk_d<FWT>(a);
   const int n = (d - (int)threadIdx.x + 255) / 256;     // columns threadIdx.x, +256, ... below d (d <= 1024)
-  bool ok = pk_fetch<4>(s4, n, n > 0, tag, [&](int i) { return hT + threadIdx.x + 256 * i; }, a, stage);
-  // a second row group is written by units of its own: their first row (16) as well
-  if (rows > 16) ok = pk_fetch<4>(s4, n, n > 0, tag, [&](int i) { return hT + 16l * d + threadIdx.x + 256 * i; }, a, stage) && ok;
+  bool ok = true;
+  for (int r0 = 0; r0 < rows; r0 += 16) {               // a second row group is written by units of its own
+    const int last = min(3, rows - r0 - 1);
+    ok = pk_fetch<16>(seen, 4 * n, n > 0, tag, [&](int i) { return hT + (long)(r0 + min(i & 3, last)) * d + threadIdx.x + 256 * (i >> 2); }, a, stage) && ok;
+  }
   return ok;
 }
 
@@ -921,7 +921,7 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
       for (int r = 0; r < Rf_; r++) if (a.pos[fl][r] >= 0) F0 = min(F0, a.pos[fl][r]);
       PK_MINE(Rc_) {
         const int j = a.pos[cl][u];
-        bool ok = pk_wait_stack<FWT>(a, a.hT[st], tagn, stage, QT == 1 ? 16 : Rf_);
+        bool ok = pk_wait_stack<FWT>(a, a.hT[st], tagn, stage, Rf_);
         for (int i0 = 0; i0 < d; i0 += 512) {
           const int i = i0 + 2 * threadIdx.x;       // two adjacent columns per thread
           float s0 = 0.f, s1 = 0.f;
@@ -963,7 +963,7 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
         const int p = a.pos[fl][u];
         int slot = -1;
         if (p >= 0) for (int r = 0; r < Rc_; r++) if (a.pos[cl][r] == p / 3) slot = r;
-        bool ok = pk_wait_stack<FWT>(a, a.hT[st], tagn, stage, QT == 1 ? 16 : Rc_);
+        bool ok = pk_wait_stack<FWT>(a, a.hT[st], tagn, stage, Rc_);
         for (int i = threadIdx.x; i < d; i += 256) {
           unsigned r0[1], r1[1];
           ok = pk_fetch<1>(r0, 1, true, tag_skip, [&](int) { return skip + (long)u * d + i; }, a, stage) && ok;
