@@ -1030,7 +1030,8 @@ int fm_create(const fm_config* cfg, void* hip_stream, fm_ctx** out) {
   {
     const int nl = g.l_cpre + g.l_cpost + g.l_vpre + g.l_vpost + g.l_face;
     const char* env = getenv("FM_PERSIST");
-    c->persist = c->bf16 && D.hd == 64 && D.S == 1 && D.Bm <= 32 && D.d % 128 == 0 && D.d <= 1024 && c->ff % 512 == 0 && nl < 62 &&
+    // (a wave of the single-launch kernel holds 8 K fragments of a quarter of the hidden width: up to 4096)
+    c->persist = c->bf16 && D.hd == 64 && D.S == 1 && D.Bm <= 32 && D.d % 128 == 0 && D.d <= 1024 && c->ff % 512 == 0 && c->ff <= 4096 && nl < 62 &&
                  !(env && env[0] == '0');
   }
   int rc = build_params(c);

@@ -33,6 +33,16 @@ CASES = [
     # the single-launch kernel: one split per group of four key blocks, the last group partly filled; two query tiles
     _cfg("one_launch_splits", 128, 2, 1001, "bf16", 1, 6, 2, 9, 9),
     _cfg("one_launch_two_tiles", 256, 4, 545, "bf16", 1, 6, 2, 15, 18),
+    # its instances: the widths known to the compiler, and the general one (other widths, another hidden width), one and two row groups
+    _cfg("one_launch_w512", 512, 8, 70, "bf16", 1, 3, 2, 9, 9, bins=45),
+    _cfg("one_launch_w768", 768, 12, 33, "bf16", 1, 3, 2, 9, 9),
+    _cfg("one_launch_w1024_two_tiles", 1024, 16, 40, "bf16", 1, 4, 17, 0, 0),
+    _cfg("one_launch_w640_two_tiles", 640, 10, 70, "bf16", 1, 4, 2, 15, 18),
+    _cfg("one_launch_w896", 896, 14, 40, "bf16", 1, 3, 2, 9, 9),
+    _cfg("one_launch_hidden", 256, 4, 40, "bf16", 1, 4, 2, 9, 9, ffn_mult=8),
+    _cfg("one_launch_widest_hidden", 128, 2, 40, "bf16", 1, 4, 2, 9, 9, ffn_mult=32),
+    # a hidden width past what the single-launch kernel holds: the per-operator path
+    _cfg("past_the_hidden", 256, 4, 40, "bf16", 1, 4, 2, 9, 9, ffn_mult=18),
     # more than 32 draft rows per sequence: two row sets of one attention launch
     _cfg("two_sets", 128, 2, 40, "bf16", 2, 8, 2, 27, 27),
     # fp32: tall tiles in the condition GEMM, K past one trip, splits, head widths
