@@ -166,9 +166,7 @@ __global__ __launch_bounds__(NW * 64) void k_dec_gemm(DecGemm a) {
 #pragma unroll
     for (int c = 0; c < NC; c++) red[(wave * NTILE + mt * NC + c) * 64 + lane] = acc[mt][c];
     if constexpr (NORM) {
-      float t = ss[mt];
-      t += __shfl_xor(t, 16, 64);
-      t += __shfl_xor(t, 32, 64);
+      const float t = rows_sum(ss[mt]);
       if (g == 0) sq[(wave * MT + mt) * 16 + rl] = t;
     }
   }
@@ -207,9 +205,7 @@ __global__ __launch_bounds__(NW * 64) void k_dec_gemm(DecGemm a) {
         }
       }
       if (a.ssq_out) {
-        float s2 = v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
-        s2 += __shfl_xor(s2, 16, 64);
-        s2 += __shfl_xor(s2, 32, 64);
+        const float s2 = rows_sum(v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3]);
         if (g == 0 && on) a.ssq_out[((long)(mt0 + mt) * (a.N >> 4) + ntc) * 16 + rl] = s2;
       }
     } else if constexpr (EPI == DE_GELU || EPI == DE_TILE) {
@@ -254,7 +250,7 @@ __global__ __launch_bounds__(NW * 64) void k_dec_gemm(DecGemm a) {
         const f32x4 cx = {c0[0], c0[2], c1[0], c1[2]}, sx = {c0[1], c0[3], c1[1], c1[3]};
 #pragma unroll
         for (int i = 0; i < 4; i++) {
-          const float o = __shfl_xor(v[i], 32, 64);
+          const float o = lane_xor32(v[i]);
           v[i] = g < 2 ? v[i] * cx[i] - o * sx[i] : v[i] * cx[i] + o * sx[i];
         }
         dim = (g < 2 ? 0 : a.hd >> 1) + qd * 8 + (g & 1) * 4;
@@ -400,9 +396,7 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
     first[t] = A->window > 0 ? max(lim[t] - A->window + 1, 0) : 0;     // sliding window: keys first .. lim
     maxlim = max(maxlim, lim[t]);
   }
-#pragma unroll
-  for (int o = 1; o < 16; o <<= 1) maxlim = max(maxlim, __shfl_xor(maxlim, o, 64));
-  maxlim = __builtin_amdgcn_readfirstlane(maxlim);
+  maxlim = __builtin_amdgcn_readfirstlane(row16_max(maxlim));
   // With a window the cache is a ring of capb blocks: position p lives in slot p mod (32 capb), and a slot holds
   // the latest position written to it.  Seen from the newest visible position `maxlim`, slot j holds lapbase + j if that
   // is <= maxlim, else the position one lap earlier (anything newer in the ring is a stale row of a rejected block: it
@@ -451,8 +445,7 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
           sT[t][hb][i] = v;
           mx = fmaxf(mx, v);
         }
-      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      mx = rows_max(mx);
       const float mnew = fmaxf(mrun[t], mx);
       const float msafe = mnew == -INFINITY ? 0.f : mnew;
       const float alpha = __builtin_amdgcn_exp2f(mrun[t] - msafe);   // exp2(-inf) = 0 on the first block
@@ -488,9 +481,7 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
   // sum is NaN or 0 (scores that are not finite) gives NaN, which the pass counts.
 #pragma unroll
   for (int t = 0; t < QT; t++) {
-    float l = lrun[t];
-    l += __shfl_xor(l, 16, 64);
-    l += __shfl_xor(l, 32, 64);
+    const float l = rows_sum(lrun[t]);
     if (g == 0) { lm[wave * NQ + t * 16 + ql] = lim[t] < 0 ? 0.f : mrun[t]; ll[wave * NQ + t * 16 + ql] = lim[t] < 0 ? -1.f : l; }
 #pragma unroll
     for (int dt = 0; dt < DT; dt++) *reinterpret_cast<f32x4*>(lo + (wave * NQ + t * 16 + ql) * LD + dt * 16 + g * 4) = o[t][dt];
