@@ -23,6 +23,7 @@
 #include "fm_device.h"
 #include "fm_kernels_mfma.h"
 #include "fm_kernels_step.h"
+#include "fm_transition.h"
 
 typedef unsigned long long u64;
 
@@ -187,15 +188,17 @@ __device__ __forceinline__ bool pk_fetch(unsigned (&out)[N], int n, bool active,
 // exchange buffers, even when its own rows are inactive or only need data of earlier passes: it first
 // waits for the stack output from EVERY tile, the first row of each of the tile's four waves (wave w stores rows w, w + 4, ...
 // behind its last read, of the partial tiles of the FFN down projection, and no barrier follows that one).  All in one trip.
-template <int FWT>
+// No barrier stands between this wait and what the unit publishes.  Hence COLS (fm_transition.h): a thread waits for the columns that it then
+// publishes; who needs the row of the unit needs all its columns, and so all tiles have been waited for.
+template <int FWT, class COLS>
 __device__ __forceinline__ bool pk_wait_stack(const PkArgs& a, const u64* hT, unsigned tag, int stage, int rows) {
-  unsigned seen[16];
+  unsigned seen[4 * FM_TR_COLS];
   const int d = pk_d<FWT>(a);
-  const int n = (d - (int)threadIdx.x + 255) / 256;     // columns threadIdx.x, +256, ... below d (d <= 1024)
+  const int n = COLS::count(d, threadIdx.x);
   bool ok = true;
   for (int r0 = 0; r0 < rows; r0 += 16) {               // a second row group is written by units of its own
     const int last = min(3, rows - r0 - 1);
-    ok = pk_fetch<16>(seen, 4 * n, n > 0, tag, [&](int i) { return hT + (long)(r0 + min(i & 3, last)) * d + threadIdx.x + 256 * (i >> 2); }, a, stage) && ok;
+    ok = pk_fetch<4 * FM_TR_COLS>(seen, 4 * n, n > 0, tag, [&](int i) { return hT + (long)(r0 + min(i & 3, last)) * d + COLS::col(threadIdx.x, i >> 2); }, a, stage) && ok;
   }
   return ok;
 }
@@ -921,9 +924,9 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
       for (int r = 0; r < Rf_; r++) if (a.pos[fl][r] >= 0) F0 = min(F0, a.pos[fl][r]);
       PK_MINE(Rc_) {
         const int j = a.pos[cl][u];
-        bool ok = pk_wait_stack<FWT>(a, a.hT[st], tagn, stage, Rf_);
-        for (int i0 = 0; i0 < d; i0 += 512) {
-          const int i = i0 + 2 * threadIdx.x;       // two adjacent columns per thread
+        bool ok = pk_wait_stack<FWT, PoolCols>(a, a.hT[st], tagn, stage, Rf_);
+        for (int k = 0; k < PoolCols::count(d, 0); k += 2) {
+          const int i = PoolCols::col(threadIdx.x, k);   // two adjacent columns per thread
           float s0 = 0.f, s1 = 0.f;
           if (j >= 0 && i < d) {
             for (int p = 3 * j - 2; p <= 3 * j; p++) {
@@ -963,8 +966,9 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
         const int p = a.pos[fl][u];
         int slot = -1;
         if (p >= 0) for (int r = 0; r < Rc_; r++) if (a.pos[cl][r] == p / 3) slot = r;
-        bool ok = pk_wait_stack<FWT>(a, a.hT[st], tagn, stage, Rc_);
-        for (int i = threadIdx.x; i < d; i += 256) {
+        bool ok = pk_wait_stack<FWT, SkipCols>(a, a.hT[st], tagn, stage, Rc_);
+        for (int k = 0; k < SkipCols::count(d, threadIdx.x); k++) {
+          const int i = SkipCols::col(threadIdx.x, k);
           unsigned r0[1], r1[1];
           ok = pk_fetch<1>(r0, 1, true, tag_skip, [&](int) { return skip + (long)u * d + i; }, a, stage) && ok;
           float v = __uint_as_float(r0[0]);
