@@ -297,25 +297,24 @@ __device__ __forceinline__ float wave_scan(float v) {
 // Inverse CDF in index order over n weights by one wave: lane t owns the contiguous chunk [t*chunk, (t+1)*chunk); `wf(i)`
 // gives weight i.  Returns, in every lane, the smallest i whose cumulative weight exceeds u * total (the last index with weight
 // if rounding leaves none).
-template <class F>
+// KEPT > 0: the weights of a lane are asked for together and stay in registers (up to 64 KEPT weights in all): the second walk ends at the
+// pick, and a load in each of its rounds is a trip of its own (k_sample_rows 12.3 -> 11.1 us at 1024 weights).  Sums in index order either way.
+template <int KEPT, class F>
 __device__ __forceinline__ int wave_inverse_cdf(int n, float u, F wf, float& total) {
   const int lane = threadIdx.x & 63;
   const int chunk = (n + 63) / 64;
   const int i0 = min(lane * chunk, n), i1 = min(i0 + chunk, n);
-  // The weights of a lane are asked for together and stay in registers (up to 1280 weights in all): the second walk ends at the pick, and a
-  // load in each of its rounds is a trip of its own.  Sums in index order either way.
-  constexpr int C = 20;
-  const bool kept = chunk <= C;
-  float w[C];
+  const bool kept = chunk <= KEPT;
+  float w[KEPT > 0 ? KEPT : 1];
   if (kept) {
 #pragma unroll
-    for (int k = 0; k < C; k++) w[k] = k < chunk ? wf(min(i0 + k, n - 1)) : 0.f;
+    for (int k = 0; k < KEPT; k++) w[k] = k < chunk ? wf(min(i0 + k, n - 1)) : 0.f;
   }
   float local = 0.f;
   int last = -1;
   if (kept) {
 #pragma unroll
-    for (int k = 0; k < C; k++)
+    for (int k = 0; k < KEPT; k++)
       if (i0 + k < i1) {
         local += w[k];
         if (w[k] > 0.f) last = i0 + k;
@@ -335,7 +334,7 @@ __device__ __forceinline__ int wave_inverse_cdf(int n, float u, F wf, float& tot
     float run = excl;
     if (kept) {
 #pragma unroll
-      for (int k = 0; k < C; k++)
+      for (int k = 0; k < KEPT; k++)
         if (i0 + k < i1) {
           run += w[k];
           if (run > thr && pick == 0x7fffffff) pick = i0 + k;
@@ -575,12 +574,12 @@ __global__ __launch_bounds__(256) void k_sample_rows(StateDev st, Dims D, const 
   float tot = 0.f;
   int y;
   if (!has_draft) {
-    y = wave_inverse_cdf(nlim, u, pf, tot);
+    y = wave_inverse_cdf<20>(nlim, u, pf, tot);
   } else {
     auto wf = [&](int j) { return fromq ? fmaxf(pf(j) - q[j] * invZq, 0.f) : (j == xd ? 0.f : pf(j)); };
-    y = wave_inverse_cdf(nlim, u, wf, tot);
+    y = wave_inverse_cdf<20>(nlim, u, wf, tot);
     // all the mass can vanish only if p and q agree everywhere (or p sits on the draft alone): then p itself
-    if (!(tot > 0.f)) y = wave_inverse_cdf(nlim, u, pf, tot);
+    if (!(tot > 0.f)) y = wave_inverse_cdf<20>(nlim, u, pf, tot);
   }
   if (threadIdx.x == 0) {
     st.y[row] = y;
@@ -670,10 +669,12 @@ __global__ __launch_bounds__(1024) void k_merge(StateDev st, Dims D, DraftRows R
       }
       if (sampled) {
         // the kept row is the proposal that the verify pass tests against; a wave reads back what its own lanes stored
+        // (no weights in registers: with the row's values above they do not fit the 128 that 1024 threads leave, and went to scratch memory, 124
+        // bytes a lane, in greedy steps too: 33.1 us a launch for five sequences of 18 tokens and 10.7 greedy, against 25.2 and 9.6)
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
         float total;
-        bi = wave_inverse_cdf(nlim, sample_uniform(pr.seed, FM_U_DRAFT, s, p), [&](int i) { return qr[i]; }, total);
+        bi = wave_inverse_cdf<0>(nlim, sample_uniform(pr.seed, FM_U_DRAFT, s, p), [&](int i) { return qr[i]; }, total);
         if (lane == 0 && p < budget) { sm.qtok[s * D.Bm + idx] = bi; sm.qsum[s * D.Bm + idx] = total; }
       } else {
 #pragma unroll

@@ -1,0 +1,41 @@
+"""What the compiler made of the kernels, as the built library's own metadata says."""
+import os
+import re
+import shutil
+import struct
+import subprocess
+
+import pytest
+
+from paper_2511_15618_amd import binding
+
+READELF = shutil.which("llvm-readelf") or "/opt/rocm/llvm/bin/llvm-readelf"
+
+
+def _device_code(data: bytes) -> bytes:
+    """The gfx950 code object inside the shared library (an ELF of machine AMDGPU = 224)."""
+    at = data.find(b"\x7fELF", 4)
+    while at >= 0:
+        if struct.unpack_from("<H", data, at + 18)[0] == 224:
+            return data[at:]
+        at = data.find(b"\x7fELF", at + 4)
+    raise AssertionError("no device code in the library")
+
+
+def _scratch(notes: str) -> dict:
+    """Bytes of scratch memory per lane, by kernel."""
+    return {name: int(size) for name, size in
+            re.findall(r"\.name:\s+(_Z\w*k_\w+)\n(?:\s+\.(?!name)\w+:.*\n)*?\s+\.private_segment_fixed_size:\s+(\d+)", notes)}
+
+
+@pytest.mark.skipif(not os.path.exists(READELF), reason="no llvm-readelf")
+def test_no_kernel_needs_scratch_memory(tmp_path):
+    """Registers that do not fit go to memory, lane by lane: every kernel here is written to stay within its registers."""
+    if not os.path.exists(binding.LIB_PATH):
+        from paper_2511_15618_amd import build
+        build.build()
+    obj = tmp_path / "device.elf"
+    obj.write_bytes(_device_code(open(binding.LIB_PATH, "rb").read()))
+    scratch = _scratch(subprocess.run([READELF, "--notes", str(obj)], capture_output=True, text=True, check=True).stdout)
+    assert len(scratch) > 100 and any("k_merge" in k for k in scratch) and any("k_verify_persist" in k for k in scratch)
+    assert {k: n for k, n in scratch.items() if n} == {}
