@@ -51,8 +51,8 @@ struct PkLayer {
   int stack;      // 0 cpre, 1 vpre, 2 face, 3 vpost, 4 cpost
 };
 
-// Width of the model: FWT fragments of 32 per wave in a GEMM over d, i.e. d = 128 FWT, known to the compiler for the usual widths
-// (the hidden width is then 4 d), read from the arguments for the others (FWT = 0).
+// Width of the model: FWT fragments of 32 per wave in a GEMM over d, i.e. d = 128 FWT, known to the compiler for some widths (pk_kernel;
+// the hidden width is then 4 d), read from the arguments for the others (FWT = 0).
 struct PkArgs;
 template <int FWT> __device__ __forceinline__ int pk_d(const PkArgs& a);
 
@@ -1002,17 +1002,14 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
   }
 }
 
-// The instance of a context: two row groups or one, and the width where it is one that the compiler knows.
+// The instance of a context: two row groups or one, and the width where the compiler's knowing it measures faster than reading it from the
+// arguments.  Verify pass of 20 blocks behind 4500 tokens, us, sized against general: one row group d = 256 468 / 479, 512 524 / 525 (eight
+// faces token by token 30 110 / 30 560), 768 573 / 585; two row groups 512 601 / 604, 768 678 / 711.  No faster, and hence general: two row
+// groups at 256 (541 / 542), and 1024, whose eight fragments a wave are what the general instance holds anyway (40 blocks behind 9000 tokens:
+// 1365 / 1368, two row groups 1639 / 1636).
 typedef void (*pk_kernel_t)(PkArgs);
 inline pk_kernel_t pk_kernel(const PkArgs& a) {
   const int d = a.ff == 4 * a.D.d ? a.D.d : 0;
-#define PK_PICK(FWT) return a.RS == 32 ? k_verify_persist<2, FWT> : k_verify_persist<1, FWT>
-  switch (d) {
-    case 256: PK_PICK(2);
-    case 512: PK_PICK(4);
-    case 768: PK_PICK(6);
-    case 1024: PK_PICK(8);
-    default: PK_PICK(0);
-  }
-#undef PK_PICK
+  if (a.RS == 32) return d == 512 ? k_verify_persist<2, 4> : d == 768 ? k_verify_persist<2, 6> : k_verify_persist<2, 0>;
+  return d == 256 ? k_verify_persist<1, 2> : d == 512 ? k_verify_persist<1, 4> : d == 768 ? k_verify_persist<1, 6> : k_verify_persist<1, 0>;
 }

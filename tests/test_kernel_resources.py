@@ -28,14 +28,32 @@ def _scratch(notes: str) -> dict:
             re.findall(r"\.name:\s+(_Z\w*k_\w+)\n(?:\s+\.(?!name)\w+:.*\n)*?\s+\.private_segment_fixed_size:\s+(\d+)", notes)}
 
 
-@pytest.mark.skipif(not os.path.exists(READELF), reason="no llvm-readelf")
-def test_no_kernel_needs_scratch_memory(tmp_path):
-    """Registers that do not fit go to memory, lane by lane: every kernel here is written to stay within its registers."""
+def _kernels(tmp_path) -> dict:
     if not os.path.exists(binding.LIB_PATH):
         from paper_2511_15618_amd import build
         build.build()
     obj = tmp_path / "device.elf"
     obj.write_bytes(_device_code(open(binding.LIB_PATH, "rb").read()))
-    scratch = _scratch(subprocess.run([READELF, "--notes", str(obj)], capture_output=True, text=True, check=True).stdout)
+    return _scratch(subprocess.run([READELF, "--notes", str(obj)], capture_output=True, text=True, check=True).stdout)
+
+
+@pytest.mark.skipif(not os.path.exists(READELF), reason="no llvm-readelf")
+def test_no_kernel_needs_scratch_memory(tmp_path):
+    """Registers that do not fit go to memory, lane by lane: every kernel here is written to stay within its registers."""
+    scratch = _kernels(tmp_path)
     assert len(scratch) > 100 and any("k_merge" in k for k in scratch) and any("k_verify_persist" in k for k in scratch)
     assert {k: n for k, n in scratch.items() if n} == {}
+
+
+@pytest.mark.skipif(not os.path.exists(READELF), reason="no llvm-readelf")
+def test_every_instance_of_the_single_launch_kernel_has_a_lockstep_case(tmp_path):
+    """Row groups and width as the kernel's template parameters have them; a width without an instance of its own runs the general one."""
+    from test_gpu_decode_kernels import CASES
+    built = {tuple(map(int, m)) for k in _kernels(tmp_path) for m in re.findall(r"k_verify_persistILi(\d)ELi(\d+)E", k)}
+    assert {(1, 0), (2, 0)} <= built
+    run = set()
+    for c in CASES:
+        if c.name.startswith("one_launch"):
+            sized = (2 if c.block_max > 16 else 1, c.d_model // 128 if c.ffn_mult == 4 else 0)
+            run.add(sized if sized in built else (sized[0], 0))
+    assert run == built
