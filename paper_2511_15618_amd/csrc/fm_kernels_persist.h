@@ -203,16 +203,18 @@ __device__ __forceinline__ bool pk_wait_stack(const PkArgs& a, const u64* hT, un
   return ok;
 }
 
-// phase timing inside the units of one chosen stage (debug): latest time each phase was reached
-#define PK_MARK(k) do { if (a.prof && stage == a.prof_stage && threadIdx.x == 0) atomicMax(a.prof + 600 + (k), (u64)wall_clock64()); } while (0)
+// Times of a stage (debug), the latest of all waves: each of them finishes a quarter of a unit, and no barrier follows.
+#define PK_STAMP(i) do { if ((threadIdx.x & 63) == 0) atomicMax(a.prof + (i), (u64)wall_clock64()); } while (0)
+// phase timing inside the units of one chosen stage: latest time each phase was reached
+#define PK_MARK(k) do { if (a.prof && stage == a.prof_stage) PK_STAMP(600 + (k)); } while (0)
 
 // ------------------------------------------------------------------------------------------
 // GEMM tile: C[16 rows x 16 cols] = A[16 x K] * W_tile^T, four waves split K (K <= 1024).  Behind the one barrier of the unit every wave
 // owns a quarter of the result: wave w of lane (g, col) has row g*4 + w, column col in `result`.
 // A is a half-pair exchange buffer [16][K/2].  NORM: its rows are half(x * gain), written so by the producers of the residual stream
 // together with the sums of squares of every 16 columns, sq[row][K/16]; the row factor 1/rms goes onto the result.
-// (One wave doing the whole epilogue, and gain and sums computed here: 1.3 to 2 us from the arrival of the operands to the barrier, and
-// 1 to 3.3 us of epilogue, against 0.5 to 0.8 and 0.4 to 0.9; steps 707 -> 644 us at d = 512, 1692 -> 1526 at d = 1024, with the merge below.)
+// (One wave doing the whole epilogue, and gain and sums computed here: steps of 707 us at d = 512 and 1692 us at d = 1024, against 644 and
+// 1526 with the merge below.)
 // Every wave takes the MFMA A-fragments of its K-quarter straight from the exchange buffer: lane (r, g) of
 // fragment f needs the 8 consecutive values k0 = f*32 + g*8 .. +8 of row r, which are 32 contiguous bytes of
 // tagged half pairs, i.e. two 16-byte agent-scope loads.  No LDS staging, no barrier before the multiplication;
@@ -705,7 +707,7 @@ __device__ __forceinline__ void pk_merge_unit(const PkArgs& a, SH& sh, int maxli
 #define PK_MINE(units) for (int u = (int)((blockIdx.x + PK_NWG - (rr % PK_NWG)) % PK_NWG); u < (units) && (worked = true); u += PK_NWG)
 #define PK_NEXT(units)                                                                              \
   do {                                                                                              \
-    if (a.prof && worked && threadIdx.x == 0) atomicMax(a.prof + 1 + stage, (u64)wall_clock64());   \
+    if (a.prof && worked) PK_STAMP(1 + stage);                                                      \
     worked = false;                                                                                 \
     rr += (units);                                                                                  \
     stage++;                                                                                        \
