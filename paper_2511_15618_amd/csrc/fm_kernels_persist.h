@@ -113,7 +113,7 @@ struct PkShared {
 };
 
 // Barrier at which all waves learn whether one of them has given up.  (__syncthreads_or is three barriers and two trips to LDS, in
-// every unit: steps of 755 us at d = 512 and 1812 us at d = 1024 become 730 and 1754.)
+// every unit: steps of 755 us at d = 512 and 1817 us at d = 1024 become 728 and 1755.)
 template <class SH>
 __device__ __forceinline__ bool pk_sync(SH& sh, bool good) {
   if (!good) sh.bad = 1;
