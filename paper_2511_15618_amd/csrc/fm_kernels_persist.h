@@ -190,16 +190,47 @@ __device__ __forceinline__ bool pk_fetch(unsigned (&out)[N], int n, bool active,
 // behind its last read, of the partial tiles of the FFN down projection, and no barrier follows that one).  All in one trip.
 // No barrier stands between this wait and what the unit publishes.  Hence COLS (fm_transition.h): a thread waits for the columns that it then
 // publishes; who needs the row of the unit needs all its columns, and so all tiles have been waited for.
-template <int FWT, class COLS>
-__device__ __forceinline__ bool pk_wait_stack(const PkArgs& a, const u64* hT, unsigned tag, int stage, int rows) {
-  unsigned seen[4 * FM_TR_COLS];
+// The rows of the stack that the unit needs (`row(k)`, k < OWN) come in the same trip, the thread's columns of row k in
+// got[k].  (Each element in a trip of its own: upsampling 4.4 us
+// instead of 2.2 at d = 512, 8.0 instead of 3.4 at 1024; pooling 4.9 instead of 2.9 there.)
+template <int FWT, class COLS, int OWN, class ROW>
+__device__ __forceinline__ bool pk_wait_stack(const PkArgs& a, const u64* hT, unsigned tag, int stage, int rows, ROW row, float (&got)[OWN][FM_TR_COLS]) {
   const int d = pk_d<FWT>(a);
   const int n = COLS::count(d, threadIdx.x);
+  const agent_buf_t hb = agent_buf(hT, rows * d * 8);
+  u32x2 own[OWN][FM_TR_COLS];
   bool ok = true;
-  for (int r0 = 0; r0 < rows; r0 += 16) {               // a second row group is written by units of its own
-    const int last = min(3, rows - r0 - 1);
-    ok = pk_fetch<4 * FM_TR_COLS>(seen, 4 * n, n > 0, tag, [&](int i) { return hT + (long)(r0 + min(i & 3, last)) * d + COLS::col(threadIdx.x, i >> 2); }, a, stage) && ok;
+  for (int r0 = 0; r0 < rows && ok; r0 += 16) {               // a second row group is written by units of its own
+    const u64 t0 = wall_clock64();
+    int it = 0;
+    while (true) {
+      agent_again();
+      u32x2 seen[4][FM_TR_COLS];
+      unsigned diff = 0;
+#pragma unroll
+      for (int c = 0; c < FM_TR_COLS; c++) {
+        const int col = COLS::col(threadIdx.x, min(c, max(n - 1, 0)));      // columns that the thread does not have: its last one again
+#pragma unroll
+        for (int k = 0; k < 4; k++) seen[k][c] = ld_agent2(hb, ((r0 + min(k, rows - r0 - 1)) * d + col) * 8);
+#pragma unroll
+        for (int k = 0; k < OWN; k++) own[k][c] = ld_agent2(hb, (row(k) * d + col) * 8);
+      }
+#pragma unroll
+      for (int c = 0; c < FM_TR_COLS; c++) {
+#pragma unroll
+        for (int k = 0; k < 4; k++) diff |= seen[k][c][1] ^ tag;
+#pragma unroll
+        for (int k = 0; k < OWN; k++) diff |= own[k][c][1] ^ tag;
+      }
+      if (__all(diff == 0 || n <= 0)) break;
+      if ((++it & 63) == 0 && pk_expired(a, t0, stage)) { ok = false; break; }
+      __builtin_amdgcn_s_sleep(1);
+    }
   }
+#pragma unroll
+  for (int k = 0; k < OWN; k++)
+#pragma unroll
+    for (int c = 0; c < FM_TR_COLS; c++) got[k][c] = __uint_as_float(own[k][c][0]);
   return ok;
 }
 
@@ -400,6 +431,9 @@ __device__ __forceinline__ void pk_epi_qkv(const PkArgs& a, const PkLayer& L, fl
 }
 
 __device__ __forceinline__ int pk_active(int nblk, int ns) { return max(1, min(ns, (nblk + 3) >> 2)); }      // splits that hold visible keys
+__device__ __forceinline__ int pk_parts(int maxlim, int capb, int ns) {      // and so parts per head, uniform
+  return __builtin_amdgcn_readfirstlane(pk_active(min((maxlim + 32) >> 5, capb), ns));
+}
 
 // ------------------------------------------------------------------------------------------
 // Attention over one split of the keys of one head (flash-decoding), same arithmetic and deal as k_dec_attn: block b of 32 keys
@@ -407,12 +441,14 @@ __device__ __forceinline__ int pk_active(int nblk, int ns) { return max(1, min(n
 // 16 query rows share every K/V block that is loaded.  The first K/V block of a wave is requested before the wait for
 // the queries, the next one behind it.  Keys of this pass (positions >= P0) are taken from the
 // exchange buffers, older keys from the cache.  lim[t]: last key the lane's row of tile t may see (-1: unused slot).
-// Partial results: tile t of (head, split) at part + t * PK_PART.
+// Partial results: tile t of (head, split) at part + t * PK_PART.  Where one split holds all visible keys (contexts of up to 128) there is nothing
+// to merge: its unit writes the attention output, and the merge stage, an exchange of 1.1 to 2 us, is left
+// out (eight faces token by token at d = 512, with the trips above: 29.9 -> 26.3 ms).
 // ------------------------------------------------------------------------------------------
 template <int QT, int FWT, class SH>
 __device__ __forceinline__ bool pk_attn_unit(const PkArgs& a, SH& sh, int& par, const u64* qbuf, const int (&lim)[QT], int maxlim, int R,
                                              pk_cw_t Kc, pk_cw_t Vc, int capb, int nsplit_cfg, int hh, int split,
-                                             bool overlay, int P0, u64* part, unsigned tag, int stage, int window) {
+                                             bool overlay, int P0, u64* part, u64* att, unsigned tag, int stage, int window) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int g = lane >> 4, ql = lane & 15;
   const int d = pk_d<FWT>(a);
@@ -432,13 +468,13 @@ __device__ __forceinline__ bool pk_attn_unit(const PkArgs& a, SH& sh, int& par, 
     on[t] = t * 16 + ql < R;
     first[t] = window > 0 ? max(lim[t] - window + 1, 0) : 0;
   }
-  if (split >= pk_active(nblk, nsplit_cfg)) return true;      // nothing visible in this split: the merge knows the same count
+  const int nact = pk_active(nblk, nsplit_cfg);
+  if (split >= nact) return true;      // nothing visible in this split: the merge knows the same count
   par ^= 1;
   const int b0 = split * 4 + wave, step = nsplit_cfg * 4;     // this wave's blocks: b0, b0 + step, ...
 
-  // The wave's query fragments and, if one of its blocks holds rows written by this pass, those rows, in ONE
-  // batch.  K fragment f = (hb, dh) holds key b*32 + hb*16 + lane%16, dims dh*32 + g*8..+8 (4 elements);
-  // V fragment dt holds dim dt*16 + lane%16 and the 8 slots g*8 + j <-> key b*32 + (j/4)*16 + g*4 + j%4.
+  // The block of this wave, if any, that holds rows written by this pass.  K fragment f = (hb, dh) holds key b*32 + hb*16 + lane%16, dims
+  // dh*32 + g*8..+8 (4 elements); V fragment dt holds dim dt*16 + lane%16 and the 8 slots g*8 + j <-> key b*32 + (j/4)*16 + g*4 + j%4.
   int bov = -1;
   if (overlay) {
     // slot blocks of the rows of this pass: neighbours (also around a ring, whose blocks are a multiple of four), so in different waves;
@@ -463,24 +499,59 @@ __device__ __forceinline__ bool pk_attn_unit(const PkArgs& a, SH& sh, int& par, 
   };
   if (b0 < nblk) load(ka[0], va[0], b0);
   // q of this lane: dims g*8..+8 and 32 + g*8..+8 of the head = two runs of four tagged elements = four 16-byte
-  // agent-scope loads per query tile, simply repeated until every tag matches (small enough to poll with the data itself)
+  // agent-scope loads per query tile, simply repeated until every tag matches (small enough to poll with the data itself).  Where one
+  // of the wave's blocks holds rows written by this pass, those come in the same trip: the tiles that produce them are units of the same stage.
+  // (In a trip of their own behind the queries the attention stage of 1500 keys takes 3.6 us instead of 2.6 at d = 512, 6.0 instead of 4.7 at 1024.)
   f16x8 qf0[QT], qf1[QT];
+  f16x8 nk[4], nv[4];       // fragments of that block, valid where fromK / fromV
+  int keyK[2], keyV[8];     // positions of this lane's keys in it
   bool ok = true;
   {
     const agent_buf_t qb = agent_buf(qbuf, QT * 16 * (d >> 1) * 8);
     int qo[QT];
 #pragma unroll
     for (int t = 0; t < QT; t++) qo[t] = ((on[t] ? t * 16 + ql : 0) * (d >> 1) + ((hh * 64 + g * 8) >> 1)) * 8;
+    const agent_buf_t kb = agent_buf(a.newK + (long)hh * (QT * 16) * 32, QT * 16 * 32 * 8), vb = agent_buf(a.newV + (long)hh * (QT * 16) * 32, QT * 16 * 32 * 8);
+    int ko[2], vo[8];
+    auto row_of = [&](int key) { return min(max(key - P0, 0), R - 1) * 256; };
+#pragma unroll
+    for (int h = 0; h < 2; h++) { keyK[h] = held(bov * 32 + h * 16 + ql); ko[h] = row_of(keyK[h]) + g * 32; }
+#pragma unroll
+    for (int j = 0; j < 8; j++) { keyV[j] = held(bov * 32 + (j >> 2) * 16 + g * 4 + (j & 3)); vo[j] = row_of(keyV[j]) + (ql >> 1) * 8; }
     const u64 t0 = wall_clock64();
     int it = 0;
     u32x4 qv[QT][4];
     while (true) {
       agent_again();
+      unsigned diff = 0;
 #pragma unroll
       for (int t = 0; t < QT; t++)
 #pragma unroll
         for (int j = 0; j < 4; j++) qv[t][j] = ld_agent4(qb, qo[t] + ((j >> 1) * 16 + (j & 1) * 2) * 8);
-      unsigned diff = 0;
+      if (bov >= 0) {
+        u32x4 kk[4][2];
+        u32x2 vv[4][8];
+#pragma unroll
+        for (int f = 0; f < 4; f++)
+#pragma unroll
+          for (int j = 0; j < 2; j++) kk[f][j] = ld_agent4(kb, ko[f >> 1] + (f & 1) * 128 + j * 16);
+#pragma unroll
+        for (int dt = 0; dt < 4; dt++)
+#pragma unroll
+          for (int j = 0; j < 8; j++) vv[dt][j] = ld_agent2(vb, vo[j] + dt * 64);
+#pragma unroll
+        for (int f = 0; f < 4; f++) {
+          diff |= (kk[f][0][1] ^ tag) | (kk[f][0][3] ^ tag) | (kk[f][1][1] ^ tag) | (kk[f][1][3] ^ tag);
+          nk[f] = __builtin_bit_cast(f16x8, (u32x4{kk[f][0][0], kk[f][0][2], kk[f][1][0], kk[f][1][2]}));
+        }
+#pragma unroll
+        for (int dt = 0; dt < 4; dt++)
+#pragma unroll
+          for (int j = 0; j < 8; j++) {
+            diff |= vv[dt][j][1] ^ tag;
+            nv[dt][j] = __builtin_bit_cast(f16_t, (unsigned short)(ql & 1 ? vv[dt][j][0] >> 16 : vv[dt][j][0] & 0xFFFFu));
+          }
+      }
 #pragma unroll
       for (int t = 0; t < QT; t++)
 #pragma unroll
@@ -497,22 +568,6 @@ __device__ __forceinline__ bool pk_attn_unit(const PkArgs& a, SH& sh, int& par, 
       qf1[t] = __builtin_bit_cast(f16x8, hi4);
     }
   }
-  // rows written by this pass that fall into one of this wave's blocks (at most one block)
-  unsigned raw[48];
-  if (bov >= 0) {
-    ok = pk_fetch<48>(raw, 48, true, tag, [&](int i) {
-      if (i < 16) {
-        const int f = i >> 2;
-        int nr = held(bov * 32 + (f >> 1) * 16 + (lane & 15)) - P0;
-        nr = nr < 0 ? 0 : (nr >= R ? R - 1 : nr);
-        return (const u64*)(a.newK + ((long)hh * (QT * 16) + nr) * 32 + (((f & 1) * 32 + g * 8) >> 1) + (i & 3));
-      }
-      const int j = (i - 16) & 7, dt = (i - 16) >> 3;
-      int nr = held(bov * 32 + (j >> 2) * 16 + g * 4 + (j & 3)) - P0;
-      nr = nr < 0 ? 0 : (nr >= R ? R - 1 : nr);
-      return (const u64*)(a.newV + ((long)hh * (QT * 16) + nr) * 32 + ((dt * 16 + (lane & 15)) >> 1));
-    }, a, stage) && ok;
-  }
 
   float mrun[QT], lrun[QT];
   f32x4 o[QT][4];
@@ -526,25 +581,16 @@ __device__ __forceinline__ bool pk_attn_unit(const PkArgs& a, SH& sh, int& par, 
   auto attend = [&](f16x8 (&kf)[4], f16x8 (&vf)[4], int b) {
     if (b == bov) {
 #pragma unroll
-      for (int f = 0; f < 4; f++) {
-        const int nr = held(b * 32 + (f >> 1) * 16 + (lane & 15)) - P0;
-        if (nr >= 0 && nr < R) kf[f] = __builtin_bit_cast(f16x8, (u32x4{raw[f * 4], raw[f * 4 + 1], raw[f * 4 + 2], raw[f * 4 + 3]}));
-      }
+      for (int f = 0; f < 4; f++)
+        if (keyK[f >> 1] >= P0 && keyK[f >> 1] < P0 + R) kf[f] = nk[f];
+      // From this pass: positions >= P0, all of them rows of it.  A slot that this stream has not reached (position below 0) takes the
+      // value too that was fetched for it, the first row's: its probability is 0, but what an earlier mesh left there may not be
+      // finite, and 0 times that is NaN.
 #pragma unroll
-      for (int dt = 0; dt < 4; dt++) {
-        const int dim = dt * 16 + (lane & 15);
+      for (int dt = 0; dt < 4; dt++)
 #pragma unroll
-        for (int j = 0; j < 8; j++) {
-          // From this pass: positions >= P0, all of them rows of it.  A slot that this stream has not reached (position below 0) takes the
-          // value too that was fetched for it, the first row's: its probability is 0, but what an earlier mesh left there may not be
-          // finite, and 0 times that is NaN.
-          if ((unsigned)held(b * 32 + (j >> 2) * 16 + g * 4 + (j & 3)) >= (unsigned)P0) {
-            const unsigned w = raw[16 + dt * 8 + j];
-            const unsigned short hbits = (dim & 1) ? (unsigned short)(w >> 16) : (unsigned short)(w & 0xFFFFu);
-            vf[dt][j] = __builtin_bit_cast(f16_t, hbits);
-          }
-        }
-      }
+        for (int j = 0; j < 8; j++)
+          if ((unsigned)keyV[j] >= (unsigned)P0) vf[dt][j] = nv[dt][j];
     }
 #pragma unroll
     for (int t = 0; t < QT; t++) {
@@ -623,6 +669,15 @@ __device__ __forceinline__ bool pk_attn_unit(const PkArgs& a, SH& sh, int& par, 
         f[w] = __builtin_amdgcn_exp2f(m[w] - Ms);
         den += sh.ll[par][w][qi] * f[w];
       }
+      if (nact == 1) {      // the only part: the row's result, four neighbouring dims (what a merge of one part would give, bit by bit)
+        f32x4 num = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < 4; w++) num += *reinterpret_cast<const f32x4*>(&sh.lo[par][w][qi][4 * j]) * f[w];
+        u64* at = att + (long)qi * (d >> 1) + hh * 32 + 2 * j;
+        pk_st(at, den < 0.f ? pk_pack(0.f, 0.f) : pk_pack(num[0] / den, num[1] / den), tag);
+        pk_st(at + 1, den < 0.f ? pk_pack(0.f, 0.f) : pk_pack(num[2] / den, num[3] / den), tag);
+        continue;
+      }
       u64* pt = part + (long)t * PK_PART;
 #pragma unroll
       for (int k = 0; k < 4; k++) {
@@ -647,7 +702,7 @@ template <int QT, int FWT, class SH>
 __device__ __forceinline__ void pk_merge_unit(const PkArgs& a, SH& sh, int maxlim, int R, int row0, int capb, int nsplit_cfg,
                                               int hh, const u64* parts, u64* att, unsigned tag, int stage) {
   const int d = pk_d<FWT>(a);
-  const int nsplit = __builtin_amdgcn_readfirstlane(pk_active(min((maxlim + 32) >> 5, capb), nsplit_cfg));
+  const int nsplit = pk_parts(maxlim, capb, nsplit_cfg);
   constexpr int rec = QT * PK_PART * 8;                 // bytes of one (head, split) record: a tile per row group
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int g = lane >> 4, j = lane & 15, row = row0 + wave;
@@ -761,9 +816,18 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
     const int r = u;
     const bool onr = a.pos[0][r] >= 0;
     const f16_t* e = a.emb + (long)a.vtok[r] * d;
-    for (int i = threadIdx.x; i < d; i += 256) {     // region of layer 0, and its copy for the first norm (d is a multiple of 128)
-      const float v = onr ? (float)e[i] : 0.f;
-      pk_put_row(v, true, r, i, d, a.hA, a.xA, a.sA, ((pk_cf_t)a.layers[0].g1)[i], PK_TAG(0) + a.test_skew);
+    const int n = SkipCols::count(d, threadIdx.x);
+    float v[FM_TR_COLS], gain[FM_TR_COLS];
+#pragma unroll
+    for (int k = 0; k < FM_TR_COLS; k++) {           // all loads together
+      const int i = min(SkipCols::col(threadIdx.x, k), d - 1);
+      v[k] = (float)e[i];
+      gain[k] = ((pk_cf_t)a.layers[0].g1)[i];
+    }
+#pragma unroll
+    for (int k = 0; k < FM_TR_COLS; k++) {           // region of layer 0, and its copy for the first norm (d is a multiple of 128)
+      if (k >= n) break;
+      pk_put_row(onr ? v[k] : 0.f, true, r, SkipCols::col(threadIdx.x, k), d, a.hA, a.xA, a.sA, gain[k], PK_TAG(0) + a.test_skew);
     }
   }
   PK_NEXT(a.R[0]);
@@ -814,10 +878,10 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
           // split-major: the splits that hold keys come first and spread over all workgroups
           const int hh = u % H, sp = u / H;
           if (!pk_attn_unit<QT, FWT>(a, sh, par, a.q, limS[lev], maxS[lev], R, L.Kc, L.Vc, capb, ns, hh, sp, true, P0,
-                                a.partS + ((long)hh * PK_MAXSPLIT + sp) * (RS >> 4) * PK_PART, tag, stage, a.win[lev])) return;
+                                a.partS + ((long)hh * PK_MAXSPLIT + sp) * (RS >> 4) * PK_PART, att_l, tag, stage, a.win[lev])) return;
         }
         PK_NEXT(H * ns);
-        PK_MINE(H * RQ) pk_merge_unit<QT, FWT>(a, sh, maxS[lev], R, u / H * 4, capb, ns, u % H, a.partS, att_l, tag, stage);
+        if (pk_parts(maxS[lev], capb, ns) > 1) PK_MINE(H * RQ) pk_merge_unit<QT, FWT>(a, sh, maxS[lev], R, u / H * 4, capb, ns, u % H, a.partS, att_l, tag, stage);
         PK_NEXT(H * RQ);
       }
       // ---- Wo + residual -> hB (tap: the layer input is what the draft heads of this level start from)
@@ -848,10 +912,10 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
         PK_MINE(H * ns) {
           const int hh = u / ns, sp = u % ns;
           if (!pk_attn_unit<QT, FWT>(a, sh, par, a.q2, limX[lev], maxX[lev], R, L.Km, L.Vm, a.capbM, ns, hh, sp, false, 0,
-                                a.partX + ((long)hh * PK_MAXSPLIT + sp) * (RS >> 4) * PK_PART, tag, stage, 0)) return;
+                                a.partX + ((long)hh * PK_MAXSPLIT + sp) * (RS >> 4) * PK_PART, att2_l, tag, stage, 0)) return;
         }
         PK_NEXT(H * ns);
-        PK_MINE(H * RQ) pk_merge_unit<QT, FWT>(a, sh, maxX[lev], R, u / H * 4, a.capbM, ns, u % H, a.partX, att2_l, tag, stage);
+        if (pk_parts(maxX[lev], a.capbM, ns) > 1) PK_MINE(H * RQ) pk_merge_unit<QT, FWT>(a, sh, maxX[lev], R, u / H * 4, a.capbM, ns, u % H, a.partX, att2_l, tag, stage);
         PK_NEXT(H * RQ);
       }
       // ---- cross output projection + residual -> hC
@@ -922,26 +986,26 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
       const float* ring = st == 0 ? a.ring_hc : a.ring_hv;
       const int rs = st == 0 ? 32 : 16;
       const int Rf_ = a.R[fl], Rc_ = a.R[cl];
-      int F0 = 0x3fffffff;   // first fine position of this pass
-      for (int r = 0; r < Rf_; r++) if (a.pos[fl][r] >= 0) F0 = min(F0, a.pos[fl][r]);
+      const int F0 = firstP[fl];   // first fine position of this pass
       PK_MINE(Rc_) {
-        const int j = a.pos[cl][u];
-        bool ok = pk_wait_stack<FWT, PoolCols>(a, a.hT[st], tagn, stage, Rf_);
-        for (int k = 0; k < PoolCols::count(d, 0); k += 2) {
+        constexpr int C = FM_TR_COLS;
+        const int j = firstP[cl] + u <= maxS[cl] ? firstP[cl] + u : -1;      // active rows are the first ones, positions side by side
+        const int p0 = 3 * j - 2;      // positions p0 .. p0 + 2; j < 0: an inactive row, zeros
+        float was[3][C], now[3][C];
+#pragma unroll
+        for (int q = 0; q < 3; q++)
+#pragma unroll
+          for (int k = 0; k < C; k++) was[q][k] = ring[(long)((p0 + q) & (rs - 1)) * d + min(PoolCols::col(threadIdx.x, k), d - 1)];
+        const bool ok = pk_wait_stack<FWT, PoolCols>(a, a.hT[st], tagn, stage, Rf_, [&](int q) { return min(max(p0 + q - F0, 0), Rf_ - 1); }, now);
+#pragma unroll
+        for (int k = 0; k < C; k += 2) {
           const int i = PoolCols::col(threadIdx.x, k);   // two adjacent columns per thread
           float s0 = 0.f, s1 = 0.f;
-          if (j >= 0 && i < d) {
-            for (int p = 3 * j - 2; p <= 3 * j; p++) {
-              if (p < 0) continue;
-              if (p >= F0) {
-                unsigned raw[2];
-                const u64* src = a.hT[st] + (long)(p - F0) * d + i;
-                ok = pk_fetch<2>(raw, 2, true, tagn, [&](int t) { return src + t; }, a, stage) && ok;
-                s0 += __uint_as_float(raw[0]); s1 += __uint_as_float(raw[1]);
-              } else {
-                s0 += ring[(long)(p & (rs - 1)) * d + i]; s1 += ring[(long)(p & (rs - 1)) * d + i + 1];
-              }
-            }
+#pragma unroll
+          for (int q = 0; q < 3; q++) {
+            const bool in = p0 + q >= F0, on = j >= 0 && p0 + q >= 0;
+            s0 += !on ? 0.f : in ? now[q][k] : was[q][k];
+            s1 += !on ? 0.f : in ? now[q][k + 1] : was[q][k + 1];
           }
           if (i < d) pk_st(a.pool + (long)st * 8 * d + (long)u * (d >> 1) + (i >> 1), pk_pack(s0 / 3.0f, s1 / 3.0f), tagn);
         }
@@ -965,24 +1029,30 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
       const int rs = st == 2 ? 8 : 16;
       const int Rf_ = a.R[fl], Rc_ = a.R[cl];
       PK_MINE(Rf_) {
-        const int p = a.pos[fl][u];
-        int slot = -1;
-        if (p >= 0) for (int r = 0; r < Rc_; r++) if (a.pos[cl][r] == p / 3) slot = r;
-        bool ok = pk_wait_stack<FWT, SkipCols>(a, a.hT[st], tagn, stage, Rc_);
-        for (int k = 0; k < SkipCols::count(d, threadIdx.x); k++) {
+        constexpr int C = FM_TR_COLS;
+        const int p = firstP[fl] + u <= maxS[fl] ? firstP[fl] + u : -1;      // active rows are the first ones, positions side by side
+        const int slot = p / 3 - firstP[cl];                                  // row of the coarse output, below 0: it is in the ring
+        const int n = SkipCols::count(d, threadIdx.x);
+        // what has been there since the level's first half leaves in front of the wait
+        const agent_buf_t kb = agent_buf(skip, Rf_ * d * 8);
+        u32x2 kept[C];
+        float was[C], now[1][C], gain[C];
+#pragma unroll
+        for (int k = 0; k < C; k++) {
+          const int i = min(SkipCols::col(threadIdx.x, k), d - 1);
+          kept[k] = ld_agent2(kb, (u * d + i) * 8);
+          was[k] = ring[(long)((max(p, 0) / 3) & (rs - 1)) * d + i];
+          gain[k] = a.layers[ln].g1[i];
+        }
+        bool ok = pk_wait_stack<FWT, SkipCols>(a, a.hT[st], tagn, stage, Rc_, [&](int) { return min(max(slot, 0), Rc_ - 1); }, now);
+#pragma unroll
+        for (int k = 0; k < C; k++) {
+          if (k >= n) break;
           const int i = SkipCols::col(threadIdx.x, k);
-          unsigned r0[1], r1[1];
-          ok = pk_fetch<1>(r0, 1, true, tag_skip, [&](int) { return skip + (long)u * d + i; }, a, stage) && ok;
-          float v = __uint_as_float(r0[0]);
-          if (p >= 0) {
-            if (slot >= 0) {
-              ok = pk_fetch<1>(r1, 1, true, tagn, [&](int) { return a.hT[st] + (long)slot * d + i; }, a, stage) && ok;
-              v += __uint_as_float(r1[0]);
-            } else {
-              v += ring[(long)((p / 3) & (rs - 1)) * d + i];
-            }
-          }
-          pk_put_row(v, true, u, i, d, a.hA + (long)ln * RS * d, a.xA + (long)ln * RH * d, a.sA + (long)ln * RS * (d >> 4), a.layers[ln].g1[i], tagn);
+          unsigned raw[1] = {kept[k][0]};
+          if (!__all(kept[k][1] == tag_skip)) ok = pk_fetch<1>(raw, 1, true, tag_skip, [&](int) { return skip + (long)u * d + i; }, a, stage) && ok;
+          const float v = __uint_as_float(raw[0]) + (p < 0 ? 0.f : slot >= 0 ? now[0][k] : was[k]);
+          pk_put_row(v, true, u, i, d, a.hA + (long)ln * RS * d, a.xA + (long)ln * RH * d, a.sA + (long)ln * RS * (d >> 4), gain[k], tagn);
         }
         if (!ok) sh.bad = 1;
       }

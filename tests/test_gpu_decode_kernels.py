@@ -174,3 +174,16 @@ def test_recorded_steps_follow_buffers_and_settings(name):
     assert stepped(cfg.faces, many[:2]) == drawn and drawn != whole
     fm.set_sampling(0.0, 0)
     assert mesh(cfg.faces) == whole and stepped(cfg.faces, many[:2]) == whole
+
+
+@pytest.mark.parametrize("drafts", ["native", "none"])
+@pytest.mark.parametrize("m,n", [(9, 9), (15, 18)])
+def test_single_launch_past_the_first_group_of_keys(m, n, drafts):
+    """The single-launch kernel from a context that one split holds (128 keys, no merge) to one that two do, one and two row groups, blocks and
+    token by token (passes whose vertex and face levels have no row)."""
+    from parity_harness import lockstep
+    cfg = _cfg("one_launch_parts%d%s" % (n, drafts), 128, 2, 60, "bf16", 1, 17, 2, m, n)
+    print("case", cfg.name, flush=True)
+    rep, streams, fm = lockstep(cfg, cfg.faces, TOL[cfg.dtype], drafts=drafts)
+    print(rep, flush=True)
+    assert len(streams[0]) == 9 * cfg.faces > 128 + 18 and fm.verify_path() == 1
