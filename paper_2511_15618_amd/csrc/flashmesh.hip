@@ -428,7 +428,7 @@ int verify_impl(fm_ctx* c, const int32_t* block_tok, const int32_t* block_len, f
   verify_setup<T>(c, block_tok, block_len, !c->persist);
   if (c->persist) {
     // the whole backbone forward in one launch (see fm_kernels_persist.h)
-    c->pk.logits = lg;
+    c->pk.logits = (pk_f_t)lg;
     hipLaunchKernelGGL(pk_kernel(c->pk), dim3(PK_NWG), dim3(256), c->pk_lds, c->stream, c->pk);
   } else {
     forward<T>(c, lg);
@@ -753,29 +753,12 @@ int build_persist(fm_ctx* c) {
   const size_t d = D.d;
   PkArgs& a = c->pk;
   memset(&a, 0, sizeof a);
-  std::vector<PkLayer> hl;
   for (int st = 0; st < 5; st++) {
-    a.first[st] = (int)hl.size();
+    a.first[st] = a.n_layers;
     a.count[st] = (int)c->stacks[st].size();
-    for (size_t i = 0; i < c->stacks[st].size(); i++) {
-      const Layer& L = c->stacks[st][i];
-      PkLayer p{};
-      p.g1 = (pk_cf_t)L.g1; p.g2 = (pk_cf_t)L.g2; p.g3 = (pk_cf_t)L.g3;
-      p.wqkv = (pk_cw_t)L.wqkv; p.wo = (pk_cw_t)L.wo; p.cq = (pk_cw_t)L.cq; p.co = (pk_cw_t)L.co;
-      p.w1 = (pk_cw_t)L.w1; p.w2 = (pk_cw_t)L.w2;
-      p.Kc = (pk_w_t)L.Kc; p.Vc = (pk_w_t)L.Vc; p.Km = (pk_cw_t)L.Km; p.Vm = (pk_cw_t)L.Vm;
-      p.level = L.level;
-      p.last = i + 1 == c->stacks[st].size();
-      p.tap = p.last && (st == 2 || st == 3 || st == 4);
-      p.stack = st;
-      hl.push_back(p);
-    }
+    a.n_layers += a.count[st];
+    a.gain1[st] = (pk_cf_t)c->stacks[st][0].g1;
   }
-  a.n_layers = (int)hl.size();
-  PkLayer* dl;
-  TRY(dalloc(c, &dl, hl.size()));
-  if (hipMemcpy(dl, hl.data(), hl.size() * sizeof(PkLayer), hipMemcpyHostToDevice) != hipSuccess) return fail(c, FM_EHIP, "layer table copy failed");
-  a.layers = dl;
   a.D = D; a.ff = c->ff; a.eps = c->cfg.rms_eps;
   a.R[0] = D.Bm; a.R[1] = D.VB; a.R[2] = D.FB;
   const int caps[3] = {D.capc, D.capv, D.capf};
@@ -791,32 +774,78 @@ int build_persist(fm_ctx* c) {
   for (int l = 0; l < 3; l++) {
     a.capb[l] = (caps[l] + 31) / 32;
     a.nsplit[l] = splits(a.capb[l]);
-    a.pos[l] = c->pos[l]; a.limx[l] = c->limx[l]; a.cs[l] = c->cs[l];
-    a.win[l] = level_window(c, l);
+    a.pos[l] = (pk_ci_t)c->pos[l];
   }
   a.capbM = (D.M + 31) / 32;
   a.nsplitM = splits(a.capbM);
-  a.vtok = c->st.vtok;
-  a.ring_hc = c->ring_hc; a.ring_hv = c->ring_hv; a.ring_yf = c->ring_yf; a.ring_yv = c->ring_yv;
-  a.tap[0] = c->tap_c; a.tap[1] = c->tap_v; a.tap[2] = c->tap_f;
-  a.emb = (const f16_t*)c->emb; a.short_cv = (const f16_t*)c->short_cv; a.short_vf = (const f16_t*)c->short_vf;
-  a.lm = (const f16_t*)c->lm; a.gf = c->gf; a.logits = c->logits;
-  const size_t nl = hl.size();
+  a.vtok = (pk_ci_t)c->st.vtok;
+  a.ring[0] = (pk_f_t)c->ring_hc; a.ring[1] = (pk_f_t)c->ring_hv; a.ring[2] = (pk_f_t)c->ring_yf; a.ring[3] = (pk_f_t)c->ring_yv;
+  a.emb = (pk_cw_t)c->emb; a.logits = (pk_f_t)c->logits;
+  const size_t nl = a.n_layers;
   // GEMM inputs (fp32 residual stream and its half-pair copy, attention outputs, FFN hidden): one region per layer,
   // so that no address is written twice within a launch
   // rows per exchange region: one group of 16, or two when the block is longer than 16 tokens
   a.RS = D.Bm > 16 ? 32 : 16;
   const size_t RS = a.RS, RH = RS / 2, RG = RS / 16;
-  TRY(dalloc(c, &a.hA, (nl + 1) * RS * d)); TRY(dalloc(c, &a.hB, nl * RS * d)); TRY(dalloc(c, &a.hC, nl * RS * d));
-  for (int i = 0; i < 4; i++) TRY(dalloc(c, &a.hT[i], RS * d));
-  TRY(dalloc(c, &a.xA, (nl + 1) * RH * d)); TRY(dalloc(c, &a.xB, nl * RH * d)); TRY(dalloc(c, &a.xC, nl * RH * d));
-  TRY(dalloc(c, &a.sA, (nl + 1) * RS * d / 16)); TRY(dalloc(c, &a.sB, nl * RS * d / 16)); TRY(dalloc(c, &a.sC, nl * RS * d / 16));
-  TRY(dalloc(c, &a.q, RH * d)); TRY(dalloc(c, &a.att, nl * RH * d)); TRY(dalloc(c, &a.q2, RH * d));
-  TRY(dalloc(c, &a.att2, nl * RH * d));
-  TRY(dalloc(c, &a.pool, 2 * 8 * d)); TRY(dalloc(c, &a.mid, nl * RH * c->ff));
+  u64 *h[3], *x[3], *sq[3], *hT[4], *q[2], *att[2], *part[2], *mid;      // index 0: in front of the self-attention, 1: the cross-attention, 2: the FFN
+  for (int i = 0; i < 3; i++) {
+    const size_t n = nl + (i == 0);
+    TRY(dalloc(c, &h[i], n * RS * d)); TRY(dalloc(c, &x[i], n * RH * d)); TRY(dalloc(c, &sq[i], n * RS * d / 16));
+  }
+  a.h = (pk_x_t)h[0]; a.x = (pk_x_t)x[0]; a.s = (pk_x_t)sq[0];
+  for (int i = 0; i < 4; i++) { TRY(dalloc(c, &hT[i], RS * d)); a.hT[i] = (pk_x_t)hT[i]; }
+  for (int i = 0; i < 2; i++) {      // queries (half pairs), attention outputs, parts of the splits
+    TRY(dalloc(c, &q[i], RH * d)); TRY(dalloc(c, &att[i], nl * RH * d)); TRY(dalloc(c, &part[i], (size_t)D.H * PK_MAXSPLIT * RG * PK_PART));
+  }
+  TRY(dalloc(c, &a.pool, 2 * 8 * d)); TRY(dalloc(c, &mid, nl * RH * c->ff));
   TRY(dalloc(c, &a.newK, (size_t)D.H * RS * 32)); TRY(dalloc(c, &a.newV, (size_t)D.H * RS * 32));
-  TRY(dalloc(c, &a.partS, (size_t)D.H * PK_MAXSPLIT * RG * PK_PART)); TRY(dalloc(c, &a.partX, (size_t)D.H * PK_MAXSPLIT * RG * PK_PART));
   TRY(dalloc(c, &a.w2part, (d / 16) * RG * 3 * 256));
+  {
+    std::vector<PkRecord> recs;
+    auto put = [&](std::initializer_list<const volatile void*> p) {
+      PkRecord r{};
+      int k = 0;
+      for (const volatile void* v : p) r.p[k++] = (u64)v;
+      recs.push_back(r);
+    };
+    float* ring[4] = {c->ring_hc, c->ring_hv, c->ring_yf, c->ring_yv};
+    float* tap[3] = {c->tap_c, c->tap_v, c->tap_f};
+    auto* newK = (u64*)a.newK;
+    auto* newV = (u64*)a.newV;
+    size_t l = 0;
+    for (int st = 0; st < 5; st++) {
+      const int lev = kStackLevel[st];
+      for (size_t i = 0; i < c->stacks[st].size(); i++, l++) {
+        const Layer& L = c->stacks[st][i];
+        const bool last = i + 1 == c->stacks[st].size(), out = last && st < 4;      // a stack output feeds a level transition, not a norm
+        auto H = [&](int k, size_t n) { return h[k] + n * RS * d; };
+        auto X = [&](int k, size_t n) { return x[k] + n * RH * d; };
+        auto Q = [&](int k, size_t n) { return sq[k] + n * RS * d / 16; };
+        u64 *A0 = att[0] + l * RH * d, *A1 = att[1] + l * RH * d, *mi = mid + l * RH * c->ff;
+        auto sizes = [](int ns, int capb) { return (const void*)(((u64)(unsigned)capb << 32) | (unsigned)ns); };
+        put({L.wqkv, X(0, l), Q(0, l), L.Kc, q[0], newK, newV, c->cs[lev], L.Vc});
+        put({L.Kc, L.Vc, q[0], part[0], A0, sizes(a.nsplit[lev], a.capb[lev]), (const void*)(u64)level_window(c, lev)});
+        put({L.wo, A0, nullptr, H(0, l), H(1, l), X(1, l), Q(1, l), L.g2, last && st >= 2 ? tap[lev] : nullptr});
+        put({L.cq, X(1, l), Q(1, l), nullptr, q[1]});
+        put({L.Km, L.Vm, q[1], part[1], A1, sizes(a.nsplitM, a.capbM), nullptr});
+        put({L.co, A1, nullptr, H(1, l), H(2, l), X(2, l), Q(2, l), L.g3, nullptr});
+        put({L.w1, X(2, l), Q(2, l), nullptr, mi});
+        put({L.w2, mi, nullptr, H(2, l), out ? hT[st] : H(0, l + 1), out ? nullptr : X(0, l + 1), Q(0, l + 1),
+             last ? c->gf : c->stacks[st][i + 1].g1, out ? ring[st] : nullptr});
+      }
+    }
+    for (int st = 0; st < 2; st++) {
+      const size_t n = a.first[st + 1];
+      put({st == 0 ? c->short_cv : c->short_vf, (u64*)a.pool + (size_t)st * 8 * d, nullptr, nullptr, h[0] + n * RS * d, x[0] + n * RH * d, sq[0] + n * RS * d / 16,
+           c->stacks[st + 1][0].g1, nullptr});
+    }
+    put({c->lm, x[0] + nl * RH * d, sq[0] + nl * RS * d / 16});
+    a.n_records = (int)recs.size();
+    uint8_t* dev;
+    TRY(dalloc(c, &dev, (recs.size() * sizeof(PkRecord) + 1023) / 1024 * 1024));
+    if (hipMemcpy(dev, recs.data(), recs.size() * sizeof(PkRecord), hipMemcpyHostToDevice) != hipSuccess) return fail(c, FM_EHIP, "record table copy failed");
+    a.records = (const PK_GLOBAL PkRecord*)dev;
+  }
   TRY(dalloc(c, &a.abort_word, 16));
   if (hipMemset(a.abort_word + 1, 0xFF, 4) != hipSuccess) return fail(c, FM_EHIP, "hipMemset failed");
   a.run_flag = c->st.alive;

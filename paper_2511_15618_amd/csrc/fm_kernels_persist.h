@@ -39,26 +39,31 @@ typedef unsigned long long u64;
 typedef const PK_GLOBAL f16_t* pk_cw_t;     // weights, condition-memory caches
 typedef PK_GLOBAL f16_t* pk_w_t;            // self-attention caches (appended to by this kernel)
 typedef const PK_GLOBAL float* pk_cf_t;     // gains
+typedef PK_GLOBAL float* pk_f_t;            // rings, logits
+typedef const PK_GLOBAL int* pk_ci_t;
+typedef PK_GLOBAL u64* pk_x_t;              // exchange buffers
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+// The kernel's arguments where they lie: reads of them are scalar loads, and no store of the kernel makes the compiler read them again.
+#define PK_CONST const __attribute__((address_space(4)))
 
-struct PkLayer {
-  pk_cf_t g1, g2, g3;
-  pk_cw_t wqkv, wo, cq, co, w1, w2;   // tiled; wqkv with rotary pairs inside one tile
-  pk_w_t Kc, Vc;
-  pk_cw_t Km, Vm;
-  int level;      // 0 coordinate, 1 vertex, 2 face
-  int tap;        // store the layer input to the level's tap ring (input of the last layer of a stack)
-  int last;       // last layer of its stack: output goes to hT[stack] and to the stack's ring
-  int stack;      // 0 cpre, 1 vpre, 2 face, 3 vpost, 4 cpost
-};
+// The stages of a block in their order, then what stands between stacks, then the output head.
+enum { PK_QKV = 0, PK_ATT, PK_MRG, PK_WO, PK_CQ, PK_XATT, PK_XMRG, PK_CO, PK_W1, PK_W2, PK_POOL, PK_SHORT, PK_UP, PK_LM };
 
-// Width of the model: FWT fragments of 32 per wave in a GEMM over d, i.e. d = 128 FWT, known to the compiler for some widths (pk_kernel;
-// the hidden width is then 4 d), read from the arguments for the others (FWT = 0).
-struct PkArgs;
-template <int FWT> __device__ __forceinline__ int pk_d(const PkArgs& a);
+// Pointers of a stage, laid out by the host; a workgroup holds all records in LDS (from memory, each would be a cold trip in front of the cold
+// trip to what it points at).  Eight per layer: q,k,v; self-attention; self output; cross query; cross-attention; cross output; FFN up;
+// FFN down; behind the layers the two shortenings and the output head.
+//   GEMM: 0 weights, 1 input rows, 2 their sums of squares (null: no norm), 3 residual stream that is added, 4 output, and for rows that go on 5 their copy
+//     for the norm behind them (null: none), 6 its sums of squares, 7 its gain, 8 ring (null: none).
+//   q,k,v: 4 queries, 5, 6 new keys and values, 3, 8 caches, 7 rotary table.
+//   attention: 0, 1 keys and values, 2 queries, 3 parts, 4 output, 5 splits and capacity in blocks, 6 sliding window (0 = none; the caches of the
+//     self-attention are then rings of that capacity).
+struct PkRecord { u64 p[9]; };
+#define PK_RECS 8
+#define PK_MAX_RECORDS (61 * PK_RECS + 3)      // layers + 2 fit the six bits of a tag
 
 struct PkArgs {
-  const PkLayer* layers;
-  int n_layers;
+  const PK_GLOBAL PkRecord* records;      // [n_records], readable up to whole KiB
+  int n_layers, n_records;
   int first[5], count[5];
   Dims D;
   int ff;
@@ -67,28 +72,19 @@ struct PkArgs {
   int RS;                   // rows the exchange buffers hold per region: 16, or 32 when the coordinate level has two row groups
   int capb[3], capbM;       // cache capacity in 32-key blocks per level / of the condition memory
   int nsplit[3], nsplitM;   // launch-time split counts (fixed partition of the key axis)
-  int win[3];               // sliding window per level (0 = none); the self-attention caches are then rings of capb blocks
-  const int* pos[3];
-  const int* limx[3];
-  const float2* cs[3];
-  const int* vtok;
-  float *ring_hc, *ring_hv, *ring_yf, *ring_yv;
-  float* tap[3];
-  const f16_t *emb, *short_cv, *short_vf, *lm;
-  const float* gf;
-  float* logits;
-  // exchange buffers (u64 = payload | tag << 32)
-  u64 *hA, *hB, *hC;        // [layers + 1][RS][d]: one region per layer, written once per launch
-  u64* hT[4];               // outputs of cpre, vpre, face, vpost  [RS][d]
-  u64 *xA, *xB, *xC;        // [layers (+ 1)][RS][d/2]: half(row of hA, hB, hC times the gain of the norm that reads it), pairs
-  u64 *sA, *sB, *sC;        // [layers (+ 1)][RS][d/16]: sums of squares of 16 columns of those rows
-  u64 *q, *q2;              // [RS][d/2] rotated queries of the self- / cross-attention (half pairs)
-  u64 *att, *att2;          // [layers][RS][d/2] attention outputs
-  u64* pool;                // [2][16][d/2] pooled groups before the two shortening projections (coarse rows: at most 9)
-  u64* mid;                 // [layers][RS][ff/2]
-  u64 *newK, *newV;         // [H][RS][32]
-  u64 *partS, *partX;       // [H][PK_MAXSPLIT][RS/16][PK_PART]
-  u64* w2part;              // [d/16][RS/16][3][256]: partial tiles of the K-quarters 1..3 of the FFN down projection
+  pk_ci_t pos[3];
+  pk_ci_t vtok;
+  pk_f_t ring[4];           // outputs of cpre, vpre, face, vpost by position
+  pk_cw_t emb;
+  pk_cf_t gain1[5];         // gain of the first norm of each stack
+  pk_f_t logits;
+  // Exchange buffers (u64 = payload | tag << 32) that the stages outside of the records name:
+  pk_x_t h, x, s;           // rows in front of a layer [layers + 1][RS][d]: one region per layer, written once per launch; half(row times the gain of the
+                            // norm that reads it) [layers + 1][RS][d/2], pairs; sums of squares of 16 columns of those rows [layers + 1][RS][d/16]
+  pk_x_t hT[4];             // outputs of cpre, vpre, face, vpost  [RS][d]
+  pk_x_t pool;              // [2][16][d/2] pooled groups before the two shortening projections (coarse rows: at most 9)
+  pk_x_t newK, newV;        // [H][RS][32]
+  pk_x_t w2part;            // [d/16][RS/16][3][256]: partial tiles of the K-quarters 1..3 of the FFN down projection
   const unsigned* epoch_word;  // passes so far, counted by k_verify_setup
   u64 timeout_ticks;        // bound of every wait (100 MHz wall clock)
   unsigned test_skew;       // test hook: added to the tag the embedding publishes, so that nothing downstream ever arrives
@@ -98,8 +94,11 @@ struct PkArgs {
   int prof_stage;           // stage whose inner phases are timed into prof[600..]
   u64* prof;                // optional [1 + stages]: earliest start, latest completion per stage (wall clock ticks)
 };
+typedef PK_CONST PkArgs PkA;
 
-template <int FWT> __device__ __forceinline__ int pk_d(const PkArgs& a) { return FWT ? FWT * 128 : a.D.d; }
+// Width of the model: FWT fragments of 32 per wave in a GEMM over d, i.e. d = 128 FWT, known to the compiler for some widths (pk_kernel;
+// the hidden width is then 4 d), read from the arguments for the others (FWT = 0).
+template <int FWT> __device__ __forceinline__ int pk_d(PkA& a) { return FWT ? FWT * 128 : a.D.d; }
 
 // Exchanges between the waves of a workgroup.  Two sets, used by the GEMM and attention units in turn: a unit writes its set, passes its one
 // barrier and reads; who writes the same set two units later has passed the barrier between, so all have read.
@@ -110,29 +109,47 @@ struct PkShared {
   __align__(16) float lo[2][4][16 * QT][68];
   float lm[2][4][16 * QT], ll[2][4][16 * QT];
   int bad;                  // raised by a wave whose wait gave up
+  __align__(16) PkRecord rec[(PK_MAX_RECORDS * sizeof(PkRecord) + 1023) / 1024 * 1024 / sizeof(PkRecord) + 1];
 };
 
-// Barrier at which all waves learn whether one of them has given up.  (__syncthreads_or is three barriers and two trips to LDS, in
-// every unit: steps of 755 us at d = 512 and 1817 us at d = 1024 become 728 and 1755.)
-template <class SH>
-__device__ __forceinline__ bool pk_sync(SH& sh, bool good) {
-  if (!good) sh.bad = 1;
-  __syncthreads();
-  return sh.bad == 0;
+// Has a wave of this workgroup given up?  What a unit publishes after that is noise under a valid tag: the abort word is up, so the pass accepts and
+// commits nothing, and what it wrote to caches and rings belongs to positions that are not committed.
+template <class SH> __device__ __forceinline__ bool pk_bad(const SH& sh) { return __builtin_amdgcn_readfirstlane(sh.bad) != 0; }
+// a record, lane k has pointer k; and one of its pointers, uniform
+template <class SH> __device__ __forceinline__ u64 pk_record(const SH& sh, int i) { return sh.rec[i].p[min((int)(threadIdx.x & 63), 8)]; }
+template <class P> __device__ __forceinline__ P pk_ptr(u64 rec, int k) {
+  const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)rec, k), hi = __builtin_amdgcn_readlane((int)(unsigned)(rec >> 32), k);
+  return (P)((u64)hi << 32 | lo);
+}
+// The thread's number, new to the compiler at each call: what a unit derives from it (offsets, row and column of a tile) is not computed ahead
+// of the loop over the stages and kept for all units at once.
+__device__ __forceinline__ int pk_tid() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
 }
 
-__device__ __forceinline__ u64 pk_ld(const u64* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ void pk_st(u64* p, unsigned payload, unsigned tag) {
+// Barrier of a unit.  Whether a wave has given up is looked at behind the unit's results (pk_bad): an LDS trip that nobody waits for.  (In front of
+// them: steps of 595 us at d = 512 and 1484 at d = 1024 instead of 590 and 1463.)
+template <class SH>
+__device__ __forceinline__ void pk_sync(SH& sh, bool good) {
+  if (!good) sh.bad = 1;
+  __syncthreads();
+}
+
+__device__ __forceinline__ u64 pk_ld(pk_x_t p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void pk_st(pk_x_t p, unsigned payload, unsigned tag) {
   __hip_atomic_store(p, ((u64)tag << 32) | payload, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void pk_stf(u64* p, float v, unsigned tag) { pk_st(p, __float_as_uint(v), tag); }
+__device__ __forceinline__ void pk_stf(pk_x_t p, float v, unsigned tag) { pk_st(p, __float_as_uint(v), tag); }
+__device__ __forceinline__ agent_buf_t pk_buf(pk_x_t p, int bytes) { return agent_buf((const void*)p, bytes); }
 __device__ __forceinline__ unsigned pk_pack(float lo, float hi) {
   const f16_t a = (f16_t)lo, b = (f16_t)hi;
   return (unsigned)__builtin_bit_cast(unsigned short, a) | ((unsigned)__builtin_bit_cast(unsigned short, b) << 16);
 }
-__device__ __forceinline__ bool pk_expired(const PkArgs& a, u64 t0, int stage) {
+__device__ __forceinline__ bool pk_expired(PkA& a, u64 t0, int stage) {
   // every waiter that gives up records its stage; the smallest one is where the chain broke
-  if (__hip_atomic_load(a.abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+  if (__builtin_amdgcn_readfirstlane((int)__hip_atomic_load(a.abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
     atomicMin(a.abort_word + 1, (unsigned)stage);
     return true;
   }
@@ -148,7 +165,7 @@ __device__ __forceinline__ bool pk_expired(const PkArgs& a, u64 t0, int stage) {
 // All loads are issued before any is checked; the whole set is re-read until every tag matches.  (Watching one element first costs a
 // second trip once it is there: 40 us of a step at d = 1024.  The abort word is another trip, so it is looked at every 64 rounds only.)
 template <int N, class F>
-__device__ __forceinline__ bool pk_fetch(unsigned (&out)[N], int n, bool active, unsigned tag, F addr, const PkArgs& a, int stage) {
+__device__ __forceinline__ bool pk_fetch(unsigned (&out)[N], int n, bool active, unsigned tag, F addr, PkA& a, int stage) {
   const u64 t0 = wall_clock64();
   int it = 0;
   while (true) {
@@ -194,10 +211,10 @@ __device__ __forceinline__ bool pk_fetch(unsigned (&out)[N], int n, bool active,
 // got[k].  (Each element in a trip of its own: upsampling 4.4 us
 // instead of 2.2 at d = 512, 8.0 instead of 3.4 at 1024; pooling 4.9 instead of 2.9 there.)
 template <int FWT, class COLS, int OWN, class ROW>
-__device__ __forceinline__ bool pk_wait_stack(const PkArgs& a, const u64* hT, unsigned tag, int stage, int rows, ROW row, float (&got)[OWN][FM_TR_COLS]) {
+__device__ __forceinline__ bool pk_wait_stack(PkA& a, pk_x_t hT, unsigned tag, int stage, int rows, ROW row, float (&got)[OWN][FM_TR_COLS]) {
   const int d = pk_d<FWT>(a);
   const int n = COLS::count(d, threadIdx.x);
-  const agent_buf_t hb = agent_buf(hT, rows * d * 8);
+  const agent_buf_t hb = pk_buf(hT, rows * d * 8);
   u32x2 own[OWN][FM_TR_COLS];
   bool ok = true;
   for (int r0 = 0; r0 < rows && ok; r0 += 16) {               // a second row group is written by units of its own
@@ -242,7 +259,7 @@ __device__ __forceinline__ bool pk_wait_stack(const PkArgs& a, const u64* hT, un
 // ------------------------------------------------------------------------------------------
 // GEMM tile: C[16 rows x 16 cols] = A[16 x K] * W_tile^T, four waves split K (K <= 1024).  Behind the one barrier of the unit every wave
 // owns a quarter of the result: wave w of lane (g, col) has row g*4 + w, column col in `result`.
-// A is a half-pair exchange buffer [16][K/2].  NORM: its rows are half(x * gain), written so by the producers of the residual stream
+// A is a half-pair exchange buffer [16][K/2].  sq not null: its rows are half(x * gain), written so by the producers of the residual stream
 // together with the sums of squares of every 16 columns, sq[row][K/16]; the row factor 1/rms goes onto the result.
 // (One wave doing the whole epilogue, and gain and sums computed here: steps of 707 us at d = 512 and 1692 us at d = 1024, against 644 and
 // 1526 with the merge below.)
@@ -251,32 +268,39 @@ __device__ __forceinline__ bool pk_wait_stack(const PkArgs& a, const u64* hT, un
 // tagged half pairs, i.e. two 16-byte agent-scope loads.  No LDS staging, no barrier before the multiplication;
 // the tags are checked per lane and the whole set is re-read until complete.
 // ------------------------------------------------------------------------------------------
-template <int FWT, bool NORM, class SH>
-__device__ __forceinline__ bool pk_gemm_tile(const PkArgs& a, SH& sh, int& par, pk_cw_t Wt, int KT, const u64* A,
-                                             unsigned tagA, const u64* sq, int R, float& result, int stage, int lda = 0) {
+template <int FWT> struct PkWeights { f16x8 f[FWT ? FWT : 8]; };      // a wave's fragments of a tile
+template <int FWT>
+__device__ __forceinline__ void pk_weights(PkWeights<FWT>& w, pk_cw_t Wt, int KT) {
+  const int tid = pk_tid(), wave = __builtin_amdgcn_readfirstlane(tid >> 6), FW = FWT ? FWT : KT >> 2;
+  const pk_cw_t p = Wt + (long)wave * FW * 512;
+#pragma unroll
+  for (int f = 0; f < (FWT ? FWT : 8); f++) {
+    const int o = (f * 64 + (tid & 63)) * 8;
+    if constexpr (FWT > 0) w.f[f] = *(const PK_GLOBAL f16x8*)(p + o);
+    else w.f[f] = __builtin_bit_cast(f16x8, __builtin_amdgcn_raw_buffer_load_b128(agent_buf((const void*)p, FW * 1024), o * 2, 0, 0));      // fragments past the last are zeros
+  }
+}
+template <int FWT, class SH>
+__device__ __forceinline__ void pk_gemm_tile(PkA& a, SH& sh, int& par, const PkWeights<FWT>& wt, int KT, pk_x_t A, int lda,
+                                             unsigned tagA, pk_x_t sq, int R, float& result, int stage) {
   constexpr int NL = 2;       // 16-byte loads per fragment and lane
   constexpr int EF = 16;      // tagged elements (half pairs) per fragment row
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const bool norm = sq != nullptr;
+  const int tid = pk_tid(), wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int r = lane & 15, g = lane >> 4;
   const bool on = r < R;
   constexpr int NF = FWT ? FWT : 8;
   const int FW = FWT ? FWT : KT >> 2;      // fragments per wave (host guarantees KT % 4 == 0, KT <= 32)
   const int K = FW * 128;
-  if (lda == 0) lda = K >> 1;
   par ^= 1;
   f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
-  // weights go out before the wait for the activations: they depend on nothing
-  f16x8 wf[NF];
-#pragma unroll
-  for (int f = 0; f < NF; f++)
-    if (f < FW) wf[f] = *(const PK_GLOBAL f16x8*)(Wt + ((long)(wave * FW + f) * 64 + lane) * 8);
   // this wave's part of the rows: element (wave*FW + f)*EF + g*(EF/4) of row r is where fragment f starts; rows past the last lie outside the
   // buffer and read 0 (a branch around every load instead: step of d = 1024 1810 -> 1907 us, d = 512 761 -> 805)
-  const agent_buf_t Ab = agent_buf(A, ((R - 1) * lda + KT * EF) * 8);
+  const agent_buf_t Ab = pk_buf(A, ((R - 1) * lda + FW * 4 * EF) * 8);
   const int mine = on ? (r * lda + (wave * FW) * EF + g * (EF / 4)) * 8 : 1 << 30;
   // sums of squares of the columns of this K-quarter: pair p of 16-column sums belongs to fragment p, lane (r, g) takes p = g and g + 4
-  const agent_buf_t Sb = agent_buf(NORM ? sq : A, NORM ? R * FW * 8 * 8 : 0);
-  const bool son[2] = {on && g < FW, on && g + 4 < FW};
+  const agent_buf_t Sb = pk_buf(norm ? sq : A, norm ? R * FW * 8 * 8 : 0);      // no norm: nothing to read, zeros that nobody looks at
+  const bool son[2] = {norm && on && g < FW, norm && on && g + 4 < FW};
   int so[2];
 #pragma unroll
   for (int j = 0; j < 2; j++) so[j] = son[j] ? ((r * 4 + wave) * FW + g + 4 * j) * 16 : 1 << 30;
@@ -289,30 +313,26 @@ __device__ __forceinline__ bool pk_gemm_tile(const PkArgs& a, SH& sh, int& par, 
   // fragments again once those show the tag: waiting costs the memory system 64 small loads per round, not 32 KiB (reading all
   // again instead, steps in us: d = 1024 1893 -> 1905, d = 512 800 -> 810; for up to four rows only: 1904, 805).
   const int fs_ = min(lane >> 3, FW - 1), hs_ = (lane >> 2) & 1, rs_ = max(R - 1 - (lane & 3), 0);
-  const u64* watched = A + (long)(wave * FW) * EF + (long)rs_ * lda + fs_ * EF + hs_ * (EF / 2);
+  const pk_x_t watched = A + (long)(wave * FW) * EF + (long)rs_ * lda + fs_ * EF + hs_ * (EF / 2);
+  const float eps = a.eps;
   PK_MARK(1);
   u32x4 v[NF * NL], sv[2];
   while (good) {
     agent_again();
 #pragma unroll
     for (int f = 0; f < NF; f++)
-      if (f < FW)
 #pragma unroll
-        for (int j = 0; j < NL; j++) v[f * NL + j] = ld_agent4(Ab, mine + (f * EF + 2 * j) * 8);
-    if (NORM) {
-      sv[0] = ld_agent4(Sb, so[0]);
-      if (NF > 4) sv[1] = ld_agent4(Sb, so[1]);
-    }
+      for (int j = 0; j < NL; j++) v[f * NL + j] = ld_agent4(Ab, f < FW ? mine + (f * EF + 2 * j) * 8 : 1 << 30);
+    sv[0] = ld_agent4(Sb, so[0]);
+    if (NF > 4) sv[1] = ld_agent4(Sb, so[1]);
     unsigned diff = 0;
 #pragma unroll
     for (int f = 0; f < NF; f++)
       if (f < FW)
 #pragma unroll
         for (int j = 0; j < NL; j++) diff |= (v[f * NL + j][1] ^ tagA) | (v[f * NL + j][3] ^ tagA);
-    if (NORM) {
-      if (son[0]) diff |= (sv[0][1] ^ tagA) | (sv[0][3] ^ tagA);
-      if (NF > 4 && son[1]) diff |= (sv[1][1] ^ tagA) | (sv[1][3] ^ tagA);
-    }
+    if (son[0]) diff |= (sv[0][1] ^ tagA) | (sv[0][3] ^ tagA);
+    if (NF > 4 && son[1]) diff |= (sv[1][1] ^ tagA) | (sv[1][3] ^ tagA);
     if (__all(diff == 0 || !on)) break;
     if ((++it & 63) == 0 && pk_expired(a, t0, stage)) { good = false; break; }
     while (!__all((unsigned)(pk_ld(watched) >> 32) == tagA)) {
@@ -323,12 +343,10 @@ __device__ __forceinline__ bool pk_gemm_tile(const PkArgs& a, SH& sh, int& par, 
   PK_MARK(2);
 #pragma unroll
   for (int f = 0; f < NF; f++) {
-    if (f < FW) {
-      const u32x4 pk = {v[2 * f][0], v[2 * f][2], v[2 * f + 1][0], v[2 * f + 1][2]};
-      acc[f & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, pk), wf[f], acc[f & 1], 0, 0, 0);
-    }
+    const u32x4 pk = {v[2 * f][0], v[2 * f][2], v[2 * f + 1][0], v[2 * f + 1][2]};
+    acc[f & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, pk), wt.f[f], acc[f & 1], 0, 0, 0);
   }
-  if (NORM) {       // what lies outside the buffer has read 0
+  if (norm) {       // what lies outside the buffer has read 0
     float ss = __uint_as_float(sv[0][0]) + __uint_as_float(sv[0][2]);
     if (NF > 4) ss += __uint_as_float(sv[1][0]) + __uint_as_float(sv[1][2]);
     ss = rows_sum(ss);
@@ -337,22 +355,21 @@ __device__ __forceinline__ bool pk_gemm_tile(const PkArgs& a, SH& sh, int& par, 
   acc[0] += acc[1];
 #pragma unroll
   for (int i = 0; i < 4; i++) sh.red[par][wave][i][lane] = acc[0][i];
-  if (!pk_sync(sh, good)) return false;
+  pk_sync(sh, good);
   PK_MARK(3);
-  result = sh.red[par][0][wave][lane] + sh.red[par][1][wave][lane] + sh.red[par][2][wave][lane] + sh.red[par][3][wave][lane];
-  if (NORM) {
-    const int row = g * 4 + wave;
-    const float tot = sh.ssq[par][0][row] + sh.ssq[par][1][row] + sh.ssq[par][2][row] + sh.ssq[par][3][row];
-    result *= 1.0f / sqrtf(tot / (float)K + a.eps);
-  }
-  return true;
+  const int row = g * 4 + wave;
+  float p[4], q[4];
+#pragma unroll
+  for (int k = 0; k < 4; k++) { p[k] = sh.red[par][k][wave][lane]; q[k] = sh.ssq[par][k][row]; }      // one trip to LDS
+  result = p[0] + p[1] + p[2] + p[3];
+  if (norm) result *= rsqrt_f((q[0] + q[1] + q[2] + q[3]) / (float)K + eps);
 }
 
 // Epilogues: a thread has row g*4 + wave (wave, lane as above) and column n = nt*16 + lane%16 of the tile.
 
 // One value of a row of the residual stream: the value, half(value * gain of the norm that reads it) and, per 16 columns, the sum of squares.
 // x null: no norm reads this row.
-__device__ __forceinline__ void pk_put_row(float v, bool on, int row, int n, int d, u64* h, u64* x, u64* sq, float gain, unsigned tag) {
+__device__ __forceinline__ void pk_put_row(float v, bool on, int row, int n, int d, pk_x_t h, pk_x_t x, pk_x_t sq, float gain, unsigned tag) {
   const float xg = v * gain, w = lane_xor1(xg), ss = row16_sum(v * v);
   if (!on) return;
   if (x) {
@@ -362,121 +379,77 @@ __device__ __forceinline__ void pk_put_row(float v, bool on, int row, int n, int
   pk_stf(h + (long)row * d + n, v, tag);
 }
 
-// The residual operand of a tile (complete long before the tile's GEMM input is) is requested at the start of the unit and looked at behind
-// the multiplication; only then, if it was not there yet, it is waited for.
-struct PkOld { u32x2 v; int p; float gain; };
-template <int FWT>
-__device__ __forceinline__ void pk_res_request(const PkArgs& a, int n, const u64* hold, int R, const int* pos, pk_cf_t gain, PkOld& o) {
-  const int d = pk_d<FWT>(a), row = min(((threadIdx.x & 63) >> 4) * 4 + (int)(threadIdx.x >> 6), R - 1);
-  o.v = ld_agent2(agent_buf(hold, R * d * 8), (row * d + n) * 8);
-  o.p = pos[row];
-  o.gain = gain ? gain[n] : 0.f;
-}
-template <int FWT>
-__device__ __forceinline__ bool pk_res_take(const PkArgs& a, int n, const u64* hold, unsigned tag, int R, const PkOld& o, float& old, int stage) {
-  const int d = pk_d<FWT>(a), row = min(((threadIdx.x & 63) >> 4) * 4 + (int)(threadIdx.x >> 6), R - 1);
-  unsigned raw[1] = {o.v[0]};
-  bool ok = true;
-  if (!__all(o.v[1] == tag)) ok = pk_fetch<1>(raw, 1, true, tag, [&](int) { return hold + (long)row * d + n; }, a, stage);
-  old = __uint_as_float(raw[0]);
-  return ok;
-}
-
 // dst[row][n/2] = (c[n], c[n+1]) as halves
-__device__ __forceinline__ void pk_put_half(float v, bool on, int row, int n, u64* dst, int ld2, unsigned tag) {
+__device__ __forceinline__ void pk_put_half(float v, bool on, int row, int n, pk_x_t dst, int ld2, unsigned tag) {
   const float w = lane_xor1(v);
   if (on && (n & 1) == 0) pk_st(dst + (long)row * ld2 + (n >> 1), pk_pack(v, w), tag);
 }
 
 // QKV epilogue.  Tiles of the q and k parts hold 8 rotary pairs: columns 0..7 = dims qd*8.., columns
-// 8..15 = the same dims + 32.  q -> exchange buffer; k, v -> cache (for later passes) and exchange buffers.
-struct PkQkvPre {     // what the QKV epilogue needs besides the tile: requested before the tile's input arrives
-  float2 t;           // rotary (cos, sin) of the thread's pair in its row
-  int p;              // position of that row
-};
-__device__ __forceinline__ void pk_qkv_prefetch(int nt, int d, int R, const int* pos, const float2* cs, PkQkvPre& pre) {
-  const int lane = threadIdx.x & 63, col = lane & 15, rr = min((lane >> 4) * 4 + (int)(threadIdx.x >> 6), R - 1);
-  const int part = (nt * 16) / d, cp = (nt * 16) % d;
-  const int qd = (cp & 63) >> 4;
-  pre.p = pos[rr];
-  pre.t = part < 2 ? cs[(long)rr * 32 + qd * 8 + (col & 7)] : float2{1.f, 0.f};
-}
-template <int QT, int FWT>
-__device__ __forceinline__ void pk_epi_qkv(const PkArgs& a, const PkLayer& L, float v, int nt, unsigned tag, int R,
-                                           const PkQkvPre& pre, int capb, int row0) {
-  const int lane = threadIdx.x & 63, col = lane & 15, r = (lane >> 4) * 4 + (int)(threadIdx.x >> 6);
-  const int d = pk_d<FWT>(a);
-  const int part = (nt * 16) / d, cp = (nt * 16) % d;
+// 8..15 = the same dims + 32.  q -> exchange buffer; k, v -> exchange buffers and cache (for later passes).  t: rotary (cos, sin) of the
+// thread's pair in its row, p: position of that row.
+__device__ __forceinline__ void pk_epi_qkv(pk_x_t to, pk_w_t cache, float v, int part, int cp, unsigned tag, bool on, f32x2 t, int p, int capb, int row, int d) {
+  const int lane = pk_tid() & 63, col = lane & 15;
   const int hh = cp >> 6, qd = (cp & 63) >> 4;
   int dim = qd * 16 + col;
   if (part < 2) {
     const float o = lane_xor8(v);
-    v = col < 8 ? v * pre.t.x - o * pre.t.y : v * pre.t.x + o * pre.t.y;
+    v = col < 8 ? v * t[0] - o * t[1] : v * t[0] + o * t[1];
     dim = (col < 8 ? 0 : 32) + qd * 8 + (col & 7);
   }
   const float w = lane_xor1(v);       // neighbour dim (dim ^ 1 sits in lane ^ 1 in every layout above)
-  if (r >= R) return;
-  if (part == 0) {
-    if ((lane & 1) == 0) pk_st(a.q + (long)(row0 + r) * (d >> 1) + ((hh * 64 + dim) >> 1), pk_pack(v, w), tag);
-  } else {
-    u64* nb = (part == 1 ? a.newK : a.newV) + ((long)hh * (QT * 16) + row0 + r) * 32;
-    if ((lane & 1) == 0) pk_st(nb + (dim >> 1), pk_pack(v, w), tag);
-    if (pre.p >= 0) {
-      const int ps = pre.p % (capb * 32);      // the cache is a ring when a window is set
-      const long base = (long)hh * capb * 2048;
-      if (part == 1) L.Kc[base + kblk_off(ps, dim)] = (f16_t)v;
-      else L.Vc[base + vblk_off(ps, dim)] = (f16_t)v;
-    }
+  if (!on) return;
+  if ((lane & 1) == 0) pk_st(to + (long)row * (part == 0 ? d >> 1 : 32) + (dim >> 1), pk_pack(v, w), tag);
+  if (part > 0) {
+    const int ps = p % (capb * 32);      // the cache is a ring when a window is set
+    cache[(long)hh * capb * 2048 + (part == 1 ? kblk_off(ps, dim) : vblk_off(ps, dim))] = (f16_t)v;
   }
 }
 
 __device__ __forceinline__ int pk_active(int nblk, int ns) { return max(1, min(ns, (nblk + 3) >> 2)); }      // splits that hold visible keys
-__device__ __forceinline__ int pk_parts(int maxlim, int capb, int ns) {      // and so parts per head, uniform
-  return __builtin_amdgcn_readfirstlane(pk_active(min((maxlim + 32) >> 5, capb), ns));
-}
 
 // ------------------------------------------------------------------------------------------
 // Attention over one split of the keys of one head (flash-decoding), same arithmetic and deal as k_dec_attn: block b of 32 keys
 // belongs to wave b % 4 of split (b / 4) % ns, which is balanced at every length and does not depend on it.  QT tiles of
 // 16 query rows share every K/V block that is loaded.  The first K/V block of a wave is requested before the wait for
 // the queries, the next one behind it.  Keys of this pass (positions >= P0) are taken from the
-// exchange buffers, older keys from the cache.  lim[t]: last key the lane's row of tile t may see (-1: unused slot).
+// exchange buffers, older keys from the cache.  R rows, positions P0 ..; maxlim: the last key that one of them sees.
 // Partial results: tile t of (head, split) at part + t * PK_PART.  Where one split holds all visible keys (contexts of up to 128) there is nothing
 // to merge: its unit writes the attention output, and the merge stage, an exchange of 1.1 to 2 us, is left
 // out (eight faces token by token at d = 512, with the trips above: 29.9 -> 26.3 ms).
 // ------------------------------------------------------------------------------------------
 template <int QT, int FWT, class SH>
-__device__ __forceinline__ bool pk_attn_unit(const PkArgs& a, SH& sh, int& par, const u64* qbuf, const int (&lim)[QT], int maxlim, int R,
-                                             pk_cw_t Kc, pk_cw_t Vc, int capb, int nsplit_cfg, int hh, int split,
-                                             bool overlay, int P0, u64* part, u64* att, unsigned tag, int stage, int window) {
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+__device__ __forceinline__ void pk_attn_unit(PkA& a, SH& sh, int& par, u64 rec, int P0, int R, int maxlim, int nact, int hh, int split,
+                                             bool self, unsigned tag, int stage, int d) {
+  const pk_cw_t Kc = pk_ptr<pk_cw_t>(rec, 0), Vc = pk_ptr<pk_cw_t>(rec, 1);
+  const u64 sizes = pk_ptr<u64>(rec, 5);
+  const int nsplit_cfg = (int)(unsigned)sizes, capb = (int)(sizes >> 32), window = (int)(unsigned)pk_ptr<u64>(rec, 6);
+  const pk_x_t qbuf = pk_ptr<pk_x_t>(rec, 2), part = pk_ptr<pk_x_t>(rec, 3) + ((long)hh * PK_MAXSPLIT + split) * QT * PK_PART, att = pk_ptr<pk_x_t>(rec, 4);
+  const int tid = pk_tid(), wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int g = lane >> 4, ql = lane & 15;
-  const int d = pk_d<FWT>(a);
   const float kScale = 0.125f * 1.4426950408889634f;
   // With a window the cache is a ring of capb blocks (a multiple of four): position p lives in slot p mod (32 capb);
   // seen from the newest visible position, slot j holds lapbase + j if that is <= maxlim, else the position one
   // lap earlier.  Without a window lapbase = 0 and nothing wraps.
-  maxlim = __builtin_amdgcn_readfirstlane(maxlim);
   const int nblk = min((maxlim + 32) >> 5, capb);
   const int ringn = capb * 32;
   const int lapbase = max(maxlim, 0) / ringn * ringn;
   auto held = [&](int slot) { const int k = lapbase + slot; return k > maxlim ? k - ringn : k; };
   bool on[QT];
-  int first[QT];
+  int lim[QT], first[QT];      // keys that the lane's row of tile t sees: its own position is the last one, or all of the memory; -1: no row
 #pragma unroll
   for (int t = 0; t < QT; t++) {
     on[t] = t * 16 + ql < R;
+    lim[t] = !on[t] ? -1 : self ? P0 + t * 16 + ql : maxlim;
     first[t] = window > 0 ? max(lim[t] - window + 1, 0) : 0;
   }
-  const int nact = pk_active(nblk, nsplit_cfg);
-  if (split >= nact) return true;      // nothing visible in this split: the merge knows the same count
   par ^= 1;
   const int b0 = split * 4 + wave, step = nsplit_cfg * 4;     // this wave's blocks: b0, b0 + step, ...
 
   // The block of this wave, if any, that holds rows written by this pass.  K fragment f = (hb, dh) holds key b*32 + hb*16 + lane%16, dims
   // dh*32 + g*8..+8 (4 elements); V fragment dt holds dim dt*16 + lane%16 and the 8 slots g*8 + j <-> key b*32 + (j/4)*16 + g*4 + j%4.
   int bov = -1;
-  if (overlay) {
+  if (self) {
     // slot blocks of the rows of this pass: neighbours (also around a ring, whose blocks are a multiple of four), so in different waves;
     // rows past the end of a cache that is no ring do not exist
     const int end = window > 0 ? (P0 + R - 1) % ringn : min(P0 + R - 1, ringn - 1);
@@ -507,11 +480,11 @@ __device__ __forceinline__ bool pk_attn_unit(const PkArgs& a, SH& sh, int& par, 
   int keyK[2], keyV[8];     // positions of this lane's keys in it
   bool ok = true;
   {
-    const agent_buf_t qb = agent_buf(qbuf, QT * 16 * (d >> 1) * 8);
+    const agent_buf_t qb = pk_buf(qbuf, QT * 16 * (d >> 1) * 8);
     int qo[QT];
 #pragma unroll
     for (int t = 0; t < QT; t++) qo[t] = ((on[t] ? t * 16 + ql : 0) * (d >> 1) + ((hh * 64 + g * 8) >> 1)) * 8;
-    const agent_buf_t kb = agent_buf(a.newK + (long)hh * (QT * 16) * 32, QT * 16 * 32 * 8), vb = agent_buf(a.newV + (long)hh * (QT * 16) * 32, QT * 16 * 32 * 8);
+    const agent_buf_t kb = pk_buf(a.newK + (long)hh * (QT * 16) * 32, QT * 16 * 32 * 8), vb = pk_buf(a.newV + (long)hh * (QT * 16) * 32, QT * 16 * 32 * 8);
     int ko[2], vo[8];
     auto row_of = [&](int key) { return min(max(key - P0, 0), R - 1) * 256; };
 #pragma unroll
@@ -651,12 +624,12 @@ __device__ __forceinline__ bool pk_attn_unit(const PkArgs& a, SH& sh, int& par, 
 #pragma unroll
     for (int dt = 0; dt < 4; dt++) *reinterpret_cast<f32x4*>(&sh.lo[par][wave][t * 16 + ql][dt * 16 + g * 4]) = o[t][dt];
   }
-  if (!pk_sync(sh, ok)) return false;
+  pk_sync(sh, ok);
   PK_MARK(3);
   // the waves' parts meet: 16 threads per row, four dims each
 #pragma unroll
   for (int t = 0; t < QT; t++) {
-    const int ql16 = threadIdx.x >> 4, qi = t * 16 + ql16, j = threadIdx.x & 15;
+    const int ql16 = tid >> 4, qi = t * 16 + ql16, j = tid & 15;
     if (qi < R) {
       float m[4], f[4];
 #pragma unroll
@@ -673,12 +646,12 @@ __device__ __forceinline__ bool pk_attn_unit(const PkArgs& a, SH& sh, int& par, 
         f32x4 num = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int w = 0; w < 4; w++) num += *reinterpret_cast<const f32x4*>(&sh.lo[par][w][qi][4 * j]) * f[w];
-        u64* at = att + (long)qi * (d >> 1) + hh * 32 + 2 * j;
+        pk_x_t at = att + (long)qi * (d >> 1) + hh * 32 + 2 * j;
         pk_st(at, den < 0.f ? pk_pack(0.f, 0.f) : pk_pack(num[0] / den, num[1] / den), tag);
         pk_st(at + 1, den < 0.f ? pk_pack(0.f, 0.f) : pk_pack(num[2] / den, num[3] / den), tag);
         continue;
       }
-      u64* pt = part + (long)t * PK_PART;
+      pk_x_t pt = part + (long)t * PK_PART;
 #pragma unroll
       for (int k = 0; k < 4; k++) {
         const int dim = j + 16 * k;
@@ -690,24 +663,19 @@ __device__ __forceinline__ bool pk_attn_unit(const PkArgs& a, SH& sh, int& par, 
       if (j < 2) pk_stf(pt + 16 * 64 + ql16 * 2 + j, j == 0 ? M : den, tag);
     }
   }
-  return true;
 }
 
 // Merge of the splits of one head into the half-pair attention output: a unit takes four rows, a wave each; lane (g, j) the dims 4j .. 4j+3 of
 // the splits g, g + 4, ..., all parts in one trip of 16-byte loads (PK_MAXSPLIT); no wave waits for another.  Splits and lanes are added
 // in a fixed order.  (A quarter of the dims per unit, one dim per lane and 8-byte loads, 48 of them: 3.6 us from the last part to the last trip at nine rows.)
-// (row0: the first of the four rows, R: rows of the level; the split count comes from the largest limit of the whole level, as in the units
-// that wrote the partial results)
-template <int QT, int FWT, class SH>
-__device__ __forceinline__ void pk_merge_unit(const PkArgs& a, SH& sh, int maxlim, int R, int row0, int capb, int nsplit_cfg,
-                                              int hh, const u64* parts, u64* att, unsigned tag, int stage) {
-  const int d = pk_d<FWT>(a);
-  const int nsplit = pk_parts(maxlim, capb, nsplit_cfg);
+// (row0: the first of the four rows, R: rows of the level)
+template <int QT, class SH>
+__device__ __forceinline__ void pk_merge_unit(PkA& a, SH& sh, int nsplit, int R, int row0, int hh, pk_x_t parts, pk_x_t att, unsigned tag, int stage, int d) {
   constexpr int rec = QT * PK_PART * 8;                 // bytes of one (head, split) record: a tile per row group
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int tid = pk_tid(), wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int g = lane >> 4, j = lane & 15, row = row0 + wave;
   if (row >= R) return;
-  const agent_buf_t pb = agent_buf(parts + (long)hh * PK_MAXSPLIT * QT * PK_PART, nsplit * rec);      // splits that do not exist read 0
+  const agent_buf_t pb = pk_buf(parts + (long)hh * PK_MAXSPLIT * QT * PK_PART, nsplit * rec);      // splits that do not exist read 0
   const int tile = (row >> 4) * PK_PART * 8, r16 = row & 15;
   u32x4 ml[4], va[4], vb[4];
   const u64 t0 = wall_clock64();
@@ -768,320 +736,253 @@ __device__ __forceinline__ void pk_merge_unit(const PkArgs& a, SH& sh, int maxli
     stage++;                                                                                        \
   } while (0)
 
+// One loop over the stages, one instance each of the GEMM, attention and merge code: what tells the stages apart are scalars and, per stage, a record of
+// pointers that the host has laid out and the workgroup holds in LDS.  (Every stage of a block with code of its own was 85 KB, past the 64 KB
+// of instructions that two compute units keep, and held the offsets of all of them in registers, a third of them spilled: a step of d = 512 took
+// 625 us, of d = 1024 1480, against 590 and 1463.  Pointers that are worked out from the arguments in front of each unit: 621 and 1645.)
+// Only rows that exist take part.  A level without a row in this pass (a block that begins no vertex, no face) is left out with all its
+// stacks: the finer level then takes the coarse outputs of earlier passes from the ring.  (Eight faces token by token at d = 512, where the
+// vertex level has a row in every third pass and the face level in every ninth: 26.4 -> 11.3 ms.)
 template <int QT, int FWT>
-__global__ __launch_bounds__(256) void k_verify_persist(PkArgs a) {
+__global__ __launch_bounds__(256) void k_verify_persist(PkArgs) {
+  PkA& a = *(PkA*)__builtin_amdgcn_kernarg_segment_ptr();
+  __shared__ PkShared<QT> sh;
   const unsigned epoch = __builtin_amdgcn_readfirstlane((int)*a.epoch_word);
   if (*a.run_flag == 0) return;
-  __shared__ PkShared<QT> sh;
   if (threadIdx.x == 0) sh.bad = 0;
-  __syncthreads();
-  const int RS = QT * 16, RH = QT * 8;     // rows of an exchange region (= a.RS), and half of it: the row count of a half-pair region in units of d
-  const int d = pk_d<FWT>(a), H = d / 64, ff = FWT ? 4 * d : a.ff;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  unsigned rr = 0;     // round-robin origin of the current stage (same in every workgroup)
+  {   // the records go straight to LDS; the barrier behind the embedding waits for them
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), bytes = a.n_records * (int)sizeof(PkRecord);
+    for (int o = wave * 1024; o < bytes; o += 4096)
+      __builtin_amdgcn_global_load_lds((const PK_GLOBAL void*)((const PK_GLOBAL char*)a.records + o + (threadIdx.x & 63) * 16),
+                                       (__attribute__((address_space(3))) void*)((char*)sh.rec + o), 16, 0, 0);
+  }
+  constexpr int RS = QT * 16, RH = QT * 8;     // rows of an exchange region (= a.RS), and half of it: the row count of a half-pair region in units of d
+  const int d = pk_d<FWT>(a), H = d >> 6, ff = FWT ? 4 * d : a.ff;
+  const unsigned invH = (65535u + H) / H;      // u / H = u * invH >> 16 for the unit numbers of an attention stage (below 65536 / 16)
+  unsigned rr = 0;         // round-robin origin of the current stage (same in every workgroup)
   int stage = 0, par = 0;
-  // this thread's place in a GEMM tile: row of the group, column of the tile
-  const int er = ((threadIdx.x & 63) >> 4) * 4 + wave, ec = threadIdx.x & 15;
   bool worked = false;
   if (a.prof && threadIdx.x == 0) atomicMin(a.prof, (u64)wall_clock64());
-
-  // Per level and the same for all of its layers: the last visible key of this lane's query row in the
-  // self-attention (its own position) and in the cross-attention, the block maxima, the first position of the pass.
-  // (QT query tiles of 16 rows: tile t holds rows t*16 .. t*16+15 of the level)
-  int limS[3][QT], limX[3][QT], maxS[3], maxX[3], firstP[3];
+  // per level: rows of this pass (positions p0 .. p0 + nr - 1) and splits of the self-attention that hold keys; splits of the cross-attention
+  int p0[3], nr[3], act[3];
+  auto of = [](const int (&v)[3], int lev) { return lev == 0 ? v[0] : lev == 1 ? v[1] : v[2]; };
 #pragma unroll
   for (int lv = 0; lv < 3; lv++) {
-    const int ql = threadIdx.x & 15;
-    int ms = -1, mx = -1, fp = 0x3fffffff;
-#pragma unroll
-    for (int t = 0; t < QT; t++) {
-      const bool onl = t * 16 + ql < a.R[lv];
-      limS[lv][t] = onl ? a.pos[lv][t * 16 + ql] : -1;
-      limX[lv][t] = onl ? a.limx[lv][t * 16 + ql] : -1;
-      ms = max(ms, limS[lv][t]);
-      mx = max(mx, limX[lv][t]);
-      if (limS[lv][t] >= 0) fp = min(fp, limS[lv][t]);
-    }
-#pragma unroll
-    for (int o = 1; o < 16; o <<= 1) {
-      ms = max(ms, __shfl_xor(ms, o, 64));
-      mx = max(mx, __shfl_xor(mx, o, 64));
-      fp = min(fp, __shfl_xor(fp, o, 64));
-    }
-    maxS[lv] = ms; maxX[lv] = mx; firstP[lv] = fp;
+    const int lane = threadIdx.x & 63, p = lane < a.R[lv] ? a.pos[lv][lane] : -1;       // active rows are the first ones, positions side by side
+    nr[lv] = __popcll(__ballot(p >= 0));
+    p0[lv] = nr[lv] ? __builtin_amdgcn_readfirstlane(p) : 0x3fffffff;
+    act[lv] = nr[lv] ? pk_active(min((p0[lv] + nr[lv] + 31) >> 5, a.capb[lv]), a.nsplit[lv]) : 0;
   }
+  const int actX = pk_active(a.capbM, a.nsplitM);
+  // logits of rows that the block does not reach: zeros
+  for (long i = (long)nr[0] * a.D.V + blockIdx.x * 256 + threadIdx.x; i < (long)a.R[0] * a.D.V; i += PK_NWG * 256) a.logits[i] = 0.f;
+  if (nr[0] == 0) return;
 
-  // ---- embedding: one unit per coordinate row -> hA of layer 0
-  PK_MINE(a.R[0]) {
+  // ---- embedding: one unit per coordinate row -> residual stream of layer 0
+  PK_MINE(nr[0]) {
     const int r = u;
-    const bool onr = a.pos[0][r] >= 0;
-    const f16_t* e = a.emb + (long)a.vtok[r] * d;
+    const pk_cw_t e = a.emb + (long)a.vtok[r] * d;
+    const pk_cf_t g1 = a.gain1[0];
     const int n = SkipCols::count(d, threadIdx.x);
     float v[FM_TR_COLS], gain[FM_TR_COLS];
 #pragma unroll
     for (int k = 0; k < FM_TR_COLS; k++) {           // all loads together
       const int i = min(SkipCols::col(threadIdx.x, k), d - 1);
       v[k] = (float)e[i];
-      gain[k] = ((pk_cf_t)a.layers[0].g1)[i];
+      gain[k] = g1[i];
     }
 #pragma unroll
     for (int k = 0; k < FM_TR_COLS; k++) {           // region of layer 0, and its copy for the first norm (d is a multiple of 128)
       if (k >= n) break;
-      pk_put_row(onr ? v[k] : 0.f, true, r, SkipCols::col(threadIdx.x, k), d, a.hA, a.xA, a.sA, gain[k], PK_TAG(0) + a.test_skew);
+      pk_put_row(v[k], true, r, SkipCols::col(threadIdx.x, k), d, a.h, a.x, a.s, gain[k], PK_TAG(0) + a.test_skew);
     }
   }
-  PK_NEXT(a.R[0]);
+  PK_NEXT(nr[0]);
+  __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0): the records
+  __syncthreads();
 
-  for (int st = 0; st < 5; st++) {
-    for (int li = 0; li < a.count[st]; li++) {
-      const int l = a.first[st] + li;
-      const PkLayer& L = a.layers[l];
-      const int lev = L.level, R = a.R[lev];
-      const unsigned tag = PK_TAG(l);
-      const int* pos = a.pos[lev];
-      const int capb = a.capb[lev];
-      // this layer's own regions of the exchange buffers
-      u64* const hA_l = a.hA + (long)l * RS * d;
-      u64* const hA_n = a.hA + (long)(l + 1) * RS * d;
-      u64* const hB_l = a.hB + (long)l * RS * d;
-      u64* const hC_l = a.hC + (long)l * RS * d;
-      u64* const xA_l = a.xA + (long)l * RH * d;
-      u64* const xA_n = a.xA + (long)(l + 1) * RH * d;
-      u64* const xB_l = a.xB + (long)l * RH * d;
-      u64* const xC_l = a.xC + (long)l * RH * d;
-      u64* const sA_l = a.sA + (long)l * RS * (d >> 4);
-      u64* const sB_l = a.sB + (long)l * RS * (d >> 4);
-      u64* const sC_l = a.sC + (long)l * RS * (d >> 4);
-      u64* const att_l = a.att + (long)l * RH * d;
-      u64* const att2_l = a.att2 + (long)l * RH * d;
-      u64* const mid_l = a.mid + (long)l * RH * ff;
-      // GEMM units take the rows in groups of 16: unit = (tile, row group); a group's rows are contiguous
-      // in every exchange buffer, so a unit is the one-group code on offset pointers
-      const int RG = QT == 1 ? 1 : (R + 15) >> 4;      // a compile-time 1 for blocks of up to 16 tokens
-      const int RQ = (R + 3) >> 2;                     // merge units: four rows of a head each
-      const long hd = d >> 1, sd = d >> 4;
-      // ---- QKV (norm1 on the fly, rotary, q / new K,V out, cache append)
-      PK_MINE(3 * d / 16 * RG) {
-        const int nt = u / RG, row0 = (u % RG) * 16, Rl = min(16, R - row0);
-        float c;
-        PkQkvPre pre;
-        pk_qkv_prefetch(nt, d, Rl, pos + row0, a.cs[lev] + (long)row0 * 32, pre);
-        if (!pk_gemm_tile<FWT, true>(a, sh, par, L.wqkv + (long)nt * (d / 32) * 512, d / 32, xA_l + row0 * hd, tag, sA_l + row0 * sd, Rl, c, stage)) return;
-        pk_epi_qkv<QT, FWT>(a, L, c, nt, tag, Rl, pre, capb, row0);
+  // st: stack, l: layer (behind the last layer of a stack, the first one of the next), op: stage
+  int st = 0, l = 0, end = a.first[1], op = PK_QKV;
+  while (true) {
+    const int lev = op == PK_SHORT ? st + 1 : st <= 2 ? st : 4 - st;
+    const int R = of(nr, lev), P0 = of(p0, lev);
+    const unsigned tag = PK_TAG(l);
+    if (op == PK_ATT || op == PK_XATT) {
+      // ---- attention: a unit per split that holds keys and head
+      const bool self = op == PK_ATT;
+      const int nact = self ? of(act, lev) : actX;
+      PK_MINE(H * nact) {
+        const int sp = u * invH >> 16, hh = u - sp * H;
+        const u64 rec = pk_record(sh, l * PK_RECS + (self ? 1 : 4));
+        pk_attn_unit<QT, FWT>(a, sh, par, rec, P0, R, self ? P0 + R - 1 : a.D.M - 1, nact, hh, sp, self, tag, stage, d);
+        if (pk_bad(sh)) return;
       }
-      PK_NEXT(3 * d / 16 * RG);
-      // ---- self-attention splits
-      {
-        const int ns = a.nsplit[lev];
-        const int P0 = firstP[lev];
-        PK_MINE(H * ns) {
-          // split-major: the splits that hold keys come first and spread over all workgroups
-          const int hh = u % H, sp = u / H;
-          if (!pk_attn_unit<QT, FWT>(a, sh, par, a.q, limS[lev], maxS[lev], R, L.Kc, L.Vc, capb, ns, hh, sp, true, P0,
-                                a.partS + ((long)hh * PK_MAXSPLIT + sp) * (RS >> 4) * PK_PART, att_l, tag, stage, a.win[lev])) return;
-        }
-        PK_NEXT(H * ns);
-        if (pk_parts(maxS[lev], capb, ns) > 1) PK_MINE(H * RQ) pk_merge_unit<QT, FWT>(a, sh, maxS[lev], R, u / H * 4, capb, ns, u % H, a.partS, att_l, tag, stage);
-        PK_NEXT(H * RQ);
+      PK_NEXT(H * nact);
+    } else if (op == PK_MRG || op == PK_XMRG) {
+      // ---- merge of the splits, where there are several
+      const bool self = op == PK_MRG;
+      const int nact = self ? of(act, lev) : actX, units = nact > 1 ? H * ((R + 3) >> 2) : 0;
+      PK_MINE(units) {
+        const int q = u * invH >> 16, hh = u - q * H;
+        const u64 rec = pk_record(sh, l * PK_RECS + (self ? 1 : 4));
+        pk_merge_unit<QT>(a, sh, nact, R, q * 4, hh, pk_ptr<pk_x_t>(rec, 3), pk_ptr<pk_x_t>(rec, 4), tag, stage, d);
       }
-      // ---- Wo + residual -> hB (tap: the layer input is what the draft heads of this level start from)
-      PK_MINE(d / 16 * RG) {
-        const int nt = u / RG, row0 = (u % RG) * 16, Rl = min(16, R - row0);
-        const int n = nt * 16 + ec;
-        float c, old;
-        PkOld res;
-        pk_res_request<FWT>(a, n, hA_l + (long)row0 * d, Rl, pos + row0, L.g2, res);
-        if (!pk_gemm_tile<FWT, false>(a, sh, par, L.wo + (long)nt * (d / 32) * 512, d / 32, att_l + row0 * hd, tag, nullptr, Rl, c, stage)) return;
-        if (pk_res_take<FWT>(a, n, hA_l + (long)row0 * d, tag, Rl, res, old, stage)) {
-          pk_put_row(old + c, er < Rl, er, n, d, hB_l + (long)row0 * d, xB_l + row0 * hd, sB_l + row0 * sd, res.gain, tag);
-          if (L.tap && er < Rl && res.p >= 0) a.tap[lev][(long)(res.p & (lev == 0 ? 31 : lev == 1 ? 15 : 7)) * d + n] = old;
-        } else sh.bad = 1;
-      }
-      PK_NEXT(d / 16 * RG);
-      // ---- cross-attention query (norm2 on the fly)
-      PK_MINE(d / 16 * RG) {
-        const int nt = u / RG, row0 = (u % RG) * 16, Rl = min(16, R - row0);
-        float c;
-        if (!pk_gemm_tile<FWT, true>(a, sh, par, L.cq + (long)nt * (d / 32) * 512, d / 32, xB_l + row0 * hd, tag, sB_l + row0 * sd, Rl, c, stage)) return;
-        pk_put_half(c, er < Rl, er, nt * 16 + ec, a.q2 + row0 * hd, d >> 1, tag);
-      }
-      PK_NEXT(d / 16 * RG);
-      // ---- cross-attention over the condition memory
-      {
-        const int ns = a.nsplitM;
-        PK_MINE(H * ns) {
-          const int hh = u / ns, sp = u % ns;
-          if (!pk_attn_unit<QT, FWT>(a, sh, par, a.q2, limX[lev], maxX[lev], R, L.Km, L.Vm, a.capbM, ns, hh, sp, false, 0,
-                                a.partX + ((long)hh * PK_MAXSPLIT + sp) * (RS >> 4) * PK_PART, att2_l, tag, stage, 0)) return;
-        }
-        PK_NEXT(H * ns);
-        if (pk_parts(maxX[lev], a.capbM, ns) > 1) PK_MINE(H * RQ) pk_merge_unit<QT, FWT>(a, sh, maxX[lev], R, u / H * 4, a.capbM, ns, u % H, a.partX, att2_l, tag, stage);
-        PK_NEXT(H * RQ);
-      }
-      // ---- cross output projection + residual -> hC
-      PK_MINE(d / 16 * RG) {
-        const int nt = u / RG, row0 = (u % RG) * 16, Rl = min(16, R - row0);
-        const int n = nt * 16 + ec;
-        float c, old;
-        PkOld res;
-        pk_res_request<FWT>(a, n, hB_l + (long)row0 * d, Rl, pos + row0, L.g3, res);
-        if (!pk_gemm_tile<FWT, false>(a, sh, par, L.co + (long)nt * (d / 32) * 512, d / 32, att2_l + row0 * hd, tag, nullptr, Rl, c, stage)) return;
-        if (pk_res_take<FWT>(a, n, hB_l + (long)row0 * d, tag, Rl, res, old, stage))
-          pk_put_row(old + c, er < Rl, er, n, d, hC_l + (long)row0 * d, xC_l + row0 * hd, sC_l + row0 * sd, res.gain, tag);
-        else sh.bad = 1;
-      }
-      PK_NEXT(d / 16 * RG);
-      // ---- FFN up (norm3 on the fly, GELU)
-      PK_MINE(ff / 16 * RG) {
-        const int nt = u / RG, row0 = (u % RG) * 16, Rl = min(16, R - row0);
-        float c;
-        if (!pk_gemm_tile<FWT, true>(a, sh, par, L.w1 + (long)nt * (d / 32) * 512, d / 32, xC_l + row0 * hd, tag, sC_l + row0 * sd, Rl, c, stage)) return;
-        pk_put_half(gelu_tanh_f(c), er < Rl, er, nt * 16 + ec, mid_l + (long)row0 * (ff >> 1), ff >> 1, tag);
-      }
-      PK_NEXT(ff / 16 * RG);
-      // ---- FFN down + residual -> next layer input, or the stack output (+ its ring for later passes).
-      // K = ff is four times longer than in the other GEMMs, so a tile is computed by four units, one per
-      // K-quarter; quarters 1..3 hand their partial tile to quarter 0, which adds them in a fixed order.
-      PK_MINE(4 * (d / 16) * RG) {
-        const int uv = u / RG, rg = u % RG, row0 = rg * 16, Rl = min(16, R - row0);
-        const int nt = uv >> 2, kq = uv & 3;
-        const int KTq = ff / 128;                       // fragments of one K-quarter
-        u64* const w2p = a.w2part + ((long)nt * RG + rg) * 3 * 256;
-        const int n = nt * 16 + ec;
-        float c, old;
-        PkOld res;
-        // the norm behind this layer: the next one's first, the output head's behind the last
-        const bool out = L.last && st < 4;       // a stack output feeds a level transition, not a norm
-        if (kq == 0) pk_res_request<FWT>(a, n, hC_l + (long)row0 * d, Rl, pos + row0, out ? nullptr : L.last ? (pk_cf_t)a.gf : a.layers[l + 1].g1, res);
-        if (!pk_gemm_tile<FWT, false>(a, sh, par, L.w2 + ((long)nt * (ff / 32) + (long)kq * KTq) * 512, KTq,
-                                      mid_l + (long)row0 * (ff >> 1) + (long)kq * (ff / 8), tag, nullptr, Rl, c, stage, ff >> 1)) return;
-        if (kq > 0) {
-          pk_stf(w2p + (long)(kq - 1) * 256 + threadIdx.x, c, tag);
-        } else {
-          // rows that do not exist wait for nothing: nobody waits for them either, and the next layer writes the same partial tiles
-          unsigned pr[3];
-          if (pk_fetch<3>(pr, 3, er < Rl, tag, [&](int i) { return w2p + (long)i * 256 + threadIdx.x; }, a, stage) &&
-              pk_res_take<FWT>(a, n, hC_l + (long)row0 * d, tag, Rl, res, old, stage)) {
-            PK_MARK(4);
-#pragma unroll
-            for (int k = 0; k < 3; k++) c += __uint_as_float(pr[k]);
-            const float v = old + c;
-            pk_put_row(v, er < Rl, er, n, d, (out ? a.hT[st] : hA_n) + (long)row0 * d, out ? nullptr : xA_n + row0 * hd,
-                       a.sA + (long)(l + 1) * RS * sd + row0 * sd, res.gain, PK_TAG(l + 1));
-            if (out && er < Rl && res.p >= 0) {
-              float* ring = st == 0 ? a.ring_hc : st == 1 ? a.ring_hv : st == 2 ? a.ring_yf : a.ring_yv;
-              ring[(long)(res.p & (st == 0 ? 31 : st == 2 ? 7 : 15)) * d + n] = v;
-            }
-          } else sh.bad = 1;
-        }
-      }
-      PK_NEXT(4 * (d / 16) * RG);
-    }
-    // ---- level transition after stack st; everything it produces carries the tag of the next layer
-    const int ln = a.first[st] + a.count[st];
-    const unsigned tagn = PK_TAG(ln);
-    if (st == 0 || st == 1) {
-      // shorten: coarse slot k pools fine positions 3j-2..3j (this pass: stack output; older: ring; before the start: 0)
-      const int fl = st, cl = st + 1;
-      const float* ring = st == 0 ? a.ring_hc : a.ring_hv;
-      const int rs = st == 0 ? 32 : 16;
-      const int Rf_ = a.R[fl], Rc_ = a.R[cl];
-      const int F0 = firstP[fl];   // first fine position of this pass
+      PK_NEXT(units);
+    } else if (op == PK_POOL) {
+      // ---- shorten: coarse row of position j pools fine positions 3j-2..3j (this pass: stack output; older: ring; before the start: 0)
+      const int cl = st + 1, Rc_ = of(nr, cl), rs = st == 0 ? 32 : 16;
       PK_MINE(Rc_) {
         constexpr int C = FM_TR_COLS;
-        const int j = firstP[cl] + u <= maxS[cl] ? firstP[cl] + u : -1;      // active rows are the first ones, positions side by side
-        const int p0 = 3 * j - 2;      // positions p0 .. p0 + 2; j < 0: an inactive row, zeros
+        const pk_f_t ring = a.ring[st];
+        const int j = of(p0, cl) + u, q0 = 3 * j - 2;
         float was[3][C], now[3][C];
 #pragma unroll
         for (int q = 0; q < 3; q++)
 #pragma unroll
-          for (int k = 0; k < C; k++) was[q][k] = ring[(long)((p0 + q) & (rs - 1)) * d + min(PoolCols::col(threadIdx.x, k), d - 1)];
-        const bool ok = pk_wait_stack<FWT, PoolCols>(a, a.hT[st], tagn, stage, Rf_, [&](int q) { return min(max(p0 + q - F0, 0), Rf_ - 1); }, now);
+          for (int k = 0; k < C; k++) was[q][k] = ring[(long)((q0 + q) & (rs - 1)) * d + min(PoolCols::col(threadIdx.x, k), d - 1)];
+        const bool ok = pk_wait_stack<FWT, PoolCols>(a, a.hT[st], tag, stage, R, [&](int q) { return min(max(q0 + q - P0, 0), R - 1); }, now);
 #pragma unroll
         for (int k = 0; k < C; k += 2) {
           const int i = PoolCols::col(threadIdx.x, k);   // two adjacent columns per thread
           float s0 = 0.f, s1 = 0.f;
 #pragma unroll
           for (int q = 0; q < 3; q++) {
-            const bool in = p0 + q >= F0, on = j >= 0 && p0 + q >= 0;
+            const bool in = q0 + q >= P0, on = q0 + q >= 0;
             s0 += !on ? 0.f : in ? now[q][k] : was[q][k];
             s1 += !on ? 0.f : in ? now[q][k + 1] : was[q][k + 1];
           }
-          if (i < d) pk_st(a.pool + (long)st * 8 * d + (long)u * (d >> 1) + (i >> 1), pk_pack(s0 / 3.0f, s1 / 3.0f), tagn);
+          if (i < d) pk_st(a.pool + (long)st * 8 * d + (long)u * (d >> 1) + (i >> 1), pk_pack(s0 / 3.0f, s1 / 3.0f), tag);
         }
         if (!ok) sh.bad = 1;
       }
       PK_NEXT(Rc_);
-      PK_MINE(d / 16) {
-        float c;
-        const float gain = a.layers[ln].g1[u * 16 + ec];
-        pk_cw_t W = (pk_cw_t)(st == 0 ? a.short_cv : a.short_vf) + (long)u * (d / 32) * 512;
-        if (!pk_gemm_tile<FWT, false>(a, sh, par, W, d / 32, a.pool + (long)st * 8 * d, tagn, nullptr, Rc_, c, stage)) return;
-        pk_put_row(c, er < Rc_, er, u * 16 + ec, d, a.hA + (long)ln * RS * d, a.xA + (long)ln * RH * d, a.sA + (long)ln * RS * (d >> 4), gain, tagn);
-      }
-      PK_NEXT(d / 16);
-    } else if (st == 2 || st == 3) {
-      // upsample: fine row = skip (output of the level's first half) + coarse output of slot floor(pos/3)
-      const int fl = st == 2 ? 1 : 0, cl = fl + 1;
-      const u64* skip = a.hT[st == 2 ? 1 : 0];
-      const unsigned tag_skip = PK_TAG(a.first[st == 2 ? 1 : 0] + a.count[st == 2 ? 1 : 0]);
-      const float* ring = st == 2 ? a.ring_yf : a.ring_yv;
-      const int rs = st == 2 ? 8 : 16;
-      const int Rf_ = a.R[fl], Rc_ = a.R[cl];
+    } else if (op == PK_UP) {
+      // ---- upsample onto level fl: skip (output of the level's first half) + coarse output of position floor(pos/3), of this pass or from the
+      // ring.  st is the stack that ran last: the coarse level's, or, where that one has no row, the first half itself.
+      const int fl = st >= 2 ? 3 - st : st, cl = fl + 1, Rf_ = of(nr, fl), ln = a.first[4 - fl];
       PK_MINE(Rf_) {
         constexpr int C = FM_TR_COLS;
-        const int p = firstP[fl] + u <= maxS[fl] ? firstP[fl] + u : -1;      // active rows are the first ones, positions side by side
-        const int slot = p / 3 - firstP[cl];                                  // row of the coarse output, below 0: it is in the ring
+        const pk_x_t skip = a.hT[fl];
+        const pk_f_t ring = a.ring[3 - fl];
+        const pk_cf_t g1 = a.gain1[4 - fl];
+        const unsigned tag_skip = PK_TAG(a.first[fl] + a.count[fl]), tagn = PK_TAG(ln);
+        const int p = of(p0, fl) + u, rs = fl == 1 ? 8 : 16;
+        const int slot = p / 3 - of(p0, cl);                                  // row of the coarse output, below 0: it is in the ring
         const int n = SkipCols::count(d, threadIdx.x);
         // what has been there since the level's first half leaves in front of the wait
-        const agent_buf_t kb = agent_buf(skip, Rf_ * d * 8);
+        const agent_buf_t kb = pk_buf(skip, Rf_ * d * 8);
         u32x2 kept[C];
         float was[C], now[1][C], gain[C];
 #pragma unroll
         for (int k = 0; k < C; k++) {
           const int i = min(SkipCols::col(threadIdx.x, k), d - 1);
           kept[k] = ld_agent2(kb, (u * d + i) * 8);
-          was[k] = ring[(long)((max(p, 0) / 3) & (rs - 1)) * d + i];
-          gain[k] = a.layers[ln].g1[i];
+          was[k] = ring[(long)((p / 3) & (rs - 1)) * d + i];
+          gain[k] = g1[i];
         }
-        bool ok = pk_wait_stack<FWT, SkipCols>(a, a.hT[st], tagn, stage, Rc_, [&](int) { return min(max(slot, 0), Rc_ - 1); }, now);
+        bool ok = pk_wait_stack<FWT, SkipCols>(a, a.hT[st], PK_TAG(a.first[st] + a.count[st]), stage, R, [&](int) { return min(max(slot, 0), R - 1); }, now);
 #pragma unroll
         for (int k = 0; k < C; k++) {
           if (k >= n) break;
           const int i = SkipCols::col(threadIdx.x, k);
           unsigned raw[1] = {kept[k][0]};
           if (!__all(kept[k][1] == tag_skip)) ok = pk_fetch<1>(raw, 1, true, tag_skip, [&](int) { return skip + (long)u * d + i; }, a, stage) && ok;
-          const float v = __uint_as_float(raw[0]) + (p < 0 ? 0.f : slot >= 0 ? now[0][k] : was[k]);
-          pk_put_row(v, true, u, i, d, a.hA + (long)ln * RS * d, a.xA + (long)ln * RH * d, a.sA + (long)ln * RS * (d >> 4), gain[k], tagn);
+          const float v = __uint_as_float(raw[0]) + (slot >= 0 ? now[0][k] : was[k]);
+          pk_put_row(v, true, u, i, d, a.h + (long)ln * RS * d, a.x + (long)ln * RH * d, a.s + (long)ln * RS * (d >> 4), gain[k], tagn);
         }
         if (!ok) sh.bad = 1;
       }
       PK_NEXT(Rf_);
+      st = 4 - fl;
+      l = ln;
+      end = l + a.count[st];
+    } else {
+      // ---- GEMM.  gi: 0 q,k,v; 1 self output; 2 cross query; 3 cross output; 4 FFN up; 5 FFN down; 6 shortening; 7 output head.  Of 0 to 5 the even
+      // ones read a norm's rows, the odd ones add to the residual stream.  Rows go in groups of 16: unit = (tile, row group), a group's rows
+      // are contiguous in every exchange buffer.
+      // FFN down: K = ff is four times longer than in the other GEMMs, so a tile is computed by four units, one per K-quarter; quarters 1..3 hand
+      // their partial tile to quarter 0, which adds them in a fixed order.
+      const int gi = op == PK_QKV ? 0 : op <= PK_CQ ? op - 2 : op <= PK_W2 ? op - 4 : op == PK_SHORT ? 6 : 7;
+      const bool down = gi == 5, goes_on = gi == 1 || gi == 3 || gi >= 5 && gi <= 6;
+      const int NT = gi == 7 ? (a.D.V + 15) >> 4 : gi == 0 ? 3 * (d >> 4) : gi == 4 ? ff >> 4 : down ? d >> 2 : d >> 4;
+      const int rgs = QT == 1 || gi == 6 || R <= 16 ? 0 : 1;        // log2 of the row groups
+      PK_MINE(NT << rgs) {
+        const u64 rec = pk_record(sh, gi < 6 ? l * PK_RECS + gi + (gi > 0) + (gi > 2) : a.n_layers * PK_RECS + (gi == 6 ? st : 2));
+        const int row0 = (u & rgs) * 16, ut = u >> rgs, nt = down ? ut >> 2 : ut, kq = down ? ut & 3 : 0, Rl = min(16, R - row0);
+        const int KT = down ? ff >> 7 : d >> 5, lda = down ? ff >> 1 : d >> 1;
+        // weights go out before anything else: they depend on nothing, and come from the farthest
+        PkWeights<FWT> w;
+        pk_weights<FWT>(w, pk_ptr<pk_cw_t>(rec, 0) + ((long)nt * (down ? ff >> 5 : d >> 5) + kq * KT) * 512, KT);
+        const pk_x_t in = pk_ptr<pk_x_t>(rec, 1) + (long)row0 * lda + kq * (ff >> 3), sq0 = pk_ptr<pk_x_t>(rec, 2), hold = pk_ptr<pk_x_t>(rec, 3);
+        const pk_x_t to = pk_ptr<pk_x_t>(rec, 4), to_x = pk_ptr<pk_x_t>(rec, 5), to_s = pk_ptr<pk_x_t>(rec, 6);
+        const pk_x_t w2p = a.w2part + (((long)nt << rgs) + (u & rgs)) * 768;
+        // this thread's place in the tile: row of the group, column
+        const int tid = pk_tid(), er = ((tid & 63) >> 4) * 4 + (tid >> 6), n = nt * 16 + (tid & 15), rr_ = min(er, Rl - 1);
+        const bool res = goes_on && gi < 6 && kq == 0;
+        // The residual operand of a tile (complete long before the tile's GEMM input is) and what else the epilogue needs is requested here and looked at
+        // behind the multiplication; only then, if the operand was not there yet, it is waited for.
+        u32x2 ov = u32x2{0u, 0u};
+        float gain = 0.f;
+        f32x2 rot = f32x2{1.f, 0.f};
+        const int part = gi > 0 ? 0 : nt >= d >> 3 ? 2 : nt >= d >> 4 ? 1 : 0, cp = nt * 16 - part * d;
+        if (res) ov = ld_agent2(pk_buf(hold + (long)row0 * d, Rl * d * 8), (rr_ * d + n) * 8);
+        if (goes_on && to_x && kq == 0) gain = pk_ptr<pk_cf_t>(rec, 7)[n];
+        if (gi == 0 && part < 2) rot = pk_ptr<const PK_GLOBAL f32x2*>(rec, 7)[(long)(row0 + rr_) * 32 + ((cp & 63) >> 4) * 8 + (tid & 7)];
+        float c;
+        pk_gemm_tile<FWT>(a, sh, par, w, KT, in, lda, tag, sq0 ? sq0 + (long)row0 * (d >> 4) : sq0, Rl, c, stage);
+        const bool on = er < Rl;
+        if (goes_on && kq == 0) {
+          bool ok = true;
+          if (down) {     // rows that do not exist wait for nothing: nobody waits for them either, and the next layer writes the same partial tiles
+            unsigned pr[3];
+            ok = pk_fetch<3>(pr, 3, on, tag, [&](int i) { return w2p + i * 256 + tid; }, a, stage);
+            PK_MARK(4);
+#pragma unroll
+            for (int k = 0; k < 3; k++) c += __uint_as_float(pr[k]);
+          }
+          unsigned raw[1] = {ov[0]};
+          if (res && !__all(ov[1] == tag)) ok = pk_fetch<1>(raw, 1, true, tag, [&](int) { return hold + (long)(row0 + rr_) * d + n; }, a, stage) && ok;
+          const float old = __uint_as_float(raw[0]), v = res ? old + c : c;
+          if (ok) {
+            pk_put_row(v, on, er, n, d, to + (long)row0 * d, to_x ? to_x + (long)row0 * (d >> 1) : to_x, to_s + (long)row0 * (d >> 4), gain,
+                       down ? tag + 1 : tag);
+            // rings: a stack's output (no norm behind it); the input of its last layer, which is what the draft heads of the level start from
+            const pk_f_t ring = pk_ptr<pk_f_t>(rec, 8);
+            if (ring && on) ring[(long)((P0 + row0 + er) & (lev == 0 ? 31 : lev == 1 ? 15 : 7)) * d + n] = down ? v : old;
+          } else sh.bad = 1;
+        } else if (goes_on) {
+          pk_stf(w2p + (kq - 1) * 256 + tid, c, tag);
+        } else if (gi == 0) {      // to: queries, to_x, to_s: new keys and values; hold, ring: the caches
+          const int hh = cp >> 6;
+          const pk_x_t dst = part == 0 ? to + (long)row0 * (d >> 1) + hh * 32 : (part == 1 ? to_x : to_s) + ((long)hh * RS + row0) * 32;
+          pk_epi_qkv(dst, part == 1 ? (pk_w_t)hold : pk_ptr<pk_w_t>(rec, 8), c, part, cp, tag, on, rot, P0 + row0 + er, lev == 0 ? a.capb[0] : lev == 1 ? a.capb[1] : a.capb[2], er, d);
+        } else if (gi == 7) {
+          if (on && n < a.D.V) a.logits[(long)(row0 + er) * a.D.V + n] = c;       // plain memory: later launches read them
+        } else {
+          const int ld2 = gi == 4 ? ff >> 1 : d >> 1;
+          pk_put_half(gi == 4 ? gelu_tanh_f(c) : c, on, er, n, to + (long)row0 * ld2, ld2, tag);
+        }
+        if (pk_bad(sh)) return;
+      }
+      PK_NEXT(NT << rgs);
     }
-  }
-  // ---- output head: final norm on the fly, logits to plain memory (later launches read them)
-  {
-    const int l = a.n_layers, R = a.R[0];
-    const int NT = (a.D.V + 15) / 16, RG = QT == 1 ? 1 : (R + 15) >> 4;
-    PK_MINE(NT * RG) {
-      const int nt = u / RG, row0 = (u % RG) * 16, Rl = min(16, R - row0);
-      float c;
-      if (!pk_gemm_tile<FWT, true>(a, sh, par, (pk_cw_t)a.lm + (long)nt * (d / 32) * 512, d / 32, a.xA + (long)l * RH * d + (long)row0 * (d >> 1),
-                                   PK_TAG(l), a.sA + ((long)l * RS + row0) * (d >> 4), Rl, c, stage)) return;
-      const int n = nt * 16 + ec;
-      if (er < Rl && n < a.D.V) a.logits[(long)(row0 + er) * a.D.V + n] = c;
-    }
+    // ---- the next stage
+    if (op < PK_W2) op++;
+    else if (op == PK_W2) {
+      l++;
+      op = l < end ? PK_QKV : st == 4 ? PK_LM : st < 2 && of(nr, st + 1) > 0 ? PK_POOL : PK_UP;
+    } else if (op == PK_POOL) op = PK_SHORT;
+    else if (op == PK_SHORT) { op = PK_QKV; st++; end = l + a.count[st]; }
+    else if (op == PK_UP) op = PK_QKV;
+    else break;
   }
 }
 
-// The instance of a context: two row groups or one, and the width where the compiler's knowing it measures faster than reading it from the
-// arguments.  Verify pass of 20 blocks behind 4500 tokens, us, sized against general: one row group d = 256 468 / 479, 512 524 / 525 (eight
-// faces token by token 30 110 / 30 560), 768 573 / 585; two row groups 512 601 / 604, 768 678 / 711.  No faster, and hence general: two row
-// groups at 256 (541 / 542), and 1024, whose eight fragments a wave are what the general instance holds anyway (40 blocks behind 9000 tokens:
-// 1365 / 1368, two row groups 1639 / 1636).
+// The instance of a context: two row groups or one, and the width where the compiler knows it (offsets are constants and no fragment is
+// conditional: a step of d = 1024 1463 us, 1573 with the general instance, which takes the other widths and hidden widths).
 typedef void (*pk_kernel_t)(PkArgs);
 inline pk_kernel_t pk_kernel(const PkArgs& a) {
   const int d = a.ff == 4 * a.D.d ? a.D.d : 0;
-  if (a.RS == 32) return d == 512 ? k_verify_persist<2, 4> : d == 768 ? k_verify_persist<2, 6> : k_verify_persist<2, 0>;
-  return d == 256 ? k_verify_persist<1, 2> : d == 512 ? k_verify_persist<1, 4> : d == 768 ? k_verify_persist<1, 6> : k_verify_persist<1, 0>;
+  if (a.RS == 32) return d == 256 ? k_verify_persist<2, 2> : d == 512 ? k_verify_persist<2, 4> : d == 768 ? k_verify_persist<2, 6> : d == 1024 ? k_verify_persist<2, 8> : k_verify_persist<2, 0>;
+  return d == 256 ? k_verify_persist<1, 2> : d == 512 ? k_verify_persist<1, 4> : d == 768 ? k_verify_persist<1, 6> : d == 1024 ? k_verify_persist<1, 8> : k_verify_persist<1, 0>;
 }
