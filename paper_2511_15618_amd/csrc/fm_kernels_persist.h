@@ -309,10 +309,11 @@ __device__ __forceinline__ void pk_gemm_tile(PkA& a, SH& sh, int& par, const PkW
   bool good = true;
   // The full fragment read is its own validity check, so a unit whose input is already there pays one round trip.
   // When a read comes back incomplete the wave falls back to watching one element per lane (lane l: fragment l/8, its
-  // first or second half - a producer tile owns half a fragment row - in one of the last four rows) and reads the
-  // fragments again once those show the tag: waiting costs the memory system 64 small loads per round, not 32 KiB (reading all
-  // again instead, steps in us: d = 1024 1893 -> 1905, d = 512 800 -> 810; for up to four rows only: 1904, 805).
-  const int fs_ = min(lane >> 3, FW - 1), hs_ = (lane >> 2) & 1, rs_ = max(R - 1 - (lane & 3), 0);
+  // first or second half - a producer tile owns half a fragment row - in a row of wave l%4 of that tile) and reads the
+  // fragments again once those show the tag: waiting costs the memory system 64 small loads per round, not 32 KiB.  Which of a wave's rows differs
+  // between workgroups, so that not all look at the same lines.  (Steps of d = 512 and 1024 in us: 583 and 1452; the last four rows for all 588 and
+  // 1456; reading all again instead 658 and 1516; the sums of squares or flags of the tiles, a few lines that all waiting waves share, 715 and 1557.)
+  const int fs_ = min(lane >> 3, FW - 1), hs_ = (lane >> 2) & 1, wr_ = (lane & 3) + 4 * (int)(blockIdx.x & 3), rs_ = min(wr_ < R ? wr_ : lane & 3, R - 1);
   const pk_x_t watched = A + (long)(wave * FW) * EF + (long)rs_ * lda + fs_ * EF + hs_ * (EF / 2);
   const float eps = a.eps;
   PK_MARK(1);
