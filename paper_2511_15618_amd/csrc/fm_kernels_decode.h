@@ -338,6 +338,7 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
     // Read ahead: the GEMMs behind this launch wait for cold weights, about a third of their 4 us, while a short attention leaves the
     // memory and compute units idle.  L2 outlives a launch; each die has its own, and workgroup i runs on die i mod 8, as do the column tiles
     // i mod 8 of a GEMM (only the speed depends on that).  The data goes to LDS and is never looked at.
+    if (a.run_flag && *a.run_flag == 0) return;
     const int plane = gridDim.x * gridDim.y, base = plane * a.nset * a.S, id = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
     const int die = id & 7, rank = (id - base) >> 3, ranks = max(1, (plane * a.ahead) >> 3);
     if (rank >= ranks) return;
@@ -630,8 +631,9 @@ __global__ __launch_bounds__(256) void k_dec_rmsnorm(const float* const* __restr
 // coarse slot j pools fine rows 3j-2, 3j-1, 3j (rows before the start count as zero; always / 3)
 template <typename T>
 __global__ __launch_bounds__(256) void k_dec_pool3(const float* __restrict__ ring_fine, int RSf, const int* __restrict__ pos_coarse,
-                                                    int RPS, T* __restrict__ out, int d) {
+                                                    int RPS, T* __restrict__ out, int d, const int* run_flag) {
   const int r = blockIdx.x, j = pos_coarse[r], s = r / RPS;
+  if (*run_flag == 0) return;
   for (int n = threadIdx.x * 4; n < d; n += 1024) {
     f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
     if (j >= 0) {
@@ -649,8 +651,9 @@ __global__ __launch_bounds__(256) void k_dec_pool3(const float* __restrict__ rin
 template <typename T>
 __global__ __launch_bounds__(256) void k_dec_upsample(float* __restrict__ h, const int* __restrict__ pos, int RPS,
                                                        const float* __restrict__ ring_coarse, int RSc, int d, T* __restrict__ xg,
-                                                       const float* __restrict__ gain, float* __restrict__ ssq) {
+                                                       const float* __restrict__ gain, float* __restrict__ ssq, const int* run_flag) {
   const int r = blockIdx.x, p = pos[r];
+  if (*run_flag == 0) return;
   const float* c = ring_coarse + ((long)(r / RPS) * RSc + ((max(p, 0) / 3) & (RSc - 1))) * d;
   for (int n = threadIdx.x * 4; n < d; n += 1024) {
     f32x4 v = *reinterpret_cast<const f32x4*>(h + (long)r * d + n);

@@ -29,6 +29,7 @@ struct StateDev {
   int* hist;          // [S][maxtok + 1], hist[p] = x_p
   int* budget;        // [1]
   int* alive;         // [1] unfinished sequences; doubles as the run flag of the step
+  int* level_rows;    // [3] does a level have a row in this verify pass?  Run flags of its launches (k_verify_setup)
   unsigned long long* acc_hist;  // [3][32]: accepted lengths of steps whose block carried coordinate-level drafts only /
                                  // a fresh point-level prediction / a fresh face-level prediction
   unsigned long long* counters;  // [0] steps, [1] tokens, [2] verify rows with a non-finite logit
@@ -53,6 +54,12 @@ __global__ __launch_bounds__(256) void k_verify_setup(StateDev st, Dims D, InvFr
                                                        float2* cs_f, unsigned* epoch, const T* __restrict__ emb, float* __restrict__ h,
                                                        T* __restrict__ xg, const float* __restrict__ gain, float* __restrict__ ssq) {
   if (epoch && blockIdx.x == 0 && threadIdx.x == 0) *epoch += 1;     // pass counter of the single-launch verify kernel
+  if (blockIdx.x == 0 && threadIdx.x < 64) {      // at most 64 sequences, a lane each
+    const int q = threadIdx.x < D.S ? (int)threadIdx.x : 0, n = (int)threadIdx.x < D.S ? eff_block_len(st, D, q, block_len) : 0, P0 = st.P[q];
+    const bool v = n > 0 && (P0 + 2) / 3 * 3 < P0 + n, f = n > 0 && (P0 + 8) / 9 * 9 < P0 + n;
+    const int alive = st.alive[0], anyv = __any(v), anyf = __any(f);
+    if (threadIdx.x < 3) st.level_rows[threadIdx.x] = threadIdx.x == 0 ? alive : alive && (threadIdx.x == 1 ? anyv : anyf);
+  }
   const int Rc = D.S * D.Bm, Rv = D.S * D.VB;
   const int level = (int)blockIdx.x < Rc ? 0 : (int)blockIdx.x < Rc + Rv ? 1 : 2;
   const int idx = blockIdx.x - (level == 0 ? 0 : level == 1 ? Rc : Rc + Rv);
