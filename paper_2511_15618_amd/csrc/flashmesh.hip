@@ -117,7 +117,7 @@ struct fm_ctx {
   // draft scratch
   DraftRows dr;
   DraftBufs db;
-  float *spv_out, *spf_out, *hfv_out, *dh, *dkeep, *dlogits;
+  float *spv_out, *spf_out, *hfv_out, *dh, *dlogits;
   float *dist_c, *dist_v, *dist_f;
   void* dq;
   StepParams params{};     // host copy of the settings below, StepParams on the device
@@ -443,14 +443,19 @@ int verify_impl(fm_ctx* c, const int32_t* block_tok, const int32_t* block_len, f
   return FM_OK;
 }
 
-// Query projection of draft rows: grouped GEMM over `G` sets of `M` rows each with the rotation applied, row (set g, m) -> m * G + g
+// Query projection of draft rows behind their norm: grouped GEMM over `G` sets of `M` rows each with the rotation applied, row (set g, m) -> m * G + g
+// in the tables and in the output
 template <typename T>
-void draft_query(fm_ctx* c, const void* W, int M, int G, int tiles, const float2* cs, const int* flag) {
+void draft_query(fm_ctx* c, const float* const* src, const float* gain, const void* W, int M, int G, const RowMap& rm, int per_seq, const float2* cs, const int* flag) {
   const int d = c->D.d;
   DecGemm a{};
-  a.A = c->dX; a.gsa = (long)tiles * 16 * d; a.W = W; a.gsw = (long)d * d; a.M = M; a.N = d; a.KT = d / 32; a.run_flag = flag;
+  a.W = W; a.gsw = (long)d * d; a.M = M; a.N = d; a.KT = d / 32; a.run_flag = flag; a.eps = c->cfg.rms_eps; a.inv_k = 1.0f / d;
   a.Y = c->dq; a.ldy = (long)G * d; a.gsy = d; a.cs = cs; a.ldc = G; a.hd = c->D.hd; a.H = c->D.H;
-  dec_gemm<T, DE_ROPE, false>(a, G, c->stream);
+  a.src = src; a.sgain = gain;
+  if (dec_gemm_rows<T, DE_ROPE>(a, G, c->stream)) return;
+  hipLaunchKernelGGL((k_dec_rmsnorm<T>), dim3(M * G), dim3(256), 0, c->stream, src, gain, G, (T*)c->dX, rm, per_seq, d, c->cfg.rms_eps, flag);
+  a.A = c->dX; a.gsa = (long)rm.tiles * 16 * d;
+  dec_gemm<T, DE_ROPE, DN_NONE>(a, G, c->stream);
 }
 
 // The SP chains (Eq. 1) of all three levels as one chain of grouped launches: the row set is, per sequence, the point-,
@@ -461,7 +466,7 @@ template <typename T>
 void run_sp(fm_ctx* c, const int* flag) {
   const Dims& D = c->D;
   const SpLevel& A = c->sp_all;
-  const int d = D.d, G = A.cnt, S = D.S, rows = S * G;
+  const int d = D.d, G = A.cnt, S = D.S;
   if (G == 0) return;
   const RowMap rm{G, 1, 0, c->sp_tiles};
   const int nrow[3] = {D.nspv, D.nspf, D.Dc}, lev[3] = {1, 2, 0};
@@ -481,8 +486,7 @@ void run_sp(fm_ctx* c, const int* flag) {
   };
   DecGemm g{};
   g.A = c->dX; g.gsa = (long)c->sp_tiles * 16 * d; g.gsw = (long)d * d; g.M = S; g.N = d; g.KT = d / 32; g.run_flag = flag;
-  hipLaunchKernelGGL((k_dec_rmsnorm<T>), dim3(rows), dim3(256), 0, c->stream, c->dr.src[1], A.g, G, (T*)c->dX, rm, G, c->dkeep, d, c->cfg.rms_eps, flag);
-  draft_query<T>(c, A.wq, S, G, c->sp_tiles, c->dr.cs[1], flag);
+  draft_query<T>(c, c->dr.src[1], A.g, A.wq, S, G, rm, G, c->dr.cs[1], flag);
   attn(c->dr.lim[1], false);
   // output projection of the self-attention, then straight (no norm, Eq. 1) the cross-attention query
   DecGemm a = g;
@@ -498,7 +502,7 @@ void run_sp(fm_ctx* c, const int* flag) {
   // outputs: per sequence the point, face and coordinate rows behind each other (spv_out, spf_out and the rows the output
   // head's pointer table names)
   a = g;
-  a.A = c->dmidX; a.W = A.lin; a.Y = c->spv_out; a.ldy = (long)G * d; a.gsy = d; a.R = c->dkeep; a.ldr = (long)G * d; a.gsr = d;
+  a.A = c->dmidX; a.W = A.lin; a.Y = c->spv_out; a.ldy = (long)G * d; a.gsy = d; a.Rt = c->dr.src[1]; a.ldc = G;
   dec_gemm<T, DE_F32, false>(a, G, c->stream);
 }
 
@@ -507,11 +511,10 @@ void run_sp(fm_ctx* c, const int* flag) {
 template <typename T>
 void run_hf(fm_ctx* c, int set, const HfLevel& hf, int mult, const Layer& last, int level, float* out, const int* flag) {
   const Dims& D = c->D;
-  const int d = D.d, G = hf.cnt, per_seq = G * mult, rows = D.S * per_seq, Mg = D.S * mult, tiles = c->hf_tiles[set - 3];
+  const int d = D.d, G = hf.cnt, per_seq = G * mult, Mg = D.S * mult, tiles = c->hf_tiles[set - 3];
   if (G == 0) return;
   const RowMap rm{G, mult, 0, tiles};
-  hipLaunchKernelGGL((k_dec_rmsnorm<T>), dim3(rows), dim3(256), 0, c->stream, c->dr.src[set], hf.g, G, (T*)c->dX, rm, per_seq, c->dkeep, d, c->cfg.rms_eps, flag);
-  draft_query<T>(c, hf.wq, Mg, G, tiles, c->dr.cs[set], flag);
+  draft_query<T>(c, c->dr.src[set], hf.g, hf.wq, Mg, G, rm, per_seq, c->dr.cs[set], flag);
   AttnArgs t{};
   t.S = D.S; t.H = D.H; t.ws = c->attn_ws; t.arrived = c->attn_arrived; t.run_flag = flag;
   const int cap = level_cap(c, level);
@@ -525,7 +528,7 @@ void run_hf(fm_ctx* c, int set, const HfLevel& hf, int mult, const Layer& last, 
   a.X = c->dmidX; a.gsx = (long)tiles * 16 * c->hff;
   dec_gemm<T, DE_GELU, false>(a, G, c->stream);
   a.A = c->dmidX; a.gsa = a.gsx; a.W = hf.w2; a.N = d; a.KT = c->hff / 32; a.X = nullptr;
-  a.Y = out; a.ldy = (long)G * d; a.gsy = d; a.R = c->dkeep; a.ldr = (long)G * d; a.gsr = d;
+  a.Y = out; a.ldy = (long)G * d; a.gsy = d; a.Rt = c->dr.src[set]; a.ldc = G;
   dec_gemm<T, DE_F32, false>(a, G, c->stream);
 }
 
@@ -533,10 +536,13 @@ void run_hf(fm_ctx* c, int set, const HfLevel& hf, int mult, const Layer& last, 
 template <typename T>
 void draft_logits(fm_ctx* c, int n, const int* flag) {
   const Dims& D = c->D;
-  hipLaunchKernelGGL((k_dec_rmsnorm<T>), dim3(n), dim3(256), 0, c->stream, c->lm_src, c->gf, 0, (T*)c->dX, RowMap{1, 0, 0, 0}, n, (float*)nullptr, D.d, c->cfg.rms_eps, flag);
   DecGemm a{};
-  a.A = c->dX; a.W = c->lm; a.M = n; a.N = D.V; a.KT = D.d / 32; a.run_flag = flag; a.Y = c->dlogits; a.ldy = D.V;
-  dec_gemm<T, DE_F32, false>(a, 1, c->stream);
+  a.W = c->lm; a.M = n; a.N = D.V; a.KT = D.d / 32; a.run_flag = flag; a.Y = c->dlogits; a.ldy = D.V;
+  a.src = c->lm_src; a.sgain = c->gf; a.ldc = 1; a.eps = c->cfg.rms_eps; a.inv_k = 1.0f / D.d;
+  if (dec_gemm_rows<T, DE_F32>(a, 1, c->stream)) return;
+  hipLaunchKernelGGL((k_dec_rmsnorm<T>), dim3(n), dim3(256), 0, c->stream, c->lm_src, c->gf, 0, (T*)c->dX, RowMap{1, 0, 0, 0}, n, D.d, c->cfg.rms_eps, flag);
+  a.A = c->dX;
+  dec_gemm<T, DE_F32, DN_NONE>(a, 1, c->stream);
 }
 
 template <typename T>
@@ -952,7 +958,7 @@ int build_buffers(fm_ctx* c) {
   }
   TRY(dalloc(c, &c->dlogits, nLM * D.V));
   const size_t rmax = std::max(maxset, nLM);
-  TRY(dalloc(c, &c->dkeep, rmax * d)); TRY(dalloc_t(c, &c->dq, rmax * d));
+  TRY(dalloc_t(c, &c->dq, rmax * d));
   {
     c->sp_tiles = (int)(S + 15) / 16; c->hf_tiles[0] = (int)(S + 15) / 16; c->hf_tiles[1] = (int)(2 * S + 15) / 16;
     const size_t sp = (size_t)G_all * c->sp_tiles, hv = (size_t)D.nhfv * c->hf_tiles[0], hc = (size_t)D.nhfc * c->hf_tiles[1], lmt = (nLM + 15) / 16;

@@ -39,17 +39,24 @@ __device__ __forceinline__ long map_off(const RowMap& rm, int s, int q, int n, i
 // GEMM
 // ------------------------------------------------------------------------------------------
 enum { DE_RES = 0, DE_GELU, DE_ROW, DE_TILE, DE_F32, DE_QKV, DE_ROPE };
+// The norm in front of a GEMM: none; its input is x * gain already and comes with the row sums of squares; or the input is fp32 rows, scattered in
+// memory, and every workgroup forms x * gain and the sums of squares from them (the draft heads, whose rows no GEMM has left in operand order:
+// a launch of 4 us less for each of their four norms).
+enum { DN_NONE = 0, DN_SSQ, DN_ROWS };
 
 struct DecGemm {
   const void* A; long gsa;       // tiled activations, elements per group
   const void* W; long gsw;       // tiled weights, elements per group
   int M, N, KT;                  // rows per group, columns, K / 32
-  const float* ssq;              // NORM: [row tile][K/16][16] sums of squares of 16 columns each
+  const float* ssq;              // DN_SSQ: [row tile][K/16][16] sums of squares of 16 columns each
+  const float* const* src;       // DN_ROWS: fp32 rows by pointer, row m of a group at src[m * ldc + group]
+  const float* sgain;            // and their gain, K values per group
   float inv_k, eps;
   const int* run_flag;           // the launch is skipped when *run_flag == 0 (may be null)
   // outputs (which of them: the epilogue)
   void* Y; long ldy, gsy;        // row-major output: fp32 (DE_RES, DE_F32) or half (DE_ROW, DE_QKV q, DE_ROPE)
-  const float* R; long ldr, gsr; // fp32 rows added (DE_RES, DE_F32; may be null, may be Y)
+  const float* R; long ldr, gsr; // fp32 rows added (DE_RES; may be null, may be Y)
+  const float* const* Rt;        // DE_F32: fp32 rows added, by pointer as src (may be null)
   void* X; long gsx;             // tiled half output of width N (DE_GELU, DE_TILE; DE_RES: x * gain, may be null)
   const float* gain;             // DE_RES: gain of the norm that follows
   float* ssq_out;                // DE_RES: [row tile][N/16][16]
@@ -57,14 +64,14 @@ struct DecGemm {
   int RPS;                       // rows per sequence
   float *tap, *ring; int rs;     // DE_RES: rings (rs entries per sequence) that receive the old row (tap) and the new row
   const float2* cs;              // DE_QKV, DE_ROPE: [row][hd/2] (cos, sin); DE_ROPE: row = m * ldc + group
-  int ldc, hd;
+  int ldc, hd;                   // rows of a table (cs, src, Rt) between two rows of a group
   void *Kc, *Vc; long seq_stride; int capb, H;   // DE_QKV: blocked caches
 };
 
 // MT row tiles x NC column tiles of 16 per workgroup, NW waves split K.
 // U fragments per wave and chunk: the first chunk (all of the K slice for the usual shapes) is in flight before
 // anything is waited for, later chunks one ahead.
-template <typename T, int MT, int NC, int NW, int U, bool LOOP, int EPI, bool NORM>
+template <typename T, int MT, int NC, int NW, int U, bool LOOP, int EPI, int NORM>
 __global__ __launch_bounds__(NW * 64) void k_dec_gemm(DecGemm a) {
   typedef typename Op<T>::V8 V8;
   typedef typename Op<T>::V4 V4;
@@ -87,6 +94,10 @@ __global__ __launch_bounds__(NW * 64) void k_dec_gemm(DecGemm a) {
 #pragma unroll
     for (int c = 0; c < NC; c++) acc[mt][c] = f32x4{0.f, 0.f, 0.f, 0.f};
   V8 wc[NC][U], ac[MT][U];
+  // rows by pointer: the pointers are asked for first, so that waiting for them waits for nothing else
+  const float *xrow = nullptr, *rrow = nullptr;
+  if constexpr (NORM == DN_ROWS) xrow = a.src[(long)min(mt0 * 16 + rl, a.M - 1) * a.ldc + grp];
+  if (EPI == DE_F32 && a.Rt && wave < NTILE) rrow = a.Rt[(long)min((mt0 + wave / NC) * 16 + rl, a.M - 1) * a.ldc + grp];
   auto load_chunk = [&](V8 (&w)[NC][U], V8 (&x)[MT][U], int i0) {
 #pragma unroll
     for (int u = 0; u < U; u++)
@@ -95,13 +106,36 @@ __global__ __launch_bounds__(NW * 64) void k_dec_gemm(DecGemm a) {
 #pragma unroll
         for (int c = 0; c < NC; c++) w[c][u] = *reinterpret_cast<const V8*>(Wp + ((long)c * KT + kt) * 512);
 #pragma unroll
-        for (int mt = 0; mt < MT; mt++) {
+        for (int mt = 0; mt < (NORM == DN_ROWS ? 0 : MT); mt++) {
           const int t = min(mt0 + mt, ntile - 1);          // a tile past the last one is computed on the last one's rows, never stored
           x[mt][u] = *reinterpret_cast<const V8*>(Ap + ((long)t * KT + kt) * 512);
         }
       }
   };
   load_chunk(wc, ac, 0);
+  float ss[MT];
+  if constexpr (NORM == DN_ROWS) {
+    static_assert(MT == 1 && !LOOP);
+    const float* gp = a.sgain + (long)grp * KT * 32;
+    f32x4 xv[U][2], gn[U][2];
+#pragma unroll
+    for (int u = 0; u < U; u++)
+      if (u < nk) {
+        const int k = (kt0 + u) * 32 + g * 8;
+#pragma unroll
+        for (int h = 0; h < 2; h++) { gn[u][h] = *reinterpret_cast<const f32x4*>(gp + k + 4 * h); xv[u][h] = *reinterpret_cast<const f32x4*>(xrow + k + 4 * h); }
+      }
+    ss[0] = 0.f;
+#pragma unroll
+    for (int u = 0; u < U; u++)
+      if (u < nk)
+#pragma unroll
+        for (int j = 0; j < 8; j++) {
+          const float x = xv[u][j >> 2][j & 3];
+          ss[0] += x * x;
+          ac[0][u][j] = (T)(x * gn[u][j >> 2][j & 3]);
+        }
+  }
   // operands of the epilogue of this wave's first result tile
   const int tm = wave / NC, tc = wave % NC;
   const int em = (mt0 + tm) * 16 + rl, en = (nt0 + tc) * 16 + g * 4;
@@ -109,8 +143,8 @@ __global__ __launch_bounds__(NW * 64) void k_dec_gemm(DecGemm a) {
   f32x4 rv = f32x4{0.f, 0.f, 0.f, 0.f}, gv = rv, c0 = rv, c1 = rv;
   int ep = -1;
   if (eon) {
-    if ((EPI == DE_RES || EPI == DE_F32) && a.R && (EPI == DE_RES || a.N % 16 == 0))
-      rv = *reinterpret_cast<const f32x4*>(a.R + (long)grp * a.gsr + (long)em * a.ldr + en);
+    if (EPI == DE_RES && a.R) rv = *reinterpret_cast<const f32x4*>(a.R + (long)em * a.ldr + en);
+    if (EPI == DE_F32 && a.Rt && a.N % 16 == 0) rv = *reinterpret_cast<const f32x4*>(rrow + en);
     if (EPI == DE_RES) {
       if (a.gain) gv = *reinterpret_cast<const f32x4*>(a.gain + en);
       if (a.pos) ep = a.pos[em];
@@ -126,8 +160,7 @@ __global__ __launch_bounds__(NW * 64) void k_dec_gemm(DecGemm a) {
       }
     }
   }
-  float ss[MT];
-  if constexpr (NORM) {
+  if constexpr (NORM == DN_SSQ) {
     const int ns = KT * 2;
 #pragma unroll
     for (int mt = 0; mt < MT; mt++) {
@@ -165,7 +198,7 @@ __global__ __launch_bounds__(NW * 64) void k_dec_gemm(DecGemm a) {
   for (int mt = 0; mt < MT; mt++) {
 #pragma unroll
     for (int c = 0; c < NC; c++) red[(wave * NTILE + mt * NC + c) * 64 + lane] = acc[mt][c];
-    if constexpr (NORM) {
+    if constexpr (NORM != DN_NONE) {
       const float t = rows_sum(ss[mt]);
       if (g == 0) sq[(wave * MT + mt) * 16 + rl] = t;
     }
@@ -177,7 +210,7 @@ __global__ __launch_bounds__(NW * 64) void k_dec_gemm(DecGemm a) {
     f32x4 v = red[t * 64 + lane];
 #pragma unroll
     for (int w = 1; w < NW; w++) v += red[(w * NTILE + t) * 64 + lane];
-    if constexpr (NORM) {
+    if constexpr (NORM != DN_NONE) {
       float tot = sq[mt * 16 + rl];
 #pragma unroll
       for (int w = 1; w < NW; w++) tot += sq[(w * MT + mt) * 16 + rl];
@@ -226,13 +259,13 @@ __global__ __launch_bounds__(NW * 64) void k_dec_gemm(DecGemm a) {
       if (on) {
         float* y = (float*)a.Y + (long)grp * a.gsy + (long)m * a.ldy + n;
         if (a.N % 16 == 0) {
-          if (!first && a.R) rv = *reinterpret_cast<const f32x4*>(a.R + (long)grp * a.gsr + (long)m * a.ldr + n);
+          if (!first && a.Rt) rv = *reinterpret_cast<const f32x4*>(a.Rt[(long)m * a.ldc + grp] + n);
           v += rv;
           *reinterpret_cast<f32x4*>(y) = v;
         } else {
 #pragma unroll
           for (int i = 0; i < 4; i++)
-            if (n + i < a.N) y[i] = v[i] + (a.R ? a.R[(long)grp * a.gsr + (long)m * a.ldr + n + i] : 0.f);
+            if (n + i < a.N) y[i] = v[i] + (a.Rt ? a.Rt[(long)m * a.ldc + grp][n + i] : 0.f);
         }
       }
     } else {
@@ -593,11 +626,11 @@ __device__ __forceinline__ void put_row4(const f32x4& v, int m, int n, int d, fl
   if ((threadIdx.x & 3) == 0) ssq[((long)(m >> 4) * (d >> 4) + (n >> 4)) * 16 + (m & 15)] = t;
 }
 
-// RMSNorm of gathered rows into the tiled input of a grouped GEMM (row r = s * per_seq + q, gain of head r % gain_mod),
-// keeping the fp32 rows for a later residual add
+// RMSNorm of gathered rows into the tiled input of a grouped GEMM (row r = s * per_seq + q, gain of head r % gain_mod), where the GEMM does not
+// take the rows itself (dec_gemm_rows)
 template <typename T>
 __global__ __launch_bounds__(256) void k_dec_rmsnorm(const float* const* __restrict__ srcptr, const float* __restrict__ gain, int gain_mod,
-                                                      T* __restrict__ out, RowMap rm, int per_seq, float* __restrict__ keep, int d,
+                                                      T* __restrict__ out, RowMap rm, int per_seq, int d,
                                                       float eps, const int* run_flag) {
   const int r = blockIdx.x;
   const int rf = run_flag ? *run_flag : 1;
@@ -620,7 +653,6 @@ __global__ __launch_bounds__(256) void k_dec_rmsnorm(const float* const* __restr
   for (int n = threadIdx.x * 4; n < d; n += 1024) {
     const f32x4 v = n < 1024 ? v0 : *reinterpret_cast<const f32x4*>(x + n);
     const f32x4 gv = *reinterpret_cast<const f32x4*>(g + n);
-    if (keep) *reinterpret_cast<f32x4*>(keep + (long)r * d + n) = v;
     typename Op<T>::V4 o;
 #pragma unroll
     for (int i = 0; i < 4; i++) o[i] = (T)(v[i] * inv * gv[i]);
@@ -665,7 +697,7 @@ __global__ __launch_bounds__(256) void k_dec_upsample(float* __restrict__ h, con
 // ------------------------------------------------------------------------------------------
 // Launch rules
 // ------------------------------------------------------------------------------------------
-template <typename T, int MT, int NC, int NW, int U, bool LOOP, int EPI, bool NORM>
+template <typename T, int MT, int NC, int NW, int U, bool LOOP, int EPI, int NORM>
 void dec_gemm_launch(const DecGemm& a, int groups, hipStream_t st) {
   const int tiles = (a.M + 15) / 16, NT = (a.N + 15) / 16;
   const size_t lds = (size_t)NW * MT * NC * 1024 + NW * MT * 64;
@@ -678,7 +710,7 @@ void dec_gemm_launch(const DecGemm& a, int groups, hipStream_t st) {
 // Measured in a chain of dependent launches over cold weights (us; M rows, d = K of the first four):
 //   M = 9, d = 1024: projection 3.7, up 4.5, down 6.8      M = 27, d = 768: 3.5, 4.4, 5.9
 //   M = 72, d = 1024: 4.1, 6.7, 7.6                        M = 72, d = 1536: 5.1, 11.1, 11.7
-template <typename T, int EPI, bool NORM>
+template <typename T, int EPI, int NORM>
 void dec_gemm(const DecGemm& a, int groups, hipStream_t st) {
   const int tiles = (a.M + 15) / 16, NT = (a.N + 15) / 16, KT = a.KT;
   const long wgs = (long)NT * tiles * groups;
@@ -699,6 +731,18 @@ void dec_gemm(const DecGemm& a, int groups, hipStream_t st) {
     // many: two column tiles share the activations
     return KT <= 32 ? dec_gemm_launch<T, 1, 2, 4, 8, false, EPI, NORM>(a, groups, st) : dec_gemm_launch<T, 1, 2, 8, 8, false, EPI, NORM>(a, groups, st);
   }
+}
+
+// GEMM whose workgroups norm their rows themselves (DN_ROWS); false: not for this size.  A lane holds rows and gains as fp32 beside the weights, up to
+// eight fragments of each (four waves up to K = 1024, eight up to 2048; fp32 up to 1024).  For one row tile and few workgroups: each of them
+// reads twice the bytes of rows in operand order, and gains.  Steps with the norm inside / in a launch of its own, us: d = 512 one sequence
+// 578 / 584, a mesh of d = 256 fp32 10 950 / 10 985; for all sizes d = 2048 2270 / 2210, eight sequences of d = 1024 3196 / 3184.
+template <typename T, int EPI>
+bool dec_gemm_rows(const DecGemm& a, int groups, hipStream_t st) {
+  if (a.M > 16 || (long)((a.N + 15) / 16) * groups > 400 || a.KT > (std::is_same<T, float>::value ? 32 : 64)) return false;
+  if (a.KT <= 32) dec_gemm_launch<T, 1, 1, 4, 8, false, EPI, DN_ROWS>(a, groups, st);
+  else if constexpr (!std::is_same<T, float>::value) dec_gemm_launch<T, 1, 1, 8, 8, false, EPI, DN_ROWS>(a, groups, st);
+  return true;
 }
 
 // Splits of an attention launch over `pairs` (head, sequence, set) triples: at most one workgroup of eight waves per compute

@@ -188,3 +188,26 @@ def test_single_launch_past_the_first_group_of_keys(m, n, drafts):
     rep, streams, fm = lockstep(cfg, cfg.faces, TOL[cfg.dtype], drafts=drafts)
     print(rep, flush=True)
     assert len(streams[0]) == 9 * cfg.faces > 128 + 18 and fm.verify_path() == 1
+
+
+@pytest.mark.parametrize("dtype,batch", [("f32", 1), ("bf16", 2)])
+def test_passes_whose_levels_have_no_row(dtype, batch):
+    """One launch per operator, token by token: two passes in three begin no vertex, eight in nine no face."""
+    from parity_harness import lockstep
+    cfg = _cfg("no_rows_%s%d" % (dtype, batch), 128, 2, 60, dtype, batch, 4, 2, 9, 9)
+    print("case", cfg.name, flush=True)
+    rep, streams, fm = lockstep(cfg, cfg.faces, TOL[dtype], drafts="none")
+    print(rep, flush=True)
+    assert rep.steps == 9 * cfg.faces and fm.verify_path() == 0
+
+
+@pytest.mark.parametrize("d,heads,dtype,batch", [(1152, 18, "bf16", 2), (2112, 33, "bf16", 1), (1088, 17, "f32", 1), (128, 2, "bf16", 17)])
+def test_draft_rows_normed_by_their_gemms(d, heads, dtype, batch):
+    """The norms of the draft heads inside their GEMMs with eight waves, past the widths that take them (half 2048, fp32 1024), and for more than one
+    row tile per head (the output head's rows then are too many)."""
+    from parity_harness import lockstep
+    cfg = _cfg("draft_rows%d%s" % (d, dtype), d, heads, 24, dtype, batch, 2, 2, 9, 9)
+    print("case", cfg.name, flush=True)
+    rep, streams, fm = lockstep(cfg, cfg.faces, TOL[dtype], max_steps=6)
+    print(rep, flush=True)
+    assert rep.dist_rows > 0
