@@ -291,7 +291,7 @@ void choose_and_accept(fm_ctx* c, const float* logits, int32_t* accepted) {
   const Dims& D = c->D;
   if (c->params.temperature > 0.f) {
     hipLaunchKernelGGL(k_sample_rows, dim3(c->Rc), dim3(256), 0, c->stream, c->st, D, logits, c->smp);
-    hipLaunchKernelGGL(k_accept, dim3(1), dim3(64), 0, c->stream, c->st, D, accepted, (const int*)c->smp.accflag, pass_failed(c));
+    hipLaunchKernelGGL(k_accept, dim3(D.S), dim3(64), 0, c->stream, c->st, D, accepted, (const int*)c->smp.accflag, pass_failed(c));
   } else {
     hipLaunchKernelGGL(k_choose_greedy, dim3(D.S), dim3(1024), 0, c->stream, c->st, D, logits, D.ban ? D.nbins : D.V, accepted, pass_failed(c),
                        c->st.counters + 2);
@@ -585,7 +585,7 @@ int step_flags(const fm_ctx* c, int speculative) {
   return (speculative ? 1 : 0) | (c->params.temperature > 0.f ? 2 : 0);
 }
 int commit_any(fm_ctx* c, const int32_t* accepted, bool report) {
-  hipLaunchKernelGGL(k_commit, dim3(1), dim3(64), 0, c->stream, c->st, c->D, accepted, pass_failed(c), c->commits_dev, report ? c->prog : nullptr);
+  hipLaunchKernelGGL(k_commit, dim3(1), dim3(64 * std::min(c->D.S, 16)), 0, c->stream, c->st, c->D, accepted, pass_failed(c), c->commits_dev, report ? c->prog : nullptr);
   HIPCHK(c, hipGetLastError());
   return FM_OK;
 }

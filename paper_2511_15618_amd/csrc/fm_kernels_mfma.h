@@ -73,6 +73,24 @@ __device__ __forceinline__ float rows_max(float v) {
   return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
+// Greedy choice over a wave: the largest value, among equals the lowest index; in every lane
+__device__ __forceinline__ void wave_argmax(float& bv, int& bi) {
+  float m = fmaxf(bv, lane_dpp<0xB1>(bv));
+  m = fmaxf(m, lane_dpp<0x4E>(m));
+  m = fmaxf(m, lane_dpp<0x141>(m));
+  m = rows_max(fmaxf(m, lane_dpp<0x140>(m)));
+  int i = bv == m ? bi : 0x7fffffff;
+  i = min(i, __builtin_amdgcn_update_dpp(0, i, 0xB1, 0xF, 0xF, true));
+  i = min(i, __builtin_amdgcn_update_dpp(0, i, 0x4E, 0xF, 0xF, true));
+  i = min(i, __builtin_amdgcn_update_dpp(0, i, 0x141, 0xF, 0xF, true));
+  i = min(i, __builtin_amdgcn_update_dpp(0, i, 0x140, 0xF, 0xF, true));
+  const auto a = __builtin_amdgcn_permlane16_swap((unsigned)i, (unsigned)i, false, false);
+  i = min((int)a[0], (int)a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap((unsigned)i, (unsigned)i, false, false);
+  bv = m;
+  bi = min((int)b[0], (int)b[1]);
+}
+
 // Values that workgroups of one launch hand to each other (attention parts) are written and read at agent scope: the stores are
 // written through to where all dies see them, the loads bypass the die's own L2.
 __device__ __forceinline__ void st_agent(float* p, float v) {

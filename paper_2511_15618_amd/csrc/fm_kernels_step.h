@@ -97,23 +97,20 @@ __global__ __launch_bounds__(256) void k_verify_setup(StateDev st, Dims D, InvFr
 }
 
 // accepted = 1 + number of leading drafts that equal the backbone's greedy prediction; with sampled decoding 1 + number of
-// leading drafts that passed the rejection test (flag of row i is about draft i + 1).  `passed(i)`: draft i + 1 stands.
+// leading drafts that passed the rejection test.  passed: bit i is about draft i + 1 (below len - 1; a wave's ballot).
 // (failed: the forward pass gave up and its logits mean nothing; the accepted length is 0)
-template <class F>
-__device__ __forceinline__ void accept_seq(const StateDev& st, int s, int len, int* accepted_out, bool failed, F passed) {
-  int a = 0;
-  if (len > 0 && !failed) {
-    a = 1;
-    while (a < len && passed(a - 1)) a++;
-  }
-  if (accepted_out) accepted_out[s] = a;
+__device__ __forceinline__ int accepted_length(unsigned long long passed, int len, bool failed) {
+  return len > 0 && !failed ? 1 + min(__ffsll(~passed) - 1, len - 1) : 0;
 }
 
-__global__ void k_accept(StateDev st, Dims D, int* __restrict__ accepted_out, const int* __restrict__ accflag,
-                         const unsigned* __restrict__ failed) {
-  const int s = threadIdx.x;
-  if (s >= D.S) return;
-  accept_seq(st, s, st.vlen[s], accepted_out, failed && *failed, [&](int i) { return accflag[s * D.Bm + i] != 0; });
+// one wave per sequence, a draft per lane (blocks are at most 27 tokens long)
+__global__ __launch_bounds__(64) void k_accept(StateDev st, Dims D, int* __restrict__ accepted_out, const int* __restrict__ accflag,
+                                               const unsigned* __restrict__ failed) {
+  const int s = blockIdx.x, i = threadIdx.x;
+  const bool bad = failed && *failed;
+  const int len = st.vlen[s], flag = i < D.Bm ? accflag[s * D.Bm + i] : 0;
+  const int a = accepted_length(__ballot(i + 1 < len && flag != 0), len, bad);
+  if (i == 0 && accepted_out) accepted_out[s] = a;
 }
 
 // Greedy choice of every row of a sequence (lowest index among exact ties, over [0, nlim)) and its accepted length: one
@@ -143,12 +140,7 @@ __global__ __launch_bounds__(1024) void k_choose_greedy(StateDev st, Dims D, con
           argmax_merge(bv, bi, v[k], i0 + 64 * k);
         }
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      const float ov = __shfl_xor(bv, o, 64);
-      const int oi = __shfl_xor(bi, o, 64);
-      argmax_merge(bv, bi, ov, oi);
-    }
+    wave_argmax(bv, bi);
     bad = __any(bad);
     if (lane == 0) {
       sy[i] = bi;
@@ -157,7 +149,10 @@ __global__ __launch_bounds__(1024) void k_choose_greedy(StateDev st, Dims D, con
     }
   }
   __syncthreads();
-  if (threadIdx.x == 0) accept_seq(st, s, len, accepted_out, bad_pass, [&](int i) { return stok[i + 1] == sy[i]; });
+  if (wave == 0) {      // a draft per lane
+    const int a = accepted_length(__ballot(lane + 1 < min(len, 32) && stok[min(lane + 1, 31)] == sy[min(lane, 31)]), len, bad_pass);
+    if (lane == 0 && accepted_out) accepted_out[s] = a;
+  }
 }
 
 // What the host may look at while the device runs ahead of it: one pinned word per sequence (fm_progress.h), written by the
@@ -165,49 +160,52 @@ __global__ __launch_bounds__(1024) void k_choose_greedy(StateDev st, Dims D, con
 struct Progress { unsigned long long seq[64]; };
 
 // An accepted length of 0 (a pass that did not complete) leaves the sequence as it is.  prog: null for the caller's own commits.
-__global__ void k_commit(StateDev st, Dims D, const int* __restrict__ accepted, const unsigned* __restrict__ failed, unsigned* commits,
-                         Progress* prog) {
-  const int s = threadIdx.x;
-  __shared__ int any_live;
-  auto report = [&](bool bad) {
-    if (!prog) return;
-    const unsigned n = progress_next(*commits);       // one wave: read by all lanes before lane 0 writes it
-    if (s == 0) *commits = n;
-    if (s < D.S)
-      __hip_atomic_store(&prog->seq[s], progress_word(n, bad ? 0 : st.fin[s] ? 1 : st.P[s] + 2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-  };
-  if (failed && *failed) { report(true); return; }
-  if (s == 0) any_live = 0;
-  __syncthreads();
-  if (s < D.S) {
-    const int len = st.vlen[s];
-    if (len > 0 && accepted[s] > 0) {
-      any_live = 1;
-      int a = accepted[s];
-      a = min(a, len);
-      for (int i = 1; i < a; i++)
-        if (st.vtok[s * D.Bm + i] == D.eos) { a = i; break; }   // an accepted EOS draft is not fed: it becomes the main token
-      int P = st.P[s];
-      int* h = st.hist + (long)s * (D.maxtok + 1);
-      for (int i = 0; i < a; i++) h[P + i] = st.vtok[s * D.Bm + i];
-      P += a;
-      const int mainTok = st.y[s * D.Bm + a - 1];
-      h[P] = mainTok;
-      st.P[s] = P;
-      st.main[s] = mainTok;
-      st.fin[s] = (mainTok == D.eos || P >= st.budget[0]) ? 1 : 0;
-      st.vlen[s] = 0;
-      atomicAdd(&st.acc_hist[min(max(st.kind[s], 0), 2) * 32 + min(a, 31)], 1ull);
-      atomicAdd(&st.counters[1], (unsigned long long)a);
+// A wave per sequence, a token of the block per lane: all a sequence needs is read in one trip.  (A thread per sequence that walked its block
+// token by token, and such walks at the end of k_choose_greedy and k_merge: steps of d = 512 578 us instead of 574, meshes of d = 256 in fp32 10.95 ms
+// instead of 10.84.)
+__global__ __launch_bounds__(1024) void k_commit(StateDev st, Dims D, const int* __restrict__ accepted, const unsigned* __restrict__ failed, unsigned* commits,
+                                                 Progress* prog) {
+  __shared__ int s_pos[64], s_fin[64], s_moved[64];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6, i = threadIdx.x & 63;
+  const bool bad = failed && *failed;
+  for (int s = wave; s < D.S; s += waves) {
+    const int len = st.vlen[s], acc = accepted[s], P = st.P[s], fin = st.fin[s], kind = st.kind[s], budget = st.budget[0];
+    const int tok = i < D.Bm ? st.vtok[s * D.Bm + i] : 0, y = i < D.Bm ? st.y[s * D.Bm + i] : 0;
+    const bool moves = !bad && len > 0 && acc > 0;
+    int a = min(acc, len);
+    const unsigned long long ends = __ballot(i >= 1 && i < a && tok == D.eos);      // an accepted EOS draft is not fed: it becomes the main token
+    if (ends) a = __ffsll(ends) - 1;
+    const int mainTok = __shfl(y, max(a - 1, 0), 64);
+    const int now = moves ? (mainTok == D.eos || P + a >= budget ? 1 : 0) : fin;
+    if (moves) {
+      int* h = st.hist + (long)s * (D.maxtok + 1) + P;
+      if (i < a) h[i] = tok;
+      if (i == 0) {
+        h[a] = mainTok;
+        st.P[s] = P + a;
+        st.main[s] = mainTok;
+        st.fin[s] = now;
+        st.vlen[s] = 0;
+        atomicAdd(&st.acc_hist[min(max(kind, 0), 2) * 32 + min(a, 31)], 1ull);
+        atomicAdd(&st.counters[1], (unsigned long long)a);
+      }
     }
+    if (i == 0) { s_pos[s] = moves ? P + a : P; s_fin[s] = now; s_moved[s] = moves; }
   }
   __syncthreads();
-  const int alive = __popcll(__ballot(s < D.S && !st.fin[s]));      // one wave: at most 64 sequences
-  if (s == 0) {
+  if (wave != 0) return;
+  const bool on = i < D.S;      // a sequence per lane: at most 64
+  const int alive = __popcll(__ballot(on && !s_fin[on ? i : 0]));
+  const bool moved = __any(on && s_moved[on ? i : 0]);
+  if (i == 0 && !bad) {
     st.alive[0] = alive;
-    if (any_live) st.counters[0] += 1;
+    if (moved) st.counters[0] += 1;
   }
-  report(false);
+  if (prog) {
+    const unsigned n = progress_next(*commits);       // one wave: read by all lanes before lane 0 writes it
+    if (i == 0) *commits = n;
+    if (on) __hip_atomic_store(&prog->seq[i], progress_word(n, bad ? 0 : s_fin[i] ? 1 : s_pos[i] + 2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
 }
 
 // End of fm_generate: x_1 .. of every sequence and its length to the caller, counters to pinned host memory.
@@ -602,7 +600,6 @@ __global__ __launch_bounds__(1024) void k_merge(StateDev st, Dims D, DraftRows R
                                                 int speculative, int* __restrict__ block_tok,
                                                 int* __restrict__ block_len, Sampling sm) {
   __shared__ int stok[32];
-  __shared__ int slen;
   const int s = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const StepParams pr = *sm.p;
   const Replay& rp = pr.replay;
@@ -639,18 +636,14 @@ __global__ __launch_bounds__(1024) void k_merge(StateDev st, Dims D, DraftRows R
   for (int idx = 1 + wave; idx < D.Bm; idx += 16) {
     // the averaged distributions behind draft index idx (position spos + 1 + idx), if any level covers it
     const int p = spos + 1 + idx;
-    const float* rows[3];
-    int cnt = 0;
-    const int kc = p - (basec + 2);
-    if (kc >= 0 && kc < D.Dc) rows[cnt++] = dist_c + ((long)s * D.Dc + kc) * D.V;
-    const int tv = p - 1 - basev;
-    if (basev >= 0 && tv >= D.t0 && tv < D.m) rows[cnt++] = dist_v + ((long)s * D.nhfc + (tv - D.t0)) * D.V;
-    const int tf = p - 1 - basef;
-    if (basef >= 0 && tf >= D.t0 && tf < D.n) rows[cnt++] = dist_f + ((long)s * D.nhfc + (tf - D.t0)) * D.V;
+    const int kc = p - (basec + 2), tv = p - 1 - basev, tf = p - 1 - basef;
+    const float* r0 = kc >= 0 && kc < D.Dc ? dist_c + ((long)s * D.Dc + kc) * D.V : nullptr;
+    const float* r1 = basev >= 0 && tv >= D.t0 && tv < D.m ? dist_v + ((long)s * D.nhfc + (tv - D.t0)) * D.V : nullptr;
+    const float* r2 = basef >= 0 && tf >= D.t0 && tf < D.n ? dist_f + ((long)s * D.nhfc + (tf - D.t0)) * D.V : nullptr;
+    const int cnt = (r0 != nullptr) + (r1 != nullptr) + (r2 != nullptr);
     int bi = -1;
     if (cnt > 0) {
       const float inv = 1.0f / (float)cnt;
-      const float *r0 = rows[0], *r1 = cnt > 1 ? rows[1] : nullptr, *r2 = cnt > 2 ? rows[2] : nullptr;
       float* qr = sampled || pr.keep_rows ? sm.qrow + ((long)s * D.Bm + idx) * D.V : nullptr;
       float bv = -INFINITY;
       bi = 0x7fffffff;
@@ -659,7 +652,7 @@ __global__ __launch_bounds__(1024) void k_merge(StateDev st, Dims D, DraftRows R
 #pragma unroll
         for (int k = 0; k < 16; k++) {
           const int i = min(i0 + 64 * k, nlim - 1);
-          a[k] = r0[i];
+          a[k] = r0 ? r0[i] : 0.f;
           b[k] = r1 ? r1[i] : 0.f;
           c[k] = r2 ? r2[i] : 0.f;
         }
@@ -684,24 +677,14 @@ __global__ __launch_bounds__(1024) void k_merge(StateDev st, Dims D, DraftRows R
         bi = wave_inverse_cdf<0>(nlim, sample_uniform(pr.seed, FM_U_DRAFT, s, p), [&](int i) { return qr[i]; }, total);
         if (lane == 0 && p < budget) { sm.qtok[s * D.Bm + idx] = bi; sm.qsum[s * D.Bm + idx] = total; }
       } else {
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-          const float ov = __shfl_xor(bv, o, 64);
-          const int oi = __shfl_xor(bi, o, 64);
-          argmax_merge(bv, bi, ov, oi);
-        }
+        wave_argmax(bv, bi);
       }
     }
     if (lane == 0) stok[idx] = bi;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int len = 1;
-    while (len < D.Bm && spos + 1 + len < budget && stok[len] >= 0) len++;
-    slen = len;
-  }
-  __syncthreads();
-  int len = slen;
+  // the block ends in front of the first index without a token: a lane per index, in every wave
+  int len = __ffsll(~__ballot(lane == 0 || (lane < D.Bm && spos + 1 + lane < budget && stok[min(lane, 31)] >= 0))) - 1;
   if (sampled && t >= len && t < D.Bm) sm.qtok[s * D.Bm + t] = -1;
   if (rp.stream) {
     if (t >= 1 && t <= n_replay) {
