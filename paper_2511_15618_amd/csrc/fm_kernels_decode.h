@@ -765,15 +765,10 @@ void dec_attn_go(const AttnArgs& a, int nset, hipStream_t st) {
   hipLaunchKernelGGL((k_dec_attn<T, QT, HD, NW>), dim3(a.H, a.ns_max, a.S * nset + a.ahead), dim3(NW * 64), lds, st, a);
 }
 
-// Attention of `nset` row sets (at most 32 rows each) in one launch.
-template <typename T>
-bool dec_attention(AttnArgs& a, int nset, int hd, hipStream_t st) {
-  constexpr int NW = std::is_same<T, float>::value ? 4 : 8;      // fp32 operands need the registers of four waves per workgroup
-  int QT = 1;
+template <typename T, int QT, int HD, int NW>
+void dec_attn_sized(AttnArgs& a, int nset, hipStream_t st) {
   a.ns_max = 1;
   for (int z = 0; z < nset; z++) {
-    if (a.set[z].rows > 32) return false;
-    if (a.set[z].rows > 16) QT = 2;
     a.set[z].ns = attn_splits((long)a.H * a.S * nset, a.set[z].capb, NW);
     if (a.set[z].ns > a.ns_max) a.ns_max = a.set[z].ns;
   }
@@ -781,8 +776,34 @@ bool dec_attention(AttnArgs& a, int nset, int hd, hipStream_t st) {
   // Readers come in whole planes of H * ns_max workgroups, 48 of them or more (32 to 128: no difference): 48 to 256.  Where one workgroup
   // that attends fills a compute unit (two tiles of 128-wide heads: 137 KB of LDS) and these fill the chip, the readers run behind them.
   a.ahead = a.next[0].W ? (48 + a.H * a.ns_max - 1) / (a.H * a.ns_max) : 0;
-  if (hd == 64) { if (QT == 1) dec_attn_go<T, 1, 64, NW>(a, nset, st); else dec_attn_go<T, 2, 64, NW>(a, nset, st); }
-  else if (hd == 96) { if (QT == 1) dec_attn_go<T, 1, 96, NW>(a, nset, st); else dec_attn_go<T, 2, 96, NW>(a, nset, st); }
-  else { if (QT == 1) dec_attn_go<T, 1, 128, NW>(a, nset, st); else dec_attn_go<T, 2, 128, NW>(a, nset, st); }
+  dec_attn_go<T, QT, HD, NW>(a, nset, st);
+}
+// Waves of a workgroup: 8, in fp32, whose operands take twice the registers, 4.  Over at most 16 key blocks fp32 takes two, a wave for each block on
+// two to four times as many compute units: one of them pulls about 55 KB a microsecond and a block of a 64-wide head is 16 KB (a mesh of ten
+// faces, d = 256, memory 256: 10.91 -> 10.53 ms; with eight waves 11.05).  Past 16 blocks that is more than the 8 parts which the merge reads in one
+// trip, and costs more than it gives (one sequence, 600 faces, two heads of 128: 805 us a step, 935 with two waves over any number of blocks).
+// Half precision with four waves instead of eight: d = 768, three sequences 1170 -> 1198 us a step.
+template <typename T, int QT, int HD>
+void dec_attn_waves(AttnArgs& a, int nset, hipStream_t st) {
+  int blocks = 0;
+  for (int z = 0; z < nset; z++) blocks = a.set[z].capb > blocks ? a.set[z].capb : blocks;
+  if constexpr (std::is_same<T, float>::value) {
+    if (blocks <= 16 && (long)a.H * a.S * nset * ((blocks + 1) / 2) <= 256) dec_attn_sized<T, QT, HD, 2>(a, nset, st);
+    else dec_attn_sized<T, QT, HD, 4>(a, nset, st);
+  } else {
+    dec_attn_sized<T, QT, HD, 8>(a, nset, st);
+  }
+}
+// Attention of `nset` row sets (at most 32 rows each) in one launch.
+template <typename T>
+bool dec_attention(AttnArgs& a, int nset, int hd, hipStream_t st) {
+  int QT = 1;
+  for (int z = 0; z < nset; z++) {
+    if (a.set[z].rows > 32) return false;
+    if (a.set[z].rows > 16) QT = 2;
+  }
+  if (hd == 64) { if (QT == 1) dec_attn_waves<T, 1, 64>(a, nset, st); else dec_attn_waves<T, 2, 64>(a, nset, st); }
+  else if (hd == 96) { if (QT == 1) dec_attn_waves<T, 1, 96>(a, nset, st); else dec_attn_waves<T, 2, 96>(a, nset, st); }
+  else { if (QT == 1) dec_attn_waves<T, 1, 128>(a, nset, st); else dec_attn_waves<T, 2, 128>(a, nset, st); }
   return true;
 }

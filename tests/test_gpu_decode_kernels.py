@@ -211,3 +211,14 @@ def test_draft_rows_normed_by_their_gemms(d, heads, dtype, batch):
     rep, streams, fm = lockstep(cfg, cfg.faces, TOL[dtype], max_steps=6)
     print(rep, flush=True)
     assert rep.dist_rows > 0
+
+
+@pytest.mark.parametrize("mem,batch", [(512, 2), (513, 2), (500, 16), (500, 17)])
+def test_fp32_attention_waves(mem, batch):
+    """Two heads over the memory: two waves a workgroup for 16 key blocks, four for one block more and where two would give more than 256 workgroups."""
+    from parity_harness import lockstep
+    cfg = _cfg("f32_waves%d_%d" % (mem, batch), 128, 2, mem, "f32", batch, 2, 2, 9, 9)
+    print("case", cfg.name, flush=True)
+    rep, streams, fm = lockstep(cfg, cfg.faces, TOL["f32"], max_steps=4)
+    print(rep, flush=True)
+    assert rep.steps > 0 and fm.verify_path() == 0
