@@ -610,9 +610,9 @@ int prefill_impl(fm_ctx* c, int seq, const float* mem_dev, void* stage_area, siz
   const size_t tiled = (size_t)M32 * d * sizeof(T), rows = (size_t)D.M * d * sizeof(float);      // memory in operand order; keys or values of one block
   const int parts = tiled + 2 * rows <= stage_bytes ? 1 : 2;       // keys and values of a block together, or in turn
   if (tiled + (c->pf_layers ? 0 : 2 / parts * rows) > stage_bytes) return fail(c, FM_EINVAL, "condition memory of %d x %d does not fit its staging area", D.M, d);
-  // memory -> MFMA fragment order (the same tiling as a weight matrix, zero rows up to whole key blocks)
+  // memory -> MFMA fragment order; the sequence starts over
   T* Xt = (T*)stage_area;
-  hipLaunchKernelGGL((k_tile_weight<T>), dim3(std::min(2048, (M32 * (d / 8) + 255) / 256)), dim3(256), 0, c->stream, mem_dev, Xt, D.M, d, M32, 0, D.hd);
+  hipLaunchKernelGGL((k_admit<T>), dim3(M32 / 16, (d / 32 + 3) / 4), dim3(256), 0, c->stream, mem_dev, Xt, D.M, d, c->st, D, seq, D.nbins);
   const long seq_off = (long)((size_t)seq * cache_seq_elems(c, D.M));
   if (c->pf_layers) {
 #define FM_PREFILL(HDV)                                                                                                            \
@@ -641,7 +641,6 @@ int prefill_impl(fm_ctx* c, int seq, const float* mem_dev, void* stage_area, siz
 #undef FM_MEMKVH
         }
   }
-  hipLaunchKernelGGL(k_reset_seq, dim3(1), dim3(64), 0, c->stream, c->st, D, seq, D.nbins);
   HIPCHK(c, hipGetLastError());
   return FM_OK;
 }

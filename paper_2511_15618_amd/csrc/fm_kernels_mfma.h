@@ -143,26 +143,30 @@ __global__ void k_mem_kv_store(const float* __restrict__ k, const float* __restr
   }
 }
 
-// weights [N][K] fp32 -> storage type (half: bf16-valued, exact), tiled: fragment (nt, kt) holds W[nt*16 + l%16][kt*32 + (l/16)*8 + j]
+// A lane's part of fragment (nt, kt) of a matrix [N][K] fp32: W[nt*16 + l%16][kt*32 + (l/16)*8 + j] in the storage type, rows past N zero.
 // rope_rows > 0 (projections to queries and keys): rows below it belong to heads of width hd whose rotary pairs (i, i + hd/2)
 // must meet in one result tile: tile q of a head holds dims q*8..+8 and hd/2 + q*8..+8, i.e. both halves of 8 pairs.
 template <typename T>
+__device__ __forceinline__ typename Op<T>::V8 tile_part(const float* __restrict__ src, int N, int K, int nt, int kt, int lane, int rope_rows, int hd) {
+  typedef float f32x8u __attribute__((ext_vector_type(8), aligned(4)));      // a caller's tensor is aligned to its elements, no more
+  int n = nt * 16 + (lane & 15);
+  if (n < rope_rows) {
+    const int hh = n / hd, qd = (n % hd) >> 4, c = n & 15;
+    n = hh * hd + (c < 8 ? qd * 8 + c : hd / 2 + qd * 8 + (c - 8));
+  }
+  const f32x8u v = *reinterpret_cast<const f32x8u*>(src + (long)min(n, N - 1) * K + kt * 32 + (lane >> 4) * 8);
+  typename Op<T>::V8 o;
+#pragma unroll
+  for (int j = 0; j < 8; j++) o[j] = n < N ? (T)v[j] : (T)0.f;
+  return o;
+}
+// weights [N][K] fp32 -> storage type (half: bf16-valued, exact), tiled
+template <typename T>
 __global__ void k_tile_weight(const float* __restrict__ src, T* __restrict__ dst, int N, int K, int Npad, int rope_rows, int hd) {
   const long total = (long)Npad * K / 8;
+  const int KT = K / 32;
   for (long v = blockIdx.x * (long)blockDim.x + threadIdx.x; v < total; v += (long)gridDim.x * blockDim.x) {
-    const int lane = (int)(v & 63);
     const long frag = v >> 6;
-    const int KT = K / 32;
-    const int kt = (int)(frag % KT), nt = (int)(frag / KT);
-    int n = nt * 16 + (lane & 15);
-    const int k = kt * 32 + (lane >> 4) * 8;
-    if (n < rope_rows) {
-      const int hh = n / hd, qd = (n % hd) >> 4, c = n & 15;
-      n = hh * hd + (c < 8 ? qd * 8 + c : hd / 2 + qd * 8 + (c - 8));
-    }
-    typename Op<T>::V8 o;
-#pragma unroll
-    for (int j = 0; j < 8; j++) o[j] = n < N ? (T)src[(long)n * K + k + j] : (T)0.f;
-    *reinterpret_cast<typename Op<T>::V8*>(dst + v * 8) = o;
+    *reinterpret_cast<typename Op<T>::V8*>(dst + v * 8) = tile_part<T>(src, N, K, (int)(frag / KT), (int)(frag % KT), (int)(v & 63), rope_rows, hd);
   }
 }

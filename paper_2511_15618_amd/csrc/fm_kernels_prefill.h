@@ -11,7 +11,7 @@
 //     of the last one are stored, and the stores are only issued, never waited for, until two stages later.
 //
 // Both operands are already in MFMA fragment order in global memory ([rows/16][K/32][64 lanes][8 halves]:
-// the weights from load time, the memory from k_tile_weight), so a fragment is one contiguous 1 KiB burst
+// the weights from load time, the memory from k_admit), so a fragment is one contiguous 1 KiB burst
 // from HBM to LDS.  The epilogue writes straight into the blocked cache layouts, 16 bytes per lane and store:
 // the V tile is computed as c W_v^T (a lane owns one dim and 2 x 4 keys that are neighbours in the V layout), the
 // K tile as W_k c^T (a lane owns one key and 4 consecutive dims; two lanes trade halves to own 8).

@@ -237,17 +237,27 @@ __global__ void k_set_budget(StateDev st, Dims D, int budget, unsigned generatio
   st.alive[0] = alive;
 }
 
-// Reset one sequence to x_0 = BOS with empty caches and no draft rows.
-__global__ void k_reset_seq(StateDev st, Dims D, int s, int bos) {
-  if (threadIdx.x != 0) return;
-  st.P[s] = 0; st.main[s] = bos; st.fin[s] = 0;
-  st.firedv[s] = -1; st.firedf[s] = -1;
-  st.basec[s] = -1000000; st.basev[s] = -1; st.basef[s] = -1;
-  st.vlen[s] = 0;
-  st.hist[(long)s * (D.maxtok + 1)] = bos;
-  int alive = 0;
-  for (int i = 0; i < D.S; i++) alive += st.fin[i] ? 0 : 1;
-  st.alive[0] = alive;
+// A new sequence: its condition memory [M][d] goes into operand order (fragments as k_tile_weight lays out weights, zero rows up to whole key
+// blocks) and its state starts over (x_0 = BOS, empty caches, no draft rows).  Workgroup (x, y): rows 16x..+16, a wave per 32 columns; a fragment is one trip, all of them
+// are in flight at once.  At d = 1024, 4096 rows 9.5 us for 24 MB, cold; as a
+// grid-stride loop with 64-bit divisions and a launch of its own for the state 14 + 4.6 (two sequences of d = 768 with their first block 1195 -> 1186 us).
+template <typename T>
+__global__ __launch_bounds__(256) void k_admit(const float* __restrict__ mem, T* __restrict__ Xt, int M, int d, StateDev st, Dims D, int s, int bos) {
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 64) {
+    const int i = threadIdx.x;
+    const int alive = __popcll(__ballot(i < D.S && (i == s || !st.fin[min(i, D.S - 1)])));      // at most 64 sequences, a lane each
+    if (i == 0) {
+      st.P[s] = 0; st.main[s] = bos; st.fin[s] = 0;
+      st.firedv[s] = -1; st.firedf[s] = -1;
+      st.basec[s] = -1000000; st.basev[s] = -1; st.basef[s] = -1;
+      st.vlen[s] = 0;
+      st.hist[(long)s * (D.maxtok + 1)] = bos;
+      st.alive[0] = alive;
+    }
+  }
+  const int KT = d >> 5, kt = blockIdx.y * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (kt >= KT) return;
+  *reinterpret_cast<typename Op<T>::V8*>(Xt + (((long)blockIdx.x * KT + kt) * 64 + lane) * 8) = tile_part<T>(mem, M, d, blockIdx.x, kt, lane, 0, 1);
 }
 
 

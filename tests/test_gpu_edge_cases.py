@@ -42,6 +42,22 @@ def test_static_prefill_takes_all_that_its_area_holds(d, heads, mem, dtype):
     assert fm.lib.fm_prefill_condition_static(fm.h, 0, C.c_void_p(y.data_ptr())) == -1
 
 
+@pytest.mark.parametrize("d,heads,mem,dtype", [(64, 1, 1, "bf16"), (192, 2, 33, "f32"), (192, 3, 31, "bf16")])
+def test_condition_memory_at_any_address(d, heads, mem, dtype):
+    """A memory that is aligned to its elements alone, of 1 row or around a key block, 2 and 6 column tiles (no multiple of a workgroup's four)."""
+    print("case memory address", d, mem, dtype, flush=True)
+    cfg = si.Config("address", d, heads, 32, 1, 1, 1, 1, 1, mem, dtype, 2, 2, 2, 0, 0)
+    fm = _ctx(cfg)
+    x = torch.from_numpy(si.make_memory(cfg, 0)).cuda()
+    y = torch.empty(x.numel() + 1, device="cuda")[1:].view(x.shape).copy_(x)
+    assert x.data_ptr() % 16 == 0 and y.data_ptr() % 16 == 4
+    fm.prefill_condition(0, x)
+    fm.prefill_condition(1, y)
+    for block in range(cfg.n_layers):
+        for a, b in zip(fm.debug_mem_kv(0, block), fm.debug_mem_kv(1, block)):
+            assert np.array_equal(a, b) and np.abs(a).max() > 0, block
+
+
 @pytest.mark.parametrize("hist", [1 << 30, (1 << 31) - 1])
 def test_correct_stage_with_the_longest_histories(hist):
     """Steps recorded with the correct stage off are not replayed for it, however many historical vertices it looks at."""
