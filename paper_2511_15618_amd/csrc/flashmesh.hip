@@ -285,17 +285,29 @@ size_t cache_seq_elems(const fm_ctx* c, int cap) {
 // path): the acceptance and commit kernels then report 0 accepted tokens and change nothing.
 const unsigned* pass_failed(const fm_ctx* c) { return c->persist ? c->pk.abort_word : nullptr; }
 
+int commit_any(fm_ctx* c, const int32_t* accepted, bool report) {
+  hipLaunchKernelGGL(k_commit, dim3(1), dim3(64 * std::min(c->D.S, 16)), 0, c->stream, c->st, c->D, accepted, pass_failed(c), c->commits_dev, report ? c->prog : nullptr);
+  HIPCHK(c, hipGetLastError());
+  return FM_OK;
+}
+
 // per verify row: the backbone's greedy token (or, with sampled decoding, the rejection test and the resampled token),
-// then the accepted length per sequence
-void choose_and_accept(fm_ctx* c, const float* logits, int32_t* accepted) {
+// then the accepted length per sequence; commit (in fm_generate): the commit behind them
+int choose_and_accept(fm_ctx* c, const float* logits, int32_t* accepted, bool commit) {
   const Dims& D = c->D;
   if (c->params.temperature > 0.f) {
     hipLaunchKernelGGL(k_sample_rows, dim3(c->Rc), dim3(256), 0, c->stream, c->st, D, logits, c->smp);
     hipLaunchKernelGGL(k_accept, dim3(D.S), dim3(64), 0, c->stream, c->st, D, accepted, (const int*)c->smp.accflag, pass_failed(c));
+  } else if (commit && D.S == 1) {      // (more sequences have more rows than the waves of one workgroup)
+    hipLaunchKernelGGL(k_choose_commit, dim3(1), dim3(1024), 0, c->stream, c->st, D, logits, D.ban ? D.nbins : D.V, accepted, pass_failed(c),
+                       c->st.counters + 2, c->commits_dev, c->prog);
+    commit = false;
   } else {
     hipLaunchKernelGGL(k_choose_greedy, dim3(D.S), dim3(1024), 0, c->stream, c->st, D, logits, D.ban ? D.nbins : D.V, accepted, pass_failed(c),
                        c->st.counters + 2);
   }
+  HIPCHK(c, hipGetLastError());
+  return commit ? commit_any(c, accepted, true) : FM_OK;
 }
 
 template <typename T>
@@ -428,7 +440,7 @@ void forward(fm_ctx* c, float* logits) {
 }
 
 template <typename T>
-int verify_impl(fm_ctx* c, const int32_t* block_tok, const int32_t* block_len, float* logits_out, int32_t* accepted) {
+int verify_impl(fm_ctx* c, const int32_t* block_tok, const int32_t* block_len, float* logits_out, int32_t* accepted, bool commit) {
   float* lg = logits_out ? logits_out : c->logits;
   verify_setup<T>(c, block_tok, block_len, !c->persist);
   if (c->persist) {
@@ -438,9 +450,8 @@ int verify_impl(fm_ctx* c, const int32_t* block_tok, const int32_t* block_len, f
   } else {
     forward<T>(c, lg);
   }
-  choose_and_accept(c, lg, accepted);      // greedy choice (or sampled) and acceptance
   HIPCHK(c, hipGetLastError());
-  return FM_OK;
+  return choose_and_accept(c, lg, accepted, commit);
 }
 
 // Query projection of draft rows behind their norm: grouped GEMM over `G` sets of `M` rows each with the rotation applied, row (set g, m) -> m * G + g
@@ -577,17 +588,12 @@ int draft_impl(fm_ctx* c, int32_t* block_tok, int32_t* block_len, int speculativ
 int draft_any(fm_ctx* c, int32_t* block_tok, int32_t* block_len, int speculative) {
   return c->bf16 ? draft_impl<f16_t>(c, block_tok, block_len, speculative) : draft_impl<float>(c, block_tok, block_len, speculative);
 }
-int verify_any(fm_ctx* c, const int32_t* block_tok, const int32_t* block_len, float* logits, int32_t* accepted) {
-  return c->bf16 ? verify_impl<f16_t>(c, block_tok, block_len, logits, accepted) : verify_impl<float>(c, block_tok, block_len, logits, accepted);
+int verify_any(fm_ctx* c, const int32_t* block_tok, const int32_t* block_len, float* logits, int32_t* accepted, bool commit = false) {
+  return c->bf16 ? verify_impl<f16_t>(c, block_tok, block_len, logits, accepted, commit) : verify_impl<float>(c, block_tok, block_len, logits, accepted, commit);
 }
 // settings that decide which launches a step consists of
 int step_flags(const fm_ctx* c, int speculative) {
   return (speculative ? 1 : 0) | (c->params.temperature > 0.f ? 2 : 0);
-}
-int commit_any(fm_ctx* c, const int32_t* accepted, bool report) {
-  hipLaunchKernelGGL(k_commit, dim3(1), dim3(64 * std::min(c->D.S, 16)), 0, c->stream, c->st, c->D, accepted, pass_failed(c), c->commits_dev, report ? c->prog : nullptr);
-  HIPCHK(c, hipGetLastError());
-  return FM_OK;
 }
 int put_params(fm_ctx* c) {
   hipLaunchKernelGGL(k_set_params, dim3(1), dim3(64), 0, c->stream, c->params_dev, c->params);
@@ -1496,7 +1502,12 @@ int fm_generate(fm_ctx* c, int32_t max_faces, int32_t speculative, int32_t* out_
     return speculative && c->correct_hist > 0 ? fm_correct(c, c->gen_tok, c->gen_len, nullptr) : FM_OK;
   };
   auto verify = [&]() -> int { return verify_any(c, c->gen_tok, c->gen_len, nullptr, c->gen_acc); };
-  auto whole = [&]() -> int { TRY(draft()); TRY(verify()); return commit_any(c, c->gen_acc, true); };
+  // A step in as few launches as it takes: without drafts the block is the main token (k_verify_setup knows it), one sequence is committed by the
+  // launch that chooses.
+  auto whole = [&]() -> int {
+    if (speculative) TRY(draft());
+    return verify_any(c, speculative ? c->gen_tok : nullptr, speculative ? c->gen_len : nullptr, nullptr, c->gen_acc, true);
+  };
   const fm_ctx::GraphKey kd{G_DRAFT, flags, hist, {c->gen_tok, c->gen_len, c->gen_acc, c}}, kv{G_VERIFY, flags, hist, {c->gen_tok, c->gen_len, nullptr, c->gen_acc}},
       ks{G_STEP, flags, hist, {c->gen_tok, c->gen_len, nullptr, c->gen_acc}};
   const int sample_every = 32;

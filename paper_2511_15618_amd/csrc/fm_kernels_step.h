@@ -38,7 +38,7 @@ struct StateDev {
 
 __device__ __forceinline__ int eff_block_len(const StateDev& st, const Dims& D, int s, const int* block_len) {
   if (st.fin[s]) return 0;
-  int len = block_len[s];
+  int len = block_len ? block_len[s] : 1;
   len = min(len, D.Bm);
   len = min(len, st.budget[0] - st.P[s]);
   return max(len, 0);
@@ -46,7 +46,8 @@ __device__ __forceinline__ int eff_block_len(const StateDev& st, const Dims& D, 
 
 // Rows of one verify pass, one workgroup per row (coordinate rows, then vertex, then face rows): position, last visible key of
 // the cross-attention, rotary table; every entry follows from the committed state alone.  emb != null: coordinate rows also get
-// their embedding as fp32 residual stream and as input of the first projection.
+// their embedding as fp32 residual stream and as input of the first projection.  Without a block (both pointers null) every sequence
+// feeds its main token alone, what k_merge would write for a step without drafts (8 faces of d = 512 token by token 11.08 -> 10.99 ms).
 template <typename T>
 __global__ __launch_bounds__(256) void k_verify_setup(StateDev st, Dims D, InvFreq inv, const int* __restrict__ block_tok,
                                                        const int* __restrict__ block_len, int* pos_c, int* pos_v, int* pos_f,
@@ -65,7 +66,7 @@ __global__ __launch_bounds__(256) void k_verify_setup(StateDev st, Dims D, InvFr
   const int idx = blockIdx.x - (level == 0 ? 0 : level == 1 ? Rc : Rc + Rv);
   const int per = level == 0 ? D.Bm : level == 1 ? D.VB : D.FB, step = level == 0 ? 1 : level == 1 ? 3 : 9;
   const int s = idx / per, i = idx % per;
-  const int bt = level == 0 ? block_tok[idx] : 0;
+  const int bt = level != 0 ? 0 : block_tok ? block_tok[idx] : st.main[s];
   const int len = eff_block_len(st, D, s, block_len), P = st.P[s];
   const int q = (P + step - 1) / step + i;
   const int p = step * q < P + len ? q : -1;       // a row the block does not reach is inactive
@@ -75,7 +76,10 @@ __global__ __launch_bounds__(256) void k_verify_setup(StateDev st, Dims D, InvFr
     (level == 0 ? limx_c : level == 1 ? limx_v : limx_f)[idx] = p >= 0 ? D.M - 1 : -1;
     if (level == 0) {
       st.vtok[idx] = t;
-      if (i == 0) st.vlen[s] = len;
+      if (i == 0) {
+        st.vlen[s] = len;
+        if (!block_len && !st.fin[s]) st.kind[s] = 0;
+      }
     }
   }
   const int np = D.hd >> 1;      // rotary pairs per head
@@ -113,16 +117,11 @@ __global__ __launch_bounds__(64) void k_accept(StateDev st, Dims D, int* __restr
   if (i == 0 && accepted_out) accepted_out[s] = a;
 }
 
-// Greedy choice of every row of a sequence (lowest index among exact ties, over [0, nlim)) and its accepted length: one
-// workgroup per sequence, one wave per row, 16 values per lane in flight.  `nonfinite` counts rows whose admissible logits
+// Greedy choice of every row of a sequence (lowest index among exact ties, over [0, nlim)), into st.y and sy; the block's tokens into stok: one
+// workgroup, one wave per row, 16 values per lane in flight.  `nonfinite` counts rows whose admissible logits
 // hold an infinity or a NaN: half-precision activations beyond 65504 overflow silently, and this is where it shows.
-__global__ __launch_bounds__(1024) void k_choose_greedy(StateDev st, Dims D, const float* __restrict__ logits, int nlim,
-                                                         int* __restrict__ accepted_out, const unsigned* __restrict__ failed,
-                                                         unsigned long long* __restrict__ nonfinite) {
-  __shared__ int sy[32], stok[32];
-  const int s = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int len = st.vlen[s];
-  const bool bad_pass = failed && *failed;
+__device__ __forceinline__ void choose_rows(const StateDev& st, const Dims& D, int s, const float* __restrict__ logits, int nlim, unsigned long long* nonfinite, int* sy, int* stok) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   if ((int)threadIdx.x < D.Bm) stok[threadIdx.x] = st.vtok[s * D.Bm + threadIdx.x];
   for (int i = wave; i < D.Bm; i += 16) {
     const float* x = logits + (long)(s * D.Bm + i) * D.V;
@@ -149,54 +148,43 @@ __global__ __launch_bounds__(1024) void k_choose_greedy(StateDev st, Dims D, con
     }
   }
   __syncthreads();
-  if (wave == 0) {      // a draft per lane
-    const int a = accepted_length(__ballot(lane + 1 < min(len, 32) && stok[min(lane + 1, 31)] == sy[min(lane, 31)]), len, bad_pass);
-    if (lane == 0 && accepted_out) accepted_out[s] = a;
-  }
 }
 
 // What the host may look at while the device runs ahead of it: one pinned word per sequence (fm_progress.h), written by the
 // commits of fm_generate.
 struct Progress { unsigned long long seq[64]; };
 
-// An accepted length of 0 (a pass that did not complete) leaves the sequence as it is.  prog: null for the caller's own commits.
-// A wave per sequence, a token of the block per lane: all a sequence needs is read in one trip.  (A thread per sequence that walked its block
-// token by token, and such walks at the end of k_choose_greedy and k_merge: steps of d = 512 578 us instead of 574, meshes of d = 256 in fp32 10.95 ms
-// instead of 10.84.)
-__global__ __launch_bounds__(1024) void k_commit(StateDev st, Dims D, const int* __restrict__ accepted, const unsigned* __restrict__ failed, unsigned* commits,
-                                                 Progress* prog) {
-  __shared__ int s_pos[64], s_fin[64], s_moved[64];
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6, i = threadIdx.x & 63;
-  const bool bad = failed && *failed;
-  for (int s = wave; s < D.S; s += waves) {
-    const int len = st.vlen[s], acc = accepted[s], P = st.P[s], fin = st.fin[s], kind = st.kind[s], budget = st.budget[0];
-    const int tok = i < D.Bm ? st.vtok[s * D.Bm + i] : 0, y = i < D.Bm ? st.y[s * D.Bm + i] : 0;
-    const bool moves = !bad && len > 0 && acc > 0;
-    int a = min(acc, len);
-    const unsigned long long ends = __ballot(i >= 1 && i < a && tok == D.eos);      // an accepted EOS draft is not fed: it becomes the main token
-    if (ends) a = __ffsll(ends) - 1;
-    const int mainTok = __shfl(y, max(a - 1, 0), 64);
-    const int now = moves ? (mainTok == D.eos || P + a >= budget ? 1 : 0) : fin;
-    if (moves) {
-      int* h = st.hist + (long)s * (D.maxtok + 1) + P;
-      if (i < a) h[i] = tok;
-      if (i == 0) {
-        h[a] = mainTok;
-        st.P[s] = P + a;
-        st.main[s] = mainTok;
-        st.fin[s] = now;
-        st.vlen[s] = 0;
-        atomicAdd(&st.acc_hist[min(max(kind, 0), 2) * 32 + min(a, 31)], 1ull);
-        atomicAdd(&st.counters[1], (unsigned long long)a);
-      }
+struct SeqState { int len, P, fin, kind, budget; };
+__device__ __forceinline__ SeqState read_sequence(const StateDev& st, int s) { return SeqState{st.vlen[s], st.P[s], st.fin[s], st.kind[s], st.budget[0]}; }
+struct Committed { int pos, fin, moved; };
+// One wave commits sequence s; lane i holds token i of the block and the choice behind it (block past its end: anything).
+// An accepted length of 0 (a pass that did not complete) leaves the sequence as it is.
+__device__ __forceinline__ Committed commit_sequence(const StateDev& st, const Dims& D, int s, int i, const SeqState& q, int acc, int tok, int y, bool bad) {
+  const bool moves = !bad && q.len > 0 && acc > 0;
+  int a = min(acc, q.len);
+  const unsigned long long ends = __ballot(i >= 1 && i < a && tok == D.eos);      // an accepted EOS draft is not fed: it becomes the main token
+  if (ends) a = __ffsll(ends) - 1;
+  const int mainTok = __shfl(y, max(a - 1, 0), 64);
+  const int now = moves ? (mainTok == D.eos || q.P + a >= q.budget ? 1 : 0) : q.fin;
+  if (moves) {
+    int* h = st.hist + (long)s * (D.maxtok + 1) + q.P;
+    if (i < a) h[i] = tok;
+    if (i == 0) {
+      h[a] = mainTok;
+      st.P[s] = q.P + a;
+      st.main[s] = mainTok;
+      st.fin[s] = now;
+      st.vlen[s] = 0;
+      atomicAdd(&st.acc_hist[min(max(q.kind, 0), 2) * 32 + min(a, 31)], 1ull);
+      atomicAdd(&st.counters[1], (unsigned long long)a);
     }
-    if (i == 0) { s_pos[s] = moves ? P + a : P; s_fin[s] = now; s_moved[s] = moves; }
   }
-  __syncthreads();
-  if (wave != 0) return;
-  const bool on = i < D.S;      // a sequence per lane: at most 64
-  const int alive = __popcll(__ballot(on && !s_fin[on ? i : 0]));
-  const bool moved = __any(on && s_moved[on ? i : 0]);
+  return Committed{moves ? q.P + a : q.P, now, moves};
+}
+// ... and, with a sequence in each lane that is `on`, what concerns all of them.  prog: null for the caller's own commits.
+__device__ __forceinline__ void commit_end(const StateDev& st, int i, bool on, const Committed& m, bool bad, unsigned* commits, Progress* prog) {
+  const int alive = __popcll(__ballot(on && !m.fin));
+  const bool moved = __any(on && m.moved);
   if (i == 0 && !bad) {
     st.alive[0] = alive;
     if (moved) st.counters[0] += 1;
@@ -204,8 +192,58 @@ __global__ __launch_bounds__(1024) void k_commit(StateDev st, Dims D, const int*
   if (prog) {
     const unsigned n = progress_next(*commits);       // one wave: read by all lanes before lane 0 writes it
     if (i == 0) *commits = n;
-    if (on) __hip_atomic_store(&prog->seq[i], progress_word(n, bad ? 0 : s_fin[i] ? 1 : s_pos[i] + 2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (on) __hip_atomic_store(&prog->seq[i], progress_word(n, bad ? 0 : m.fin ? 1 : m.pos + 2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
+}
+
+// Greedy choice of every row of a sequence and the accepted length, see choose_rows.
+__global__ __launch_bounds__(1024) void k_choose_greedy(StateDev st, Dims D, const float* __restrict__ logits, int nlim,
+                                                         int* __restrict__ accepted_out, const unsigned* __restrict__ failed,
+                                                         unsigned long long* __restrict__ nonfinite) {
+  __shared__ int sy[32], stok[32];
+  const int s = blockIdx.x, lane = threadIdx.x & 63;
+  const int len = st.vlen[s];
+  const bool bad_pass = failed && *failed;
+  choose_rows(st, D, s, logits, nlim, nonfinite, sy, stok);
+  if (threadIdx.x < 64) {      // a draft per lane
+    const int a = accepted_length(__ballot(lane + 1 < min(len, 32) && stok[min(lane + 1, 31)] == sy[min(lane, 31)]), len, bad_pass);
+    if (lane == 0 && accepted_out) accepted_out[s] = a;
+  }
+}
+
+// The commit of every sequence.  A wave per sequence, a token of the block per lane: all a sequence needs is read in one trip.  (A thread per
+// sequence that walked its block token by token, and such walks at the end of k_choose_greedy and k_merge: steps of d = 512 578 us instead of 574,
+// meshes of d = 256 in fp32 10.95 ms instead of 10.84.)
+__global__ __launch_bounds__(1024) void k_commit(StateDev st, Dims D, const int* __restrict__ accepted, const unsigned* __restrict__ failed, unsigned* commits,
+                                                 Progress* prog) {
+  __shared__ int s_pos[64], s_fin[64], s_moved[64];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6, i = threadIdx.x & 63;
+  const bool bad = failed && *failed;
+  for (int s = wave; s < D.S; s += waves) {
+    const int acc = accepted[s], tok = i < D.Bm ? st.vtok[s * D.Bm + i] : 0, y = i < D.Bm ? st.y[s * D.Bm + i] : 0;
+    const Committed m = commit_sequence(st, D, s, i, read_sequence(st, s), acc, tok, y, bad);
+    if (i == 0) { s_pos[s] = m.pos; s_fin[s] = m.fin; s_moved[s] = m.moved; }
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  const int q = min(i, D.S - 1);      // a sequence per lane: at most 64
+  commit_end(st, i, i < D.S, Committed{s_pos[q], s_fin[q], s_moved[q]}, bad, commits, prog);
+}
+
+// One sequence, greedy: choice, acceptance and commit in one launch (fm_generate).  A launch of this size costs 1.7 us a step: 8 faces of
+// d = 512 token by token 10.99 -> 10.87 ms, a mesh of ten faces of d = 256 in fp32 10.56 -> 10.51.
+__global__ __launch_bounds__(1024) void k_choose_commit(StateDev st, Dims D, const float* __restrict__ logits, int nlim, int* __restrict__ accepted_out,
+                                                        const unsigned* __restrict__ failed, unsigned long long* __restrict__ nonfinite, unsigned* commits, Progress* prog) {
+  __shared__ int sy[32], stok[32];
+  const int i = threadIdx.x & 63;
+  const SeqState q = read_sequence(st, 0);
+  const bool bad = failed && *failed;
+  choose_rows(st, D, 0, logits, nlim, nonfinite, sy, stok);
+  if (threadIdx.x >= 64) return;
+  const int a = accepted_length(__ballot(i + 1 < min(q.len, 32) && stok[min(i + 1, 31)] == sy[min(i, 31)]), q.len, bad);
+  if (i == 0) accepted_out[0] = a;
+  const Committed m = commit_sequence(st, D, 0, i, q, a, i < D.Bm ? stok[min(i, 31)] : 0, i < D.Bm ? sy[min(i, 31)] : 0, bad);
+  commit_end(st, i, i == 0, m, bad, commits, prog);
 }
 
 // End of fm_generate: x_1 .. of every sequence and its length to the caller, counters to pinned host memory.

@@ -58,6 +58,48 @@ def test_condition_memory_at_any_address(d, heads, mem, dtype):
             assert np.array_equal(a, b) and np.abs(a).max() > 0, block
 
 
+@pytest.mark.parametrize("dtype,batch,temperature", [("f32", 1, 0.0), ("bf16", 1, 0.0), ("bf16", 2, 0.0), ("bf16", 1, 0.5)])
+def test_steps_of_generate_are_those_of_the_calls(dtype, batch, temperature):
+    """fm_generate writes no block for a step without drafts and commits one greedy sequence in the launch that chooses: the tokens and counts
+    are those of separate calls, with drafts and without, over more steps than those that it times phase by phase."""
+    cfg = si.Config("steps", 128, 2, 32, 1, 1, 1, 1, 1, 40, dtype, batch, 5, 2, 9, 9)
+    for speculative in (False, True):
+        print("case steps of generate", dtype, batch, temperature, speculative, flush=True)
+        got = []
+        for calls in (False, True):
+            fm = _ctx(cfg)
+            if temperature:
+                fm.set_sampling(temperature, 7)
+            for s in range(batch):
+                fm.prefill_condition(s, torch.from_numpy(si.make_memory(cfg, s)).cuda())
+            if calls:
+                fm.set_budget(cfg.faces)
+                tok, ln = fm.new_block()
+                lg, acc = torch.zeros(batch, fm.block_max, fm.vocab, device="cuda"), torch.zeros_like(ln)
+                lens = [[] for _ in range(batch)]
+                for _ in range(9 * cfg.faces):
+                    fm.draft(tok, ln)
+                    if not speculative:
+                        ln.clamp_(max=1)
+                    fm.verify_block(tok, ln, lg, acc)
+                    fm.commit(acc)
+                    for s, a in enumerate(acc.tolist()):
+                        if a:
+                            lens[s].append(a)
+                state = fm.read_state()
+            out, n, st = fm.generate(cfg.faces, speculative)
+            if not calls:
+                hist = np.array([list(h) for h in st.acc_hist]).sum(0)
+                state = fm.read_state()
+                assert st.steps == st.tokens == 9 * cfg.faces if not speculative and batch == 1 else st.steps <= st.tokens
+            else:
+                hist = np.bincount([a for l in lens for a in l], minlength=32)
+            got.append((out.cpu().numpy(), n.cpu().numpy(), hist, state[:, :5]))      # length, rows per level, main token, finished
+        for a, b in zip(*got):
+            assert np.array_equal(a, b)
+        assert got[0][1].tolist() == [9 * cfg.faces] * batch
+
+
 @pytest.mark.parametrize("hist", [1 << 30, (1 << 31) - 1])
 def test_correct_stage_with_the_longest_histories(hist):
     """Steps recorded with the correct stage off are not replayed for it, however many historical vertices it looks at."""
