@@ -315,7 +315,7 @@ void verify_setup(fm_ctx* c, const int32_t* block_tok, const int32_t* block_len,
   const Dims& D = c->D;
   hipLaunchKernelGGL((k_verify_setup<T>), dim3(c->Rc + c->Rv + c->Rf), dim3(256), 0, c->stream, c->st, D, c->inv, block_tok, block_len,
                      c->pos[0], c->pos[1], c->pos[2], c->limx[0], c->limx[1], c->limx[2], c->cs[0], c->cs[1], c->cs[2], c->persist ? c->pk_epoch : nullptr,
-                     embed ? (const T*)c->emb : nullptr, c->h[0], (T*)c->xg[0], c->stacks[0][0].g1, c->ssq[0]);
+                     embed ? (const T*)c->emb : nullptr, c->h[0], (T*)c->xg[0], c->stacks[0][0].g1, c->ssq[0], c->smp.qtok);
 }
 
 // ------------------------------------------------------------------------------------------

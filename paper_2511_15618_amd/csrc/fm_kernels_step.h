@@ -47,13 +47,14 @@ __device__ __forceinline__ int eff_block_len(const StateDev& st, const Dims& D, 
 // Rows of one verify pass, one workgroup per row (coordinate rows, then vertex, then face rows): position, last visible key of
 // the cross-attention, rotary table; every entry follows from the committed state alone.  emb != null: coordinate rows also get
 // their embedding as fp32 residual stream and as input of the first projection.  Without a block (both pointers null) every sequence
-// feeds its main token alone, what k_merge would write for a step without drafts (8 faces of d = 512 token by token 11.08 -> 10.99 ms).
+// feeds its main token alone, what k_merge would write for a step without drafts (8 faces of d = 512 token by token 11.08 -> 10.99 ms); qtok: the
+// sampled drafts' record, cleared then (none of them may count as drawn for a later block of the caller's).
 template <typename T>
 __global__ __launch_bounds__(256) void k_verify_setup(StateDev st, Dims D, InvFreq inv, const int* __restrict__ block_tok,
                                                        const int* __restrict__ block_len, int* pos_c, int* pos_v, int* pos_f,
                                                        int* limx_c, int* limx_v, int* limx_f, float2* cs_c, float2* cs_v,
                                                        float2* cs_f, unsigned* epoch, const T* __restrict__ emb, float* __restrict__ h,
-                                                       T* __restrict__ xg, const float* __restrict__ gain, float* __restrict__ ssq) {
+                                                       T* __restrict__ xg, const float* __restrict__ gain, float* __restrict__ ssq, int* __restrict__ qtok) {
   if (epoch && blockIdx.x == 0 && threadIdx.x == 0) *epoch += 1;     // pass counter of the single-launch verify kernel
   if (blockIdx.x == 0 && threadIdx.x < 64) {      // at most 64 sequences, a lane each
     const int q = threadIdx.x < D.S ? (int)threadIdx.x : 0, n = (int)threadIdx.x < D.S ? eff_block_len(st, D, q, block_len) : 0, P0 = st.P[q];
@@ -76,6 +77,7 @@ __global__ __launch_bounds__(256) void k_verify_setup(StateDev st, Dims D, InvFr
     (level == 0 ? limx_c : level == 1 ? limx_v : limx_f)[idx] = p >= 0 ? D.M - 1 : -1;
     if (level == 0) {
       st.vtok[idx] = t;
+      if (!block_len) qtok[idx] = -1;
       if (i == 0) {
         st.vlen[s] = len;
         if (!block_len && !st.fin[s]) st.kind[s] = 0;

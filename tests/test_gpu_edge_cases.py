@@ -100,6 +100,38 @@ def test_steps_of_generate_are_those_of_the_calls(dtype, batch, temperature):
         assert got[0][1].tolist() == [9 * cfg.faces] * batch
 
 
+def test_a_step_without_drafts_forgets_the_sampled_ones():
+    """fm_generate for one token, no drafts, behind an fm_draft: tokens of that draft in a block of the caller's are proposals with all their mass, as in a
+    context that never drafted (the generator is keyed by position)."""
+    cfg = si.Config("forget", 128, 2, 32, 1, 1, 1, 1, 1, 40, "bf16", 8, 5, 2, 9, 9)
+    block, got = None, []
+    for drafts in (True, False):
+        print("case forgotten drafts", drafts, flush=True)
+        fm = _ctx(cfg)
+        fm.set_sampling(1.0, 7)
+        for s in range(cfg.batch):
+            fm.prefill_condition(s, torch.from_numpy(si.make_memory(cfg, s)).cuda())
+        fm.set_budget(5)
+        tok, ln = fm.new_block()
+        lg, acc = torch.zeros(cfg.batch, fm.block_max, fm.vocab, device="cuda"), torch.zeros_like(ln)
+        for _ in range(17):
+            tok[:, 0] = torch.from_numpy(fm.read_state()[:, 3].astype(np.int32)).cuda()
+            fm.verify_block(tok, ln.fill_(1), lg, acc)
+            fm.commit(acc)
+        if drafts:
+            fm.draft(tok, ln)
+            assert ln.min() > 2
+            block = tok.clone()
+        _, _, st = fm.generate(2, False)
+        assert st.steps == 1
+        fm.set_budget(5)
+        block[:, 0] = torch.from_numpy(fm.read_state()[:, 3].astype(np.int32)).cuda()
+        fm.verify_block(block, ln.fill_(3), lg, acc)
+        got.append((acc.tolist(), lg[:, :3].cpu().numpy(), fm.read_state()[:, :3]))
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
+
+
 @pytest.mark.parametrize("hist", [1 << 30, (1 << 31) - 1])
 def test_correct_stage_with_the_longest_histories(hist):
     """Steps recorded with the correct stage off are not replayed for it, however many historical vertices it looks at."""
