@@ -400,13 +400,17 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
   const int bstep = A->ns * NW;
   int b = split * NW + wave;
   V8 kf[2 * KC], vf[DT];
+  // Keys and values are read once a pass, and those of eight sequences are more than all caches hold (134 MB a block at d = 1024, memory 4096): as
+  // non-temporal loads they do not push the weights that the readers above fetched, or the rows between the launches, out of L2.  Steps with / without the hint, us:
+  // eight sequences of d = 1024 3086 / 3191, four of d = 1536 3964 / 4083; 20 faces of five sequences, d = 512, sampled 53.2 / 56.3 ms; one
+  // sequence of d = 2048 2216 / 2225, of d = 512 (draft heads only) the same.  The same hint on the weights of k_dec_gemm, whose row tiles share them: d = 1536 4086 / 3964.
   auto load_k = [&](int blk) {
 #pragma unroll
-    for (int f = 0; f < 2 * KC; f++) kf[f] = *reinterpret_cast<const V8*>(Kb + (long)blk * BLK + f * 512);
+    for (int f = 0; f < 2 * KC; f++) kf[f] = __builtin_nontemporal_load(reinterpret_cast<const V8*>(Kb + (long)blk * BLK + f * 512));
   };
   auto load_v = [&](int blk) {
 #pragma unroll
-    for (int dt = 0; dt < DT; dt++) vf[dt] = *reinterpret_cast<const V8*>(Vb + (long)blk * BLK + dt * 512);
+    for (int dt = 0; dt < DT; dt++) vf[dt] = __builtin_nontemporal_load(reinterpret_cast<const V8*>(Vb + (long)blk * BLK + dt * 512));
   };
   load_k(min(b, A->capb - 1));
   load_v(min(b, A->capb - 1));
