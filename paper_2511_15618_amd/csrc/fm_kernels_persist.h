@@ -268,16 +268,24 @@ __device__ __forceinline__ bool pk_wait_stack(PkA& a, pk_x_t hT, unsigned tag, i
 // tagged half pairs, i.e. two 16-byte agent-scope loads.  No LDS staging, no barrier before the multiplication;
 // the tags are checked per lane and the whole set is re-read until complete.
 // ------------------------------------------------------------------------------------------
+// Weights, keys and values: with one row group a unit is the only one that reads them in the launch, and takes them as non-temporal loads.  Two row groups
+// read every weight tile twice, on two dies.  Steps without / with the hint, us: d = 512 580 / 564, d = 256 515 / 508, d = 768 664 / 658, d = 1024 1451 / 1441;
+// with two groups d = 512 681 / 677, d = 768 809 / 812, d = 1024 1705 / 1716 (for keys and values alone 1702 / 1705).
+template <bool ONCE>
+__device__ __forceinline__ f16x8 pk_once(pk_cw_t p) {
+  if constexpr (ONCE) return __builtin_nontemporal_load((const PK_GLOBAL f16x8*)p);
+  return *(const PK_GLOBAL f16x8*)p;
+}
 template <int FWT> struct PkWeights { f16x8 f[FWT ? FWT : 8]; };      // a wave's fragments of a tile
-template <int FWT>
+template <int FWT, bool ONCE>
 __device__ __forceinline__ void pk_weights(PkWeights<FWT>& w, pk_cw_t Wt, int KT) {
   const int tid = pk_tid(), wave = __builtin_amdgcn_readfirstlane(tid >> 6), FW = FWT ? FWT : KT >> 2;
   const pk_cw_t p = Wt + (long)wave * FW * 512;
 #pragma unroll
   for (int f = 0; f < (FWT ? FWT : 8); f++) {
     const int o = (f * 64 + (tid & 63)) * 8;
-    if constexpr (FWT > 0) w.f[f] = *(const PK_GLOBAL f16x8*)(p + o);
-    else w.f[f] = __builtin_bit_cast(f16x8, __builtin_amdgcn_raw_buffer_load_b128(agent_buf((const void*)p, FW * 1024), o * 2, 0, 0));      // fragments past the last are zeros
+    if constexpr (FWT > 0) w.f[f] = pk_once<ONCE>(p + o);
+    else w.f[f] = __builtin_bit_cast(f16x8, __builtin_amdgcn_raw_buffer_load_b128(agent_buf((const void*)p, FW * 1024), o * 2, 0, ONCE ? 2 : 0));      // fragments past the last are zeros; 2: non-temporal
   }
 }
 template <int FWT, class SH>
@@ -467,9 +475,9 @@ __device__ __forceinline__ void pk_attn_unit(PkA& a, SH& sh, int& par, u64 rec, 
   f16x8 ka[2][4], va[2][4];
   auto load = [&](f16x8 (&kf)[4], f16x8 (&vf)[4], int b) {
 #pragma unroll
-    for (int f = 0; f < 4; f++) kf[f] = *(const PK_GLOBAL f16x8*)(Kb + (long)b * 2048 + f * 512);
+    for (int f = 0; f < 4; f++) kf[f] = pk_once<QT == 1>(Kb + (long)b * 2048 + f * 512);
 #pragma unroll
-    for (int dt = 0; dt < 4; dt++) vf[dt] = *(const PK_GLOBAL f16x8*)(Vb + (long)b * 2048 + dt * 512);
+    for (int dt = 0; dt < 4; dt++) vf[dt] = pk_once<QT == 1>(Vb + (long)b * 2048 + dt * 512);
   };
   if (b0 < nblk) load(ka[0], va[0], b0);
   // q of this lane: dims g*8..+8 and 32 + g*8..+8 of the head = two runs of four tagged elements = four 16-byte
@@ -913,7 +921,7 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs) {
         const int KT = down ? ff >> 7 : d >> 5, lda = down ? ff >> 1 : d >> 1;
         // weights go out before anything else: they depend on nothing, and come from the farthest
         PkWeights<FWT> w;
-        pk_weights<FWT>(w, pk_ptr<pk_cw_t>(rec, 0) + ((long)nt * (down ? ff >> 5 : d >> 5) + kq * KT) * 512, KT);
+        pk_weights<FWT, QT == 1>(w, pk_ptr<pk_cw_t>(rec, 0) + ((long)nt * (down ? ff >> 5 : d >> 5) + kq * KT) * 512, KT);
         const pk_x_t in = pk_ptr<pk_x_t>(rec, 1) + (long)row0 * lda + kq * (ff >> 3), sq0 = pk_ptr<pk_x_t>(rec, 2), hold = pk_ptr<pk_x_t>(rec, 3);
         const pk_x_t to = pk_ptr<pk_x_t>(rec, 4), to_x = pk_ptr<pk_x_t>(rec, 5), to_s = pk_ptr<pk_x_t>(rec, 6);
         const pk_x_t w2p = a.w2part + (((long)nt << rgs) + (u & rgs)) * 768;
