@@ -342,6 +342,7 @@ struct AttnArgs {
   unsigned* arrived;         // [set][sequence][head] splits that have published their part, zero between launches
   float* ws;                 // [set][sequence][head][ns_max][QT*16*HD unnormalised O | QT*16 running max (log2 units) | QT*16 sums]
   const int* run_flag;
+  bool once;                 // attn_once
   int nset, ahead;           // planes of the grid (blockIdx.z) that attend: nset * S; `ahead` more read weights ahead
   WeightRange next[4];
 };
@@ -355,7 +356,8 @@ __device__ __forceinline__ int attn_active(int maxlim, int capb, int ns, int NW)
   return max(1, min(ns, (nblk + NW - 1) / NW));
 }
 
-template <typename T, int QT, int HD, int NW>
+// ONCE: keys and values as non-temporal loads (attn_once)
+template <typename T, int QT, int HD, int NW, bool ONCE>
 __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
   typedef typename Op<T>::V8 V8;
   typedef typename Op<T>::V4 V4;
@@ -400,17 +402,14 @@ __global__ __launch_bounds__(NW * 64) void k_dec_attn(AttnArgs a) {
   const int bstep = A->ns * NW;
   int b = split * NW + wave;
   V8 kf[2 * KC], vf[DT];
-  // Keys and values are read once a pass, and those of eight sequences are more than all caches hold (134 MB a block at d = 1024, memory 4096): as
-  // non-temporal loads they do not push the weights that the readers above fetched, or the rows between the launches, out of L2.  Steps with / without the hint, us:
-  // eight sequences of d = 1024 3086 / 3191, four of d = 1536 3964 / 4083; 20 faces of five sequences, d = 512, sampled 53.2 / 56.3 ms; one
-  // sequence of d = 2048 2216 / 2225, of d = 512 (draft heads only) the same.  The same hint on the weights of k_dec_gemm, whose row tiles share them: d = 1536 4086 / 3964.
+  auto fetch = [](const V8* p) { return ONCE ? __builtin_nontemporal_load(p) : *p; };
   auto load_k = [&](int blk) {
 #pragma unroll
-    for (int f = 0; f < 2 * KC; f++) kf[f] = __builtin_nontemporal_load(reinterpret_cast<const V8*>(Kb + (long)blk * BLK + f * 512));
+    for (int f = 0; f < 2 * KC; f++) kf[f] = fetch(reinterpret_cast<const V8*>(Kb + (long)blk * BLK + f * 512));
   };
   auto load_v = [&](int blk) {
 #pragma unroll
-    for (int dt = 0; dt < DT; dt++) vf[dt] = __builtin_nontemporal_load(reinterpret_cast<const V8*>(Vb + (long)blk * BLK + dt * 512));
+    for (int dt = 0; dt < DT; dt++) vf[dt] = fetch(reinterpret_cast<const V8*>(Vb + (long)blk * BLK + dt * 512));
   };
   load_k(min(b, A->capb - 1));
   load_v(min(b, A->capb - 1));
@@ -762,14 +761,23 @@ inline size_t attn_ws_floats(int H, int S, int sets, int hd) {
   return (size_t)(256 + pairs) * (32 * hd + 64);
 }
 
-template <typename T, int QT, int HD, int NW>
+// Whether keys and values are loaded as read once (non-temporal), so that they do not push the weights that the readers have fetched, and the rows between the
+// launches, out of L2: from 10 MB of the memory's keys and values a block (L2 has 4 MB a die).  Steps without / with the hint, us, by that size:
+//   134 MB (eight sequences of d = 1024) 3191 / 3086     101 MB (four, 1536) 4083 / 3964        75 MB (twelve, 768) 1232 / 1211
+//   34 MB (one, 2048, heads of 128) 2225 / 2216          17 MB (four, 512) 450 / 431            17 MB (four, 256) 905 / 852
+//   13 MB (twelve, 512) 916 / 909                        8 MB (one, 1024, heads of 128) 1197 / 1200   6 MB (one, 1536) 1303 / 1305
+//   1 MB (two, 512) 780 / 783, (two, 256, token by token) 29.37 / 30.47 ms: there L2 keeps them from pass to pass
+// The same hint on the weights of k_dec_gemm, whose row tiles share them: 3964 -> 4086 for four sequences of d = 1536.
+inline bool attn_once(double block_kv_bytes) { return block_kv_bytes >= 10e6; }
+
+template <typename T, int QT, int HD, int NW, bool ONCE>
 void dec_attn_go(const AttnArgs& a, int nset, hipStream_t st) {
   const size_t lds = ((size_t)NW * QT * 16 * (HD + 4) + 2 * NW * QT * 16) * 4;
-  if (lds > 65536) (void)hipFuncSetAttribute((const void*)k_dec_attn<T, QT, HD, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  hipLaunchKernelGGL((k_dec_attn<T, QT, HD, NW>), dim3(a.H, a.ns_max, a.S * nset + a.ahead), dim3(NW * 64), lds, st, a);
+  if (lds > 65536) (void)hipFuncSetAttribute((const void*)k_dec_attn<T, QT, HD, NW, ONCE>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipLaunchKernelGGL((k_dec_attn<T, QT, HD, NW, ONCE>), dim3(a.H, a.ns_max, a.S * nset + a.ahead), dim3(NW * 64), lds, st, a);
 }
 
-template <typename T, int QT, int HD, int NW>
+template <typename T, int QT, int HD, int NW, bool ONCE = false>
 void dec_attn_sized(AttnArgs& a, int nset, hipStream_t st) {
   a.ns_max = 1;
   for (int z = 0; z < nset; z++) {
@@ -780,7 +788,7 @@ void dec_attn_sized(AttnArgs& a, int nset, hipStream_t st) {
   // Readers come in whole planes of H * ns_max workgroups, 48 of them or more (32 to 128: no difference): 48 to 256.  Where one workgroup
   // that attends fills a compute unit (two tiles of 128-wide heads: 137 KB of LDS) and these fill the chip, the readers run behind them.
   a.ahead = a.next[0].W ? (48 + a.H * a.ns_max - 1) / (a.H * a.ns_max) : 0;
-  dec_attn_go<T, QT, HD, NW>(a, nset, st);
+  dec_attn_go<T, QT, HD, NW, ONCE>(a, nset, st);
 }
 // Waves of a workgroup: 8, in fp32, whose operands take twice the registers, 4.  Over at most 16 key blocks fp32 takes two, a wave for each block on
 // two to four times as many compute units: one of them pulls about 55 KB a microsecond and a block of a 64-wide head is 16 KB (a mesh of ten
@@ -795,7 +803,8 @@ void dec_attn_waves(AttnArgs& a, int nset, hipStream_t st) {
     if (blocks <= 16 && (long)a.H * a.S * nset * ((blocks + 1) / 2) <= 256) dec_attn_sized<T, QT, HD, 2>(a, nset, st);
     else dec_attn_sized<T, QT, HD, 4>(a, nset, st);
   } else {
-    dec_attn_sized<T, QT, HD, 8>(a, nset, st);
+    if (a.once) dec_attn_sized<T, QT, HD, 8, true>(a, nset, st);
+    else dec_attn_sized<T, QT, HD, 8>(a, nset, st);
   }
 }
 // Attention of `nset` row sets (at most 32 rows each) in one launch.
