@@ -624,17 +624,20 @@ int prefill_impl(fm_ctx* c, int seq, const float* mem_dev, void* stage_area, siz
   hipLaunchKernelGGL((k_admit<T>), dim3(M32 / 16, (d / 32 + 3) / 4), dim3(256), 0, c->stream, mem_dev, Xt, D.M, d, c->st, D, seq, D.nbins);
   const long seq_off = (long)((size_t)seq * cache_seq_elems(c, D.M));
   if (c->pf_layers) {
-#define FM_PREFILL(HDV)                                                                                                            \
-  {                                                                                                                                \
-    if (D.M % 256 == 0 && d % 256 == 0)                                                                                            \
-      hipLaunchKernelGGL((k_prefill_kv<HDV, false>), dim3(c->pf_grid), dim3(256), PF_LDS_BYTES, c->stream, (const f16_t*)Xt,       \
-                         (const PrefillLayer*)c->pf_layers, seq_off, d / 32, d, D.M, c->pf_n);                                     \
-    else                                                                                                                           \
-      hipLaunchKernelGGL((k_prefill_kv<HDV, true>), dim3(c->pf_grid), dim3(256), PF_LDS_BYTES, c->stream, (const f16_t*)Xt,        \
-                         (const PrefillLayer*)c->pf_layers, seq_off, d / 32, d, D.M, c->pf_n);                                     \
+    // keys and values of one sequence past the last-level cache: as non-temporal stores they leave the memory tiles in L2.
+    // Eight sequences of d = 1024 with their first block (671 MB each) 7873 -> 7781 us, two of d = 1536 (302 MB) 2250 -> 2225; two of d = 256 (6 MB) 628 -> 635,
+    // where that block then finds nothing in the caches.
+    const bool past = 2.0 * c->pf_n * M32 * d * c->esz > 256e6;
+#define FM_PREFILL_GO(...) hipLaunchKernelGGL((k_prefill_kv<__VA_ARGS__>), dim3(c->pf_grid), dim3(256), PF_LDS_BYTES, c->stream, (const f16_t*)Xt, (const PrefillLayer*)c->pf_layers, seq_off, d / 32, d, D.M, c->pf_n)
+#define FM_PREFILL(HDV)                                       \
+  {                                                           \
+    if (D.M % 256 || d % 256) FM_PREFILL_GO(HDV, true, false); \
+    else if (past) FM_PREFILL_GO(HDV, false, true);           \
+    else FM_PREFILL_GO(HDV, false, false);                    \
   }
     if (D.hd == 64) FM_PREFILL(64) else if (D.hd == 96) FM_PREFILL(96) else FM_PREFILL(128)
 #undef FM_PREFILL
+#undef FM_PREFILL_GO
   } else {
     float* kv = (float*)(Xt + (size_t)M32 * d);
     for (int st = 0; st < 5; st++)
@@ -993,8 +996,10 @@ int build_buffers(fm_ctx* c) {
       c->pf_layers = (PrefillLayer*)raw;
       HIPCHK(c, hipMemcpy(c->pf_layers, tab.data(), tab.size() * sizeof(PrefillLayer), hipMemcpyHostToDevice));
       c->pf_n = (int)tab.size();
-#define FM_PREFILL_LDS(HDV, E) HIPCHK(c, hipFuncSetAttribute((const void*)k_prefill_kv<HDV, E>, hipFuncAttributeMaxDynamicSharedMemorySize, PF_LDS_BYTES))
-      FM_PREFILL_LDS(64, false); FM_PREFILL_LDS(64, true); FM_PREFILL_LDS(96, false); FM_PREFILL_LDS(96, true); FM_PREFILL_LDS(128, false); FM_PREFILL_LDS(128, true);
+#define FM_PREFILL_LDS(HDV, ...) HIPCHK(c, hipFuncSetAttribute((const void*)k_prefill_kv<HDV, __VA_ARGS__>, hipFuncAttributeMaxDynamicSharedMemorySize, PF_LDS_BYTES))
+#define FM_PREFILL_ALL(HDV) FM_PREFILL_LDS(HDV, false, false); FM_PREFILL_LDS(HDV, false, true); FM_PREFILL_LDS(HDV, true, false)
+      FM_PREFILL_ALL(64); FM_PREFILL_ALL(96); FM_PREFILL_ALL(128);
+#undef FM_PREFILL_ALL
 #undef FM_PREFILL_LDS
       hipDeviceProp_t prop;
       int dev = 0;

@@ -38,7 +38,8 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // EDGE = false: M and d are multiples of 256 (whole tiles; the clamps cost 4 %).  EDGE = true: any M; d a multiple of HD (the head width, a multiple of 32) and at least 128 (KT = d / 32 >= 4: the stages of one tile cover
 // the ring).  Tiles that reach past the last memory row or weight row are multiplied whole, their fragments clamped to the last
 // one that exists, and store only what exists (whole 32-key blocks: Xt holds zero rows up to a multiple of 32).
-template <int HD, bool EDGE>
+// PAST: results as non-temporal stores (prefill_impl says when).
+template <int HD, bool EDGE, bool PAST>
 __global__ __launch_bounds__(256, 1) void k_prefill_kv(const f16_t* __restrict__ Xt, const PrefillLayer* __restrict__ layers,
                                                        long seq_off, int KT, int d, int M, int n_layers) {
   extern __shared__ pf_u32x4 pf_smem[];
@@ -51,6 +52,10 @@ __global__ __launch_bounds__(256, 1) void k_prefill_kv(const f16_t* __restrict__
   const int lrow = ((lane & 31) >> 4) * 64 + (lane >> 5) * 16 + (lane & 15);
   const int xbase = wm * 512 + lrow, wbase = 1024 + wn * 512 + lrow;
   const int capb = (M + 31) >> 5;
+  auto put = [](auto* p, auto v) {
+    if constexpr (PAST) __builtin_nontemporal_store(v, p);
+    else *p = v;
+  };
 
   // Tile sequence.  Workgroup b runs on die b % 8, and each die has its own L2: a die takes gridDim/8 consecutive
   // tiles of the sequence per round, and the sequence is ordered in groups of XT memory tiles x all 2 nw weight tiles
@@ -201,7 +206,7 @@ __global__ __launch_bounds__(256, 1) void k_prefill_kv(const f16_t* __restrict__
               f16x8o o;
 #pragma unroll
               for (int i = 0; i < 4; i++) { o[i] = (f16_t)acc[x][w][q * 4 + i]; o[4 + i] = (f16_t)acc[x][w][(q + 2) * 4 + i]; }
-              if (on) *(__attribute__((address_space(1))) f16x8o*)(base + vblk_off<HD>(row0 + q * 8, col % HD)) = o;
+              if (on) put((__attribute__((address_space(1))) f16x8o*)(base + vblk_off<HD>(row0 + q * 8, col % HD)), o);
             }
           } else {
             // rows = dims, column = key.  Lanes l and l+32 hold dims 0-3 and 4-7 of the same 8-dim run of a key, which
@@ -218,7 +223,7 @@ __global__ __launch_bounds__(256, 1) void k_prefill_kv(const f16_t* __restrict__
               const auto s1 = __builtin_amdgcn_permlane32_swap(l2[1], h2[1], false, false);
               const pf_u32x4 o = {s0[0], s1[0], s0[1], s1[1]};
               const int e0 = a0 + wm * 128 + x * 32 + (2 * qp + (lane >> 5)) * 8;   // first dim of the run this lane stores
-              if (!EDGE || (e0 < d && (col >> 5) < capb)) *(__attribute__((address_space(1))) pf_u32x4*)(L.Km + seq_off + (long)(e0 / HD) * capb * (32 * HD) + kblk_off<HD>(col, e0 % HD)) = o;
+              if (!EDGE || (e0 < d && (col >> 5) < capb)) put((__attribute__((address_space(1))) pf_u32x4*)(L.Km + seq_off + (long)(e0 / HD) * capb * (32 * HD) + kblk_off<HD>(col, e0 % HD)), o);
             }
           }
 #pragma unroll

@@ -234,3 +234,23 @@ def test_memory_past_the_caches(d, heads, mem, batch, blocks, dc, m, n):
     rep, streams, fm = lockstep(cfg, cfg.faces, TOL[cfg.dtype], max_steps=3)
     print(rep, flush=True)
     assert rep.steps == 3 and fm.verify_path() == 0
+
+
+@pytest.mark.parametrize("d,heads,mem", [(768, 8, 16384), (1024, 8, 12288), (1024, 16, 12288)])
+def test_condition_kv_past_the_caches(d, heads, mem):
+    """Five blocks of 50 MB lie below the line from which the prefill stores its results past the caches, six above: the leading blocks are the same bits."""
+    from paper_2511_15618_amd import FlashMesh
+    from paper_2511_15618_amd.binding import config_struct
+    got = []
+    for blocks in (1, 2):
+        cfg = _cfg("past", d, heads, mem, "bf16", 1, 1, 2, 0, 0).replace(l_face=blocks)
+        print("case prefill past the caches", d, heads, 4 + blocks, flush=True)
+        assert ((4 + blocks) * 4 * mem * d > 256e6) == (blocks == 2)
+        fm = FlashMesh(config_struct(cfg))
+        fm.load_weights(si.pack_blob(cfg, si.make_weights(cfg, 0)))
+        fm.prefill_condition(0, torch.from_numpy(si.make_memory(cfg, 0)).cuda())
+        got.append([fm.debug_mem_kv(0, b) for b in range(3)])
+        del fm
+    for few, many in zip(*got):
+        for a, b in zip(few, many):
+            assert np.array_equal(a, b) and np.abs(a).max() > 0
