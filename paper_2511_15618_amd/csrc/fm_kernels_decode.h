@@ -762,13 +762,14 @@ inline size_t attn_ws_floats(int H, int S, int sets, int hd) {
 }
 
 // Whether keys and values are loaded as read once (non-temporal), so that they do not push the weights that the readers have fetched, and the rows between the
-// launches, out of L2: from 10 MB of the memory's keys and values a block (L2 has 4 MB a die).  Steps without / with the hint, us, by that size:
+// launches, out of L2: from 7 MB of the memory's keys and values a block (L2 has 4 MB a die).  Steps without / with the hint, us, by that size:
 //   134 MB (eight sequences of d = 1024) 3191 / 3086     101 MB (four, 1536) 4083 / 3964        75 MB (twelve, 768) 1232 / 1211
 //   34 MB (one, 2048, heads of 128) 2225 / 2216          17 MB (four, 512) 450 / 431            17 MB (four, 256) 905 / 852
-//   13 MB (twelve, 512) 916 / 909                        8 MB (one, 1024, heads of 128) 1197 / 1200   6 MB (one, 1536) 1303 / 1305
+//   13 MB (twelve, 512) 916 / 909                        8 MB (five, 512, 20 faces sampled) 56.3 / 53.2 ms, (one, 1024, heads of 128) 1197 / 1200
+//   6 MB (two, 768) 1052 / 1050, (one, 1536) 1303 / 1305   4 MB (two, 512) 879 / 881
 //   1 MB (two, 512) 780 / 783, (two, 256, token by token) 29.37 / 30.47 ms: there L2 keeps them from pass to pass
 // The same hint on the weights of k_dec_gemm, whose row tiles share them: 3964 -> 4086 for four sequences of d = 1536.
-inline bool attn_once(double block_kv_bytes) { return block_kv_bytes >= 10e6; }
+inline bool attn_once(double block_kv_bytes) { return block_kv_bytes >= 7e6; }
 
 template <typename T, int QT, int HD, int NW, bool ONCE>
 void dec_attn_go(const AttnArgs& a, int nset, hipStream_t st) {
