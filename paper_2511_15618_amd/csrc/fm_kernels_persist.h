@@ -371,7 +371,7 @@ __device__ __forceinline__ void pk_gemm_tile(PkA& a, SH& sh, int& par, const PkW
 #pragma unroll
   for (int k = 0; k < 4; k++) { p[k] = sh.red[par][k][wave][lane]; q[k] = sh.ssq[par][k][row]; }      // one trip to LDS
   result = p[0] + p[1] + p[2] + p[3];
-  if (norm) result *= rsqrt_f((q[0] + q[1] + q[2] + q[3]) / (float)K + eps);
+  if (norm) result *= 1.0f / sqrtf((q[0] + q[1] + q[2] + q[3]) / (float)K + eps);
 }
 
 // Epilogues: a thread has row g*4 + wave (wave, lane as above) and column n = nt*16 + lane%16 of the tile.
