@@ -461,7 +461,7 @@ template <typename T>
 void draft_query(fm_ctx* c, const float* const* src, const float* gain, const void* W, int M, int G, const RowMap& rm, int per_seq, const float2* cs, const int* flag) {
   const int d = c->D.d;
   DecGemm a{};
-  a.W = W; a.gsw = (long)d * d; a.M = M; a.N = d; a.KT = d / 32; a.run_flag = flag; a.eps = c->cfg.rms_eps; a.inv_k = 1.0f / d;
+  a.W = W; a.gsw = (long)d * d; a.M = M; a.N = d; a.KT = d / 32; a.run_flag = flag; a.eps = c->cfg.rms_eps;
   a.Y = c->dq; a.ldy = (long)G * d; a.gsy = d; a.cs = cs; a.ldc = G; a.hd = c->D.hd; a.H = c->D.H;
   a.src = src; a.sgain = gain;
   if (dec_gemm_rows<T, DE_ROPE>(a, G, c->stream)) return;
@@ -552,7 +552,7 @@ void draft_logits(fm_ctx* c, int n, const int* flag) {
   const Dims& D = c->D;
   DecGemm a{};
   a.W = c->lm; a.M = n; a.N = D.V; a.KT = D.d / 32; a.run_flag = flag; a.Y = c->dlogits; a.ldy = D.V;
-  a.src = c->lm_src; a.sgain = c->gf; a.ldc = 1; a.eps = c->cfg.rms_eps; a.inv_k = 1.0f / D.d;
+  a.src = c->lm_src; a.sgain = c->gf; a.ldc = 1; a.eps = c->cfg.rms_eps;
   if (dec_gemm_rows<T, DE_F32>(a, 1, c->stream)) return;
   hipLaunchKernelGGL((k_dec_rmsnorm<T>), dim3(n), dim3(256), 0, c->stream, c->lm_src, c->gf, 0, (T*)c->dX, RowMap{1, 0, 0, 0}, n, D.d, c->cfg.rms_eps, flag);
   a.A = c->dX;

@@ -40,7 +40,7 @@ __device__ __forceinline__ long map_off(const RowMap& rm, int s, int q, int n, i
 // ------------------------------------------------------------------------------------------
 enum { DE_RES = 0, DE_GELU, DE_ROW, DE_TILE, DE_F32, DE_QKV, DE_ROPE };
 // The norm in front of a GEMM: none; its input is x * gain already and comes with the row sums of squares; or the input is fp32 rows, scattered in
-// memory, and every workgroup forms x * gain and the sums of squares from them (the draft heads, whose rows no GEMM has left in operand order:
+// memory, and every workgroup norms them, in fp32 as k_dec_rmsnorm does (the draft heads, whose rows no GEMM has left in operand order:
 // a launch of 4 us less for each of their four norms).
 enum { DN_NONE = 0, DN_SSQ, DN_ROWS };
 
@@ -51,7 +51,7 @@ struct DecGemm {
   const float* ssq;              // DN_SSQ: [row tile][K/16][16] sums of squares of 16 columns each
   const float* const* src;       // DN_ROWS: fp32 rows by pointer, row m of a group at src[m * ldc + group]
   const float* sgain;            // and their gain, K values per group
-  float inv_k, eps;
+  float inv_k, eps;              // inv_k: DN_SSQ
   const int* run_flag;           // the launch is skipped when *run_flag == 0 (may be null)
   // outputs (which of them: the epilogue)
   void* Y; long ldy, gsy;        // row-major output: fp32 (DE_RES, DE_F32) or half (DE_ROW, DE_QKV q, DE_ROPE)
@@ -114,10 +114,10 @@ __global__ __launch_bounds__(NW * 64) void k_dec_gemm(DecGemm a) {
   };
   load_chunk(wc, ac, 0);
   float ss[MT];
+  f32x4 xv[NORM == DN_ROWS ? U : 1][2], gn[NORM == DN_ROWS ? U : 1][2];
   if constexpr (NORM == DN_ROWS) {
     static_assert(MT == 1 && !LOOP);
     const float* gp = a.sgain + (long)grp * KT * 32;
-    f32x4 xv[U][2], gn[U][2];
 #pragma unroll
     for (int u = 0; u < U; u++)
       if (u < nk) {
@@ -125,16 +125,6 @@ __global__ __launch_bounds__(NW * 64) void k_dec_gemm(DecGemm a) {
 #pragma unroll
         for (int h = 0; h < 2; h++) { gn[u][h] = *reinterpret_cast<const f32x4*>(gp + k + 4 * h); xv[u][h] = *reinterpret_cast<const f32x4*>(xrow + k + 4 * h); }
       }
-    ss[0] = 0.f;
-#pragma unroll
-    for (int u = 0; u < U; u++)
-      if (u < nk)
-#pragma unroll
-        for (int j = 0; j < 8; j++) {
-          const float x = xv[u][j >> 2][j & 3];
-          ss[0] += x * x;
-          ac[0][u][j] = (T)(x * gn[u][j >> 2][j & 3]);
-        }
   }
   // operands of the epilogue of this wave's first result tile
   const int tm = wave / NC, tc = wave % NC;
@@ -172,6 +162,28 @@ __global__ __launch_bounds__(NW * 64) void k_dec_gemm(DecGemm a) {
   }
   asm volatile("" ::: "memory");      // the loads above stay above the exit
   if (rf == 0) return;
+  if constexpr (NORM == DN_ROWS) {
+    // The row factor comes before the rounding to half: a row may be far from 1 (the residual stream grows, a head's linear layer has any scale), and
+    // x * gain alone would leave the range of half or lose bits to its subnormals.
+    float t = 0.f;
+#pragma unroll
+    for (int u = 0; u < U; u++)
+      if (u < nk)
+#pragma unroll
+        for (int j = 0; j < 8; j++) t += xv[u][j >> 2][j & 3] * xv[u][j >> 2][j & 3];
+    t = rows_sum(t);
+    if (g == 0) sq[wave * 16 + rl] = t;
+    __syncthreads();
+    float tot = sq[rl];
+#pragma unroll
+    for (int w = 1; w < NW; w++) tot += sq[w * 16 + rl];
+    const float inv = 1.0f / sqrtf(tot / (float)(KT * 32) + a.eps);
+#pragma unroll
+    for (int u = 0; u < U; u++)
+      if (u < nk)
+#pragma unroll
+        for (int j = 0; j < 8; j++) ac[0][u][j] = (T)(xv[u][j >> 2][j & 3] * inv * gn[u][j >> 2][j & 3]);
+  }
   auto mul_chunk = [&](V8 (&w)[NC][U], V8 (&x)[MT][U], int i0) {
 #pragma unroll
     for (int u = 0; u < U; u++)
@@ -198,7 +210,7 @@ __global__ __launch_bounds__(NW * 64) void k_dec_gemm(DecGemm a) {
   for (int mt = 0; mt < MT; mt++) {
 #pragma unroll
     for (int c = 0; c < NC; c++) red[(wave * NTILE + mt * NC + c) * 64 + lane] = acc[mt][c];
-    if constexpr (NORM != DN_NONE) {
+    if constexpr (NORM == DN_SSQ) {
       const float t = rows_sum(ss[mt]);
       if (g == 0) sq[(wave * MT + mt) * 16 + rl] = t;
     }
@@ -210,7 +222,7 @@ __global__ __launch_bounds__(NW * 64) void k_dec_gemm(DecGemm a) {
     f32x4 v = red[t * 64 + lane];
 #pragma unroll
     for (int w = 1; w < NW; w++) v += red[(w * NTILE + t) * 64 + lane];
-    if constexpr (NORM != DN_NONE) {
+    if constexpr (NORM == DN_SSQ) {
       float tot = sq[mt * 16 + rl];
 #pragma unroll
       for (int w = 1; w < NW; w++) tot += sq[(w * MT + mt) * 16 + rl];

@@ -213,6 +213,26 @@ def test_draft_rows_normed_by_their_gemms(d, heads, dtype, batch):
     assert rep.dist_rows > 0
 
 
+@pytest.mark.parametrize("d,heads,dtype,batch", [(128, 2, "bf16", 1), (1152, 18, "bf16", 1), (128, 2, "bf16", 17), (128, 2, "f32", 1)])
+def test_draft_rows_past_the_range_of_half(d, heads, dtype, batch):
+    """The linear layers of the SP heads 2^16 times as large: their outputs, which the HF blocks and the output head norm, have elements past 65504 while the
+    weights stay below it.  What a norm hands on is of order 1 whatever the row, so the bars on the draft distributions are the usual ones, for
+    norms inside the GEMMs (four and eight waves) and, at 17 sequences, outside."""
+    from parity_harness import lockstep, make_pair
+    cfg = _cfg("large_rows%d%s" % (d, dtype), d, heads, 2, dtype, batch, 2, 2, 9, 9)
+    print("case", cfg.name, batch, flush=True)
+
+    def enlarge(w):
+        for name in w:
+            if name.startswith("sp.") and name.endswith(".lin"):
+                w[name] = w[name] * np.float32(65536)
+                assert np.abs(w[name]).max() < 65504
+    pair = make_pair(cfg, edit_weights=enlarge)
+    rep, streams, fm = lockstep(cfg, cfg.faces, TOL[dtype], max_steps=6, pair=pair)
+    print(rep, flush=True)
+    assert rep.dist_rows > 0
+
+
 @pytest.mark.parametrize("mem,batch", [(512, 2), (513, 2), (500, 16), (500, 17)])
 def test_fp32_attention_waves(mem, batch):
     """Two heads over the memory: two waves a workgroup for 16 key blocks, four for one block more and where two would give more than 256 workgroups."""
