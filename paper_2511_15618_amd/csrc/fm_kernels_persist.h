@@ -942,7 +942,7 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs) {
         const bool on = er < Rl;
         if (goes_on && kq == 0) {
           bool ok = true;
-          if (down) {     // rows that do not exist wait for nothing: nobody waits for them either, and the next layer writes the same partial tiles
+          if (down) {
             unsigned pr[3];
             ok = pk_fetch<3>(pr, 3, on, tag, [&](int i) { return w2p + i * 256 + tid; }, a, stage);
             PK_MARK(4);
@@ -960,7 +960,9 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs) {
             if (ring && on) ring[(long)((P0 + row0 + er) & (lev == 0 ? 31 : lev == 1 ? 15 : 7)) * d + n] = down ? v : old;
           } else sh.bad = 1;
         } else if (goes_on) {
-          pk_stf(w2p + (kq - 1) * 256 + tid, c, tag);
+          // Only what quarter 0 waits for: the next layer writes the same partial tiles, maybe with more rows, and a store that nobody has waited for
+          // could land on top of one of its.
+          if (on) pk_stf(w2p + (kq - 1) * 256 + tid, c, tag);
         } else if (gi == 0) {      // to: queries, to_x, to_s: new keys and values; hold, ring: the caches
           const int hh = cp >> 6;
           const pk_x_t dst = part == 0 ? to + (long)row0 * (d >> 1) + hh * 32 : (part == 1 ? to_x : to_s) + ((long)hh * RS + row0) * 32;

@@ -1,4 +1,5 @@
-"""Level transitions of the single-launch verify kernel: what a transition publishes proves that every tile of the stack below was waited for."""
+"""What the single-launch verify kernel publishes into buffers that it uses again: a level transition proves that every tile of the stack below was waited
+for, and no element of a partial tile is published that nobody waits for."""
 import os
 import re
 import subprocess
@@ -59,3 +60,45 @@ def test_columns_that_are_not_published_are_told_from_it(tmp_path):
     """A unit that pools pairs and waits for every 256th column leaves tiles out in narrow models."""
     res = _run(tmp_path, "SkipCols", "SkipCols")
     assert res.returncode != 0 and "shorten, d = 128: nobody who publishes waits for tile" in res.stdout
+
+
+# The partial tiles of the FFN down projection are the same memory in every layer, and a later layer (behind an upsampling) may have more rows.  A store into
+# them is known to have landed only if quarter 0 waited for its element before it published what the next layers read.
+PARTIALS = r"""
+#include <cstdio>
+int main() {
+  int waited = 0;
+  for (int Rl = 1; Rl <= 16; Rl++)
+    for (int tid = 0; tid < 256; tid++) {
+      const int er = ((tid & 63) >> 4) * 4 + (tid >> 6);      // row of a thread in a tile
+      const bool on = er < Rl;
+      waited += WAIT;
+      if (on && !(PUT)) return printf("row %d of %d is not published\n", er, Rl), 1;
+      if ((PUT) && !(WAIT)) return printf("row %d of %d is published and not waited for\n", er, Rl), 1;
+    }
+  return waited != 16 * (16 * 17 / 2);
+}
+"""
+
+
+def _run_partials(tmp_path, put, wait):
+    src, exe = tmp_path / "partials.cc", tmp_path / "partials"
+    src.write_text(PARTIALS)
+    subprocess.run(["g++", "-std=c++17", "-O1", f"-DPUT={put}", f"-DWAIT={wait}", str(src), "-o", str(exe)], check=True)
+    return subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+
+
+def test_no_partial_is_published_that_nobody_waits_for(tmp_path):
+    """With the conditions that stand in front of the kernel's store and in its wait."""
+    src = open(os.path.join(CSRC, "fm_kernels_persist.h")).read()
+    assert "er = ((tid & 63) >> 4) * 4 + (tid >> 6)" in src and "const bool on = er < Rl;" in src
+    put = re.findall(r"(if \(([^()]*)\) )?pk_stf\(w2p \+ ", src)
+    wait = re.findall(r"pk_fetch<3>\(pr, 3, (\w+), tag, \[&\]\(int i\) \{ return w2p \+ i \* 256 \+ tid; \}", src)
+    assert len(put) == 1 and len(wait) == 1
+    res = _run_partials(tmp_path, put[0][1] or "true", wait[0])
+    assert res.returncode == 0, res.stdout
+
+
+def test_a_partial_of_a_row_that_does_not_exist_is_told(tmp_path):
+    res = _run_partials(tmp_path, "true", "on")
+    assert res.returncode != 0 and "row 4 of 1 is published and not waited for" in res.stdout
