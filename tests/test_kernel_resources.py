@@ -28,13 +28,17 @@ def _scratch(notes: str) -> dict:
             re.findall(r"\.name:\s+(_Z\w*k_\w+)\n(?:\s+\.(?!name)\w+:.*\n)*?\s+\.private_segment_fixed_size:\s+(\d+)", notes)}
 
 
-def _kernels(tmp_path) -> dict:
+def _notes(tmp_path) -> str:
     if not os.path.exists(binding.LIB_PATH):
         from paper_2511_15618_amd import build
         build.build()
     obj = tmp_path / "device.elf"
     obj.write_bytes(_device_code(open(binding.LIB_PATH, "rb").read()))
-    return _scratch(subprocess.run([READELF, "--notes", str(obj)], capture_output=True, text=True, check=True).stdout)
+    return subprocess.run([READELF, "--notes", str(obj)], capture_output=True, text=True, check=True).stdout
+
+
+def _kernels(tmp_path) -> dict:
+    return _scratch(_notes(tmp_path))
 
 
 @pytest.mark.skipif(not os.path.exists(READELF), reason="no llvm-readelf")
@@ -57,3 +61,15 @@ def test_every_instance_of_the_single_launch_kernel_has_a_lockstep_case(tmp_path
             sized = (2 if c.block_max > 16 else 1, c.d_model // 128 if c.ffn_mult == 4 else 0)
             run.add(sized if sized in built else (sized[0], 0))
     assert run == built
+
+
+@pytest.mark.skipif(not os.path.exists(READELF), reason="no llvm-readelf")
+def test_the_single_launch_kernel_stays_small(tmp_path):
+    """One loop over the stages with one instance of each unit's code: 27 to 40 KB an instance and 82 to 180 scalars that do not fit their registers.  With code of its
+    own for every stage of a block it was 56 to 88 KB and 173 to 308.  Two compute units hold 64 KB of instructions together."""
+    spills = {m[0]: int(m[1]) for m in re.findall(r"\.name:\s+(_Z\w*k_verify_persist\w+)\n(?:\s+\.(?!name)\w+:.*\n)*?\s+\.sgpr_spill_count:\s+(\d+)", _notes(tmp_path))}
+    symbols = subprocess.run([READELF, "--symbols", "--wide", str(tmp_path / "device.elf")], capture_output=True, text=True, check=True).stdout
+    code = {f[7]: int(f[2], 0) for f in (line.split() for line in symbols.splitlines()) if len(f) > 7 and f[3] == "FUNC" and f[7] in spills}
+    assert len(spills) == 10 and code.keys() == spills.keys()
+    assert {k: n for k, n in code.items() if n > 50000} == {}
+    assert {k: n for k, n in spills.items() if n > 190} == {}
