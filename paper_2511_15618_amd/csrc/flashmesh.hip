@@ -769,7 +769,7 @@ int build_params(fm_ctx* c) {
   return FM_OK;
 }
 
-// exchange buffers, layer table and argument block of the persistent verify kernel
+// exchange buffers, stage records and argument block of the persistent verify kernel
 int build_persist(fm_ctx* c) {
   const Dims& D = c->D;
   const size_t d = D.d;

@@ -55,7 +55,7 @@ struct DecGemm {
   const int* run_flag;           // the launch is skipped when *run_flag == 0 (may be null)
   // outputs (which of them: the epilogue)
   void* Y; long ldy, gsy;        // row-major output: fp32 (DE_RES, DE_F32) or half (DE_ROW, DE_QKV q, DE_ROPE)
-  const float* R; long ldr, gsr; // fp32 rows added (DE_RES; may be null, may be Y)
+  const float* R; long ldr;      // fp32 rows added (DE_RES; may be null, may be Y)
   const float* const* Rt;        // DE_F32: fp32 rows added, by pointer as src (may be null)
   void* X; long gsx;             // tiled half output of width N (DE_GELU, DE_TILE; DE_RES: x * gain, may be null)
   const float* gain;             // DE_RES: gain of the norm that follows

@@ -485,7 +485,7 @@ __device__ __forceinline__ void pk_attn_unit(PkA& a, SH& sh, int& par, u64 rec, 
   // of the wave's blocks holds rows written by this pass, those come in the same trip: the tiles that produce them are units of the same stage.
   // (In a trip of their own behind the queries the attention stage of 1500 keys takes 3.6 us instead of 2.6 at d = 512, 6.0 instead of 4.7 at 1024.)
   f16x8 qf0[QT], qf1[QT];
-  f16x8 nk[4], nv[4];       // fragments of that block, valid where fromK / fromV
+  f16x8 nk[4], nv[4];       // fragments of that block, in use where the key's position is one of this pass
   int keyK[2], keyV[8];     // positions of this lane's keys in it
   bool ok = true;
   {
@@ -746,12 +746,12 @@ __device__ __forceinline__ void pk_merge_unit(PkA& a, SH& sh, int nsplit, int R,
   } while (0)
 
 // One loop over the stages, one instance each of the GEMM, attention and merge code: what tells the stages apart are scalars and, per stage, a record of
-// pointers that the host has laid out and the workgroup holds in LDS.  (Every stage of a block with code of its own was 85 KB, past the 64 KB
-// of instructions that two compute units keep, and held the offsets of all of them in registers, a third of them spilled: a step of d = 512 took
-// 625 us, of d = 1024 1480, against 590 and 1463.  Pointers that are worked out from the arguments in front of each unit: 621 and 1645.)
+// pointers that the host has laid out and the workgroup holds in LDS.  (With code of its own for every stage of a block an instance was 56 to 88 KB, where two compute
+// units keep 64 KB of instructions, and held the offsets of all stages at once, 173 to 308 scalars of them outside of their registers, against 27 to 40 KB and 82 to 180: a
+// step of d = 512 took 625 us, of d = 1024 1483, against 595 and 1471.  Pointers that are worked out from the arguments in front of each unit: 31 and 182 us more.)
 // Only rows that exist take part.  A level without a row in this pass (a block that begins no vertex, no face) is left out with all its
 // stacks: the finer level then takes the coarse outputs of earlier passes from the ring.  (Eight faces token by token at d = 512, where the
-// vertex level has a row in every third pass and the face level in every ninth: 26.4 -> 11.3 ms.)
+// vertex level has a row in every third pass and the face level in every ninth: 26.4 -> 11.5 ms, with the loop.)
 template <int QT, int FWT>
 __global__ __launch_bounds__(256) void k_verify_persist(PkArgs) {
   PkA& a = *(PkA*)__builtin_amdgcn_kernarg_segment_ptr();
@@ -990,7 +990,10 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs) {
 }
 
 // The instance of a context: two row groups or one, and the width where the compiler knows it (offsets are constants and no fragment is
-// conditional: a step of d = 1024 1463 us, 1573 with the general instance, which takes the other widths and hidden widths).
+// conditional); other widths (128, 384, 640, 896) and hidden widths take the general one.  Steps with the instance / with the general one, us:
+//   blocks of 9   d = 256 527 / 575   512 573 / 619   768 755 / 794   1024 1439 / 1458
+//   blocks of 18          604 / 653       695 / 734       934 / 977        1788 / 1812
+// (20, 20, 24 and 40 blocks, memory 2048 and at d = 1024 4096, window 4500 and 9000)
 typedef void (*pk_kernel_t)(PkArgs);
 inline pk_kernel_t pk_kernel(const PkArgs& a) {
   const int d = a.ff == 4 * a.D.d ? a.D.d : 0;
