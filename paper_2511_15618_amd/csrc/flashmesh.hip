@@ -354,7 +354,6 @@ void run_block(fm_ctx* c, const Layer& L, int level, const float* next_gain, flo
   const double cross_bytes = sizeof(T) * (2.0 * D.S * D.M * d + 4.0 * d * d + 2.0 * d * c->ff);
   auto attn = [&](const int* limit, void* K, void* V, int kcap, int window, bool cross) {
     AttnArgs t{};
-    t.once = attn_once(2.0 * D.S * D.M * D.d * c->esz);
     int n = 0;
     auto ahead = [&](const void* W, int N, int Kw) { if (W) t.next[n++] = WeightRange{W, Kw * 16 * (int)sizeof(T), N / 16}; };
     if (cross) {
@@ -485,7 +484,6 @@ void run_sp(fm_ctx* c, const int* flag) {
   const Layer* last[3] = {&c->stacks[3].back(), &c->stacks[2].back(), &c->stacks[4].back()};
   auto attn = [&](const int* limit, bool cross) {
     AttnArgs t{};
-    t.once = attn_once(2.0 * D.S * D.M * D.d * c->esz);
     t.S = S; t.H = D.H; t.ws = c->attn_ws; t.arrived = c->attn_arrived; t.run_flag = flag;
     int n = 0, q0 = 0;
     for (int z = 0; z < 3; z++) {
@@ -529,7 +527,6 @@ void run_hf(fm_ctx* c, int set, const HfLevel& hf, int mult, const Layer& last, 
   const RowMap rm{G, mult, 0, tiles};
   draft_query<T>(c, c->dr.src[set], hf.g, hf.wq, Mg, G, rm, per_seq, c->dr.cs[set], flag);
   AttnArgs t{};
-  t.once = attn_once(2.0 * D.S * D.M * D.d * c->esz);
   t.S = D.S; t.H = D.H; t.ws = c->attn_ws; t.arrived = c->attn_arrived; t.run_flag = flag;
   const int cap = level_cap(c, level);
   int n = 0;

@@ -354,7 +354,6 @@ struct AttnArgs {
   unsigned* arrived;         // [set][sequence][head] splits that have published their part, zero between launches
   float* ws;                 // [set][sequence][head][ns_max][QT*16*HD unnormalised O | QT*16 running max (log2 units) | QT*16 sums]
   const int* run_flag;
-  bool once;                 // attn_once
   int nset, ahead;           // planes of the grid (blockIdx.z) that attend: nset * S; `ahead` more read weights ahead
   WeightRange next[4];
 };
@@ -773,15 +772,26 @@ inline size_t attn_ws_floats(int H, int S, int sets, int hd) {
   return (size_t)(256 + pairs) * (32 * hd + 64);
 }
 
-// Whether keys and values are loaded as read once (non-temporal), so that they do not push the weights that the readers have fetched, and the rows between the
-// launches, out of L2: from 7 MB of the memory's keys and values a block (L2 has 4 MB a die).  Steps without / with the hint, us, by that size:
+// Whether a launch loads its keys and values as read once (non-temporal), so that they do not push the weights that the readers have fetched, and the rows between
+// the launches, out of L2: where its own caches hold 5 MB or more (L2 has 4 MB a die), as they are allocated: how much of them is in use only the device
+// knows.  Two sets over one cache count once.  Steps without / with the hint, us.  By the memory's keys and values of a block:
 //   134 MB (eight sequences of d = 1024) 3191 / 3086     101 MB (four, 1536) 4083 / 3964        75 MB (twelve, 768) 1232 / 1211
 //   34 MB (one, 2048, heads of 128) 2225 / 2216          17 MB (four, 512) 450 / 431            17 MB (four, 256) 905 / 852
 //   13 MB (twelve, 512) 916 / 909                        8 MB (five, 512, 20 faces sampled) 56.3 / 53.2 ms, (one, 1024, heads of 128) 1197 / 1200
 //   6 MB (two, 768) 1052 / 1050, (one, 1536) 1303 / 1305   4 MB (two, 512) 879 / 881
 //   1 MB (two, 512) 780 / 783, (two, 256, token by token) 29.37 / 30.47 ms: there L2 keeps them from pass to pass
+// By the self-attention's at the coordinate level, memory of 0.5 to 4 MB a block: 147 MB (eight, 1024) 1372 / 1355     18 MB (two, 512) 835 / 787
+//   15 MB (four, 512) 747 / 743     74 MB, the most 0.8 in use (two, 512, 20 faces with room for 2000) 18.55 / 17.17 ms
+//   37 MB, the most 0.2 in use (two, 256, 8 faces token by token with room for 2000) 15.70 / 15.81 ms
+//   and with 25 to 67 MB of memory a block, hinted or not:  4 MB (eight, 512) 971 / 974     1 MB (three, 256) 313 / 316
 // The same hint on the weights of k_dec_gemm, whose row tiles share them: 3964 -> 4086 for four sequences of d = 1536.
-inline bool attn_once(double block_kv_bytes) { return block_kv_bytes >= 7e6; }
+template <class SET>
+bool attn_once(const SET* set, int nset, int S, int H, int hd) {
+  double bytes = 0;
+  for (int z = 0; z < nset; z++)
+    if (z == 0 || set[z].Kc != set[z - 1].Kc) bytes += 2.0 * 2.0 * S * set[z].capb * 32 * H * hd;
+  return bytes >= 5e6;
+}
 
 template <typename T, int QT, int HD, int NW, bool ONCE>
 void dec_attn_go(const AttnArgs& a, int nset, hipStream_t st) {
@@ -816,7 +826,7 @@ void dec_attn_waves(AttnArgs& a, int nset, hipStream_t st) {
     if (blocks <= 16 && (long)a.H * a.S * nset * ((blocks + 1) / 2) <= 256) dec_attn_sized<T, QT, HD, 2>(a, nset, st);
     else dec_attn_sized<T, QT, HD, 4>(a, nset, st);
   } else {
-    if (a.once) dec_attn_sized<T, QT, HD, 8, true>(a, nset, st);
+    if (attn_once(a.set, nset, a.S, a.H, HD)) dec_attn_sized<T, QT, HD, 8, true>(a, nset, st);
     else dec_attn_sized<T, QT, HD, 8>(a, nset, st);
   }
 }

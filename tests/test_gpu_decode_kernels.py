@@ -256,6 +256,19 @@ def test_memory_past_the_caches(d, heads, mem, batch, blocks, dc, m, n):
     assert rep.steps == 3 and fm.verify_path() == 0
 
 
+@pytest.mark.parametrize("faces,m,n", [(53, 9, 9), (54, 9, 9), (54, 15, 18)])
+def test_caches_on_both_sides_of_the_line(faces, m, n):
+    """13 sequences with caches of 4.8 and 5.1 MB at the coordinate level, a third of it at the vertex level, 0.6 MB of memory a block: coordinate blocks on
+    both sides of the line of 5 MB, SP heads (all levels) past it, vertex blocks and memory below; one and two query tiles."""
+    from parity_harness import lockstep
+    cfg = _cfg("line%d_%d" % (faces, n), 192, 3, 40, "bf16", 13, faces, 2, m, n)
+    assert (4 * 13 * -(-cfg.max_tokens // 32) * 32 * 192 >= 5e6) == (faces == 54)
+    print("case", cfg.name, flush=True)
+    rep, streams, fm = lockstep(cfg, cfg.faces, TOL[cfg.dtype], max_steps=4)
+    print(rep, flush=True)
+    assert rep.steps == 4 and fm.verify_path() == 0
+
+
 @pytest.mark.parametrize("d,heads,mem", [(768, 8, 16384), (1024, 8, 12288), (1024, 16, 12288)])
 def test_condition_kv_past_the_caches(d, heads, mem):
     """Five blocks of 50 MB lie below the line from which the prefill stores its results past the caches, six above: the leading blocks are the same bits."""
