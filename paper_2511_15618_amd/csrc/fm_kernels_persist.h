@@ -990,13 +990,20 @@ __global__ __launch_bounds__(256) void k_verify_persist(PkArgs) {
 }
 
 // The instance of a context: two row groups or one, and the width where the compiler knows it (offsets are constants and no fragment is
-// conditional); other widths (128, 384, 640, 896) and hidden widths take the general one.  Steps with the instance / with the general one, us:
-//   blocks of 9   d = 256 527 / 575   512 573 / 619   768 755 / 794   1024 1439 / 1458
-//   blocks of 18          604 / 653       695 / 734       934 / 977        1788 / 1812
-// (20, 20, 24 and 40 blocks, memory 2048 and at d = 1024 4096, window 4500 and 9000)
+// conditional); 640 and 896 and hidden widths other than 4 d take the general one.  Steps with the instance / with the general one, us:
+//   blocks of 9   d = 128 500 / 549   256 527 / 575   384 559 / 592   512 573 / 619   768 755 / 794   1024 1439 / 1458
+//   blocks of 18          567 / 619       604 / 653       656 / 692       695 / 734       934 / 977        1788 / 1812
+// (20, at 768 24 and at 1024 40 blocks, memory 2048 and at 1024 4096, window 4500 and 9000).  The narrow widths are where the general one, which multiplies
+// eight fragments a wave whatever the width, loses most: with stages of their own code and fragments behind branches it took 522 and 575 us for the passes of
+// 18 tokens at 128 and 384, with the loop 535 and 579, the instances 484 and 539.  (Branches in the loop: 1459 -> 1526 at 1024.)
 typedef void (*pk_kernel_t)(PkArgs);
 inline pk_kernel_t pk_kernel(const PkArgs& a) {
   const int d = a.ff == 4 * a.D.d ? a.D.d : 0;
-  if (a.RS == 32) return d == 256 ? k_verify_persist<2, 2> : d == 512 ? k_verify_persist<2, 4> : d == 768 ? k_verify_persist<2, 6> : d == 1024 ? k_verify_persist<2, 8> : k_verify_persist<2, 0>;
-  return d == 256 ? k_verify_persist<1, 2> : d == 512 ? k_verify_persist<1, 4> : d == 768 ? k_verify_persist<1, 6> : d == 1024 ? k_verify_persist<1, 8> : k_verify_persist<1, 0>;
+  const bool two = a.RS == 32;
+  switch (d) {
+#define FM_PK(FWT) case FWT * 128: return two ? k_verify_persist<2, FWT> : k_verify_persist<1, FWT>
+    FM_PK(1); FM_PK(2); FM_PK(3); FM_PK(4); FM_PK(6); FM_PK(8);
+#undef FM_PK
+  }
+  return two ? k_verify_persist<2, 0> : k_verify_persist<1, 0>;
 }

@@ -45,6 +45,9 @@ CASES = [
     _cfg("one_launch_w512_two_tiles", 512, 8, 70, "bf16", 1, 4, 2, 15, 18),
     _cfg("one_launch_w1024", 1024, 16, 33, "bf16", 1, 3, 2, 9, 9),
     _cfg("one_launch_w768_two_tiles", 768, 12, 33, "bf16", 1, 4, 2, 9, 27),
+    _cfg("one_launch_w128_two_tiles", 128, 2, 70, "bf16", 1, 4, 2, 15, 18),
+    _cfg("one_launch_w384", 384, 6, 33, "bf16", 1, 3, 2, 9, 9),
+    _cfg("one_launch_w384_two_tiles", 384, 6, 70, "bf16", 1, 4, 2, 9, 27),
     # a hidden width past what the single-launch kernel holds: the per-operator path
     _cfg("past_the_hidden", 256, 4, 40, "bf16", 1, 4, 2, 9, 9, ffn_mult=18),
     # more than 32 draft rows per sequence: two row sets of one attention launch
