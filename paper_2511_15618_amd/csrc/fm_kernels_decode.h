@@ -750,7 +750,8 @@ void dec_gemm(const DecGemm& a, int groups, hipStream_t st) {
 // GEMM whose workgroups norm their rows themselves (DN_ROWS); false: not for this size.  A lane holds rows and gains as fp32 beside the weights, up to
 // eight fragments of each (four waves up to K = 1024, eight up to 2048; fp32 up to 1024).  For one row tile and few workgroups: each of them
 // reads twice the bytes of rows in operand order, and gains.  Steps with the norm inside / in a launch of its own, us: d = 512 one sequence
-// 578 / 584, a mesh of d = 256 fp32 10 950 / 10 985; for all sizes d = 2048 2270 / 2210, eight sequences of d = 1024 3196 / 3184.
+// 575 / 579, d = 768 three 1182 / 1188, d = 1024 one 1436 / 1435, a mesh of d = 256 fp32 10 480 / 10 580; for all sizes (with the factor on the result, a barrier less)
+// d = 2048 2270 / 2210, eight sequences of d = 1024 3196 / 3184.
 template <typename T, int EPI>
 bool dec_gemm_rows(const DecGemm& a, int groups, hipStream_t st) {
   if (a.M > 16 || (long)((a.N + 15) / 16) * groups > 400 || a.KT > (std::is_same<T, float>::value ? 32 : 64)) return false;
